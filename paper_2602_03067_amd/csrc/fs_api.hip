@@ -145,10 +145,11 @@ double stage_eps(double e0, double e1, int stages, int s)
 
 // Lay the prepared problem out in the workspace; returns bytes needed.  With base == nullptr
 // only the size is computed.
-size_t layout(const Ctx *c, const fs_problem *p, Prepared *P, char *base, size_t extra)
+size_t layout_with(const Ctx *c, const fs_problem *p, Prepared *P, char *base, size_t extra, int fx_ks)
 {
     Arena A;
     P->path = choose_path(p);
+    P->fx_ks = fx_ks;
     P->d = p->d;
     auto side = [&](Side &S, int64_t cnt, const float *w) {
         S.cnt = cnt;
@@ -184,6 +185,10 @@ size_t layout(const Ctx *c, const fs_problem *p, Prepared *P, char *base, size_t
             S.pts_d = base ? (double *)(base + o) : nullptr;
             o = A.take((size_t)S.cnt_pad * 8);
             S.bias_d = base ? (double *)(base + o) : nullptr;
+            o = A.take((size_t)S.cnt_pad * P->fx_ks * 128);
+            S.dig = (base && P->fx_ks) ? (unsigned char *)(base + o) : nullptr;
+            o = A.take(P->fx_ks ? (size_t)S.cnt_pad * 16 : 0);
+            S.brec = (base && P->fx_ks) ? (int *)(base + o) : nullptr;
             break;
         case Path::BF16:
             P->kp = (int)round_up(p->d, 32);
@@ -219,6 +224,18 @@ size_t layout(const Ctx *c, const fs_problem *p, Prepared *P, char *base, size_t
     o = A.take(extra);
     (void)o;
     return A.off;
+}
+
+size_t layout(const Ctx *c, const fs_problem *p, Prepared *P, char *base, size_t extra)
+{
+    // Below this much work a float64 pass takes under 20 us (n = m = 2800 at d = 64), which the second launch of a pass and
+    // the digits of the prologue would eat up: n = 3000, m = 2500, d = 64 measured 28 us a half-step in float64, 17 in
+    // fixed point, n = m = 1000 8 and 13.
+    const bool worth = (double)p->n * (double)p->m * (double)p->d >= 4.0e8 || c->dbg_fx_any_size;
+    const int ks = choose_path(p) == Path::F64 && worth ? fx_ksteps(p->d) : 0;
+    // digit images are left out where only the problem without them fits the static scratch array
+    if (ks && c->ws_static && layout_with(c, p, P, nullptr, extra, ks) > c->ws_bytes) return layout_with(c, p, P, base, extra, 0);
+    return layout_with(c, p, P, base, extra, ks);
 }
 
 fs_status ensure_ws(Ctx *c, size_t need)
@@ -279,7 +296,7 @@ fs_status prepare(Ctx *c, const fs_problem *p, Prepared *P, size_t extra, char *
 }
 
 // merge the splits of the pass that just ran over `res` (see launch_finalize)
-fs_status finalize(Ctx *c, const Prepared *P, Side *res, int splits, double eps, double eps_next_bias, float *user_out,
+fs_status finalize(Ctx *c, const Prepared *P, Side *res, Splits splits, double eps, double eps_next_bias, float *user_out,
                    double *abs_dev_sum, double mix = 1.0, double *save_old = nullptr, GaugeMode gauge = GaugeMode::None,
                    int64_t gauge_prev_cnt = 0, double gauge_prev_eps = 0.0)
 {
@@ -288,7 +305,7 @@ fs_status finalize(Ctx *c, const Prepared *P, Side *res, int splits, double eps,
                            gauge_prev_cnt, gauge_prev_eps);
 }
 
-fs_status run_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, int *splits)
+fs_status run_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, Splits *splits)
 {
     switch (P->path) {
     case Path::LowD: return lowd_lse(c, P, res, str, eps, splits);
@@ -310,7 +327,7 @@ fs_status apply_begin(Ctx *c, const fs_problem *prob, float eps, const float *f,
     size_t extra = 0;
     switch (choose_path(prob)) {
     case Path::LowD: extra = lowd_apply_ws(c, n_res, n_str, prob->d, p); break;
-    case Path::F64: extra = f64_apply_ws(c, n_res, n_str, prob->d, p); break;
+    case Path::F64: extra = f64_apply_ws(c, n_res, n_str, prob->d, p); break;   // (covers both kernels of a pass)
     case Path::BF16: extra = bf16_apply_ws(c, n_res, n_str); break;
     }
     extra = (extra + 255) & ~size_t(255);
@@ -532,7 +549,7 @@ fs_status fs_update_f(fs_ctx *ctx, const fs_problem *prob, float eps, const floa
     Prepared P;
     if ((st = prepare(c, prob, &P, 0, nullptr)) != FS_OK) return st;
     if ((st = launch_bias_from_user(c, &P, &P.Y, g, eps)) != FS_OK) return st;
-    int splits = 1;
+    Splits splits;
     if ((st = run_lse(c, &P, &P.X, &P.Y, eps, &splits)) != FS_OK) return st;
     return finalize(c, &P, &P.X, splits, eps, 0.0, f_out, nullptr);
 }
@@ -551,7 +568,7 @@ fs_status fs_update_g(fs_ctx *ctx, const fs_problem *prob, float eps, const floa
     Prepared P;
     if ((st = prepare(c, prob, &P, 0, nullptr)) != FS_OK) return st;
     if ((st = launch_bias_from_user(c, &P, &P.X, f, eps)) != FS_OK) return st;
-    int splits = 1;
+    Splits splits;
     if ((st = run_lse(c, &P, &P.Y, &P.X, eps, &splits)) != FS_OK) return st;
     return finalize(c, &P, &P.Y, splits, eps, 0.0, g_out, nullptr);
 }
@@ -627,7 +644,7 @@ static fs_status solve_impl(Ctx *c, const fs_problem *prob, float eps_start, flo
             bool last = (s == n_stages - 1) && (t == iters_per_stage - 1);
             double eps_next = eps;
             if (t == iters_per_stage - 1 && !last) eps_next = stage_eps(eps_start, eps_end, n_stages, s + 1);
-            int splits = 1;
+            Splits splits;
             // Alg. 1: f from g
             if ((st = run_lse(c, &P, &P.X, &P.Y, eps, &splits)) != FS_OK) return st;
             if ((st = finalize(c, &P, &P.X, splits, eps, eps, nullptr, nullptr, 1.0, nullptr,
@@ -751,7 +768,7 @@ fs_status fs_solve_tol(fs_ctx *ctx, const fs_problem *prob, float eps_in, int32_
     int t = 0;
     double err = -1.0;
     while (true) {
-        int splits = 1;
+        Splits splits;
         if (!pending) {   // Alg. 1: f from g
             if ((st = run_lse(c, &P, &P.X, &P.Y, eps, &splits)) != FS_OK) return st;
             if ((st = finalize(c, &P, &P.X, splits, eps, eps, nullptr, nullptr, 1.0, nullptr,
@@ -815,7 +832,7 @@ fs_status fs_solve_symmetric(fs_ctx *ctx, const fs_problem *prob, float eps_in, 
     if ((st = launch_fill_f64(c, P.scalars + 8, 0.0, 2)) != FS_OK) return st;
     for (int t = 0; t < iters; ++t) {
         const bool last = t == iters - 1;
-        int splits_f = 1, splits_g = 1;
+        Splits splits_f, splits_g;
         const double eps_bias = last ? 0.0 : eps;
         if (P.path == Path::LowD) {
             // both passes in one launch and both merges in another, when the half-steps run on the
@@ -876,7 +893,7 @@ fs_status fs_marginal_err(fs_ctx *ctx, const fs_problem *prob, float eps, const 
     if ((st = launch_bias_from_user(c, &P, &P.Y, g, eps, false, true)) != FS_OK) return st;
     // (the two error sums only: slots 5..7 belong to the prologue and, with kept derived copies, to later calls)
     if ((st = launch_fill_f64(c, P.scalars, 0.0, 2)) != FS_OK) return st;
-    int splits = 1;
+    Splits splits;
     if (err_row_l1) {
         if ((st = run_lse(c, &P, &P.X, &P.Y, eps, &splits)) != FS_OK) return st;
         if ((st = finalize(c, &P, &P.X, splits, eps, 0.0, nullptr, P.scalars + 0)) != FS_OK) return st;
@@ -908,7 +925,7 @@ fs_status fs_ot_value(fs_ctx *ctx, const fs_problem *prob, float eps, const floa
     if ((st = prepare(c, prob, &P, scratch_bytes, &scratch)) != FS_OK) return st;
     if ((st = launch_bias_from_user(c, &P, &P.X, f, eps, true, false)) != FS_OK) return st;
     if ((st = launch_bias_from_user(c, &P, &P.Y, g, eps, false, true)) != FS_OK) return st;
-    int splits = 1;
+    Splits splits;
     if ((st = run_lse(c, &P, &P.X, &P.Y, eps, &splits)) != FS_OK) return st;
     const double *nrm = (P.path == Path::LowD && !lowd_precise(&P, eps)) ? P.X.norm_f : P.X.norm;
     if ((st = launch_value_terms(c, &P, &P.X, nrm, &P.Y, splits, eps, reinterpret_cast<double *>(scratch), P.scalars)) !=
@@ -1162,7 +1179,10 @@ fs_status fs_debug_set(fs_ctx *ctx, const char *key, int64_t value)
         c->dbg_lowd_precise_valu = (int)value;
     else if (k == "lowd_precise_any_bias" && (value == 0 || value == 1))
         c->dbg_lowd_any_bias = (int)value;
-    else
+    else if (k == "fx_any_size" && (value == 0 || value == 1)) {
+        c->dbg_fx_any_size = (int)value;
+        c->kept_valid = false;   // (the layout depends on it)
+    } else
         return fail(c, FS_ERR_INVALID_ARG, "unknown switch or value out of range: %s = %lld", key, (long long)value);
     return FS_OK;
 }

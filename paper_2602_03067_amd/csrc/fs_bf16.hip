@@ -677,7 +677,7 @@ static fs_status lse_pass_args(Ctx *c, const Prepared *P, const Side *res, const
     return FS_OK;
 }
 
-fs_status bf16_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, int *splits_out)
+fs_status bf16_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, Splits *splits_out)
 {
     BfArgs a;
     int blocks = 0;
@@ -699,7 +699,7 @@ fs_status bf16_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, 
 
 // The f-pass (records to partial_x) and the g-pass (records to partial_y) of one iteration of the averaged
 // schedule (Eq. 4-5) in ONE launch.
-fs_status bf16_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, void *partial_y, int *splits_x, int *splits_y)
+fs_status bf16_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, void *partial_y, Splits *splits_x, Splits *splits_y)
 {
     BfArgs ax, ay;
     int bx = 0, by = 0;

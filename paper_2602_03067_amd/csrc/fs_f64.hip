@@ -1,5 +1,7 @@
 // fp32-accuracy path for d > 16: the score contraction <x_i, y_j> runs on the fp64 matrix
-// cores (v_mfma_f64_16x16x4_f64).
+// cores (v_mfma_f64_16x16x4_f64).  For 16 < d <= 128 and all but small problems the fixed-point kernels of
+// fs_fx.hip take its place (three times faster) wherever the points' scale allows; these kernels are then launched as
+// well and leave at once.
 //
 // Why fp64: with d = 64 and eps = 0.1 a score (2<x,y> - |y|^2 + g)/eps reaches ~2e3, where an
 // fp32 ulp is 1.2e-4 -- the whole error budget of 1e-4.  MI355X has 78.6 TFLOP/s of fp64 MFMA,
@@ -62,6 +64,7 @@ struct PassArgs {
     const float *hadA;       // [n_res][lda]
     int64_t lda, n_res;
     int d;                   // real number of coordinates (columns of hadA)
+    FxGate gate;             // r2 != nullptr: the fixed-point kernel of the same pass runs where the gate is on
 };
 
 // (never more than 256 registers per lane: with at most 256 the compiler keeps the MFMA
@@ -491,6 +494,7 @@ __device__ __forceinline__ void pass_f64_body(const PassArgs &a, const int bx, c
 template <bool APPLY, bool HAD = false, int NCT = 4, int JT = 4, int NW = 4, bool LAZY = APPLY>
 __global__ __launch_bounds__(64 * NW, (APPLY && !HAD && NCT <= 4) ? 3 : 2) void k_pass_f64(PassArgs a)
 {
+    if (a.gate.r2 && a.gate.on()) return;   // (uniform over the grid)
     pass_f64_body<APPLY, HAD, NCT, JT, NW, LAZY>(a, blockIdx.x, blockIdx.y);
 }
 
@@ -500,6 +504,7 @@ __global__ __launch_bounds__(64 * NW, (APPLY && !HAD && NCT <= 4) ? 3 : 2) void 
 template <int JT, int NW, bool LAZY>
 __global__ __launch_bounds__(64 * NW, 2) void k_pass_f64_pair(PassArgs a0, PassArgs a1, int rb0, int splits0, int splits1)
 {
+    if (a0.gate.r2 && a0.gate.on()) return;
     const bool second = (int)blockIdx.x >= rb0;   // uniform over the workgroup
     if ((int)blockIdx.y >= (second ? splits1 : splits0)) return;
     pass_f64_body<false, false, 4, JT, NW, LAZY>(second ? a1 : a0, (int)blockIdx.x - (second ? rb0 : 0), blockIdx.y);
@@ -565,6 +570,7 @@ static fs_status lse_pass_args(Ctx *c, const Prepared *P, const Side *res, const
     a.kp = P->kp;
     a.kc = (int)round_up(P->d, 8);
     a.cscale = 2.0 * kLog2e / eps;
+    a.gate = fx_gate(P, eps);
     a.n_tiles = (int)ceil_div(str->cnt, BC);
     a.tiles_per_split = (int)(s.cols_per_split / BC);
     a.partial = (double2 *)partial;
@@ -577,13 +583,16 @@ static fs_status lse_pass_args(Ctx *c, const Prepared *P, const Side *res, const
     return FS_OK;
 }
 
-fs_status f64_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, int *splits_out, int prof_kind)
+// (with digit images: the fixed-point kernel and the float64 one, one of which leaves at once; see FxGate)
+fs_status f64_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, Splits *splits_out, int prof_kind)
 {
     PassArgs a;
     PassShape s;
     fs_status st = lse_pass_args(c, P, res, str, eps, P->partial, &a, &s);
     if (st != FS_OK) return st;
     prof_begin(c, (double)res->cnt * (double)str->cnt, prof_kind);
+    int fx_splits = 0;
+    if (P->fx_ks && (st = fx_lse(c, P, res, str, eps, &fx_splits)) != FS_OK) return st;
     const dim3 grid((unsigned)s.row_blocks, (unsigned)s.splits);
     if (P->path == Path::LowD)
         hipLaunchKernelGGL((k_pass_f64<false, false, 4, kLseJT, kLseNW, true>), grid, dim3(64 * kLseNW), 0, c->stream, a);
@@ -591,13 +600,13 @@ fs_status f64_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, d
         hipLaunchKernelGGL((k_pass_f64<false, false, 4, kLseJT, kLseNW, false>), grid, dim3(64 * kLseNW), 0, c->stream, a);
     prof_end(c);
     FS_HIP(c, hipGetLastError());
-    *splits_out = s.splits;
+    *splits_out = P->fx_ks ? Splits(fx_splits, s.splits) : Splits(s.splits);
     return FS_OK;
 }
 
 // The f-pass (records to partial_x) and the g-pass (records to partial_y) of one iteration of the averaged
 // schedule (Eq. 4-5) in ONE launch.
-fs_status f64_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, void *partial_y, int *splits_x, int *splits_y)
+fs_status f64_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, void *partial_y, Splits *splits_x, Splits *splits_y)
 {
     PassArgs ax, ay;
     PassShape sx, sy;
@@ -606,6 +615,8 @@ fs_status f64_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, v
     if ((st = lse_pass_args(c, P, &P->Y, &P->X, eps, partial_y, &ay, &sy)) != FS_OK) return st;
     const dim3 grid((unsigned)(sx.row_blocks + sy.row_blocks), (unsigned)(sx.splits > sy.splits ? sx.splits : sy.splits));
     prof_begin(c, 2.0 * (double)P->X.cnt * (double)P->Y.cnt, P->path == Path::LowD ? 1 : 0);
+    int fx_x = 0, fx_y = 0;
+    if (P->fx_ks && (st = fx_lse_pair(c, P, eps, partial_x, partial_y, &fx_x, &fx_y)) != FS_OK) return st;
     if (P->path == Path::LowD)
         hipLaunchKernelGGL((k_pass_f64_pair<kLseJT, kLseNW, true>), grid, dim3(64 * kLseNW), 0, c->stream, ax, ay, sx.row_blocks,
                            sx.splits, sy.splits);
@@ -614,8 +625,8 @@ fs_status f64_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, v
                            sx.splits, sy.splits);
     prof_end(c);
     FS_HIP(c, hipGetLastError());
-    *splits_x = sx.splits;
-    *splits_y = sy.splits;
+    *splits_x = P->fx_ks ? Splits(fx_x, sx.splits) : Splits(sx.splits);
+    *splits_y = P->fx_ks ? Splits(fx_y, sy.splits) : Splits(sy.splits);
     return FS_OK;
 }
 
@@ -623,11 +634,12 @@ constexpr int kWidePCH = 128;   // value columns of a pass of the wide form
 
 size_t f64_apply_ws(const Ctx *c, int64_t n_res, int64_t n_str, int64_t d, int64_t p)
 {
-    (void)p;
     // the larger of the shapes of the plain and of the Hadamard-weighted / wide application, at the wide row length
     const PassShape s1 = shape_f64(c, n_res, n_str, 16 * kApplyJT, 16 * kApplyNW, d, kApplyWgPerCu);
     const PassShape s2 = shape_f64(c, n_res, n_str, 16 * kApplyJT, 16 * kApplyNW, d, 2);
-    return (size_t)(s1.splits > s2.splits ? s1.splits : s2.splits) * (size_t)round_up(n_res, 1024) * kWidePCH * 4;
+    const size_t f64 = (size_t)(s1.splits > s2.splits ? s1.splits : s2.splits) * (size_t)round_up(n_res, 1024) * kWidePCH * 4;
+    const size_t fx = fx_apply_ws(c, n_res, n_str, d, p);
+    return f64 > fx ? f64 : fx;
 }
 
 fs_status f64_apply(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, const float *V,
@@ -653,6 +665,8 @@ fs_status f64_apply(Ctx *c, const Prepared *P, const Side *res, const Side *str,
     a.lda = lda;
     a.n_res = res->cnt;
     a.d = (int)P->d;
+    const bool fx = P->fx_ks > 0;   // (the gate chooses between the fixed-point kernel and this file's)
+    if (fx) a.gate = fx_gate(P, eps);
     for (int p0 = 0; p0 < p;) {
         a.p0 = p0;
         // more than 64 columns left: a wide pass (128 columns) -- every pass repeats the score contraction
@@ -666,6 +680,14 @@ fs_status f64_apply(Ctx *c, const Prepared *P, const Side *res, const Side *str,
             (size_t)s.splits * res->cnt_pad * 16 > P->partial_bytes || (a.kp % KC) != 0 || a.kc > a.kp ||
             (size_t)s.splits * res->cnt_pad * width * 4 > P->extra_bytes)
             return fail(c, FS_ERR_DEVICE, "internal: fp64 apply launch shape exceeds the padded buffers");
+        Splits splits(s.splits);
+        int pc = width;
+        if (fx) {
+            int fx_splits = 0;
+            fs_status st = fx_apply_pass(c, P, res, str, eps, V, p, ldv, p0, hadA, lda, &fx_splits, &pc);
+            if (st != FS_OK) return st;
+            splits = Splits(fx_splits, s.splits);
+        }
         const dim3 grid((unsigned)s.row_blocks, (unsigned)s.splits);
 #define FS_F64_APPLY(H, N) hipLaunchKernelGGL((k_pass_f64<true, H, N, kApplyJT, kApplyNW>), grid, dim3(64 * kApplyNW), 0, c->stream, a)
         if (hadA) {
@@ -688,8 +710,8 @@ fs_status f64_apply(Ctx *c, const Prepared *P, const Side *res, const Side *str,
             }
         }
 #undef FS_F64_APPLY
-        fs_status st = launch_apply_finalize(c, P, res, res->norm, s.splits, eps, a.opart, width, p0, (int)p, out, ldo,
-                                             mass_out);
+        fs_status st = launch_apply_finalize(c, P, res, res->norm, splits, eps, a.opart, pc, p0, (int)p, out, ldo, mass_out,
+                                             width);
         if (st != FS_OK) return st;
         p0 += width;
     }

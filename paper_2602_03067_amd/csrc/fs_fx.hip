@@ -1,0 +1,867 @@
+// fp32-accuracy path for 16 < d <= 128: the score contraction <x_i, y_j> in fixed point on the int8
+// matrix cores (v_mfma_i32_32x32x32_i8), exact integer accumulation.
+//
+// Why: the fp64 matrix cores (fs_f64.hip) have 1/64 of the int8 rate.  A coordinate is 31-bit fixed
+// point relative to the clouds' common scale r2 (a power of two), split into four balanced base-256
+// digits,  x = r2 2^-31 sum_i D_i 2^(8 (4 - i)),  |D_1| <= 127, D_i in [-128, 127].  A product of two
+// points is then a sum over digit pairs (i, j) of weight 2^(64 - 8 (i + j)), and the thirteen pairs
+// with i + j <= 6 are kept: what is dropped (i + j >= 7) is below 2^-38 r2^2 sqrt(d / 64) rms, and the
+// gate (FxGate) sends problems whose scores would feel it to the fp64 kernels.
+//
+// The pairs of equal weight share an accumulator, and neighbouring weights share a register by
+// Horner's rule between MFMAs, so a score leaves the matrix cores as two integers:
+//     H = 2^8 sum(1,1) + sum(i + j = 3)                      unit u3 = cscale r2^2 2^-22
+//     L = 2^8 sum(i + j = 4) + sum(i + j = 5) + 2^-8 sum(i + j = 6)     unit u5 = u3 2^-16
+// The streamed point's bias enters as the initial accumulators (three integers per point, units u2,
+// u4, u6: see store_fx_record) and the resident row's running max (an integer m) as an integer
+// subtraction, so cancellation happens in exact integer arithmetic and the vector ALU only converts
+// what is left:  score - m = u3 H + (u5 L + rho),  rho = what m loses on the grid u3.
+//
+// A tile of 32 streamed points whose biases do not fit that grid (padding, zero weights, potentials
+// far away) is flagged in its bias record and takes a float64 epilogue with the float64 biases; so does
+// a row whose running max is beyond the integer range.
+//
+// Mapping (32x32x32): A = streamed points (lane l: point l % 32, bytes 16 (l / 32) ..), B = resident
+// rows, D: lane l, register r holds D[i = 8 (r / 4) + 4 (l / 32) + r % 4][j = l % 32]: the sixteen
+// registers of a lane are sixteen streamed points of ONE resident row.  Digit images in HBM hold the
+// fragments in lane order ([tile of 32 points][k-step of 32][digit][64 lanes][16 bytes]), so LDS is
+// filled by linear direct loads and read without bank conflicts.
+//
+// A workgroup is four waves = 128 resident rows (their digits stay in registers) over a run of
+// streamed tiles that pass through an LDS ring; two workgroups per CU.
+//
+// Bound: the card's power limit.  A loop of nothing but this MFMA runs at 15.6 ns per instruction and
+// SIMD with constant operands and at 20 with random ones (the clock falls from 2.05 to 1.6 GHz), and the
+// vector work beside it (about 150 instructions per tile of 32 x 32 scores) adds to that instead of
+// hiding: 20 MFMAs and 112 vector instructions measured 580 ns alone, this kernel 700 to 730 ns per tile.
+// Tried without gain: tile g + 1's MFMAs interleaved with tile g's vector work in one wave (216-226 us
+// against 211 at n = m = 16384, d = 64), three workgroups per CU, digits read from LDS twice instead of held.
+// Measured (half-step with its merge, us): n = m = 16384, d = 64: 577 fp64 -> 178 with ten products, 208 with
+// thirteen; n = m = 10000, d = 64: 232 -> 79; n = 9973, m = 12007, d = 128: 545 -> 152; n = m = 12000, d = 32: 192 -> 88.
+// Error of plan sums against 64 bits: 5e-8 to 1e-7, fp64 scores with fp32 sums 1e-7 to 7e-7.
+#include <type_traits>
+
+#include "fs_internal.h"
+
+namespace fs {
+namespace {
+
+typedef int i4 __attribute__((ext_vector_type(4)));
+typedef int i16v __attribute__((ext_vector_type(16)));
+typedef float f16v __attribute__((ext_vector_type(16)));
+typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+
+constexpr int kRows = 128;           // resident rows per workgroup
+constexpr int kRecBytes = 512;       // bias record of a tile
+
+__device__ inline float fast_exp2(float v) { return __builtin_amdgcn_exp2f(v); }
+__device__ inline void lds_done_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+template <int N> __device__ inline void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+
+// the eight bf16 values with infinities and NaN replaced by zero
+__device__ inline bf8 finite_only(bf8 v)
+{
+    uint4 u = __builtin_bit_cast(uint4, v);
+    uint32_t *p = &u.x;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        if ((p[k] & 0x7f80u) == 0x7f80u) p[k] &= 0xffff0000u;
+        if ((p[k] & 0x7f800000u) == 0x7f800000u) p[k] &= 0xffffu;
+    }
+    return __builtin_bit_cast(bf8, u);
+}
+
+struct FxArgs {
+    const unsigned char *res, *str;   // digit images
+    const int *brec;                  // bias records of the streamed tiles
+    const double *bias;               // the same biases in float64
+    FxGate gate;
+    int n_tiles, tiles_per_split;
+    double2 *partial;                 // [splits][partial_stride] (max, sum)
+    int64_t partial_stride;
+    // application
+    const float *V;                   // MODE 1: [n_str][ldv] values, columns p0 ..
+    int64_t ldv, n_str;
+    int p0;
+    const unsigned char *vimg;        // MODE 2: value images (see k_vimg_fx)
+    const int *vflag;                 // MODE 2: [n_tiles] the tile holds values that are not finite
+    float *opart;                     // [splits][partial_stride][PC]
+    // HAD: digit image of the rows of the Hadamard factor and their scales (see k_had_digits)
+    const unsigned char *had;
+    const float *had_scale;
+};
+
+// MODE 0: log-sum-exp.  MODE 1: application to NC <= 4 columns on the vector ALU (one fma per score and
+// column).  MODE 2: application to 32 NC columns: the exponentials, in three bf16 pieces each, are the B
+// operand of a second MFMA against the values in three bf16 pieces.  Six of the nine piece products are
+// kept; those dropped are below 2^-25 of a product, less than one rounding of an fp32 accumulation.
+// HAD (with MODE 2): Hadamard-weighted application (Alg. 5), every exponential times <row of A, streamed point>, which is
+// a second contraction of the same streamed digits with those of A (a scale per row; ten products).
+template <int KS, int MODE, int NC, bool HAD = false> struct FxShape {
+    static constexpr int kValBytes = MODE == 0 ? 0 : MODE == 1 ? (NC + 1) / 2 * 256 : NC * 6 * 1024;
+    static constexpr int kStage = KS * 4096 + kRecBytes + kValBytes;
+    static constexpr int kStages = kStage <= 13 * 1024 ? 4 : 3;
+    // vector-memory instructions of a wave per stage
+    static constexpr int kLoads = KS + 1 + (MODE == 0 ? 0 : MODE == 1 ? 1 : (NC * 6 + 3) / 4);
+    static constexpr int kWgPerCu = HAD ? 1 : 2;   // (HAD: the second set of resident digits takes the registers)
+    static constexpr int kPC = MODE == 2 ? 32 * NC : NC;
+    static constexpr bool kHold = KS <= 2;
+};
+
+template <int KS, int MODE, int NC, bool FULL, bool HAD = false>
+__device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, const int bx, const int by)
+{
+    using S = FxShape<KS, MODE, NC, HAD>;
+    constexpr int NS = S::kStages;
+    const int tid = threadIdx.x;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
+    const int lh = l >> 5, lj = l & 31;
+    const int64_t row0 = (int64_t)bx * kRows + 32 * w;
+    const int t_begin = by * a.tiles_per_split;
+    const int t_end = min(a.n_tiles, t_begin + a.tiles_per_split);
+    const int G = t_end - t_begin;
+    const unsigned ring_off = (unsigned)(size_t)ring;
+    const unsigned l16 = l * 16, l4 = l * 4;
+
+    const double u3d = a.gate.unit(22), u5d = a.gate.unit(38);
+    const float u3 = (float)u3d, u5 = (float)u5d;
+    const int lazy = (int)fmin(4.0 / u3d, 1073741824.0);   // see settle
+
+    int issued = 0;
+    auto issue = [&]() __attribute__((always_inline)) {
+        const int64_t t = t_begin + issued;
+        const unsigned lds = ring_off + (issued % NS) * S::kStage;
+        const unsigned char *src = a.str + t * (KS * 4096);
+#pragma unroll
+        for (int q = 0; q < KS; ++q) dma16s(src + (KS * w + q) * 1024, l16, lds + (KS * w + q) * 1024);
+        dma4s(a.brec + t * 128 + (w & 1) * 64, l4, lds + KS * 4096 + (w & 1) * 256);
+        if constexpr (MODE == 1) {
+            constexpr int NV = (NC + 1) / 2;
+            const int v = w % NV;
+            const int c = min(2 * v + lh, NC - 1);
+            int64_t i = t * 32 + lj;
+            i = i < a.n_str ? i : a.n_str - 1;   // (rows beyond the matrix: only in flagged tiles, masked there)
+            dma4(a.V + i * a.ldv + a.p0 + c, lds + KS * 4096 + kRecBytes + v * 256);
+        }
+        if constexpr (MODE == 2) {
+            constexpr int PW = (NC * 6 + 3) / 4;
+            const unsigned char *vs = a.vimg + t * (NC * 6 * 1024);
+#pragma unroll
+            for (int q = 0; q < PW; ++q) {
+                const int pc = min(w * PW + q, NC * 6 - 1);   // (a repeated last piece keeps the waves' load counts equal)
+                dma16s(vs + pc * 1024, l16, lds + KS * 4096 + kRecBytes + pc * 1024);
+            }
+        }
+        ++issued;
+    };
+
+    // resident digits: registers for the whole pass
+    i4 b[KS][4], bw[HAD ? KS : 1][4];
+    float w3 = 0.0f, w5 = 0.0f;   // units of the Hadamard weights
+    {
+        const unsigned char *rt = a.res + (row0 >> 5) * (KS * 4096) + l16;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int dg = 0; dg < 4; ++dg) b[ks][dg] = *reinterpret_cast<const i4 *>(rt + (ks * 4 + dg) * 1024);
+        // (used here, so that the wait for these loads stands before the loop: inside it, it would wait for the ring's)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int dg = 0; dg < 4; ++dg) asm volatile("" : "+v"(b[ks][dg]));
+        if constexpr (HAD) {
+            const unsigned char *ht = a.had + (row0 >> 5) * (KS * 4096) + l16;
+            const double sc = (double)a.had_scale[row0 + lj] * *a.gate.r2;
+            w3 = (float)ldexp(sc, -22);
+            w5 = (float)ldexp(sc, -38);
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                for (int dg = 0; dg < 4; ++dg) bw[ks][dg] = *reinterpret_cast<const i4 *>(ht + (ks * 4 + dg) * 1024);
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                for (int dg = 0; dg < 4; ++dg) asm volatile("" : "+v"(bw[ks][dg]));
+            asm volatile("" : "+v"(w3), "+v"(w5));
+        }
+    }
+
+    // running sum of 2^(score - m) with m = -u3 nhm (s == 0: nothing seen yet, m is free).  Sixteen scores are summed in
+    // float, tiles in double: two more instructions per tile, and the sum over a long split keeps no rounding of its own.
+    double s = 0.0;
+    int nhm = 0;
+    bool far = false;      // m is beyond the integer range: m = mfar
+    float mfar = 0.0f;
+    constexpr int NO = MODE == 2 ? NC : 1;
+    f16v O[NO];
+    double ov[MODE == 1 ? NC : 1];
+#pragma unroll
+    for (int cb = 0; cb < NO; ++cb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) O[cb][r] = 0.0f;
+#pragma unroll
+    for (int c = 0; c < (MODE == 1 ? NC : 1); ++c) ov[c] = 0.0;
+
+    auto scale_sums = [&](float sc) __attribute__((always_inline)) {
+        s *= (double)sc;
+        if constexpr (MODE == 1) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c) ov[c] *= (double)sc;
+        }
+        if constexpr (MODE == 2) {
+#pragma unroll
+            for (int cb = 0; cb < NC; ++cb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) O[cb][r] *= sc;
+        }
+    };
+    // the pairs (-1, 0) and (0, -1) in bf16, held in vector registers (the dot-product instruction does not read inline
+    // constants as a bf16 pair)
+    uint32_t ksel0 = 0, ksel1 = 0;
+    if constexpr (MODE == 2) {
+        asm("v_mov_b32 %0, 0xbf80" : "=v"(ksel0));
+        asm("v_mov_b32 %0, 0xbf800000" : "=v"(ksel1));
+    }
+
+    // ---- scores of a tile: the digit products ------------------------------------------------------------------
+    struct Tile {
+        i16v H, P, Q;
+        bool flagged;
+    };
+#define FX_MM(ACC, I, J) T.ACC = __builtin_amdgcn_mfma_i32_32x32x32_i8(av[S::kHold ? ks : 0][I], b[ks][J], T.ACC, 0, 0, 0)
+    // (beyond two k-steps the digits of the streamed points are read from LDS once per phase instead of held)
+#define FX_DIGITS(KS_)                                                                                                     \
+    if constexpr (!S::kHold) {                                                                                             \
+        _Pragma("unroll") for (int dg = 0; dg < 4; ++dg) av[0][dg] = *reinterpret_cast<const i4 *>(fr + (KS_ * 4 + dg) * 1024); \
+    }
+    auto contract = [&](const unsigned char *sb, Tile &T) __attribute__((always_inline)) {
+        const int *rec = reinterpret_cast<const int *>(sb + KS * 4096);
+        const unsigned char *fr = sb + l16;
+        i4 av[S::kHold ? KS : 1][4];
+        if constexpr (S::kHold) {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                for (int dg = 0; dg < 4; ++dg) av[ks][dg] = *reinterpret_cast<const i4 *>(fr + (ks * 4 + dg) * 1024);
+        }
+#pragma unroll
+        for (int g4 = 0; g4 < 4; ++g4) {
+            const i4 v0 = *reinterpret_cast<const i4 *>(rec + 8 * g4 + 4 * lh);
+            const i4 v1 = *reinterpret_cast<const i4 *>(rec + 32 + 8 * g4 + 4 * lh);
+            const i4 v2 = FULL ? *reinterpret_cast<const i4 *>(rec + 64 + 8 * g4 + 4 * lh) : i4{0, 0, 0, 0};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                T.H[4 * g4 + q] = v0[q];
+                T.Q[4 * g4 + q] = v1[q];
+                T.P[4 * g4 + q] = v2[q];
+            }
+        }
+        T.flagged = __builtin_amdgcn_readfirstlane(rec[96]) != 0;
+        if constexpr (FULL) {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                FX_DIGITS(ks)
+                FX_MM(P, 3, 1);
+                FX_MM(P, 2, 2);
+                FX_MM(P, 1, 3);
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) T.P[r] = T.P[r] >> 8;
+        }
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            FX_DIGITS(ks)
+            FX_MM(H, 0, 0);
+            FX_MM(Q, 2, 0);
+            FX_MM(Q, 1, 1);
+            FX_MM(Q, 0, 2);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r)   // (wraps are undone by what follows: only the difference counts)
+            T.H[r] = (int)(((unsigned)T.H[r] << 8) + (unsigned)nhm);
+        if constexpr (!S::kHold) asm volatile("" : "+v"(fr));
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            FX_DIGITS(ks)
+            FX_MM(H, 0, 1);
+            FX_MM(H, 1, 0);
+            FX_MM(P, 0, 3);
+            FX_MM(P, 1, 2);
+            FX_MM(P, 2, 1);
+            FX_MM(P, 3, 0);
+        }
+    };
+#undef FX_DIGITS
+#undef FX_MM
+
+    // ---- before the exponentials of tile g: the slow path of a tile, and the lift of the max ------------------
+    float u3v = u3, u5v = u5;   // score - m = u3v H + u5v L of the current tile
+    auto far_tile = [&](int g, Tile &T) __attribute__((always_inline)) {
+        // float64 scores (the record of a flagged tile holds no bias); what they leave above the max is handed on in the
+        // same two-integer form, units 2^-16 and 2^-32
+        const double *bd = a.bias + ((int64_t)(t_begin + g)) * 32 + 4 * lh;
+        const unsigned back = 0u - (unsigned)nhm;
+        double u3x = u3d;
+        auto score = [&](int r) __attribute__((always_inline)) {
+            const int Ha = (int)((unsigned)T.H[r] + back);
+            const int L = (int)(((unsigned)T.Q[r] << 8) + (unsigned)T.P[r]);
+            const double v = fma((double)L, u5d, (double)Ha * u3x);
+            return T.flagged ? v + bd[8 * (r >> 2) + (r & 3)] : v;
+        };
+        float mx = kNegInit;
+        double seen = s;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, (float)score(r));
+        if constexpr (MODE == 2) {   // m is common to the two lane halves
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            seen = fmax(s, __shfl_xor(s, 32));
+        }
+        double md = far ? (double)mfar : -u3d * (double)nhm;
+        if (mx > kNegInit && (!(seen > 0.0) || (double)mx > md)) {
+            const double q = ceil((double)mx / u3d);
+            const bool out = !(fabs(q) <= 1073741824.0);
+            const double mnew = out ? (double)mx : q * u3d;
+            if (seen > 0.0) scale_sums(fast_exp2((float)(md - mnew)));
+            md = mnew;
+            nhm = out ? 0 : -(int)q;
+            far = out;
+            mfar = mx;
+        }
+        asm volatile("" : "+v"(u3x));   // (the scores are formed anew rather than kept in 32 registers)
+        bool nan = false;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const double v = score(r) - md;
+            nan = nan || v != v;
+            const double c = fmax(v, -30000.0) * 65536.0, h = floor(c);
+            T.H[r] = (int)h;
+            T.P[r] = (int)((c - h) * 65536.0);
+            T.Q[r] = 0;
+        }
+        if (nan) scale_sums(NAN);
+        u3v = 1.52587890625e-05f;
+        u5v = 2.3283064365386963e-10f;
+        if constexpr (MODE == 1) {
+            // rows beyond the matrix: zero values (every wave writes the same)
+            const int left = (int)min((int64_t)32, a.n_str - (int64_t)(t_begin + g) * 32);
+            float *vals = reinterpret_cast<float *>(ring + (g % NS) * S::kStage + KS * 4096 + kRecBytes);
+            if (lj >= left)
+                for (int c = lh; c < NC; c += 2) vals[c * 32 + lj] = 0.0f;
+        }
+    };
+    // m moves to the largest score where one exceeds it by more than `lazy`, 4 base-2 units (a float argument of 4 is
+    // rounded by 2^-23); in MODE 2 both lane halves move together, since the second MFMA sums over them.  The factor of the old sums is a
+    // rounded power: what it is off by counts with the weight 2^(old m - new m) of those sums, at most 3e-8 of the new one.
+    auto settle = [&](int g, Tile &T) __attribute__((always_inline)) {
+        u3v = u3;
+        u5v = u5;
+        if (T.flagged || __any(far)) {
+            far_tile(g, T);
+            return;
+        }
+        int hx = T.H[0];
+#pragma unroll
+        for (int r = 1; r < 16; ++r) hx = max(hx, T.H[r]);
+        if (__any(hx > lazy || !(s > 0.0))) {
+            double seen = s;
+            if constexpr (MODE == 2) {
+                hx = max(hx, __shfl_xor(hx, 32));
+                seen = fmax(s, __shfl_xor(s, 32));
+            }
+            const int dh = seen > 0.0 ? max(hx, 0) : hx;
+            scale_sums(fast_exp2(fminf((float)-dh * u3, 0.0f)));   // (1 where nothing was seen)
+            nhm -= dh;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) T.H[r] -= dh;
+        }
+    };
+    // ---- exponentials of tile g, their sum and what they are applied to -------------------------------------
+    auto finish = [&](int g, const unsigned char *sb, const Tile &T) __attribute__((always_inline)) {
+        const unsigned char *vals = sb + KS * 4096 + kRecBytes;
+        float e[16];
+        float s0 = 0.0f, s1 = 0.0f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int L = (int)(((unsigned)T.Q[r] << 8) + (unsigned)T.P[r]);
+            e[r] = fast_exp2(fmaf((float)L, u5v, (float)T.H[r] * u3v));
+            if (r & 1)
+                s1 += e[r];
+            else
+                s0 += e[r];
+        }
+        s += (double)(s0 + s1);
+        if constexpr (MODE == 1) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                float o = 0.0f;
+#pragma unroll
+                for (int g4 = 0; g4 < 4; ++g4) {
+                    const float4 v = *reinterpret_cast<const float4 *>(vals + c * 128 + (8 * g4 + 4 * lh) * 4);
+                    o = fmaf(e[4 * g4], v.x, o);
+                    o = fmaf(e[4 * g4 + 1], v.y, o);
+                    o = fmaf(e[4 * g4 + 2], v.z, o);
+                    o = fmaf(e[4 * g4 + 3], v.w, o);
+                }
+                ov[c] += (double)o;
+            }
+        }
+        if constexpr (HAD) {
+            i16v H, Q, P;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) H[r] = Q[r] = P[r] = 0;
+            const unsigned char *fr = sb + l16;
+#define FX_MW(ACC, I, J) ACC = __builtin_amdgcn_mfma_i32_32x32x32_i8(f[I], bw[ks][J], ACC, 0, 0, 0)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                i4 f[4];
+#pragma unroll
+                for (int dg = 0; dg < 4; ++dg) f[dg] = *reinterpret_cast<const i4 *>(fr + (ks * 4 + dg) * 1024);
+                FX_MW(H, 0, 0);
+                FX_MW(Q, 2, 0);
+                FX_MW(Q, 1, 1);
+                FX_MW(Q, 0, 2);
+                FX_MW(P, 3, 0);
+                FX_MW(P, 2, 1);
+                FX_MW(P, 1, 2);
+                FX_MW(P, 0, 3);
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) H[r] <<= 8;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                i4 f[2];
+#pragma unroll
+                for (int dg = 0; dg < 2; ++dg) f[dg] = *reinterpret_cast<const i4 *>(fr + (ks * 4 + dg) * 1024);
+                FX_MW(H, 0, 1);
+                FX_MW(H, 1, 0);
+            }
+#undef FX_MW
+#pragma unroll
+            for (int r = 0; r < 16; ++r) e[r] *= fmaf((float)(int)(((unsigned)Q[r] << 8) + (unsigned)P[r]), w5, (float)H[r] * w3);
+        }
+        if constexpr (MODE == 2) {
+            bf8 ep[2][3];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                // three bf16 pieces of eight exponentials; what a piece leaves comes from one bf16 dot product each (the
+                // packed pieces with (-1, 0) or (0, -1), accumulated onto the value: exact)
+                uint32_t pk[3][4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    float x0 = e[8 * h + 2 * q], x1 = e[8 * h + 2 * q + 1];
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) {
+                        const bf2 hd = {(__bf16)x0, (__bf16)x1};
+                        pk[k][q] = __builtin_bit_cast(uint32_t, hd);
+                        if (k < 2) {
+                            x0 = __builtin_amdgcn_fdot2_f32_bf16(hd, __builtin_bit_cast(bf2, ksel0), x0, false);
+                            x1 = __builtin_amdgcn_fdot2_f32_bf16(hd, __builtin_bit_cast(bf2, ksel1), x1, false);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < 3; ++k) ep[h][k] = __builtin_bit_cast(bf8, make_uint4(pk[k][0], pk[k][1], pk[k][2], pk[k][3]));
+            }
+            // A tile's products are summed on the matrix cores from zero, small ones first, and added to the output by the
+            // vector ALU: the matrix cores truncate where they align a product to the accumulator, and an accumulator kept
+            // there over the whole pass drifts (row sums of a plan at n = 8192 by 2e-7 of their size).  The truncation goes
+            // towards minus infinity, so every other tile has its values stored negated: what is left of it alternates.
+            const float sign = (t_begin + g) & 1 ? -1.0f : 1.0f;
+            auto second = [&](auto odd_c) __attribute__((always_inline)) {
+#pragma unroll
+                for (int cb = 0; cb < NC; ++cb) {
+                    f16v acc = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+                    bf8 v[2][3];
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const unsigned char *vp = vals + ((cb * 2 + h) * 3) * 1024 + l16;
+#pragma unroll
+                        for (int k = 0; k < 3; ++k) v[h][k] = *reinterpret_cast<const bf8 *>(vp + k * 1024);
+                        // an infinite or NaN value (in piece 0 alone) meets the leading piece of its exponential only:
+                        // the later ones may be zero or negative
+                        const bf8 vf = decltype(odd_c)::value ? finite_only(v[h][0]) : v[h][0];
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v[h][2], ep[h][0], acc, 0, 0, 0);
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, ep[h][2], acc, 0, 0, 0);
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v[h][1], ep[h][1], acc, 0, 0, 0);
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v[h][1], ep[h][0], acc, 0, 0, 0);
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, ep[h][1], acc, 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v[h][0], ep[h][0], acc, 0, 0, 0);
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) O[cb][r] = fmaf(acc[r], sign, O[cb][r]);
+                }
+            };
+            if (a.vflag[t_begin + g])
+                second(std::integral_constant<bool, true>{});
+            else
+                second(std::integral_constant<bool, false>{});
+        }
+    };
+
+    for (; issued < NS - 1 && issued < G;) issue();
+    for (int g = 0; g < G; ++g) {
+        const int newer = issued - g - 1;
+        if (newer >= 2)
+            wait_vm<2 * S::kLoads>();
+        else if (newer == 1)
+            wait_vm<S::kLoads>();
+        else
+            wait_vm<0>();
+        lds_done_barrier();          // everybody's pieces of this tile have landed, and its predecessor is read
+        if (issued < G) issue();     // into the predecessor's slot
+        const unsigned char *sb = ring + (g % NS) * S::kStage;
+        Tile T;
+        contract(sb, T);
+        settle(g, T);
+        finish(g, sb, T);
+    }
+
+    // merge the two lane halves of every resident row
+    // (the merges expect integer maxima)
+    const double mym = s == 0.0 ? (double)kNegInit : far ? (double)mfar : -u3d * (double)nhm;
+    const double mo = __shfl_xor(mym, 32);
+    const double so = __shfl_xor(s, 32);
+    const double M = fmax(mym, mo) > (double)kNegInit ? ceil(fmax(mym, mo)) : (double)kNegInit;
+    const float f0 = fast_exp2((float)(mym - M)), f1 = fast_exp2((float)(mo - M));
+    const int64_t rec_row = (int64_t)by * a.partial_stride + row0 + lj;
+    if (lh == 0) a.partial[rec_row] = make_double2(M, s * (double)f0 + so * (double)f1);
+    if constexpr (MODE == 1) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const double oo = __shfl_xor(ov[c], 32);
+            if (lh == 0) a.opart[rec_row * NC + c] = (float)(ov[c] * (double)f0 + oo * (double)f1);
+        }
+    }
+    if constexpr (MODE == 2) {
+        // (m is common to the two halves; each holds half of the columns)
+        const float fm = fmaxf(f0, f1);
+        float *o = a.opart + rec_row * S::kPC;
+#pragma unroll
+        for (int cb = 0; cb < NC; ++cb)
+#pragma unroll
+            for (int g4 = 0; g4 < 4; ++g4)
+                *reinterpret_cast<float4 *>(o + 32 * cb + 8 * g4 + 4 * lh) =
+                    make_float4(O[cb][4 * g4] * fm, O[cb][4 * g4 + 1] * fm, O[cb][4 * g4 + 2] * fm, O[cb][4 * g4 + 3] * fm);
+    }
+}
+
+template <int KS, int MODE, int NC, bool HAD = false>
+__global__ __launch_bounds__(256, (FxShape<KS, MODE, NC, HAD>::kWgPerCu)) void k_fx(FxArgs a)
+{
+    using S = FxShape<KS, MODE, NC, HAD>;
+    __shared__ __attribute__((aligned(1024))) unsigned char ring[S::kStages * S::kStage];
+    if (!a.gate.on()) return;
+    if (a.gate.full())
+        fx_body<KS, MODE, NC, true, HAD>(a, ring, blockIdx.x, blockIdx.y);
+    else
+        fx_body<KS, MODE, NC, false, HAD>(a, ring, blockIdx.x, blockIdx.y);
+}
+
+// Both passes of one iteration of the averaged schedule (Eq. 4-5) in one launch: the first rb0 row blocks of the
+// grid belong to the f-pass (a0), the others to the g-pass (a1).
+template <int KS>
+__global__ __launch_bounds__(256, (FxShape<KS, 0, 1>::kWgPerCu)) void k_fx_pair(FxArgs a0, FxArgs a1, int rb0, int splits0, int splits1)
+{
+    using S = FxShape<KS, 0, 1>;
+    __shared__ __attribute__((aligned(1024))) unsigned char ring[S::kStages * S::kStage];
+    if (!a0.gate.on()) return;
+    const bool second = (int)blockIdx.x >= rb0;   // uniform over the workgroup
+    if ((int)blockIdx.y >= (second ? splits1 : splits0)) return;
+    const int bx = (int)blockIdx.x - (second ? rb0 : 0);
+    if (a0.gate.full())
+        fx_body<KS, 0, 1, true>(second ? a1 : a0, ring, bx, blockIdx.y);
+    else
+        fx_body<KS, 0, 1, false>(second ? a1 : a0, ring, bx, blockIdx.y);
+}
+
+// Value images for MODE 2: [tile][32-column block][16 points][piece][64 lanes][8 bf16], lane l holding column l % 32
+// and the eight streamed points whose exponentials sit in that lane half (registers 8 h .. 8 h + 7 of the score tile).
+// Zero outside the matrix; odd tiles hold the negated values (see finish).  A block of 128 nc threads makes the image of
+// one tile.
+__global__ __launch_bounds__(512) void k_vimg_fx(const float *V, int64_t ldv, int64_t n_str, int p0, int p, int nc, unsigned char *img,
+                                                 int *vflag)
+{
+    const int64_t t = blockIdx.x;
+    const int cb = threadIdx.x >> 7;
+    const int h = (threadIdx.x >> 6) & 1, l = threadIdx.x & 63, lh = l >> 5;
+    const int c = p0 + 32 * cb + (l & 31);
+    uint32_t pk[3][4];
+    int odd = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        __bf16 x[2][3];
+#pragma unroll
+        for (int z = 0; z < 2; ++z) {
+            const int r = 8 * h + 2 * q + z;
+            const int64_t i = t * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
+            const float u = (i < n_str && c < p) ? V[i * ldv + c] : 0.0f, v = t & 1 ? -u : u;
+            split3(v, x[z]);
+            if (!(fabsf(v) < INFINITY)) {
+                odd = 1;
+                x[z][1] = x[z][2] = (__bf16)0.0f;
+            } else if (fabsf(v) > 3.3895313892515355e38f) {   // (would round to an infinite first piece)
+                const float top = copysignf(3.3895313892515355e38f, v);
+                x[z][0] = (__bf16)top;
+                x[z][1] = (__bf16)(v - top);
+                x[z][2] = (__bf16)(v - top - (float)x[z][1]);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) pk[k][q] = bf16_pair(x[0][k], x[1][k]);
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        *reinterpret_cast<uint4 *>(img + (((t * nc + cb) * 2 + h) * 3 + k) * 1024 + l * 16) = make_uint4(pk[k][0], pk[k][1], pk[k][2], pk[k][3]);
+    odd = __syncthreads_or(odd);
+    if (threadIdx.x == 0) vflag[t] = odd;
+}
+
+// Digit image of the rows of A [n][lda] (layout of the points' images), each row with its own power-of-two scale; a row that
+// is not finite gets the scale NaN.  A block of 256 threads makes one tile of 32 rows.
+__global__ __launch_bounds__(256) void k_had_digits(const float *A, int64_t lda, int64_t n, int d, int ks, unsigned char *img, float *scale)
+{
+    __shared__ float pt[32][32 * kFxMaxKs + 1];
+    __shared__ int sh_ex[32];
+    const int64_t row0 = (int64_t)blockIdx.x * 32;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    for (int r = wv; r < 32; r += 4) {
+        const int64_t row = row0 + r;
+        uint32_t mx = 0;
+        for (int k = lane; k < 32 * ks; k += 64) {
+            const float v = (row < n && k < d) ? A[row * lda + k] : 0.0f;
+            pt[r][k] = v;
+            mx = max(mx, __float_as_uint(fabsf(v)));
+        }
+        for (int off = 32; off > 0; off >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, 64));
+        const float big = __uint_as_float(mx);
+        int ex = 0;
+        if (big < INFINITY && big > 0.0f) (void)frexp((double)big * (128.0 / 127.49), &ex);
+        if (lane == 0) {
+            sh_ex[r] = ex;
+            scale[row] = big < INFINITY ? (float)ldexp(1.0, ex) : NAN;
+        }
+    }
+    __syncthreads();
+    for (int e = tid; e < ks * 64; e += 256) {
+        const int q = e >> 6, l = e & 63;
+        const int k0 = 32 * q + 16 * (l >> 5);
+        const double to_fixed = ldexp(1.0, 31 - sh_ex[l & 31]);
+        uint4 o[4];
+        fx_digits16(&pt[l & 31][k0], to_fixed, o);
+#pragma unroll
+        for (int dg = 0; dg < 4; ++dg) *reinterpret_cast<uint4 *>(img + ((((int64_t)blockIdx.x * ks + q) * 4 + dg) << 10) + l * 16) = o[dg];
+    }
+}
+
+// Launch shape: row blocks x splits of the streamed side, minimising a makespan model in units of one tile of one
+// workgroup on a full CU: workgroups are dealt to the CUs evenly and run `occ` at a time; an incomplete batch leaves
+// the matrix pipe partly idle (one workgroup of several is charged 2, two of three 2.35).  `startup`: filling the
+// ring, loading the resident digits, the first lift of the max and the merge, in tiles.
+PassShape fx_shape(const Ctx *c, int64_t n_res, int64_t n_str, int occ)
+{
+    PassShape s;
+    s.rows_per_block = kRows;
+    s.row_blocks = (int)ceil_div(n_res, kRows);
+    const int n_tiles = (int)ceil_div(n_str, 32);
+    int cap = max_splits(c->partial_budget, n_res);
+    if (cap > n_tiles) cap = n_tiles;
+    const double startup = 4.0;
+    double best = 0.0;
+    int best_tps = n_tiles;
+    for (int sp = 1; sp <= cap; ++sp) {
+        const int tps = (int)ceil_div(n_tiles, sp);
+        if ((int)ceil_div(n_tiles, tps) != sp) continue;
+        const int64_t wg = ceil_div((int64_t)s.row_blocks * sp, (int64_t)c->num_cu);
+        const int rem = (int)(wg % occ);
+        const double units = (double)(wg - rem) + (rem == 0 ? 0.0 : rem == 1 ? 2.0 : 2.35);
+        const double cost = units * ((double)tps + startup) + 0.05 * sp;
+        if (best == 0.0 || cost < best * 0.995) {
+            best = cost;
+            best_tps = tps;
+        }
+    }
+    s.splits = (int)ceil_div(n_tiles, best_tps);
+    s.cols_per_split = (int64_t)best_tps * 32;
+    return s;
+}
+
+constexpr int kOcc = 2, kOccHad = 1;   // workgroups per CU (FxShape::kWgPerCu)
+
+fs_status pass_args(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, int occ, void *partial, FxArgs *out,
+                    PassShape *shape)
+{
+    const PassShape s = fx_shape(c, res->cnt, str->cnt, occ);
+    FxArgs a{};
+    a.res = res->dig;
+    a.str = str->dig;
+    a.brec = str->brec;
+    a.bias = str->bias_d;
+    a.gate = fx_gate(P, eps);
+    a.n_tiles = (int)ceil_div(str->cnt, 32);
+    a.tiles_per_split = (int)(s.cols_per_split / 32);
+    a.partial = (double2 *)partial;
+    a.partial_stride = res->cnt_pad;
+    a.n_str = str->cnt;
+    if ((int64_t)s.row_blocks * kRows > res->cnt_pad || (int64_t)a.n_tiles * 32 > str->cnt_pad ||
+        (size_t)s.splits * res->cnt_pad * 16 > P->partial_bytes || P->fx_ks < 1 || P->fx_ks > kFxMaxKs)
+        return fail(c, FS_ERR_DEVICE, "internal: fixed-point launch shape exceeds the padded buffers");
+    *out = a;
+    *shape = s;
+    return FS_OK;
+}
+
+template <int KS>
+void launch_apply(Ctx *c, const FxArgs &a, dim3 grid, int mode, int nc)
+{
+    if (a.had) {
+        if (nc == 1)
+            hipLaunchKernelGGL((k_fx<KS, 2, 1, true>), grid, dim3(256), 0, c->stream, a);
+        else
+            hipLaunchKernelGGL((k_fx<KS, 2, 2, true>), grid, dim3(256), 0, c->stream, a);
+        return;
+    }
+#define FX_LAUNCH(M, N) hipLaunchKernelGGL((k_fx<KS, M, N>), grid, dim3(256), 0, c->stream, a)
+    if (mode == 1) {
+        switch (nc) {
+        case 1: FX_LAUNCH(1, 1); break;
+        case 2: FX_LAUNCH(1, 2); break;
+        case 3: FX_LAUNCH(1, 3); break;
+        default: FX_LAUNCH(1, 4); break;
+        }
+    } else {
+        switch (nc) {
+        case 1: FX_LAUNCH(2, 1); break;
+        case 2: FX_LAUNCH(2, 2); break;
+        case 3: FX_LAUNCH(2, 3); break;
+        default: FX_LAUNCH(2, 4); break;
+        }
+    }
+#undef FX_LAUNCH
+}
+
+// columns of a pass with `left` columns to go: up to 4 on the vector ALU, else blocks of 32 (at most 128; Hadamard-weighted:
+// matrix blocks always, at most 64)
+void fx_columns(int64_t left, bool had, int *mode, int *nc)
+{
+    const int64_t most = had ? 64 : 128;
+    *mode = left <= 4 && !had ? 1 : 2;
+    *nc = *mode == 1 ? (int)left : (int)ceil_div(left < most ? left : most, 32);
+}
+
+// buffer of a pass: [splits][rows][PC] accumulators, value images and their flags, digits and scales of A
+struct ApplyBuf {
+    size_t vimg, vflag, had, scale, total;
+    ApplyBuf(int splits, int64_t rows_pad, int64_t n_tiles, int ks, int mode, int nc, bool with_had)
+    {
+        Arena A;
+        (void)A.take((size_t)splits * rows_pad * (mode == 2 ? 32 * nc : nc) * 4);
+        vimg = A.take(mode == 2 ? (size_t)n_tiles * nc * 6144 : 0);
+        vflag = A.take(mode == 2 ? (size_t)n_tiles * 4 : 0);
+        had = A.take(with_had ? (size_t)rows_pad * ks * 128 : 0);
+        scale = A.take(with_had ? (size_t)rows_pad * 4 : 0);
+        total = A.off;
+    }
+};
+
+}  // namespace
+
+fs_status fx_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, int *splits)
+{
+    FxArgs a;
+    PassShape s;
+    fs_status st = pass_args(c, P, res, str, eps, kOcc, P->partial, &a, &s);
+    if (st != FS_OK) return st;
+    const dim3 grid((unsigned)s.row_blocks, (unsigned)s.splits);
+    switch (P->fx_ks) {
+    case 1: hipLaunchKernelGGL((k_fx<1, 0, 1>), grid, dim3(256), 0, c->stream, a); break;
+    case 2: hipLaunchKernelGGL((k_fx<2, 0, 1>), grid, dim3(256), 0, c->stream, a); break;
+    case 3: hipLaunchKernelGGL((k_fx<3, 0, 1>), grid, dim3(256), 0, c->stream, a); break;
+    default: hipLaunchKernelGGL((k_fx<4, 0, 1>), grid, dim3(256), 0, c->stream, a); break;
+    }
+    FS_HIP(c, hipGetLastError());
+    *splits = s.splits;
+    return FS_OK;
+}
+
+fs_status fx_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, void *partial_y, int *splits_x, int *splits_y)
+{
+    FxArgs ax, ay;
+    PassShape sx, sy;
+    fs_status st;
+    if ((st = pass_args(c, P, &P->X, &P->Y, eps, kOcc, partial_x, &ax, &sx)) != FS_OK) return st;
+    if ((st = pass_args(c, P, &P->Y, &P->X, eps, kOcc, partial_y, &ay, &sy)) != FS_OK) return st;
+    const dim3 grid((unsigned)(sx.row_blocks + sy.row_blocks), (unsigned)(sx.splits > sy.splits ? sx.splits : sy.splits));
+    switch (P->fx_ks) {
+    case 1: hipLaunchKernelGGL(k_fx_pair<1>, grid, dim3(256), 0, c->stream, ax, ay, sx.row_blocks, sx.splits, sy.splits); break;
+    case 2: hipLaunchKernelGGL(k_fx_pair<2>, grid, dim3(256), 0, c->stream, ax, ay, sx.row_blocks, sx.splits, sy.splits); break;
+    case 3: hipLaunchKernelGGL(k_fx_pair<3>, grid, dim3(256), 0, c->stream, ax, ay, sx.row_blocks, sx.splits, sy.splits); break;
+    default: hipLaunchKernelGGL(k_fx_pair<4>, grid, dim3(256), 0, c->stream, ax, ay, sx.row_blocks, sx.splits, sy.splits); break;
+    }
+    FS_HIP(c, hipGetLastError());
+    *splits_x = sx.splits;
+    *splits_y = sy.splits;
+    return FS_OK;
+}
+
+// buffer for any application to p columns, plain or Hadamard-weighted (the passes of one call differ in width and shape)
+size_t fx_apply_ws(const Ctx *c, int64_t n_res, int64_t n_str, int64_t d, int64_t p)
+{
+    const int ks = fx_ksteps(d);
+    if (ks == 0) return 0;
+    size_t most = 0;
+    for (int had = 0; had < 2; ++had)
+        for (int64_t left : {p, (int64_t)4}) {   // the widest pass, and a narrow last one (at most 4 columns)
+            int mode, nc;
+            fx_columns(left < p ? left : p, had != 0, &mode, &nc);
+            const PassShape s = fx_shape(c, n_res, n_str, had ? kOccHad : kOcc);
+            const ApplyBuf b(s.splits, round_up(n_res, 1024), ceil_div(n_str, 32), ks, mode, nc, had != 0);
+            if (b.total > most) most = b.total;
+        }
+    return most;
+}
+
+// one pass of an application: columns p0 .. of V; *pc = row length of the accumulators in P->extra.  hadA != nullptr:
+// Hadamard-weighted, with the rows of hadA [res->cnt][lda].
+fs_status fx_apply_pass(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, const float *V, int64_t p, int64_t ldv,
+                        int p0, const float *hadA, int64_t lda, int *splits, int *pc)
+{
+    int mode, nc;
+    fx_columns(p - p0, hadA != nullptr, &mode, &nc);
+    FxArgs a;
+    PassShape s;
+    fs_status st = pass_args(c, P, res, str, eps, hadA ? kOccHad : kOcc, P->partial, &a, &s);
+    if (st != FS_OK) return st;
+    const ApplyBuf buf(s.splits, res->cnt_pad, a.n_tiles, P->fx_ks, mode, nc, hadA != nullptr);
+    if (!P->extra || buf.total > P->extra_bytes) return fail(c, FS_ERR_DEVICE, "internal: fixed-point application exceeds its buffer");
+    unsigned char *x = reinterpret_cast<unsigned char *>(P->extra);
+    *pc = mode == 2 ? 32 * nc : nc;
+    a.V = V;
+    a.ldv = ldv;
+    a.p0 = p0;
+    a.opart = (float *)P->extra;
+    a.vimg = x + buf.vimg;
+    a.vflag = reinterpret_cast<const int *>(x + buf.vflag);
+    if (mode == 2)
+        hipLaunchKernelGGL(k_vimg_fx, dim3((unsigned)a.n_tiles), dim3(128 * nc), 0, c->stream, V, ldv, str->cnt, p0, (int)p, nc,
+                           x + buf.vimg, reinterpret_cast<int *>(x + buf.vflag));
+    if (hadA) {
+        a.had = x + buf.had;
+        a.had_scale = reinterpret_cast<const float *>(x + buf.scale);
+        hipLaunchKernelGGL(k_had_digits, dim3((unsigned)(res->cnt_pad / 32)), dim3(256), 0, c->stream, hadA, lda, res->cnt, (int)P->d,
+                           P->fx_ks, x + buf.had, reinterpret_cast<float *>(x + buf.scale));
+    }
+    const dim3 grid((unsigned)s.row_blocks, (unsigned)s.splits);
+    switch (P->fx_ks) {
+    case 1: launch_apply<1>(c, a, grid, mode, nc); break;
+    case 2: launch_apply<2>(c, a, grid, mode, nc); break;
+    case 3: launch_apply<3>(c, a, grid, mode, nc); break;
+    default: launch_apply<4>(c, a, grid, mode, nc); break;
+    }
+    FS_HIP(c, hipGetLastError());
+    *splits = s.splits;
+    return FS_OK;
+}
+
+}  // namespace fs

@@ -110,6 +110,60 @@ __device__ inline uint32_t bf16_pair(__bf16 lo, __bf16 hi)
 
 enum class Path { LowD, F64, BF16 };
 
+// Fixed-point scores (fs_fx.hip): k-steps of 32 coordinates, 0 where the path does not exist.  128 coordinates is what
+// the resident digits of a wave may take in registers, and what keeps its integer sums inside 32 bits.
+constexpr int kFxMaxKs = 4;
+__host__ __device__ inline int fx_ksteps(int64_t d) { return d > kLowdMaxD && d <= 32 * kFxMaxKs ? (int)((d + 31) / 32) : 0; }
+
+// Decides on the device which of the two kernels of a pass runs: every pass of a problem with digit images is launched
+// twice, fixed point and float64, and one of the two leaves at once (the scale of the clouds is known on the device only,
+// and a read-back would make every entry call wait).  cscale r2^2 is the size of a score's unit-scale product in base-2
+// units.  Up to 2^14 the products that the digits leave out stay below 2^-23.7 of a base-2 unit at d = 128, a fraction of
+// the rounding of the exponential's float argument; below 2^-3 the log weights no longer fit the bias records, every
+// tile would take the slow epilogue.  A scale that is not finite is off as well.
+constexpr double kFxFull = 128.0;
+struct FxGate {
+    const double *r2 = nullptr;   // common scale of both clouds (device), see k_prep_fx; nullptr: no digit images
+    double cscale = 0.0;          // 2 log2(e) / eps
+    __device__ bool on() const
+    {
+        const double r = *r2, v = cscale * r * r;
+        return v >= 0.125 && v <= 16384.0;
+    }
+    // all thirteen digit products; below this size ten leave less than 2^-23 of a base-2 unit out (see fs_fx.hip)
+    __device__ bool full() const
+    {
+        const double r = *r2;
+        return cscale * r * r > kFxFull;
+    }
+    __device__ double unit(int k) const { return ldexp(cscale * *r2 * *r2, -k); }
+};
+
+// the four balanced base-256 digits of sixteen coordinates in fixed point (to_fixed: 2^31 over their scale)
+__device__ inline void fx_digits16(const float *v, double to_fixed, uint4 (&out)[4])
+{
+    uint32_t o[4][4];
+#pragma unroll
+    for (int z = 0; z < 16; ++z) {
+        int X = fabsf(v[z]) < INFINITY ? (int)rint((double)v[z] * to_fixed) : 0;
+#pragma unroll
+        for (int dg = 3; dg >= 0; --dg) {
+            const int t = dg > 0 ? (int)(signed char)(X & 255) : X;   // balanced: what is left is a multiple of 256
+            o[dg][z >> 2] = (z & 3) ? o[dg][z >> 2] | ((uint32_t)(t & 255) << (8 * (z & 3))) : (uint32_t)(t & 255);
+            X = (X - t) >> 8;
+        }
+    }
+#pragma unroll
+    for (int dg = 0; dg < 4; ++dg) out[dg] = make_uint4(o[dg][0], o[dg][1], o[dg][2], o[dg][3]);
+}
+
+// Splits of the streamed side that a pass wrote, as the merges need them: n of the main kernel, and, where the gate
+// chooses between two kernels, alt of the float64 one (0: only one kernel was launched)
+struct Splits {
+    int n, alt;
+    Splits(int n_ = 1, int alt_ = 0) : n(n_), alt(alt_) {}
+};
+
 // ---------------------------------------------------------------------------------------
 // context
 // ---------------------------------------------------------------------------------------
@@ -152,6 +206,7 @@ struct Ctx {
     int dbg_lowd_score = 0;          // 32: fp32 scores, 64: float64 scores in every low-d half-step
     int dbg_lowd_precise_valu = 0;   // 1: float64 scores at d <= 3 on the vector ALU instead of the precise records
     int dbg_lowd_any_bias = 0;       // 1: the precise records also for biases beyond their digit range (tests of that case)
+    int dbg_fx_any_size = 0;         // 1: digit images for problems of any size
     // profiling of the streaming LSE launches
     bool prof_on = false;
     std::vector<hipEvent_t> ev_pool;   // pairs (start, stop)
@@ -211,6 +266,10 @@ struct Side {
     // BF16: uint16 [cnt_pad][kp], kp = round_up(d, 32), bias in bias_f[cnt_pad]
     uint16_t *pts_b = nullptr;
     float *bias_f = nullptr;
+    // F64 with digit images (16 < d <= 128): [cnt_pad / 32][fx_ks][4][1024] bytes, and the bias records
+    // [cnt_pad / 32][128] ints (see store_fx_record)
+    unsigned char *dig = nullptr;
+    int *brec = nullptr;
     double *norm = nullptr;   // [cnt_pad] squared norms of the derived points
     double *pot = nullptr;    // [cnt_pad] UNSHIFTED potential (f or g) in float64
 };
@@ -231,6 +290,7 @@ struct Prepared {
     bool dbg_precise_valu = false;   // LowD: the context's kernel switch (see Ctx::dbg_lowd_precise_valu)
     bool dbg_any_bias = false;       // LowD: see Ctx::dbg_lowd_any_bias
     int kp = 0;   // F64 / BF16: padded contraction length
+    int fx_ks = 0;   // F64: k-steps of the digit images, 0: none
     Side X, Y;
     // partial reductions of a streaming pass: [splits][max(n,m)_pad] records
     void *partial = nullptr;
@@ -238,11 +298,20 @@ struct Prepared {
     double *dev_part = nullptr;  // [ceil(max(n,m)/256)] per-block sums of the marginal deviation
     double *gauge_part = nullptr;   // [2][ceil(max(n,m)/256)] per-block sums of the plan's mass seen by a g-update
     double *gauge_part_x = nullptr; // the same for an f-update (averaged schedule: both passes measure, halves by parity)
-    double *scalars = nullptr;   // [16] device doubles (marginal errors, centring sums...; [8], [9]: gauge drift, see GaugeMode)
+    double *scalars = nullptr;   // [16] device doubles (marginal errors, centring sums...; [8], [9]: gauge drift, see GaugeMode; [10]: FxGate::r2)
     double *mean = nullptr;      // [kLowdMaxD] common mean (LowD)
     char *extra = nullptr;       // entry-point specific scratch (plan application partials)
     size_t extra_bytes = 0;
 };
+
+// the gate of a pass at `eps` (r2 sits in scalars[10])
+inline FxGate fx_gate(const Prepared *P, double eps)
+{
+    FxGate g;
+    g.r2 = P->fx_ks ? P->scalars + 10 : nullptr;
+    g.cscale = 2.0 * kLog2e * (1.0 / eps);   // (as store_fx_record forms it)
+    return g;
+}
 
 // ---------------------------------------------------------------------------------------
 // kernel launchers (implemented in the path-specific translation units)
@@ -279,7 +348,7 @@ fs_status launch_bias_from_user(Ctx *c, Prepared *P, Side *side, const float *po
 //   Measure: this merge is a g-update of an alternating solve: leave the block sums of c_j in gauge_part
 //   Collect: this merge is the f-update after one: its first workgroup adds eps_prev ln(sum gauge_part) to scalars[8]
 enum class GaugeMode { None, Measure, Collect };
-fs_status launch_finalize(Ctx *c, const Prepared *P, Side *res, const double *res_norm, int splits,
+fs_status launch_finalize(Ctx *c, const Prepared *P, Side *res, const double *res_norm, Splits splits,
                           double eps_cur, double eps_next_bias, float *user_out, double *abs_dev_sum,
                           double mix = 1.0, double *save_old = nullptr, GaugeMode gauge = GaugeMode::None,
                           int64_t gauge_prev_cnt = 0, double gauge_prev_eps = 0.0);
@@ -294,8 +363,8 @@ fs_status launch_gauge_export(Ctx *c, const Prepared *P, bool collect_last, doub
 // gauge_part_x / gauge_part, and, `collect_prev`, the first workgroup adds the previous iteration's term
 // eps (ln mass_g - ln mass_f) / 4 to scalars[8] and [9] from the other half; the caller hands out f - scalars[9],
 // g + scalars[8] (launch_gauge_collect_pair for the last iteration, then launch_gauge_export with collect_last = false).
-fs_status launch_finalize_pair(Ctx *c, const Prepared *P, Side *X, const double *norm_x, const void *partial_x, int splits_x,
-                               float *f_out, Side *Y, const double *norm_y, const void *partial_y, int splits_y,
+fs_status launch_finalize_pair(Ctx *c, const Prepared *P, Side *X, const double *norm_x, const void *partial_x, Splits splits_x,
+                               float *f_out, Side *Y, const double *norm_y, const void *partial_y, Splits splits_y,
                                float *g_out, double eps_cur, double eps_next_bias, double mix, int gauge_parity = -1,
                                bool collect_prev = false);
 fs_status launch_gauge_collect_pair(Ctx *c, const Prepared *P, double eps, int gauge_parity);
@@ -311,17 +380,18 @@ fs_status launch_pts_to_f32(Ctx *c, const void *pts, int dtype, int64_t rows, in
 fs_status launch_grad_assemble(Ctx *c, float *g, int64_t ldg, const void *pts, int dtype, int64_t ld, int64_t rows,
                                int64_t d, const float *w, const float *mass, int mode);
 fs_status launch_value_terms(Ctx *c, const Prepared *P, const Side *res, const double *res_norm, const Side *str,
-                             int splits, double eps, double *scratch, double *dst);
+                             Splits splits, double eps, double *scratch, double *dst);
 fs_status launch_row_norms(Ctx *c, const void *pts, int dtype, int64_t rows, int64_t d, int64_t ld,
                            float *out);
 fs_status launch_fill_f64(Ctx *c, double *dst, double v, int64_t cnt);
 fs_status launch_weight_stats(Ctx *c, const float *w, int64_t cnt, double *scratch, double *dst);
 fs_status launch_count_nonfinite(Ctx *c, const float *v, int64_t cnt, double *scratch, double *dst);
 // merge the splits of an application pass (partial (max,sum) + opart[split][row][PC]) and apply
-// the epilogue  out_i = w_i exp(pot_shifted_i/eps + m_i) O_i  for columns p0 .. p0+PC-1
-fs_status launch_apply_finalize(Ctx *c, const Prepared *P, const Side *res, const double *res_norm, int splits,
+// the epilogue  out_i = w_i exp(pot_shifted_i/eps + m_i) O_i  for columns p0 .. p0+PC-1 (PC_alt: row length of the
+// accumulators where the gate chose the other kernel)
+fs_status launch_apply_finalize(Ctx *c, const Prepared *P, const Side *res, const double *res_norm, Splits splits,
                                 double eps, const float *opart, int PC, int p0, int p, float *out, int64_t ldo,
-                                float *mass_out);
+                                float *mass_out, int PC_alt = 0);
 
 // fs_hvp.hip
 size_t hvp_scratch_bytes(int64_t n, int64_t m, int64_t d);
@@ -338,10 +408,10 @@ PassShape lowd_shape(const Ctx *c, int64_t n_res, int64_t n_str);
 // true: this half-step runs the low-d pass with float64 scores (norm), false: float (norm_f)
 bool lowd_precise(const Prepared *P, double eps);
 fs_status lowd_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps,
-                   int *splits_out);
+                   Splits *splits_out);
 // both half-steps of an averaged iteration (Eq. 4-5) in one launch; *done = false: not applicable
-fs_status lowd_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, void *partial_y, int *splits_x,
-                        int *splits_y, bool *done);
+fs_status lowd_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, void *partial_y, Splits *splits_x,
+                        Splits *splits_y, bool *done);
 size_t lowd_apply_ws(const Ctx *c, int64_t n_res, int64_t n_str, int64_t d, int64_t p);
 // had_A != nullptr: Hadamard-weighted transport (Alg. 5), every plan entry times <had_A row i, centred
 // streamed point j>; had_A is [res->cnt][lda] floats.
@@ -352,19 +422,26 @@ fs_status lowd_apply(Ctx *c, const Prepared *P, const Side *res, const Side *str
 // fs_f64.hip
 // (prof_kind: how the launch is booked by the profiling hooks, see Ctx::ev_kind)
 fs_status f64_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps,
-                  int *splits_out, int prof_kind = 0);
-fs_status f64_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, void *partial_y, int *splits_x,
-                       int *splits_y);
+                  Splits *splits_out, int prof_kind = 0);
+fs_status f64_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, void *partial_y, Splits *splits_x,
+                       Splits *splits_y);
 size_t f64_apply_ws(const Ctx *c, int64_t n_res, int64_t n_str, int64_t d, int64_t p);
 fs_status f64_apply(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps,
                     const float *V, int64_t p, int64_t ldv, float *out, int64_t ldo, float *mass_out,
                     const float *hadA = nullptr, int64_t lda = 0);
 
+// fs_fx.hip: the fixed-point kernels of a pass (P->fx_ks > 0); they leave at once where the gate is off
+fs_status fx_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, int *splits);
+fs_status fx_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, void *partial_y, int *splits_x, int *splits_y);
+size_t fx_apply_ws(const Ctx *c, int64_t n_res, int64_t n_str, int64_t d, int64_t p);
+fs_status fx_apply_pass(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, const float *V, int64_t p, int64_t ldv,
+                        int p0, const float *hadA, int64_t lda, int *splits, int *pc);
+
 // fs_bf16.hip
 fs_status bf16_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps,
-                   int *splits_out);
-fs_status bf16_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, void *partial_y, int *splits_x,
-                        int *splits_y);
+                   Splits *splits_out);
+fs_status bf16_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, void *partial_y, Splits *splits_x,
+                        Splits *splits_y);
 // plan application in bf16 mode (Alg. 2 / Alg. 4): workspace bytes and the pass itself
 size_t bf16_apply_ws(const Ctx *c, int64_t n_res, int64_t n_str);
 fs_status bf16_apply(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, const float *V, int64_t p,

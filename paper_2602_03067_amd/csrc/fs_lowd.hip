@@ -1046,7 +1046,7 @@ void launch_lse_split_pair(dim3 grid, hipStream_t st, const SplitArgs &a0, const
     default: { constexpr int KS_ = 9; CALL; } break;                                                         \
     }
 
-fs_status lowd_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, int *splits_out)
+fs_status lowd_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, Splits *splits_out)
 {
     // fp32-accuracy half-steps run on the bf16 matrix cores from the split records; float64-score
     // ones too when d <= 3 (precise records); other float64-score half-steps are handled further down
@@ -1093,8 +1093,8 @@ fs_status lowd_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, 
 // The f-pass (records to partial_x) and the g-pass (records to partial_y) of one iteration of the
 // averaged schedule (Eq. 4-5) in ONE launch.  *done = false (nothing launched) when the half-steps
 // of this problem do not run on the split-record kernels; the caller then runs them one by one.
-fs_status lowd_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, void *partial_y, int *splits_x,
-                        int *splits_y, bool *done)
+fs_status lowd_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, void *partial_y, Splits *splits_x,
+                        Splits *splits_y, bool *done)
 {
     *done = false;
     SplitArgs ax, ay;

@@ -2,6 +2,7 @@
 // clouds and their squared norms (Prop. 1: alpha, beta), the per-point bias
 // (Alg. 1, "precompute bias"), and the merge of the per-split LSE statistics into
 // the new shifted potential.
+#include "fs_finalize.h"
 #include "fs_internal.h"
 
 namespace fs {
@@ -21,18 +22,6 @@ __device__ inline uint16_t float_to_bf16(float v)
 __device__ inline float load_pt(const void *pts, int dtype, int64_t idx)
 {
     return dtype == FS_BF16 ? bf16_to_float(((const uint16_t *)pts)[idx]) : ((const float *)pts)[idx];
-}
-
-// block-wide sum of one double per thread (blockDim.x == 256); result valid in thread 0
-__device__ inline double block_sum_256(double v, double *sh)
-{
-    sh[threadIdx.x] = v;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-        __syncthreads();
-    }
-    return sh[0];
 }
 
 __global__ void k_fill_f64(double *dst, double v, int64_t cnt)
@@ -99,16 +88,6 @@ __global__ __launch_bounds__(256) void k_mean_final(const double *partX, const d
         mean[threadIdx.x] = t * inv_cnt;
     }
     if (threadIdx.x < 3) zeroed[threadIdx.x] = 0.0;
-}
-
-// piece d of a streamed-role split record: the bias in three bf16 pieces, then the three ones
-// that pick up the resident row's (negated) running max
-__device__ inline uint4 split_bias_piece(float bias)
-{
-    __bf16 b[3];
-    split3(bias, b);
-    const __bf16 one = (__bf16)1.0f;
-    return make_uint4(bf16_pair(b[0], b[1]), bf16_pair(b[2], one), bf16_pair(one, one), 0u);
 }
 
 // ---- low-d derived copies: coordinates centred at the common mean, packed with a bias slot;
@@ -190,34 +169,6 @@ __global__ __launch_bounds__(256) void k_prep_lowd(PrepLowdSide s0, PrepLowdSide
 //   1: Ba Bb Bc 1 1 1 0 0                bias digits on the grid gx gy, ones    x  1 1 1 m1 m2 m3
 //   2+k: ry1 ry2 ry3 Y1 Y1 Y1 ry1 ry2    residual pieces of coordinate k        x  X1 X1 X1 rx1 rx2 rx3 rx1 rx1
 //   5: rb1 rb2 rb3 0 0 ry1_0 ry1_1 ry1_2 bias residual, second-order terms      x  1 1 1 0 0 rx2_0 rx2_1 rx2_2
-// The three 8-bit digits of a bias on the grid q and what they leave.  Inside the digit range (|bias| < 2^21 q: the
-// launcher checks the biases it can foresee) every digit is exact in bf16 and the residual is bias - rint(bias/q) q.
-// Each digit is taken from what the ROUNDED digits before it leave, and the residual from all three as stored, so a
-// bias beyond the range (potentials that grew during a solve) still has pieces that sum to it to double precision:
-// the exact window of the first k-step is lost there and the score falls back to fp32-grade accuracy instead of
-// carrying a silently rounded digit.
-__device__ inline void split_precise_bias(double bias, double q, uint4 *digits, uint2 *residual)
-{
-    const __bf16 one = (__bf16)1.0f, z = (__bf16)0.0f;
-    if (!(fabs(bias) < INFINITY)) {   // padding and zero-weight points: -inf
-        *digits = make_uint4(bf16_pair((__bf16)(float)bias, z), bf16_pair(z, one), bf16_pair(one, one), 0u);
-        if (residual) *residual = make_uint2(0u, 0u);
-        return;
-    }
-    const double B = rint(bias / q);
-    const __bf16 da = (__bf16)(float)(rint(B * (1.0 / 65536.0)) * 65536.0 * q);
-    const double ra = B * q - (double)(float)da;
-    const __bf16 db = (__bf16)(float)(rint(ra / (256.0 * q)) * 256.0 * q);
-    const double rb = ra - (double)(float)db;
-    const __bf16 dc = (__bf16)(float)rb;
-    *digits = make_uint4(bf16_pair(da, db), bf16_pair(dc, one), bf16_pair(one, one), 0u);
-    if (residual) {
-        __bf16 r[3];
-        split3d(bias - ((double)(float)da + (double)(float)db + (double)(float)dc), r);
-        *residual = make_uint2(bf16_pair(r[0], r[1]), bf16_pair(r[2], z));
-    }
-}
-
 // `rho_max`: device scalar (largest squared norm after centring): the grid comes from it
 // (blockIdx.y: 0 = the x cloud, 1 = the y cloud)
 __global__ void k_prep_split_precise(const double *packed_d0, int64_t cnt_pad0, uint16_t *out0, const double *packed_d1,
@@ -318,47 +269,108 @@ __global__ void k_prep_bf16(const void *pts, int dtype, int64_t cnt, int64_t cnt
     }
 }
 
-// Where the bias of point i of a side lives, by path, and the squared norms that turn the
-// unshifted potential into the shifted one of Prop. 1 (fhat = f - alpha, ghat = g - beta).
-struct BiasSink {
-    float *packed;          // LowD float copy: packed[i*dp + d], shifted by norm_f
-    uint16_t *split;        // LowD split records (same value as the float copy), ks > 0
-    int ks;
-    uint16_t *split_p;      // LowD precise split records (d <= 3) and the grid of their bias digits:
-    double q;               // q itself, or (q == 0) the device scalar rho_max and the eps it is derived from
-    const double *rho_dev;
-    double q_eps;
-    double *packed_d;       // LowD double copy: packed_d[i*dpd + d], shifted by norm
-    int dp, dpd, d;
-    float *bias_f;          // BF16 path
-    double *bias_d;         // F64 path
-    const double *norm_f;
-    const double *norm;
-};
-
-// bias in base-2 units of a streamed point:  ((pot_shifted)/eps + log w) * log2(e)
-// (Alg. 1: (ghat_j + delta_j)/eps with delta = eps*log b)
-__device__ inline void store_bias(const BiasSink &s, int64_t i, double pot, double inv_eps, double lw)
+// ---- derived copies for 16 < d <= 128: the float64 records as above, and the digit images of the fixed-point
+//      kernels (layout and digits: fs_fx.hip) ----------------------------------------------------------
+// stage 1: largest |coordinate| of both clouds as bit patterns of non-negative floats (NaN and infinity order above
+// every finite value), block b of side y writes part[y][b]
+constexpr int kFxMaxBlocks = 128;
+__global__ __launch_bounds__(256) void k_coord_max(CloudIn c0, CloudIn c1, int dtype, int d, uint32_t *part)
 {
-    double b = ((pot - s.norm[i]) * inv_eps + lw) * kLog2e;
-    if (s.packed) {
-        const float bf = (float)(((pot - s.norm_f[i]) * inv_eps + lw) * kLog2e);
-        s.packed[i * s.dp + s.d] = bf;
-        if (s.split) reinterpret_cast<uint4 *>(s.split)[i * (2 * s.ks) + split_piece_pos(s.ks, i, s.d)] = split_bias_piece(bf);
-    }
-    if (s.packed_d) s.packed_d[i * s.dpd + s.d] = b;
-    if (s.split_p) {
-        double q = s.q;
-        if (!(q > 0.0)) {
-            double gx, gy;
-            split_grids(*s.rho_dev, s.q_eps, &gx, &gy);
-            q = gx * gy;
+    const CloudIn &cl = blockIdx.y ? c1 : c0;
+    __shared__ uint32_t sh[4];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    uint32_t mx = 0;
+    // eight rows in flight per wave: the loop is bound by the latency of its loads
+    const int64_t step = (int64_t)gridDim.x * 4;
+    for (int64_t i = (int64_t)blockIdx.x * 4 + wv; i < cl.rows; i += 8 * step)
+        for (int k = lane; k < d; k += 64) {
+            float v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = i + q * step < cl.rows ? load_pt(cl.pts, dtype, (i + q * step) * cl.ld + k) : 0.0f;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) mx = max(mx, __float_as_uint(fabsf(v[q])));
         }
-        uint4 *rec = reinterpret_cast<uint4 *>(s.split_p) + i * 6;
-        split_precise_bias(b, q, rec + 1, reinterpret_cast<uint2 *>(rec + 5));
+    for (int off = 32; off > 0; off >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, 64));
+    if (lane == 0) sh[wv] = mx;
+    __syncthreads();
+    if (threadIdx.x == 0) part[blockIdx.y * kFxMaxBlocks + blockIdx.x] = max(max(sh[0], sh[1]), max(sh[2], sh[3]));
+}
+
+// stage 2: block = tile of 32 points.  The common scale r2 is the smallest power of two whose 127.49 / 128 covers the
+// largest coordinate, so the first digit stays within 127; a float's 24 bits are then kept exactly down to 2^-7 r2.
+struct PrepFxSide {
+    const void *pts;
+    int64_t cnt, cnt_pad, ld;
+    double *out, *bias, *norm;
+    unsigned char *dig;
+    int *brec;
+};
+__global__ __launch_bounds__(256) void k_prep_fx(PrepFxSide s0, PrepFxSide s1, int dtype, int d, int kp, int ks, const uint32_t *part,
+                                                 double *r2_out)
+{
+    const PrepFxSide &sd = blockIdx.y ? s1 : s0;
+    const int64_t row0 = (int64_t)blockIdx.x * 32;
+    if (row0 >= sd.cnt_pad) return;
+    __shared__ float pt[32][32 * kFxMaxKs + 1];
+    __shared__ uint32_t shm[4];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    static_assert(2 * kFxMaxBlocks == 256, "one partial maximum per thread");
+    uint32_t mx = part[tid];
+    for (int off = 32; off > 0; off >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, 64));
+    if (lane == 0) shm[wv] = mx;
+    // a wave takes eight rows, two coordinates per lane and row, all loads in flight
+    float v[8][2];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+#pragma unroll
+        for (int z = 0; z < 2; ++z) {
+            const int64_t row = row0 + 8 * wv + q;
+            const int k = lane + 64 * z;
+            v[q][z] = (row < sd.cnt && k < d) ? load_pt(sd.pts, dtype, row * sd.ld + k) : 0.0f;
+        }
+    static_assert(32 * kFxMaxKs == 128, "two coordinates per lane");
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const int64_t row = row0 + 8 * wv + q;
+        double nrm = 0.0;
+#pragma unroll
+        for (int z = 0; z < 2; ++z) {
+            const int k = lane + 64 * z;
+            if (k < kp) {
+                pt[8 * wv + q][k] = v[q][z];
+                sd.out[row * kp + k] = (double)v[q][z];
+            }
+            nrm += (double)v[q][z] * (double)v[q][z];
+        }
+        for (int off = 32; off > 0; off >>= 1) nrm += __shfl_xor(nrm, off, 64);
+        if (lane == 0) {
+            sd.norm[row] = nrm;
+            sd.bias[row] = -INFINITY;
+        }
     }
-    if (s.bias_f) s.bias_f[i] = (float)b;
-    if (s.bias_d) s.bias_d[i] = b;
+    __syncthreads();
+    mx = max(max(shm[0], shm[1]), max(shm[2], shm[3]));
+    const float big = __uint_as_float(mx);
+    int ex = 0;
+    double r2 = 1.0;
+    if (!(big < INFINITY))
+        r2 = INFINITY;   // (the gate is off)
+    else if (big > 0.0f) {
+        (void)frexp((double)big * (128.0 / 127.49), &ex);
+        r2 = ldexp(1.0, ex);
+    }
+    if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) *r2_out = r2;
+    const double to_fixed = big < INFINITY ? ldexp(1.0, 31 - ex) : 0.0;
+    for (int e = tid; e < ks * 64; e += 256) {
+        const int q = e >> 6, l = e & 63;
+        const int k0 = 32 * q + 16 * (l >> 5);
+        uint4 o[4];
+        fx_digits16(&pt[l & 31][k0], to_fixed, o);
+#pragma unroll
+        for (int dg = 0; dg < 4; ++dg)
+            *reinterpret_cast<uint4 *>(sd.dig + ((((int64_t)blockIdx.x * ks + q) * 4 + dg) << 10) + l * 16) = o[dg];
+    }
+    if (tid < 128) sd.brec[(int64_t)blockIdx.x * 128 + tid] = tid >= 96 ? 1 : 0;   // flagged until biases come in
 }
 
 // ---- workspace potential (float64, unshifted) + bias from a user potential (float) -------
@@ -370,15 +382,16 @@ __global__ void k_bias_from_user(const float *pot_user, int64_t cnt, double inv_
                                  double log_uniform, double *pot, BiasSink sink, unsigned long long *absmax)
 {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    double mag_pot = 0.0, mag_w = 0.0;
+    double mag_pot = 0.0, mag_w = 0.0, b = 0.0;
     if (i < cnt) {
         double pu = (double)pot_user[i];
         pot[i] = pu;
         double lw = w ? log((double)w[i]) : log_uniform;
-        store_bias(sink, i, pu, inv_eps, lw);
+        b = store_bias(sink, i, pu, inv_eps, lw);
         mag_pot = fabs((pu - sink.norm[i]) * inv_eps) * kLog2e;
         mag_w = fabs(lw) < INFINITY ? fabs(lw) * kLog2e : 0.0;   // zero-weight points never contribute
     }
+    if (sink.brec) store_fx_record(sink, i, cnt, b, inv_eps);
     if (absmax) {   // one pair of atomics per workgroup (256 threads)
         __shared__ double shm[2][4];
         for (int off = 32; off > 0; off >>= 1) {
@@ -399,78 +412,6 @@ __global__ void k_bias_from_user(const float *pot_user, int64_t cnt, double inv_
     }
 }
 
-// Rescaling of a split's sums to the common maximum.  Every streaming kernel keeps integer-valued
-// running maxima (and -3e38 for "nothing seen"), so the factor 2^(m_k - M) is an exact ldexp.
-__device__ inline double rescale_split(double v, double mk, double M)
-{
-    const double dlt = mk - M;
-    return dlt >= -1100.0 ? ldexp(v, (int)dlt) : 0.0;   // also 0 for a NaN difference (-inf - -inf)
-}
-
-// ---- merge the per-split (max, sum) statistics of a streaming pass -----------------------
-//   LSE_2 = M + log2(sum_k s_k 2^(m_k - M)),  pot_new = -eps * ln2 * LSE_2      (Alg. 1, last lines)
-// and, as asked: store pot_new, the bias for the pass that streams this side next, the
-// unshifted potential for the caller, or the marginal deviation |w e^((pot_old-pot_new)/eps) - w|.
-struct FinalizeArgs {
-    const double2 *partial;
-    int64_t stride;
-    int splits;
-    int64_t cnt;
-    double eps, inv_eps_next;
-    const float *w;
-    double log_uniform;
-    const double *res_norm;
-    double *pot;
-    BiasSink sink;
-    float *user_out;
-    double *dev_part;
-    double mix;
-    double *save_old;
-    int blocks;   // workgroups of this side
-    // gauge drift (see GaugeMode): where a g-update leaves the block sums of the plan's column marginals, and what
-    // the first workgroup of the following f-update collects
-    double *gauge_out;
-    const double *gauge_prev;
-    int64_t gauge_prev_cnt;
-    double gauge_prev_eps;
-    double *gauge_scalars;   // [0]: the sum so far, [1]: the sum without its last term
-    const double *gauge_prev_x;   // averaged schedule: the f-pass's block sums of the previous iteration
-    int64_t gauge_prev_x_cnt;
-};
-
-// one workgroup: scalars[1] <- scalars[0], scalars[0] += eps ln(sum of part[0..cnt)), in a fixed order
-__device__ inline void gauge_collect(const double *part, int64_t cnt, double eps, double *scalars, double *sh)
-{
-    double acc = 0.0;
-    for (int64_t i = threadIdx.x; i < cnt; i += 256) acc += part[i];
-    const double t = block_sum_256(acc, sh);
-    if (threadIdx.x == 0) {
-        const double prev = scalars[0];
-        scalars[1] = prev;
-        scalars[0] = prev + ((t > 0.0 && t < INFINITY) ? eps * log(t) : 0.0);
-    }
-    __syncthreads();
-}
-
-// averaged schedule, one workgroup: scalars[0] = scalars[1] += eps (ln sum(part_y) - ln sum(part_x)) / 4
-__device__ inline void gauge_collect_pair(const double *part_x, int64_t cnt_x, const double *part_y, int64_t cnt_y, double eps,
-                                          double *scalars, double *sh)
-{
-    double ax = 0.0, ay = 0.0;
-    for (int64_t i = threadIdx.x; i < cnt_x; i += 256) ax += part_x[i];
-    for (int64_t i = threadIdx.x; i < cnt_y; i += 256) ay += part_y[i];
-    const double sx = block_sum_256(ax, sh);
-    __syncthreads();
-    const double sy = block_sum_256(ay, sh);
-    if (threadIdx.x == 0) {
-        const bool ok = sx > 0.0 && sx < INFINITY && sy > 0.0 && sy < INFINITY;
-        const double v = scalars[0] + (ok ? 0.25 * eps * (log(sy) - log(sx)) : 0.0);
-        scalars[0] = v;
-        scalars[1] = v;
-    }
-    __syncthreads();
-}
-
 __device__ __forceinline__ void finalize_body(const FinalizeArgs &a, const int bx)
 {
     // dev_part == nullptr: store the update.  dev_part != nullptr: measure the marginal deviation
@@ -484,41 +425,24 @@ __device__ __forceinline__ void finalize_body(const FinalizeArgs &a, const int b
             gauge_collect(a.gauge_prev, a.gauge_prev_cnt, a.gauge_prev_eps, a.gauge_scalars, sh);
     }
     const int64_t i = (int64_t)bx * 256 + threadIdx.x;
-    double dev = 0.0, mass = 0.0;
+    double dev = 0.0, mass = 0.0, bias = 0.0;
+    const int splits = a.splits_alt && !a.gate.on() ? a.splits_alt : a.splits;
     if (i < a.cnt) {
         double M = -INFINITY;
 #pragma unroll 8
-        for (int k = 0; k < a.splits; ++k) {
+        for (int k = 0; k < splits; ++k) {
             double mk = a.partial[(int64_t)k * a.stride + i].x;
             M = mk > M ? mk : M;
         }
         double S = 0.0;
 #pragma unroll 8
-        for (int k = 0; k < a.splits; ++k) {
+        for (int k = 0; k < splits; ++k) {
             double2 ms = a.partial[(int64_t)k * a.stride + i];
             S += rescale_split(ms.y, ms.x, M);
         }
-        // fhat = -eps * LSE (Alg. 1), f = fhat + alpha (Prop. 1)
-        double pot_new = -a.eps * kLn2 * (M + log2(S)) + a.res_norm[i];
-        const double pot_upd = pot_new;
-        if (a.mix != 1.0) pot_new = (1.0 - a.mix) * a.pot[i] + a.mix * pot_new;   // averaged schedule (Eq. 4-5)
-        if (a.dev_part) {
-            double wi = a.w ? (double)a.w[i] : exp(a.log_uniform);
-            dev = fabs(wi * exp((a.pot[i] - pot_new) / a.eps) - wi);   // Prop. 3: r = a exp((fhat - fhat+)/eps)
-        }
-        if (a.gauge_out) {
-            // Prop. 3: the plan's column (row) sum, from the UPDATE itself also where the stored potential is an average
-            const double wi = a.w ? (double)a.w[i] : exp(a.log_uniform);
-            mass = wi > 0.0 ? wi * exp((a.pot[i] - pot_upd) / a.eps) : 0.0;
-        }
-        if (!a.dev_part || a.save_old) {
-            if (a.save_old) a.save_old[i] = a.pot[i];
-            a.pot[i] = pot_new;
-            if (a.inv_eps_next > 0.0)
-                store_bias(a.sink, i, pot_new, a.inv_eps_next, a.w ? log((double)a.w[i]) : a.log_uniform);
-            if (a.user_out) a.user_out[i] = (float)pot_new;
-        }
+        finalize_point(a, i, M, S, &dev, &mass, &bias);
     }
+    if (a.sink.brec && a.inv_eps_next > 0.0 && (!a.dev_part || a.save_old)) store_fx_record(a.sink, i, a.cnt, bias, a.inv_eps_next);
     if (a.dev_part) {
         double t = block_sum_256(dev, sh);
         if (threadIdx.x == 0) a.dev_part[bx] = t;
@@ -599,13 +523,14 @@ __global__ __launch_bounds__(256) void k_sum_value_terms(const double *pr, int64
 // After an LSE pass over `res`: mass_i = w_i exp((pot_i - pot_i^+)/eps) is the row sum of the plan
 // that the CURRENT potentials induce (Prop. 3).  Block sums of mass_i, w_i pot_i and w_i go to
 // part[0][.], part[1][.], part[2][.] (part has 3 * gridDim.x doubles).
-__global__ __launch_bounds__(256) void k_value_terms(const double2 *partial, int64_t stride, int splits, int64_t cnt,
+__global__ __launch_bounds__(256) void k_value_terms(const double2 *partial, int64_t stride, int splits_n, int splits_alt, FxGate gate, int64_t cnt,
                                                      double eps, const float *w, double log_uniform,
                                                      const double *res_norm, const double *pot, double *part)
 {
     __shared__ double sh[256];
     int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     double t[3] = {0.0, 0.0, 0.0};
+    const int splits = splits_alt && !gate.on() ? splits_alt : splits_n;
     if (i < cnt) {
         double M = -INFINITY;
 #pragma unroll 8
@@ -686,15 +611,20 @@ __global__ __launch_bounds__(256) void k_weighted_sums(int64_t cnt, const float 
 // reads of the [splits][rows][PC] accumulators are contiguous; the row's max and factor are
 // computed once (by its thread c = 0) and shared.  (When PC does not divide 256 the last 256 % PC threads idle.)
 __global__ __launch_bounds__(256) void k_apply_finalize(const double2 *partial, int64_t stride, const float *opart,
-                                                        int64_t opart_stride, int PC, int splits, int64_t cnt,
+                                                        int64_t opart_stride, int PC_n, int PC_alt, int splits_n, int splits_alt,
+                                                        FxGate gate, int64_t cnt,
                                                         double inv_eps, const float *w, double log_uniform,
                                                         const double *pot, const double *res_norm, int p0, int p,
                                                         float *out, int64_t ldo, float *mass_out)
 {
     __shared__ double shM[256], shFac[256];
+    const bool alt = splits_alt && !gate.on();
+    const int PC = alt ? PC_alt : PC_n, splits = alt ? splits_alt : splits_n;
     const int rows_per_block = 256 / PC;
     const int rl = threadIdx.x / PC, c = threadIdx.x - rl * PC;
-    const int64_t i = rl < rows_per_block ? (int64_t)blockIdx.x * rows_per_block + rl : cnt;   // (idle threads: no row)
+    // (the grid fits PC_n; where the other kernel has longer rows, a block takes several groups of rows)
+    for (int64_t base = (int64_t)blockIdx.x * rows_per_block; base < cnt; base += (int64_t)gridDim.x * rows_per_block) {
+    const int64_t i = rl < rows_per_block ? base + rl : cnt;   // (idle threads: no row)
     if (c == 0 && i < cnt) {
         double M = -INFINITY;
 #pragma unroll 8
@@ -718,7 +648,7 @@ __global__ __launch_bounds__(256) void k_apply_finalize(const double2 *partial, 
         }
     }
     __syncthreads();
-    if (i >= cnt || p0 + c >= p) return;
+    if (i < cnt && p0 + c < p) {
     const double M = shM[rl];
     double acc = 0.0;
 #pragma unroll 4
@@ -727,6 +657,9 @@ __global__ __launch_bounds__(256) void k_apply_finalize(const double2 *partial, 
         acc += rescale_split((double)opart[((int64_t)k * opart_stride + i) * PC + c], mk, M);
     }
     out[i * ldo + p0 + c] = (float)(shFac[rl] * acc);
+    }
+    __syncthreads();
+    }
 }
 
 // `eps`: the eps of the pass that will stream these biases
@@ -758,6 +691,8 @@ BiasSink sink_of(const Prepared *P, const Side *s, double eps, bool rho_on_devic
     k.d = (int)P->d;
     k.bias_f = s->bias_f;
     k.bias_d = s->bias_d;
+    k.brec = s->brec;
+    k.r2 = P->scalars + 10;
     k.norm_f = s->norm_f;
     k.norm = s->norm;
     return k;
@@ -765,13 +700,13 @@ BiasSink sink_of(const Prepared *P, const Side *s, double eps, bool rho_on_devic
 
 }  // namespace
 
-fs_status launch_apply_finalize(Ctx *c, const Prepared *P, const Side *res, const double *res_norm, int splits,
+fs_status launch_apply_finalize(Ctx *c, const Prepared *P, const Side *res, const double *res_norm, Splits splits,
                                 double eps, const float *opart, int PC, int p0, int p, float *out, int64_t ldo,
-                                float *mass_out)
+                                float *mass_out, int PC_alt)
 {
-    if (PC < 1 || PC > 256) return fail(c, FS_ERR_DEVICE, "internal: accumulator width of the application merge");
+    if (PC < 1 || PC > 256 || (splits.alt && (PC_alt < 1 || PC_alt > 256))) return fail(c, FS_ERR_DEVICE, "internal: accumulator width of the application merge");
     hipLaunchKernelGGL(k_apply_finalize, dim3((unsigned)ceil_div(res->cnt, 256 / PC)), dim3(256), 0, c->stream,
-                       (const double2 *)P->partial, res->cnt_pad, opart, res->cnt_pad, PC, splits, res->cnt, 1.0 / eps,
+                       (const double2 *)P->partial, res->cnt_pad, opart, res->cnt_pad, PC, PC_alt, splits.n, splits.alt, fx_gate(P, eps), res->cnt, 1.0 / eps,
                        res->w, res->log_uniform, res->pot, res_norm, p0, p, out, ldo, mass_out);
     FS_HIP(c, hipGetLastError());
     return FS_OK;
@@ -944,6 +879,18 @@ fs_status launch_prepare(Ctx *c, const fs_problem *p, Prepared *P)
                                P->X.packed_d, P->X.cnt_pad, P->X.split_p, P->Y.packed_d, P->Y.cnt_pad, P->Y.split_p, (int)p->d,
                                P->dpd, P->scalars + 7);
         FS_HIP(c, hipGetLastError());
+    } else if (P->path == Path::F64 && P->fx_ks) {
+        uint32_t *part = reinterpret_cast<uint32_t *>(P->mean);
+        const CloudIn cx{p->x, p->n, p->ldx, nullptr}, cy{p->y, p->m, p->ldy, nullptr};
+        hipLaunchKernelGGL(k_coord_max, dim3(kFxMaxBlocks, 2), dim3(256), 0, c->stream, cx, cy, dtype, (int)p->d, part);
+        PrepFxSide sd[2];
+        for (int k = 0; k < 2; ++k) {
+            const Side *S = in[k].S;
+            sd[k] = PrepFxSide{in[k].pts, S->cnt, S->cnt_pad, in[k].ld, S->pts_d, S->bias_d, S->norm, S->dig, S->brec};
+        }
+        const int64_t pad_max = P->X.cnt_pad > P->Y.cnt_pad ? P->X.cnt_pad : P->Y.cnt_pad;
+        hipLaunchKernelGGL(k_prep_fx, dim3((unsigned)(pad_max / 32), 2), dim3(256), 0, c->stream, sd[0], sd[1], dtype, (int)p->d, P->kp,
+                           P->fx_ks, part, P->scalars + 10);
     } else if (P->path == Path::F64) {
         for (auto &s : in)
             hipLaunchKernelGGL(k_prep_f64, dim3((unsigned)ceil_div(s.S->cnt_pad, 4)), dim3(256), 0, c->stream, s.pts,
@@ -986,14 +933,16 @@ fs_status launch_bias_from_user(Ctx *c, Prepared *P, Side *side, const float *po
     return FS_OK;
 }
 
-static FinalizeArgs finalize_args(const Prepared *P, const void *partial, Side *res, const double *res_norm, int splits,
+static FinalizeArgs finalize_args(const Prepared *P, const void *partial, Side *res, const double *res_norm, Splits splits,
                                   double eps_cur, double eps_next_bias, float *user_out, double *dev_part, double mix,
                                   double *save_old)
 {
     FinalizeArgs a{};
     a.partial = (const double2 *)partial;
     a.stride = res->cnt_pad;
-    a.splits = splits;
+    a.splits = splits.n;
+    a.splits_alt = splits.alt;
+    a.gate = fx_gate(P, eps_cur);
     a.cnt = res->cnt;
     a.eps = eps_cur;
     a.inv_eps_next = eps_next_bias > 0.0 ? 1.0 / eps_next_bias : 0.0;
@@ -1022,7 +971,7 @@ fs_status launch_gauge_export(Ctx *c, const Prepared *P, bool collect_last, doub
     return FS_OK;
 }
 
-fs_status launch_finalize(Ctx *c, const Prepared *P, Side *res, const double *res_norm, int splits, double eps_cur,
+fs_status launch_finalize(Ctx *c, const Prepared *P, Side *res, const double *res_norm, Splits splits, double eps_cur,
                           double eps_next_bias, float *user_out, double *abs_dev_sum, double mix, double *save_old,
                           GaugeMode gauge, int64_t gauge_prev_cnt, double gauge_prev_eps)
 {
@@ -1044,8 +993,8 @@ fs_status launch_finalize(Ctx *c, const Prepared *P, Side *res, const double *re
 }
 
 // merges of the f-pass (records in partial_x) and of the g-pass (partial_y) in one launch
-fs_status launch_finalize_pair(Ctx *c, const Prepared *P, Side *X, const double *norm_x, const void *partial_x, int splits_x,
-                               float *f_out, Side *Y, const double *norm_y, const void *partial_y, int splits_y,
+fs_status launch_finalize_pair(Ctx *c, const Prepared *P, Side *X, const double *norm_x, const void *partial_x, Splits splits_x,
+                               float *f_out, Side *Y, const double *norm_y, const void *partial_y, Splits splits_y,
                                float *g_out, double eps_cur, double eps_next_bias, double mix, int gauge_parity, bool collect_prev)
 {
     FinalizeArgs ax = finalize_args(P, partial_x, X, norm_x, splits_x, eps_cur, eps_next_bias, f_out, nullptr, mix, nullptr);
@@ -1107,12 +1056,12 @@ fs_status launch_weight_stats(Ctx *c, const float *w, int64_t cnt, double *scrat
 // dst[0..4] <- sum_i mass_i, <w_res, pot_res>, sum w_res, <w_str, pot_str>, sum w_str  (see k_value_terms);
 // `scratch` holds 3 * blocks(res) + 2 * blocks(str) doubles
 fs_status launch_value_terms(Ctx *c, const Prepared *P, const Side *res, const double *res_norm, const Side *str,
-                             int splits, double eps, double *scratch, double *dst)
+                             Splits splits, double eps, double *scratch, double *dst)
 {
     const unsigned br = (unsigned)ceil_div(res->cnt, 256), bs = (unsigned)ceil_div(str->cnt, 256);
     double *pr = scratch, *ps = scratch + 3 * (size_t)br;
-    hipLaunchKernelGGL(k_value_terms, dim3(br), dim3(256), 0, c->stream, (const double2 *)P->partial, res->cnt_pad, splits,
-                       res->cnt, eps, res->w, res->log_uniform, res_norm, res->pot, pr);
+    hipLaunchKernelGGL(k_value_terms, dim3(br), dim3(256), 0, c->stream, (const double2 *)P->partial, res->cnt_pad, splits.n,
+                       splits.alt, fx_gate(P, eps), res->cnt, eps, res->w, res->log_uniform, res_norm, res->pot, pr);
     hipLaunchKernelGGL(k_weighted_sums, dim3(bs), dim3(256), 0, c->stream, str->cnt, str->w, str->log_uniform, str->pot, ps);
     hipLaunchKernelGGL(k_sum_value_terms, dim3(5), dim3(256), 0, c->stream, pr, (int64_t)br, ps, (int64_t)bs, dst);
     FS_HIP(c, hipGetLastError());

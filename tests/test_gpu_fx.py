@@ -1,0 +1,148 @@
+"""GPU parity of the fixed-point kernels (16 < d <= 128, fp32 accuracy) against the float64 oracle, at the sizes where
+they can go wrong: edges of their tiles (32 points, 128 resident rows) and k-steps (32 coordinates), both sides of the
+gate that chooses between them and the fp64 kernels, tiles that take the float64 epilogue (padding, zero weights,
+potentials far away), and values that are not finite.
+
+Tolerances: potentials to 1e-6 eps (scores are exact to 2^-23 base-2 units, sums to a few 1e-8) plus the rounding of a
+float output, 2^-24 |f|; applications to 1e-6 of the largest value (float values in three bf16 pieces, sums of 16
+products in fp32: a few 1e-7)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_03067_amd import binding
+from tests._gpu_common import dev, host, make_problem, say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = binding.Context(0)
+    c.fs_debug_set("fx_any_size", 1)   # the library itself takes small problems to the fp64 kernels
+    yield c
+    c.close()
+
+
+def _problem(seed, n, m, d, scale=1.0):
+    rng = np.random.default_rng(seed)
+    x = (rng.random((n, d)) * scale).astype(np.float32)
+    y = ((rng.random((m, d)) * 0.9 + 0.1) * scale).astype(np.float32)
+    a = rng.random(n) + 0.1
+    b = rng.random(m) + 0.1
+    return rng, x, y, (a / a.sum()).astype(np.float32), (b / b.sum()).astype(np.float32)
+
+
+def _check_pot(got, want, eps):
+    assert np.all(np.abs(host(got) - want) <= 1e-6 * eps + 2.0 ** -24 * np.abs(want) * 1.01)
+
+
+def _check_values(got, want):
+    assert np.abs(host(got) - want).max() <= 1e-6 * max(np.abs(want).max(), 1e-300)
+
+
+# (n, m, d): tile and row-block edges, k-step edges, the last dimension of the path and the first beyond it
+SHAPES = [(1, 1, 17), (31, 33, 32), (32, 64, 33), (33, 31, 64), (127, 129, 65), (128, 96, 96), (129, 1, 97), (257, 300, 128), (65, 200, 129)]
+
+
+@pytest.mark.parametrize("n,m,d", SHAPES)
+@pytest.mark.parametrize("eps", [0.02, 0.5, 30.0])   # thirteen products, ten (at most), the gate's lower end for unit-cube data
+def test_updates_and_applications(ctx, oracle, n, m, d, eps):
+    eps = float(np.float32(eps))
+    rng, x, y, a, b = _problem(n + 7 * m + d, n, m, d)
+    prob = make_problem(x, y, a, b)
+    say("fx n=%d m=%d d=%d eps=%g" % (n, m, d, eps))
+    g = (rng.standard_normal(m) * eps).astype(np.float32)
+    f = oracle.update_f(x, y, b, eps, g).astype(np.float32)
+    _check_pot(ctx.fs_update_f(prob, eps, dev(g)), oracle.update_f(x, y, b, eps, g), eps)
+    _check_pot(ctx.fs_update_g(prob, eps, dev(f)), oracle.update_g(x, y, a, eps, f), eps)
+    for p in (1, 4, 5, 33, 97):
+        V = rng.standard_normal((m, p)).astype(np.float32)
+        U = rng.standard_normal((n, p)).astype(np.float32)
+        _check_values(ctx.fs_apply_plan(prob, eps, dev(f), dev(g), dev(V)), oracle.apply_plan(x, y, a, b, eps, f, g, V))
+        _check_values(ctx.fs_apply_plan_T(prob, eps, dev(f), dev(g), dev(U)), oracle.apply_plan_T(x, y, a, b, eps, f, g, U))
+
+
+@pytest.mark.parametrize("scale,eps", [(1e-3, 1.0), (1.0, 0.3), (60.0, 0.3), (300.0, 0.3), (1e-30, 1e-6)])
+def test_both_sides_of_the_gate(ctx, oracle, scale, eps):
+    """scale^2 / eps from far below to far above the window of the fixed-point scores."""
+    eps = float(np.float32(eps))
+    n, m, d = 150, 190, 40
+    rng, x, y, a, b = _problem(3, n, m, d, scale)
+    prob = make_problem(x, y, a, b)
+    say("fx gate scale=%g eps=%g" % (scale, eps))
+    g = (rng.standard_normal(m) * eps).astype(np.float32)
+    want = oracle.update_f(x, y, b, eps, g)
+    _check_pot(ctx.fs_update_f(prob, eps, dev(g)), want, eps)
+    f = want.astype(np.float32)
+    V = rng.standard_normal((m, 3)).astype(np.float32)
+    _check_values(ctx.fs_apply_plan(prob, eps, dev(f), dev(g), dev(V)), oracle.apply_plan(x, y, a, b, eps, f, g, V))
+
+
+@pytest.mark.parametrize("offset", [0.0, 3e3, -3e3, 1e8])
+def test_far_potentials_and_zero_weights(ctx, oracle, offset):
+    """Biases beyond the records (a whole side, or single points of it) and points that never contribute."""
+    eps = float(np.float32(0.3))
+    n, m, d = 100, 400, 48
+    rng, x, y, a, b = _problem(11, n, m, d)
+    b[5] = b[200:264] = 0.0
+    prob = make_problem(x, y, a, b)
+    say("fx far potentials offset=%g" % offset)
+    g = (rng.standard_normal(m) * eps).astype(np.float32)
+    g[300:] += np.float32(offset)
+    _check_pot(ctx.fs_update_f(prob, eps, dev(g)), oracle.update_f(x, y, b, eps, g), eps)
+    g = (g + np.float32(offset)).astype(np.float32)
+    f = oracle.update_f(x, y, b, eps, g).astype(np.float32)
+    _check_pot(ctx.fs_update_f(prob, eps, dev(g)), oracle.update_f(x, y, b, eps, g), eps)
+    if offset < 1e6:   # (an offset of 1e8 leaves nothing of a float potential's difference)
+        V = rng.standard_normal((m, 2)).astype(np.float32)
+        _check_values(ctx.fs_apply_plan(prob, eps, dev(f), dev(g), dev(V)), oracle.apply_plan(x, y, a, b, eps, f, g, V))
+        V = rng.standard_normal((m, 40)).astype(np.float32)
+        _check_values(ctx.fs_apply_plan(prob, eps, dev(f), dev(g), dev(V)), oracle.apply_plan(x, y, a, b, eps, f, g, V))
+
+
+def test_values_that_are_not_finite(ctx):
+    """A column with an infinite or NaN value is infinite or NaN in every row it reaches, its neighbours are untouched."""
+    eps = float(np.float32(1.0))
+    n, m, d = 70, 90, 33
+    rng, x, y, a, b = _problem(5, n, m, d)
+    prob = make_problem(x, y, a, b)
+    f, g = torch.zeros(n, device="cuda:0"), torch.zeros(m, device="cuda:0")
+    say("fx values that are not finite")
+    for p in (3, 40):
+        V = rng.standard_normal((m, p)).astype(np.float32)
+        clean = host(ctx.fs_apply_plan(prob, eps, f, g, dev(V)))
+        V[m - 1, 0], V[40, 1], V[3, 2] = np.inf, -np.inf, np.nan
+        out = host(ctx.fs_apply_plan(prob, eps, f, g, dev(V)))
+        assert np.all(out[:, 0] == np.inf) and np.all(out[:, 1] == -np.inf) and np.all(np.isnan(out[:, 2]))
+        assert np.array_equal(out[:, 3:], clean[:, 3:])
+    # a point that is not finite turns the gate off: the fp64 kernels propagate it
+    x[7, 2] = np.nan
+    fu = host(ctx.fs_update_f(make_problem(x, y, a, b), eps, g))
+    assert np.isnan(fu[7]) and np.isfinite(np.delete(fu, 7)).all()
+
+
+@pytest.mark.parametrize("n,m,d", [(40, 70, 24), (130, 97, 64), (33, 129, 128)])
+def test_hadamard_weights(ctx, n, m, d):
+    """Rows of A of very different sizes, a zero row, columns beyond one block of 32."""
+    eps = float(np.float32(0.5))
+    rng, x, y, a, b = _problem(9, n, m, d)
+    prob = make_problem(x, y, a, b)
+    say("fx hadamard n=%d m=%d d=%d" % (n, m, d))
+    A = (rng.standard_normal((n, d)) * np.exp(rng.uniform(-8, 8, (n, 1)))).astype(np.float32)
+    A[1] = 0.0
+    g = np.zeros(m, dtype=np.float32)
+    f = host(ctx.fs_update_f(prob, eps, dev(g))).astype(np.float32)
+    X, Y = x.astype(np.float64), y.astype(np.float64)
+    C = ((X[:, None, :] - Y[None, :, :]) ** 2).sum(2)
+    e = np.float64(eps)
+    P = a[:, None].astype(np.float64) * b[None, :].astype(np.float64) * np.exp((f[:, None].astype(np.float64) + g[None, :] - C) / e)
+    W = P * (A.astype(np.float64) @ Y.T)
+    for p in (2, 70):
+        V = rng.standard_normal((m, p)).astype(np.float32)
+        got = host(ctx.fs_apply_plan_hadamard(prob, eps, dev(f), dev(g), dev(A), dev(V)))
+        want = W @ V.astype(np.float64)
+        # per row: the weights of a row share its scale
+        scale = np.abs(W).sum(1, keepdims=True) * np.abs(V).max() + 1e-300
+        assert (np.abs(got - want) / scale).max() <= 1e-6
+        assert np.all(got[1] == 0.0)
