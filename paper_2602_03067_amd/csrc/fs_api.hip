@@ -328,7 +328,7 @@ fs_status apply_begin(Ctx *c, const fs_problem *prob, float eps, const float *f,
     switch (choose_path(prob)) {
     case Path::LowD: extra = lowd_apply_ws(c, n_res, n_str, prob->d, p); break;
     case Path::F64: extra = f64_apply_ws(c, n_res, n_str, prob->d, p); break;   // (covers both kernels of a pass)
-    case Path::BF16: extra = bf16_apply_ws(c, n_res, n_str); break;
+    case Path::BF16: extra = bf16_apply_ws(c, n_res, n_str, prob->d, p); break;
     }
     extra = (extra + 255) & ~size_t(255);
     if ((st = prepare(c, prob, P, extra + tail_bytes, &P->extra)) != FS_OK) return st;

@@ -89,7 +89,24 @@ struct BfArgs {
     // plan application only
     const unsigned char *vimg;   // [n_itiles] value images (see k_vimg_bf16)
     float *opart;                // [splits][partial_stride][PC]
+    // plan slab (see Epi)
+    const float *rowmax;         // Plan: [resident rows] the fixed, integer-valued stabiliser of each row
+    unsigned char *eslab;        // Plan: E of this slab's resident rows, tiled like the point copies with the streamed points as coordinates
+    int e_chunks;                // Plan: chunks of 32 streamed points per row group of the slab; Product: chunks of both operands
+    int ch_per_split;            // Product: chunks of a split of the contraction
+    int row_off;                 // Plan: first row of the slab
+    int out_rows;                // Product: rows of the slab, opart is [splits][out_rows][opart_ld]
+    int64_t opart_ld;
 };
+
+// What a tile's 256 x 256 contraction is used for:
+//   Lse      running (max, sum) of every resident row
+//   Plan     the exponentials themselves, exp2(score - rowmax), rounded to bf16 and stored as the left operand of a second
+//            product, with their row sums.  No running max: bf16 has the exponent range of a float, and the plan's entries
+//            are what the caller's potentials say they are.
+//   Product  the second product out[row][c] = sum_i E[row][i] V[i][c]: the same contraction over the stored exponentials
+//            (streamed role: rows) and the transposed values (resident role: columns), its accumulators stored as they are
+enum class Epi { Lse, Plan, Product };
 
 // Workgroup shapes (WJ = waves along the resident side, each owning 128 resident rows; four waves
 // along the streamed side, each owning 64 of the tile's 256 streamed points):
@@ -131,7 +148,7 @@ struct BfArgs {
 constexpr int kVRow = 520;                       // bytes per value column in the LDS image (256 points + pad)
 constexpr int kVImgBytes(int pc) { return (pc * kVRow + 1023) / 1024 * 1024; }
 
-template <int WJ, int NS, int JTW, int PC, bool HALF = false>
+template <int WJ, int NS, int JTW, int PC, bool HALF = false, Epi EPI = Epi::Lse>
 __device__ __forceinline__ void lse_bf16_body(const BfArgs &a, const int block)
 {
     constexpr bool APPLY = PC > 0;
@@ -187,10 +204,15 @@ __device__ __forceinline__ void lse_bf16_body(const BfArgs &a, const int block)
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
     const int wi = w & 3, wj = w >> 2;
     const int lh = l >> 5, lr = l & 31;
-    const int n_chunks = a.kp / KC;
-    const int64_t row0 = (int64_t)jtile * BJ;
-    const int t_begin = split * a.tiles_per_split;
-    const int t_end = min(a.n_itiles, t_begin + a.tiles_per_split);
+    constexpr bool PRODUCT = EPI == Epi::Product;
+    // Product: one tile per workgroup, `split` counts (row tile, split of the contraction)
+    const int ksplit = PRODUCT ? split / a.n_itiles : 0;
+    const int ch0 = PRODUCT ? ksplit * a.ch_per_split : 0;
+    const int all_chunks = PRODUCT ? a.e_chunks : a.kp / KC;                     // chunks of a row group in memory
+    const int n_chunks = PRODUCT ? min(a.ch_per_split, all_chunks - ch0) : all_chunks;
+    const int64_t row0 = (int64_t)jtile * BJ + (EPI == Epi::Plan ? a.row_off : 0);
+    const int t_begin = PRODUCT ? split % a.n_itiles : split * a.tiles_per_split;
+    const int t_end = PRODUCT ? t_begin + 1 : min(a.n_itiles, t_begin + a.tiles_per_split);
     const int G = (t_end - t_begin) * n_chunks;   // pipeline stages of this workgroup
 
     const unsigned ring_off = (unsigned)(size_t)ring;
@@ -203,7 +225,7 @@ __device__ __forceinline__ void lse_bf16_body(const BfArgs &a, const int block)
     // 0..15 streamed rows, then the resident rows), so a wave's loads of a stage, and of the next, walk
     // through memory linearly.
     const unsigned char *res_tiles = reinterpret_cast<const unsigned char *>(a.res) +
-                                     (((int64_t)(row0 >> 8) * n_chunks * 16 + ((row0 >> 4) & 15)) << 10);
+                                     ((((int64_t)(row0 >> 8) * all_chunks + ch0) * 16 + ((row0 >> 4) & 15)) << 10);
     const unsigned char *str_tiles = reinterpret_cast<const unsigned char *>(a.str);
     const unsigned l16 = l * 16, l4 = l * 4;
 
@@ -212,12 +234,12 @@ __device__ __forceinline__ void lse_bf16_body(const BfArgs &a, const int block)
     // streamed group and / or one of the resident group; with the first stage of a tile also the wave's quarter of the
     // tile's biases (with two waves per streamed quarter both write the same 256 bytes: harmless).
     auto issue_stage = [&]() {
-        if (pch == 0) dma4s(a.bias + (int64_t)pt * BI + wi * 64, l4, bias_off + ((pt - t_begin) & (NBIAS - 1)) * (BI * 4) + wi * 256);
+        if (!PRODUCT && pch == 0) dma4s(a.bias + (int64_t)pt * BI + wi * 64, l4, bias_off + ((pt - t_begin) & (NBIAS - 1)) * (BI * 4) + wi * 256);
         const int s0 = w * PPW;
         const int n_str = s0 >= 16 ? 0 : (16 - s0 < PPW ? 16 - s0 : PPW);
         const unsigned lds = ring_off + (pg % NS) * STAGE_BYTES;
         if (n_str > 0)
-            dma16_run_n(n_str, str_tiles + ((((int64_t)pt * n_chunks + pch) * 16 + s0) << 10), l16, lds + s0 * 1024);
+            dma16_run_n(n_str, str_tiles + ((((int64_t)pt * all_chunks + ch0 + pch) * 16 + s0) << 10), l16, lds + s0 * 1024);
         if (n_str < PPW)
             dma16_run_n(PPW - n_str, res_tiles + (((int64_t)pch * 16 + (s0 + n_str - 16)) << 10), l16, lds + (s0 + n_str) * 1024);
         ++pg;
@@ -231,8 +253,9 @@ __device__ __forceinline__ void lse_bf16_body(const BfArgs &a, const int block)
     f16v O[APPLY ? JTW : 1][NCB];
 #pragma unroll
     for (int jt = 0; jt < JTW; ++jt) {
-        mrun[jt] = kNegInit;
+        mrun[jt] = EPI == Epi::Plan ? a.rowmax[row0 + 32 * JTW * wj + 32 * jt + lr] : kNegInit;
         srun[jt] = 0.0f;
+        if constexpr (EPI == Epi::Plan) asm volatile("" : "+v"(mrun[jt]));   // (loaded before the ring's loads start)
     }
     if constexpr (APPLY) {
 #pragma unroll
@@ -318,25 +341,19 @@ __device__ __forceinline__ void lse_bf16_body(const BfArgs &a, const int block)
 #define FS_MFMA1(IT, JT) acc[IT][JT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1[IT], b1[JT], acc[IT][JT], 0, 0, 0)
                 // (only F0(g) is pending here, so the wait the compiler puts before the first MFMA is
                 // exactly "F0 has arrived"; F1 is requested behind the first MFMA group)
-                FS_MFMA0(0, 0);
-                FS_MFMA0(0, 1);
-                FS_MFMA0(0, 2);
-                FS_MFMA0(0, 3);
+#pragma unroll
+                for (int jt = 0; jt < JTW; ++jt) FS_MFMA0(0, jt);
                 __builtin_amdgcn_sched_barrier(0);
                 if constexpr (!skip_second) read_frags(a1, b1, g, pk1);
                 if (g + D < G) issue_stage();
                 __builtin_amdgcn_sched_barrier(0);
-                FS_MFMA0(1, 0);
-                FS_MFMA0(1, 1);
-                FS_MFMA0(1, 2);
-                FS_MFMA0(1, 3);
+#pragma unroll
+                for (int jt = 0; jt < JTW; ++jt) FS_MFMA0(1, jt);
                 // (the second 16 coordinates of a tile's last chunk are zero padding when d ends in its first half:
                 // 784 = 49 x 16 saves 2 % of the MFMAs this way)
                 if constexpr (!skip_second) {
-                    FS_MFMA1(0, 0);
-                    FS_MFMA1(0, 1);
-                    FS_MFMA1(0, 2);
-                    FS_MFMA1(0, 3);
+#pragma unroll
+                    for (int jt = 0; jt < JTW; ++jt) FS_MFMA1(0, jt);
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 if (g + 1 < G) {
@@ -346,10 +363,8 @@ __device__ __forceinline__ void lse_bf16_body(const BfArgs &a, const int block)
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 if constexpr (!skip_second) {
-                    FS_MFMA1(1, 0);
-                    FS_MFMA1(1, 1);
-                    FS_MFMA1(1, 2);
-                    FS_MFMA1(1, 3);
+#pragma unroll
+                    for (int jt = 0; jt < JTW; ++jt) FS_MFMA1(1, jt);
                 }
 #undef FS_MFMA0
 #undef FS_MFMA1
@@ -412,6 +427,21 @@ __device__ __forceinline__ void lse_bf16_body(const BfArgs &a, const int block)
         // ---- epilogue: fold 2 x 16 streamed points per resident row into (max, sum) ----------
         // lazy stabiliser: exponents against the current integer running max; the slow branch
         // (lift the max, rescale by an exact power of two) runs only when a sum leaves [0, 2^60)
+        if constexpr (PRODUCT) {
+            // accumulator register r of block it: row 64 wi + 32 it + 8 (r / 4) + 4 lh + r % 4 of the tile; lane: column
+#pragma unroll
+            for (int jt = 0; jt < JTW; ++jt) {
+                const int64_t c = row0 + 32 * JTW * wj + 32 * jt + lr;
+#pragma unroll
+                for (int it = 0; it < 2; ++it)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const int64_t row = (int64_t)t * BI + 64 * wi + 32 * it + 8 * (r >> 2) + 4 * lh + (r & 3);
+                        a.opart[((int64_t)ksplit * a.out_rows + row) * a.opart_ld + c] = acc[it][jt][r];
+                    }
+            }
+            continue;
+        }
         const int bslot = (t - t_begin) & (NBIAS - 1);   // the first stage of this tile carried its biases
         float bias[2][16];
 #pragma unroll
@@ -424,7 +454,41 @@ __device__ __forceinline__ void lse_bf16_body(const BfArgs &a, const int block)
                 bias[it][4 * g4 + 2] = bv.z;
                 bias[it][4 * g4 + 3] = bv.w;
             }
-        if constexpr (!APPLY) {
+        if constexpr (EPI == Epi::Plan) {
+            // A lane half holds streamed points 8 g4 + 4 lh .. + 3 of resident row rl, half a 16-byte piece of the slab's
+            // tile.  Swapping the upper lanes of an even g4 with the lower ones of the next gives every lane a whole
+            // piece: g4 in the lower half, g4 + 1 in the upper one.
+#pragma unroll
+            for (int jt = 0; jt < JTW; ++jt) {
+                const int rl = 32 * JTW * wj + 32 * jt + lr;
+                const int64_t group = (row0 - a.row_off + rl) >> 8, rb = (row0 + rl) >> 4 & 15;
+                float part = 0.0f;
+#pragma unroll
+                for (int it = 0; it < 2; ++it) {
+                    unsigned char *dst = a.eslab + (((group * a.e_chunks + t * (BI / KC) + 2 * wi + it) * 16 + rb) << 10) + (rl & 15) * 64;
+#pragma unroll
+                    for (int g2 = 0; g2 < 2; ++g2) {
+                        uint32_t pk[2][2];
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            float ev[4];
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) {
+                                const int e = 4 * (2 * g2 + h) + q;
+                                ev[q] = fast_exp2(fmaf(acc[it][jt][e], a.cscale, bias[it][e]) - mrun[jt]);
+                                part += ev[q];
+                            }
+                            pk[h][0] = bf16_pair((__bf16)ev[0], (__bf16)ev[1]);
+                            pk[h][1] = bf16_pair((__bf16)ev[2], (__bf16)ev[3]);
+                        }
+                        const auto s0 = __builtin_amdgcn_permlane32_swap(pk[0][0], pk[1][0], false, false);
+                        const auto s1 = __builtin_amdgcn_permlane32_swap(pk[0][1], pk[1][1], false, false);
+                        *reinterpret_cast<uint4 *>(dst + (((2 * g2 + lh) ^ ((rl >> 2) & 3)) << 4)) = make_uint4(s0[0], s1[0], s0[1], s1[1]);
+                    }
+                }
+                srun[jt] += part;
+            }
+        } else if constexpr (!APPLY) {
             float csum[JTW];
             bool bad = false;
 #pragma unroll
@@ -541,6 +605,7 @@ __device__ __forceinline__ void lse_bf16_body(const BfArgs &a, const int block)
         }
     }
 
+    if constexpr (PRODUCT) return;
     // ---- merge the 2 lane halves x 4 streamed-side waves of every resident row -------------
     lds_done_barrier();   // the ring is free: reuse it for the merge
     float2 *red = reinterpret_cast<float2 *>(ring);   // [BJ][8]: 4 streamed-side waves x 2 lane halves per row
@@ -591,10 +656,10 @@ __device__ __forceinline__ void lse_bf16_body(const BfArgs &a, const int block)
     }
 }
 
-template <int WJ, int NS, int JTW, int PC, bool HALF = false>
+template <int WJ, int NS, int JTW, int PC, bool HALF = false, Epi EPI = Epi::Lse>
 __global__ __launch_bounds__(256 * WJ, WJ == 2 ? 1 : 2) void k_lse_bf16(BfArgs a)
 {
-    lse_bf16_body<WJ, NS, JTW, PC, HALF>(a, blockIdx.x);
+    lse_bf16_body<WJ, NS, JTW, PC, HALF, EPI>(a, blockIdx.x);
 }
 
 // Both LSE passes of one iteration of the averaged schedule (Eq. 4-5) in one launch: the first `blocks0`
@@ -619,6 +684,60 @@ __global__ __launch_bounds__(BI) void k_vimg_bf16(const float *V, int64_t ldv, i
     for (int cc = 0; cc < pc; ++cc) {
         const float v = (row < n_str && p0 + cc < p) ? V[row * ldv + p0 + cc] : 0.0f;
         *reinterpret_cast<__bf16 *>(dst + cc * kVRow + 2 * i) = (__bf16)v;
+    }
+}
+
+// Transposed values for the second product: bf16 V^T, tiled like the point copies with the value columns as rows and the
+// streamed points as coordinates; zero outside the matrix.  A block: 64 columns x 32 points (one chunk); thread (column,
+// piece of eight points).
+__global__ __launch_bounds__(256) void k_vt_bf16(const float *V, int64_t ldv, int64_t n_str, int p, int chunks, unsigned char *img)
+{
+    const int c = blockIdx.y * 64 + (threadIdx.x & 63), piece = threadIdx.x >> 6;
+    const int64_t ch = blockIdx.x;
+    uint32_t pk[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        __bf16 v[2];
+#pragma unroll
+        for (int z = 0; z < 2; ++z) {
+            const int64_t i = ch * KC + piece * 8 + 2 * q + z;
+            v[z] = (__bf16)((i < n_str && c < p) ? V[i * ldv + c] : 0.0f);
+        }
+        pk[q] = bf16_pair(v[0], v[1]);
+    }
+    const int64_t rb = c >> 4;
+    *reinterpret_cast<uint4 *>(img + ((((rb >> 4) * chunks + ch) * 16 + (rb & 15)) << 10) + (c & 15) * 64 +
+                               ((piece ^ ((c >> 2) & 3)) << 4)) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+}
+
+// The stabiliser of a row of the plan slab: minus the base-2 exponent its own potential contributes, rounded, so that
+// exp2(score - rowmax) is the plan's entry without the row's weight, to a factor below sqrt(2).  Padding rows: no entry.
+__global__ void k_plan_rowmax(const double *pot, const double *norm, double inv_eps, int64_t cnt, int64_t cnt_pad, float *rowmax)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < cnt_pad) rowmax[i] = i < cnt ? (float)-rint((pot[i] - norm[i]) * inv_eps * kLog2e) : 3.0e38f;
+}
+
+// out_i = w_i exp(fhat_i/eps) 2^rowmax_i (sum over the splits of the product), columns col0 .. col0 + cols; a block per row
+__global__ __launch_bounds__(256) void k_plan_finalize(const float *opart, int64_t ld, int splits, int slab_rows, int row_off, int64_t cnt,
+                                                       double inv_eps, const float *w, double log_uniform, const double *pot,
+                                                       const double *norm, const float *rowmax, int col0, int cols, float *out, int64_t ldo,
+                                                       const double2 *partial, int64_t stride, int plan_splits, float *mass_out)
+{
+    const int64_t i = row_off + (int64_t)blockIdx.x;
+    if (i >= cnt) return;
+    const double lw = w ? log((double)w[i]) : log_uniform;
+    const double fac = exp2(((pot[i] - norm[i]) * inv_eps + lw) * kLog2e + (double)rowmax[i]);
+    const float *o = opart + (int64_t)blockIdx.x * ld;
+    for (int c = threadIdx.x; c < cols; c += 256) {
+        double acc = 0.0;
+        for (int k = 0; k < splits; ++k) acc += (double)o[(int64_t)k * slab_rows * ld + c];
+        out[i * ldo + col0 + c] = (float)(fac * acc);
+    }
+    if (mass_out && threadIdx.x == 0) {
+        double S = 0.0;
+        for (int k = 0; k < plan_splits; ++k) S += partial[(int64_t)k * stride + i].y;
+        mass_out[i] = (float)(fac * S);
     }
 }
 
@@ -647,6 +766,78 @@ int choose_splits(const Ctx *c, int n_jtiles, int n_itiles, int cap, int per_cu)
 constexpr int kApplyPC = 64;    // value columns per application pass
 constexpr int kApplyPCWide = 96;   // ... when there are more than 64 (every pass repeats the score contraction)
 constexpr int kApplyBJ = 128;   // resident rows per workgroup of the application kernel
+
+// ---- application through a stored slab of the plan -------------------------------------------------------------------
+// The fused kernel takes 96 value columns per pass and repeats the contraction over d in every pass.  With many columns it
+// is cheaper to form the exponentials once, store them in bf16 (which is what the fused kernel multiplies with as well) and
+// run the second product as a matrix product of its own: slabs of resident rows, at most kSlabBytes of exponentials each
+// (what the last-level cache holds; 128 MB measured 8 % slower, 512 MB 1 % faster for twice the memory).
+// Measured at n = 40009, m = 30011, d = 784, 784 columns: 20.7 ms in nine fused passes, 4.4 ms here; of a slab of 4096 rows
+// the exponentials take 212 us (0.93 PFLOP/s with the store of 247 MB), 768 columns of the product 161 us (1.18 PFLOP/s) and
+// the last 16 columns 54 us, which is the time to read the slab once more.
+constexpr size_t kSlabBytes = size_t(256) << 20;
+
+struct SlabPlan {
+    int rows = 0;            // resident rows of a slab (multiple of 256)
+    int e_chunks = 0;        // chunks of 32 streamed points
+    int wide_tiles = 0;      // 256-column tiles of the product
+    int rest = 0;            // columns beyond them, taken by a 128-column tile (0: none)
+    int ks_wide = 0, ks_rest = 0;   // splits of the product's contraction
+    size_t eslab = 0, vt = 0, rowmax = 0, opart = 0, total = 0;
+};
+
+int product_splits(const Ctx *c, int tiles, int chunks)
+{
+    // about one workgroup per CU, each with at least 32 chunks of the contraction
+    int ks = c->num_cu / (tiles < 1 ? 1 : tiles);
+    const int most = chunks / 32 < 1 ? 1 : chunks / 32;
+    if (ks > most) ks = most;
+    if (ks < 1) ks = 1;
+    const int per = (int)ceil_div(chunks, ks);
+    return (int)ceil_div(chunks, per);
+}
+
+SlabPlan slab_plan(const Ctx *c, int64_t n_res, int64_t n_str, int64_t p)
+{
+    SlabPlan s;
+    s.e_chunks = (int)(round_up(n_str, BI) / KC);
+    const int64_t most = (int64_t)(kSlabBytes / ((size_t)s.e_chunks * KC * 2)) / 256 * 256;
+    const int64_t all = round_up(n_res, 256);
+    // (slabs of equal size)
+    const int64_t cnt = most < 256 ? 0 : ceil_div(all, most);
+    s.rows = cnt ? (int)round_up(ceil_div(all, cnt), 256) : 0;
+    s.wide_tiles = (int)(p / 256);
+    s.rest = (int)(p % 256);
+    if (s.rest > 128) {
+        ++s.wide_tiles;
+        s.rest = 0;
+    }
+    const int rt = s.rows / 256;
+    s.ks_wide = s.wide_tiles ? product_splits(c, rt * s.wide_tiles, s.e_chunks) : 0;
+    s.ks_rest = s.rest ? product_splits(c, rt, s.e_chunks) : 0;
+    Arena A;
+    s.eslab = A.take((size_t)s.rows * s.e_chunks * KC * 2);
+    s.vt = A.take((size_t)round_up(p, 256) * s.e_chunks * KC * 2);
+    s.rowmax = A.take((size_t)round_up(n_res, 1024) * 4);
+    const size_t ow = (size_t)s.ks_wide * s.rows * s.wide_tiles * 256 * 4, orr = (size_t)s.ks_rest * s.rows * 128 * 4;
+    s.opart = A.take(ow > orr ? ow : orr);
+    s.total = A.off;
+    return s;
+}
+
+// Which of the two: columns of contraction per pair, the fused kernel's at 0.8 of the rate of the two plain products, the
+// store and the load of an exponential counted as kSlabTraffic columns.  At n = 20000, m = 15000 (us, fused / stored):
+// d = 64, 128 columns 405 / 433; d = 128, 128 columns 536 / 425; d = 192, 192 columns 623 / 520; d = 96, 200 columns
+// 655 / 533; d = 256, 256 columns 1020 / 554; d = 784, 100 columns 1357 / 772.
+constexpr double kSlabTraffic = 230.0;
+bool use_slab(int64_t n_str, int64_t d, int64_t p)
+{
+    if (p <= kApplyPCWide || (size_t)round_up(n_str, BI) * 2 * 256 > kSlabBytes) return false;
+    const double fused = (double)ceil_div(p, kApplyPCWide) * (double)(round_up(d, KC) + kApplyPCWide);
+    const int64_t rest = p % 256;
+    const double cols = (double)(p / 256 * 256 + (rest == 0 ? 0 : rest > 128 ? 256 : 128));
+    return (double)round_up(d, KC) + cols + kSlabTraffic < 1.25 * fused;
+}
 
 }  // namespace
 
@@ -726,9 +917,83 @@ fs_status bf16_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, 
     return FS_OK;
 }
 
-// workspace of bf16_apply: [splits][rows][kApplyPC] float accumulators, then the value images
-size_t bf16_apply_ws(const Ctx *c, int64_t n_res, int64_t n_str)
+static fs_status slab_apply(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, const float *V, int64_t p, int64_t ldv,
+                            float *out, int64_t ldo, float *mass_out)
 {
+    const SlabPlan sp = slab_plan(c, res->cnt, str->cnt, p);
+    char *x = P->extra;
+    if (!x || sp.total > P->extra_bytes || sp.rows < 256) return fail(c, FS_ERR_DEVICE, "internal: plan slab exceeds its buffer");
+    float *rowmax = reinterpret_cast<float *>(x + sp.rowmax), *opart = reinterpret_cast<float *>(x + sp.opart);
+    unsigned char *vt = reinterpret_cast<unsigned char *>(x + sp.vt);
+    hipLaunchKernelGGL(k_vt_bf16, dim3((unsigned)sp.e_chunks, (unsigned)(round_up(p, 256) / 64)), dim3(256), 0, c->stream, V, ldv, str->cnt,
+                       (int)p, sp.e_chunks, vt);
+    hipLaunchKernelGGL(k_plan_rowmax, dim3((unsigned)ceil_div(res->cnt_pad, 256)), dim3(256), 0, c->stream, res->pot, res->norm, 1.0 / eps,
+                       res->cnt, res->cnt_pad, rowmax);
+    const int n_itiles = (int)ceil_div(str->cnt, BI);
+    const int64_t all = round_up(res->cnt, 256);
+    for (int64_t off = 0; off < all; off += sp.rows) {
+        const int rows = (int)(all - off < sp.rows ? all - off : sp.rows), rt = rows / 256;
+        // the exponentials of the slab
+        BfArgs a{};
+        a.res = res->pts_b;
+        a.str = str->pts_b;
+        a.bias = str->bias_f;
+        a.kp = P->kp;
+        a.cscale = (float)(2.0 * kLog2e / eps);
+        a.n_jtiles = rt;
+        a.n_itiles = n_itiles;
+        a.splits = choose_splits(c, rt, n_itiles, max_splits(c->partial_budget, res->cnt), 1);
+        a.tiles_per_split = (int)ceil_div(n_itiles, a.splits);
+        a.partial = (double2 *)P->partial;
+        a.partial_stride = res->cnt_pad;
+        a.rowmax = rowmax;
+        a.eslab = reinterpret_cast<unsigned char *>(x + sp.eslab);
+        a.e_chunks = sp.e_chunks;
+        a.row_off = (int)off;
+        if (off + rows > res->cnt_pad || (int64_t)n_itiles * BI > str->cnt_pad || n_itiles * (BI / KC) != sp.e_chunks ||
+            (size_t)a.splits * res->cnt_pad * 16 > P->partial_bytes || (a.kp & 31) != 0 || a.kp < 32)
+            return fail(c, FS_ERR_DEVICE, "internal: plan slab launch shape exceeds the padded buffers");
+        const bool half = (P->d % 32) >= 1 && (P->d % 32) <= 16 && a.kp >= 64;   // (as in bf16_lse)
+        const dim3 grid((unsigned)round_up(rt * a.splits, 8));
+        if (half)
+            hipLaunchKernelGGL((k_lse_bf16<2, 4, 4, 0, true, Epi::Plan>), grid, dim3(512), 0, c->stream, a);
+        else
+            hipLaunchKernelGGL((k_lse_bf16<2, 4, 4, 0, false, Epi::Plan>), grid, dim3(512), 0, c->stream, a);
+        // times the values: the 256-column tiles, then the rest
+        for (int part = 0; part < 2; ++part) {
+            const int tiles = part ? (sp.rest ? 1 : 0) : sp.wide_tiles, ks = part ? sp.ks_rest : sp.ks_wide;
+            if (!tiles) continue;
+            const int col0 = part ? sp.wide_tiles * 256 : 0;
+            const int cols = (int)(part ? sp.rest : (p < (int64_t)tiles * 256 ? p : (int64_t)tiles * 256));
+            BfArgs b{};
+            b.str = reinterpret_cast<const uint16_t *>(x + sp.eslab);
+            b.res = reinterpret_cast<const uint16_t *>(vt + (size_t)sp.wide_tiles * part * 256 * sp.e_chunks * KC * 2);
+            b.n_jtiles = tiles;
+            b.n_itiles = rt;
+            b.splits = rt * ks;
+            b.e_chunks = sp.e_chunks;
+            b.ch_per_split = (int)ceil_div(sp.e_chunks, ks);
+            b.out_rows = rows;
+            b.opart = opart;
+            b.opart_ld = part ? 128 : tiles * 256;
+            const dim3 g2((unsigned)round_up(tiles * b.splits, 8));
+            if (part)
+                hipLaunchKernelGGL((k_lse_bf16<2, 4, 2, 0, false, Epi::Product>), g2, dim3(512), 0, c->stream, b);
+            else
+                hipLaunchKernelGGL((k_lse_bf16<2, 4, 4, 0, false, Epi::Product>), g2, dim3(512), 0, c->stream, b);
+            hipLaunchKernelGGL(k_plan_finalize, dim3((unsigned)rows), dim3(256), 0, c->stream, opart, b.opart_ld, ks, rows, (int)off, res->cnt,
+                               1.0 / eps, res->w, res->log_uniform, res->pot, res->norm, rowmax, col0, cols, out, ldo,
+                               (const double2 *)P->partial, res->cnt_pad, a.splits, (part == 0 || !sp.wide_tiles) ? mass_out : nullptr);
+        }
+        FS_HIP(c, hipGetLastError());
+    }
+    return FS_OK;
+}
+
+// workspace of bf16_apply: [splits][rows][kApplyPC] float accumulators, then the value images
+size_t bf16_apply_ws(const Ctx *c, int64_t n_res, int64_t n_str, int64_t d, int64_t p)
+{
+    if (use_slab(n_str, d, p)) return slab_plan(c, n_res, n_str, p).total;
     const int n_jtiles = (int)ceil_div(n_res, kApplyBJ), n_itiles = (int)ceil_div(n_str, BI);
     const int splits = choose_splits(c, n_jtiles, n_itiles, max_splits(c->partial_budget, n_res), 1);
     const size_t opart = (size_t)splits * (size_t)round_up(n_res, 1024) * kApplyPCWide * 4;
@@ -738,6 +1003,7 @@ size_t bf16_apply_ws(const Ctx *c, int64_t n_res, int64_t n_str)
 fs_status bf16_apply(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, const float *V, int64_t p,
                      int64_t ldv, float *out, int64_t ldo, float *mass_out)
 {
+    if (use_slab(str->cnt, P->d, p)) return slab_apply(c, P, res, str, eps, V, p, ldv, out, ldo, mass_out);
     BfArgs a{};
     a.res = res->pts_b;
     a.str = str->pts_b;

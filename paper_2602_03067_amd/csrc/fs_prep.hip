@@ -717,7 +717,8 @@ __global__ void k_pts_to_f32(const void *pts, int dtype, int64_t rows, int64_t d
 {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= rows * d) return;
-    const int64_t i = e / d, k = e - i * d;
+    // (a 64-bit division costs more than the rest of an entry)
+    const int64_t i = rows * d < (int64_t(1) << 32) ? (int64_t)((uint32_t)e / (uint32_t)d) : e / d, k = e - i * d;
     dst[e] = load_pt(pts, dtype, i * ld + k);
 }
 
@@ -730,7 +731,8 @@ __global__ void k_grad_assemble(float *g, int64_t ldg, const void *pts, int dtyp
 {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= rows * d) return;
-    const int64_t i = e / d, k = e - i * d;
+    // (a 64-bit division costs more than the rest of an entry)
+    const int64_t i = rows * d < (int64_t(1) << 32) ? (int64_t)((uint32_t)e / (uint32_t)d) : e / d, k = e - i * d;
     const double z = (double)load_pt(pts, dtype, i * ld + k);
     const double t = (double)g[i * ldg + k];
     const double wi = w ? (double)w[i] : uniform_w;

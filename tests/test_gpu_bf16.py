@@ -221,3 +221,34 @@ def test_apply_bf16_mode_large_score_spread(ctx, oracle):
     say("  PY %.3e  mass %.3e  element-wise / (P|y|) %.3e" % (e1, em, el))
     assert e1 <= TOL_APPLY_B and em <= TOL_APPLY_B
     assert el <= TOL_APPLY_EL_B
+
+
+@pytest.mark.parametrize("n,m,d,p", [(300, 500, 784, 97), (257, 255, 320, 128), (40, 700, 160, 300), (513, 33, 512, 257),
+                                     (600, 290, 100, 400), (1, 1, 128, 520),
+                                     # two slabs of resident rows (a slab holds 2^27 exponentials), the second one shorter
+                                     (6000, 24000, 96, 300)])
+def test_apply_through_stored_plan(ctx, oracle, n, m, d, p):
+    """More columns than a fused pass takes: exponentials stored in bf16, then a matrix product in column tiles of 256 and
+    128.  The same roundings as in the fused pass (exponentials and values to bf16, sums in fp32), so the same tolerances."""
+    rng = np.random.default_rng(3 * n + m + d + p)
+    x = rng.random((n, d)).astype(np.float32)
+    y = (rng.random((m, d)) * 0.9).astype(np.float32)
+    xb, yb = workloads.to_bf16_round(x), workloads.to_bf16_round(y)
+    a, b = rng.random(n) + 0.1, rng.random(m) + 0.1
+    a, b = (a / a.sum()).astype(np.float32), (b / b.sum()).astype(np.float32)
+    eps = float(np.float32(0.02 * d))
+    g = (0.3 * eps * rng.standard_normal(m)).astype(np.float32)
+    rows = np.unique(np.concatenate([np.arange(min(n, 20)), np.arange(max(0, n - 20), n), rng.integers(0, n, 40)]))
+    f = np.full(n, 0.11 * d, dtype=np.float32)   # potentials need not be converged: plan entries far from one
+    f[rows] = oracle.update_f(xb, yb, b, eps, g, rows=rows).astype(np.float32)
+    f[rows[0]] += np.float32(30.0 * eps)
+    V = rng.standard_normal((m, p)).astype(np.float32)
+    prob = make_problem(x, y, a, b, compute=binding.FS_COMPUTE_BF16_MFMA)
+    say("bf16 stored plan n=%d m=%d d=%d p=%d" % (n, m, d, p))
+    out, mass = ctx.fs_apply_plan(prob, eps, dev(f), dev(g), dev(V), want_mass=True)
+    want, r = oracle.apply_plan(xb, yb, a, b, eps, f, g, V, rows=rows, return_mass=True)
+    scale = oracle.apply_plan(xb, yb, a, b, eps, f, g, np.abs(V), rows=rows)
+    got = host(out)[rows]
+    assert np.abs(host(mass)[rows] / r - 1.0).max() <= TOL_APPLY_B
+    assert (np.abs(got - want) / scale).max() <= TOL_APPLY_EL_B
+    assert np.linalg.norm((got - want) / r[:, None]) <= TOL_APPLY_B * np.linalg.norm(scale / r[:, None])
