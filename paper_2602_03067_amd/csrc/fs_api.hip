@@ -213,7 +213,8 @@ size_t layout_with(const Ctx *c, const fs_problem *p, Prepared *P, char *base, s
     P->partial = base ? (void *)(base + o) : nullptr;
     o = A.take((size_t)ceil_div(big, 256) * 8);
     P->dev_part = base ? (double *)(base + o) : nullptr;
-    o = A.take((size_t)ceil_div(big, 256) * 16);
+    // (two halves of one sum per 256 rows, or one sum per 32 rows of a small low-d problem)
+    o = A.take(P->path == Path::LowD && lowd_small(p->n, p->m, p->d) ? (size_t)ceil_div(big, 32) * 8 + 16 : (size_t)ceil_div(big, 256) * 16);
     P->gauge_part = base ? (double *)(base + o) : nullptr;
     o = A.take((size_t)ceil_div(big, 256) * 16);
     P->gauge_part_x = base ? (double *)(base + o) : nullptr;
@@ -313,6 +314,29 @@ fs_status run_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, d
     case Path::BF16: return bf16_lse(c, P, res, str, eps, splits);
     }
     return FS_ERR_UNSUPPORTED;
+}
+
+// One half-step of the alternating schedules: the pass of `str` over `res` at eps and the merge into res's new potential.
+// *gauge_cnt: in, how many gauge sums the g-update before this Collect left; out, how many this Measure leaves.
+fs_status half_step(Ctx *c, const Prepared *P, Side *res, Side *str, double eps, double eps_next_bias, float *user_out,
+                    GaugeMode gauge, int64_t *gauge_cnt, double gauge_prev_eps)
+{
+    fs_status st;
+    if (P->path == Path::LowD) {
+        const double *nrm = lowd_precise(P, eps) ? res->norm : res->norm_f;
+        const FinalizeArgs fz = make_finalize_args(P, res, nrm, eps, eps_next_bias, user_out, gauge, *gauge_cnt, gauge_prev_eps);
+        bool done = false;
+        if ((st = lowd_half_small(c, P, res, str, eps, fz, &done)) != FS_OK) return st;
+        if (done) {
+            if (gauge == GaugeMode::Measure) *gauge_cnt = ceil_div(res->cnt, 32);
+            return FS_OK;
+        }
+    }
+    Splits splits;
+    if ((st = run_lse(c, P, res, str, eps, &splits)) != FS_OK) return st;
+    st = finalize(c, P, res, splits, eps, eps_next_bias, user_out, nullptr, 1.0, nullptr, gauge, *gauge_cnt, gauge_prev_eps);
+    if (gauge == GaugeMode::Measure) *gauge_cnt = ceil_div(res->cnt, 256);
+    return st;
 }
 
 // Plan application in two phases, so that a caller can place data in the workspace in between:
@@ -549,9 +573,8 @@ fs_status fs_update_f(fs_ctx *ctx, const fs_problem *prob, float eps, const floa
     Prepared P;
     if ((st = prepare(c, prob, &P, 0, nullptr)) != FS_OK) return st;
     if ((st = launch_bias_from_user(c, &P, &P.Y, g, eps)) != FS_OK) return st;
-    Splits splits;
-    if ((st = run_lse(c, &P, &P.X, &P.Y, eps, &splits)) != FS_OK) return st;
-    return finalize(c, &P, &P.X, splits, eps, 0.0, f_out, nullptr);
+    int64_t none = 0;
+    return half_step(c, &P, &P.X, &P.Y, eps, 0.0, f_out, GaugeMode::None, &none, 0.0);
 }
 
 fs_status fs_update_g(fs_ctx *ctx, const fs_problem *prob, float eps, const float *f, float *g_out)
@@ -568,9 +591,8 @@ fs_status fs_update_g(fs_ctx *ctx, const fs_problem *prob, float eps, const floa
     Prepared P;
     if ((st = prepare(c, prob, &P, 0, nullptr)) != FS_OK) return st;
     if ((st = launch_bias_from_user(c, &P, &P.X, f, eps)) != FS_OK) return st;
-    Splits splits;
-    if ((st = run_lse(c, &P, &P.Y, &P.X, eps, &splits)) != FS_OK) return st;
-    return finalize(c, &P, &P.Y, splits, eps, 0.0, g_out, nullptr);
+    int64_t none = 0;
+    return half_step(c, &P, &P.Y, &P.X, eps, 0.0, g_out, GaugeMode::None, &none, 0.0);
 }
 
 // fs_solve and fs_solve_noalloc: `static_only` runs in the library's static scratch array and fails instead of allocating
@@ -637,6 +659,7 @@ static fs_status solve_impl(Ctx *c, const fs_problem *prob, float eps_start, flo
     // out when the potentials are handed to the caller
     if ((st = launch_fill_f64(c, P.scalars + 8, 0.0, 2)) != FS_OK) return st;
     double eps_prev = 0.0;
+    int64_t gauge_cnt = 0;
     double eps = eps0;
     for (int s = 0; s < n_stages; ++s) {
         eps = stage_eps(eps_start, eps_end, n_stages, s);
@@ -644,21 +667,17 @@ static fs_status solve_impl(Ctx *c, const fs_problem *prob, float eps_start, flo
             bool last = (s == n_stages - 1) && (t == iters_per_stage - 1);
             double eps_next = eps;
             if (t == iters_per_stage - 1 && !last) eps_next = stage_eps(eps_start, eps_end, n_stages, s + 1);
-            Splits splits;
             // Alg. 1: f from g
-            if ((st = run_lse(c, &P, &P.X, &P.Y, eps, &splits)) != FS_OK) return st;
-            if ((st = finalize(c, &P, &P.X, splits, eps, eps, nullptr, nullptr, 1.0, nullptr,
-                               eps_prev > 0.0 ? GaugeMode::Collect : GaugeMode::None, prob->m, eps_prev)) != FS_OK)
+            if ((st = half_step(c, &P, &P.X, &P.Y, eps, eps, nullptr, eps_prev > 0.0 ? GaugeMode::Collect : GaugeMode::None, &gauge_cnt,
+                                eps_prev)) != FS_OK)
                 return st;
             // Alg. 3: g from the new f
-            if ((st = run_lse(c, &P, &P.Y, &P.X, eps, &splits)) != FS_OK) return st;
-            if ((st = finalize(c, &P, &P.Y, splits, eps, last ? 0.0 : eps_next, nullptr, nullptr, 1.0, nullptr,
-                               GaugeMode::Measure)) != FS_OK)
+            if ((st = half_step(c, &P, &P.Y, &P.X, eps, last ? 0.0 : eps_next, nullptr, GaugeMode::Measure, &gauge_cnt, 0.0)) != FS_OK)
                 return st;
             eps_prev = eps;
         }
     }
-    return launch_gauge_export(c, &P, true, eps, P.X.pot, f, g);
+    return launch_gauge_export(c, &P, gauge_cnt, eps, P.X.pot, f, g);
 }
 
 fs_status fs_solve(fs_ctx *ctx, const fs_problem *prob, float eps_start, float eps_end, int32_t n_stages,
@@ -772,7 +791,7 @@ fs_status fs_solve_tol(fs_ctx *ctx, const fs_problem *prob, float eps_in, int32_
         if (!pending) {   // Alg. 1: f from g
             if ((st = run_lse(c, &P, &P.X, &P.Y, eps, &splits)) != FS_OK) return st;
             if ((st = finalize(c, &P, &P.X, splits, eps, eps, nullptr, nullptr, 1.0, nullptr,
-                               gauge_pending ? GaugeMode::Collect : GaugeMode::None, prob->m, eps)) != FS_OK)
+                               gauge_pending ? GaugeMode::Collect : GaugeMode::None, ceil_div(prob->m, 256), eps)) != FS_OK)
                 return st;
             gauge_pending = false;
         }
@@ -785,7 +804,7 @@ fs_status fs_solve_tol(fs_ctx *ctx, const fs_problem *prob, float eps_in, int32_
         if (t % check_every != 0 && t != max_iters) continue;
         // the next f-update, measuring the error of (f_t, g_t) on the way
         if ((st = run_lse(c, &P, &P.X, &P.Y, eps, &splits)) != FS_OK) return st;
-        if ((st = finalize(c, &P, &P.X, splits, eps, eps, nullptr, P.scalars, 1.0, f_before, GaugeMode::Collect, prob->m, eps)) !=
+        if ((st = finalize(c, &P, &P.X, splits, eps, eps, nullptr, P.scalars, 1.0, f_before, GaugeMode::Collect, ceil_div(prob->m, 256), eps)) !=
             FS_OK)
             return st;
         gauge_pending = false;
@@ -795,7 +814,7 @@ fs_status fs_solve_tol(fs_ctx *ctx, const fs_problem *prob, float eps_in, int32_
         pending = true;
     }
     // f_t sat before the last g-update's term entered the sum, g_t behind it
-    if ((st = launch_gauge_export(c, &P, false, eps, f_before, f, g)) != FS_OK) return st;
+    if ((st = launch_gauge_export(c, &P, 0, eps, f_before, f, g)) != FS_OK) return st;
     FS_HIP(c, hipStreamSynchronize(c->stream));
     *iters_done = t;
     *err_row_l1 = (float)err;
@@ -874,7 +893,7 @@ fs_status fs_solve_symmetric(fs_ctx *ctx, const fs_problem *prob, float eps_in, 
     }
     // the drift along (f + t, g - t) that the iterations measured (see launch_finalize_pair), taken out on the way out
     if ((st = launch_gauge_collect_pair(c, &P, eps, iters - 1)) != FS_OK) return st;
-    return launch_gauge_export(c, &P, false, eps, P.X.pot, f, g);
+    return launch_gauge_export(c, &P, 0, eps, P.X.pot, f, g);
 }
 
 fs_status fs_marginal_err(fs_ctx *ctx, const fs_problem *prob, float eps, const float *f, const float *g,

@@ -43,10 +43,11 @@ __device__ inline void split_precise_bias(double bias, double q, uint4 *digits, 
         if (residual) *residual = make_uint2(0u, 0u);
         return;
     }
-    const double B = rint(bias / q);
+    const double iq = 1.0 / q;   // (q is a power of two: the products below are exact quotients)
+    const double B = rint(bias * iq);
     const __bf16 da = (__bf16)(float)(rint(B * (1.0 / 65536.0)) * 65536.0 * q);
     const double ra = B * q - (double)(float)da;
-    const __bf16 db = (__bf16)(float)(rint(ra / (256.0 * q)) * 256.0 * q);
+    const __bf16 db = (__bf16)(float)(rint(ra * (iq * (1.0 / 256.0))) * 256.0 * q);
     const double rb = ra - (double)(float)db;
     const __bf16 dc = (__bf16)(float)rb;
     *digits = make_uint4(bf16_pair(da, db), bf16_pair(dc, one), bf16_pair(one, one), 0u);
@@ -56,26 +57,6 @@ __device__ inline void split_precise_bias(double bias, double q, uint4 *digits, 
         *residual = make_uint2(bf16_pair(r[0], r[1]), bf16_pair(r[2], z));
     }
 }
-
-// Where the bias of point i of a side lives, by path, and the squared norms that turn the
-// unshifted potential into the shifted one of Prop. 1 (fhat = f - alpha, ghat = g - beta).
-struct BiasSink {
-    float *packed;          // LowD float copy: packed[i*dp + d], shifted by norm_f
-    uint16_t *split;        // LowD split records (same value as the float copy), ks > 0
-    int ks;
-    uint16_t *split_p;      // LowD precise split records (d <= 3) and the grid of their bias digits:
-    double q;               // q itself, or (q == 0) the device scalar rho_max and the eps it is derived from
-    const double *rho_dev;
-    double q_eps;
-    double *packed_d;       // LowD double copy: packed_d[i*dpd + d], shifted by norm
-    int dp, dpd, d;
-    float *bias_f;          // BF16 path
-    double *bias_d;         // F64 path
-    int *brec;              // F64 path: bias records of the fixed-point kernels and the scale r2 they refer to
-    const double *r2;
-    const double *norm_f;
-    const double *norm;
-};
 
 // bias in base-2 units of a streamed point:  ((pot_shifted)/eps + log w) * log2(e)
 // (Alg. 1: (ghat_j + delta_j)/eps with delta = eps*log b)
@@ -140,37 +121,6 @@ __device__ inline double rescale_split(double v, double mk, double M)
     return dlt >= -1100.0 ? ldexp(v, (int)dlt) : 0.0;   // also 0 for a NaN difference (-inf - -inf)
 }
 
-// ---- merge the per-split (max, sum) statistics of a streaming pass -----------------------
-//   LSE_2 = M + log2(sum_k s_k 2^(m_k - M)),  pot_new = -eps * ln2 * LSE_2      (Alg. 1, last lines)
-// and, as asked: store pot_new, the bias for the pass that streams this side next, the
-// unshifted potential for the caller, or the marginal deviation |w e^((pot_old-pot_new)/eps) - w|.
-struct FinalizeArgs {
-    const double2 *partial;
-    int64_t stride;
-    int splits, splits_alt;   // (splits_alt: where the gate chose the float64 kernel)
-    FxGate gate;
-    int64_t cnt;
-    double eps, inv_eps_next;
-    const float *w;
-    double log_uniform;
-    const double *res_norm;
-    double *pot;
-    BiasSink sink;
-    float *user_out;
-    double *dev_part;
-    double mix;
-    double *save_old;
-    int blocks;   // workgroups of this side
-    // gauge drift (see GaugeMode): where a g-update leaves the block sums of the plan's column marginals, and what
-    // the first workgroup of the following f-update collects
-    double *gauge_out;
-    const double *gauge_prev;
-    int64_t gauge_prev_cnt;
-    double gauge_prev_eps;
-    double *gauge_scalars;   // [0]: the sum so far, [1]: the sum without its last term
-    const double *gauge_prev_x;   // averaged schedule: the f-pass's block sums of the previous iteration
-    int64_t gauge_prev_x_cnt;
-};
 
 // one workgroup: scalars[1] <- scalars[0], scalars[0] += eps ln(sum of part[0..cnt)), in a fixed order
 __device__ inline void gauge_collect(const double *part, int64_t cnt, double eps, double *scalars, double *sh)

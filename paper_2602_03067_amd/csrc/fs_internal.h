@@ -313,6 +313,58 @@ inline FxGate fx_gate(const Prepared *P, double eps)
     return g;
 }
 
+// Where the bias of point i of a side lives, by path, and the squared norms that turn the
+// unshifted potential into the shifted one of Prop. 1 (fhat = f - alpha, ghat = g - beta).
+struct BiasSink {
+    float *packed;          // LowD float copy: packed[i*dp + d], shifted by norm_f
+    uint16_t *split;        // LowD split records (same value as the float copy), ks > 0
+    int ks;
+    uint16_t *split_p;      // LowD precise split records (d <= 3) and the grid of their bias digits:
+    double q;               // q itself, or (q == 0) the device scalar rho_max and the eps it is derived from
+    const double *rho_dev;
+    double q_eps;
+    double *packed_d;       // LowD double copy: packed_d[i*dpd + d], shifted by norm
+    int dp, dpd, d;
+    float *bias_f;          // BF16 path
+    double *bias_d;         // F64 path
+    int *brec;              // F64 path: bias records of the fixed-point kernels and the scale r2 they refer to
+    const double *r2;
+    const double *norm_f;
+    const double *norm;
+};
+
+// ---- merge the per-split (max, sum) statistics of a streaming pass -----------------------
+//   LSE_2 = M + log2(sum_k s_k 2^(m_k - M)),  pot_new = -eps * ln2 * LSE_2      (Alg. 1, last lines)
+// and, as asked: store pot_new, the bias for the pass that streams this side next, the
+// unshifted potential for the caller, or the marginal deviation |w e^((pot_old-pot_new)/eps) - w|.
+struct FinalizeArgs {
+    const double2 *partial;
+    int64_t stride;
+    int splits, splits_alt;   // (splits_alt: where the gate chose the float64 kernel)
+    FxGate gate;
+    int64_t cnt;
+    double eps, inv_eps_next;
+    const float *w;
+    double log_uniform;
+    const double *res_norm;
+    double *pot;
+    BiasSink sink;
+    float *user_out;
+    double *dev_part;
+    double mix;
+    double *save_old;
+    int blocks;   // workgroups of this side
+    // gauge drift (see GaugeMode): where a g-update leaves the block sums of the plan's column marginals, and what
+    // the first workgroup of the following f-update collects
+    double *gauge_out;
+    const double *gauge_prev;
+    int64_t gauge_prev_cnt;
+    double gauge_prev_eps;
+    double *gauge_scalars;   // [0]: the sum so far, [1]: the sum without its last term
+    const double *gauge_prev_x;   // averaged schedule: the f-pass's block sums of the previous iteration
+    int64_t gauge_prev_x_cnt;
+};
+
 // ---------------------------------------------------------------------------------------
 // kernel launchers (implemented in the path-specific translation units)
 // ---------------------------------------------------------------------------------------
@@ -347,14 +399,19 @@ fs_status launch_bias_from_user(Ctx *c, Prepared *P, Side *side, const float *po
 // (scalars[8]; scalars[9] keeps the sum without the last term) and hands f - scalars[9], g + scalars[8] to the caller.
 //   Measure: this merge is a g-update of an alternating solve: leave the block sums of c_j in gauge_part
 //   Collect: this merge is the f-update after one: its first workgroup adds eps_prev ln(sum gauge_part) to scalars[8]
+//            (gauge_prev_cnt: how many sums that g-update left)
 enum class GaugeMode { None, Measure, Collect };
 fs_status launch_finalize(Ctx *c, const Prepared *P, Side *res, const double *res_norm, Splits splits,
                           double eps_cur, double eps_next_bias, float *user_out, double *abs_dev_sum,
                           double mix = 1.0, double *save_old = nullptr, GaugeMode gauge = GaugeMode::None,
                           int64_t gauge_prev_cnt = 0, double gauge_prev_eps = 0.0);
+// the same merge's arguments, for a half-step kernel that merges on its own
+FinalizeArgs make_finalize_args(const Prepared *P, Side *res, const double *res_norm, double eps_cur, double eps_next_bias,
+                                float *user_out, GaugeMode gauge, int64_t gauge_prev_cnt, double gauge_prev_eps);
 // the last g-update's term, then f_user = (float)(X.pot - scalars[9]) and g_user = (float)(Y.pot + scalars[8])
 // (x_pot: the f to hand out, X.pot or a saved copy of it)
-fs_status launch_gauge_export(Ctx *c, const Prepared *P, bool collect_last, double eps_last, const double *x_pot,
+// (collect_last: how many sums the last g-update left in gauge_part, 0: nothing to collect)
+fs_status launch_gauge_export(Ctx *c, const Prepared *P, int64_t collect_last, double eps_last, const double *x_pot,
                               float *f_user, float *g_user);
 // `gauge`: the averaged schedule's form of the drift removal (see GaugeMode): both passes of an iteration read the
 // same old potentials, so the plan's mass as the f-pass sees it (row sums) and as the g-pass sees it (column sums)
@@ -409,6 +466,15 @@ PassShape lowd_shape(const Ctx *c, int64_t n_res, int64_t n_str);
 bool lowd_precise(const Prepared *P, double eps);
 fs_status lowd_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps,
                    Splits *splits_out);
+// a half-step and its merge in one launch (small problems); *done = false: not applicable.  It leaves one gauge sum per 32
+// rows, the merge kernels one per 256.
+// The line, from half-steps in two launches and in one (us): d = 3: n = m = 1024 10.4 / 6.4, 4096 12.0 / 10.1, 8192
+// 16.8 / 16.0, 12000 28 / 31; d = 10: 3000 14.2 / 13.2, 6000 18.2 / 21.6; d = 16: 6000 21.6 / 29.6.
+inline bool lowd_small(int64_t n, int64_t m, int64_t d)
+{
+    return n <= 8192 && m <= 8192 && (double)n * (double)m * split_ksteps(d) <= 1.0e8;
+}
+fs_status lowd_half_small(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, const FinalizeArgs &fz, bool *done);
 // both half-steps of an averaged iteration (Eq. 4-5) in one launch; *done = false: not applicable
 fs_status lowd_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, void *partial_y, Splits *splits_x,
                         Splits *splits_y, bool *done);

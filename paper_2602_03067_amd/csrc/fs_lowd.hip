@@ -17,6 +17,7 @@
 //
 // Score precision: fp32 when (log2e/eps) * max|x|^2 is small enough for fp32 scores to hold the
 // 1e-4 target, float64 otherwise (a score of magnitude 500 has an fp32 ulp of 6e-5).
+#include "fs_finalize.h"
 #include "fs_internal.h"
 
 #include <stdlib.h>
@@ -229,6 +230,48 @@ struct SplitArgs {
     const unsigned char *vimg;   // PC == 8: value images of the streamed tiles (see k_vimg_lowd)
 };
 
+// the B operands of resident row `row` (pieces 2 ks + lh, the max slots left at zero)
+template <int KS, bool PRECISE>
+__device__ __forceinline__ void resident_operand(const SplitArgs &a, const int64_t row, const int lh, bf8 (&b)[KS])
+{
+    const int d = a.d;
+    const __bf16 one = (__bf16)1.0f, zero = (__bf16)0.0f;
+    const double inv_gx = PRECISE ? 1.0 / a.gx : 0.0;   // (gx is a power of two: the products below are exact quotients)
+    if constexpr (!PRECISE) {
+        const float *px = static_cast<const float *>(a.res) + row * a.dp;
+        const float cscale = (float)a.cscale;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const int c = 2 * ks + lh;
+            __bf16 x[3];
+            split3(c < d ? px[c] * cscale : 0.0f, x);
+            bf8 v = {x[0], x[0], x[1], x[0], x[1], x[2], x[1], x[2]};
+            if (c == d) v = bf8{one, one, one, zero, zero, zero, zero, zero};
+            b[ks] = v;
+        }
+    } else {
+        const double *px = static_cast<const double *>(a.res) + row * a.dp;
+        __bf16 X1[3], rx[3][3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const double cx = c < d ? px[c] * a.cscale : 0.0;
+            const double x1 = rint(cx * inv_gx) * a.gx;
+            X1[c] = (__bf16)(float)x1;
+            split3d(cx - x1, rx[c]);
+        }
+        // pieces 0..5 (piece = 2 ks + lh); see split_precise_record for the streamed counterparts
+        const bf8 p0 = {X1[0], X1[1], X1[2], zero, zero, zero, zero, zero};
+        const bf8 p1 = {one, one, one, zero, zero, zero, zero, zero};
+        const bf8 p5 = {one, one, one, zero, zero, rx[0][1], rx[1][1], rx[2][1]};
+        bf8 pc[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) pc[c] = bf8{X1[c], X1[c], X1[c], rx[c][0], rx[c][1], rx[c][2], rx[c][0], rx[c][0]};
+        b[0] = lh ? p1 : p0;
+        b[1] = lh ? pc[1] : pc[0];
+        b[2] = lh ? p5 : pc[2];
+    }
+}
+
 // one workgroup of the pass: row block bx, column split by.
 // PC > 0 makes it the plan application (Alg. 2 / Alg. 4) for PC value columns, in one of two forms.
 // PC == 4: every exponential also multiplies the value row of its streamed point, which all lanes of a
@@ -351,42 +394,9 @@ __device__ __forceinline__ void lse_split_body(const SplitArgs &a, const int bx,
     // the first tile is on its way while the resident operands are built
     if (t_begin < t_end) fetch(t_begin, 0);
 
-    const __bf16 one = (__bf16)1.0f, zero = (__bf16)0.0f;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        if constexpr (!PRECISE) {
-            const float *px = static_cast<const float *>(a.res) + (row0 + 32 * r + lj) * a.dp;
-            const float cscale = (float)a.cscale;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                const int c = 2 * ks + lh;
-                __bf16 x[3];
-                split3(c < d ? px[c] * cscale : 0.0f, x);
-                bf8 v = {x[0], x[0], x[1], x[0], x[1], x[2], x[1], x[2]};
-                if (c == d) v = bf8{one, one, one, zero, zero, zero, zero, zero};
-                b[r][ks] = v;
-            }
-        } else {
-            const double *px = static_cast<const double *>(a.res) + (row0 + 32 * r + lj) * a.dp;
-            __bf16 X1[3], rx[3][3];
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const double cx = c < d ? px[c] * a.cscale : 0.0;
-                const double x1 = rint(cx / a.gx) * a.gx;
-                X1[c] = (__bf16)(float)x1;
-                split3d(cx - x1, rx[c]);
-            }
-            // pieces 0..5 (piece = 2 ks + lh); see split_precise_record for the streamed counterparts
-            const bf8 p0 = {X1[0], X1[1], X1[2], zero, zero, zero, zero, zero};
-            const bf8 p1 = {one, one, one, zero, zero, zero, zero, zero};
-            const bf8 p5 = {one, one, one, zero, zero, rx[0][1], rx[1][1], rx[2][1]};
-            bf8 pc[3];
-#pragma unroll
-            for (int c = 0; c < 3; ++c) pc[c] = bf8{X1[c], X1[c], X1[c], rx[c][0], rx[c][1], rx[c][2], rx[c][0], rx[c][0]};
-            b[r][0] = lh ? p1 : p0;
-            b[r][1] = lh ? pc[1] : pc[0];
-            b[r][2] = lh ? p5 : pc[2];
-        }
+        resident_operand<KS, PRECISE>(a, row0 + 32 * r + lj, lh, b[r]);
         mrun[r] = kNegInit;
         srun[r] = 0.0f;
         stile[r] = 0.0f;
@@ -738,6 +748,120 @@ __global__ __launch_bounds__(kBlock, 2) void k_lse_lowd_split_pair(SplitArgs a0,
     lse_split_body<KS, R, TJ, CH, PRECISE>(a, (int)blockIdx.x - (second ? a0.row_blocks : 0), blockIdx.y);
 }
 
+// A whole half-step in one launch, for problems whose passes are shorter than their launches: a workgroup of eight waves
+// takes 32 resident rows against ALL streamed points (a wave every eighth group of 32, straight from memory), merges in
+// LDS and makes the new potential and bias on the spot, so there are no split records and no merge kernel.
+// Bound by latency: launch, two dependent loads, the merge.  n = m = 1024, d = 3, precise records: 10.4 us a half-step as
+// two kernels (6.6 + 4.7 while traced), 6.4 as one.
+constexpr int kSmallWaves = 8;
+template <int KS, bool PRECISE>
+__global__ __launch_bounds__(64 * kSmallWaves) void k_half_lowd_small(SplitArgs a, FinalizeArgs fz, int n_groups)
+{
+    constexpr int NP = 2 * KS;
+    __shared__ float sm[kSmallWaves][32];
+    __shared__ double ss[kSmallWaves][32];
+    const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, lj = l & 31, lh = l >> 5;
+    const int64_t row0 = (int64_t)blockIdx.x * 32;
+    constexpr int MK = PRECISE ? 0 : KS - 1;   // the piece with the max slots (as in lse_split_body)
+    const bool holds_max = PRECISE ? (lh == 1) : (lh == (a.d & 1));
+    bf8 b[KS];
+    auto set_max = [&](float neg_m) {
+        __bf16 q[3];
+        split3(neg_m, q);
+        if (holds_max) {
+            b[MK][3] = q[0];
+            b[MK][4] = q[1];
+            b[MK][5] = q[2];
+        }
+    };
+    const Unit *str = reinterpret_cast<const Unit *>(a.str);
+    auto load_a = [&](int g, bf8 (&av)[KS]) {
+        const int64_t point = (int64_t)g * 32 + lj;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) av[ks] = *reinterpret_cast<const bf8 *>(str + point * NP + split_piece_pos(KS, point, 2 * ks + lh));
+    };
+    auto scores = [&](const bf8 (&av)[KS], f16v &dd) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) dd[e] = 0.0f;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) dd = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[ks], b[ks], dd, 0, 0, 0);
+    };
+    auto sums = [&](const f16v &dd) {
+        float s0 = 0.0f, s1 = 0.0f;
+#pragma unroll
+        for (int e = 0; e < 16; e += 2) {
+            s0 += fast_exp2(dd[e]);
+            s1 += fast_exp2(dd[e + 1]);
+        }
+        return s0 + s1;
+    };
+    bf8 av[KS];
+    if (w < n_groups) load_a(w, av);
+    resident_operand<KS, PRECISE>(a, row0 + lj, lh, b);
+    float m = kNegInit;
+    double s = 0.0;
+    set_max(-kNegInit);
+    for (int g = w; g < n_groups; g += kSmallWaves) {
+        bf8 nx[KS];
+        load_a(min(g + kSmallWaves, n_groups - 1), nx);
+        f16v dd;
+        scores(av, dd);
+        float cs = sums(dd);
+        // lift the max, common to the two lane halves (see lse_split_body); sixteen scores at or below it sum to 16 at most,
+        // and a wave sees too few groups to start far below its largest score: 5 base-2 units here, 60 there
+        if (__any(!(cs < 32.0f))) {
+            set_max(0.0f);
+            scores(av, dd);
+            float mx = kNegInit;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) mx = fmaxf(mx, dd[e]);
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            const float mnew = fmaxf(m, ceilf(mx));
+            s *= (double)fast_exp2(m - mnew);
+            m = mnew;
+            set_max(-mnew);
+            scores(av, dd);
+            cs = sums(dd);
+        }
+        s += (double)cs;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) av[ks] = nx[ks];
+    }
+    s += __shfl_xor(s, 32);
+    if (lh == 0) {
+        sm[w][lj] = m;
+        ss[w][lj] = s;
+    }
+    __syncthreads();
+    if (w == 1 && fz.gauge_prev && blockIdx.x == 0) {
+        // what the g-update before this f-update measured (see GaugeMode), in a fixed order
+        double t = 0.0;
+        for (int64_t i = l; i < fz.gauge_prev_cnt; i += 64) t += fz.gauge_prev[i];
+        for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off);
+        if (l == 0) {
+            const double prev = fz.gauge_scalars[0];
+            fz.gauge_scalars[1] = prev;
+            fz.gauge_scalars[0] = prev + ((t > 0.0 && t < INFINITY) ? fz.gauge_prev_eps * log(t) : 0.0);
+        }
+    }
+    if (w != 0) return;
+    const int64_t i = row0 + lj;
+    double mass = 0.0;
+    if (lh == 0 && i < fz.cnt) {
+        double M = (double)sm[0][lj];
+#pragma unroll
+        for (int k = 1; k < kSmallWaves; ++k) M = fmax(M, (double)sm[k][lj]);
+        double S = 0.0, dev = 0.0, bias = 0.0;
+#pragma unroll
+        for (int k = 0; k < kSmallWaves; ++k) S += rescale_split(ss[k][lj], (double)sm[k][lj], M);
+        finalize_point(fz, i, M, S, &dev, &mass, &bias);
+    }
+    if (fz.gauge_out) {
+        for (int off = 16; off > 0; off >>= 1) mass += __shfl_xor(mass, off);
+        if (l == 0) fz.gauge_out[blockIdx.x] = mass;
+    }
+}
+
 // ---- plan application (Alg. 2 / Alg. 4): the same pass with a value accumulator ----------
 // Every lane owns ONE resident row and PC columns of the output; the streamed tile carries
 // the PC values of each streamed point next to its coordinates.
@@ -1087,6 +1211,38 @@ fs_status lowd_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, 
     prof_end(c);
     FS_HIP(c, hipGetLastError());
     *splits_out = s.splits;
+    return FS_OK;
+}
+
+template <int KS>
+void launch_half_small(unsigned blocks, hipStream_t st, const SplitArgs &a, const FinalizeArgs &fz, int n_groups)
+{
+    hipLaunchKernelGGL((k_half_lowd_small<KS, false>), dim3(blocks), dim3(64 * kSmallWaves), 0, st, a, fz, n_groups);
+}
+
+// The half-step in one launch, where the problem is small enough and runs on the split records; *done = false: nothing
+// was launched.  `fz` as launch_finalize makes it (partial and splits unused).
+fs_status lowd_half_small(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, const FinalizeArgs &fz, bool *done)
+{
+    *done = false;
+    if (!lowd_small(P->X.cnt, P->Y.cnt, P->d) || c->dbg_lowd_splits) return FS_OK;   // (a forced split count asks for the split kernels)
+    SplitArgs a;
+    bool precise = false;
+    fs_status st;
+    if (!split_pass_args(c, P, res, str, eps, P->partial, &a, &precise, &st)) return st;
+    const int n_groups = (int)ceil_div(str->cnt, 32);
+    const unsigned blocks = (unsigned)ceil_div(res->cnt, 32);
+    if ((int64_t)blocks * 32 > res->cnt_pad || (int64_t)n_groups * 32 > str->cnt_pad)
+        return fail(c, FS_ERR_DEVICE, "internal: low-d launch shape exceeds the padded buffers");
+    prof_begin(c, (double)res->cnt * (double)str->cnt, precise ? 1 : 0);
+    if (precise) {
+        hipLaunchKernelGGL((k_half_lowd_small<3, true>), dim3(blocks), dim3(64 * kSmallWaves), 0, c->stream, a, fz, n_groups);
+    } else {
+        FS_SPLIT_KS_DISPATCH(P->ks, (launch_half_small<KS_>(blocks, c->stream, a, fz, n_groups)));
+    }
+    prof_end(c);
+    FS_HIP(c, hipGetLastError());
+    *done = true;
     return FS_OK;
 }
 

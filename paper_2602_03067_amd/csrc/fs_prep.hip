@@ -57,16 +57,29 @@ __global__ __launch_bounds__(256) void k_coord_sums(CloudIn c0, CloudIn c1, int 
     const void *pts = cl.pts;
     const int64_t rows = cl.rows, ld = cl.ld;
     double *part = cl.part;
-    __shared__ double sh[256];
+    // (all sixteen accumulators in registers, and one reduction over the wave per coordinate in use: sixteen block-wide
+    // reductions through LDS took 13.7 us whatever the size)
+    __shared__ double sh[4][kLowdMaxD];
     double acc[kLowdMaxD];
+#pragma unroll
     for (int k = 0; k < kLowdMaxD; ++k) acc[k] = 0.0;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < rows; i += (int64_t)gridDim.x * 256)
-        for (int k = 0; k < d; ++k) acc[k] += (double)load_pt(pts, dtype, i * ld + k);
-    for (int k = 0; k < kLowdMaxD; ++k) {
-        double t = block_sum_256(acc[k], sh);
-        if (threadIdx.x == 0) part[(int64_t)blockIdx.x * kLowdMaxD + k] = t;
-        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kLowdMaxD; ++k)
+            if (k < d) acc[k] += (double)load_pt(pts, dtype, i * ld + k);
+#pragma unroll
+    for (int k = 0; k < kLowdMaxD; ++k)
+        if (k < d) {
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) acc[k] += __shfl_xor(acc[k], off);
+        }
+    if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+        for (int k = 0; k < kLowdMaxD; ++k) sh[threadIdx.x >> 6][k] = acc[k];
     }
+    __syncthreads();
+    if (threadIdx.x < kLowdMaxD)
+        part[(int64_t)blockIdx.x * kLowdMaxD + threadIdx.x] = sh[0][threadIdx.x] + sh[1][threadIdx.x] + sh[2][threadIdx.x] + sh[3][threadIdx.x];
 }
 
 // stage 2: mean[k] = (sum of partX[.][k] + sum of partY[.][k]) / (n + m).  One block of 256: thread
@@ -610,55 +623,70 @@ __global__ __launch_bounds__(256) void k_weighted_sums(int64_t cnt, const float 
 // A block of 256 threads covers 256 / PC rows; thread (row, c) produces one output entry, so the
 // reads of the [splits][rows][PC] accumulators are contiguous; the row's max and factor are
 // computed once (by its thread c = 0) and shared.  (When PC does not divide 256 the last 256 % PC threads idle.)
-__global__ __launch_bounds__(256) void k_apply_finalize(const double2 *partial, int64_t stride, const float *opart,
-                                                        int64_t opart_stride, int PC_n, int PC_alt, int splits_n, int splits_alt,
-                                                        FxGate gate, int64_t cnt,
-                                                        double inv_eps, const float *w, double log_uniform,
-                                                        const double *pot, const double *res_norm, int p0, int p,
-                                                        float *out, int64_t ldo, float *mass_out)
+struct ApplyFinalizeArgs {
+    const double2 *partial;
+    int64_t stride;
+    const float *opart;
+    int64_t opart_stride;
+    int PC, splits, PC_alt, splits_alt;   // (alt: where the gate chose the float64 kernel of the pass)
+    FxGate gate;
+    int64_t cnt;
+    double inv_eps;
+    const float *w;
+    double log_uniform;
+    const double *pot, *res_norm;
+    int p0, p;
+    float *out;
+    int64_t ldo;
+    float *mass_out;
+};
+// ALT: one of two kernels wrote the accumulators; the grid fits the row length of the first, so where the gate chose the
+// other, whose rows may be longer, a block takes several groups of rows
+template <bool ALT>
+__global__ __launch_bounds__(256) void k_apply_finalize(ApplyFinalizeArgs a)
 {
     __shared__ double shM[256], shFac[256];
-    const bool alt = splits_alt && !gate.on();
-    const int PC = alt ? PC_alt : PC_n, splits = alt ? splits_alt : splits_n;
+    const bool alt = ALT && !a.gate.on();
+    const int PC = alt ? a.PC_alt : a.PC, splits = alt ? a.splits_alt : a.splits;
     const int rows_per_block = 256 / PC;
     const int rl = threadIdx.x / PC, c = threadIdx.x - rl * PC;
-    // (the grid fits PC_n; where the other kernel has longer rows, a block takes several groups of rows)
-    for (int64_t base = (int64_t)blockIdx.x * rows_per_block; base < cnt; base += (int64_t)gridDim.x * rows_per_block) {
-    const int64_t i = rl < rows_per_block ? base + rl : cnt;   // (idle threads: no row)
-    if (c == 0 && i < cnt) {
-        double M = -INFINITY;
-#pragma unroll 8
-        for (int k = 0; k < splits; ++k) {
-            double mk = partial[(int64_t)k * stride + i].x;
-            M = mk > M ? mk : M;
-        }
-        double lw = w ? log((double)w[i]) : log_uniform;
-        // row factor  a_i * exp(fhat_i/eps + m_i): add the exponents BEFORE exponentiating
-        const double fac = exp2(((pot[i] - res_norm[i]) * inv_eps + lw) * kLog2e + M);
-        shM[rl] = M;
-        shFac[rl] = fac;
-        if (mass_out && p0 == 0) {
-            double S = 0.0;
+    for (int64_t base = (int64_t)blockIdx.x * rows_per_block; base < a.cnt; base += (int64_t)gridDim.x * rows_per_block) {
+        const int64_t i = rl < rows_per_block ? base + rl : a.cnt;   // (idle threads: no row)
+        if (c == 0 && i < a.cnt) {
+            double M = -INFINITY;
 #pragma unroll 8
             for (int k = 0; k < splits; ++k) {
-                double2 ms = partial[(int64_t)k * stride + i];
-                S += rescale_split(ms.y, ms.x, M);
+                double mk = a.partial[(int64_t)k * a.stride + i].x;
+                M = mk > M ? mk : M;
             }
-            mass_out[i] = (float)(fac * S);
+            double lw = a.w ? log((double)a.w[i]) : a.log_uniform;
+            // row factor  a_i * exp(fhat_i/eps + m_i): add the exponents BEFORE exponentiating
+            const double fac = exp2(((a.pot[i] - a.res_norm[i]) * a.inv_eps + lw) * kLog2e + M);
+            shM[rl] = M;
+            shFac[rl] = fac;
+            if (a.mass_out && a.p0 == 0) {
+                double S = 0.0;
+#pragma unroll 8
+                for (int k = 0; k < splits; ++k) {
+                    double2 ms = a.partial[(int64_t)k * a.stride + i];
+                    S += rescale_split(ms.y, ms.x, M);
+                }
+                a.mass_out[i] = (float)(fac * S);
+            }
         }
-    }
-    __syncthreads();
-    if (i < cnt && p0 + c < p) {
-    const double M = shM[rl];
-    double acc = 0.0;
+        __syncthreads();
+        if (i < a.cnt && a.p0 + c < a.p) {
+            const double M = shM[rl];
+            double acc = 0.0;
 #pragma unroll 4
-    for (int k = 0; k < splits; ++k) {
-        const double mk = partial[(int64_t)k * stride + i].x;
-        acc += rescale_split((double)opart[((int64_t)k * opart_stride + i) * PC + c], mk, M);
-    }
-    out[i * ldo + p0 + c] = (float)(shFac[rl] * acc);
-    }
-    __syncthreads();
+            for (int k = 0; k < splits; ++k) {
+                const double mk = a.partial[(int64_t)k * a.stride + i].x;
+                acc += rescale_split((double)a.opart[((int64_t)k * a.opart_stride + i) * PC + c], mk, M);
+            }
+            a.out[i * a.ldo + a.p0 + c] = (float)(shFac[rl] * acc);
+        }
+        if (!ALT) break;
+        __syncthreads();
     }
 }
 
@@ -705,9 +733,14 @@ fs_status launch_apply_finalize(Ctx *c, const Prepared *P, const Side *res, cons
                                 float *mass_out, int PC_alt)
 {
     if (PC < 1 || PC > 256 || (splits.alt && (PC_alt < 1 || PC_alt > 256))) return fail(c, FS_ERR_DEVICE, "internal: accumulator width of the application merge");
-    hipLaunchKernelGGL(k_apply_finalize, dim3((unsigned)ceil_div(res->cnt, 256 / PC)), dim3(256), 0, c->stream,
-                       (const double2 *)P->partial, res->cnt_pad, opart, res->cnt_pad, PC, PC_alt, splits.n, splits.alt, fx_gate(P, eps), res->cnt, 1.0 / eps,
-                       res->w, res->log_uniform, res->pot, res_norm, p0, p, out, ldo, mass_out);
+    const ApplyFinalizeArgs a{(const double2 *)P->partial, res->cnt_pad, opart,           res->cnt_pad, PC,       splits.n,  PC_alt, splits.alt, fx_gate(P, eps),
+                              res->cnt,                    1.0 / eps,    res->w,          res->log_uniform,       res->pot,  res_norm, p0,       p,
+                              out,                         ldo,          mass_out};
+    const dim3 grid((unsigned)ceil_div(res->cnt, 256 / PC));
+    if (splits.alt)
+        hipLaunchKernelGGL(k_apply_finalize<true>, grid, dim3(256), 0, c->stream, a);
+    else
+        hipLaunchKernelGGL(k_apply_finalize<false>, grid, dim3(256), 0, c->stream, a);
     FS_HIP(c, hipGetLastError());
     return FS_OK;
 }
@@ -961,16 +994,34 @@ static FinalizeArgs finalize_args(const Prepared *P, const void *partial, Side *
     return a;
 }
 
-fs_status launch_gauge_export(Ctx *c, const Prepared *P, bool collect_last, double eps_last, const double *x_pot,
+fs_status launch_gauge_export(Ctx *c, const Prepared *P, int64_t collect_last, double eps_last, const double *x_pot,
                               float *f_user, float *g_user)
 {
     if (collect_last)
-        hipLaunchKernelGGL(k_gauge_collect, dim3(1), dim3(256), 0, c->stream, P->gauge_part, (int64_t)ceil_div(P->Y.cnt, 256),
-                           eps_last, P->scalars + 8);
+        hipLaunchKernelGGL(k_gauge_collect, dim3(1), dim3(256), 0, c->stream, P->gauge_part, collect_last, eps_last, P->scalars + 8);
     hipLaunchKernelGGL(k_gauge_export, dim3((unsigned)ceil_div(P->X.cnt + P->Y.cnt, 256)), dim3(256), 0, c->stream, x_pot,
                        P->X.cnt, P->Y.pot, P->Y.cnt, P->scalars + 8, f_user, g_user);
     FS_HIP(c, hipGetLastError());
     return FS_OK;
+}
+
+static void set_gauge(FinalizeArgs *a, const Prepared *P, GaugeMode gauge, int64_t prev_cnt, double prev_eps)
+{
+    if (gauge == GaugeMode::Measure) a->gauge_out = P->gauge_part;
+    if (gauge == GaugeMode::Collect && prev_cnt > 0) {
+        a->gauge_prev = P->gauge_part;
+        a->gauge_prev_cnt = prev_cnt;
+        a->gauge_prev_eps = prev_eps;
+        a->gauge_scalars = P->scalars + 8;
+    }
+}
+
+FinalizeArgs make_finalize_args(const Prepared *P, Side *res, const double *res_norm, double eps_cur, double eps_next_bias,
+                                float *user_out, GaugeMode gauge, int64_t gauge_prev_cnt, double gauge_prev_eps)
+{
+    FinalizeArgs a = finalize_args(P, nullptr, res, res_norm, Splits(), eps_cur, eps_next_bias, user_out, nullptr, 1.0, nullptr);
+    set_gauge(&a, P, gauge, gauge_prev_cnt, gauge_prev_eps);
+    return a;
 }
 
 fs_status launch_finalize(Ctx *c, const Prepared *P, Side *res, const double *res_norm, Splits splits, double eps_cur,
@@ -980,13 +1031,7 @@ fs_status launch_finalize(Ctx *c, const Prepared *P, Side *res, const double *re
     double *dev_part = abs_dev_sum ? P->dev_part : nullptr;   // per-block sums of the marginal deviation
     FinalizeArgs a = finalize_args(P, P->partial, res, res_norm, splits, eps_cur, eps_next_bias, user_out, dev_part,
                                    mix, save_old);
-    if (gauge == GaugeMode::Measure) a.gauge_out = P->gauge_part;
-    if (gauge == GaugeMode::Collect && gauge_prev_cnt > 0) {
-        a.gauge_prev = P->gauge_part;
-        a.gauge_prev_cnt = (int64_t)ceil_div(gauge_prev_cnt, 256);
-        a.gauge_prev_eps = gauge_prev_eps;
-        a.gauge_scalars = P->scalars + 8;
-    }
+    set_gauge(&a, P, gauge, gauge_prev_cnt, gauge_prev_eps);
     hipLaunchKernelGGL(k_finalize, dim3((unsigned)a.blocks), dim3(256), 0, c->stream, a);
     if (abs_dev_sum)
         hipLaunchKernelGGL(k_sum_to, dim3(1), dim3(256), 0, c->stream, dev_part, (int64_t)a.blocks, abs_dev_sum);

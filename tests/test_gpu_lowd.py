@@ -567,3 +567,39 @@ def test_alternative_launch_shapes_and_kernels_agree(ctx, oracle, hook, value):
         ctx.fs_debug_set(hook, 0)
     assert max_err_over_eps(f_gpu, oracle.update_f(x, y, b, eps, g), eps) <= TOL
     assert max_err_over_eps(g_gpu, oracle.update_g(x, y, a, eps, f), eps) <= TOL
+
+
+@pytest.mark.parametrize("n,m,d", [(1, 1, 1), (31, 33, 2), (32, 257, 3), (33, 300, 3), (1, 5000, 3), (5000, 1, 2), (700, 255, 7), (256, 900, 12),
+                                   (1000, 1030, 16), (7001, 7100, 3)])
+@pytest.mark.parametrize("score", [32, 64])
+def test_half_steps_in_one_launch(oracle, n, m, d, score):
+    """Small problems run a half-step and its merge in one kernel: against the oracle, and against the split kernels, which
+    a forced split count asks for.  Both are exact to a few 1e-8 of the sums; what is left is the rounding of a float
+    output, 2^-24 |f| (and, with fp32 scores, of scores of up to 2 log2e / eps = 58 base-2 units: 2^-18)."""
+    if score == 64 and d > 3:
+        pytest.skip("float64-grade scores at d > 3 run on the fp64 kernels")
+    rng = np.random.default_rng(n + 3 * m + 5 * d)
+    x, y = rng.random((n, d)).astype(np.float32), (rng.random((m, d)) * 0.8 + 0.1).astype(np.float32)
+    a, b = rng.random(n) + 0.1, rng.random(m) + 0.1
+    a, b = (a / a.sum()).astype(np.float32), (b / b.sum()).astype(np.float32)
+    eps = float(np.float32(0.05 * d))
+    g = (0.5 * eps * rng.standard_normal(m)).astype(np.float32)
+    say("one-launch half-steps n=%d m=%d d=%d score=%d" % (n, m, d, score))
+    prob = make_problem(x, y, a, b)
+    out = []
+    for splits in (0, 1):
+        c = binding.Context(0)
+        c.fs_debug_set("lowd_score", score)
+        c.fs_debug_set("lowd_splits", splits)
+        f = c.fs_update_f(prob, eps, dev(g))
+        fs, gs = torch.zeros(n, device="cuda:0"), dev(g)
+        c.fs_solve(prob, 4 * eps, eps, 2, 3, fs, gs)
+        out.append((host(f), host(fs), host(gs)))
+        c.close()
+    want = oracle.update_f(x, y, b, eps, g)
+    tol = (1e-6 if score == 64 else 1e-5) * eps + 2.0 ** -24 * np.abs(want).max() * 1.01
+    assert np.abs(out[0][0] - want).max() <= tol
+    fo, go = oracle.solve(x, y, a, b, 4 * eps, eps, 2, 3, g0=g)
+    for k, ref in ((1, fo), (2, go)):   # twelve half-steps, each adding at most its own error
+        assert np.abs(out[0][k] - out[1][k]).max() <= 12 * tol
+        assert np.abs(out[0][k] - ref).max() <= 12 * tol
