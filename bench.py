@@ -26,7 +26,7 @@ if ROOT not in sys.path:
 # MI355X fp32 vector peak: 256 CUs x 4 SIMDs x 32 lanes x 2.4 GHz = 78.64e12 lane-operations
 # per second (x 2 flop per FMA = the published 157.3 TFLOP/s).
 VALU_LANE_SLOTS_PER_S = 256 * 4 * 32 * 2.4e9
-PEAKS = {"bf16": 2.5e15, "f64": 78.6e12}
+PEAKS = {"bf16": 2.5e15, "i8": 5.0e15, "f64": 78.6e12}
 # HBM bytes per launch of the dominant kernel: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this script on the
 # default size of each workload, scaled by what the same counters read for a 1 GiB device copy in the same run.
 # These are NOT measured by this run (they need the profiler); each entry names the summary under profiles/ it was
@@ -35,7 +35,6 @@ MEASURED_TRAFFIC = {
     "lowdim_anneal": (191.79e6, "profiles/lse_lowd_split__lowdim_anneal.txt"),
     "mnist_shape": (16499.31e6, "profiles/lse_bf16__mnist_shape.txt"),
     "embedding": (4391.51e6, "profiles/lse_bf16__embedding.txt"),
-    "transport_grad": (77.17e6, "profiles/pass_f64__transport_grad.txt"),
 }
 PER_CONFIG = ("tiny", "mnist_shape", "embedding", "transport_grad")
 
@@ -170,6 +169,14 @@ def run_workload(name, steps, warmup, schedule="alternating", n_override=None, c
         roof = {"bound": "mfma", "achieved": flops / (avg_ms * 1e-3) / 1e12, "peak": PEAKS["bf16"] / 1e12,
                 "unit": "TFLOP/s"}
         dtype = "bf16"
+    elif 16 < w.d <= 128 and float(w.n) * w.m * w.d >= 4.0e8:
+        # fixed-point scores: thirteen digit products per coordinate (ten where cscale r2^2 <= 128) on the int8 matrix cores
+        flops = 2.0 * ((w.d + 31) // 32 * 32) * 13 * pairs
+        roof = {"bound": "mfma", "achieved": flops / (avg_ms * 1e-3) / 1e12, "peak": PEAKS["i8"] / 1e12,
+                "unit": "TOP/s"}
+        # the contraction itself as float operations against the fp32 vector peak (157.3 TFLOP/s)
+        roof["frac_of_fp32_vector_peak"] = 2.0 * w.d * pairs / (avg_ms * 1e-3) / 157.3e12
+        dtype = "f32"
     elif w.d > 16:
         flops = 2.0 * w.d * pairs
         roof = {"bound": "mfma", "achieved": flops / (avg_ms * 1e-3) / 1e12, "peak": PEAKS["f64"] / 1e12,

@@ -30,10 +30,11 @@
 // A workgroup is four waves = 128 resident rows (their digits stay in registers) over a run of
 // streamed tiles that pass through an LDS ring; two workgroups per CU.
 //
-// Bound: the card's power limit.  A loop of nothing but this MFMA runs at 15.6 ns per instruction and
-// SIMD with constant operands and at 20 with random ones (the clock falls from 2.05 to 1.6 GHz), and the
-// vector work beside it (about 150 instructions per tile of 32 x 32 scores) adds to that instead of
-// hiding: 20 MFMAs and 112 vector instructions measured 580 ns alone, this kernel 700 to 730 ns per tile.
+// Bound: matrix and vector instructions together, which do not hide behind each other with these operands.  A loop of
+// nothing but this MFMA takes 15.6 ns per instruction and SIMD with constant operands and 20 with random ones; with seven
+// vector instructions after two of every three MFMAs 17.7 and 24 (whether they come from the same wave or another), so the
+// chip's power is what runs out.  A tile of 32 x 32 scores at d = 64 is 20 or 26 MFMAs and about 190 vector instructions:
+// 700 to 800 ns (counters: matrix pipe busy 46 %, vector ALU 48 %, clock 2.0 GHz).
 // Tried without gain: tile g + 1's MFMAs interleaved with tile g's vector work in one wave (216-226 us
 // against 211 at n = m = 16384, d = 64), three workgroups per CU, digits read from LDS twice instead of held.
 // Measured (half-step with its merge, us): n = m = 16384, d = 64: 577 fp64 -> 178 with ten products, 208 with
