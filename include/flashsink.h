@@ -6,7 +6,8 @@
  * target points y in R^{m x d} with weights b, cost C_ij = |x_i - y_j|^2,
  * regularisation eps > 0, dual potentials f in R^n, g in R^m.  Every half-step
  * is evaluated as a streaming row-wise LogSumExp of biased dot-product scores
- * (Prop. 1); no n x m matrix is ever stored.
+ * (Prop. 1); no n x m matrix is stored as a whole (bf16-mode applications to many
+ * columns keep a slab of plan entries, at most 256 MB, in the workspace).
  *
  * Conventions common to all entry points
  *  - Every pointer inside fs_problem and every pointer argument is a DEVICE
@@ -265,13 +266,14 @@ fs_status fs_divergence(fs_ctx *ctx, const fs_problem *prob, float eps, int32_t 
 
 /*
  * out = P V with P_ij = a_i b_j exp((f_i + g_j - C_ij)/eps) for ANY potentials
- * (Prop. 3, Alg. 2): streaming passes, P never stored.
+ * (Prop. 3, Alg. 2): streaming passes, P never stored as a whole.
  * V: m x p (ldv), out: n x p (ldo), r_out: NULL or n floats receiving P 1_m.
  * The gradient of Cor. 4 is 2*(diag(a) x - P y) (or with r_out in place of a, App. G).
  * Cost: a pass recomputes all n m scores and takes a block of value columns, so a call is
  * one pass for p <= 8 and ceil(p / 15) passes beyond at d <= 16,
  * ceil(p / 64) passes at d > 16 (when p > 64: ceil(p / 128) with FS_COMPUTE_FP32, ceil(p / 96) with
- * FS_COMPUTE_BF16_MFMA).
+ * FS_COMPUTE_BF16_MFMA).  Where P's entries and the product are cheaper apart, FS_COMPUTE_BF16_MFMA with p > 96
+ * computes them once, slab by slab (at most 256 MB of bfloat16 entries), and multiplies all columns from there.
  * Accuracy at d <= 16, FS_COMPUTE_FP32: every plan entry enters the products to 2^-17 relative
  * (1e-6 to 3e-6 of the result's norm in practice), values to 24 bits (p <= 8) or 2^-17 (p > 8).
  */
