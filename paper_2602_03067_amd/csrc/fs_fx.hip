@@ -340,6 +340,11 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
             T.P[r] = (int)((c - h) * 65536.0);
             T.Q[r] = 0;
         }
+        // (MODE 2: a lane's outputs are columns, half of them, while the NaN score is in one lane half: common to the two)
+        if constexpr (MODE == 2) {
+            const int other = __shfl_xor((int)nan, 32);   // (by all lanes, so not behind the ||)
+            nan = nan || other != 0;
+        }
         if (nan) scale_sums(NAN);
         u3v = 1.52587890625e-05f;
         u5v = 2.3283064365386963e-10f;

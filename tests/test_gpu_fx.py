@@ -122,6 +122,25 @@ def test_values_that_are_not_finite(ctx):
     assert np.isnan(fu[7]) and np.isfinite(np.delete(fu, 7)).all()
 
 
+@pytest.mark.parametrize("point", [66, 5])   # one in each half of a wave: bit 2 of the number within a tile
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+def test_potentials_that_are_not_finite(ctx, point, value):
+    """A NaN or +inf potential of one streamed point leaves no finite entry in any row, whatever form the product takes."""
+    eps = float(np.float32(1.0))
+    n, m, d = 70, 90, 33
+    rng, x, y, a, b = _problem(6, n, m, d)
+    prob = make_problem(x, y, a, b)
+    f, g = np.zeros(n, dtype=np.float32), np.zeros(m, dtype=np.float32)
+    g[point] = value
+    say("fx potential %g at %d" % (value, point))
+    assert not np.isfinite(host(ctx.fs_update_f(prob, eps, dev(g)))).any()
+    for p in (3, 40):
+        V = rng.standard_normal((m, p)).astype(np.float32)
+        assert not np.isfinite(host(ctx.fs_apply_plan(prob, eps, dev(f), dev(g), dev(V)))).any()
+        A = rng.standard_normal((n, d)).astype(np.float32)
+        assert not np.isfinite(host(ctx.fs_apply_plan_hadamard(prob, eps, dev(f), dev(g), dev(A), dev(V)))).any()
+
+
 @pytest.mark.parametrize("n,m,d", [(40, 70, 24), (130, 97, 64), (33, 129, 128)])
 def test_hadamard_weights(ctx, n, m, d):
     """Rows of A of very different sizes, a zero row, columns beyond one block of 32."""
