@@ -367,6 +367,7 @@ fs_status fs_points_release(fs_ctx *ctx);
  *   "lowd_precise_valu"  1: float64-grade scores at d <= 3 on the vector ALU instead of the matrix cores
  *   "lowd_precise_any_bias"  1: those matrix-core records also for biases beyond their digit range
  *   "fx_any_size"        1: fixed-point scores (16 < d <= 128, FS_COMPUTE_FP32) for problems of any size
+ *   "fx_splits"          number of splits of the streamed side of a fixed-point pass, 0..1024
  * Unknown keys and values out of range: FS_ERR_INVALID_ARG.  key: HOST string.
  */
 fs_status fs_debug_set(fs_ctx *ctx, const char *key /* host */, int64_t value);

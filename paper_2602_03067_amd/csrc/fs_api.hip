@@ -1201,7 +1201,9 @@ fs_status fs_debug_set(fs_ctx *ctx, const char *key, int64_t value)
     else if (k == "fx_any_size" && (value == 0 || value == 1)) {
         c->dbg_fx_any_size = (int)value;
         c->kept_valid = false;   // (the layout depends on it)
-    } else
+    } else if (k == "fx_splits" && value >= 0 && value <= 1024)
+        c->dbg_fx_splits = (int)value;
+    else
         return fail(c, FS_ERR_INVALID_ARG, "unknown switch or value out of range: %s = %lld", key, (long long)value);
     return FS_OK;
 }

@@ -98,7 +98,7 @@ struct FxArgs {
 // operand of a second MFMA against the values in three bf16 pieces.  Six of the nine piece products are
 // kept; those dropped are below 2^-25 of a product, less than one rounding of an fp32 accumulation.
 // HAD (with MODE 2): Hadamard-weighted application (Alg. 5), every exponential times <row of A, streamed point>, which is
-// a second contraction of the same streamed digits with those of A (a scale per row; ten products).
+// a second contraction of the same streamed digits with those of A (a scale per row; thirteen products).
 template <int KS, int MODE, int NC, bool HAD = false> struct FxShape {
     static constexpr int kValBytes = MODE == 0 ? 0 : MODE == 1 ? (NC + 1) / 2 * 256 : NC * 6 * 1024;
     static constexpr int kStage = KS * 4096 + kRecBytes + kValBytes;
@@ -418,6 +418,18 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
             for (int r = 0; r < 16; ++r) H[r] = Q[r] = P[r] = 0;
             const unsigned char *fr = sb + l16;
 #define FX_MW(ACC, I, J) ACC = __builtin_amdgcn_mfma_i32_32x32x32_i8(f[I], bw[ks][J], ACC, 0, 0, 0)
+            // (all thirteen products: a weight may be a small remainder of large products, and nothing else of it is rounded)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                i4 f[4];
+#pragma unroll
+                for (int dg = 1; dg < 4; ++dg) f[dg] = *reinterpret_cast<const i4 *>(fr + (ks * 4 + dg) * 1024);
+                FX_MW(P, 3, 1);
+                FX_MW(P, 2, 2);
+                FX_MW(P, 1, 3);
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) P[r] = P[r] >> 8;
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
                 i4 f[4];
@@ -673,6 +685,13 @@ PassShape fx_shape(const Ctx *c, int64_t n_res, int64_t n_str, int occ)
     const int n_tiles = (int)ceil_div(n_str, 32);
     int cap = max_splits(c->partial_budget, n_res);
     if (cap > n_tiles) cap = n_tiles;
+    if (c->dbg_fx_splits > 0) {
+        const int sp = c->dbg_fx_splits < cap ? c->dbg_fx_splits : cap;
+        const int tps = (int)ceil_div(n_tiles, sp);
+        s.splits = (int)ceil_div(n_tiles, tps);
+        s.cols_per_split = (int64_t)tps * 32;
+        return s;
+    }
     const double startup = 4.0;
     double best = 0.0;
     int best_tps = n_tiles;

@@ -207,6 +207,7 @@ struct Ctx {
     int dbg_lowd_precise_valu = 0;   // 1: float64 scores at d <= 3 on the vector ALU instead of the precise records
     int dbg_lowd_any_bias = 0;       // 1: the precise records also for biases beyond their digit range (tests of that case)
     int dbg_fx_any_size = 0;         // 1: digit images for problems of any size
+    int dbg_fx_splits = 0;           // forced split count of the streamed side of a fixed-point pass
     // profiling of the streaming LSE launches
     bool prof_on = false;
     std::vector<hipEvent_t> ev_pool;   // pairs (start, stop)

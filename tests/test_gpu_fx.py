@@ -165,3 +165,64 @@ def test_hadamard_weights(ctx, n, m, d):
         scale = np.abs(W).sum(1, keepdims=True) * np.abs(V).max() + 1e-300
         assert (np.abs(got - want) / scale).max() <= 1e-6
         assert np.all(got[1] == 0.0)
+
+
+# Streams of many tiles through one workgroup: what the small shapes above, where every workgroup has one tile, never reach
+# (slots of the LDS ring used again, the max lifted with sums in hand, tiles with and without the float64 epilogue in turn,
+# the alternating sign of the second product).
+PROFILES = ["flat", "rise", "steep", "fall", "mixed"]
+
+
+def _stream(rng, m, eps, profile):
+    """Potentials of the streamed points in units of eps, and the points without weight."""
+    t = np.arange(m) // 32
+    g = rng.standard_normal(m)
+    dead = np.zeros(m, dtype=bool)
+    if profile == "rise":        # by more than the 4 base-2 units that a running max may lag behind, every tile
+        g += 8.0 * t
+    elif profile == "steep":     # by more than 2^10, beyond the bias records for the later tiles
+        g += 1000.0 * t
+    elif profile == "fall":
+        g -= 700.0 * t
+    elif profile == "mixed":
+        dead[[0, 3, 37]] = True                    # the first tile, and a tile after one that is whole
+        dead[6 * 32:8 * 32] = True                 # tiles without any weight
+        g[5 * 32 + 9] += 1.0e5                     # far above, in the middle
+        g[9 * 32:9 * 32 + 3] -= 1.0e5              # far below
+        g[m - 1] += 1.0e5 + 3.0                    # the last, ragged tile
+    return (g * eps).astype(np.float32), dead
+
+
+@pytest.mark.parametrize("d", [20, 50, 90, 128])
+@pytest.mark.parametrize("eps", [0.5, 0.03])       # ten and thirteen digit products
+@pytest.mark.parametrize("splits", [1, 2])
+def test_many_tiles_per_workgroup(oracle, d, eps, splits):
+    n, m = 140, 13 * 32 + 7
+    eps = float(np.float32(eps))
+    c = binding.Context(0)
+    c.fs_debug_set("fx_any_size", 1)
+    c.fs_debug_set("fx_splits", splits)
+    for k, profile in enumerate(PROFILES):
+        rng, x, y, a, b = _problem(100 * d + k, n, m, d)
+        g, dead = _stream(rng, m, eps, profile)
+        b[dead] = 0.0
+        prob = make_problem(x, y, a, b)
+        say("fx many tiles d=%d eps=%g splits=%d %s" % (d, eps, splits, profile))
+        want = oracle.update_f(x, y, b, eps, g)
+        _check_pot(c.fs_update_f(prob, eps, dev(g)), want, eps)
+        f = want.astype(np.float32)
+        for p in (3, 40):
+            V = rng.standard_normal((m, p)).astype(np.float32)
+            _check_values(c.fs_apply_plan(prob, eps, dev(f), dev(g), dev(V)), oracle.apply_plan(x, y, a, b, eps, f, g, V))
+        # Hadamard weights: per row, since a row's weights share a scale
+        A = (rng.standard_normal((n, d)) * np.exp(rng.uniform(-3, 3, (n, 1)))).astype(np.float32)
+        V = rng.standard_normal((m, 2)).astype(np.float32)
+        X, Y = x.astype(np.float64), y.astype(np.float64)
+        cost = ((X[:, None, :] - Y[None, :, :]) ** 2).sum(2)
+        with np.errstate(over="ignore"):
+            P = a[:, None].astype(np.float64) * b[None, :] * np.exp((f[:, None].astype(np.float64) + g[None, :] - cost) / np.float64(eps))
+        W = P * (A.astype(np.float64) @ Y.T)
+        got = host(c.fs_apply_plan_hadamard(prob, eps, dev(f), dev(g), dev(A), dev(V)))
+        scale = np.abs(W).sum(1, keepdims=True) * np.abs(V).max() + 1e-300
+        assert (np.abs(got - W @ V.astype(np.float64)) / scale).max() <= 1e-6
+    c.close()
