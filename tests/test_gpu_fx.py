@@ -226,3 +226,108 @@ def test_many_tiles_per_workgroup(oracle, d, eps, splits):
         scale = np.abs(W).sum(1, keepdims=True) * np.abs(V).max() + 1e-300
         assert (np.abs(got - W @ V.astype(np.float64)) / scale).max() <= 1e-6
     c.close()
+
+
+@pytest.mark.parametrize("n,m,d", [(140, 423, 20), (300, 97, 50), (33, 700, 90), (260, 500, 128)])
+@pytest.mark.parametrize("splits", [0, 1])
+def test_paired_passes(oracle, n, m, d, splits):
+    """Both passes of an averaged iteration in one launch."""
+    eps = float(np.float32(0.2))
+    rng, x, y, a, b = _problem(n + m + d, n, m, d)
+    c = binding.Context(0)
+    c.fs_debug_set("fx_any_size", 1)
+    c.fs_debug_set("fx_splits", splits)
+    prob = make_problem(x, y, a, b)
+    say("fx paired passes n=%d m=%d d=%d splits=%d" % (n, m, d, splits))
+    f, g = torch.zeros(n, device="cuda:0"), torch.zeros(m, device="cuda:0")
+    c.fs_solve_symmetric(prob, eps, 7, f, g)
+    fo, go = oracle.solve_symmetric(x, y, a, b, eps, 7)
+    for got, want in ((f, fo), (g, go)):   # (seven iterations, each adding at most its own error)
+        assert np.all(np.abs(host(got) - want) <= 7e-6 * eps + 2.0 ** -24 * np.abs(want) * 1.01)
+    c.close()
+
+
+def test_annealing_across_the_gate(ctx, oracle):
+    """eps from where the weights no longer fit the bias records to where the scale is too large: the stages run on the
+    fp64 kernels, on ten and on thirteen digit products, and on the fp64 kernels again."""
+    n, m, d = 150, 210, 40
+    rng, x, y, a, b = _problem(8, n, m, d)
+    prob = make_problem(x, y, a, b)
+    say("fx annealing across the gate")
+    f, g = torch.zeros(n, device="cuda:0"), torch.zeros(m, device="cuda:0")
+    e0, e1 = float(np.float32(200.0)), float(np.float32(2e-4))
+    ctx.fs_solve(prob, e0, e1, 12, 3, f, g)
+    fo, go = oracle.solve(x, y, a, b, e0, e1, 12, 3)
+    # What an early half-step leaves is common to all points, (f + t, g - t), and not damped: at most 1e-6 of its eps each
+    # (measured: 1.6e-8 of the first eps).  The rest is damped by the half-steps after it.
+    t = float(np.median(host(f) - fo))
+    steps = 6 * sum(e0 * (e1 / e0) ** (s / 11) for s in range(12))
+    say("  common shift %.2e" % t)
+    assert abs(t) <= 1e-6 * steps
+    ulp = 2.0 ** -23 * max(np.abs(fo).max(), np.abs(go).max()) * 1.01   # of the potential itself, and of those t is taken from
+    for got, want, sign in ((f, fo, 1.0), (g, go, -1.0)):
+        assert np.abs(host(got) - sign * t - want).max() <= 1e-5 * e1 + ulp
+
+
+def _borrowed():
+    from tests import test_gpu_edge as e, test_gpu_f64 as q, test_gpu_grad as r, test_gpu_hadamard as h, test_gpu_hvp as w
+    from tests import test_gpu_labels as l, test_gpu_schedules as s, test_gpu_value as v
+    return {
+        "half steps": (q.test_single_half_steps, (300, 500, 64)),
+        "half steps d=33": (q.test_single_half_steps, (129, 1000, 33)),
+        "bf16 storage": (q.test_bf16_storage_in_fp32_mode, ()),
+        "trajectory": (q.test_transport_grad_trajectory_scaled_down, ()),
+        "apply": (q.test_apply_shapes, (257, 190, 40, 70)),
+        "apply wide": (q.test_apply_shapes, (150, 333, 100, 200)),
+        "gradients": (r.test_gradients_all_modes, (200, 333, 64, "fp32")),
+        "strides": (e.test_row_strides_larger_than_the_rows, (40, "fp32", 1e-4)),
+        "one context": (e.test_one_context_many_problems, ()),
+        "kept copies": (e.test_kept_derived_copies_change_nothing, (40, "fp32")),
+        "hadamard": (h.test_hadamard_transport_matches_dense_oracle, (150, 260, 64, 7, 6.0, 10, 0.2)),
+        "hvp": (w.test_hvp_matches_dense_oracle, (150, 260, 64, 6.0, 30)),
+        "labels": (l.test_labeled_cost_matches_dense_sinkhorn_on_the_explicit_cost, (200, 330, 40, 10, "fp32", 0.5, 0.5)),
+        "tolerance": (s.test_solve_tol_stops_where_the_oracle_does, (300, 260, 40, 0.15)),
+        "few rows": (s.test_few_rows_many_columns, (64, "fp32")),
+        "value": (v.test_value_matches_oracle_dual, (130, 257, 64, 1.0, 5)),
+        "divergence": (v.test_divergence_entry_point, (180, 410, 24, 0.5, 15)),
+    }
+
+
+@pytest.mark.parametrize("name", ["half steps", "half steps d=33", "bf16 storage", "trajectory", "apply", "apply wide", "gradients",
+                                  "strides", "one context", "kept copies", "hadamard", "hvp", "labels", "tolerance", "few rows",
+                                  "value", "divergence"])
+def test_entry_points_on_fixed_point_scores(ctx, oracle, monkeypatch, name):
+    """Tests of the other files, whose problems are small enough for the fp64 kernels, on the fixed-point ones."""
+    import inspect
+    make = binding.Context
+
+    def with_switch(*args, **kw):
+        c = make(*args, **kw)
+        c.fs_debug_set("fx_any_size", 1)
+        return c
+
+    monkeypatch.setattr(binding, "Context", with_switch)
+    fn, args = _borrowed()[name]
+    names = list(inspect.signature(fn).parameters)
+    given = [{"ctx": ctx, "oracle": oracle}[k] for k in names if k in ("ctx", "oracle")]
+    fn(*given, *args)
+
+
+def test_noalloc_without_room_for_digits():
+    """A solve whose digit images do not fit the static scratch array runs on the fp64 kernels there."""
+    n, d = 20000, 64
+    eps = float(np.float32(0.1))
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(3)
+    x, y = torch.rand(n, d, generator=gen, device="cuda:0"), torch.rand(n, d, generator=gen, device="cuda:0")
+    c = binding.Context(0)
+    prob = binding.Problem(x, y)
+    say("fx noalloc n=m=%d d=%d" % (n, d))
+    out = []
+    for solve in (c.fs_solve, c.fs_solve_noalloc):
+        f, g = torch.zeros(n, device="cuda:0"), torch.zeros(n, device="cuda:0")
+        solve(prob, eps, eps, 1, 2, f, g)
+        out.append((host(f), host(g)))
+    c.close()
+    for u, v in zip(*out):   # four half-steps on either side, and the rounding of two float outputs
+        assert np.all(np.abs(u - v) <= 8e-6 * eps + 2.0 ** -23 * np.abs(u) * 1.01)
