@@ -64,6 +64,7 @@ struct PassArgs {
     const float *hadA;       // [n_res][lda]
     int64_t lda, n_res;
     int d;                   // real number of coordinates (columns of hadA)
+    const double *had_add;   // [rows] or nullptr: summand of the weights of a row (points stored shifted, see k_had_digits)
     FxGate gate;             // r2 != nullptr: the fixed-point kernel of the same pass runs where the gate is on
 };
 
@@ -235,11 +236,16 @@ __device__ __forceinline__ void pass_f64_body(const PassArgs &a, const int bx, c
 
     d4 acc[JT];
     d4 accW[HAD ? JT : 1];   // <hadA row, streamed point> (Hadamard weights)
+    double w_add[HAD ? JT : 1];
+    if constexpr (HAD) {
+#pragma unroll
+        for (int jt = 0; jt < JT; ++jt) w_add[jt] = a.had_add ? a.had_add[row0 + 16 * jt + lj] : 0.0;
+    }
     auto zero_acc = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int jt = 0; jt < JT; ++jt) {
             acc[jt] = d4{0.0, 0.0, 0.0, 0.0};
-            if constexpr (HAD) accW[jt] = d4{0.0, 0.0, 0.0, 0.0};
+            if constexpr (HAD) accW[jt] = d4{w_add[jt], w_add[jt], w_add[jt], w_add[jt]};
         }
     };
 
@@ -684,7 +690,7 @@ fs_status f64_apply(Ctx *c, const Prepared *P, const Side *res, const Side *str,
         int pc = width;
         if (fx) {
             int fx_splits = 0;
-            fs_status st = fx_apply_pass(c, P, res, str, eps, V, p, ldv, p0, hadA, lda, &fx_splits, &pc);
+            fs_status st = fx_apply_pass(c, P, res, str, eps, V, p, ldv, p0, hadA, lda, &fx_splits, &pc, &a.had_add);
             if (st != FS_OK) return st;
             splits = Splits(fx_splits, s.splits);
         }

@@ -5,8 +5,9 @@
 // point relative to the clouds' common scale r2 (a power of two), split into four balanced base-256
 // digits,  x = r2 2^-31 sum_i D_i 2^(8 (4 - i)),  |D_1| <= 127, D_i in [-128, 127].  A product of two
 // points is then a sum over digit pairs (i, j) of weight 2^(64 - 8 (i + j)), and the thirteen pairs
-// with i + j <= 6 are kept: what is dropped (i + j >= 7) is below 2^-38 r2^2 sqrt(d / 64) rms, and the
-// gate (FxGate) sends problems whose scores would feel it to the fp64 kernels.
+// with i + j <= 6 are kept (ten, i + j <= 5, where the scores are small): what is dropped is 2^-38 r2^2 sqrt(d / 64)
+// rms for random digits, and the gate (FxGate, with the bounds for any digits) sends problems whose scores would feel
+// it, or the rounding of the coordinates, to the fp64 kernels.  The clouds are shifted first (k_prep_fx).
 //
 // The pairs of equal weight share an accumulator, and neighbouring weights share a register by
 // Horner's rule between MFMAs, so a score leaves the matrix cores as two integers:
@@ -91,6 +92,7 @@ struct FxArgs {
     // HAD: digit image of the rows of the Hadamard factor and their scales (see k_had_digits)
     const unsigned char *had;
     const float *had_scale;
+    const double *had_add;            // what the shift of the streamed points takes from the weights of a row
 };
 
 // MODE 0: log-sum-exp.  MODE 1: application to NC <= 4 columns on the vector ALU (one fma per score and
@@ -159,7 +161,7 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
 
     // resident digits: registers for the whole pass
     i4 b[KS][4], bw[HAD ? KS : 1][4];
-    float w3 = 0.0f, w5 = 0.0f;   // units of the Hadamard weights
+    double w3 = 0.0, w5 = 0.0, wadd = 0.0;   // units of the Hadamard weights
     {
         const unsigned char *rt = a.res + (row0 >> 5) * (KS * 4096) + l16;
 #pragma unroll
@@ -174,8 +176,9 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
         if constexpr (HAD) {
             const unsigned char *ht = a.had + (row0 >> 5) * (KS * 4096) + l16;
             const double sc = (double)a.had_scale[row0 + lj] * *a.gate.r2;
-            w3 = (float)ldexp(sc, -22);
-            w5 = (float)ldexp(sc, -38);
+            w3 = ldexp(sc, -22);
+            w5 = ldexp(sc, -38);
+            wadd = a.had_add[row0 + lj];
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
@@ -184,7 +187,7 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
             for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
                 for (int dg = 0; dg < 4; ++dg) asm volatile("" : "+v"(bw[ks][dg]));
-            asm volatile("" : "+v"(w3), "+v"(w5));
+            asm volatile("" : "+v"(w3), "+v"(w5), "+v"(wadd));
         }
     }
 
@@ -456,7 +459,10 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
             }
 #undef FX_MW
 #pragma unroll
-            for (int r = 0; r < 16; ++r) e[r] *= fmaf((float)(int)(((unsigned)Q[r] << 8) + (unsigned)P[r]), w5, (float)H[r] * w3);
+            for (int r = 0; r < 16; ++r) {
+                const int L = (int)(((unsigned)Q[r] << 8) + (unsigned)P[r]);
+                e[r] *= (float)fma((double)L, w5, fma((double)H[r], w3, wadd));
+            }
         }
         if constexpr (MODE == 2) {
             bf8 ep[2][3];
@@ -637,8 +643,10 @@ __global__ __launch_bounds__(512) void k_vimg_fx(const float *V, int64_t ldv, in
 }
 
 // Digit image of the rows of A [n][lda] (layout of the points' images), each row with its own power-of-two scale; a row that
-// is not finite gets the scale NaN.  A block of 256 threads makes one tile of 32 rows.
-__global__ __launch_bounds__(256) void k_had_digits(const float *A, int64_t lda, int64_t n, int d, int ks, unsigned char *img, float *scale)
+// is not finite gets the scale NaN.  add: the streamed points are stored shifted, y - origin in every coordinate, so
+// <row, y> = <row, y - origin> + origin sum(row).  A block of 256 threads makes one tile of 32 rows.
+__global__ __launch_bounds__(256) void k_had_digits(const float *A, int64_t lda, int64_t n, int d, int ks, const double *origin,
+                                                    unsigned char *img, float *scale, double *add)
 {
     __shared__ float pt[32][32 * kFxMaxKs + 1];
     __shared__ int sh_ex[32];
@@ -647,18 +655,24 @@ __global__ __launch_bounds__(256) void k_had_digits(const float *A, int64_t lda,
     for (int r = wv; r < 32; r += 4) {
         const int64_t row = row0 + r;
         uint32_t mx = 0;
+        double sum = 0.0;
         for (int k = lane; k < 32 * ks; k += 64) {
             const float v = (row < n && k < d) ? A[row * lda + k] : 0.0f;
             pt[r][k] = v;
             mx = max(mx, __float_as_uint(fabsf(v)));
+            sum += (double)v;
         }
-        for (int off = 32; off > 0; off >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, 64));
+        for (int off = 32; off > 0; off >>= 1) {
+            mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, 64));
+            sum += __shfl_xor(sum, off, 64);
+        }
         const float big = __uint_as_float(mx);
         int ex = 0;
         if (big < INFINITY && big > 0.0f) (void)frexp((double)big * (128.0 / 127.49), &ex);
         if (lane == 0) {
             sh_ex[r] = ex;
             scale[row] = big < INFINITY ? (float)ldexp(1.0, ex) : NAN;
+            add[row] = *origin * sum;
         }
     }
     __syncthreads();
@@ -666,8 +680,14 @@ __global__ __launch_bounds__(256) void k_had_digits(const float *A, int64_t lda,
         const int q = e >> 6, l = e & 63;
         const int k0 = 32 * q + 16 * (l >> 5);
         const double to_fixed = ldexp(1.0, 31 - sh_ex[l & 31]);
+        int X[16];
+#pragma unroll
+        for (int z = 0; z < 16; ++z) {
+            const float v = pt[l & 31][k0 + z];
+            X[z] = fabsf(v) < INFINITY ? (int)rint((double)v * to_fixed) : 0;
+        }
         uint4 o[4];
-        fx_digits16(&pt[l & 31][k0], to_fixed, o);
+        fx_digits16(X, o);
 #pragma unroll
         for (int dg = 0; dg < 4; ++dg) *reinterpret_cast<uint4 *>(img + ((((int64_t)blockIdx.x * ks + q) * 4 + dg) << 10) + l * 16) = o[dg];
     }
@@ -775,9 +795,9 @@ void fx_columns(int64_t left, bool had, int *mode, int *nc)
     *nc = *mode == 1 ? (int)left : (int)ceil_div(left < most ? left : most, 32);
 }
 
-// buffer of a pass: [splits][rows][PC] accumulators, value images and their flags, digits and scales of A
+// buffer of a pass: [splits][rows][PC] accumulators, value images and their flags, digits, scales and summands of A
 struct ApplyBuf {
-    size_t vimg, vflag, had, scale, total;
+    size_t vimg, vflag, had, scale, add, total;
     ApplyBuf(int splits, int64_t rows_pad, int64_t n_tiles, int ks, int mode, int nc, bool with_had)
     {
         Arena A;
@@ -786,6 +806,7 @@ struct ApplyBuf {
         vflag = A.take(mode == 2 ? (size_t)n_tiles * 4 : 0);
         had = A.take(with_had ? (size_t)rows_pad * ks * 128 : 0);
         scale = A.take(with_had ? (size_t)rows_pad * 4 : 0);
+        add = A.take(with_had ? (size_t)rows_pad * 8 : 0);
         total = A.off;
     }
 };
@@ -848,9 +869,9 @@ size_t fx_apply_ws(const Ctx *c, int64_t n_res, int64_t n_str, int64_t d, int64_
 }
 
 // one pass of an application: columns p0 .. of V; *pc = row length of the accumulators in P->extra.  hadA != nullptr:
-// Hadamard-weighted, with the rows of hadA [res->cnt][lda].
+// Hadamard-weighted, with the rows of hadA [res->cnt][lda]; *had_add: see FxArgs.
 fs_status fx_apply_pass(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, const float *V, int64_t p, int64_t ldv,
-                        int p0, const float *hadA, int64_t lda, int *splits, int *pc)
+                        int p0, const float *hadA, int64_t lda, int *splits, int *pc, const double **had_add)
 {
     int mode, nc;
     fx_columns(p - p0, hadA != nullptr, &mode, &nc);
@@ -874,8 +895,11 @@ fs_status fx_apply_pass(Ctx *c, const Prepared *P, const Side *res, const Side *
     if (hadA) {
         a.had = x + buf.had;
         a.had_scale = reinterpret_cast<const float *>(x + buf.scale);
+        double *add = reinterpret_cast<double *>(x + buf.add);
+        a.had_add = add;
+        *had_add = add;
         hipLaunchKernelGGL(k_had_digits, dim3((unsigned)(res->cnt_pad / 32)), dim3(256), 0, c->stream, hadA, lda, res->cnt, (int)P->d,
-                           P->fx_ks, x + buf.had, reinterpret_cast<float *>(x + buf.scale));
+                           P->fx_ks, P->scalars + 11, x + buf.had, reinterpret_cast<float *>(x + buf.scale), add);
     }
     const dim3 grid((unsigned)s.row_blocks, (unsigned)s.splits);
     switch (P->fx_ks) {

@@ -118,19 +118,30 @@ __host__ __device__ inline int fx_ksteps(int64_t d) { return d > kLowdMaxD && d 
 // Decides on the device which of the two kernels of a pass runs: every pass of a problem with digit images is launched
 // twice, fixed point and float64, and one of the two leaves at once (the scale of the clouds is known on the device only,
 // and a read-back would make every entry call wait).  cscale r2^2 is the size of a score's unit-scale product in base-2
-// units.  Up to 2^14 the products that the digits leave out stay below 2^-23.7 of a base-2 unit at d = 128, a fraction of
-// the rounding of the exponential's float argument; below 2^-3 the log weights no longer fit the bias records, every
-// tile would take the slow epilogue.  A scale that is not finite is off as well.
-constexpr double kFxFull = 128.0;
+// units, v below; r2 covers the distance of the coordinates from the middle of their range, where k_prep_fx puts the origin.
+//
+// The upper line lies where the error of a score reaches the rounding of the exponential's float argument.  What counts there
+// is that a coordinate below 2^-7 r2 loses bits of its float; at d = 128 (rms over pairs, in base-2 units) normal points have
+// 2^-23.4 at v = 1846 and 2^-20.1 at v = 18466, unit-cube points 2^-26 at v = 288.  Plan sums at v = 1846 are off by
+// 5e-8 to 6e-8 of their size, as float64 scores leave 4e-8 to 5e-8; at v = 16000 it was 2.5e-7 to 7e-7.  Bounds for data whose
+// digits conspire: the products left out at most 2 d 2^14 2^-54 v (2^-21 at the line, d = 128), the coordinates' rounding
+// d 2^-31 v (one cloud within 2^-7 r2 of the origin and rounded one way, the other at the far end).
+// Below v = 1/2 weights of 2^-60 no longer fit the bias records (every tile with one would take the slow epilogue), and
+// the fp64 kernels take over.  A scale that is not finite is off as well.
+//
+// Up to kFxFull, ten products: those left out are 2^-24.3 rms at that line for random digits and d = 128, and for two-valued
+// coordinates; d 2^-30.4 v at most (2^-18.4, every digit at its largest and of one sign).  At four times the line, two-valued
+// coordinates already cost plan sums a digit against the fp64 kernels.
+constexpr double kFxLow = 0.5, kFxHigh = 2048.0, kFxFull = 32.0;
 struct FxGate {
     const double *r2 = nullptr;   // common scale of both clouds (device), see k_prep_fx; nullptr: no digit images
     double cscale = 0.0;          // 2 log2(e) / eps
     __device__ bool on() const
     {
         const double r = *r2, v = cscale * r * r;
-        return v >= 0.125 && v <= 16384.0;
+        return v >= kFxLow && v <= kFxHigh;
     }
-    // all thirteen digit products; below this size ten leave less than 2^-23 of a base-2 unit out (see fs_fx.hip)
+    // all thirteen digit products (see fs_fx.hip)
     __device__ bool full() const
     {
         const double r = *r2;
@@ -139,13 +150,13 @@ struct FxGate {
     __device__ double unit(int k) const { return ldexp(cscale * *r2 * *r2, -k); }
 };
 
-// the four balanced base-256 digits of sixteen coordinates in fixed point (to_fixed: 2^31 over their scale)
-__device__ inline void fx_digits16(const float *v, double to_fixed, uint4 (&out)[4])
+// the four balanced base-256 digits of sixteen coordinates in fixed point
+__device__ inline void fx_digits16(const int *v, uint4 (&out)[4])
 {
     uint32_t o[4][4];
 #pragma unroll
     for (int z = 0; z < 16; ++z) {
-        int X = fabsf(v[z]) < INFINITY ? (int)rint((double)v[z] * to_fixed) : 0;
+        int X = v[z];
 #pragma unroll
         for (int dg = 3; dg >= 0; --dg) {
             const int t = dg > 0 ? (int)(signed char)(X & 255) : X;   // balanced: what is left is a multiple of 256
@@ -299,7 +310,7 @@ struct Prepared {
     double *dev_part = nullptr;  // [ceil(max(n,m)/256)] per-block sums of the marginal deviation
     double *gauge_part = nullptr;   // [2][ceil(max(n,m)/256)] per-block sums of the plan's mass seen by a g-update
     double *gauge_part_x = nullptr; // the same for an f-update (averaged schedule: both passes measure, halves by parity)
-    double *scalars = nullptr;   // [16] device doubles (marginal errors, centring sums...; [8], [9]: gauge drift, see GaugeMode; [10]: FxGate::r2)
+    double *scalars = nullptr;   // [16] device doubles (marginal errors, centring sums...; [8], [9]: gauge drift, see GaugeMode; [10], [11]: FxGate::r2 and the origin of the digits)
     double *mean = nullptr;      // [kLowdMaxD] common mean (LowD)
     char *extra = nullptr;       // entry-point specific scratch (plan application partials)
     size_t extra_bytes = 0;
@@ -502,7 +513,7 @@ fs_status fx_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, do
 fs_status fx_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, void *partial_y, int *splits_x, int *splits_y);
 size_t fx_apply_ws(const Ctx *c, int64_t n_res, int64_t n_str, int64_t d, int64_t p);
 fs_status fx_apply_pass(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, const float *V, int64_t p, int64_t ldv,
-                        int p0, const float *hadA, int64_t lda, int *splits, int *pc);
+                        int p0, const float *hadA, int64_t lda, int *splits, int *pc, const double **had_add);
 
 // fs_bf16.hip
 fs_status bf16_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps,

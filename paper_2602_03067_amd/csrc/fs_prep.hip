@@ -284,33 +284,58 @@ __global__ void k_prep_bf16(const void *pts, int dtype, int64_t cnt, int64_t cnt
 
 // ---- derived copies for 16 < d <= 128: the float64 records as above, and the digit images of the fixed-point
 //      kernels (layout and digits: fs_fx.hip) ----------------------------------------------------------
-// stage 1: largest |coordinate| of both clouds as bit patterns of non-negative floats (NaN and infinity order above
-// every finite value), block b of side y writes part[y][b]
+// Floats as unsigned integers of the same order: -NaN < -inf < ... < inf < NaN
+__device__ inline uint32_t order_key(float v)
+{
+    const uint32_t u = __float_as_uint(v);
+    return u & 0x80000000u ? ~u : u | 0x80000000u;
+}
+__device__ inline float order_value(uint32_t k) { return __uint_as_float(k & 0x80000000u ? k & 0x7fffffffu : ~k); }
+
+// smallest and largest of a workgroup of four waves, in every thread after the caller's barrier
+__device__ inline void wave_range(uint32_t &mn, uint32_t &mx, uint2 *sh)
+{
+    for (int off = 32; off > 0; off >>= 1) {
+        mn = min(mn, (uint32_t)__shfl_xor((int)mn, off, 64));
+        mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, 64));
+    }
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = make_uint2(mn, mx);
+}
+
+// stage 1: range of the coordinates of both clouds (as order keys), block b of side y writes part[y][b]
 constexpr int kFxMaxBlocks = 128;
-__global__ __launch_bounds__(256) void k_coord_max(CloudIn c0, CloudIn c1, int dtype, int d, uint32_t *part)
+__global__ __launch_bounds__(256) void k_coord_range(CloudIn c0, CloudIn c1, int dtype, int d, uint2 *part)
 {
     const CloudIn &cl = blockIdx.y ? c1 : c0;
-    __shared__ uint32_t sh[4];
+    __shared__ uint2 sh[4];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    uint32_t mx = 0;
+    uint32_t mn = 0xffffffffu, mx = 0;
     // eight rows in flight per wave: the loop is bound by the latency of its loads
     const int64_t step = (int64_t)gridDim.x * 4;
     for (int64_t i = (int64_t)blockIdx.x * 4 + wv; i < cl.rows; i += 8 * step)
         for (int k = lane; k < d; k += 64) {
             float v[8];
 #pragma unroll
-            for (int q = 0; q < 8; ++q) v[q] = i + q * step < cl.rows ? load_pt(cl.pts, dtype, (i + q * step) * cl.ld + k) : 0.0f;
+            for (int q = 0; q < 8; ++q) v[q] = load_pt(cl.pts, dtype, (i + q * step < cl.rows ? i + q * step : i) * cl.ld + k);
 #pragma unroll
-            for (int q = 0; q < 8; ++q) mx = max(mx, __float_as_uint(fabsf(v[q])));
+            for (int q = 0; q < 8; ++q) {
+                mn = min(mn, order_key(v[q]));
+                mx = max(mx, order_key(v[q]));
+            }
         }
-    for (int off = 32; off > 0; off >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, 64));
-    if (lane == 0) sh[wv] = mx;
+    wave_range(mn, mx, sh);
     __syncthreads();
-    if (threadIdx.x == 0) part[blockIdx.y * kFxMaxBlocks + blockIdx.x] = max(max(sh[0], sh[1]), max(sh[2], sh[3]));
+    if (threadIdx.x == 0)
+        part[blockIdx.y * kFxMaxBlocks + blockIdx.x] = make_uint2(min(min(sh[0].x, sh[1].x), min(sh[2].x, sh[3].x)),
+                                                                  max(max(sh[0].y, sh[1].y), max(sh[2].y, sh[3].y)));
 }
 
-// stage 2: block = tile of 32 points.  The common scale r2 is the smallest power of two whose 127.49 / 128 covers the
-// largest coordinate, so the first digit stays within 127; a float's 24 bits are then kept exactly down to 2^-7 r2.
+// stage 2: block = tile of 32 points.  Both clouds are shifted by the middle of the range of all their coordinates (the same
+// shift for every coordinate; the cost does not change): coordinates of one sign, pixels for instance, get half the scale,
+// which leaves a quarter of the error, and products of theirs have both signs, so that digits left out do not add up.  The
+// shift is a multiple of 2^-7 r2, so a coordinate that is exact in fixed point stays exact; it is exact in the float64 records.
+// The common scale r2 is the smallest power of two whose 127.49 / 128 covers the largest shifted coordinate, so the first
+// digit stays within 127; a float's 24 bits are then kept exactly down to 2^-7 r2.
 struct PrepFxSide {
     const void *pts;
     int64_t cnt, cnt_pad, ld;
@@ -318,19 +343,18 @@ struct PrepFxSide {
     unsigned char *dig;
     int *brec;
 };
-__global__ __launch_bounds__(256) void k_prep_fx(PrepFxSide s0, PrepFxSide s1, int dtype, int d, int kp, int ks, const uint32_t *part,
+__global__ __launch_bounds__(256) void k_prep_fx(PrepFxSide s0, PrepFxSide s1, int dtype, int d, int kp, int ks, const uint2 *part,
                                                  double *r2_out)
 {
     const PrepFxSide &sd = blockIdx.y ? s1 : s0;
     const int64_t row0 = (int64_t)blockIdx.x * 32;
     if (row0 >= sd.cnt_pad) return;
-    __shared__ float pt[32][32 * kFxMaxKs + 1];
-    __shared__ uint32_t shm[4];
+    __shared__ int pt[32][32 * kFxMaxKs + 1];
+    __shared__ uint2 shm[4];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    static_assert(2 * kFxMaxBlocks == 256, "one partial maximum per thread");
-    uint32_t mx = part[tid];
-    for (int off = 32; off > 0; off >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, 64));
-    if (lane == 0) shm[wv] = mx;
+    static_assert(2 * kFxMaxBlocks == 256, "one partial range per thread");
+    uint32_t mn = part[tid].x, mx = part[tid].y;
+    wave_range(mn, mx, shm);
     // a wave takes eight rows, two coordinates per lane and row, all loads in flight
     float v[8][2];
 #pragma unroll
@@ -342,6 +366,24 @@ __global__ __launch_bounds__(256) void k_prep_fx(PrepFxSide s0, PrepFxSide s1, i
             v[q][z] = (row < sd.cnt && k < d) ? load_pt(sd.pts, dtype, row * sd.ld + k) : 0.0f;
         }
     static_assert(32 * kFxMaxKs == 128, "two coordinates per lane");
+    __syncthreads();
+    const double lo = (double)order_value(min(min(shm[0].x, shm[1].x), min(shm[2].x, shm[3].x)));
+    const double hi = (double)order_value(max(max(shm[0].y, shm[1].y), max(shm[2].y, shm[3].y)));
+    int ex = 0;
+    double r2 = 1.0, origin = 0.0, to_fixed = 0.0;
+    if (!(lo > -INFINITY && hi < INFINITY))
+        r2 = INFINITY;   // (the gate is off)
+    else {
+        // (126.99: the rounding of the shift is at most half a unit of the first digit)
+        if (hi > lo) (void)frexp(0.5 * (hi - lo) * (128.0 / 126.99), &ex);
+        r2 = ldexp(1.0, ex);
+        origin = ldexp(rint(ldexp(0.5 * (hi + lo), 7 - ex)), ex - 7);
+        to_fixed = ldexp(1.0, 31 - ex);
+    }
+    if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) {
+        r2_out[0] = r2;
+        r2_out[1] = origin;
+    }
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
         const int64_t row = row0 + 8 * wv + q;
@@ -349,11 +391,12 @@ __global__ __launch_bounds__(256) void k_prep_fx(PrepFxSide s0, PrepFxSide s1, i
 #pragma unroll
         for (int z = 0; z < 2; ++z) {
             const int k = lane + 64 * z;
+            const double t = (row < sd.cnt && k < d) ? (double)v[q][z] - origin : 0.0;
             if (k < kp) {
-                pt[8 * wv + q][k] = v[q][z];
-                sd.out[row * kp + k] = (double)v[q][z];
+                pt[8 * wv + q][k] = to_fixed > 0.0 ? (int)rint(t * to_fixed) : 0;
+                sd.out[row * kp + k] = t;
             }
-            nrm += (double)v[q][z] * (double)v[q][z];
+            nrm += t * t;
         }
         for (int off = 32; off > 0; off >>= 1) nrm += __shfl_xor(nrm, off, 64);
         if (lane == 0) {
@@ -362,23 +405,11 @@ __global__ __launch_bounds__(256) void k_prep_fx(PrepFxSide s0, PrepFxSide s1, i
         }
     }
     __syncthreads();
-    mx = max(max(shm[0], shm[1]), max(shm[2], shm[3]));
-    const float big = __uint_as_float(mx);
-    int ex = 0;
-    double r2 = 1.0;
-    if (!(big < INFINITY))
-        r2 = INFINITY;   // (the gate is off)
-    else if (big > 0.0f) {
-        (void)frexp((double)big * (128.0 / 127.49), &ex);
-        r2 = ldexp(1.0, ex);
-    }
-    if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) *r2_out = r2;
-    const double to_fixed = big < INFINITY ? ldexp(1.0, 31 - ex) : 0.0;
     for (int e = tid; e < ks * 64; e += 256) {
         const int q = e >> 6, l = e & 63;
         const int k0 = 32 * q + 16 * (l >> 5);
         uint4 o[4];
-        fx_digits16(&pt[l & 31][k0], to_fixed, o);
+        fx_digits16(&pt[l & 31][k0], o);
 #pragma unroll
         for (int dg = 0; dg < 4; ++dg)
             *reinterpret_cast<uint4 *>(sd.dig + ((((int64_t)blockIdx.x * ks + q) * 4 + dg) << 10) + l * 16) = o[dg];
@@ -915,9 +946,9 @@ fs_status launch_prepare(Ctx *c, const fs_problem *p, Prepared *P)
                                P->dpd, P->scalars + 7);
         FS_HIP(c, hipGetLastError());
     } else if (P->path == Path::F64 && P->fx_ks) {
-        uint32_t *part = reinterpret_cast<uint32_t *>(P->mean);
+        uint2 *part = reinterpret_cast<uint2 *>(P->mean);
         const CloudIn cx{p->x, p->n, p->ldx, nullptr}, cy{p->y, p->m, p->ldy, nullptr};
-        hipLaunchKernelGGL(k_coord_max, dim3(kFxMaxBlocks, 2), dim3(256), 0, c->stream, cx, cy, dtype, (int)p->d, part);
+        hipLaunchKernelGGL(k_coord_range, dim3(kFxMaxBlocks, 2), dim3(256), 0, c->stream, cx, cy, dtype, (int)p->d, part);
         PrepFxSide sd[2];
         for (int k = 0; k < 2; ++k) {
             const Side *S = in[k].S;

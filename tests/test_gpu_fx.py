@@ -331,3 +331,69 @@ def test_noalloc_without_room_for_digits():
     c.close()
     for u, v in zip(*out):   # four half-steps on either side, and the rounding of two float outputs
         assert np.all(np.abs(u - v) <= 8e-6 * eps + 2.0 ** -23 * np.abs(u) * 1.01)
+
+
+@pytest.mark.parametrize("offset", [-5.0, 40.0, 1000.0])
+@pytest.mark.parametrize("eps", [0.3, 0.01])   # fixed point, and beyond the gate
+def test_clouds_far_from_the_origin(ctx, oracle, offset, eps):
+    """The digits are those of the shifted points: potentials, applications and, where the points themselves enter, Hadamard
+    weights, whose rows sum to nearly nothing here so that the shift's share of a weight is large and cancels."""
+    eps = float(np.float32(eps))
+    n, m, d = 130, 170, 40
+    rng, x, y, a, b = _problem(17, n, m, d, 4.0)
+    x, y = (x + np.float32(offset)).astype(np.float32), (y + np.float32(offset)).astype(np.float32)
+    prob = make_problem(x, y, a, b)
+    say("fx offset %g eps=%g" % (offset, eps))
+    g = (rng.standard_normal(m) * eps).astype(np.float32)
+    want = oracle.update_f(x, y, b, eps, g)
+    _check_pot(ctx.fs_update_f(prob, eps, dev(g)), want, eps)
+    f = want.astype(np.float32)
+    V = rng.standard_normal((m, 9)).astype(np.float32)
+    _check_values(ctx.fs_apply_plan(prob, eps, dev(f), dev(g), dev(V)), oracle.apply_plan(x, y, a, b, eps, f, g, V))
+    A = rng.standard_normal((n, d)).astype(np.float32)
+    A -= A.mean(1, keepdims=True)
+    X, Y = x.astype(np.float64), y.astype(np.float64)
+    cost = ((X[:, None, :] - Y[None, :, :]) ** 2).sum(2)
+    W = a[:, None].astype(np.float64) * b[None, :] * np.exp((f[:, None].astype(np.float64) + g[None, :] - cost) / np.float64(eps))
+    W *= A.astype(np.float64) @ Y.T
+    got = host(ctx.fs_apply_plan_hadamard(prob, eps, dev(f), dev(g), dev(A), dev(V)))
+    scale = np.abs(W).sum(1, keepdims=True) * np.abs(V).max()
+    assert (np.abs(got - W @ V.astype(np.float64)) / scale).max() <= 1e-6
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("kind", ["pixels", "two values", "one direction", "normal"])
+def test_plan_sums_of_data_with_regular_digits(ctx, oracle, d, kind):
+    """Coordinates whose base-256 digits repeat (k / 255, a single constant): the digit products left out add up instead of
+    averaging out.  Plan sums at the upper end of ten products, a little above it, and at the upper end of the gate stay at
+    what the fp64 kernels leave (4e-8 to 4e-7 for these).  Points along one direction are the exception: a point within
+    2^-7 of the range from the origin, one in 64, has all its d coordinates rounded the same way, by at most 2^-32 of the
+    scale, which against a point at the far end is d 2^-31 v base-2 units of a score."""
+    n, m = 200, 333
+    rng = np.random.default_rng(d)
+
+    def cloud(k):
+        if kind == "pixels":
+            return rng.integers(0, 256, (k, d)) / 255.0
+        if kind == "two values":
+            return 0.7 * rng.integers(0, 2, (k, d))
+        if kind == "one direction":
+            return np.ones((k, d)) * rng.random((k, 1))
+        return rng.standard_normal((k, d))
+
+    x, y = cloud(n).astype(np.float32), cloud(m).astype(np.float32)
+    half = 0.5 * (max(x.max(), y.max()) - min(x.min(), y.min()))
+    r2 = 2.0 ** np.frexp(half * 128 / 126.99)[1]
+    a, b = np.full(n, 1.0 / n, dtype=np.float32), np.full(m, 1.0 / m, dtype=np.float32)
+    for v in (30.0, 40.0, 2000.0):
+        eps = float(np.float32(2.0 / np.log(2.0) * r2 * r2 / v))
+        fo, go = oracle.solve(x, y, a, b, eps, eps, 1, 3)
+        f, g = fo.astype(np.float32), go.astype(np.float32)
+        prob = make_problem(x, y, a, b)
+        say("fx digits %s d=%d v=%g eps=%.4g" % (kind, d, v, eps))
+        for p in (1, 5):
+            got, mass = ctx.fs_apply_plan(prob, eps, dev(f), dev(g), torch.ones(m, p, device="cuda:0"), want_mass=True)
+            want = oracle.apply_plan(x, y, a, b, eps, f, g, np.ones((m, p), dtype=np.float32))
+            e = [np.linalg.norm(host(got) - want) / np.linalg.norm(want), np.linalg.norm(host(mass) - want[:, 0]) / np.linalg.norm(want[:, 0])]
+            say("  p=%d sums %.2e mass %.2e" % (p, *e))
+            assert max(e) <= 2.5e-7 + (np.log(2.0) * d * 2.0 ** -31 * v / 64 if kind == "one direction" else 0.0)
