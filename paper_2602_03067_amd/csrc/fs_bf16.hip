@@ -102,11 +102,27 @@ struct BfArgs {
 // What a tile's 256 x 256 contraction is used for:
 //   Lse      running (max, sum) of every resident row
 //   Plan     the exponentials themselves, exp2(score - rowmax), rounded to bf16 and stored as the left operand of a second
-//            product, with their row sums.  No running max: bf16 has the exponent range of a float, and the plan's entries
-//            are what the caller's potentials say they are.
+//            product, with their row sums.  No running max: bf16 has the exponent range of a float, and a row whose entries
+//            leave it (its sum tells) is done again by Direct.
 //   Product  the second product out[row][c] = sum_i E[row][i] V[i][c]: the same contraction over the stored exponentials
 //            (streamed role: rows) and the transposed values (resident role: columns), its accumulators stored as they are
-enum class Epi { Lse, Plan, Product };
+//   Direct   (with PC > 0) the application over all streamed points in one workgroup, which writes its rows of the result
+enum class Epi { Lse, Plan, Product, Direct };
+
+// where Direct writes: rows of resident tiles whose flag is set
+struct DirectArgs {
+    const int *flags;            // [0]: any; [1 + tile of kApplyBJ rows]
+    int64_t cnt;
+    double inv_eps;
+    const float *w;
+    double log_uniform;
+    const double *pot, *norm;
+    int p;
+    float *out;
+    int64_t ldo;
+    float *mass_out;
+    int64_t img_stride;          // bytes of the value images of a column block
+};
 
 // Workgroup shapes (WJ = waves along the resident side, each owning 128 resident rows; four waves
 // along the streamed side, each owning 64 of the tile's 256 streamed points):
@@ -149,7 +165,7 @@ constexpr int kVRow = 520;                       // bytes per value column in th
 constexpr int kVImgBytes(int pc) { return (pc * kVRow + 1023) / 1024 * 1024; }
 
 template <int WJ, int NS, int JTW, int PC, bool HALF = false, Epi EPI = Epi::Lse>
-__device__ __forceinline__ void lse_bf16_body(const BfArgs &a, const int block)
+__device__ __forceinline__ void lse_bf16_body(const BfArgs &a, const int block, const DirectArgs *direct = nullptr, const int p0 = 0)
 {
     constexpr bool APPLY = PC > 0;
     constexpr int BJ = 32 * JTW * WJ;            // resident rows per workgroup
@@ -637,6 +653,32 @@ __device__ __forceinline__ void lse_bf16_body(const BfArgs &a, const int block)
             }
             __syncthreads();
         }
+        if constexpr (EPI == Epi::Direct) {
+            // (as launch_apply_finalize does it from the records of the splits)
+            double *fac = reinterpret_cast<double *>(&bias_ring[0][0]);
+            static_assert(BJ * 8 <= sizeof(bias_ring), "row factors fit the bias ring");
+            if (tid < BJ) {
+                float M = kNegInit;
+                double S = 0.0;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) M = fmaxf(M, red[tid * 8 + k].x);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) S += (double)(red[tid * 8 + k].y * fast_exp2(red[tid * 8 + k].x - M));
+                const int64_t i = row0 + tid;
+                if (i < direct->cnt) {
+                    const double lw = direct->w ? log((double)direct->w[i]) : direct->log_uniform;
+                    fac[tid] = exp2(((direct->pot[i] - direct->norm[i]) * direct->inv_eps + lw) * kLog2e + (double)M);
+                    if (direct->mass_out && p0 == 0) direct->mass_out[i] = (float)(fac[tid] * S);
+                }
+            }
+            __syncthreads();
+            for (int e = tid; e < BJ * PC; e += 256 * WJ) {
+                const int j = e / PC, cc = e - j * PC;
+                if (row0 + j < direct->cnt && p0 + cc < direct->p)
+                    direct->out[(row0 + j) * direct->ldo + p0 + cc] = (float)(fac[j] * (double)obuf[e]);
+            }
+            return;
+        }
         for (int e = tid; e < BJ * PC; e += 256 * WJ) {
             const int j = e / PC, cc = e - j * PC;
             a.opart[((int64_t)split * a.partial_stride + row0 + j) * PC + cc] = obuf[e];
@@ -672,11 +714,23 @@ __global__ __launch_bounds__(256 * WJ, WJ == 2 ? 1 : 2) void k_lse_bf16_pair(BfA
     lse_bf16_body<WJ, NS, JTW, 0>(second ? a1 : a0, (int)blockIdx.x - (second ? blocks0 : 0));
 }
 
+// Rows of the plan whose entries left the exponent range of a stored slab (see k_plan_finalize): workgroup (row tile, column
+// block), all of which leave at once where the row tile has no such row.
+template <int PC>
+__global__ __launch_bounds__(512, 1) void k_apply_direct(BfArgs a, DirectArgs o)
+{
+    const int jtile = blockIdx.x;
+    if (!o.flags[1 + jtile]) return;
+    a.vimg += blockIdx.y * o.img_stride;
+    const int per = (a.n_jtiles + 7) >> 3;   // (the inverse of the body's dealing, for one split)
+    lse_bf16_body<2, 4, 2, PC, false, Epi::Direct>(a, (jtile % per) * 8 + jtile / per, &o, (int)blockIdx.y * PC);
+}
+
 // Value image of every streamed tile for the plan application: bf16 Vt[c][i], c < pc value columns
 // starting at p0, i < 256 points of tile t, rows of kVRow bytes, one image per img_bytes; zero
 // outside the matrix.  (The pad bytes are copied to LDS with the rest and never read.)
-__global__ __launch_bounds__(BI) void k_vimg_bf16(const float *V, int64_t ldv, int64_t n_str, int p0, int p, int pc,
-                                                   int img_bytes, unsigned char *img)
+__device__ __forceinline__ void vimg_tile(const float *V, int64_t ldv, int64_t n_str, int p0, int p, int pc, int img_bytes,
+                                          unsigned char *img)
 {
     const int i = threadIdx.x;
     const int64_t row = (int64_t)blockIdx.x * BI + i;
@@ -685,6 +739,18 @@ __global__ __launch_bounds__(BI) void k_vimg_bf16(const float *V, int64_t ldv, i
         const float v = (row < n_str && p0 + cc < p) ? V[row * ldv + p0 + cc] : 0.0f;
         *reinterpret_cast<__bf16 *>(dst + cc * kVRow + 2 * i) = (__bf16)v;
     }
+}
+__global__ __launch_bounds__(BI) void k_vimg_bf16(const float *V, int64_t ldv, int64_t n_str, int p0, int p, int pc,
+                                                   int img_bytes, unsigned char *img)
+{
+    vimg_tile(V, ldv, n_str, p0, p, pc, img_bytes, img);
+}
+// ... of all column blocks (blockIdx.y), for k_apply_direct
+__global__ __launch_bounds__(BI) void k_vimg_direct(const float *V, int64_t ldv, int64_t n_str, int p, int pc, int img_bytes,
+                                                     int64_t img_stride, unsigned char *img, const int *flags)
+{
+    if (!flags[0]) return;
+    vimg_tile(V, ldv, n_str, (int)blockIdx.y * pc, p, pc, img_bytes, img + blockIdx.y * img_stride);
 }
 
 // Transposed values for the second product: bf16 V^T, tiled like the point copies with the value columns as rows and the
@@ -710,34 +776,57 @@ __global__ __launch_bounds__(256) void k_vt_bf16(const float *V, int64_t ldv, in
                                ((piece ^ ((c >> 2) & 3)) << 4)) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
 }
 
-// The stabiliser of a row of the plan slab: minus the base-2 exponent its own potential contributes, rounded, so that
-// exp2(score - rowmax) is the plan's entry without the row's weight, to a factor below sqrt(2).  Padding rows: no entry.
-__global__ void k_plan_rowmax(const double *pot, const double *norm, double inv_eps, int64_t cnt, int64_t cnt_pad, float *rowmax)
+// The stabiliser of a row of the plan slab: minus the base-2 exponent t its own potential contributes, rounded, so that
+// exp2(score - rowmax) is 2^30 times the plan's entry without the row's weight, to a factor below sqrt(2).  Kept where a
+// float holds it exactly; a row beyond that (a potential that masks it, for one) has sums that say so, see k_plan_finalize.
+// Padding rows: no entry.  Also clears the flags of the rows to do again.
+constexpr double kPlanShift = 30.0, kPlanLimit = 16777216.0;
+__global__ void k_plan_rowmax(const double *pot, const double *norm, double inv_eps, int64_t cnt, int64_t cnt_pad, float *rowmax,
+                              int *flags, int n_flags)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < cnt_pad) rowmax[i] = i < cnt ? (float)-rint((pot[i] - norm[i]) * inv_eps * kLog2e) : 3.0e38f;
+    if (i < n_flags) flags[i] = 0;
+    if (i >= cnt_pad) return;
+    double r = 3.0e38;
+    if (i < cnt) {
+        r = -rint((pot[i] - norm[i]) * inv_eps * kLog2e) - kPlanShift;
+        r = r > kPlanLimit ? kPlanLimit : r < -kPlanLimit ? -kPlanLimit : r;   // (NaN stays)
+    }
+    rowmax[i] = (float)r;
 }
 
-// out_i = w_i exp(fhat_i/eps) 2^rowmax_i (sum over the splits of the product), columns col0 .. col0 + cols; a block per row
+// out_i = w_i exp(fhat_i/eps) 2^rowmax_i (sum over the splits of the product), columns col0 .. col0 + cols; a block per row.
+//
+// Which rows that is good for is read off the row's sum of stored exponentials (mass_out and flags are given with the first
+// columns only).  Within 2^-40 .. 2^60, that is a row mass of 2^-70 .. 2^30 times its weight, the entries that were rounded to
+// zero are below 2^-126 each, 2^-62 of the sum for 2^24 points.  A row below that whose factor is below 2^-400 is zero
+// in float, whatever the values: potentials of -inf or -1e30 that mask a row.  A sum that is not a number comes from such a
+// score, and the row is NaN here as anywhere.  All other rows are flagged and done by k_apply_direct.
 __global__ __launch_bounds__(256) void k_plan_finalize(const float *opart, int64_t ld, int splits, int slab_rows, int row_off, int64_t cnt,
                                                        double inv_eps, const float *w, double log_uniform, const double *pot,
                                                        const double *norm, const float *rowmax, int col0, int cols, float *out, int64_t ldo,
-                                                       const double2 *partial, int64_t stride, int plan_splits, float *mass_out)
+                                                       const double2 *partial, int64_t stride, int plan_splits, float *mass_out, int *flags)
 {
     const int64_t i = row_off + (int64_t)blockIdx.x;
     if (i >= cnt) return;
     const double lw = w ? log((double)w[i]) : log_uniform;
-    const double fac = exp2(((pot[i] - norm[i]) * inv_eps + lw) * kLog2e + (double)rowmax[i]);
+    const double e0 = ((pot[i] - norm[i]) * inv_eps + lw) * kLog2e + (double)rowmax[i];
+    const double fac = exp2(e0);
     const float *o = opart + (int64_t)blockIdx.x * ld;
     for (int c = threadIdx.x; c < cols; c += 256) {
         double acc = 0.0;
         for (int k = 0; k < splits; ++k) acc += (double)o[(int64_t)k * slab_rows * ld + c];
         out[i * ldo + col0 + c] = (float)(fac * acc);
     }
-    if (mass_out && threadIdx.x == 0) {
+    if (flags && threadIdx.x < 64) {
         double S = 0.0;
-        for (int k = 0; k < plan_splits; ++k) S += partial[(int64_t)k * stride + i].y;
-        mass_out[i] = (float)(fac * S);
+        for (int k = threadIdx.x; k < plan_splits; k += 64) S += partial[(int64_t)k * stride + i].y;
+        for (int off = 32; off > 0; off >>= 1) S += __shfl_xor(S, off);
+        if (threadIdx.x == 0) {
+            if (mass_out) mass_out[i] = (float)(fac * S);
+            const bool kept = (S >= 0x1p-40 && S <= 0x1p60) || S != S || (S <= 0x1p60 && e0 < -400.0);
+            if (!kept) flags[0] = flags[1 + i / 128] = 1;
+        }
     }
 }
 
@@ -783,7 +872,9 @@ struct SlabPlan {
     int wide_tiles = 0;      // 256-column tiles of the product
     int rest = 0;            // columns beyond them, taken by a 128-column tile (0: none)
     int ks_wide = 0, ks_rest = 0;   // splits of the product's contraction
-    size_t eslab = 0, vt = 0, rowmax = 0, opart = 0, total = 0;
+    int col_blocks = 0;             // column blocks of k_apply_direct
+    size_t img_stride = 0;          // bytes of the value images of one of them (they take the slab's place)
+    size_t eslab = 0, vt = 0, rowmax = 0, flags = 0, opart = 0, total = 0;
 };
 
 int product_splits(const Ctx *c, int tiles, int chunks)
@@ -801,24 +892,28 @@ SlabPlan slab_plan(const Ctx *c, int64_t n_res, int64_t n_str, int64_t p)
 {
     SlabPlan s;
     s.e_chunks = (int)(round_up(n_str, BI) / KC);
-    const int64_t most = (int64_t)(kSlabBytes / ((size_t)s.e_chunks * KC * 2)) / 256 * 256;
-    const int64_t all = round_up(n_res, 256);
-    // (slabs of equal size)
-    const int64_t cnt = most < 256 ? 0 : ceil_div(all, most);
-    s.rows = cnt ? (int)round_up(ceil_div(all, cnt), 256) : 0;
     s.wide_tiles = (int)(p / 256);
     s.rest = (int)(p % 256);
     if (s.rest > 128) {
         ++s.wide_tiles;
         s.rest = 0;
     }
+    const int64_t most = (int64_t)(kSlabBytes / ((size_t)s.e_chunks * KC * 2)) / 256 * 256;
+    const int64_t all = round_up(n_res, 256);
+    // (slabs of equal size)
+    const int64_t cnt = most < 256 ? 0 : ceil_div(all, most);
+    s.rows = cnt ? (int)round_up(ceil_div(all, cnt), 256) : 0;
     const int rt = s.rows / 256;
     s.ks_wide = s.wide_tiles ? product_splits(c, rt * s.wide_tiles, s.e_chunks) : 0;
     s.ks_rest = s.rest ? product_splits(c, rt, s.e_chunks) : 0;
+    s.col_blocks = (int)ceil_div(p, kApplyPCWide);
+    s.img_stride = (size_t)ceil_div(n_str, BI) * kVImgBytes(kApplyPCWide);
+    const size_t e_bytes = (size_t)s.rows * s.e_chunks * KC * 2, img_bytes = s.col_blocks * s.img_stride;
     Arena A;
-    s.eslab = A.take((size_t)s.rows * s.e_chunks * KC * 2);
+    s.eslab = A.take(e_bytes > img_bytes ? e_bytes : img_bytes);
     s.vt = A.take((size_t)round_up(p, 256) * s.e_chunks * KC * 2);
     s.rowmax = A.take((size_t)round_up(n_res, 1024) * 4);
+    s.flags = A.take((size_t)(1 + ceil_div(n_res, kApplyBJ)) * 4);
     const size_t ow = (size_t)s.ks_wide * s.rows * s.wide_tiles * 256 * 4, orr = (size_t)s.ks_rest * s.rows * 128 * 4;
     s.opart = A.take(ow > orr ? ow : orr);
     s.total = A.off;
@@ -925,10 +1020,12 @@ static fs_status slab_apply(Ctx *c, const Prepared *P, const Side *res, const Si
     if (!x || sp.total > P->extra_bytes || sp.rows < 256) return fail(c, FS_ERR_DEVICE, "internal: plan slab exceeds its buffer");
     float *rowmax = reinterpret_cast<float *>(x + sp.rowmax), *opart = reinterpret_cast<float *>(x + sp.opart);
     unsigned char *vt = reinterpret_cast<unsigned char *>(x + sp.vt);
-    hipLaunchKernelGGL(k_vt_bf16, dim3((unsigned)sp.e_chunks, (unsigned)(round_up(p, 256) / 64)), dim3(256), 0, c->stream, V, ldv, str->cnt,
-                       (int)p, sp.e_chunks, vt);
+    int *flags = reinterpret_cast<int *>(x + sp.flags);
+    const int n_jtiles = (int)ceil_div(res->cnt, kApplyBJ);
+    hipLaunchKernelGGL(k_vt_bf16, dim3((unsigned)sp.e_chunks, (unsigned)((sp.wide_tiles * 256 + (sp.rest ? 128 : 0)) / 64)), dim3(256), 0,
+                       c->stream, V, ldv, str->cnt, (int)p, sp.e_chunks, vt);
     hipLaunchKernelGGL(k_plan_rowmax, dim3((unsigned)ceil_div(res->cnt_pad, 256)), dim3(256), 0, c->stream, res->pot, res->norm, 1.0 / eps,
-                       res->cnt, res->cnt_pad, rowmax);
+                       res->cnt, res->cnt_pad, rowmax, flags, 1 + n_jtiles);   // (fewer flags than padded rows)
     const int n_itiles = (int)ceil_div(str->cnt, BI);
     const int64_t all = round_up(res->cnt, 256);
     for (int64_t off = 0; off < all; off += sp.rows) {
@@ -983,8 +1080,33 @@ static fs_status slab_apply(Ctx *c, const Prepared *P, const Side *res, const Si
                 hipLaunchKernelGGL((k_lse_bf16<2, 4, 4, 0, false, Epi::Product>), g2, dim3(512), 0, c->stream, b);
             hipLaunchKernelGGL(k_plan_finalize, dim3((unsigned)rows), dim3(256), 0, c->stream, opart, b.opart_ld, ks, rows, (int)off, res->cnt,
                                1.0 / eps, res->w, res->log_uniform, res->pot, res->norm, rowmax, col0, cols, out, ldo,
-                               (const double2 *)P->partial, res->cnt_pad, a.splits, (part == 0 || !sp.wide_tiles) ? mass_out : nullptr);
+                               (const double2 *)P->partial, res->cnt_pad, a.splits, mass_out, (part == 0 || !sp.wide_tiles) ? flags : nullptr);
         }
+        FS_HIP(c, hipGetLastError());
+    }
+    // rows that the stored slab is not good for (two launches that leave at once where there are none); the slab's memory is
+    // free by now and takes the value images
+    {
+        constexpr int pc = kApplyPCWide;
+        unsigned char *img = reinterpret_cast<unsigned char *>(x + sp.eslab);
+        hipLaunchKernelGGL(k_vimg_direct, dim3((unsigned)n_itiles, (unsigned)sp.col_blocks), dim3(BI), 0, c->stream, V, ldv, str->cnt, (int)p,
+                           pc, kVImgBytes(pc), (int64_t)sp.img_stride, img, flags);
+        BfArgs a{};
+        a.res = res->pts_b;
+        a.str = str->pts_b;
+        a.bias = str->bias_f;
+        a.kp = P->kp;
+        a.cscale = (float)(2.0 * kLog2e / eps);
+        a.n_jtiles = n_jtiles;
+        a.n_itiles = n_itiles;
+        a.splits = 1;
+        a.tiles_per_split = n_itiles;
+        a.partial_stride = res->cnt_pad;
+        a.vimg = img;
+        const DirectArgs o{flags, res->cnt, 1.0 / eps, res->w, res->log_uniform, res->pot, res->norm, (int)p, out, ldo, mass_out,
+                           (int64_t)sp.img_stride};
+        if ((int64_t)n_jtiles * kApplyBJ > res->cnt_pad) return fail(c, FS_ERR_DEVICE, "internal: bf16 apply launch shape exceeds the padded buffers");
+        hipLaunchKernelGGL((k_apply_direct<pc>), dim3((unsigned)n_jtiles, (unsigned)sp.col_blocks), dim3(512), 0, c->stream, a, o);
         FS_HIP(c, hipGetLastError());
     }
     return FS_OK;

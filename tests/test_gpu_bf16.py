@@ -252,3 +252,48 @@ def test_apply_through_stored_plan(ctx, oracle, n, m, d, p):
     assert np.abs(host(mass)[rows] / r - 1.0).max() <= TOL_APPLY_B
     assert (np.abs(got - want) / scale).max() <= TOL_APPLY_EL_B
     assert np.linalg.norm((got - want) / r[:, None]) <= TOL_APPLY_B * np.linalg.norm(scale / r[:, None])
+
+
+@pytest.mark.parametrize("n,m,d,p", [(700, 600, 320, 300), (300, 513, 784, 97), (129, 300, 512, 257)])
+def test_stored_plan_rows_beyond_its_exponents(ctx, oracle, n, m, d, p):
+    """Rows whose plan entries do not fit the stored slab: masked by a potential of -inf or the lowest values (zero rows),
+    far above and far below one, without weight, +inf and NaN.  As through the fused kernel (p <= 96), and the rows of
+    other 128-row tiles keep their bits."""
+    rng = np.random.default_rng(n + p)
+    x, y, a, b = _rand_problem(rng, n, m, d)
+    eps = float(np.float32(0.05))
+    xb, yb = workloads.to_bf16_round(x), workloads.to_bf16_round(y)
+    g = (0.3 * eps * rng.standard_normal(m)).astype(np.float32)
+    f0 = oracle.update_f(xb, yb, b, eps, g).astype(np.float32)
+    zero = {3: -np.inf, 7: -1e38, 8: -1e30, 9: -3.4e38, 10: -1e6}
+    f, a = f0.copy(), a.copy()
+    for i, v in zero.items():
+        f[i] = v
+    a[12] = 0.0
+    scaled = {20: 70.0, 21: 25.0, 22: -35.0, 23: -55.0, 127: 60.0}   # e^+-55: beyond the slab, within float
+    for i, v in scaled.items():
+        f[i] += np.float32(v * eps)
+    bad = {30: np.inf, 31: np.nan}
+    for i, v in bad.items():
+        f[i] = v
+    V = rng.standard_normal((m, p)).astype(np.float32)
+    say("bf16 stored plan, rows beyond its exponents n=%d m=%d d=%d p=%d" % (n, m, d, p))
+    plain, _ = ctx.fs_apply_plan(make_problem(x, y, a, b, compute=BF), eps, dev(f0), dev(g), dev(V), want_mass=True)
+    out, mass = ctx.fs_apply_plan(make_problem(x, y, a, b, compute=BF), eps, dev(f), dev(g), dev(V), want_mass=True)
+    got, gm = host(out), host(mass)
+    rows = np.array([i for i in range(128) if i not in zero and i not in bad])
+    fin = np.where(np.isfinite(f), f, np.float32(0.0))
+    want, r = oracle.apply_plan(xb, yb, a, b, eps, fin, g, V, rows=rows, return_mass=True)
+    scale = oracle.apply_plan(xb, yb, a, b, eps, fin, g, np.abs(V), rows=rows)
+    live = a[rows] > 0
+    assert np.abs(gm[rows][live] / r[live] - 1.0).max() <= TOL_APPLY_B
+    assert (np.abs(got[rows][live] - want[live]) / scale[live]).max() <= TOL_APPLY_EL_B
+    for i in list(zero) + [12]:
+        assert np.all(got[i] == 0.0) and gm[i] == 0.0, i
+    assert not np.isfinite(got[30]).any() and np.isnan(got[31]).all() and not np.isfinite(gm[[30, 31]]).any()
+    assert np.array_equal(got[128:], host(plain)[128:])
+    # the fused kernel (96 columns) says the same
+    fused, fm = ctx.fs_apply_plan(make_problem(x, y, a, b, compute=BF), eps, dev(f), dev(g), dev(V[:, :96]), want_mass=True)
+    fused, fm = host(fused), host(fm)
+    assert np.array_equal(np.isfinite(fused).all(1), np.isfinite(got).all(1)) and np.array_equal(np.isfinite(fm), np.isfinite(gm))
+    assert np.all(fused[list(zero) + [12]] == 0.0)
