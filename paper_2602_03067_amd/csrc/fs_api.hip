@@ -251,8 +251,10 @@ fs_status ensure_ws(Ctx *c, size_t need)
     }
     void *pnew = nullptr;
     hipError_t e = hipMalloc(&pnew, need);
-    if (e != hipSuccess)
+    if (e != hipSuccess) {
+        (void)hipGetLastError();   // (reported here, not by the check after the next launch)
         return fail(c, FS_ERR_ALLOC, "workspace of %zu bytes: %s", need, hipGetErrorString(e));
+    }
     c->ws = (char *)pnew;
     c->ws_bytes = need;
     return FS_OK;
@@ -348,14 +350,20 @@ fs_status apply_begin(Ctx *c, const fs_problem *prob, float eps, const float *f,
     fs_status st;
     const int64_t n_res = transposed ? prob->m : prob->n;
     const int64_t n_str = transposed ? prob->n : prob->m;
-    size_t extra = 0;
+    size_t extra = 0, least = 0;
     switch (choose_path(prob)) {
     case Path::LowD: extra = lowd_apply_ws(c, n_res, n_str, prob->d, p); break;
     case Path::F64: extra = f64_apply_ws(c, n_res, n_str, prob->d, p); break;   // (covers both kernels of a pass)
-    case Path::BF16: extra = bf16_apply_ws(c, n_res, n_str, prob->d, p); break;
+    case Path::BF16: extra = bf16_apply_ws(c, n_res, n_str, prob->d, p, &least); break;
     }
     extra = (extra + 255) & ~size_t(255);
-    if ((st = prepare(c, prob, P, extra + tail_bytes, &P->extra)) != FS_OK) return st;
+    least = (least + 255) & ~size_t(255);
+    st = prepare(c, prob, P, extra + tail_bytes, &P->extra);
+    if (st == FS_ERR_ALLOC && least && least < extra) {   // no memory for the faster form: the one that needs less
+        extra = least;
+        st = prepare(c, prob, P, extra + tail_bytes, &P->extra);
+    }
+    if (st != FS_OK) return st;
     P->extra_bytes = extra;
     if (tail) *tail = P->extra + extra;
     if ((st = launch_bias_from_user(c, P, &P->X, f, eps, true, false)) != FS_OK) return st;

@@ -865,6 +865,9 @@ constexpr int kApplyBJ = 128;   // resident rows per workgroup of the applicatio
 // the exponentials take 212 us (0.93 PFLOP/s with the store of 247 MB), 768 columns of the product 161 us (1.18 PFLOP/s) and
 // the last 16 columns 54 us, which is the time to read the slab once more.
 constexpr size_t kSlabBytes = size_t(256) << 20;
+// The whole workspace of this route (slab, accumulators, transposed values, value images of the rows done again): beyond it
+// the fused kernel runs, which needs a fraction of it.
+constexpr size_t kSlabTotalBytes = size_t(1) << 30;
 
 struct SlabPlan {
     int rows = 0;            // resident rows of a slab (multiple of 256)
@@ -898,7 +901,10 @@ SlabPlan slab_plan(const Ctx *c, int64_t n_res, int64_t n_str, int64_t p)
         ++s.wide_tiles;
         s.rest = 0;
     }
-    const int64_t most = (int64_t)(kSlabBytes / ((size_t)s.e_chunks * KC * 2)) / 256 * 256;
+    // a row's exponentials and its accumulators for one split of the contraction (more splits are taken only where there are
+    // so few rows that a tile per CU does not come together: 64 MB of accumulators at most)
+    const size_t per_row = (size_t)s.e_chunks * KC * 2 + (size_t)(s.wide_tiles ? s.wide_tiles * 256 : 128) * 4;
+    const int64_t most = (int64_t)(kSlabBytes / per_row) / 256 * 256;
     const int64_t all = round_up(n_res, 256);
     // (slabs of equal size)
     const int64_t cnt = most < 256 ? 0 : ceil_div(all, most);
@@ -925,9 +931,11 @@ SlabPlan slab_plan(const Ctx *c, int64_t n_res, int64_t n_str, int64_t p)
 // d = 64, 128 columns 405 / 433; d = 128, 128 columns 536 / 425; d = 192, 192 columns 623 / 520; d = 96, 200 columns
 // 655 / 533; d = 256, 256 columns 1020 / 554; d = 784, 100 columns 1357 / 772.
 constexpr double kSlabTraffic = 230.0;
-bool use_slab(int64_t n_str, int64_t d, int64_t p)
+bool use_slab(const Ctx *c, int64_t n_res, int64_t n_str, int64_t d, int64_t p)
 {
-    if (p <= kApplyPCWide || (size_t)round_up(n_str, BI) * 2 * 256 > kSlabBytes) return false;
+    if (p <= kApplyPCWide) return false;
+    const SlabPlan plan = slab_plan(c, n_res, n_str, p);
+    if (plan.rows < 256 || plan.total > kSlabTotalBytes) return false;
     const double fused = (double)ceil_div(p, kApplyPCWide) * (double)(round_up(d, KC) + kApplyPCWide);
     const int64_t rest = p % 256;
     const double cols = (double)(p / 256 * 256 + (rest == 0 ? 0 : rest > 128 ? 256 : 128));
@@ -1112,20 +1120,22 @@ static fs_status slab_apply(Ctx *c, const Prepared *P, const Side *res, const Si
     return FS_OK;
 }
 
-// workspace of bf16_apply: [splits][rows][kApplyPC] float accumulators, then the value images
-size_t bf16_apply_ws(const Ctx *c, int64_t n_res, int64_t n_str, int64_t d, int64_t p)
+// workspace of bf16_apply: [splits][rows][kApplyPC] float accumulators, then the value images (fused kernel), or what the
+// stored slab takes; *least: what the call can do with
+size_t bf16_apply_ws(const Ctx *c, int64_t n_res, int64_t n_str, int64_t d, int64_t p, size_t *least)
 {
-    if (use_slab(n_str, d, p)) return slab_plan(c, n_res, n_str, p).total;
     const int n_jtiles = (int)ceil_div(n_res, kApplyBJ), n_itiles = (int)ceil_div(n_str, BI);
     const int splits = choose_splits(c, n_jtiles, n_itiles, max_splits(c->partial_budget, n_res), 1);
     const size_t opart = (size_t)splits * (size_t)round_up(n_res, 1024) * kApplyPCWide * 4;
-    return ((opart + 1023) & ~size_t(1023)) + (size_t)n_itiles * kVImgBytes(kApplyPCWide);
+    *least = ((opart + 1023) & ~size_t(1023)) + (size_t)n_itiles * kVImgBytes(kApplyPCWide);
+    return use_slab(c, n_res, n_str, d, p) ? slab_plan(c, n_res, n_str, p).total : *least;
 }
 
 fs_status bf16_apply(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, const float *V, int64_t p,
                      int64_t ldv, float *out, int64_t ldo, float *mass_out)
 {
-    if (use_slab(str->cnt, P->d, p)) return slab_apply(c, P, res, str, eps, V, p, ldv, out, ldo, mass_out);
+    if (use_slab(c, res->cnt, str->cnt, P->d, p) && slab_plan(c, res->cnt, str->cnt, p).total <= P->extra_bytes)
+        return slab_apply(c, P, res, str, eps, V, p, ldv, out, ldo, mass_out);
     BfArgs a{};
     a.res = res->pts_b;
     a.str = str->pts_b;

@@ -521,7 +521,7 @@ fs_status bf16_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, 
 fs_status bf16_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, void *partial_y, Splits *splits_x,
                         Splits *splits_y);
 // plan application in bf16 mode (Alg. 2 / Alg. 4): workspace bytes and the pass itself
-size_t bf16_apply_ws(const Ctx *c, int64_t n_res, int64_t n_str, int64_t d, int64_t p);
+size_t bf16_apply_ws(const Ctx *c, int64_t n_res, int64_t n_str, int64_t d, int64_t p, size_t *least);
 fs_status bf16_apply(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, const float *V, int64_t p,
                      int64_t ldv, float *out, int64_t ldo, float *mass_out);
 

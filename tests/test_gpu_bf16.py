@@ -297,3 +297,28 @@ def test_stored_plan_rows_beyond_its_exponents(ctx, oracle, n, m, d, p):
     fused, fm = host(fused), host(fm)
     assert np.array_equal(np.isfinite(fused).all(1), np.isfinite(got).all(1)) and np.array_equal(np.isfinite(fm), np.isfinite(gm))
     assert np.all(fused[list(zero) + [12]] == 0.0)
+
+
+@pytest.mark.parametrize("n,m,d,p,most", [(262144, 256, 512, 1024, 600), (256, 200000, 512, 512, 700), (300000, 300, 300, 97, 500)])
+def test_stored_plan_workspace_is_bounded(n, m, d, p, most):
+    """Few points on one side: neither the accumulators of a slab nor the transposed values grow beyond what is stated
+    (256 MB of slab, 1 GiB in all)."""
+    free = lambda: torch.cuda.mem_get_info()[0]
+    c = binding.Context(0)
+    x, y = torch.rand(n, d, device="cuda:0"), torch.rand(m, d, device="cuda:0")
+    prob = binding.Problem(x, y, None, None, BF)
+    f, g = torch.zeros(n, device="cuda:0"), torch.zeros(m, device="cuda:0")
+    V = torch.rand(m, p, device="cuda:0")
+    say("bf16 stored plan workspace n=%d m=%d d=%d p=%d" % (n, m, d, p))
+    c.fs_update_f(prob, 5.0, g)   # the problem itself: its workspace is there
+    out = c.fs_apply_plan(prob, 5.0, f, g, V)
+    torch.cuda.synchronize()
+    del out
+    torch.cuda.empty_cache()
+    with_ws = free()
+    c.close()
+    torch.cuda.synchronize()
+    used = (free() - with_ws) / 2 ** 20
+    say("  workspace %.0f MiB" % used)
+    problem = (n + m) * (d + 32) * 2 / 2 ** 20 + 2 * 64   # bf16 copies, potentials, split records
+    assert used <= problem + most
