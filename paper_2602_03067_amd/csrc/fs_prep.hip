@@ -671,8 +671,8 @@ struct ApplyFinalizeArgs {
     int64_t ldo;
     float *mass_out;
 };
-// ALT: one of two kernels wrote the accumulators; the grid fits the row length of the first, so where the gate chose the
-// other, whose rows may be longer, a block takes several groups of rows
+// ALT: one of two kernels wrote the accumulators, with rows of different length, so a block may take several groups of rows
+// (see the launch)
 template <bool ALT>
 __global__ __launch_bounds__(256) void k_apply_finalize(ApplyFinalizeArgs a)
 {
@@ -767,11 +767,16 @@ fs_status launch_apply_finalize(Ctx *c, const Prepared *P, const Side *res, cons
     const ApplyFinalizeArgs a{(const double2 *)P->partial, res->cnt_pad, opart,           res->cnt_pad, PC,       splits.n,  PC_alt, splits.alt, fx_gate(P, eps),
                               res->cnt,                    1.0 / eps,    res->w,          res->log_uniform,       res->pot,  res_norm, p0,       p,
                               out,                         ldo,          mass_out};
-    const dim3 grid((unsigned)ceil_div(res->cnt, 256 / PC));
-    if (splits.alt)
-        hipLaunchKernelGGL(k_apply_finalize<true>, grid, dim3(256), 0, c->stream, a);
-    else
-        hipLaunchKernelGGL(k_apply_finalize<false>, grid, dim3(256), 0, c->stream, a);
+    int64_t blocks = ceil_div(res->cnt, 256 / PC);
+    if (splits.alt) {
+        // enough blocks for either kernel's rows, up to 2048 for the other's: with the main kernel's grid alone (one column:
+        // 256 rows a block, eleven blocks at n = 2600) the 64-column rows of the fp64 kernel took 64 rounds, 240 us instead of 8
+        const int64_t other = ceil_div(res->cnt, 256 / PC_alt);
+        const int64_t enough = other < 2048 ? other : 2048;
+        if (enough > blocks) blocks = enough;
+        hipLaunchKernelGGL(k_apply_finalize<true>, dim3((unsigned)blocks), dim3(256), 0, c->stream, a);
+    } else
+        hipLaunchKernelGGL(k_apply_finalize<false>, dim3((unsigned)blocks), dim3(256), 0, c->stream, a);
     FS_HIP(c, hipGetLastError());
     return FS_OK;
 }

@@ -397,3 +397,20 @@ def test_plan_sums_of_data_with_regular_digits(ctx, oracle, d, kind):
             e = [np.linalg.norm(host(got) - want) / np.linalg.norm(want), np.linalg.norm(host(mass) - want[:, 0]) / np.linalg.norm(want[:, 0])]
             say("  p=%d sums %.2e mass %.2e" % (p, *e))
             assert max(e) <= 2.5e-7 + (np.log(2.0) * d * 2.0 ** -31 * v / 64 if kind == "one direction" else 0.0)
+
+
+@pytest.mark.parametrize("p", [1, 4, 70])
+def test_merge_of_an_application_beyond_the_gate(ctx, oracle, p):
+    """The fp64 kernel's accumulator rows are longer than those the merge's grid is made for; more rows than one round of it."""
+    n, m, d = 9001, 40, 20
+    eps = float(np.float32(1e-4))
+    rng, x, y, a, b = _problem(23, n, m, d)
+    prob = make_problem(x, y, a, b)
+    say("fx merge beyond the gate p=%d" % p)
+    g = (rng.standard_normal(m) * eps).astype(np.float32)
+    f = oracle.update_f(x, y, b, eps, g).astype(np.float32)
+    V = rng.standard_normal((m, p)).astype(np.float32)
+    got, mass = ctx.fs_apply_plan(prob, eps, dev(f), dev(g), dev(V), want_mass=True)
+    want, r = oracle.apply_plan(x, y, a, b, eps, f, g, V, return_mass=True)
+    _check_values(got, want)
+    _check_values(mass, r)
