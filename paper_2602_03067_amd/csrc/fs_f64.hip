@@ -65,7 +65,8 @@ struct PassArgs {
     int64_t lda, n_res;
     int d;                   // real number of coordinates (columns of hadA)
     const double *had_add;   // [rows] or nullptr: summand of the weights of a row (points stored shifted, see k_had_digits)
-    FxGate gate;             // r2 != nullptr: the fixed-point kernel of the same pass runs where the gate is on
+    FxGate gate;             // GATED: the fixed-point kernel of the same pass runs where the gate is on
+    int row_blocks, splits;  // GATED half-step: the work of the grid
 };
 
 // (never more than 256 registers per lane: with at most 256 the compiler keeps the MFMA
@@ -497,20 +498,44 @@ __device__ __forceinline__ void pass_f64_body(const PassArgs &a, const int bx, c
 }
 
 // (the plain application needs at most 158 registers and 51 KB of LDS: three workgroups per CU)
-template <bool APPLY, bool HAD = false, int NCT = 4, int JT = 4, int NW = 4, bool LAZY = APPLY>
+// GATED: launched beside the fixed-point kernel, and mostly for nothing.  In the half-steps a grid of what the chip holds at a
+// time goes through the (row block, split) pairs: it leaves sooner than one workgroup per pair.  (Not in the
+// applications, one per call: around their body the loop costs forty registers.)
+template <bool APPLY, bool HAD = false, int NCT = 4, int JT = 4, int NW = 4, bool LAZY = APPLY, bool GATED = false>
 __global__ __launch_bounds__(64 * NW, (APPLY && !HAD && NCT <= 4) ? 3 : 2) void k_pass_f64(PassArgs a)
 {
-    if (a.gate.r2 && a.gate.on()) return;   // (uniform over the grid)
-    pass_f64_body<APPLY, HAD, NCT, JT, NW, LAZY>(a, blockIdx.x, blockIdx.y);
+    if constexpr (GATED) {
+        if (a.gate.on()) return;   // (uniform over the grid)
+    }
+    if constexpr (GATED && !APPLY) {
+        const int total = a.row_blocks * a.splits;
+        for (int k = blockIdx.x; k < total; k += gridDim.x) {
+            const int by = k / a.row_blocks;
+            pass_f64_body<APPLY, HAD, NCT, JT, NW, LAZY>(a, k - by * a.row_blocks, by);
+            __syncthreads();   // the merge has read its scratch
+        }
+    } else
+        pass_f64_body<APPLY, HAD, NCT, JT, NW, LAZY>(a, blockIdx.x, blockIdx.y);
 }
 
 // Both LSE passes of one iteration of the averaged schedule (Eq. 4-5) in one launch: they read the same
 // old potentials, so the row blocks of the f-pass (a0, the first rb0 of the grid) and of the g-pass (a1)
 // share a grid; grid.y covers the larger of the two split counts.
-template <int JT, int NW, bool LAZY>
+// (GATED: as above)
+template <int JT, int NW, bool LAZY, bool GATED = false>
 __global__ __launch_bounds__(64 * NW, 2) void k_pass_f64_pair(PassArgs a0, PassArgs a1, int rb0, int splits0, int splits1)
 {
-    if (a0.gate.r2 && a0.gate.on()) return;
+    if constexpr (GATED) {
+        if (a0.gate.on()) return;
+        const int total0 = rb0 * splits0, total = total0 + a1.row_blocks * splits1;
+        for (int k = blockIdx.x; k < total; k += gridDim.x) {
+            const bool second = k >= total0;
+            const int q = second ? k - total0 : k, rb = second ? a1.row_blocks : rb0;
+            pass_f64_body<false, false, 4, JT, NW, LAZY>(second ? a1 : a0, q % rb, q / rb);
+            __syncthreads();
+        }
+        return;
+    }
     const bool second = (int)blockIdx.x >= rb0;   // uniform over the workgroup
     if ((int)blockIdx.y >= (second ? splits1 : splits0)) return;
     pass_f64_body<false, false, 4, JT, NW, LAZY>(second ? a1 : a0, (int)blockIdx.x - (second ? rb0 : 0), blockIdx.y);
@@ -580,6 +605,8 @@ static fs_status lse_pass_args(Ctx *c, const Prepared *P, const Side *res, const
     a.n_tiles = (int)ceil_div(str->cnt, BC);
     a.tiles_per_split = (int)(s.cols_per_split / BC);
     a.partial = (double2 *)partial;
+    a.row_blocks = s.row_blocks;
+    a.splits = s.splits;
     a.partial_stride = res->cnt_pad;
     if ((int64_t)s.row_blocks * s.rows_per_block > res->cnt_pad || (int64_t)a.n_tiles * BC > str->cnt_pad ||
         (size_t)s.splits * res->cnt_pad * 16 > P->partial_bytes || (a.kp % KC) != 0 || a.kc > a.kp)
@@ -587,6 +614,13 @@ static fs_status lse_pass_args(Ctx *c, const Prepared *P, const Side *res, const
     *out = a;
     *shape = s;
     return FS_OK;
+}
+
+// grid of a GATED launch with `total` pairs of row block and split
+static unsigned gated_grid(const Ctx *c, int64_t total, int wg_per_cu)
+{
+    const int64_t slots = (int64_t)c->num_cu * wg_per_cu;
+    return (unsigned)(total < slots ? total : slots);
 }
 
 // (with digit images: the fixed-point kernel and the float64 one, one of which leaves at once; see FxGate)
@@ -602,6 +636,9 @@ fs_status f64_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, d
     const dim3 grid((unsigned)s.row_blocks, (unsigned)s.splits);
     if (P->path == Path::LowD)
         hipLaunchKernelGGL((k_pass_f64<false, false, 4, kLseJT, kLseNW, true>), grid, dim3(64 * kLseNW), 0, c->stream, a);
+    else if (P->fx_ks)
+        hipLaunchKernelGGL((k_pass_f64<false, false, 4, kLseJT, kLseNW, false, true>),
+                           dim3(gated_grid(c, (int64_t)s.row_blocks * s.splits, kLseWgPerCu)), dim3(64 * kLseNW), 0, c->stream, a);
     else
         hipLaunchKernelGGL((k_pass_f64<false, false, 4, kLseJT, kLseNW, false>), grid, dim3(64 * kLseNW), 0, c->stream, a);
     prof_end(c);
@@ -626,6 +663,10 @@ fs_status f64_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, v
     if (P->path == Path::LowD)
         hipLaunchKernelGGL((k_pass_f64_pair<kLseJT, kLseNW, true>), grid, dim3(64 * kLseNW), 0, c->stream, ax, ay, sx.row_blocks,
                            sx.splits, sy.splits);
+    else if (P->fx_ks)
+        hipLaunchKernelGGL((k_pass_f64_pair<kLseJT, kLseNW, false, true>),
+                           dim3(gated_grid(c, (int64_t)sx.row_blocks * sx.splits + (int64_t)sy.row_blocks * sy.splits, kLseWgPerCu)),
+                           dim3(64 * kLseNW), 0, c->stream, ax, ay, sx.row_blocks, sx.splits, sy.splits);
     else
         hipLaunchKernelGGL((k_pass_f64_pair<kLseJT, kLseNW, false>), grid, dim3(64 * kLseNW), 0, c->stream, ax, ay, sx.row_blocks,
                            sx.splits, sy.splits);
@@ -695,7 +736,13 @@ fs_status f64_apply(Ctx *c, const Prepared *P, const Side *res, const Side *str,
             splits = Splits(fx_splits, s.splits);
         }
         const dim3 grid((unsigned)s.row_blocks, (unsigned)s.splits);
-#define FS_F64_APPLY(H, N) hipLaunchKernelGGL((k_pass_f64<true, H, N, kApplyJT, kApplyNW>), grid, dim3(64 * kApplyNW), 0, c->stream, a)
+#define FS_F64_APPLY(H, N)                                                                                                         \
+    do {                                                                                                                           \
+        if (fx)                                                                                                                    \
+            hipLaunchKernelGGL((k_pass_f64<true, H, N, kApplyJT, kApplyNW, true, true>), grid, dim3(64 * kApplyNW), 0, c->stream, a); \
+        else                                                                                                                       \
+            hipLaunchKernelGGL((k_pass_f64<true, H, N, kApplyJT, kApplyNW>), grid, dim3(64 * kApplyNW), 0, c->stream, a);           \
+    } while (0)
         if (hadA) {
             switch (nct) {
             case 1: FS_F64_APPLY(true, 1); break;

@@ -605,8 +605,9 @@ __global__ __launch_bounds__(256, (FxShape<KS, 0, 1>::kWgPerCu)) void k_fx_pair(
 // Zero outside the matrix; odd tiles hold the negated values (see finish).  A block of 128 nc threads makes the image of
 // one tile.
 __global__ __launch_bounds__(512) void k_vimg_fx(const float *V, int64_t ldv, int64_t n_str, int p0, int p, int nc, unsigned char *img,
-                                                 int *vflag)
+                                                 int *vflag, FxGate gate)
 {
+    if (!gate.on()) return;
     const int64_t t = blockIdx.x;
     const int cb = threadIdx.x >> 7;
     const int h = (threadIdx.x >> 6) & 1, l = threadIdx.x & 63, lh = l >> 5;
@@ -891,7 +892,7 @@ fs_status fx_apply_pass(Ctx *c, const Prepared *P, const Side *res, const Side *
     a.vflag = reinterpret_cast<const int *>(x + buf.vflag);
     if (mode == 2)
         hipLaunchKernelGGL(k_vimg_fx, dim3((unsigned)a.n_tiles), dim3(128 * nc), 0, c->stream, V, ldv, str->cnt, p0, (int)p, nc,
-                           x + buf.vimg, reinterpret_cast<int *>(x + buf.vflag));
+                           x + buf.vimg, reinterpret_cast<int *>(x + buf.vflag), a.gate);
     if (hadA) {
         a.had = x + buf.had;
         a.had_scale = reinterpret_cast<const float *>(x + buf.scale);

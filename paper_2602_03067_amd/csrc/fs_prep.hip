@@ -422,6 +422,8 @@ __global__ __launch_bounds__(256) void k_prep_fx(PrepFxSide s0, PrepFxSide s1, i
 // largest finite |log w| log2e in absmax[0] (the two parts of a bias, which scale differently with
 // eps), as bit patterns of non-negative doubles (for those, the order of the bit patterns is the
 // order of the values)
+// (FX here and below: the side has bias records of the fixed-point kernels, or two kernels may have written the statistics)
+template <bool FX>
 __global__ void k_bias_from_user(const float *pot_user, int64_t cnt, double inv_eps, const float *w,
                                  double log_uniform, double *pot, BiasSink sink, unsigned long long *absmax)
 {
@@ -435,7 +437,7 @@ __global__ void k_bias_from_user(const float *pot_user, int64_t cnt, double inv_
         mag_pot = fabs((pu - sink.norm[i]) * inv_eps) * kLog2e;
         mag_w = fabs(lw) < INFINITY ? fabs(lw) * kLog2e : 0.0;   // zero-weight points never contribute
     }
-    if (sink.brec) store_fx_record(sink, i, cnt, b, inv_eps);
+    if constexpr (FX) store_fx_record(sink, i, cnt, b, inv_eps);
     if (absmax) {   // one pair of atomics per workgroup (256 threads)
         __shared__ double shm[2][4];
         for (int off = 32; off > 0; off >>= 1) {
@@ -456,6 +458,7 @@ __global__ void k_bias_from_user(const float *pot_user, int64_t cnt, double inv_
     }
 }
 
+template <bool FX>
 __device__ __forceinline__ void finalize_body(const FinalizeArgs &a, const int bx)
 {
     // dev_part == nullptr: store the update.  dev_part != nullptr: measure the marginal deviation
@@ -470,7 +473,7 @@ __device__ __forceinline__ void finalize_body(const FinalizeArgs &a, const int b
     }
     const int64_t i = (int64_t)bx * 256 + threadIdx.x;
     double dev = 0.0, mass = 0.0, bias = 0.0;
-    const int splits = a.splits_alt && !a.gate.on() ? a.splits_alt : a.splits;
+    const int splits = FX && !a.gate.on() ? a.splits_alt : a.splits;
     if (i < a.cnt) {
         double M = -INFINITY;
 #pragma unroll 8
@@ -486,7 +489,7 @@ __device__ __forceinline__ void finalize_body(const FinalizeArgs &a, const int b
         }
         finalize_point(a, i, M, S, &dev, &mass, &bias);
     }
-    if (a.sink.brec && a.inv_eps_next > 0.0 && (!a.dev_part || a.save_old)) store_fx_record(a.sink, i, a.cnt, bias, a.inv_eps_next);
+    if (FX && a.inv_eps_next > 0.0 && (!a.dev_part || a.save_old)) store_fx_record(a.sink, i, a.cnt, bias, a.inv_eps_next);
     if (a.dev_part) {
         double t = block_sum_256(dev, sh);
         if (threadIdx.x == 0) a.dev_part[bx] = t;
@@ -522,15 +525,17 @@ __global__ void k_gauge_export(const double *x_pot, int64_t n, const double *y_p
         g_user[i - n] = (float)(y_pot[i - n] + scalars[0]);
 }
 
-__global__ __launch_bounds__(256) void k_finalize(FinalizeArgs a) { finalize_body(a, blockIdx.x); }
+template <bool FX>
+__global__ __launch_bounds__(256) void k_finalize(FinalizeArgs a) { finalize_body<FX>(a, blockIdx.x); }
 
 // the merges of the two passes of an averaged iteration (Eq. 4-5) in one launch
+template <bool FX>
 __global__ __launch_bounds__(256) void k_finalize_pair(FinalizeArgs a0, FinalizeArgs a1)
 {
     if ((int)blockIdx.x < a0.blocks)
-        finalize_body(a0, blockIdx.x);
+        finalize_body<FX>(a0, blockIdx.x);
     else
-        finalize_body(a1, (int)blockIdx.x - a0.blocks);
+        finalize_body<FX>(a1, (int)blockIdx.x - a0.blocks);
 }
 
 __global__ void k_export_f32(const double *src, int64_t cnt, float *dst)
@@ -567,6 +572,7 @@ __global__ __launch_bounds__(256) void k_sum_value_terms(const double *pr, int64
 // After an LSE pass over `res`: mass_i = w_i exp((pot_i - pot_i^+)/eps) is the row sum of the plan
 // that the CURRENT potentials induce (Prop. 3).  Block sums of mass_i, w_i pot_i and w_i go to
 // part[0][.], part[1][.], part[2][.] (part has 3 * gridDim.x doubles).
+template <bool FX>
 __global__ __launch_bounds__(256) void k_value_terms(const double2 *partial, int64_t stride, int splits_n, int splits_alt, FxGate gate, int64_t cnt,
                                                      double eps, const float *w, double log_uniform,
                                                      const double *res_norm, const double *pot, double *part)
@@ -574,7 +580,7 @@ __global__ __launch_bounds__(256) void k_value_terms(const double2 *partial, int
     __shared__ double sh[256];
     int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     double t[3] = {0.0, 0.0, 0.0};
-    const int splits = splits_alt && !gate.on() ? splits_alt : splits_n;
+    const int splits = FX && !gate.on() ? splits_alt : splits_n;
     if (i < cnt) {
         double M = -INFINITY;
 #pragma unroll 8
@@ -988,7 +994,7 @@ fs_status launch_bias_from_user(Ctx *c, Prepared *P, Side *side, const float *po
             if (st != FS_OK) return st;
         }
     }
-    hipLaunchKernelGGL(k_bias_from_user, dim3((unsigned)ceil_div(side->cnt, 256)), dim3(256), 0, c->stream, pot_user,
+    hipLaunchKernelGGL(P->fx_ks ? k_bias_from_user<true> : k_bias_from_user<false>, dim3((unsigned)ceil_div(side->cnt, 256)), dim3(256), 0, c->stream, pot_user,
                        side->cnt, 1.0 / eps, side->w, side->log_uniform, side->pot, sink_of(P, side, eps, P->rho_max < 0.0),
                        absmax);
     FS_HIP(c, hipGetLastError());
@@ -1068,7 +1074,7 @@ fs_status launch_finalize(Ctx *c, const Prepared *P, Side *res, const double *re
     FinalizeArgs a = finalize_args(P, P->partial, res, res_norm, splits, eps_cur, eps_next_bias, user_out, dev_part,
                                    mix, save_old);
     set_gauge(&a, P, gauge, gauge_prev_cnt, gauge_prev_eps);
-    hipLaunchKernelGGL(k_finalize, dim3((unsigned)a.blocks), dim3(256), 0, c->stream, a);
+    hipLaunchKernelGGL(P->fx_ks ? k_finalize<true> : k_finalize<false>, dim3((unsigned)a.blocks), dim3(256), 0, c->stream, a);
     if (abs_dev_sum)
         hipLaunchKernelGGL(k_sum_to, dim3(1), dim3(256), 0, c->stream, dev_part, (int64_t)a.blocks, abs_dev_sum);
     FS_HIP(c, hipGetLastError());
@@ -1098,7 +1104,7 @@ fs_status launch_finalize_pair(Ctx *c, const Prepared *P, Side *X, const double 
             ax.gauge_scalars = P->scalars + 8;
         }
     }
-    hipLaunchKernelGGL(k_finalize_pair, dim3((unsigned)(ax.blocks + ay.blocks)), dim3(256), 0, c->stream, ax, ay);
+    hipLaunchKernelGGL(P->fx_ks ? k_finalize_pair<true> : k_finalize_pair<false>, dim3((unsigned)(ax.blocks + ay.blocks)), dim3(256), 0, c->stream, ax, ay);
     FS_HIP(c, hipGetLastError());
     return FS_OK;
 }
@@ -1143,7 +1149,7 @@ fs_status launch_value_terms(Ctx *c, const Prepared *P, const Side *res, const d
 {
     const unsigned br = (unsigned)ceil_div(res->cnt, 256), bs = (unsigned)ceil_div(str->cnt, 256);
     double *pr = scratch, *ps = scratch + 3 * (size_t)br;
-    hipLaunchKernelGGL(k_value_terms, dim3(br), dim3(256), 0, c->stream, (const double2 *)P->partial, res->cnt_pad, splits.n,
+    hipLaunchKernelGGL(P->fx_ks ? k_value_terms<true> : k_value_terms<false>, dim3(br), dim3(256), 0, c->stream, (const double2 *)P->partial, res->cnt_pad, splits.n,
                        splits.alt, fx_gate(P, eps), res->cnt, eps, res->w, res->log_uniform, res_norm, res->pot, pr);
     hipLaunchKernelGGL(k_weighted_sums, dim3(bs), dim3(256), 0, c->stream, str->cnt, str->w, str->log_uniform, str->pot, ps);
     hipLaunchKernelGGL(k_sum_value_terms, dim3(5), dim3(256), 0, c->stream, pr, (int64_t)br, ps, (int64_t)bs, dst);

@@ -414,3 +414,21 @@ def test_merge_of_an_application_beyond_the_gate(ctx, oracle, p):
     want, r = oracle.apply_plan(x, y, a, b, eps, f, g, V, return_mass=True)
     _check_values(got, want)
     _check_values(mass, r)
+
+
+def test_half_steps_beyond_the_gate_with_many_row_blocks(ctx, oracle):
+    """More (row block, split) pairs than the fp64 kernel beside the fixed-point one has workgroups: each takes several."""
+    n, m, d = 40003, 70, 20
+    eps = float(np.float32(1e-4))
+    rng, x, y, a, b = _problem(29, n, m, d)
+    prob = make_problem(x, y, a, b)
+    say("fx many row blocks beyond the gate")
+    g = (rng.standard_normal(m) * eps).astype(np.float32)
+    f = oracle.update_f(x, y, b, eps, g)
+    _check_pot(ctx.fs_update_f(prob, eps, dev(g)), f, eps)
+    _check_pot(ctx.fs_update_g(prob, eps, dev(f.astype(np.float32))), oracle.update_g(x, y, a, eps, f.astype(np.float32)), eps)
+    fs, gs = torch.zeros(n, device="cuda:0"), torch.zeros(m, device="cuda:0")
+    ctx.fs_solve_symmetric(prob, eps, 3, fs, gs)
+    fo, go = oracle.solve_symmetric(x, y, a, b, eps, 3)
+    for got, want in ((fs, fo), (gs, go)):
+        assert np.all(np.abs(host(got) - want) <= 3e-6 * eps + 2.0 ** -24 * np.abs(want) * 1.01)
