@@ -87,11 +87,11 @@ __device__ inline double store_bias(const BiasSink &s, int64_t i, double pot, do
 
 // Bias record of the fixed-point kernels, per tile of 32 points four times 32 integers:
 //   b = u2 hi + u4 lo + u6 lo2,  u2 = cscale r2^2 2^-14,  u4 = u2 2^-16,  u6 = u4 2^-16 (lo2 only where the pass forms
-//   products of that weight, see FxGate::full);  the flag of the tile
+//   products of that weight, see FxGate::full);  the kind of the tile, and the set of its points without weight
 // These are the initial values of the three accumulators.  |hi| <= 0.95 2^21 keeps 2^8 (hi + the leading digit products)
-// within half of the integer range, so the difference of any two scores is representable.  A tile with a bias beyond
-// that (or not finite), or one that is not full, is flagged and its record left zero.  All threads of a wave call this
-// with consecutive i; a side's points start at a multiple of 32.
+// within half of the integer range, so the difference of any two scores is representable.  Kind (rec[96]): 2 where points have
+// a bias of -inf, each a bit of rec[97]; 1 (flagged, its record left zero) where another bias is beyond that range or not
+// finite, or where the tile is not full; else 0.  All threads of a wave call this with consecutive i; a side's points start at a multiple of 32.
 __device__ inline void store_fx_record(const BiasSink &s, int64_t i, int64_t cnt, double b, double inv_eps)
 {
     FxGate gate;
@@ -99,18 +99,21 @@ __device__ inline void store_fx_record(const BiasSink &s, int64_t i, int64_t cnt
     gate.cscale = 2.0 * kLog2e * inv_eps;
     const double B = b / gate.unit(14);
     const double hi = floor(B);
-    const bool ok = i < cnt && fabs(hi) <= 1992294.0;
-    const unsigned long long all = __ballot(ok);
+    const bool none = i < cnt && b == -INFINITY;
+    const bool ok = none || (i < cnt && fabs(hi) <= 1992294.0);
+    const unsigned long long all = __ballot(ok), all_none = __ballot(none);
     const bool full = (uint32_t)(threadIdx.x & 32 ? all >> 32 : all) == 0xffffffffu;
+    const uint32_t set = (uint32_t)(threadIdx.x & 32 ? all_none >> 32 : all_none);
     if (i >= cnt) return;
     int *rec = s.brec + (i >> 5) * 128 + (i & 31);
-    const double r = full ? (B - hi) * 65536.0 : 0.0;
+    const bool in = full && !none;
+    const double r = in ? (B - hi) * 65536.0 : 0.0;
     const bool fine = gate.full();
     const double lo = fine ? floor(r) : rint(r);
-    rec[0] = full ? (int)hi : 0;
+    rec[0] = in ? (int)hi : 0;
     rec[32] = (int)lo;
     rec[64] = fine ? (int)floor((r - lo) * 65536.0) : 0;
-    rec[96] = full ? 0 : 1;
+    rec[96] = i & 1 ? (int)set : !full ? 1 : set ? 2 : 0;   // (the set is read where the tile is full)
 }
 
 // Rescaling of a split's sums to the common maximum.  Every streaming kernel keeps integer-valued

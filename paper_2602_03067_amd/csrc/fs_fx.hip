@@ -18,9 +18,11 @@
 // subtraction, so cancellation happens in exact integer arithmetic and the vector ALU only converts
 // what is left:  score - m = u3 H + (u5 L + rho),  rho = what m loses on the grid u3.
 //
-// A tile of 32 streamed points whose biases do not fit that grid (padding, zero weights, potentials
-// far away) is flagged in its bias record and takes a float64 epilogue with the float64 biases; so does
-// a row whose running max is beyond the integer range.
+// A tile of 32 streamed points whose biases do not fit that grid (padding, potentials far away) is flagged in its bias
+// record and takes a float64 epilogue with the float64 biases; so does a row whose running max is beyond the integer
+// range.  Points without weight are a bit mask of their tile, which costs it 32 vector instructions (in applications to more
+// than four columns they take the float64 epilogue as well).  With 5 % of them most tiles hold one: ten iterations at
+// n = m = 4000, d = 32 take 428 us with the mask, 890 with the float64 epilogue, 610 on the fp64 kernels.
 //
 // Mapping (32x32x32): A = streamed points (lane l: point l % 32, bytes 16 (l / 32) ..), B = resident
 // rows, D: lane l, register r holds D[i = 8 (r / 4) + 4 (l / 32) + r % 4][j = l % 32]: the sixteen
@@ -231,7 +233,7 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
     // ---- scores of a tile: the digit products ------------------------------------------------------------------
     struct Tile {
         i16v H, P, Q;
-        bool flagged;
+        int kind;   // of the tile: 0 whole, 1 flagged, 2 with points without weight
     };
 #define FX_MM(ACC, I, J) T.ACC = __builtin_amdgcn_mfma_i32_32x32x32_i8(av[S::kHold ? ks : 0][I], b[ks][J], T.ACC, 0, 0, 0)
     // (beyond two k-steps the digits of the streamed points are read from LDS once per phase instead of held)
@@ -261,7 +263,7 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
                 T.P[4 * g4 + q] = v2[q];
             }
         }
-        T.flagged = __builtin_amdgcn_readfirstlane(rec[96]) != 0;
+        T.kind = __builtin_amdgcn_readfirstlane(rec[96]);
         if constexpr (FULL) {
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
@@ -300,18 +302,32 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
 #undef FX_MM
 
     // ---- before the exponentials of tile g: the slow path of a tile, and the lift of the max ------------------
-    float u3v = u3, u5v = u5;   // score - m = u3v H + u5v L of the current tile
+    // The points without weight as this lane's registers see them: register r is bit 8 (r / 4) + r % 4.  (Opaque to the
+    // compiler, which would keep sixteen masks in registers over the whole pass.)
+    auto none_of_lane = [&](int g) __attribute__((always_inline)) {
+        unsigned none = reinterpret_cast<const unsigned *>(ring + (g % NS) * S::kStage + KS * 4096)[97] >> (4 * lh);
+        asm volatile("" : "+v"(none));
+        return none;
+    };
+    // their scores: 2^31 units below, 2^8 base-2 units or more (see FxGate)
+    auto mask_none = [&](int g, Tile &T) __attribute__((always_inline)) {
+        const unsigned none = none_of_lane(g);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) T.H[r] = none >> (8 * (r >> 2) + (r & 3)) & 1 ? INT32_MIN : T.H[r];
+    };
     auto far_tile = [&](int g, Tile &T) __attribute__((always_inline)) {
         // float64 scores (the record of a flagged tile holds no bias); what they leave above the max is handed on in the
         // same two-integer form, units 2^-16 and 2^-32
         const double *bd = a.bias + ((int64_t)(t_begin + g)) * 32 + 4 * lh;
         const unsigned back = 0u - (unsigned)nhm;
+        // (the record's biases are in where the tile is not flagged, but for points without weight)
+        const unsigned add = T.kind == 1 ? 0xffffffffu : T.kind == 2 ? none_of_lane(g) : 0u;
         double u3x = u3d;
         auto score = [&](int r) __attribute__((always_inline)) {
             const int Ha = (int)((unsigned)T.H[r] + back);
             const int L = (int)(((unsigned)T.Q[r] << 8) + (unsigned)T.P[r]);
             const double v = fma((double)L, u5d, (double)Ha * u3x);
-            return T.flagged ? v + bd[8 * (r >> 2) + (r & 3)] : v;
+            return add >> (8 * (r >> 2) + (r & 3)) & 1 ? v + bd[8 * (r >> 2) + (r & 3)] : v;
         };
         float mx = kNegInit;
         double seen = s;
@@ -349,8 +365,6 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
             nan = nan || other != 0;
         }
         if (nan) scale_sums(NAN);
-        u3v = 1.52587890625e-05f;
-        u5v = 2.3283064365386963e-10f;
         if constexpr (MODE == 1) {
             // rows beyond the matrix: zero values (every wave writes the same)
             const int left = (int)min((int64_t)32, a.n_str - (int64_t)(t_begin + g) * 32);
@@ -362,13 +376,9 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
     // m moves to the largest score where one exceeds it by more than `lazy`, 4 base-2 units (a float argument of 4 is
     // rounded by 2^-23); in MODE 2 both lane halves move together, since the second MFMA sums over them.  The factor of the old sums is a
     // rounded power: what it is off by counts with the weight 2^(old m - new m) of those sums, at most 3e-8 of the new one.
-    auto settle = [&](int g, Tile &T) __attribute__((always_inline)) {
-        u3v = u3;
-        u5v = u5;
-        if (T.flagged || __any(far)) {
-            far_tile(g, T);
-            return;
-        }
+    // (masked: a tile with points without weight)
+    auto settle = [&](int g, Tile &T, auto masked) __attribute__((always_inline)) {
+        if constexpr (decltype(masked)::value) mask_none(g, T);
         int hx = T.H[0];
 #pragma unroll
         for (int r = 1; r < 16; ++r) hx = max(hx, T.H[r]);
@@ -378,15 +388,16 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
                 hx = max(hx, __shfl_xor(hx, 32));
                 seen = fmax(s, __shfl_xor(s, 32));
             }
-            const int dh = seen > 0.0 ? max(hx, 0) : hx;
+            const int dh = seen > 0.0 ? max(hx, 0) : hx == INT32_MIN ? 0 : hx;
             scale_sums(fast_exp2(fminf((float)-dh * u3, 0.0f)));   // (1 where nothing was seen)
             nhm -= dh;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) T.H[r] -= dh;
+            for (int r = 0; r < 16; ++r) T.H[r] = (int)((unsigned)T.H[r] - (unsigned)dh);
+            if constexpr (decltype(masked)::value) mask_none(g, T);   // (the subtraction has wrapped)
         }
     };
-    // ---- exponentials of tile g, their sum and what they are applied to -------------------------------------
-    auto finish = [&](int g, const unsigned char *sb, const Tile &T) __attribute__((always_inline)) {
+    // ---- exponentials of tile g (score - m = u3v H + u5v L), their sum and what they are applied to -----------
+    auto finish = [&](int g, const unsigned char *sb, const Tile &T, const float u3v, const float u5v) __attribute__((always_inline)) {
         const unsigned char *vals = sb + KS * 4096 + kRecBytes;
         float e[16];
         float s0 = 0.0f, s1 = 0.0f;
@@ -538,8 +549,27 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
         const unsigned char *sb = ring + (g % NS) * S::kStage;
         Tile T;
         contract(sb, T);
-        settle(g, T);
-        finish(g, sb, T);
+        float u3v = u3, u5v = u5;
+        // (Whole tiles, and those with points without weight, have code copies of their own: where the others' scores join
+        // theirs, the compiler moves all of them from one set of registers to another in every tile, 3 % of a half-step.  In
+        // MODE 2 the copies would spill, and points without weight take the float64 epilogue.)
+        const bool near = !__any(far);
+        if (__builtin_expect(T.kind == 0 && near, 1)) {
+            settle(g, T, std::bool_constant<false>{});
+            if constexpr (MODE != 2) {
+                finish(g, sb, T, u3, u5);
+                continue;
+            }
+        } else if (MODE != 2 && T.kind == 2 && near) {
+            settle(g, T, std::bool_constant<true>{});
+            finish(g, sb, T, u3, u5);
+            continue;
+        } else {
+            far_tile(g, T);
+            u3v = 1.52587890625e-05f;
+            u5v = 2.3283064365386963e-10f;
+        }
+        finish(g, sb, T, u3v, u5v);
     }
 
     // merge the two lane halves of every resident row

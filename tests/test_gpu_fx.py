@@ -170,7 +170,7 @@ def test_hadamard_weights(ctx, n, m, d):
 # Streams of many tiles through one workgroup: what the small shapes above, where every workgroup has one tile, never reach
 # (slots of the LDS ring used again, the max lifted with sums in hand, tiles with and without the float64 epilogue in turn,
 # the alternating sign of the second product).
-PROFILES = ["flat", "rise", "steep", "fall", "mixed"]
+PROFILES = ["flat", "rise", "steep", "fall", "mixed", "none"]
 
 
 def _stream(rng, m, eps, profile):
@@ -190,6 +190,13 @@ def _stream(rng, m, eps, profile):
         g[5 * 32 + 9] += 1.0e5                     # far above, in the middle
         g[9 * 32:9 * 32 + 3] -= 1.0e5              # far below
         g[m - 1] += 1.0e5 + 3.0                    # the last, ragged tile
+        dead[10 * 32 + 5] = True                   # in a tile of its own kind after those far away
+    elif profile == "none":      # nothing seen for two tiles, then in one half of the lanes only, then rising
+        dead[:2 * 32] = True
+        dead[[2 * 32 + i for i in range(32) if not i & 4]] = True
+        dead[7 * 32 + 1::64] = True
+        g += 8.0 * t
+        g[4 * 32 + 6] = -np.inf
     return (g * eps).astype(np.float32), dead
 
 
