@@ -103,13 +103,24 @@ struct FxArgs {
 // kept; those dropped are below 2^-25 of a product, less than one rounding of an fp32 accumulation.
 // HAD (with MODE 2): Hadamard-weighted application (Alg. 5), every exponential times <row of A, streamed point>, which is
 // a second contraction of the same streamed digits with those of A (a scale per row; thirteen products).
+constexpr int fx_stage_bytes(int ks, int mode, int nc)
+{
+    return ks * 4096 + kRecBytes + (mode == 0 ? 0 : mode == 1 ? (nc + 1) / 2 * 256 : nc * 6 * 1024);
+}
+constexpr int fx_stages(int stage_bytes) { return stage_bytes <= 13 * 1024 ? 4 : 3; }
+// Workgroups per CU: two where two rings fit the 160 KB of LDS, which the widest applications do not (four column blocks
+// at any d, three at d > 64, two at d > 96).  HAD: one, the second set of resident digits takes the registers.
+constexpr int fx_wg_per_cu(int ks, int mode, int nc, bool had)
+{
+    const int stage = fx_stage_bytes(ks, mode, nc);
+    return had || 2 * fx_stages(stage) * stage > 160 * 1024 ? 1 : 2;
+}
 template <int KS, int MODE, int NC, bool HAD = false> struct FxShape {
-    static constexpr int kValBytes = MODE == 0 ? 0 : MODE == 1 ? (NC + 1) / 2 * 256 : NC * 6 * 1024;
-    static constexpr int kStage = KS * 4096 + kRecBytes + kValBytes;
-    static constexpr int kStages = kStage <= 13 * 1024 ? 4 : 3;
+    static constexpr int kStage = fx_stage_bytes(KS, MODE, NC);
+    static constexpr int kStages = fx_stages(kStage);
     // vector-memory instructions of a wave per stage
     static constexpr int kLoads = KS + 1 + (MODE == 0 ? 0 : MODE == 1 ? 1 : (NC * 6 + 3) / 4);
-    static constexpr int kWgPerCu = HAD ? 1 : 2;   // (HAD: the second set of resident digits takes the registers)
+    static constexpr int kWgPerCu = fx_wg_per_cu(KS, MODE, NC, HAD);
     static constexpr int kPC = MODE == 2 ? 32 * NC : NC;
     static constexpr bool kHold = KS <= 2;
 };
@@ -725,9 +736,9 @@ __global__ __launch_bounds__(256) void k_had_digits(const float *A, int64_t lda,
 }
 
 // Launch shape: row blocks x splits of the streamed side, minimising a makespan model in units of one tile of one
-// workgroup on a full CU: workgroups are dealt to the CUs evenly and run `occ` at a time; an incomplete batch leaves
-// the matrix pipe partly idle (one workgroup of several is charged 2, two of three 2.35).  `startup`: filling the
-// ring, loading the resident digits, the first lift of the max and the merge, in tiles.
+// workgroup on a full CU: workgroups are dealt to the CUs evenly and run `occ` at a time (one or two); one left over where
+// two would run leaves the matrix pipe partly idle and is charged 2.  `startup`: filling the ring, loading the resident digits,
+// the first lift of the max and the merge, in tiles.
 PassShape fx_shape(const Ctx *c, int64_t n_res, int64_t n_str, int occ)
 {
     PassShape s;
@@ -751,7 +762,7 @@ PassShape fx_shape(const Ctx *c, int64_t n_res, int64_t n_str, int occ)
         if ((int)ceil_div(n_tiles, tps) != sp) continue;
         const int64_t wg = ceil_div((int64_t)s.row_blocks * sp, (int64_t)c->num_cu);
         const int rem = (int)(wg % occ);
-        const double units = (double)(wg - rem) + (rem == 0 ? 0.0 : rem == 1 ? 2.0 : 2.35);
+        const double units = (double)(wg - rem) + (rem ? 2.0 : 0.0);
         const double cost = units * ((double)tps + startup) + 0.05 * sp;
         if (best == 0.0 || cost < best * 0.995) {
             best = cost;
@@ -762,8 +773,6 @@ PassShape fx_shape(const Ctx *c, int64_t n_res, int64_t n_str, int occ)
     s.cols_per_split = (int64_t)best_tps * 32;
     return s;
 }
-
-constexpr int kOcc = 2, kOccHad = 1;   // workgroups per CU (FxShape::kWgPerCu)
 
 fs_status pass_args(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, int occ, void *partial, FxArgs *out,
                     PassShape *shape)
@@ -848,7 +857,7 @@ fs_status fx_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, do
 {
     FxArgs a;
     PassShape s;
-    fs_status st = pass_args(c, P, res, str, eps, kOcc, P->partial, &a, &s);
+    fs_status st = pass_args(c, P, res, str, eps, fx_wg_per_cu(P->fx_ks, 0, 1, false), P->partial, &a, &s);
     if (st != FS_OK) return st;
     const dim3 grid((unsigned)s.row_blocks, (unsigned)s.splits);
     switch (P->fx_ks) {
@@ -866,9 +875,10 @@ fs_status fx_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, vo
 {
     FxArgs ax, ay;
     PassShape sx, sy;
+    const int occ = fx_wg_per_cu(P->fx_ks, 0, 1, false);
     fs_status st;
-    if ((st = pass_args(c, P, &P->X, &P->Y, eps, kOcc, partial_x, &ax, &sx)) != FS_OK) return st;
-    if ((st = pass_args(c, P, &P->Y, &P->X, eps, kOcc, partial_y, &ay, &sy)) != FS_OK) return st;
+    if ((st = pass_args(c, P, &P->X, &P->Y, eps, occ, partial_x, &ax, &sx)) != FS_OK) return st;
+    if ((st = pass_args(c, P, &P->Y, &P->X, eps, occ, partial_y, &ay, &sy)) != FS_OK) return st;
     const dim3 grid((unsigned)(sx.row_blocks + sy.row_blocks), (unsigned)(sx.splits > sy.splits ? sx.splits : sy.splits));
     switch (P->fx_ks) {
     case 1: hipLaunchKernelGGL(k_fx_pair<1>, grid, dim3(256), 0, c->stream, ax, ay, sx.row_blocks, sx.splits, sy.splits); break;
@@ -889,10 +899,11 @@ size_t fx_apply_ws(const Ctx *c, int64_t n_res, int64_t n_str, int64_t d, int64_
     if (ks == 0) return 0;
     size_t most = 0;
     for (int had = 0; had < 2; ++had)
-        for (int64_t left : {p, (int64_t)4}) {   // the widest pass, and a narrow last one (at most 4 columns)
+        for (int64_t left : {p, p % (had ? 64 : 128)}) {   // the first pass and the last one (those between are as the first)
+            if (left == 0) continue;
             int mode, nc;
-            fx_columns(left < p ? left : p, had != 0, &mode, &nc);
-            const PassShape s = fx_shape(c, n_res, n_str, had ? kOccHad : kOcc);
+            fx_columns(left, had != 0, &mode, &nc);
+            const PassShape s = fx_shape(c, n_res, n_str, fx_wg_per_cu(ks, mode, nc, had != 0));
             const ApplyBuf b(s.splits, round_up(n_res, 1024), ceil_div(n_str, 32), ks, mode, nc, had != 0);
             if (b.total > most) most = b.total;
         }
@@ -908,7 +919,7 @@ fs_status fx_apply_pass(Ctx *c, const Prepared *P, const Side *res, const Side *
     fx_columns(p - p0, hadA != nullptr, &mode, &nc);
     FxArgs a;
     PassShape s;
-    fs_status st = pass_args(c, P, res, str, eps, hadA ? kOccHad : kOcc, P->partial, &a, &s);
+    fs_status st = pass_args(c, P, res, str, eps, fx_wg_per_cu(P->fx_ks, mode, nc, hadA != nullptr), P->partial, &a, &s);
     if (st != FS_OK) return st;
     const ApplyBuf buf(s.splits, res->cnt_pad, a.n_tiles, P->fx_ks, mode, nc, hadA != nullptr);
     if (!P->extra || buf.total > P->extra_bytes) return fail(c, FS_ERR_DEVICE, "internal: fixed-point application exceeds its buffer");

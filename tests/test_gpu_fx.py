@@ -439,3 +439,22 @@ def test_half_steps_beyond_the_gate_with_many_row_blocks(ctx, oracle):
     fo, go = oracle.solve_symmetric(x, y, a, b, eps, 3)
     for got, want in ((fs, fo), (gs, go)):
         assert np.all(np.abs(host(got) - want) <= 3e-6 * eps + 2.0 ** -24 * np.abs(want) * 1.01)
+
+
+@pytest.mark.parametrize("n,m,d", [(300, 4000, 24), (2000, 700, 100)])
+def test_workspace_covers_every_pass_of_a_wide_application(ctx, n, m, d):
+    """The passes of one call differ in width, workgroups per CU and so in splits; the buffer is sized from the first and
+    the last.  Column by column the same as one column at a time (to rounding: those run on the vector ALU)."""
+    eps = float(np.float32(0.5))
+    rng, x, y, a, b = _problem(31, n, m, d)
+    prob = make_problem(x, y, a, b)
+    f, g = torch.zeros(n, device="cuda:0"), torch.zeros(m, device="cuda:0")
+    f = ctx.fs_update_f(prob, eps, g)
+    V, A = rng.standard_normal((m, 333)).astype(np.float32), dev(rng.standard_normal((n, d)).astype(np.float32))
+    one = host(ctx.fs_apply_plan(prob, eps, f, g, dev(V[:, :3].copy())))
+    for p in (5, 33, 64, 65, 96, 97, 127, 128, 129, 132, 133, 160, 192, 193, 200, 256, 257, 333):
+        say("fx wide application n=%d m=%d d=%d p=%d" % (n, m, d, p))
+        out = host(ctx.fs_apply_plan(prob, eps, f, g, dev(V[:, :p].copy())))
+        assert np.abs(out[:, :3] - one).max() <= 1e-6 * np.abs(one).max()
+        assert np.isfinite(out).all()
+        assert np.isfinite(host(ctx.fs_apply_plan_hadamard(prob, eps, f, g, A, dev(V[:, :p].copy())))).all()
