@@ -47,6 +47,21 @@ def algorithmic_slots_per_pair(exp_cost: float = 4.0) -> float:
     return exp_cost + 1
 
 
+def digit_products(w) -> int:
+    """int8 products per coordinate of a half-step at the workload's last eps: ten or thirteen where the library runs
+    fixed-point scores (16 < d <= 128, enough work, the scale of the points inside the window), 0 where it does not."""
+    import math
+
+    import numpy as np
+
+    if not (16 < w.d <= 128) or float(w.n) * w.m * w.d < 4.0e8:
+        return 0
+    lo, hi = min(float(w.x.min()), float(w.y.min())), max(float(w.x.max()), float(w.y.max()))
+    r2 = 2.0 ** math.frexp(0.5 * (hi - lo) * 128 / 126.99)[1] if hi > lo else 1.0
+    size = 2.0 / math.log(2.0) / float(np.float32(w.eps_end)) * r2 * r2   # of a unit-scale product in a score
+    return 0 if not 0.5 <= size <= 2048.0 else 13 if size > 32.0 else 10
+
+
 def run_workload(name, steps, warmup, schedule="alternating", n_override=None, cpu_baseline=False,
                  calibrate_copy=False):
     """Time `steps` steps of the hot path on workload `name`; returns the fields of the JSON line."""
@@ -169,9 +184,9 @@ def run_workload(name, steps, warmup, schedule="alternating", n_override=None, c
         roof = {"bound": "mfma", "achieved": flops / (avg_ms * 1e-3) / 1e12, "peak": PEAKS["bf16"] / 1e12,
                 "unit": "TFLOP/s"}
         dtype = "bf16"
-    elif 16 < w.d <= 128 and float(w.n) * w.m * w.d >= 4.0e8:
-        # fixed-point scores: thirteen digit products per coordinate (ten where cscale r2^2 <= 128) on the int8 matrix cores
-        flops = 2.0 * ((w.d + 31) // 32 * 32) * 13 * pairs
+    elif digit_products(w):
+        # fixed-point scores on the int8 matrix cores
+        flops = 2.0 * ((w.d + 31) // 32 * 32) * digit_products(w) * pairs
         roof = {"bound": "mfma", "achieved": flops / (avg_ms * 1e-3) / 1e12, "peak": PEAKS["i8"] / 1e12,
                 "unit": "TOP/s"}
         # the contraction itself as float operations against the fp32 vector peak (157.3 TFLOP/s)

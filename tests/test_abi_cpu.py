@@ -4,6 +4,7 @@ import ctypes
 import os
 import re
 
+import numpy as np
 import pytest
 
 from paper_2602_03067_amd import binding
@@ -306,3 +307,15 @@ def test_bench_refuses_more_than_one_gpu():
     env = dict(os.environ, WORLD_SIZE="4")
     r = subprocess.run([sys.executable, os.path.join(root, "bench.py")], capture_output=True, text=True, timeout=120, env=env)
     assert r.returncode == 2 and "ONE GPU" in r.stderr
+
+
+@pytest.mark.parametrize("scale,eps,d,n,products", [(1.0, 0.1, 64, 3000, 10), (1.0, 0.05, 64, 3000, 13), (1.0, 0.001, 64, 3000, 0),
+                                                    (1.0, 8.0, 64, 3000, 0), (1.0, 0.1, 64, 2000, 0), (1.0, 0.1, 200, 3000, 0),
+                                                    (8.0, 0.1, 64, 3000, 13)])
+def test_bench_prices_the_products_that_run(scale, eps, d, n, products):
+    """Unit-cube points have the scale 1 after the shift to the middle of their range: 2.885 / eps against 0.5, 32 and 2048."""
+    from types import SimpleNamespace
+
+    import bench
+    x = np.linspace(0.0, scale * 0.999, n * d).reshape(n, d).astype(np.float32)
+    assert bench.digit_products(SimpleNamespace(x=x, y=x, n=n, m=n, d=d, eps_end=eps)) == products
