@@ -8,7 +8,7 @@
  * is evaluated as a streaming row-wise LogSumExp of biased dot-product scores
  * (Prop. 1); no n x m matrix is stored as a whole (bf16-mode applications to many
  * columns keep a slab of plan entries in the workspace: slab and its products at
- * most 256 MB, 1 GiB with the copies of the values).
+ * most 320 MB, 1 GiB with a copy of the values).
  *
  * Conventions common to all entry points
  *  - Every pointer inside fs_problem and every pointer argument is a DEVICE
@@ -274,8 +274,8 @@ fs_status fs_divergence(fs_ctx *ctx, const fs_problem *prob, float eps, int32_t 
  * one pass for p <= 8 and ceil(p / 15) passes beyond at d <= 16,
  * ceil(p / 64) passes at d > 16 (when p > 64: ceil(p / 128) with FS_COMPUTE_FP32, ceil(p / 96) with
  * FS_COMPUTE_BF16_MFMA).  Where P's entries and the product are cheaper apart, FS_COMPUTE_BF16_MFMA with p > 96
- * computes them once, slab by slab (bfloat16 entries and their products: at most 256 MB), and multiplies all columns from
- * there.  With its two bfloat16 copies of V that takes up to 1 GiB of workspace; where it would take more, or the memory is
+ * computes them once, slab by slab (bfloat16 entries and their products: at most 320 MB), and multiplies all columns from
+ * there.  With a bfloat16 copy of V that takes up to 1 GiB of workspace; where it would take more, or the memory is
  * not there, the passes of above run.
  * Accuracy at d <= 16, FS_COMPUTE_FP32: every plan entry enters the products to 2^-17 relative
  * (1e-6 to 3e-6 of the result's norm in practice), values to 24 bits (p <= 8) or 2^-17 (p > 8).

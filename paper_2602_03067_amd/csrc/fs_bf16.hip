@@ -121,7 +121,9 @@ struct DirectArgs {
     float *out;
     int64_t ldo;
     float *mass_out;
-    int64_t img_stride;          // bytes of the value images of a column block
+    const float *V;              // [n_str][ldv]: the value images are made in LDS
+    int64_t ldv, n_str;
+    int col_blocks;
 };
 
 // Workgroup shapes (WJ = waves along the resident side, each owning 128 resident rows; four waves
@@ -309,7 +311,15 @@ __device__ __forceinline__ void lse_bf16_body(const BfArgs &a, const int block, 
     };
     int vstamp = 0;   // pg when this wave issued its pieces of the current tile's value image
     auto issue_vimg = [&](int t) {
-        if constexpr (APPLY) {
+        if constexpr (EPI == Epi::Direct) {
+            for (int e = tid; e < BI * PC; e += 256 * WJ) {
+                const int i = e / PC, cc = e - i * PC;
+                const int64_t row = (int64_t)t * BI + i;
+                const float v = (row < direct->n_str && p0 + cc < direct->p) ? direct->V[row * direct->ldv + p0 + cc] : 0.0f;
+                *reinterpret_cast<__bf16 *>(vimg + cc * kVRow + 2 * i) = (__bf16)v;
+            }
+            vstamp = pg;
+        } else if constexpr (APPLY) {
             const unsigned char *src = reinterpret_cast<const unsigned char *>(a.vimg) + (int64_t)t * VIMG;
             // consecutive pieces per wave, in runs of up to four behind one LDS base each
             constexpr int VPW = (NVP + NW - 1) / NW;
@@ -714,23 +724,26 @@ __global__ __launch_bounds__(256 * WJ, WJ == 2 ? 1 : 2) void k_lse_bf16_pair(BfA
     lse_bf16_body<WJ, NS, JTW, 0>(second ? a1 : a0, (int)blockIdx.x - (second ? blocks0 : 0));
 }
 
-// Rows of the plan whose entries left the exponent range of a stored slab (see k_plan_finalize): workgroup (row tile, column
-// block), all of which leave at once where the row tile has no such row.
+// Rows of the plan whose entries left the exponent range of a stored slab (see k_plan_finalize): workgroup (row tile, first of
+// every gridDim.y column blocks), all of which leave at once where the row tile has no such row.  (Mostly that is all of them,
+// one at a time per CU with this much LDS: a workgroup for each of 313 x 9 pairs took 12 us to leave.)
 template <int PC>
 __global__ __launch_bounds__(512, 1) void k_apply_direct(BfArgs a, DirectArgs o)
 {
     const int jtile = blockIdx.x;
     if (!o.flags[1 + jtile]) return;
-    a.vimg += blockIdx.y * o.img_stride;
     const int per = (a.n_jtiles + 7) >> 3;   // (the inverse of the body's dealing, for one split)
-    lse_bf16_body<2, 4, 2, PC, false, Epi::Direct>(a, (jtile % per) * 8 + jtile / per, &o, (int)blockIdx.y * PC);
+    for (int cb = blockIdx.y; cb < o.col_blocks; cb += gridDim.y) {
+        lse_bf16_body<2, 4, 2, PC, false, Epi::Direct>(a, (jtile % per) * 8 + jtile / per, &o, cb * PC);
+        __syncthreads();   // the rows are written from LDS
+    }
 }
 
 // Value image of every streamed tile for the plan application: bf16 Vt[c][i], c < pc value columns
 // starting at p0, i < 256 points of tile t, rows of kVRow bytes, one image per img_bytes; zero
 // outside the matrix.  (The pad bytes are copied to LDS with the rest and never read.)
-__device__ __forceinline__ void vimg_tile(const float *V, int64_t ldv, int64_t n_str, int p0, int p, int pc, int img_bytes,
-                                          unsigned char *img)
+__global__ __launch_bounds__(BI) void k_vimg_bf16(const float *V, int64_t ldv, int64_t n_str, int p0, int p, int pc,
+                                                   int img_bytes, unsigned char *img)
 {
     const int i = threadIdx.x;
     const int64_t row = (int64_t)blockIdx.x * BI + i;
@@ -739,18 +752,6 @@ __device__ __forceinline__ void vimg_tile(const float *V, int64_t ldv, int64_t n
         const float v = (row < n_str && p0 + cc < p) ? V[row * ldv + p0 + cc] : 0.0f;
         *reinterpret_cast<__bf16 *>(dst + cc * kVRow + 2 * i) = (__bf16)v;
     }
-}
-__global__ __launch_bounds__(BI) void k_vimg_bf16(const float *V, int64_t ldv, int64_t n_str, int p0, int p, int pc,
-                                                   int img_bytes, unsigned char *img)
-{
-    vimg_tile(V, ldv, n_str, p0, p, pc, img_bytes, img);
-}
-// ... of all column blocks (blockIdx.y), for k_apply_direct
-__global__ __launch_bounds__(BI) void k_vimg_direct(const float *V, int64_t ldv, int64_t n_str, int p, int pc, int img_bytes,
-                                                     int64_t img_stride, unsigned char *img, const int *flags)
-{
-    if (!flags[0]) return;
-    vimg_tile(V, ldv, n_str, (int)blockIdx.y * pc, p, pc, img_bytes, img + blockIdx.y * img_stride);
 }
 
 // Transposed values for the second product: bf16 V^T, tiled like the point copies with the value columns as rows and the
@@ -865,8 +866,8 @@ constexpr int kApplyBJ = 128;   // resident rows per workgroup of the applicatio
 // the exponentials take 212 us (0.93 PFLOP/s with the store of 247 MB), 768 columns of the product 161 us (1.18 PFLOP/s) and
 // the last 16 columns 54 us, which is the time to read the slab once more.
 constexpr size_t kSlabBytes = size_t(256) << 20;
-// The whole workspace of this route (slab, accumulators, transposed values, value images of the rows done again): beyond it
-// the fused kernel runs, which needs a fraction of it.
+// The whole workspace of this route (slab, accumulators, transposed values): beyond it the fused kernel runs, which needs a
+// fraction of it.
 constexpr size_t kSlabTotalBytes = size_t(1) << 30;
 
 struct SlabPlan {
@@ -876,7 +877,6 @@ struct SlabPlan {
     int rest = 0;            // columns beyond them, taken by a 128-column tile (0: none)
     int ks_wide = 0, ks_rest = 0;   // splits of the product's contraction
     int col_blocks = 0;             // column blocks of k_apply_direct
-    size_t img_stride = 0;          // bytes of the value images of one of them (they take the slab's place)
     size_t eslab = 0, vt = 0, rowmax = 0, flags = 0, opart = 0, total = 0;
 };
 
@@ -913,10 +913,8 @@ SlabPlan slab_plan(const Ctx *c, int64_t n_res, int64_t n_str, int64_t p)
     s.ks_wide = s.wide_tiles ? product_splits(c, rt * s.wide_tiles, s.e_chunks) : 0;
     s.ks_rest = s.rest ? product_splits(c, rt, s.e_chunks) : 0;
     s.col_blocks = (int)ceil_div(p, kApplyPCWide);
-    s.img_stride = (size_t)ceil_div(n_str, BI) * kVImgBytes(kApplyPCWide);
-    const size_t e_bytes = (size_t)s.rows * s.e_chunks * KC * 2, img_bytes = s.col_blocks * s.img_stride;
     Arena A;
-    s.eslab = A.take(e_bytes > img_bytes ? e_bytes : img_bytes);
+    s.eslab = A.take((size_t)s.rows * s.e_chunks * KC * 2);
     s.vt = A.take((size_t)round_up(p, 256) * s.e_chunks * KC * 2);
     s.rowmax = A.take((size_t)round_up(n_res, 1024) * 4);
     s.flags = A.take((size_t)(1 + ceil_div(n_res, kApplyBJ)) * 4);
@@ -1092,13 +1090,9 @@ static fs_status slab_apply(Ctx *c, const Prepared *P, const Side *res, const Si
         }
         FS_HIP(c, hipGetLastError());
     }
-    // rows that the stored slab is not good for (two launches that leave at once where there are none); the slab's memory is
-    // free by now and takes the value images
+    // rows that the stored slab is not good for (a launch that leaves at once where there are none)
     {
         constexpr int pc = kApplyPCWide;
-        unsigned char *img = reinterpret_cast<unsigned char *>(x + sp.eslab);
-        hipLaunchKernelGGL(k_vimg_direct, dim3((unsigned)n_itiles, (unsigned)sp.col_blocks), dim3(BI), 0, c->stream, V, ldv, str->cnt, (int)p,
-                           pc, kVImgBytes(pc), (int64_t)sp.img_stride, img, flags);
         BfArgs a{};
         a.res = res->pts_b;
         a.str = str->pts_b;
@@ -1110,11 +1104,13 @@ static fs_status slab_apply(Ctx *c, const Prepared *P, const Side *res, const Si
         a.splits = 1;
         a.tiles_per_split = n_itiles;
         a.partial_stride = res->cnt_pad;
-        a.vimg = img;
         const DirectArgs o{flags, res->cnt, 1.0 / eps, res->w, res->log_uniform, res->pot, res->norm, (int)p, out, ldo, mass_out,
-                           (int64_t)sp.img_stride};
+                           V, ldv, str->cnt, sp.col_blocks};
+        const int per_tile = n_jtiles >= 512 ? 1 : 512 / n_jtiles;
+
         if ((int64_t)n_jtiles * kApplyBJ > res->cnt_pad) return fail(c, FS_ERR_DEVICE, "internal: bf16 apply launch shape exceeds the padded buffers");
-        hipLaunchKernelGGL((k_apply_direct<pc>), dim3((unsigned)n_jtiles, (unsigned)sp.col_blocks), dim3(512), 0, c->stream, a, o);
+        hipLaunchKernelGGL((k_apply_direct<pc>), dim3((unsigned)n_jtiles, (unsigned)(sp.col_blocks < per_tile ? sp.col_blocks : per_tile)),
+                           dim3(512), 0, c->stream, a, o);
         FS_HIP(c, hipGetLastError());
     }
     return FS_OK;
