@@ -229,9 +229,11 @@ size_t layout_with(const Ctx *c, const fs_problem *p, Prepared *P, char *base, s
 
 size_t layout(const Ctx *c, const fs_problem *p, Prepared *P, char *base, size_t extra)
 {
-    // Below this much work a float64 pass takes under 20 us (n = m = 2800 at d = 64), which the second launch of a pass and
-    // the digits of the prologue would eat up: n = 3000, m = 2500, d = 64 measured 28 us a half-step in float64, 17 in
-    // fixed point, n = m = 1000 8 and 13.
+    // Below this much work a float64 pass takes under 20 us (n = m = 2500 at d = 64), which the second launch of a pass and
+    // the digits of the prologue would eat up.  At the line, n = m = 2500, d = 64, whole calls in float64 / here (us): a half-step
+    // 36 / 31, five iterations 297 / 207, one column 54 / 36, 64 columns 60 / 55, 128 columns 74 / 68; n = m = 1000: a half-step 8 / 13.
+    // Points beyond the gate pay for it: half-step 38 / 45, ten iterations 586 / 637, one column 57 / 65 at n = m = 2600;
+    // ten iterations 4660 / 4703 at n = m = 10000.
     const bool worth = (double)p->n * (double)p->m * (double)p->d >= 4.0e8 || c->dbg_fx_any_size;
     const int ks = choose_path(p) == Path::F64 && worth ? fx_ksteps(p->d) : 0;
     // digit images are left out where only the problem without them fits the static scratch array

@@ -14,9 +14,9 @@
 //     H = 2^8 sum(1,1) + sum(i + j = 3)                      unit u3 = cscale r2^2 2^-22
 //     L = 2^8 sum(i + j = 4) + sum(i + j = 5) + 2^-8 sum(i + j = 6)     unit u5 = u3 2^-16
 // The streamed point's bias enters as the initial accumulators (three integers per point, units u2,
-// u4, u6: see store_fx_record) and the resident row's running max (an integer m) as an integer
+// u4, u6: see store_fx_record) and the resident row's running max m, a multiple of u3, as an integer
 // subtraction, so cancellation happens in exact integer arithmetic and the vector ALU only converts
-// what is left:  score - m = u3 H + (u5 L + rho),  rho = what m loses on the grid u3.
+// what is left:  score - m = u3 H + u5 L.
 //
 // A tile of 32 streamed points whose biases do not fit that grid (padding, potentials far away) is flagged in its bias
 // record and takes a float64 epilogue with the float64 biases; so does a row whose running max is beyond the integer
@@ -31,7 +31,7 @@
 // filled by linear direct loads and read without bank conflicts.
 //
 // A workgroup is four waves = 128 resident rows (their digits stay in registers) over a run of
-// streamed tiles that pass through an LDS ring; two workgroups per CU.
+// streamed tiles that pass through an LDS ring; two workgroups per CU, one where two rings do not fit (fx_wg_per_cu).
 //
 // Bound: matrix and vector instructions together, which do not hide behind each other with these operands.  A loop of
 // nothing but this MFMA takes 15.6 ns per instruction and SIMD with constant operands and 20 with random ones; with seven
@@ -40,9 +40,12 @@
 // 700 to 800 ns (counters: matrix pipe busy 46 %, vector ALU 48 %, clock 2.0 GHz).
 // Tried without gain: tile g + 1's MFMAs interleaved with tile g's vector work in one wave (216-226 us
 // against 211 at n = m = 16384, d = 64), three workgroups per CU, digits read from LDS twice instead of held.
-// Measured (half-step with its merge, us): n = m = 16384, d = 64: 577 fp64 -> 178 with ten products, 208 with
-// thirteen; n = m = 10000, d = 64: 232 -> 79; n = 9973, m = 12007, d = 128: 545 -> 152; n = m = 12000, d = 32: 192 -> 88.
-// Error of plan sums against 64 bits: 5e-8 to 1e-7, fp64 scores with fp32 sums 1e-7 to 7e-7.
+// Measured (half-step with its merge, us, fp64 and here; the other kernel's empty launch included): n = m = 10000, d = 64:
+// 232 -> 81 (ten products); n = m = 16384, d = 64: 577 -> 217 (thirteen); n = 9973, m = 12007, d = 128: 545 -> 156 (ten);
+// n = 9973, m = 12007, d = 20: 71 (ten).
+// Error of plan sums against 64 bits (n = 3001, m = 2800, d = 64 and 128; cube, normal, pixel and two-valued points,
+// everywhere between the gates): 3e-8 to 6.5e-8, 64 columns of both signs 7e-8 to 1.1e-7; fp64 scores with fp32 sums 3.4e-8 to
+// 4.3e-7 and 5e-8 to 5.6e-7.
 #include <type_traits>
 
 #include "fs_internal.h"

@@ -122,8 +122,9 @@ __host__ __device__ inline int fx_ksteps(int64_t d) { return d > kLowdMaxD && d 
 //
 // The upper line lies where the error of a score reaches the rounding of the exponential's float argument.  What counts there
 // is that a coordinate below 2^-7 r2 loses bits of its float; at d = 128 (rms over pairs, in base-2 units) normal points have
-// 2^-23.4 at v = 1846 and 2^-20.1 at v = 18466, unit-cube points 2^-26 at v = 288.  Plan sums at v = 1846 are off by
-// 5e-8 to 6e-8 of their size, as float64 scores leave 4e-8 to 5e-8; at v = 16000 it was 2.5e-7 to 7e-7.  Bounds for data whose
+// 2^-23.4 at v = 1846 and 2^-20.1 at v = 18466, unit-cube points 2^-26 at v = 288.  Plan sums of normal points at v = 1846 are
+// off by 5.3e-8 of their size at d = 64 and 6.5e-8 at d = 128, where float64 scores leave 5.0e-8 and 3.7e-8 and the rounding of the
+// output alone 3.4e-8; at v = 500 by 4.6e-8 where float64 scores leave 1.4e-7 to 2.2e-7; at v = 16000 it was 2.5e-7 to 7e-7.  Bounds for data whose
 // digits conspire: the products left out at most 2 d 2^14 2^-54 v (2^-21 at the line, d = 128), the coordinates' rounding
 // d 2^-31 v (one cloud within 2^-7 r2 of the origin and rounded one way, the other at the far end).
 // Below v = 1/2 weights of 2^-60 no longer fit the bias records (every tile with one would take the slow epilogue), and
