@@ -757,7 +757,7 @@ __global__ __launch_bounds__(BI) void k_vimg_bf16(const float *V, int64_t ldv, i
 // Transposed values for the second product: bf16 V^T, tiled like the point copies with the value columns as rows and the
 // streamed points as coordinates; zero outside the matrix.  A block: 64 columns x 32 points (one chunk); thread (column,
 // piece of eight points).
-__global__ __launch_bounds__(256) void k_vt_bf16(const float *V, int64_t ldv, int64_t n_str, int p, int chunks, unsigned char *img)
+__device__ __forceinline__ void transpose_values(const float *V, int64_t ldv, int64_t n_str, int p, int chunks, unsigned char *img)
 {
     const int c = blockIdx.y * 64 + (threadIdx.x & 63), piece = threadIdx.x >> 6;
     const int64_t ch = blockIdx.x;
@@ -782,18 +782,35 @@ __global__ __launch_bounds__(256) void k_vt_bf16(const float *V, int64_t ldv, in
 // float holds it exactly; a row beyond that (a potential that masks it, for one) has sums that say so, see k_plan_finalize.
 // Padding rows: no entry.  Also clears the flags of the rows to do again.
 constexpr double kPlanShift = 30.0, kPlanLimit = 16777216.0;
-__global__ void k_plan_rowmax(const double *pot, const double *norm, double inv_eps, int64_t cnt, int64_t cnt_pad, float *rowmax,
-                              int *flags, int n_flags)
+struct RowmaxArgs {
+    const double *pot, *norm;
+    double inv_eps;
+    int64_t cnt, cnt_pad;
+    float *rowmax;
+    int *flags, n_flags;
+};
+__device__ __forceinline__ void plan_rowmax(const RowmaxArgs &a, const int64_t i)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n_flags) flags[i] = 0;
-    if (i >= cnt_pad) return;
+    if (i < a.n_flags) a.flags[i] = 0;
+    if (i >= a.cnt_pad) return;
     double r = 3.0e38;
-    if (i < cnt) {
-        r = -rint((pot[i] - norm[i]) * inv_eps * kLog2e) - kPlanShift;
+    if (i < a.cnt) {
+        r = -rint((a.pot[i] - a.norm[i]) * a.inv_eps * kLog2e) - kPlanShift;
         r = r > kPlanLimit ? kPlanLimit : r < -kPlanLimit ? -kPlanLimit : r;   // (NaN stays)
     }
-    rowmax[i] = (float)r;
+    a.rowmax[i] = (float)r;
+}
+
+// both in one launch: rows of blocks from `vt_rows` make the stabilisers
+__global__ __launch_bounds__(256) void k_plan_prep(const float *V, int64_t ldv, int64_t n_str, int p, int chunks, unsigned char *img,
+                                                   int vt_rows, RowmaxArgs rm)
+{
+    if ((int)blockIdx.y < vt_rows) {
+        transpose_values(V, ldv, n_str, p, chunks, img);
+        return;
+    }
+    const int64_t block = (int64_t)(blockIdx.y - vt_rows) * gridDim.x + blockIdx.x, blocks = (int64_t)(gridDim.y - vt_rows) * gridDim.x;
+    for (int64_t i = block * 256 + threadIdx.x; i < rm.cnt_pad; i += blocks * 256) plan_rowmax(rm, i);
 }
 
 // out_i = w_i exp(fhat_i/eps) 2^rowmax_i (sum over the splits of the product), columns col0 .. col0 + cols; a block per row.
@@ -810,6 +827,9 @@ __global__ __launch_bounds__(256) void k_plan_finalize(const float *opart, int64
 {
     const int64_t i = row_off + (int64_t)blockIdx.x;
     if (i >= cnt) return;
+    double S = 0.0;   // (asked for before the products: its latency is that of a block)
+    if (flags && threadIdx.x < 64)
+        for (int k = threadIdx.x; k < plan_splits; k += 64) S += partial[(int64_t)k * stride + i].y;
     const double lw = w ? log((double)w[i]) : log_uniform;
     const double e0 = ((pot[i] - norm[i]) * inv_eps + lw) * kLog2e + (double)rowmax[i];
     const double fac = exp2(e0);
@@ -820,9 +840,8 @@ __global__ __launch_bounds__(256) void k_plan_finalize(const float *opart, int64
         out[i * ldo + col0 + c] = (float)(fac * acc);
     }
     if (flags && threadIdx.x < 64) {
-        double S = 0.0;
-        for (int k = threadIdx.x; k < plan_splits; k += 64) S += partial[(int64_t)k * stride + i].y;
-        for (int off = 32; off > 0; off >>= 1) S += __shfl_xor(S, off);
+        if (plan_splits > 1)
+            for (int off = 32; off > 0; off >>= 1) S += __shfl_xor(S, off);
         if (threadIdx.x == 0) {
             if (mass_out) mass_out[i] = (float)(fac * S);
             const bool kept = (S >= 0x1p-40 && S <= 0x1p60) || S != S || (S <= 0x1p60 && e0 < -400.0);
@@ -1028,10 +1047,13 @@ static fs_status slab_apply(Ctx *c, const Prepared *P, const Side *res, const Si
     unsigned char *vt = reinterpret_cast<unsigned char *>(x + sp.vt);
     int *flags = reinterpret_cast<int *>(x + sp.flags);
     const int n_jtiles = (int)ceil_div(res->cnt, kApplyBJ);
-    hipLaunchKernelGGL(k_vt_bf16, dim3((unsigned)sp.e_chunks, (unsigned)((sp.wide_tiles * 256 + (sp.rest ? 128 : 0)) / 64)), dim3(256), 0,
-                       c->stream, V, ldv, str->cnt, (int)p, sp.e_chunks, vt);
-    hipLaunchKernelGGL(k_plan_rowmax, dim3((unsigned)ceil_div(res->cnt_pad, 256)), dim3(256), 0, c->stream, res->pot, res->norm, 1.0 / eps,
-                       res->cnt, res->cnt_pad, rowmax, flags, 1 + n_jtiles);   // (fewer flags than padded rows)
+    // (fewer flags than padded rows)
+    const RowmaxArgs rm{res->pot, res->norm, 1.0 / eps, res->cnt, res->cnt_pad, rowmax, flags, 1 + n_jtiles};
+    const int vt_rows = (sp.wide_tiles * 256 + (sp.rest ? 128 : 0)) / 64;
+    int64_t rm_rows = ceil_div(res->cnt_pad, (int64_t)sp.e_chunks * 256);   // (a row per thread, up to 1024 rows of blocks)
+    if (rm_rows > 1024) rm_rows = 1024;
+    hipLaunchKernelGGL(k_plan_prep, dim3((unsigned)sp.e_chunks, (unsigned)(vt_rows + rm_rows)), dim3(256), 0, c->stream, V, ldv, str->cnt,
+                       (int)p, sp.e_chunks, vt, vt_rows, rm);
     const int n_itiles = (int)ceil_div(str->cnt, BI);
     const int64_t all = round_up(res->cnt, 256);
     for (int64_t off = 0; off < all; off += sp.rows) {
