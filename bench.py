@@ -205,8 +205,14 @@ def run_workload(name, steps, warmup, schedule="alternating", n_override=None, c
         roof = {"bound": "alu", "achieved": slots / (avg_ms * 1e-3) / 1e12,
                 "peak": VALU_LANE_SLOTS_PER_S / 1e12, "unit": "Tlane-op/s"}
         dtype = "f32"
-    roof["frac"] = roof["achieved"] / roof["peak"]
-    traffic = MEASURED_TRAFFIC.get(w.name) if n_override is None else None
+    # half-steps through cell moments (d <= 3, fs_moments.hip) evaluate no pairs: no rate of pairs can exceed the exponentials'
+    moments = w.d <= 3 and pairs / (avg_ms * 1e-3) > VALU_LANE_SLOTS_PER_S / 4.0
+    if moments:
+        roof = {"bound": "mfma + alu", "achieved": pairs / (avg_ms * 1e-3) / 1e12, "peak": None, "frac": None,
+                "unit": "T pairs/s stood for"}
+    else:
+        roof["frac"] = roof["achieved"] / roof["peak"]
+    traffic = MEASURED_TRAFFIC.get(w.name) if n_override is None and not moments else None
     roof["traffic"] = traffic[0] if traffic else None
     roof["traffic_source"] = (traffic[1] + " (rocprofv3 counters of an earlier run of this command, not of this run)") \
         if traffic else None

@@ -222,6 +222,10 @@ size_t layout_with(const Ctx *c, const fs_problem *p, Prepared *P, char *base, s
     P->scalars = base ? (double *)(base + o) : nullptr;
     o = A.take((size_t)(256 + 1) * 16 * 8);
     P->mean = base ? (double *)(base + o) : nullptr;
+    const bool moments = P->path == Path::LowD && mom_size(c, p->n, p->m, p->d);
+    P->mom.bytes = moments ? mom_bytes(p->n, p->m) : 0;
+    o = A.take(P->mom.bytes);
+    P->mom.base = base && moments ? base + o : nullptr;
     o = A.take(extra);
     (void)o;
     return A.off;
@@ -305,7 +309,7 @@ fs_status finalize(Ctx *c, const Prepared *P, Side *res, Splits splits, double e
                    double *abs_dev_sum, double mix = 1.0, double *save_old = nullptr, GaugeMode gauge = GaugeMode::None,
                    int64_t gauge_prev_cnt = 0, double gauge_prev_eps = 0.0)
 {
-    const double *nrm = (P->path == Path::LowD && !lowd_precise(P, eps)) ? res->norm_f : res->norm;
+    const double *nrm = P->path == Path::LowD ? lowd_norm(P, res, eps) : res->norm;
     return launch_finalize(c, P, res, nrm, splits, eps, eps_next_bias, user_out, abs_dev_sum, mix, save_old, gauge,
                            gauge_prev_cnt, gauge_prev_eps);
 }
@@ -444,6 +448,7 @@ fs_status grad_common(Ctx *c, const fs_problem *prob, float eps, const float *f,
         V = vf;
         ldv = d;
     }
+    P.mom.values_finite = true;   // (mom_ready looks at the bounds of both clouds)
     if ((st = apply_run(c, &P, eps, wrt_y, V, d, ldv, grad, ldg, mode == 1 ? mass : nullptr)) != FS_OK) return st;
     return launch_grad_assemble(c, grad, ldg, wrt_y ? prob->y : prob->x, prob->dtype, wrt_y ? prob->ldy : prob->ldx, rows, d,
                                 wrt_y ? prob->b : prob->a, mass, mode);
@@ -848,6 +853,7 @@ fs_status fs_solve_symmetric(fs_ctx *ctx, const fs_problem *prob, float eps_in, 
     const double eps = (double)eps_in;
     Prepared P;
     P.halfsteps_per_eps = 2 * iters;
+    P.mom.off = true;   // (both passes of an iteration are one launch over the pairs)
     // Both passes of an iteration read the old potentials, so the second one must not overwrite
     // the split partials of the first before they are merged: it gets a partial buffer of its own.
     Prepared sizing;
@@ -956,7 +962,7 @@ fs_status fs_ot_value(fs_ctx *ctx, const fs_problem *prob, float eps, const floa
     if ((st = launch_bias_from_user(c, &P, &P.Y, g, eps, false, true)) != FS_OK) return st;
     Splits splits;
     if ((st = run_lse(c, &P, &P.X, &P.Y, eps, &splits)) != FS_OK) return st;
-    const double *nrm = (P.path == Path::LowD && !lowd_precise(&P, eps)) ? P.X.norm_f : P.X.norm;
+    const double *nrm = P.path == Path::LowD ? lowd_norm(&P, &P.X, eps) : P.X.norm;
     if ((st = launch_value_terms(c, &P, &P.X, nrm, &P.Y, splits, eps, reinterpret_cast<double *>(scratch), P.scalars)) !=
         FS_OK)
         return st;
@@ -1208,7 +1214,10 @@ fs_status fs_debug_set(fs_ctx *ctx, const char *key, int64_t value)
         c->dbg_lowd_precise_valu = (int)value;
     else if (k == "lowd_precise_any_bias" && (value == 0 || value == 1))
         c->dbg_lowd_any_bias = (int)value;
-    else if (k == "fx_any_size" && (value == 0 || value == 1)) {
+    else if (k == "lowd_moments" && value >= 0 && value <= 2) {
+        c->dbg_lowd_moments = (int)value;
+        c->kept_valid = false;   // (the layout depends on it)
+    } else if (k == "fx_any_size" && (value == 0 || value == 1)) {
         c->dbg_fx_any_size = (int)value;
         c->kept_valid = false;   // (the layout depends on it)
     } else if (k == "fx_splits" && value >= 0 && value <= 1024)
@@ -1235,18 +1244,19 @@ fs_status fs_profile_read(fs_ctx *ctx, double *avg_ms, int64_t *launches, double
     if (c->device < 0) return fail(c, FS_ERR_DEVICE, "host-only context");
     FS_HIP(c, hipStreamSynchronize(c->stream));
     // per kernel kind; the one with the largest total time is the dominant kernel
-    double total[2] = {0.0, 0.0}, pairs[2] = {0.0, 0.0};
-    int64_t cnt[2] = {0, 0};
+    double total[3] = {0.0, 0.0, 0.0}, pairs[3] = {0.0, 0.0, 0.0};
+    int64_t cnt[3] = {0, 0, 0};
     for (size_t k = 0; k + 1 < c->ev_used; k += 2) {
         float ms = 0.0f;
         if (hipEventElapsedTime(&ms, c->ev_pool[k], c->ev_pool[k + 1]) == hipSuccess) {
-            const int kind = c->ev_kind[k / 2] ? 1 : 0;
+            const int kind = c->ev_kind[k / 2];
             total[kind] += ms;
             pairs[kind] += c->ev_pairs[k / 2];
             ++cnt[kind];
         }
     }
-    const int dom = total[1] > total[0] ? 1 : 0;
+    int dom = total[1] > total[0] ? 1 : 0;
+    if (total[2] > total[dom]) dom = 2;
     if (avg_ms) *avg_ms = cnt[dom] ? total[dom] / (double)cnt[dom] : 0.0;
     if (launches) *launches = cnt[dom];
     if (pairs_per_launch) *pairs_per_launch = cnt[dom] ? pairs[dom] / (double)cnt[dom] : 0.0;

@@ -218,6 +218,7 @@ struct Ctx {
     int dbg_lowd_score = 0;          // 32: fp32 scores, 64: float64 scores in every low-d half-step
     int dbg_lowd_precise_valu = 0;   // 1: float64 scores at d <= 3 on the vector ALU instead of the precise records
     int dbg_lowd_any_bias = 0;       // 1: the precise records also for biases beyond their digit range (tests of that case)
+    int dbg_lowd_moments = 0;        // d <= 3: 1: half-steps through cell moments wherever they can be, 2: never
     int dbg_fx_any_size = 0;         // 1: digit images for problems of any size
     int dbg_fx_splits = 0;           // forced split count of the streamed side of a fixed-point pass
     // profiling of the streaming LSE launches
@@ -225,7 +226,7 @@ struct Ctx {
     std::vector<hipEvent_t> ev_pool;   // pairs (start, stop)
     size_t ev_used = 0;
     std::vector<int> ev_kind;          // per recorded launch: which kernel it was (0 = the path's main
-                                       // kernel, 1 = the low-d float64-score kernel)
+                                       // kernel, 1 = the low-d float64-score kernel, 2 = a pass through cell moments)
     std::vector<double> ev_pairs;      // per recorded launch: pair evaluations
 };
 
@@ -287,6 +288,49 @@ struct Side {
     double *pot = nullptr;    // [cnt_pad] UNSHIFTED potential (f or g) in float64
 };
 
+// Half-steps through cell moments (fs_moments.hip, d <= 3).  A grid of cells over one cloud: corner, edges, cells per coordinate.
+constexpr int kMomMaxCells = 8192;   // per cloud
+constexpr int kMomBlock = 256;       // streamed points a workgroup takes at a time; a block of a cell is one to four times that
+constexpr int kMomTerms = 224;       // monomials at most
+constexpr int kMomRows = 256;        // rows per workgroup
+struct MomGeom {
+    double lo[3], h[3];
+    int nc[3];
+};
+// one cloud dealt to its cells (device)
+struct MomSide {
+    uint16_t *key;          // [cnt] cell of a point
+    int *perm;              // [cnt] point at a place of the sorted order
+    float4 *xi;             // [cnt] sorted: coordinates in half cells
+    int *hist, *total;      // of the sort
+    int4 *cell;             // cells that hold points: (cell, first place, points, -)
+    int4 *block, *rows;     // blocks and groups of rows: (number of their cell among those, first place, points, -)
+    double4 *centre;        // [cells]
+    int *several;           // cells of several blocks
+    int *first_block, *first_rows;   // [cells + 1]
+    int *counts;
+};
+// What the passes of one entry call share: the grids belong to one eps and are laid out when it is first met.
+struct MomState {
+    char *base = nullptr;   // nullptr: no buffers
+    size_t bytes = 0;
+    bool off = false;       // the caller's schedule does not take them
+    bool values_finite = false;   // the values of this application are points of a cloud (an infinite one would reach whole
+                                  // cells as NaN)
+    double lo[2][3], hi[2][3];   // bounds of both centred clouds (host)
+    double eps = 0.0;
+    bool on = false;        // ... whether half-steps at that eps run through moments
+    int kind = 0;
+    MomGeom g[2];
+    MomSide side[2];
+    int cells[2], blocks[2], groups[2], several[2];
+    size_t slab = 0;        // bytes of M
+    float coef[kMomTerms];
+    double s[3];
+    unsigned char *M = nullptr;
+    std::vector<int> host;
+};
+
 struct Prepared {
     Path path = Path::LowD;
     int64_t d = 0;
@@ -302,6 +346,7 @@ struct Prepared {
     int dbg_score = 0;            // LowD: the context's score switch (see Ctx::dbg_lowd_score)
     bool dbg_precise_valu = false;   // LowD: the context's kernel switch (see Ctx::dbg_lowd_precise_valu)
     bool dbg_any_bias = false;       // LowD: see Ctx::dbg_lowd_any_bias
+    mutable MomState mom;            // LowD, d <= 3
     int kp = 0;   // F64 / BF16: padded contraction length
     int fx_ks = 0;   // F64: k-steps of the digit images, 0: none
     Side X, Y;
@@ -311,7 +356,7 @@ struct Prepared {
     double *dev_part = nullptr;  // [ceil(max(n,m)/256)] per-block sums of the marginal deviation
     double *gauge_part = nullptr;   // [2][ceil(max(n,m)/256)] per-block sums of the plan's mass seen by a g-update
     double *gauge_part_x = nullptr; // the same for an f-update (averaged schedule: both passes measure, halves by parity)
-    double *scalars = nullptr;   // [16] device doubles (marginal errors, centring sums...; [8], [9]: gauge drift, see GaugeMode; [10], [11]: FxGate::r2 and the origin of the digits)
+    double *scalars = nullptr;   // [16] device doubles (marginal errors, centring sums...; [8], [9]: gauge drift, see GaugeMode; [10], [11]: FxGate::r2 and the origin of the digits; LowD: [10..15] bounds of the centred clouds, see k_mean_final)
     double *mean = nullptr;      // [kLowdMaxD] common mean (LowD)
     char *extra = nullptr;       // entry-point specific scratch (plan application partials)
     size_t extra_bytes = 0;
@@ -479,6 +524,23 @@ PassShape lowd_shape(const Ctx *c, int64_t n_res, int64_t n_str);
 bool lowd_precise(const Prepared *P, double eps);
 fs_status lowd_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps,
                    Splits *splits_out);
+// the squared norms that belong to the coordinates of the half-steps at eps (Side::norm or norm_f)
+inline const double *lowd_norm(const Prepared *P, const Side *res, double eps)
+{
+    return (P->mom.on && P->mom.eps == eps) || lowd_precise(P, eps) ? res->norm : res->norm_f;
+}
+// fs_moments.hip
+size_t mom_bytes(int64_t n, int64_t m);
+// (below this a pass over the pairs takes less than the cells' launches)
+inline bool mom_size(const Ctx *c, int64_t n, int64_t m, int64_t d)
+{
+    return d <= 3 && !c->ws_static && c->dbg_lowd_moments != 2 && ((double)n * (double)m >= 3.0e8 || c->dbg_lowd_moments == 1);
+}
+fs_status mom_ready(Ctx *c, const Prepared *P, double eps, bool *use);
+// V != nullptr: the plan application to the p columns of V as well, accumulators [rows][p] in opart
+fs_status mom_pass(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, const float *V, int p, int64_t ldv, float *opart);
+bool mom_fits(const Prepared *P, const Side *str, int p);
+constexpr int kMomMaxP = 8;   // columns of an application through moments
 // a half-step and its merge in one launch (small problems); *done = false: not applicable.  It leaves one gauge sum per 32
 // rows, the merge kernels one per 256.
 // The line, from half-steps in two launches and in one (us): d = 3: n = m = 1024 10.4 / 6.4, 4096 12.0 / 10.1, 8192

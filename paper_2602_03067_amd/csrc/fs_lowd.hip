@@ -1172,6 +1172,15 @@ void launch_lse_split_pair(dim3 grid, hipStream_t st, const SplitArgs &a0, const
 
 fs_status lowd_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, Splits *splits_out)
 {
+    {
+        bool moments = false;
+        fs_status ms = mom_ready(c, P, eps, &moments);
+        if (ms != FS_OK) return ms;
+        if (moments) {
+            *splits_out = 1;
+            return mom_pass(c, P, res, str, eps, nullptr, 0, 0, nullptr);
+        }
+    }
     // fp32-accuracy half-steps run on the bf16 matrix cores from the split records; float64-score
     // ones too when d <= 3 (precise records); other float64-score half-steps are handled further down
     SplitArgs a;
@@ -1226,6 +1235,7 @@ fs_status lowd_half_small(Ctx *c, const Prepared *P, const Side *res, const Side
 {
     *done = false;
     if (!lowd_small(P->X.cnt, P->Y.cnt, P->d) || c->dbg_lowd_splits) return FS_OK;   // (a forced split count asks for the split kernels)
+    if (P->mom.base && c->dbg_lowd_moments == 1) return FS_OK;
     SplitArgs a;
     bool precise = false;
     fs_status st;
@@ -1371,6 +1381,16 @@ fs_status lowd_apply(Ctx *c, const Prepared *P, const Side *res, const Side *str
                      int64_t p, int64_t ldv, float *out, int64_t ldo, float *mass_out, const float *had_A, int64_t lda)
 {
     float *opart = (float *)P->extra;
+    if (!had_A && P->mom.values_finite && p <= kMomMaxP) {
+        bool moments = false;
+        fs_status st = mom_ready(c, P, eps, &moments);
+        if (st != FS_OK) return st;
+        if (moments && mom_fits(P, str, (int)p)) {
+            if (!opart || (size_t)res->cnt_pad * p * 4 > P->extra_bytes) return fail(c, FS_ERR_DEVICE, "internal: low-d apply workspace");
+            if ((st = mom_pass(c, P, res, str, eps, V, (int)p, ldv, opart)) != FS_OK) return st;
+            return launch_apply_finalize(c, P, res, res->norm, 1, eps, opart, (int)p, 0, (int)p, out, ldo, mass_out);
+        }
+    }
     // Plain applications run on the split records (scores and products on the matrix cores);
     // the Hadamard-weighted form and float64 scores outside the matrix cores' reach stay on the
     // vector-ALU kernel below.

@@ -2,6 +2,8 @@
 // clouds and their squared norms (Prop. 1: alpha, beta), the per-point bias
 // (Alg. 1, "precompute bias"), and the merge of the per-split LSE statistics into
 // the new shifted potential.
+#include <string.h>
+
 #include "fs_finalize.h"
 #include "fs_internal.h"
 
@@ -43,6 +45,8 @@ __global__ void k_row_norms(const void *pts, int dtype, int64_t rows, int64_t d,
     out[i] = (float)s;
 }
 
+__device__ inline float max_or_nan(float a, float b) { return a >= b || a != a ? a : b; }
+
 // ---- common mean of both clouds (low-d path), deterministic two-stage reduction ---------
 // stage 1: block b writes the coordinate sums of its slice to part[b][0..15]
 // (blockIdx.y: 0 = the x cloud, 1 = the y cloud)
@@ -73,32 +77,83 @@ __global__ __launch_bounds__(256) void k_coord_sums(CloudIn c0, CloudIn c1, int 
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) acc[k] += __shfl_xor(acc[k], off);
         }
+    // at d <= 3 columns 4 + k and 8 + k hold the largest -v and v of coordinate k
+    float down[3] = {-INFINITY, -INFINITY, -INFINITY}, up[3] = {-INFINITY, -INFINITY, -INFINITY};
+    if (d <= 3) {
+        for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < rows; i += (int64_t)gridDim.x * 256)
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                if (k < d) {
+                    const float v = load_pt(pts, dtype, i * ld + k);
+                    down[k] = max_or_nan(down[k], -v);
+                    up[k] = max_or_nan(up[k], v);
+                }
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) {
+                down[k] = max_or_nan(down[k], __shfl_xor(down[k], off));
+                up[k] = max_or_nan(up[k], __shfl_xor(up[k], off));
+            }
+    }
     if ((threadIdx.x & 63) == 0) {
 #pragma unroll
         for (int k = 0; k < kLowdMaxD; ++k) sh[threadIdx.x >> 6][k] = acc[k];
+        if (d <= 3) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                sh[threadIdx.x >> 6][4 + k] = (double)down[k];
+                sh[threadIdx.x >> 6][8 + k] = (double)up[k];
+            }
+        }
     }
     __syncthreads();
-    if (threadIdx.x < kLowdMaxD)
+    if (d <= 3 && threadIdx.x >= 4 && threadIdx.x < kLowdMaxD) {
+        float b = -INFINITY;
+        for (int w = 0; w < 4; ++w) b = max_or_nan(b, (float)sh[w][threadIdx.x]);
+        part[(int64_t)blockIdx.x * kLowdMaxD + threadIdx.x] = (double)b;
+    } else if (threadIdx.x < kLowdMaxD)
         part[(int64_t)blockIdx.x * kLowdMaxD + threadIdx.x] = sh[0][threadIdx.x] + sh[1][threadIdx.x] + sh[2][threadIdx.x] + sh[3][threadIdx.x];
 }
 
 // stage 2: mean[k] = (sum of partX[.][k] + sum of partY[.][k]) / (n + m).  One block of 256: thread
 // (group g, coordinate k) sums the blocks b = g mod 16, then coordinate k's 16 group sums are added
-// in a fixed order.  Also clears zeroed[0..2] (the slots the next kernels take maxima into).
+// in a fixed order.  Also clears zeroed[0..2] (the slots the next kernels take maxima into), and at d <= 3 leaves the bounds
+// of the centred clouds as floats in bounds[2 side + 0 (smallest) / 1 (largest)][coordinate] (a NaN where one is).
 __global__ __launch_bounds__(256) void k_mean_final(const double *partX, const double *partY, int blocks, double inv_cnt,
-                                                    double *mean, double *zeroed)
+                                                    double *mean, double *zeroed, int d, float *bounds)
 {
     static_assert(kLowdMaxD == 16, "thread mapping below");
     __shared__ double sh[16][kLowdMaxD];
     const int k = threadIdx.x & 15, g = threadIdx.x >> 4;
+    const bool is_bound = d <= 3 && k >= 4;   // (columns 4..6 and 8..10 of the partial sums, see k_coord_sums)
+    __shared__ float shb[2][16][kLowdMaxD];
+    if (is_bound) {
+        float b[2] = {-INFINITY, -INFINITY};
+        for (int q = g; q < blocks; q += 16) {
+            b[0] = max_or_nan(b[0], (float)partX[(int64_t)q * kLowdMaxD + k]);
+            b[1] = max_or_nan(b[1], (float)partY[(int64_t)q * kLowdMaxD + k]);
+        }
+        shb[0][g][k] = b[0];
+        shb[1][g][k] = b[1];
+    }
     double s = 0.0;
-    for (int b = g; b < blocks; b += 16) s += partX[(int64_t)b * kLowdMaxD + k] + partY[(int64_t)b * kLowdMaxD + k];
+    if (!is_bound)
+        for (int b = g; b < blocks; b += 16) s += partX[(int64_t)b * kLowdMaxD + k] + partY[(int64_t)b * kLowdMaxD + k];
     sh[g][k] = s;
     __syncthreads();
     if (threadIdx.x < kLowdMaxD) {
         double t = 0.0;
         for (int q = 0; q < 16; ++q) t += sh[q][threadIdx.x];
         mean[threadIdx.x] = t * inv_cnt;
+    }
+    __syncthreads();   // (mean is read below)
+    if (d <= 3 && threadIdx.x < 12) {
+        const int side = threadIdx.x / 6, top = threadIdx.x / 3 % 2, c = threadIdx.x % 3;
+        float b = -INFINITY;
+        for (int q = 0; q < 16; ++q) b = max_or_nan(b, shb[side][q][top ? 8 + c : 4 + c]);
+        // (column 4 + c holds the largest -v)
+        bounds[(2 * side + top) * 3 + c] = c < d ? (float)((top ? (double)b : -(double)b) - mean[c]) : 0.0f;
     }
     if (threadIdx.x < 3) zeroed[threadIdx.x] = 0.0;
 }
@@ -939,7 +994,7 @@ fs_status launch_prepare(Ctx *c, const fs_problem *p, Prepared *P)
         hipLaunchKernelGGL(k_coord_sums, dim3(half, 2), dim3(256), 0, c->stream, cx, cy, dtype, (int)p->d);
         // (also clears scalars[5..7]: the sizes of the biases and the largest squared norm, all taken by atomic maxima)
         hipLaunchKernelGGL(k_mean_final, dim3(1), dim3(256), 0, c->stream, partX, partY, half,
-                           1.0 / (double)(p->n + p->m), P->mean, P->scalars + 5);
+                           1.0 / (double)(p->n + p->m), P->mean, P->scalars + 5, (int)p->d, reinterpret_cast<float *>(P->scalars + 10));
         const int64_t pad_max = P->X.cnt_pad > P->Y.cnt_pad ? P->X.cnt_pad : P->Y.cnt_pad;
         PrepLowdSide sd[2];
         for (int k = 0; k < 2; ++k) {
@@ -999,12 +1054,19 @@ fs_status launch_bias_from_user(Ctx *c, Prepared *P, Side *side, const float *po
                        absmax);
     FS_HIP(c, hipGetLastError());
     if (absmax && last) {
-        double h[3] = {0.0, 0.0, 0.0};   // |log w| part, potential part, rho_max
+        double h[11] = {};   // |log w| part, potential part, rho_max; [5..]: bounds of the clouds, see k_mean_final
         FS_HIP(c, hipMemcpyAsync(h, P->scalars + 5, sizeof h, hipMemcpyDeviceToHost, c->stream));
         FS_HIP(c, hipStreamSynchronize(c->stream));
         if (h[0] > P->logw_mag) P->logw_mag = h[0];
         if (h[1] * eps > P->pot_mag_eps) P->pot_mag_eps = h[1] * eps;
         P->rho_max = h[2];
+        float b[12];
+        memcpy(b, h + 5, sizeof b);
+        for (int s = 0; s < 2 && P->d <= 3; ++s)
+            for (int k = 0; k < 3; ++k) {
+                P->mom.lo[s][k] = (double)b[6 * s + k];
+                P->mom.hi[s][k] = (double)b[6 * s + 3 + k];
+            }
         if (c->kept_valid) c->kept_rho_max = h[2];   // belongs to the kept derived copies (no-op when they are another problem's)
     }
     return FS_OK;

@@ -1,0 +1,214 @@
+"""GPU parity of the half-steps and gradients through cell moments (d <= 3) against the float64 oracle.
+
+The passes are forced with the context's "lowd_moments" switch, so that small clouds reach every part of them: cells of several
+blocks, more streamed cells than one segment, several launches, ragged groups of rows, empty cells, one-cell clouds.
+
+Tolerance of a half-step in units of eps (= relative error of a row sum): the series of e^t is off by 3e-8, monomials, weights and
+moments are kept to 2^-22, and a row in a corner of its cell can lose e^(2 tau) = 14 of that to cancellation: 14 (3e-8 + 3 2^-22) =
+1.1e-5; the float output adds |f| 2^-24 / eps.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_03067_amd import binding, workloads
+from tests._gpu_common import dev, host, make_problem, max_err_over_eps, say
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1.1e-5
+
+
+def _tol(f, eps):
+    return TOL + float(np.max(np.abs(f))) * 2.0 ** -24 / eps
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = binding.Context(0)
+    c.fs_debug_set("lowd_moments", 1)
+    yield c
+    c.close()
+
+
+def _cloud(rng, kind, n, d):
+    if kind == "cube":
+        x = rng.random((n, d))
+    elif kind == "clusters":      # most points in a few cells
+        x = 0.5 + 0.002 * rng.standard_normal((n, d))
+        x[: n // 10] = rng.random((n // 10, d))
+    elif kind == "flat":          # no extent in the last coordinate
+        x = rng.random((n, d))
+        x[:, -1] = 0.25
+    else:                         # one point, n times
+        x = np.full((n, d), 0.3)
+    return x.astype(np.float32)
+
+
+def _weights(rng, n, zeros=False):
+    a = rng.random(n) + 0.1
+    if zeros:
+        a[rng.random(n) < 0.3] = 0.0
+        a[0] = 0.5
+    return (a / a.sum()).astype(np.float32)
+
+
+# one point, ragged tiles of 32 rows and points, cells of more than 256 rows and of several blocks, every kind of expansion (it
+# follows from d and eps), more than 1024 cells (two segments, several launches)
+@pytest.mark.parametrize("n,m,d,eps,kind", [
+    (1, 1, 3, 0.1, "cube"), (5, 3, 1, 0.05, "cube"), (255, 257, 2, 0.05, "cube"), (1000, 777, 3, 0.1, "cube"),
+    (700, 3000, 3, 3.0, "cube"), (2049, 513, 3, 0.05, "cube"), (900, 1100, 3, 0.6, "cube"), (5000, 4000, 3, 0.3, "clusters"),
+    (1500, 9000, 2, 0.1, "clusters"), (3000, 6000, 1, 0.2, "clusters"), (4000, 3000, 3, 0.012, "cube"), (3000, 2500, 2, 0.003, "cube"),
+    (800, 900, 3, 0.1, "flat"), (300, 500, 2, 0.2, "point")])
+@pytest.mark.parametrize("pot", ["zero", "smooth", "rough"])
+def test_half_steps(ctx, oracle, n, m, d, eps, kind, pot):
+    rng = np.random.default_rng(n + 7 * m + d)
+    x, y = _cloud(rng, "cube" if kind == "clusters" else kind, n, d), _cloud(rng, kind, m, d)
+    a, b = _weights(rng, n), _weights(rng, m, zeros=pot == "rough")
+    eps = float(np.float32(eps))
+    g = np.zeros(m, np.float32)
+    f = np.zeros(n, np.float32)
+    if pot == "smooth":
+        g, f = (y ** 2).sum(1) - 0.3 * y[:, 0], (x ** 2).sum(1) + 0.2 * x[:, -1]
+    elif pot == "rough":
+        g, f = 8.0 * eps * rng.standard_normal(m), 8.0 * eps * rng.standard_normal(n)
+    g, f = g.astype(np.float32), f.astype(np.float32)
+    say("moments n=%d m=%d d=%d eps=%g %s %s" % (n, m, d, eps, kind, pot))
+    prob = make_problem(x, y, a, b)
+    f1 = host(ctx.fs_update_f(prob, eps, dev(g)))
+    g1 = host(ctx.fs_update_g(prob, eps, dev(f)))
+    fw, gw = oracle.update_f(x, y, b, eps, g), oracle.update_g(x, y, a, eps, f)
+    assert max_err_over_eps(f1, fw, eps) <= _tol(fw, eps)
+    assert max_err_over_eps(g1, gw, eps) <= _tol(gw, eps)
+    # a fixed order of every sum
+    assert np.array_equal(f1, host(ctx.fs_update_f(prob, eps, dev(g))))
+
+
+def test_runs_through_moments_and_falls_back(oracle):
+    """Forced and left out the results differ (they are other sums); where the cells would be too many both run over the pairs."""
+    rng = np.random.default_rng(3)
+    n, m, eps = 1500, 1300, float(np.float32(0.1))
+    for spread, differs in ((1.0, True), (40.0, False)):
+        x, y = _cloud(rng, "cube", n, 3) * spread, _cloud(rng, "cube", m, 3) * spread
+        a, b = _weights(rng, n), _weights(rng, m)
+        g = rng.standard_normal(m).astype(np.float32) * eps
+        out = []
+        for mode in (1, 2):
+            c = binding.Context(0)
+            c.fs_debug_set("lowd_moments", mode)
+            say("moments mode %d spread %g" % (mode, spread))
+            out.append(host(c.fs_update_f(make_problem(x, y, a, b), eps, dev(g))))
+            c.close()
+        assert np.array_equal(out[0], out[1]) != differs
+        assert max_err_over_eps(out[0], oracle.update_f(x, y, b, eps, g), eps) <= 1e-4
+
+
+@pytest.mark.parametrize("where", ["nan", "inf", "-inf", "all -inf"])
+def test_potentials_that_are_not_finite(oracle, where):
+    """The same rows are NaN or infinite as over the pairs."""
+    rng = np.random.default_rng(5)
+    n, m, eps = 900, 800, float(np.float32(0.1))
+    x, y = _cloud(rng, "cube", n, 3), _cloud(rng, "cube", m, 3)
+    g = np.zeros(m, np.float32)
+    g[:: 1 if where == "all -inf" else 97] = {"nan": np.nan, "inf": np.inf}.get(where, -np.inf)
+    out = []
+    for mode in (1, 2):
+        c = binding.Context(0)
+        c.fs_debug_set("lowd_moments", mode)
+        say("moments mode %d potentials %s" % (mode, where))
+        out.append(host(c.fs_update_f(make_problem(x, y, None, None), eps, dev(g))))
+        c.close()
+    same = np.isnan(out[0]) == np.isnan(out[1])
+    assert same.all() and (np.isposinf(out[0]) == np.isposinf(out[1])).all() and (np.isneginf(out[0]) == np.isneginf(out[1])).all()
+    ok = np.isfinite(out[0])
+    if ok.any():
+        assert np.max(np.abs(out[0][ok] - out[1][ok])) <= 1e-4 * eps
+
+
+def test_strides_and_bf16_storage(ctx, oracle):
+    rng = np.random.default_rng(9)
+    n, m, eps = 1200, 1100, float(np.float32(0.05))
+    x, y = workloads.to_bf16_round(_cloud(rng, "cube", n, 3)), workloads.to_bf16_round(_cloud(rng, "cube", m, 3))
+    g = (0.1 * rng.standard_normal(m)).astype(np.float32)
+    want = oracle.update_f(x, y, np.full(m, 1.0 / m), eps, g)
+    xt = torch.zeros(n, 5, device="cuda:0", dtype=torch.bfloat16)
+    xt[:, :3] = dev(x, torch.bfloat16)
+    say("moments bf16 storage, strided")
+    f = host(ctx.fs_update_f(binding.Problem(xt[:, :3], dev(y, torch.bfloat16), None, None), eps, dev(g)))
+    assert max_err_over_eps(f, want, eps) <= _tol(want, eps) + 1e-6   # (uniform weights: log(1/m) in float64 on both sides)
+
+
+@pytest.mark.parametrize("n,m,d,eps,kind", [(1100, 900, 3, 0.1, "cube"), (3000, 5000, 3, 0.3, "clusters"), (700, 600, 2, 0.05, "cube"),
+                                            (400, 500, 1, 0.05, "cube"), (900, 800, 3, 0.1, "flat")])
+@pytest.mark.parametrize("mode", [0, 1, 2])
+def test_gradients(ctx, oracle, n, m, d, eps, kind, mode):
+    """Gradients run the plan application of the other cloud's points through moments of their own."""
+    rng = np.random.default_rng(n + m + d + mode)
+    x, y = _cloud(rng, "cube" if kind == "clusters" else kind, n, d) - 0.5, _cloud(rng, kind, m, d) - 0.4
+    a, b = _weights(rng, n), _weights(rng, m)
+    eps = float(np.float32(eps))
+    f, g = oracle.solve(x, y, a, b, eps, eps, 1, 5)
+    f, g = f.astype(np.float32), g.astype(np.float32)
+    say("moments gradient n=%d m=%d d=%d mode=%d" % (n, m, d, mode))
+    prob = make_problem(x, y, a, b)
+    for wrt_y in (False, True):
+        z, o, w = (y, x, b) if wrt_y else (x, y, a)
+        apply = oracle.apply_plan_T if wrt_y else oracle.apply_plan
+        T = apply(x, y, a, b, eps, f, g, o)
+        ones = apply(x, y, a, b, eps, f, g, np.ones((len(o), 1), np.float32))
+        want = 2 * (w[:, None] * z - T) if mode == 0 else 2 * (ones * z - T) if mode == 1 else z - T / w[:, None]
+        got = host((ctx.fs_grad_y if wrt_y else ctx.fs_grad_x)(prob, eps, dev(f), dev(g), mode))
+        # sums of |entries| times |values| bound the error of T; the row factor adds the float potentials' share, which the
+        # oracle has as well
+        scale = np.abs(ones) * np.abs(o).max() * (2.0 if mode < 2 else 1.0 / w[:, None])
+        assert np.max(np.abs(got - want) / scale) <= 2 * TOL
+
+
+def test_annealed_solve(ctx, oracle):
+    rng = np.random.default_rng(11)
+    n, m = 2000, 1700
+    x, y = _cloud(rng, "cube", n, 3), _cloud(rng, "clusters", m, 3) * 0.5 + 0.2
+    a, b = _weights(rng, n), _weights(rng, m)
+    f, g = torch.zeros(n, device="cuda:0"), torch.zeros(m, device="cuda:0")
+    say("moments annealed solve")
+    prob = make_problem(x, y.astype(np.float32), a, b)
+    ctx.fs_solve(prob, 1.0, 0.03, 4, 5, f, g)
+    fo, go = oracle.solve(x, y.astype(np.float32), a, b, 1.0, 0.03, 4, 5)
+    eps = float(np.float32(0.03))
+    assert max_err_over_eps(host(f), fo, eps) <= 1e-4 and max_err_over_eps(host(g), go, eps) <= 1e-4
+    # kept copies of the clouds change nothing
+    ctx.fs_points_keep(prob)
+    for _ in range(2):
+        f2, g2 = torch.zeros_like(f), torch.zeros_like(g)
+        ctx.fs_solve(prob, 1.0, 0.03, 4, 5, f2, g2)
+        assert torch.equal(f, f2) and torch.equal(g, g2)
+    ctx.fs_points_release()
+    err_r, err_c = ctx.fs_marginal_err(prob, eps, f, g)
+    wr, wc = oracle.marginal_err(x, y.astype(np.float32), a, b, eps, host(f), host(g))
+    assert abs(err_r - wr) <= 1e-5 and abs(err_c - wc) <= 1e-5
+
+
+def test_large_clouds_take_moments_by_themselves():
+    """Sampled rows of a half-step at a size where the library chooses, against float64 sums over all points."""
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(2)
+    n, m = 70001, 60007
+    x = torch.rand(n, 3, generator=gen, device="cuda:0")
+    y = torch.rand(m, 3, generator=gen, device="cuda:0") * 0.9
+    g = 0.05 * torch.randn(m, generator=gen, device="cuda:0")
+    eps = float(np.float32(0.1))
+    prob = binding.Problem(x, y, None, None)
+    out = []
+    for mode in (0, 2):
+        c = binding.Context(0)
+        c.fs_debug_set("lowd_moments", mode)
+        say("moments by themselves, mode %d" % mode)
+        out.append(c.fs_update_f(prob, eps, g))
+        torch.cuda.synchronize()
+        c.close()
+    assert not torch.equal(out[0], out[1])
+    rows = torch.arange(0, n, 97, device="cuda:0")
+    xs, ys = x[rows].double(), y.double()
+    s = ((g.double() - (ys * ys).sum(1)) / eps)[None, :] + 2.0 / eps * xs @ ys.t()
+    want = (xs * xs).sum(1) - eps * (torch.logsumexp(s, 1) - np.log(m))
+    assert float((out[0][rows].double() - want).abs().max()) / eps <= TOL + float(want.abs().max()) * 2.0 ** -24 / eps
