@@ -67,7 +67,7 @@ __device__ inline double store_bias(const BiasSink &s, int64_t i, double pot, do
     if (s.packed) {
         const float bf = (float)(((pot - s.norm_f[i]) * inv_eps + lw) * kLog2e);
         s.packed[i * s.dp + s.d] = bf;
-        if (s.split) reinterpret_cast<uint4 *>(s.split)[i * (2 * s.ks) + split_piece_pos(s.ks, i, s.d)] = split_bias_piece(bf);
+        if (s.split) reinterpret_cast<uint4 *>(s.split)[split_unit(s.ks, i, s.d)] = split_bias_piece(bf);
     }
     if (s.packed_d) s.packed_d[i * s.dpd + s.d] = b;
     if (s.split_p) {
@@ -77,8 +77,8 @@ __device__ inline double store_bias(const BiasSink &s, int64_t i, double pot, do
             split_grids(*s.rho_dev, s.q_eps, &gx, &gy);
             q = gx * gy;
         }
-        uint4 *rec = reinterpret_cast<uint4 *>(s.split_p) + i * 6;
-        split_precise_bias(b, q, rec + 1, reinterpret_cast<uint2 *>(rec + 5));
+        uint4 *rec = reinterpret_cast<uint4 *>(s.split_p);
+        split_precise_bias(b, q, rec + split_unit(3, i, 1), reinterpret_cast<uint2 *>(rec + split_unit(3, i, 5)));
     }
     if (s.bias_f) s.bias_f[i] = (float)b;
     if (s.bias_d) s.bias_d[i] = b;

@@ -321,7 +321,6 @@ __device__ __forceinline__ void lse_split_body(const SplitArgs &a, const int bx,
     // piece 1 in the precise one
     constexpr int MK = PRECISE ? 0 : KS - 1;
     const bool holds_max = PRECISE ? (lh == 1) : (lh == (d & 1));
-    auto lds_pos = [](int point, int piece) { return point * NP + split_piece_pos(KS, point, piece); };
 
     bf8 b[R][KS];
     float mrun[R], srun[R], stile[R];
@@ -408,7 +407,7 @@ __device__ __forceinline__ void lse_split_body(const SplitArgs &a, const int bx,
 
     auto load_a = [&](const Unit *tl, int grp, bf8(&av)[KS]) {
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) av[ks] = *reinterpret_cast<const bf8 *>(tl + lds_pos(grp * 32 + lj, 2 * ks + lh));
+        for (int ks = 0; ks < KS; ++ks) av[ks] = *reinterpret_cast<const bf8 *>(tl + grp * (64 * KS) + 64 * ks + l);   // (see split_unit)
     };
     auto scores = [&](const bf8(&av)[KS], f16v(&dd)[R]) {
 #pragma unroll
@@ -757,7 +756,6 @@ constexpr int kSmallWaves = 8;
 template <int KS, bool PRECISE>
 __global__ __launch_bounds__(64 * kSmallWaves) void k_half_lowd_small(SplitArgs a, FinalizeArgs fz, int n_groups)
 {
-    constexpr int NP = 2 * KS;
     __shared__ float sm[kSmallWaves][32];
     __shared__ double ss[kSmallWaves][32];
     const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, lj = l & 31, lh = l >> 5;
@@ -776,9 +774,8 @@ __global__ __launch_bounds__(64 * kSmallWaves) void k_half_lowd_small(SplitArgs 
     };
     const Unit *str = reinterpret_cast<const Unit *>(a.str);
     auto load_a = [&](int g, bf8 (&av)[KS]) {
-        const int64_t point = (int64_t)g * 32 + lj;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) av[ks] = *reinterpret_cast<const bf8 *>(str + point * NP + split_piece_pos(KS, point, 2 * ks + lh));
+        for (int ks = 0; ks < KS; ++ks) av[ks] = *reinterpret_cast<const bf8 *>(str + (int64_t)g * (64 * KS) + 64 * ks + l);   // (see split_unit)
     };
     auto scores = [&](const bf8 (&av)[KS], f16v &dd) {
 #pragma unroll

@@ -207,7 +207,7 @@ __global__ __launch_bounds__(256) void k_prep_lowd(PrepLowdSide s0, PrepLowdSide
     norm_f[i] = nf;
     norm[i] = nd;
     if (split) {   // streamed-role split record of the float copy
-        uint4 *rec = reinterpret_cast<uint4 *>(split) + i * (2 * ks);
+        uint4 *rec = reinterpret_cast<uint4 *>(split);
         for (int k = 0; k < 2 * ks; ++k) {
             uint4 u = make_uint4(0, 0, 0, 0);
             if (k < d) {
@@ -217,7 +217,7 @@ __global__ __launch_bounds__(256) void k_prep_lowd(PrepLowdSide s0, PrepLowdSide
             } else if (k == d) {
                 u = split_bias_piece(-INFINITY);
             }
-            rec[split_piece_pos(ks, i, k)] = u;
+            rec[split_unit(ks, i, k)] = u;
         }
     }
     // largest squared norm after centring, over both clouds: non-negative doubles order like their
@@ -257,13 +257,13 @@ __global__ void k_prep_split_precise(const double *packed_d0, int64_t cnt_pad0, 
         split3d(y - y1, ry[k]);
     }
     const __bf16 z = (__bf16)0.0f;
-    uint4 *rec = reinterpret_cast<uint4 *>(out) + i * 6;
+    uint4 *rec = reinterpret_cast<uint4 *>(out) + split_unit(3, i, 0);   // (piece k: 32 k units on)
     rec[0] = make_uint4(bf16_pair(Y1[0], Y1[1]), bf16_pair(Y1[2], z), 0u, 0u);
-    split_precise_bias(-INFINITY, 1.0, rec + 1, nullptr);
+    split_precise_bias(-INFINITY, 1.0, rec + 32, nullptr);
     for (int k = 0; k < 3; ++k)
-        rec[2 + k] = make_uint4(bf16_pair(ry[k][0], ry[k][1]), bf16_pair(ry[k][2], Y1[k]), bf16_pair(Y1[k], Y1[k]),
+        rec[64 + 32 * k] = make_uint4(bf16_pair(ry[k][0], ry[k][1]), bf16_pair(ry[k][2], Y1[k]), bf16_pair(Y1[k], Y1[k]),
                                 bf16_pair(ry[k][0], ry[k][1]));
-    rec[5] = make_uint4(0u, 0u, bf16_pair(z, ry[0][0]), bf16_pair(ry[1][0], ry[2][0]));
+    rec[160] = make_uint4(0u, 0u, bf16_pair(z, ry[0][0]), bf16_pair(ry[1][0], ry[2][0]));
 }
 
 // ---- float64 derived copy (fp64 matrix-core path) ----------------------------------------
