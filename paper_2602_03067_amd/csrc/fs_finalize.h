@@ -19,14 +19,13 @@ __device__ inline double block_sum_256(double v, double *sh)
     return sh[0];
 }
 
-// piece d of a streamed-role split record: the bias in three bf16 pieces, then the three ones
-// that pick up the resident row's (negated) running max
-__device__ inline uint4 split_bias_piece(float bias)
+// the last four slots of a streamed-role split record: the bias in three pieces, and a one that picks up the resident row's
+// (negated) running max
+__device__ inline uint2 split_bias_words(float bias, bool negated)
 {
     __bf16 b[3];
-    split3(bias, b);
-    const __bf16 one = (__bf16)1.0f;
-    return make_uint4(bf16_pair(b[0], b[1]), bf16_pair(b[2], one), bf16_pair(one, one), 0u);
+    split3(negated ? -bias : bias, b);
+    return make_uint2(bf16_pair(b[0], b[1]), bf16_pair(b[2], (__bf16)(negated ? -1.0f : 1.0f)));
 }
 
 // The three 8-bit digits of a bias on the grid q and what they leave.  Inside the digit range (|bias| < 2^21 q: the
@@ -67,7 +66,7 @@ __device__ inline double store_bias(const BiasSink &s, int64_t i, double pot, do
     if (s.packed) {
         const float bf = (float)(((pot - s.norm_f[i]) * inv_eps + lw) * kLog2e);
         s.packed[i * s.dp + s.d] = bf;
-        if (s.split) reinterpret_cast<uint4 *>(s.split)[split_unit(s.ks, i, s.d)] = split_bias_piece(bf);
+        if (s.split) reinterpret_cast<uint2 *>(s.split)[2 * split_unit(s.ks, i, 2 * s.ks - 1) + 1] = split_bias_words(bf, split_negated(i));
     }
     if (s.packed_d) s.packed_d[i * s.dpd + s.d] = b;
     if (s.split_p) {

@@ -67,7 +67,27 @@ __device__ inline void dma4s(const void *g_uniform, unsigned lane_off, unsigned 
                  : "memory", "m0");
 }
 
-inline int split_ksteps(int64_t d) { return (int)(8 * d + 6 + 15) / 16; }   // 1..9 for d = 1..16
+// Split records (fp32-grade scores on the bf16 matrix cores, d <= kLowdMaxD): 8 ks words of two bf16 slots.  A coordinate is the sum
+// of three bf16 pieces p0, p1, p2 (split3), and the six products with a resident row's that count (streamed x resident, words of
+// consecutive slots; p1 p2 and p2 p1 are below 2^-25 of a product),
+//     (p0, p1) x (p1, p0)   (p1, p0) x (p1, p2)      words 2 k, 2 k + 1
+//     (p2, .) x (p0, .)                              word 2 d + k / 2, two coordinates each
+//     (p0, .) x (p0, .)                              word split_lead(ks, d) + k / 2
+// come before the bias (three pieces and a one for the running max: the last two words, see split_bias_words).  In this order
+// the sums are small until the last k-step or two, where the leading products meet the bias and what is left of both is small
+// again: the matrix cores round (and where they align a product, truncate) at the size of the sum so far.  Errors of half-steps and
+// short solves against 64 bits (n = 3001, m = 2500; normal and cube, d = 1 .. 16): 0.2 to 1.05 times, mostly 0.6 to 0.8 times,
+// those of eight products a coordinate in order
+// with the bias behind them; with the bias before them they were 1.0 to 2.6 times those.
+// Measured (both half-steps of an averaged iteration, n = m = 20011, d = 10): 8 d + 6 slots 157 us, 6 d + 4 131.  Three fp16
+// pieces, whose products carry more digits, took 140 us and a common scale of the coordinates; two of them 125 us, at 1.1 to 1.8 times
+// the errors.
+__host__ __device__ inline int split_pairs(int64_t d) { return (int)(d + 1) / 2; }
+inline int split_ksteps(int64_t d) { return (int)(2 * d + 2 * split_pairs(d) + 2 + 7) / 8; }   // 1..7 for d = 1..16
+__host__ __device__ inline int split_lead(int ks, int64_t d) { return 8 * ks - 2 - split_pairs(d); }
+// The records of odd groups of 32 points are stored negated, so their scores come out of the matrix cores negated: the cores truncate
+// towards minus infinity where they align a product, which pulls the scores of even groups down and of odd ones up.
+__host__ __device__ inline bool split_negated(int64_t point) { return point >> 5 & 1; }
 // Position (in 16-byte units) of piece `piece` of the record of point `point`: records lie in groups of 32 points, piece by
 // piece, so that the lanes that read (from LDS or memory) or write one piece of consecutive points touch consecutive units.
 // Point by point, a wave's LDS reads met in 2 (odd ks) to 16 (ks = 8) ways on a bank: six averaged iterations and the

@@ -186,13 +186,13 @@ __global__ __launch_bounds__(kBlock) void k_lse_lowd(const S *__restrict__ res, 
 // On the vector ALU the d FMAs of a score cost as much as its exp2.  The fp32 matrix instructions
 // do not help: measured, their time adds to the vector ALU's (a K = 4 fp32 MFMA variant of this
 // pass gained 10 %).  The bf16 ones are 16 times faster and take only ~13 cycles of vector issue
-// each.  With the operands split into three bf16 pieces (see split_ksteps), KS = (8 d + 6)/16
+// each.  With the operands split into three bf16 pieces (see split_ksteps), KS = (6 d + 4)/16
 // rounded up MFMA 32x32x16 per 32 x 32 pairs (two for d = 3) deliver score - max at fp32 accuracy,
 // and the vector ALU is left with one exp2 and one add per pair.
 // A = 32 streamed points (lane l: point l%32, slots 8(l/32)..+7 of the K-step), B = 32 resident
 // rows, so a lane's 16 result registers are 16 streamed points of ONE resident row (l%32); the two
 // lane halves of a row are merged once at the end.  The running max sits in the operand B itself
-// (three slots against ones in A), so the lazy stabiliser costs nothing in the common path: when a
+// (one slot against a one in A, three in the precise records), so the lazy stabiliser costs nothing in the common path: when a
 // chunk sum leaves [0, 2^60), the wave zeroes those slots, recomputes the chunk's raw scores,
 // lifts the integer max, writes it back into B and takes the chunk's sums again.
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
@@ -230,46 +230,85 @@ struct SplitArgs {
     const unsigned char *vimg;   // PC == 8: value images of the streamed tiles (see k_vimg_lowd)
 };
 
-// the B operands of resident row `row` (pieces 2 ks + lh, the max slots left at zero)
-template <int KS, bool PRECISE>
-__device__ __forceinline__ void resident_operand(const SplitArgs &a, const int64_t row, const int lh, bf8 (&b)[KS])
+// where a resident row's operand holds minus its running max: slots 3..5 of the precise record's second piece, the last slot of the
+// other record
+template <bool PRECISE> __device__ __forceinline__ void put_max(bf8 &b, const float neg_m)
+{
+    if constexpr (PRECISE) {
+        __bf16 q[3];
+        split3(neg_m, q);
+        b[3] = q[0];
+        b[4] = q[1];
+        b[5] = q[2];
+    } else
+        b[7] = (__bf16)neg_m;
+}
+// the running max for scores up to mx: an integer at or above it that its slots hold exactly
+template <bool PRECISE> __device__ __forceinline__ float lifted_max(const float mx)
+{
+    const float m = ceilf(mx);
+    if constexpr (PRECISE) return m;
+    return fabsf(m) > 256.0f && m > kNegInit ? (float)(__bf16)(m + fabsf(m) * 0x1p-7f) : m;
+}
+
+// What coordinates 2 q and 2 q + 1 of resident row `row` give of its operand in the fp32 variant (see split_ksteps; q = 0: and the
+// factors of the bias, and the words without content), as row lj of a group of 32 rows in `rec`, laid out like records
+template <int KS> __device__ __forceinline__ void resident_words(const SplitArgs &a, const int64_t row, const int lj, const int q, uint32_t *rec)
 {
     const int d = a.d;
-    const __bf16 one = (__bf16)1.0f, zero = (__bf16)0.0f;
-    const double inv_gx = PRECISE ? 1.0 / a.gx : 0.0;   // (gx is a power of two: the products below are exact quotients)
-    if constexpr (!PRECISE) {
-        const float *px = static_cast<const float *>(a.res) + row * a.dp;
-        const float cscale = (float)a.cscale;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const int c = 2 * ks + lh;
-            __bf16 x[3];
-            split3(c < d ? px[c] * cscale : 0.0f, x);
-            bf8 v = {x[0], x[0], x[1], x[0], x[1], x[2], x[1], x[2]};
-            if (c == d) v = bf8{one, one, one, zero, zero, zero, zero, zero};
-            b[ks] = v;
-        }
-    } else {
-        const double *px = static_cast<const double *>(a.res) + row * a.dp;
-        __bf16 X1[3], rx[3][3];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            const double cx = c < d ? px[c] * a.cscale : 0.0;
-            const double x1 = rint(cx * inv_gx) * a.gx;
-            X1[c] = (__bf16)(float)x1;
-            split3d(cx - x1, rx[c]);
-        }
-        // pieces 0..5 (piece = 2 ks + lh); see split_precise_record for the streamed counterparts
-        const bf8 p0 = {X1[0], X1[1], X1[2], zero, zero, zero, zero, zero};
-        const bf8 p1 = {one, one, one, zero, zero, zero, zero, zero};
-        const bf8 p5 = {one, one, one, zero, zero, rx[0][1], rx[1][1], rx[2][1]};
-        bf8 pc[3];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) pc[c] = bf8{X1[c], X1[c], X1[c], rx[c][0], rx[c][1], rx[c][2], rx[c][0], rx[c][0]};
-        b[0] = lh ? p1 : p0;
-        b[1] = lh ? pc[1] : pc[0];
-        b[2] = lh ? p5 : pc[2];
+    const float *px = static_cast<const float *>(a.res) + row * a.dp + 2 * q;
+    const float cscale = (float)a.cscale;
+    const bool both = 2 * q + 1 < d;
+    auto put = [&](int t, uint32_t v) { rec[4 * ((t >> 2) * 32 + lj) + (t & 3)] = v; };
+    __bf16 x[3], z[3];
+    split3(px[0] * cscale, x);
+    split3(both ? px[1] * cscale : 0.0f, z);
+    put(4 * q, bf16_pair(x[1], x[0]));
+    put(4 * q + 1, bf16_pair(x[1], x[2]));
+    if (both) {
+        put(4 * q + 2, bf16_pair(z[1], z[0]));
+        put(4 * q + 3, bf16_pair(z[1], z[2]));
     }
+    put(2 * d + q, bf16_pair(x[0], z[0]));
+    put(split_lead(KS, d) + q, bf16_pair(x[0], z[0]));
+    if (q == 0) {
+        const __bf16 one = (__bf16)1.0f;
+        for (int t = 2 * d + split_pairs(d); t < split_lead(KS, d); ++t) put(t, 0u);
+        put(8 * KS - 2, bf16_pair(one, one));
+        put(8 * KS - 1, bf16_pair(one, (__bf16)0.0f));
+    }
+}
+// the B operands of the lanes' resident rows from their words
+template <int KS> __device__ __forceinline__ void read_operand(const Unit *rec, const int l, bf8 (&b)[KS])
+{
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) b[ks] = *reinterpret_cast<const bf8 *>(rec + 64 * ks + l);
+}
+// the B operands of resident row `row` of the precise records (pieces 2 ks + lh, the max slots left at zero)
+__device__ __forceinline__ void resident_precise(const SplitArgs &a, const int64_t row, const int lh, bf8 (&b)[3])
+{
+    const int d = a.d;
+    const double *px = static_cast<const double *>(a.res) + row * a.dp;
+    const __bf16 one = (__bf16)1.0f, zero = (__bf16)0.0f;
+    const double inv_gx = 1.0 / a.gx;   // (gx is a power of two: the products below are exact quotients)
+    __bf16 X1[3], rx[3][3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const double cx = c < d ? px[c] * a.cscale : 0.0;
+        const double x1 = rint(cx * inv_gx) * a.gx;
+        X1[c] = (__bf16)(float)x1;
+        split3d(cx - x1, rx[c]);
+    }
+    // pieces 0..5 (piece = 2 ks + lh); see split_precise_record for the streamed counterparts
+    const bf8 p0 = {X1[0], X1[1], X1[2], zero, zero, zero, zero, zero};
+    const bf8 p1 = {one, one, one, zero, zero, zero, zero, zero};
+    const bf8 p5 = {one, one, one, zero, zero, rx[0][1], rx[1][1], rx[2][1]};
+    bf8 pc[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) pc[c] = bf8{X1[c], X1[c], X1[c], rx[c][0], rx[c][1], rx[c][2], rx[c][0], rx[c][0]};
+    b[0] = lh ? p1 : p0;
+    b[1] = lh ? pc[1] : pc[0];
+    b[2] = lh ? p5 : pc[2];
 }
 
 // one workgroup of the pass: row block bx, column split by.
@@ -304,23 +343,20 @@ __device__ __forceinline__ void lse_split_body(const SplitArgs &a, const int bx,
     constexpr int NP = 2 * KS;               // 16-byte pieces per record
     constexpr int UPT = TJ * NP / kBlock;    // pieces each thread moves per tile
     constexpr int NG = TJ / 32;              // groups of 32 streamed points per tile
-    static_assert(TJ * NP % kBlock == 0 && NG % CH == 0, "tile shape");
+    static_assert(TJ * NP % kBlock == 0 && NG % CH == 0 && CH % 2 == 0, "tile shape (a chunk starts at an even group)");
     static_assert(!PRECISE || KS == 3, "the precise record has three K-steps");
     __shared__ Unit tile[2][TJ * NP];
 
     const int tid = threadIdx.x;
     const int w = tid >> 6, l = tid & 63;
     const int lj = l & 31, lh = l >> 5;
-    const int d = a.d;
     const int tiles_per_split = a.tiles_per_split, n_tiles = a.n_tiles;
     double2 *__restrict__ partial = a.partial;
     const int64_t partial_stride = a.partial_stride;
     const uint16_t *__restrict__ str = a.str;
     const int64_t row0 = (int64_t)bx * (128 * R) + w * (32 * R);
-    // the piece with the ones and the max slots: piece d = 2 (KS-1) + (d & 1) in the fp32 record,
-    // piece 1 in the precise one
-    constexpr int MK = PRECISE ? 0 : KS - 1;
-    const bool holds_max = PRECISE ? (lh == 1) : (lh == (d & 1));
+    constexpr int MK = PRECISE ? 0 : KS - 1;   // the k-step with the max slots, in lane half 1
+    const bool holds_max = lh == 1;
 
     bf8 b[R][KS];
     float mrun[R], srun[R], stile[R];
@@ -339,13 +375,7 @@ __device__ __forceinline__ void lse_split_body(const SplitArgs &a, const int bx,
             for (int e = 0; e < 16; ++e) omm[r][e] = 0.0f;
     }
     auto set_max = [&](int r, float neg_m) {   // slots 3..5 of that piece <- pieces of -max
-        __bf16 q[3];
-        split3(neg_m, q);
-        if (holds_max) {
-            b[r][MK][3] = q[0];
-            b[r][MK][4] = q[1];
-            b[r][MK][5] = q[2];
-        }
+        if (holds_max) put_max<PRECISE>(b[r][MK], neg_m);
     };
     const int t_begin = by * tiles_per_split;
     const int t_end = min(n_tiles, t_begin + tiles_per_split);
@@ -395,7 +425,18 @@ __device__ __forceinline__ void lse_split_body(const SplitArgs &a, const int bx,
 
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        resident_operand<KS, PRECISE>(a, row0 + 32 * r + lj, lh, b[r]);
+        if constexpr (PRECISE) {
+            resident_precise(a, row0 + 32 * r + lj, lh, b[r]);
+        } else {
+            // (through the second tile buffer, which is free until the loop: made by each lane for itself, out of the pieces of
+            // up to eight coordinates a k-step, the operands took 10 of the 30 us of a pass over 3000 x 5000 points at d = 12)
+            static_assert(TJ >= 128, "32 rows of each wave in a tile buffer");
+            Unit *mine = tile[1] + w * (32 * NP);
+            asm volatile("" ::: "memory");
+            for (int q = lh; q < split_pairs(a.d); q += 2) resident_words<KS>(a, row0 + 32 * r + lj, lj, q, reinterpret_cast<uint32_t *>(mine));
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            read_operand<KS>(mine, l, b[r]);
+        }
         mrun[r] = kNegInit;
         srun[r] = 0.0f;
         stile[r] = 0.0f;
@@ -457,7 +498,7 @@ __device__ __forceinline__ void lse_split_body(const SplitArgs &a, const int bx,
                 float part = 0.0f;
 #pragma unroll
                 for (int e = e0; e < e1; ++e) {
-                    const float ev = fast_exp2(dd[st & 1][e]);
+                    const float ev = fast_exp2(!PRECISE && (g & 1) ? -dd[st & 1][e] : dd[st & 1][e]);   // (see split_negated)
                     part = e == e0 ? ev : part + ev;
                     if constexpr (APPLY) {
                         // register e of lane half lh is streamed point 8 (e / 4) + 4 lh + e % 4 of group c0 + g
@@ -540,7 +581,7 @@ __device__ __forceinline__ void lse_split_body(const SplitArgs &a, const int bx,
                 __builtin_amdgcn_sched_barrier(0);
                 if (st < NS) {
 #pragma unroll
-                    for (int e = 4 * qd; e < 4 * qd + 4; ++e) ev[e] = fast_exp2(dd[st & 1][e]);
+                    for (int e = 4 * qd; e < 4 * qd + 4; ++e) ev[e] = fast_exp2(!PRECISE && (g & 1) ? -dd[st & 1][e] : dd[st & 1][e]);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -617,13 +658,13 @@ __device__ __forceinline__ void lse_split_body(const SplitArgs &a, const int bx,
 #pragma unroll
                     for (int r = 0; r < R; ++r)
 #pragma unroll
-                        for (int e = 0; e < 16; ++e) mx[r] = fmaxf(mx[r], dd[r][e]);
+                        for (int e = 0; e < 16; ++e) mx[r] = fmaxf(mx[r], !PRECISE && (g & 1) ? -dd[r][e] : dd[r][e]);
                 }
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     // the max of a row sits once in B and serves both lane halves: lift it for both
                     const float mrow = fmaxf(mx[r], __shfl_xor(mx[r], 32));
-                    const float mnew = fmaxf(mrun[r], ceilf(mrow));
+                    const float mnew = fmaxf(mrun[r], lifted_max<PRECISE>(mrow));
                     const float scale = fast_exp2(mrun[r] - mnew);
                     srun[r] *= scale;
                     stile[r] *= scale;
@@ -722,15 +763,19 @@ __device__ __forceinline__ void lse_split_body(const SplitArgs &a, const int bx,
     }
 }
 
+// (From three k-steps on two workgroups per CU at most: the dispatcher fills one CU after the other, and the launch shape counts on two.
+// Where the registers let it put three on a CU, the 630 workgroups of both half-steps at n = 12000, m = 20011, d = 5 took 210 CUs and
+// 93 us instead of 73.  With one or two k-steps the wait for a tile shows more than that: six iterations and the gradient at n = 9000,
+// m = 30000, d = 4 take 810 us with two, 731 with what the registers allow.)
 template <int KS, int R, int TJ, int CH, bool PRECISE>
-__global__ __launch_bounds__(kBlock, 2) void k_lse_lowd_split(SplitArgs a)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, KS <= 2 ? 8 : 2))) void k_lse_lowd_split(SplitArgs a)
 {
     lse_split_body<KS, R, TJ, CH, PRECISE>(a, blockIdx.x, blockIdx.y);
 }
 
-// plan application on the split records (PC value columns per launch)
+// plan application on the split records (PC value columns per launch; workgroups per CU as above)
 template <int KS, int R, int TJ, int CH, bool PRECISE, int PC, int PCU>
-__global__ __launch_bounds__(kBlock, 2) void k_apply_lowd_split(SplitArgs a)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, KS <= 2 ? 8 : 2))) void k_apply_lowd_split(SplitArgs a)
 {
     lse_split_body<KS, R, TJ, CH, PRECISE, PC, PCU>(a, blockIdx.x, blockIdx.y);
 }
@@ -739,7 +784,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_apply_lowd_split(SplitArgs a)
 // same old potentials, so the row blocks of the f-pass (a0) and of the g-pass (a1) share a grid;
 // grid.y covers the larger of the two split counts.
 template <int KS, int R, int TJ, int CH, bool PRECISE>
-__global__ __launch_bounds__(kBlock, 2) void k_lse_lowd_split_pair(SplitArgs a0, SplitArgs a1)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, KS <= 2 ? 8 : 2))) void k_lse_lowd_split_pair(SplitArgs a0, SplitArgs a1)
 {
     const bool second = (int)blockIdx.x >= a0.row_blocks;   // uniform over the workgroup
     const SplitArgs &a = second ? a1 : a0;
@@ -760,28 +805,27 @@ __global__ __launch_bounds__(64 * kSmallWaves) void k_half_lowd_small(SplitArgs 
     __shared__ double ss[kSmallWaves][32];
     const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, lj = l & 31, lh = l >> 5;
     const int64_t row0 = (int64_t)blockIdx.x * 32;
-    constexpr int MK = PRECISE ? 0 : KS - 1;   // the piece with the max slots (as in lse_split_body)
-    const bool holds_max = PRECISE ? (lh == 1) : (lh == (a.d & 1));
+    const bool holds_max = lh == 1;
     bf8 b[KS];
     auto set_max = [&](float neg_m) {
-        __bf16 q[3];
-        split3(neg_m, q);
-        if (holds_max) {
-            b[MK][3] = q[0];
-            b[MK][4] = q[1];
-            b[MK][5] = q[2];
-        }
+        if (holds_max) put_max<PRECISE>(b[PRECISE ? 0 : KS - 1], neg_m);
     };
     const Unit *str = reinterpret_cast<const Unit *>(a.str);
     auto load_a = [&](int g, bf8 (&av)[KS]) {
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) av[ks] = *reinterpret_cast<const bf8 *>(str + (int64_t)g * (64 * KS) + 64 * ks + l);   // (see split_unit)
     };
+    static_assert(kSmallWaves % 2 == 0, "a wave's groups are all even or all odd");
+    const float sign = w & 1 ? -1.0f : 1.0f;
     auto scores = [&](const bf8 (&av)[KS], f16v &dd) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) dd[e] = 0.0f;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) dd = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[ks], b[ks], dd, 0, 0, 0);
+        if constexpr (!PRECISE) {   // (a wave's groups are all even or all odd, see split_negated)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) dd[e] *= sign;
+        }
     };
     auto sums = [&](const f16v &dd) {
         float s0 = 0.0f, s1 = 0.0f;
@@ -794,7 +838,15 @@ __global__ __launch_bounds__(64 * kSmallWaves) void k_half_lowd_small(SplitArgs 
     };
     bf8 av[KS];
     if (w < n_groups) load_a(w, av);
-    resident_operand<KS, PRECISE>(a, row0 + lj, lh, b);
+    if constexpr (PRECISE) {
+        resident_precise(a, row0 + lj, lh, b);
+    } else {
+        __shared__ Unit rec[64 * KS];
+        static_assert(2 * kSmallWaves >= (kLowdMaxD + 1) / 2, "a thread for each pair of coordinates of 32 rows");
+        if ((tid >> 5) < split_pairs(a.d)) resident_words<KS>(a, row0 + lj, lj, tid >> 5, reinterpret_cast<uint32_t *>(rec));
+        __syncthreads();
+        read_operand<KS>(rec, l, b);
+    }
     float m = kNegInit;
     double s = 0.0;
     set_max(-kNegInit);
@@ -813,7 +865,7 @@ __global__ __launch_bounds__(64 * kSmallWaves) void k_half_lowd_small(SplitArgs 
 #pragma unroll
             for (int e = 0; e < 16; ++e) mx = fmaxf(mx, dd[e]);
             mx = fmaxf(mx, __shfl_xor(mx, 32));
-            const float mnew = fmaxf(m, ceilf(mx));
+            const float mnew = fmaxf(m, lifted_max<PRECISE>(mx));
             s *= (double)fast_exp2(m - mnew);
             m = mnew;
             set_max(-mnew);
@@ -1121,7 +1173,7 @@ static bool split_pass_args(Ctx *c, const Prepared *P, const Side *res, const Si
     // host-side shape checks: every access of the kernel stays inside the padded copies
     if ((int64_t)s.row_blocks * s.rows_per_block > res->cnt_pad || (int64_t)n_tiles * kSplitTJ > str->cnt_pad ||
         (size_t)s.splits * res->cnt_pad * 16 > P->partial_bytes || (!precise && P->ks != split_ksteps(P->d)) ||
-        (!precise && (P->ks < 1 || P->ks > 9))) {
+        (!precise && (P->ks < 1 || P->ks > 7))) {
         *st = fail(c, FS_ERR_DEVICE, "internal: low-d launch shape exceeds the padded buffers");
         return false;
     }
@@ -1162,9 +1214,7 @@ void launch_lse_split_pair(dim3 grid, hipStream_t st, const SplitArgs &a0, const
     case 4: { constexpr int KS_ = 4; CALL; } break;                                                          \
     case 5: { constexpr int KS_ = 5; CALL; } break;                                                          \
     case 6: { constexpr int KS_ = 6; CALL; } break;                                                          \
-    case 7: { constexpr int KS_ = 7; CALL; } break;                                                          \
-    case 8: { constexpr int KS_ = 8; CALL; } break;                                                          \
-    default: { constexpr int KS_ = 9; CALL; } break;                                                         \
+    default: { constexpr int KS_ = 7; CALL; } break;                                                         \
     }
 
 fs_status lowd_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, Splits *splits_out)
@@ -1344,8 +1394,7 @@ size_t lowd_apply_ws(const Ctx *c, int64_t n_res, int64_t n_str, int64_t d, int6
 
 // Matrix-core application on the split records: eight value columns per pass.  Two blocks of 32 resident rows per
 // wave while the records are short; one block for KS > 4, where two would not leave registers for the operands.
-// (One block per wave and three workgroups per CU instead of two, which the registers allow for KS <= 4, measured
-// 4-6 % slower at d = 2..4 and 15 % slower at d = 6.)
+// (One block per wave and three workgroups per CU instead of two measured 4-6 % slower at d = 2..4.)
 template <int KS>
 void launch_apply_split(dim3 grid, hipStream_t st, const SplitArgs &a, bool two_pieces)
 {
@@ -1356,22 +1405,15 @@ void launch_apply_split(dim3 grid, hipStream_t st, const SplitArgs &a, bool two_
         hipLaunchKernelGGL((k_apply_lowd_split<KS, (KS <= 4 ? kSplitR : 1), kSplitTJ, kSplitCH, false, kApplyMM, kApplyMM>), grid,
                            dim3(kBlock), 0, st, a);
 }
-// The form with the products on the vector ALU (four columns per pass) is kept where it measured faster
-// (n = m = 65536): a single column on short records, where a kernel copy multiplies one column only
-// (d = 3: 0.71 against 0.89 ms), and up to four columns at d = 16, where the matrix-core form runs one
-// workgroup per CU (1.8 against 2.2 ms).  Everywhere else the matrix-core form wins: 0.92 against 1.06 ms
+// The form with the products on the vector ALU (one column) is kept where it measured faster (n = m = 65536): a single
+// column on short records (d = 3: 0.71 against 0.89 ms).  Everywhere else the matrix-core form wins: 0.92 against 1.06 ms
 // for three columns at d = 3, 0.97 against 2.02 ms for eight.
-static bool apply_on_valu(int ks, bool precise, int64_t p) { return (p == 1 && (precise || ks <= 3)) || (!precise && ks == 9 && p <= 4); }
+static bool apply_on_valu(int ks, bool precise, int64_t p) { return p == 1 && (precise || ks <= 3); }
 template <int KS>
-void launch_apply_split_valu(dim3 grid, hipStream_t st, const SplitArgs &a, int cols)
+void launch_apply_split_valu(dim3 grid, hipStream_t st, const SplitArgs &a)
 {
-    if constexpr (KS <= 3) {
-        if (cols == 1) {
-            hipLaunchKernelGGL((k_apply_lowd_split<KS, kSplitR, kSplitTJ, kSplitCH, false, kApplyPC, 1>), grid, dim3(kBlock), 0, st, a);
-            return;
-        }
-    }
-    hipLaunchKernelGGL((k_apply_lowd_split<KS, kSplitR, kSplitTJ, kSplitCH, false, kApplyPC, kApplyPC>), grid, dim3(kBlock), 0, st, a);
+    if constexpr (KS <= 3)
+        hipLaunchKernelGGL((k_apply_lowd_split<KS, kSplitR, kSplitTJ, kSplitCH, false, kApplyPC, 1>), grid, dim3(kBlock), 0, st, a);
 }
 
 fs_status lowd_apply(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, const float *V,
@@ -1409,21 +1451,18 @@ fs_status lowd_apply(Ctx *c, const Prepared *P, const Side *res, const Side *str
             a.opart = opart;
             a.vimg = vimg;
             const dim3 grid((unsigned)a.row_blocks, (unsigned)a.splits);
-            for (int p0 = 0; valu && p0 < p; p0 += kApplyPC) {
-                a.p0 = p0;
-                const int cols = (int)(p - p0 < kApplyPC ? p - p0 : kApplyPC);
+            if (valu) {
+                a.p0 = 0;
                 if (precise) {
                     hipLaunchKernelGGL((k_apply_lowd_split<3, kSplitR, kSplitTJ, kSplitCH, true, kApplyPC, 1>), grid, dim3(kBlock), 0,
                                        c->stream, a);
                 } else {
-                    FS_SPLIT_KS_DISPATCH(P->ks, (launch_apply_split_valu<KS_>(grid, c->stream, a, cols)));
+                    FS_SPLIT_KS_DISPATCH(P->ks, (launch_apply_split_valu<KS_>(grid, c->stream, a)));
                 }
                 FS_HIP(c, hipGetLastError());
-                st = launch_apply_finalize(c, P, res, precise ? res->norm : res->norm_f, a.splits, eps, opart, kApplyPC, p0,
-                                           (int)p, out, ldo, mass_out);
-                if (st != FS_OK) return st;
+                return launch_apply_finalize(c, P, res, precise ? res->norm : res->norm_f, a.splits, eps, opart, kApplyPC, 0, (int)p, out, ldo,
+                                             mass_out);
             }
-            if (valu) return FS_OK;
             // up to eight columns: values in three bf16 pieces (exact); more: passes of fifteen columns with two pieces
             const bool two = p > kApplyMM;
             const int step = two ? kApplyMM2 : kApplyMM, width = two ? 16 : kApplyMM;

@@ -206,19 +206,26 @@ __global__ __launch_bounds__(256) void k_prep_lowd(PrepLowdSide s0, PrepLowdSide
     }
     norm_f[i] = nf;
     norm[i] = nd;
-    if (split) {   // streamed-role split record of the float copy
-        uint4 *rec = reinterpret_cast<uint4 *>(split);
-        for (int k = 0; k < 2 * ks; ++k) {
-            uint4 u = make_uint4(0, 0, 0, 0);
-            if (k < d) {
-                __bf16 y[3];
-                split3(o[k], y);
-                u = make_uint4(bf16_pair(y[0], y[1]), bf16_pair(y[0], y[2]), bf16_pair(y[1], y[0]), bf16_pair(y[2], y[1]));
-            } else if (k == d) {
-                u = split_bias_piece(-INFINITY);
+    if (split) {   // streamed-role split record of the float copy (see split_ksteps)
+        auto put = [&](int t, uint32_t v) { reinterpret_cast<uint32_t *>(split)[4 * split_unit(ks, i, t >> 2) + (t & 3)] = v; };
+        const uint32_t sign = split_negated(i) ? 0x80008000u : 0u;
+        for (int q = 0; q < split_pairs(d); ++q) {
+            __bf16 y[3], z[3];
+            split3(o[2 * q], y);
+            split3(2 * q + 1 < d ? o[2 * q + 1] : 0.0f, z);
+            put(4 * q, bf16_pair(y[0], y[1]) ^ sign);
+            put(4 * q + 1, bf16_pair(y[1], y[0]) ^ sign);
+            if (2 * q + 1 < d) {
+                put(4 * q + 2, bf16_pair(z[0], z[1]) ^ sign);
+                put(4 * q + 3, bf16_pair(z[1], z[0]) ^ sign);
             }
-            rec[split_unit(ks, i, k)] = u;
+            put(2 * d + q, bf16_pair(y[2], z[2]) ^ sign);
+            put(split_lead(ks, d) + q, bf16_pair(y[0], z[0]) ^ sign);
         }
+        for (int t = 2 * d + split_pairs(d); t < split_lead(ks, d); ++t) put(t, 0u);
+        const uint2 none = split_bias_words(-INFINITY, split_negated(i));
+        put(8 * ks - 2, none.x);
+        put(8 * ks - 1, none.y);
     }
     // largest squared norm after centring, over both clouds: non-negative doubles order like their
     // bit patterns, and a maximum does not depend on the order of the atomics

@@ -603,3 +603,27 @@ def test_half_steps_in_one_launch(oracle, n, m, d, score):
     for k, ref in ((1, fo), (2, go)):   # twelve half-steps, each adding at most its own error
         assert np.abs(out[0][k] - out[1][k]).max() <= 12 * tol
         assert np.abs(out[0][k] - ref).max() <= 12 * tol
+
+
+@pytest.mark.parametrize("n,m,d", [(33, 65, 1), (97, 130, 2), (300, 257, 7), (1000, 77, 10), (64, 500, 13), (2000, 6000, 16)])
+def test_records_do_not_depend_on_the_scale_of_the_points(ctx, oracle, n, m, d):
+    """The records of d <= 16 hold coordinates in pieces of their own exponents: points times 2^k at eps times 4^k give the same
+    potentials times 4^k, bit for bit, and at k = 0 the oracle's (fp32 scores of size Mag <= 480 are off by 2^-24 Mag ln 2 in units
+    of eps where few terms dominate: 2e-5).  Odd and even groups of 32 points, odd and even d."""
+    rng = np.random.default_rng(100 * d + n)
+    x = (rng.standard_normal((n, d)) + 3.0).astype(np.float32)
+    y = (rng.standard_normal((m, d)) * np.logspace(0, -4, d)).astype(np.float32)   # coordinates of very different size
+    a, b = np.full(n, 1.0 / n, np.float32), np.full(m, 1.0 / m, np.float32)
+    eps = 0.5 * d
+    g = (0.1 * rng.standard_normal(m)).astype(np.float32)
+    want = None
+    for k in (0, -31, 29):
+        say("update_f n=%d m=%d d=%d points times 2^%d" % (n, m, d, k))
+        s = np.float32(2.0 ** k)
+        f = host(ctx.fs_update_f(make_problem(x * s, y * s, a, b), eps * 4.0 ** k, dev(g * s * s)))
+        if want is None:
+            want = f
+            exact = oracle.update_f(x, y, b, eps, g)
+            assert np.abs(f - exact).max() <= 2e-5 * eps + 2e-7 * np.abs(exact).max()
+        else:
+            assert np.array_equal(f, want * 4.0 ** k)
