@@ -552,6 +552,8 @@ fs_status fs_destroy(fs_ctx *ctx)
         for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
         if (c->ws) (void)hipFree(c->ws);
         if (c->aux) (void)hipFree(c->aux);
+        if (c->pin) (void)hipHostFree(c->pin);
+        if (c->pin_ready) (void)hipEventDestroy(c->pin_ready);
     }
     delete c;
     return FS_OK;

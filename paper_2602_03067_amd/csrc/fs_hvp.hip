@@ -25,14 +25,17 @@ __device__ inline double block_sum(double v, double *sh)
     return sh[0];
 }
 
-// out_i = <X_i, A_i> (row-wise dot products, App. E notation <X, A>)
-__global__ void k_rowdot(const float *X, int64_t ldx, const float *A, int64_t lda, int64_t rows, int d, float *out)
+// out_i = <X_i, A_i> (row-wise dot products, App. E notation <X, A>); a wave per row (a thread per row took 16.6 us,
+// this takes 3.3, for 8192 rows of 64)
+__global__ __launch_bounds__(256) void k_rowdot(const float *X, int64_t ldx, const float *A, int64_t lda, int64_t rows, int d, float *out)
 {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int l = threadIdx.x & 63;
     if (i >= rows) return;
     double s = 0.0;
-    for (int k = 0; k < d; ++k) s += (double)X[i * ldx + k] * (double)A[i * lda + k];
-    out[i] = (float)s;
+    for (int k = l; k < d; k += 64) s += (double)X[i * ldx + k] * (double)A[i * lda + k];
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+    if (l == 0) out[i] = (float)s;
 }
 
 // cA_i = <A_i, mean> (the share of the common mean in the Hadamard weights)
@@ -56,17 +59,47 @@ __global__ void k_rhs_n(const float *r, const float *u, const float *uP, int64_t
     t1[i] = v / r[i];
 }
 
-// rhs = r2 - P^T (r1 / r),  r2 = 2 (P^T u - <P^T A, Y>);  also x = 0, res = p = rhs (CG start)
-__global__ void k_rhs_m(const float *Ptu, const float *rd, const float *Ptt1, int64_t m, float *rhs, float *x, float *res,
-                        float *pdir)
+// block-wide part of a dot product: this thread's term v, the block's sum to part[blockIdx.x]
+__device__ inline void dot_part(double v, double *part)
 {
-    int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= m) return;
-    const float v = 2.0f * (Ptu[j] - rd[j]) - Ptt1[j];
-    rhs[j] = v;
-    x[j] = 0.0f;
-    res[j] = v;
-    pdir[j] = v;
+    __shared__ double sh[256];
+    const double t = block_sum(v, sh);
+    if (threadIdx.x == 0) part[blockIdx.x] = t;
+}
+// the dot product from its parts, in a fixed order, for every thread of the block
+__device__ inline double dot_sum(const double *part, int64_t cnt)
+{
+    __shared__ double sh[256];
+    double acc = 0.0;
+    for (int64_t i = threadIdx.x; i < cnt; i += 256) acc += part[i];
+    const double t = block_sum(acc, sh);
+    __syncthreads();
+    return t;
+}
+
+// rhs = r2 - P^T (r1 / r),  r2 = 2 (P^T u - <P^T A, Y>);  also x = 0, res = p = rhs (CG start), and the parts of <res, res>
+__global__ __launch_bounds__(256) void k_rhs_m(const float *Ptu, const float *rd, const float *Ptt1, int64_t m, float *rhs, float *x,
+                                               float *res, float *pdir, double *part)
+{
+    const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    float v = 0.0f;
+    if (j < m) {
+        v = 2.0f * (Ptu[j] - rd[j]) - Ptt1[j];
+        rhs[j] = v;
+        x[j] = 0.0f;
+        res[j] = v;
+        pdir[j] = v;
+    }
+    dot_part((double)v * (double)v, part);
+}
+// rr[0] = host[1] = <res, res>
+__global__ __launch_bounds__(256) void k_cg_begin(const double *part, int64_t parts, double *rr, double *host)
+{
+    const double t = dot_sum(part, parts);
+    if (threadIdx.x == 0) {
+        rr[0] = t;
+        host[1] = t;
+    }
 }
 
 __global__ void k_div(const float *a, const float *b, int64_t cnt, float *out)
@@ -75,43 +108,55 @@ __global__ void k_div(const float *a, const float *b, int64_t cnt, float *out)
     if (i < cnt) out[i] = a[i] / b[i];
 }
 
-// S_tau p = c p - P^T ((P p) / r) + tau p
-__global__ void k_schur(const float *cm, const float *pdir, const float *Ptq, float tau, int64_t m, float *Sp)
+// The vector part of a step of conjugate gradients in three launches: step lengths are formed on the device, each block for itself
+// from the parts that the launch before has left, and the host only reads them to decide whether to go on (see hvp_run).
+// S_tau p = c p - P^T ((P p) / r) + tau p, and the parts of <p, S_tau p>
+__global__ __launch_bounds__(256) void k_schur(const float *cm, const float *pdir, const float *Ptq, float tau, int64_t m, float *Sp, double *part)
 {
-    int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j < m) Sp[j] = cm[j] * pdir[j] - Ptq[j] + tau * pdir[j];
+    const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    double v = 0.0;
+    if (j < m) {
+        const float sp = cm[j] * pdir[j] - Ptq[j] + tau * pdir[j];
+        Sp[j] = sp;
+        v = (double)pdir[j] * (double)sp;
+    }
+    dot_part(v, part);
 }
-
-__global__ void k_cg_step(float alpha, const float *pdir, const float *Sp, int64_t m, float *x, float *res)
+// x += alpha p, res -= alpha S p with alpha = rr / <p, S p> (not where that is not positive), and the parts of <res, res>
+__global__ __launch_bounds__(256) void k_cg_step(const double *part_pSp, const double *rr, const float *pdir, const float *Sp, int64_t m,
+                                                 float *x, float *res, double *part)
 {
-    int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= m) return;
-    x[j] += alpha * pdir[j];
-    res[j] -= alpha * Sp[j];
+    const double pSp = dot_sum(part_pSp, gridDim.x);
+    const float alpha = pSp > 0.0 ? (float)(*rr / pSp) : 0.0f;
+    const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    double v = 0.0;
+    if (j < m) {
+        float r = res[j];
+        if (pSp > 0.0) {
+            x[j] += alpha * pdir[j];
+            r -= alpha * Sp[j];
+            res[j] = r;
+        }
+        v = (double)r * (double)r;
+    }
+    dot_part(v, part);
 }
-
-__global__ void k_cg_dir(float beta, const float *res, int64_t m, float *pdir)
+// p = res + (rr_new / rr) p; rr_new to *rr_next, and with <p, S p> of the step to the host
+__global__ __launch_bounds__(256) void k_cg_dir(const double *part_pSp, const double *part_rr, const double *rr, const float *res, int64_t m,
+                                                float *pdir, double *rr_next, double *host)
 {
-    int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const double rr_new = dot_sum(part_rr, gridDim.x);
+    const float beta = (float)(rr_new / *rr);
+    const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (j < m) pdir[j] = res[j] + beta * pdir[j];
-}
-
-__global__ __launch_bounds__(256) void k_dot(const float *a, const float *b, int64_t cnt, double *part)
-{
-    __shared__ double sh[256];
-    int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    double v = i < cnt ? (double)a[i] * (double)b[i] : 0.0;
-    double t = block_sum(v, sh);
-    if (threadIdx.x == 0) part[blockIdx.x] = t;
-}
-
-__global__ __launch_bounds__(256) void k_sum(const double *part, int64_t cnt, double *dst)
-{
-    __shared__ double sh[256];
-    double acc = 0.0;
-    for (int64_t i = threadIdx.x; i < cnt; i += 256) acc += part[i];
-    double t = block_sum(acc, sh);
-    if (threadIdx.x == 0) *dst = t;
+    if (blockIdx.x == 0) {
+        const double pSp = dot_sum(part_pSp, gridDim.x);
+        if (threadIdx.x == 0) {
+            *rr_next = rr_new;
+            host[0] = pSp;
+            host[1] = rr_new;
+        }
+    }
 }
 
 // w1 = (r1 - P w2) / r
@@ -181,7 +226,7 @@ size_t hvp_scratch_bytes(int64_t n, int64_t m, int64_t d)
 {
     auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
     return 9 * al((size_t)n * 4) + 10 * al((size_t)m * 4) + 3 * al((size_t)n * d * 4) + 2 * al((size_t)m * d * 4) +
-           al((size_t)ceil_div(n > m ? n : m, 256) * 8) + al(64);
+           2 * al((size_t)ceil_div(m, 256) * 8) + al(64);
 }
 
 // Potentials must already be in place (biases of both sides for `eps`).  x, y, A, out: device floats.
@@ -207,8 +252,9 @@ fs_status hvp_run(Ctx *c, Prepared *P, const float *x, int64_t ldx, const float 
     float *PY = (float *)take((size_t)n * d * 4), *PV2 = (float *)take((size_t)n * d * 4),
           *B5c = (float *)take((size_t)n * d * 4);
     float *PtA = (float *)take((size_t)m * d * 4), *V2 = (float *)take((size_t)m * d * 4);
-    double *part = (double *)take((size_t)ceil_div(n > m ? n : m, 256) * 8);
-    double *scal = (double *)take(64);
+    const int64_t parts = ceil_div(m, 256);
+    double *part_pSp = (double *)take((size_t)parts * 8), *part_rr = (double *)take((size_t)parts * 8);
+    double *rr_dev = (double *)take(64);   // [2] <res, res> of a step, by its parity
 
     Side *X = &P->X, *Y = &P->Y;
     fs_status s;
@@ -219,48 +265,48 @@ fs_status hvp_run(Ctx *c, Prepared *P, const float *x, int64_t ldx, const float 
         return lowd ? lowd_apply(c, P, rs, ss, eps, V, p, ldv, o, ldo_, mass, hadA, lda_)
                     : f64_apply(c, P, rs, ss, eps, V, p, ldv, o, ldo_, mass, hadA, lda_);
     };
-    auto dot = [&](const float *a, const float *b, int64_t cnt, double *host) -> fs_status {
-        hipLaunchKernelGGL(k_dot, g256(cnt), dim3(256), 0, st, a, b, cnt, part);
-        hipLaunchKernelGGL(k_sum, dim3(1), dim3(256), 0, st, part, (int64_t)ceil_div(cnt, 256), scal);
-        FS_HIP(c, hipMemcpyAsync(host, scal, 8, hipMemcpyDeviceToHost, st));
-        FS_HIP(c, hipStreamSynchronize(st));
-        return FS_OK;
-    };
+    if (!c->pin) FS_HIP(c, hipHostMalloc((void **)&c->pin, 64, hipHostMallocDefault));
+    if (!c->pin_ready) FS_HIP(c, hipEventCreateWithFlags(&c->pin_ready, hipEventDisableTiming));
 
     // transport-matrix products P Y (with r = P 1) and P^T A (with c = P^T 1); row-wise dots
     if ((s = apply(X, Y, y, d, ldy, PY, d, r)) != FS_OK) return s;
     if ((s = apply(Y, X, A, d, lda, PtA, d, cm)) != FS_OK) return s;
-    hipLaunchKernelGGL(k_rowdot, g256(n), dim3(256), 0, st, x, ldx, A, lda, n, d, u);
-    hipLaunchKernelGGL(k_rowdot, g256(n), dim3(256), 0, st, PY, (int64_t)d, A, lda, n, d, uP);
-    hipLaunchKernelGGL(k_rowdot, g256(m), dim3(256), 0, st, PtA, (int64_t)d, y, ldy, m, d, rd);
+    hipLaunchKernelGGL(k_rowdot, dim3((unsigned)ceil_div(n, 4)), dim3(256), 0, st, x, ldx, A, lda, n, d, u);
+    hipLaunchKernelGGL(k_rowdot, dim3((unsigned)ceil_div(n, 4)), dim3(256), 0, st, PY, (int64_t)d, A, lda, n, d, uP);
+    hipLaunchKernelGGL(k_rowdot, dim3((unsigned)ceil_div(m, 4)), dim3(256), 0, st, PtA, (int64_t)d, y, ldy, m, d, rd);
     hipLaunchKernelGGL(k_rowdot_mean, g256(n), dim3(256), 0, st, A, lda, lowd ? P->mean : (const double *)nullptr, n, d, cA);
     // right-hand sides
     hipLaunchKernelGGL(k_rhs_n, g256(n), dim3(256), 0, st, r, u, uP, n, r1, t1);
     if ((s = apply(Y, X, u, 1, 1, Ptu, 1, nullptr)) != FS_OK) return s;
     if ((s = apply(Y, X, t1, 1, 1, Ptt1, 1, nullptr)) != FS_OK) return s;
-    hipLaunchKernelGGL(k_rhs_m, g256(m), dim3(256), 0, st, Ptu, rd, Ptt1, m, rhs, w2, res, pdir);
+    hipLaunchKernelGGL(k_rhs_m, g256(m), dim3(256), 0, st, Ptu, rd, Ptt1, m, rhs, w2, res, pdir, part_rr);
+    hipLaunchKernelGGL(k_cg_begin, dim3(1), dim3(256), 0, st, part_rr, parts, rr_dev, c->pin);
     FS_HIP(c, hipGetLastError());
 
-    // conjugate gradients on S_tau w2 = rhs
-    double rr = 0.0;
-    if ((s = dot(res, res, m, &rr)) != FS_OK) return s;
-    const double rr0 = rr;
+    // Conjugate gradients on S_tau w2 = rhs.  Before the host waits for the numbers of a step, the product that opens the next one is
+    // launched (into q1, which nothing else reads if that step is not taken), so the GPU does not wait for the host: n = 8192, m = 8000,
+    // d = 64, 14 steps: 3.64 ms with two waits a step and its vectors in eight launches, 2.62 with one and four.
+    FS_HIP(c, hipEventRecord(c->pin_ready, st));
+    double rr0 = 0.0;
     int k = 0;
-    for (; k < max_cg; ++k) {
-        if (!(rr > 0.0) || sqrt(rr) <= eta * sqrt(rr0)) break;
-        if ((s = apply(X, Y, pdir, 1, 1, q1, 1, nullptr)) != FS_OK) return s;
+    for (;; ++k) {
+        if (k < max_cg && (s = apply(X, Y, pdir, 1, 1, q1, 1, nullptr)) != FS_OK) return s;
+        FS_HIP(c, hipEventSynchronize(c->pin_ready));
+        const double pSp = c->pin[0], rr = c->pin[1];
+        if (k == 0)
+            rr0 = rr;
+        else if (!(pSp > 0.0)) {   // the last direction was in the null space (tau = 0): nothing more to gain
+            --k;
+            break;
+        }
+        if (k >= max_cg || !(rr > 0.0) || sqrt(rr) <= eta * sqrt(rr0)) break;
         hipLaunchKernelGGL(k_div, g256(n), dim3(256), 0, st, q1, r, n, q1);
         if ((s = apply(Y, X, q1, 1, 1, Ptq, 1, nullptr)) != FS_OK) return s;
-        hipLaunchKernelGGL(k_schur, g256(m), dim3(256), 0, st, cm, pdir, Ptq, (float)tau, m, Sp);
-        double pSp = 0.0;
-        if ((s = dot(pdir, Sp, m, &pSp)) != FS_OK) return s;
-        if (!(pSp > 0.0)) break;   // direction in the null space (tau = 0): nothing more to gain
-        const double alpha = rr / pSp;
-        hipLaunchKernelGGL(k_cg_step, g256(m), dim3(256), 0, st, (float)alpha, pdir, Sp, m, w2, res);
-        double rr_new = 0.0;
-        if ((s = dot(res, res, m, &rr_new)) != FS_OK) return s;
-        hipLaunchKernelGGL(k_cg_dir, g256(m), dim3(256), 0, st, (float)(rr_new / rr), res, m, pdir);
-        rr = rr_new;
+        hipLaunchKernelGGL(k_schur, g256(m), dim3(256), 0, st, cm, pdir, Ptq, (float)tau, m, Sp, part_pSp);
+        hipLaunchKernelGGL(k_cg_step, g256(m), dim3(256), 0, st, part_pSp, rr_dev + (k & 1), pdir, Sp, m, w2, res, part_rr);
+        hipLaunchKernelGGL(k_cg_dir, g256(m), dim3(256), 0, st, part_pSp, part_rr, rr_dev + (k & 1), res, m, pdir, rr_dev + 1 - (k & 1), c->pin);
+        FS_HIP(c, hipGetLastError());
+        FS_HIP(c, hipEventRecord(c->pin_ready, st));
     }
     if (cg_iters) *cg_iters = k;
 

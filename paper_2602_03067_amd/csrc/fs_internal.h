@@ -212,6 +212,9 @@ struct Ctx {
     // grow-only second buffer for entry points that call other entry points (which lay the workspace out anew)
     char *aux = nullptr;
     size_t aux_bytes = 0;
+    // numbers that a kernel hands to the host (pinned), and when they are there: the conjugate gradients' (made when first used)
+    double *pin = nullptr;
+    hipEvent_t pin_ready = nullptr;
     std::string err;
     // Derived copies kept across entry calls (fs_points_keep): what identifies the clouds the caller has declared
     // unchanged, whether the workspace currently holds their derived copies, and the host-side value that belongs
