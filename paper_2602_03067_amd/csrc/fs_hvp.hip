@@ -26,7 +26,7 @@ __device__ inline double block_sum(double v, double *sh)
 }
 
 // out_i = <X_i, A_i> (row-wise dot products, App. E notation <X, A>); a wave per row (a thread per row took 16.6 us,
-// this takes 3.3, for 8192 rows of 64)
+// this takes 4.6, for 8192 rows of 64)
 __global__ __launch_bounds__(256) void k_rowdot(const float *X, int64_t ldx, const float *A, int64_t lda, int64_t rows, int d, float *out)
 {
     const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);

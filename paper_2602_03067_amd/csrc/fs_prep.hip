@@ -55,7 +55,7 @@ struct CloudIn {
     int64_t rows, ld;
     double *part;
 };
-__global__ __launch_bounds__(256) void k_coord_sums(CloudIn c0, CloudIn c1, int dtype, int d)
+__global__ __launch_bounds__(256) void k_coord_sums(CloudIn c0, CloudIn c1, int dtype, int d, bool bounds)
 {
     const CloudIn &cl = blockIdx.y ? c1 : c0;
     const void *pts = cl.pts;
@@ -77,9 +77,9 @@ __global__ __launch_bounds__(256) void k_coord_sums(CloudIn c0, CloudIn c1, int 
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) acc[k] += __shfl_xor(acc[k], off);
         }
-    // at d <= 3 columns 4 + k and 8 + k hold the largest -v and v of coordinate k
+    // bounds (d <= 3): columns 4 + k and 8 + k hold the largest -v and v of coordinate k
     float down[3] = {-INFINITY, -INFINITY, -INFINITY}, up[3] = {-INFINITY, -INFINITY, -INFINITY};
-    if (d <= 3) {
+    if (bounds) {
         for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < rows; i += (int64_t)gridDim.x * 256)
 #pragma unroll
             for (int k = 0; k < 3; ++k)
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(256) void k_coord_sums(CloudIn c0, CloudIn c1, int 
     if ((threadIdx.x & 63) == 0) {
 #pragma unroll
         for (int k = 0; k < kLowdMaxD; ++k) sh[threadIdx.x >> 6][k] = acc[k];
-        if (d <= 3) {
+        if (bounds) {
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
                 sh[threadIdx.x >> 6][4 + k] = (double)down[k];
@@ -108,7 +108,7 @@ __global__ __launch_bounds__(256) void k_coord_sums(CloudIn c0, CloudIn c1, int 
         }
     }
     __syncthreads();
-    if (d <= 3 && threadIdx.x >= 4 && threadIdx.x < kLowdMaxD) {
+    if (bounds && threadIdx.x >= 4 && threadIdx.x < kLowdMaxD) {
         float b = -INFINITY;
         for (int w = 0; w < 4; ++w) b = max_or_nan(b, (float)sh[w][threadIdx.x]);
         part[(int64_t)blockIdx.x * kLowdMaxD + threadIdx.x] = (double)b;
@@ -118,7 +118,7 @@ __global__ __launch_bounds__(256) void k_coord_sums(CloudIn c0, CloudIn c1, int 
 
 // stage 2: mean[k] = (sum of partX[.][k] + sum of partY[.][k]) / (n + m).  One block of 256: thread
 // (group g, coordinate k) sums the blocks b = g mod 16, then coordinate k's 16 group sums are added
-// in a fixed order.  Also clears zeroed[0..2] (the slots the next kernels take maxima into), and at d <= 3 leaves the bounds
+// in a fixed order.  Also clears zeroed[0..2] (the slots the next kernels take maxima into), and where `bounds` is given (d <= 3) leaves the bounds
 // of the centred clouds as floats in bounds[2 side + 0 (smallest) / 1 (largest)][coordinate] (a NaN where one is).
 __global__ __launch_bounds__(256) void k_mean_final(const double *partX, const double *partY, int blocks, double inv_cnt,
                                                     double *mean, double *zeroed, int d, float *bounds)
@@ -126,7 +126,7 @@ __global__ __launch_bounds__(256) void k_mean_final(const double *partX, const d
     static_assert(kLowdMaxD == 16, "thread mapping below");
     __shared__ double sh[16][kLowdMaxD];
     const int k = threadIdx.x & 15, g = threadIdx.x >> 4;
-    const bool is_bound = d <= 3 && k >= 4;   // (columns 4..6 and 8..10 of the partial sums, see k_coord_sums)
+    const bool is_bound = bounds && k >= 4;   // (columns 4..6 and 8..10 of the partial sums, see k_coord_sums)
     __shared__ float shb[2][16][kLowdMaxD];
     if (is_bound) {
         float b[2] = {-INFINITY, -INFINITY};
@@ -148,7 +148,7 @@ __global__ __launch_bounds__(256) void k_mean_final(const double *partX, const d
         mean[threadIdx.x] = t * inv_cnt;
     }
     __syncthreads();   // (mean is read below)
-    if (d <= 3 && threadIdx.x < 12) {
+    if (bounds && threadIdx.x < 12) {
         const int side = threadIdx.x / 6, top = threadIdx.x / 3 % 2, c = threadIdx.x % 3;
         float b = -INFINITY;
         for (int q = 0; q < 16; ++q) b = max_or_nan(b, shb[side][q][top ? 8 + c : 4 + c]);
@@ -170,20 +170,15 @@ struct PrepLowdSide {
     uint16_t *split;
     double *pts_d, *bias_d;   // d > 3: records of the fp64 matrix-core pass ([cnt_pad][kp] centred coordinates, bias), else null
 };
-__global__ __launch_bounds__(256) void k_prep_lowd(PrepLowdSide s0, PrepLowdSide s1, int dtype, int d, int dp, int dpd, int kp,
-                                                   const double *mean, int ks, unsigned long long *rho_max_bits)
+// point i of a side (i < cnt_pad): its derived copies; returns its squared norm after centring
+__device__ __forceinline__ double prep_lowd_point(const PrepLowdSide &sd, const int64_t i, const int dtype, const int d, const int dp, const int dpd,
+                                                  const int kp, const double *mean, const int ks)
 {
-    const PrepLowdSide &sd = blockIdx.y ? s1 : s0;
-    if ((int64_t)blockIdx.x * 256 >= sd.cnt_pad) return;
     const void *pts = sd.pts;
     const int64_t cnt = sd.cnt, ld = sd.ld;
-    float *packed = sd.packed;
-    double *packed_d = sd.packed_d, *norm_f = sd.norm_f, *norm = sd.norm;
     uint16_t *split = sd.split;
-    __shared__ double shmax[256];
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    float *o = packed + i * dp;
-    double *od = packed_d + i * dpd;
+    float *o = sd.packed + i * dp;
+    double *od = sd.packed_d + i * dpd;
     double nf = 0.0, nd = 0.0;
     for (int k = 0; k < dp; ++k) o[k] = 0.0f;
     for (int k = 0; k < dpd; ++k) od[k] = 0.0;
@@ -204,8 +199,8 @@ __global__ __launch_bounds__(256) void k_prep_lowd(PrepLowdSide s0, PrepLowdSide
         for (int k = 0; k < kp; ++k) op[k] = k < d ? od[k] : 0.0;
         sd.bias_d[i] = -INFINITY;
     }
-    norm_f[i] = nf;
-    norm[i] = nd;
+    sd.norm_f[i] = nf;
+    sd.norm[i] = nd;
     if (split) {   // streamed-role split record of the float copy (see split_ksteps)
         auto put = [&](int t, uint32_t v) { reinterpret_cast<uint32_t *>(split)[4 * split_unit(ks, i, t >> 2) + (t & 3)] = v; };
         const uint32_t sign = split_negated(i) ? 0x80008000u : 0u;
@@ -227,6 +222,15 @@ __global__ __launch_bounds__(256) void k_prep_lowd(PrepLowdSide s0, PrepLowdSide
         put(8 * ks - 2, none.x);
         put(8 * ks - 1, none.y);
     }
+    return nd;
+}
+__global__ __launch_bounds__(256) void k_prep_lowd(PrepLowdSide s0, PrepLowdSide s1, int dtype, int d, int dp, int dpd, int kp,
+                                                   const double *mean, int ks, unsigned long long *rho_max_bits)
+{
+    const PrepLowdSide &sd = blockIdx.y ? s1 : s0;
+    if ((int64_t)blockIdx.x * 256 >= sd.cnt_pad) return;
+    __shared__ double shmax[256];
+    const double nd = prep_lowd_point(sd, (int64_t)blockIdx.x * 256 + threadIdx.x, dtype, d, dp, dpd, kp, mean, ks);
     // largest squared norm after centring, over both clouds: non-negative doubles order like their
     // bit patterns, and a maximum does not depend on the order of the atomics
     shmax[threadIdx.x] = nd;
@@ -246,16 +250,11 @@ __global__ __launch_bounds__(256) void k_prep_lowd(PrepLowdSide s0, PrepLowdSide
 //   5: rb1 rb2 rb3 0 0 ry1_0 ry1_1 ry1_2 bias residual, second-order terms      x  1 1 1 0 0 rx2_0 rx2_1 rx2_2
 // `rho_max`: device scalar (largest squared norm after centring): the grid comes from it
 // (blockIdx.y: 0 = the x cloud, 1 = the y cloud)
-__global__ void k_prep_split_precise(const double *packed_d0, int64_t cnt_pad0, uint16_t *out0, const double *packed_d1,
-                                     int64_t cnt_pad1, uint16_t *out1, int d, int dpd, const double *rho_max)
+__device__ __forceinline__ void prep_precise_point(const double *packed_d, uint16_t *out, const int64_t i, const int d, const int dpd,
+                                                   const double rho_max)
 {
-    const double *packed_d = blockIdx.y ? packed_d1 : packed_d0;
-    const int64_t cnt_pad = blockIdx.y ? cnt_pad1 : cnt_pad0;
-    uint16_t *out = blockIdx.y ? out1 : out0;
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= cnt_pad) return;
     double gx_unused, gy;
-    split_grids(*rho_max, 1.0, &gx_unused, &gy);
+    split_grids(rho_max, 1.0, &gx_unused, &gy);
     __bf16 Y1[3], ry[3][3];
     for (int k = 0; k < 3; ++k) {
         const double y = k < d ? packed_d[i * dpd + k] : 0.0;
@@ -271,6 +270,78 @@ __global__ void k_prep_split_precise(const double *packed_d0, int64_t cnt_pad0, 
         rec[64 + 32 * k] = make_uint4(bf16_pair(ry[k][0], ry[k][1]), bf16_pair(ry[k][2], Y1[k]), bf16_pair(Y1[k], Y1[k]),
                                 bf16_pair(ry[k][0], ry[k][1]));
     rec[160] = make_uint4(0u, 0u, bf16_pair(z, ry[0][0]), bf16_pair(ry[1][0], ry[2][0]));
+}
+__global__ void k_prep_split_precise(const double *packed_d0, int64_t cnt_pad0, uint16_t *out0, const double *packed_d1,
+                                     int64_t cnt_pad1, uint16_t *out1, int d, int dpd, const double *rho_max)
+{
+    const double *packed_d = blockIdx.y ? packed_d1 : packed_d0;
+    const int64_t cnt_pad = blockIdx.y ? cnt_pad1 : cnt_pad0;
+    uint16_t *out = blockIdx.y ? out1 : out0;
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < cnt_pad) prep_precise_point(packed_d, out, i, d, dpd, *rho_max);
+}
+
+constexpr double kSmallPrologue = 12288.0;   // coordinates of both clouds
+// The whole prologue of a small problem in one launch: every workgroup forms the mean and the largest squared norm of both clouds
+// for itself (in the same order, so all get the same bits), then 256 points of its side.  Bound by latency: the four launches
+// (coordinate sums, mean, copies, precise records) take 19 us at n = 1000, m = 777, d = 3, this one 10.6; an f- and a g-half-step call
+// there 93.4 us before, 81.6 now.  The line is where the loads that each workgroup repeats eat that up: both calls at n = 2500, m = 2600,
+// d = 3 (15300 coordinates) 95 and 94 us, at n = m = 4000, d = 4 (32000) 111 and 129.
+__global__ __launch_bounds__(1024) void k_prep_lowd_small(PrepLowdSide s0, PrepLowdSide s1, int dtype, int d, int dp, int dpd, int kp, int ks,
+                                                          uint16_t *precise0, uint16_t *precise1, double *mean_out, double *scalars5)
+{
+    __shared__ double sh[16][kLowdMaxD], mean[kLowdMaxD], shr[16];
+    const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
+    const int64_t n = s0.cnt, all = n + s1.cnt;
+    double acc[kLowdMaxD];
+#pragma unroll
+    for (int k = 0; k < kLowdMaxD; ++k) acc[k] = 0.0;
+    for (int64_t i = tid; i < all; i += 1024) {
+        const PrepLowdSide &c = i < n ? s0 : s1;
+        const int64_t at = (i < n ? i : i - n) * c.ld;
+#pragma unroll
+        for (int k = 0; k < kLowdMaxD; ++k)
+            if (k < d) acc[k] += (double)load_pt(c.pts, dtype, at + k);
+    }
+#pragma unroll
+    for (int k = 0; k < kLowdMaxD; ++k)
+        if (k < d) {
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) acc[k] += __shfl_xor(acc[k], off);
+            if (l == 0) sh[w][k] = acc[k];
+        }
+    __syncthreads();
+    if (tid < kLowdMaxD) {
+        double t = 0.0;
+        if (tid < d)
+            for (int q = 0; q < 16; ++q) t += sh[q][tid];
+        mean[tid] = t / (double)all;
+    }
+    __syncthreads();
+    double rho = 0.0;
+    for (int64_t i = tid; i < all; i += 1024) {
+        const PrepLowdSide &c = i < n ? s0 : s1;
+        const int64_t at = (i < n ? i : i - n) * c.ld;
+        double nd = 0.0;
+        for (int k = 0; k < d; ++k) {
+            const double v = (double)load_pt(c.pts, dtype, at + k) - mean[k];
+            nd += v * v;
+        }
+        rho = fmax(rho, nd);
+    }
+    for (int off = 32; off > 0; off >>= 1) rho = fmax(rho, __shfl_xor(rho, off));
+    if (l == 0) shr[w] = rho;
+    __syncthreads();
+    for (int q = 0; q < 16; ++q) rho = fmax(rho, shr[q]);
+    if (blockIdx.x == 0 && blockIdx.y == 0) {
+        if (tid < kLowdMaxD) mean_out[tid] = mean[tid];
+        if (tid < 3) scalars5[tid] = tid == 2 ? rho : 0.0;
+    }
+    const PrepLowdSide &sd = blockIdx.y ? s1 : s0;
+    const int64_t i = (int64_t)blockIdx.x * 256 + tid;
+    if (tid >= 256 || i >= sd.cnt_pad) return;
+    (void)prep_lowd_point(sd, i, dtype, d, dp, dpd, kp, mean, ks);
+    if (d <= 3) prep_precise_point(sd.packed_d, blockIdx.y ? precise1 : precise0, i, d, dpd, rho);
 }
 
 // ---- float64 derived copy (fp64 matrix-core path) ----------------------------------------
@@ -998,10 +1069,6 @@ fs_status launch_prepare(Ctx *c, const fs_problem *p, Prepared *P)
         double *partX = P->mean + kLowdMaxD;
         double *partY = partX + (size_t)half * kLowdMaxD;
         const CloudIn cx{p->x, p->n, p->ldx, partX}, cy{p->y, p->m, p->ldy, partY};
-        hipLaunchKernelGGL(k_coord_sums, dim3(half, 2), dim3(256), 0, c->stream, cx, cy, dtype, (int)p->d);
-        // (also clears scalars[5..7]: the sizes of the biases and the largest squared norm, all taken by atomic maxima)
-        hipLaunchKernelGGL(k_mean_final, dim3(1), dim3(256), 0, c->stream, partX, partY, half,
-                           1.0 / (double)(p->n + p->m), P->mean, P->scalars + 5, (int)p->d, reinterpret_cast<float *>(P->scalars + 10));
         const int64_t pad_max = P->X.cnt_pad > P->Y.cnt_pad ? P->X.cnt_pad : P->Y.cnt_pad;
         PrepLowdSide sd[2];
         for (int k = 0; k < 2; ++k) {
@@ -1009,6 +1076,19 @@ fs_status launch_prepare(Ctx *c, const fs_problem *p, Prepared *P)
             sd[k] = PrepLowdSide{in[k].pts, S->cnt, S->cnt_pad, in[k].ld, S->packed, S->packed_d, S->norm_f, S->norm, S->split,
                                  S->pts_d,   S->bias_d};
         }
+        if ((double)(p->n + p->m) * (double)p->d <= kSmallPrologue && !P->mom.base) {
+            hipLaunchKernelGGL(k_prep_lowd_small, dim3((unsigned)ceil_div(pad_max, 256), 2), dim3(1024), 0, c->stream, sd[0], sd[1], dtype,
+                               (int)p->d, P->dp, P->dpd, P->kp, P->ks, P->X.split_p, P->Y.split_p, P->mean, P->scalars + 5);
+            P->rho_max = -1.0;
+            FS_HIP(c, hipGetLastError());
+            return FS_OK;
+        }
+        // (bounds of the clouds only where half-steps may run through cell moments)
+        const bool bounds = P->mom.base != nullptr;
+        hipLaunchKernelGGL(k_coord_sums, dim3(half, 2), dim3(256), 0, c->stream, cx, cy, dtype, (int)p->d, bounds);
+        // (also clears scalars[5..7]: the sizes of the biases and the largest squared norm, all taken by atomic maxima)
+        hipLaunchKernelGGL(k_mean_final, dim3(1), dim3(256), 0, c->stream, partX, partY, half,
+                           1.0 / (double)(p->n + p->m), P->mean, P->scalars + 5, (int)p->d, bounds ? reinterpret_cast<float *>(P->scalars + 10) : nullptr);
         hipLaunchKernelGGL(k_prep_lowd, dim3((unsigned)ceil_div(pad_max, 256), 2), dim3(256), 0, c->stream, sd[0], sd[1], dtype,
                            (int)p->d, P->dp, P->dpd, P->kp, P->mean, P->ks, reinterpret_cast<unsigned long long *>(P->scalars + 7));
         // (the host reads rho_max back together with the sizes of the biases, see launch_bias_from_user)
@@ -1069,7 +1149,7 @@ fs_status launch_bias_from_user(Ctx *c, Prepared *P, Side *side, const float *po
         P->rho_max = h[2];
         float b[12];
         memcpy(b, h + 5, sizeof b);
-        for (int s = 0; s < 2 && P->d <= 3; ++s)
+        for (int s = 0; s < 2 && P->mom.base; ++s)
             for (int k = 0; k < 3; ++k) {
                 P->mom.lo[s][k] = (double)b[6 * s + k];
                 P->mom.hi[s][k] = (double)b[6 * s + 3 + k];

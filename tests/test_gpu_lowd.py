@@ -605,7 +605,9 @@ def test_half_steps_in_one_launch(oracle, n, m, d, score):
         assert np.abs(out[0][k] - ref).max() <= 12 * tol
 
 
-@pytest.mark.parametrize("n,m,d", [(33, 65, 1), (97, 130, 2), (300, 257, 7), (1000, 77, 10), (64, 500, 13), (2000, 6000, 16)])
+@pytest.mark.parametrize("n,m,d", [(33, 65, 1), (97, 130, 2), (300, 257, 7), (1000, 77, 10), (64, 500, 13), (2000, 6000, 16),
+                                   # the largest prologue in one launch and the next one in four
+                                   (2048, 2048, 3), (2049, 2048, 3)])
 def test_records_do_not_depend_on_the_scale_of_the_points(ctx, oracle, n, m, d):
     """The records of d <= 16 hold coordinates in pieces of their own exponents: points times 2^k at eps times 4^k give the same
     potentials times 4^k, bit for bit, and at k = 0 the oracle's (fp32 scores of size Mag <= 480 are off by 2^-24 Mag ln 2 in units
