@@ -60,11 +60,11 @@ __device__ inline void split_precise_bias(double bias, double q, uint4 *digits, 
 // bias in base-2 units of a streamed point:  ((pot_shifted)/eps + log w) * log2(e)
 // (Alg. 1: (ghat_j + delta_j)/eps with delta = eps*log b)
 // (returns the float64 bias)
-__device__ inline double store_bias(const BiasSink &s, int64_t i, double pot, double inv_eps, double lw)
+__device__ inline double store_bias(const BiasSink &s, int64_t i, double pot, double inv_eps, double lw, double norm, double norm_f)
 {
-    double b = ((pot - s.norm[i]) * inv_eps + lw) * kLog2e;
+    double b = ((pot - norm) * inv_eps + lw) * kLog2e;
     if (s.packed) {
-        const float bf = (float)(((pot - s.norm_f[i]) * inv_eps + lw) * kLog2e);
+        const float bf = (float)(((pot - norm_f) * inv_eps + lw) * kLog2e);
         s.packed[i * s.dp + s.d] = bf;
         if (s.split) reinterpret_cast<uint2 *>(s.split)[2 * split_unit(s.ks, i, 2 * s.ks - 1) + 1] = split_bias_words(bf, split_negated(i));
     }
@@ -82,6 +82,11 @@ __device__ inline double store_bias(const BiasSink &s, int64_t i, double pot, do
     if (s.bias_f) s.bias_f[i] = (float)b;
     if (s.bias_d) s.bias_d[i] = b;
     return b;
+}
+
+__device__ inline double store_bias(const BiasSink &s, int64_t i, double pot, double inv_eps, double lw)
+{
+    return store_bias(s, i, pot, inv_eps, lw, s.norm[i], s.packed ? s.norm_f[i] : 0.0);
 }
 
 // Bias record of the fixed-point kernels, per tile of 32 points four times 32 integers:
@@ -157,29 +162,46 @@ __device__ inline void gauge_collect_pair(const double *part_x, int64_t cnt_x, c
     __syncthreads();
 }
 
+// What the merge needs of point i besides its statistics.  (Loaded, and its logarithm taken, before the statistics are there: behind
+// them each of these loads was a round trip to memory of its own, see k_finalize.)
+struct PointIn {
+    double res_norm, norm, norm_f, old, wi, lw;
+};
+__device__ __forceinline__ PointIn load_point(const FinalizeArgs &a, const int64_t i)
+{
+    PointIn p{};
+    p.res_norm = a.res_norm[i];
+    if (a.mix != 1.0 || a.dev_part || a.gauge_out || a.save_old) p.old = a.pot[i];
+    if (a.inv_eps_next > 0.0) {
+        p.norm = a.sink.norm[i];
+        if (a.sink.packed) p.norm_f = a.sink.norm_f[i];
+    }
+    if (a.w) {
+        p.wi = (double)a.w[i];
+        if (a.inv_eps_next > 0.0) p.lw = log(p.wi);
+    } else {
+        p.lw = a.log_uniform;
+        if (a.dev_part || a.gauge_out) p.wi = exp(a.log_uniform);
+    }
+    return p;
+}
+
 // the new potential of point i from its merged statistics, and what else is asked for; *dev, *mass and *bias are left
 // alone where they are not
-__device__ __forceinline__ void finalize_point(const FinalizeArgs &a, const int64_t i, const double M, const double S, double *dev,
-                                               double *mass, double *bias)
+__device__ __forceinline__ void finalize_point(const FinalizeArgs &a, const int64_t i, const PointIn &p, const double M, const double S,
+                                               double *dev, double *mass, double *bias)
 {
     // fhat = -eps * LSE (Alg. 1), f = fhat + alpha (Prop. 1)
-    double pot_new = -a.eps * kLn2 * (M + log2(S)) + a.res_norm[i];
+    double pot_new = -a.eps * kLn2 * (M + log2(S)) + p.res_norm;
     const double pot_upd = pot_new;
-    if (a.mix != 1.0) pot_new = (1.0 - a.mix) * a.pot[i] + a.mix * pot_new;   // averaged schedule (Eq. 4-5)
-    if (a.dev_part) {
-        double wi = a.w ? (double)a.w[i] : exp(a.log_uniform);
-        *dev = fabs(wi * exp((a.pot[i] - pot_new) / a.eps) - wi);   // Prop. 3: r = a exp((fhat - fhat+)/eps)
-    }
-    if (a.gauge_out) {
-        // Prop. 3: the plan's column (row) sum, from the UPDATE itself also where the stored potential is an average
-        const double wi = a.w ? (double)a.w[i] : exp(a.log_uniform);
-        *mass = wi > 0.0 ? wi * exp((a.pot[i] - pot_upd) / a.eps) : 0.0;
-    }
+    if (a.mix != 1.0) pot_new = (1.0 - a.mix) * p.old + a.mix * pot_new;   // averaged schedule (Eq. 4-5)
+    if (a.dev_part) *dev = fabs(p.wi * exp((p.old - pot_new) / a.eps) - p.wi);   // Prop. 3: r = a exp((fhat - fhat+)/eps)
+    // Prop. 3: the plan's column (row) sum, from the UPDATE itself also where the stored potential is an average
+    if (a.gauge_out) *mass = p.wi > 0.0 ? p.wi * exp((p.old - pot_upd) / a.eps) : 0.0;
     if (!a.dev_part || a.save_old) {
-        if (a.save_old) a.save_old[i] = a.pot[i];
+        if (a.save_old) a.save_old[i] = p.old;
         a.pot[i] = pot_new;
-        if (a.inv_eps_next > 0.0)
-            *bias = store_bias(a.sink, i, pot_new, a.inv_eps_next, a.w ? log((double)a.w[i]) : a.log_uniform);
+        if (a.inv_eps_next > 0.0) *bias = store_bias(a.sink, i, pot_new, a.inv_eps_next, p.lw, p.norm, p.norm_f);
         if (a.user_out) a.user_out[i] = (float)pot_new;
     }
 }

@@ -436,7 +436,7 @@ struct FinalizeArgs {
     double *save_old;
     int blocks;   // workgroups of this side
     // gauge drift (see GaugeMode): where a g-update leaves the block sums of the plan's column marginals, and what
-    // the first workgroup of the following f-update collects
+    // a workgroup of the following f-update collects
     double *gauge_out;
     const double *gauge_prev;
     int64_t gauge_prev_cnt;
@@ -479,7 +479,7 @@ fs_status launch_bias_from_user(Ctx *c, Prepared *P, Side *side, const float *po
 // iterations, with a scatter around that constant of 8e-6).  So a solve adds up eps ln(mass) over its g-updates
 // (scalars[8]; scalars[9] keeps the sum without the last term) and hands f - scalars[9], g + scalars[8] to the caller.
 //   Measure: this merge is a g-update of an alternating solve: leave the block sums of c_j in gauge_part
-//   Collect: this merge is the f-update after one: its first workgroup adds eps_prev ln(sum gauge_part) to scalars[8]
+//   Collect: this merge is the f-update after one: one of its workgroups adds eps_prev ln(sum gauge_part) to scalars[8]
 //            (gauge_prev_cnt: how many sums that g-update left)
 enum class GaugeMode { None, Measure, Collect };
 fs_status launch_finalize(Ctx *c, const Prepared *P, Side *res, const double *res_norm, Splits splits,
@@ -498,7 +498,7 @@ fs_status launch_gauge_export(Ctx *c, const Prepared *P, int64_t collect_last, d
 // same old potentials, so the plan's mass as the f-pass sees it (row sums) and as the g-pass sees it (column sums)
 // differ by exp((u_f - u_g)/eps) exactly, and an averaged iteration moves t by a quarter of u_f - u_g.  With
 // gauge_parity >= 0 (the iteration number) both merges leave their block sums in half `gauge_parity & 1` of
-// gauge_part_x / gauge_part, and, `collect_prev`, the first workgroup adds the previous iteration's term
+// gauge_part_x / gauge_part, and, `collect_prev`, one workgroup adds the previous iteration's term
 // eps (ln mass_g - ln mass_f) / 4 to scalars[8] and [9] from the other half; the caller hands out f - scalars[9],
 // g + scalars[8] (launch_gauge_collect_pair for the last iteration, then launch_gauge_export with collect_last = false).
 fs_status launch_finalize_pair(Ctx *c, const Prepared *P, Side *X, const double *norm_x, const void *partial_x, Splits splits_x,

@@ -847,6 +847,8 @@ __global__ __launch_bounds__(64 * kSmallWaves) void k_half_lowd_small(SplitArgs 
         __syncthreads();
         read_operand<KS>(rec, l, b);
     }
+    PointIn pt{};   // (of the rows that wave 0 merges)
+    if (w == 0 && lh == 0 && row0 + lj < fz.cnt) pt = load_point(fz, row0 + lj);
     float m = kNegInit;
     double s = 0.0;
     set_max(-kNegInit);
@@ -903,7 +905,7 @@ __global__ __launch_bounds__(64 * kSmallWaves) void k_half_lowd_small(SplitArgs 
         double S = 0.0, dev = 0.0, bias = 0.0;
 #pragma unroll
         for (int k = 0; k < kSmallWaves; ++k) S += rescale_split(ss[k][lj], (double)sm[k][lj], M);
-        finalize_point(fz, i, M, S, &dev, &mass, &bias);
+        finalize_point(fz, i, pt, M, S, &dev, &mass, &bias);
     }
     if (fz.gauge_out) {
         for (int off = 16; off > 0; off >>= 1) mass += __shfl_xor(mass, off);
