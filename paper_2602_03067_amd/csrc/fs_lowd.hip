@@ -1407,15 +1407,17 @@ void launch_apply_split(dim3 grid, hipStream_t st, const SplitArgs &a, bool two_
         hipLaunchKernelGGL((k_apply_lowd_split<KS, (KS <= 4 ? kSplitR : 1), kSplitTJ, kSplitCH, false, kApplyMM, kApplyMM>), grid,
                            dim3(kBlock), 0, st, a);
 }
-// The form with the products on the vector ALU (one column) is kept where it measured faster (n = m = 65536): a single
-// column on short records (d = 3: 0.71 against 0.89 ms).  Everywhere else the matrix-core form wins: 0.92 against 1.06 ms
-// for three columns at d = 3, 0.97 against 2.02 ms for eight.
-static bool apply_on_valu(int ks, bool precise, int64_t p) { return p == 1 && (precise || ks <= 3); }
+// The form with the products on the vector ALU is kept for a single column on short records, where it measured faster
+// (n = m = 65536, d = 3: 0.71 against 0.89 ms), and for up to four columns at d = 16, where the matrix-core form takes 2.85 ms
+// instead of 2.81 for both directions at n = 60000, m = 65000, at four times the error (it keeps exponentials to 2^-17).  Elsewhere the matrix-core form: 0.92 against 1.06 ms for three columns at d = 3, 0.97 against 2.02 ms for eight.
+static bool apply_on_valu(int ks, bool precise, int64_t p) { return (p == 1 && (precise || ks <= 3)) || (!precise && ks == 7 && p <= 4); }
 template <int KS>
 void launch_apply_split_valu(dim3 grid, hipStream_t st, const SplitArgs &a)
 {
     if constexpr (KS <= 3)
         hipLaunchKernelGGL((k_apply_lowd_split<KS, kSplitR, kSplitTJ, kSplitCH, false, kApplyPC, 1>), grid, dim3(kBlock), 0, st, a);
+    if constexpr (KS == 7)
+        hipLaunchKernelGGL((k_apply_lowd_split<KS, kSplitR, kSplitTJ, kSplitCH, false, kApplyPC, kApplyPC>), grid, dim3(kBlock), 0, st, a);
 }
 
 fs_status lowd_apply(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, const float *V,
