@@ -374,6 +374,7 @@ __global__ __launch_bounds__(512, 2) void k_mom_gather(GatherArgs a)
     __shared__ __attribute__((aligned(1024))) unsigned char frag[2][kStage];
     __shared__ __attribute__((aligned(16))) float tab[kTabRows * ST];
     __shared__ double wmax[8];
+    __shared__ float vmax[8];
     const int tid = threadIdx.x, l = tid & 63, lh = l >> 5, lj = l & 31;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int4 blk = a.block[blockIdx.x];
@@ -392,17 +393,33 @@ __global__ __launch_bounds__(512, 2) void k_mom_gather(GatherArgs a)
             xb[z] = a.xi[blk.y + tid + 512 * z];
             ub[z] = a.bias[j * a.bstride];
             if (col) vb[z] = a.V[j * a.ldv + col - 1];
-        }
-        vb[z] *= sign;
+        } else if (col)
+            vb[z] = 0.0f;
     }
+    // Values are of any size and weights close to the end of the fp16 range: a power of two that takes the block's largest value
+    // below 1 comes out of them (vexp).
     double top = fmax(ub[0], ub[1]);
-    for (int off = 32; off > 0; off >>= 1) top = fmax(top, __shfl_xor(top, off));
-    if (l == 0) wmax[w] = top;
+    float vtop = fmaxf(fabsf(vb[0]), fabsf(vb[1]));
+    for (int off = 32; off > 0; off >>= 1) {
+        top = fmax(top, __shfl_xor(top, off));
+        vtop = fmaxf(vtop, __shfl_xor(vtop, off));
+    }
+    if (l == 0) {
+        wmax[w] = top;
+        vmax[w] = vtop;
+    }
     __syncthreads();
     top = wmax[0];
+    vtop = vmax[0];
 #pragma unroll
-    for (int k = 1; k < 8; ++k) top = fmax(top, wmax[k]);
+    for (int k = 1; k < 8; ++k) {
+        top = fmax(top, wmax[k]);
+        vtop = fmaxf(vtop, vmax[k]);
+    }
     top = ceil(top);
+    const int vexp = col && vtop > 0.0f ? ilogbf(vtop) + 1 : 0;
+#pragma unroll
+    for (int z = 0; z < 2; ++z) vb[z] = sign * ldexpf(vb[z], -vexp);
 
     const int xt = a.halves ? (int)blockIdx.y * 4 + (w & 3) : (int)blockIdx.y * 8 + w;
     const int cell = xt * 32 + lj;
@@ -555,11 +572,13 @@ __global__ __launch_bounds__(512, 2) void k_mom_gather(GatherArgs a)
     }
     if (cell < a.ncells) {
         // the moments are at most the weights' sum: stored as 2^(power of two above it) times two fp16 pieces
+        // (A mass of 1 has values of 2^-7 of the block's largest where the weights are.  From 2^-60 down what there is of it is
+        // nothing beside the rounding of the others, and its scale would leave the range of a float.)
         float up = 0.0f, ex = -INFINITY;
-        if (mass > 0.0f) {
+        if (mass > 0x1p-60f) {
             const int sc = ilogbf(mass) + 1;
             up = ldexpf(sign, kMomShift - sc);
-            ex = (float)top + off + (float)(sc - kMomShift - kCoefShift);
+            ex = (float)top + off + (float)(sc - kMomShift - kCoefShift + vexp);
         }
         if (mass != mass) ex = up = NAN;
         const int64_t at = ((int64_t)col * a.ncells + cell) * a.nblock + blockIdx.x;
@@ -666,7 +685,7 @@ __global__ __launch_bounds__(512, 2) void k_mom_rows(RowArgs a)
     __shared__ int fb[kSeg];
     __shared__ __attribute__((aligned(16))) uint32_t bas[RP];
     __shared__ __attribute__((aligned(16))) float cf[RP];
-    __shared__ double wbest[8];
+    __shared__ double wbest[8], wcol[8];
     __shared__ int warg[8], wnan[8];
     const int tid = threadIdx.x, l = tid & 63, lh = l >> 5, lj = l & 31;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -706,12 +725,14 @@ __global__ __launch_bounds__(512, 2) void k_mom_rows(RowArgs a)
     }
     if (tid < kMomRows)
         fill_powers<ST>(tab, tid, tid < grp.z ? a.xi[grp.y + tid] : make_float4(0.0f, 0.0f, 0.0f, 0.0f), a.d);
-    // the streamed cell that counts most for this cell of rows: its size is the sums' scale, its centre their origin
-    double best = -INFINITY;
+    // the streamed cell that counts most for this cell of rows: its size is the sums' scale, its centre their origin.  The sums of a
+    // column of values have a scale of their own, that of their largest cell (col).
+    double best = -INFINITY, col = -INFINITY;
     int arg = 0, nan = 0;
     for (int k = tid; k < a.ncell; k += 512) {
-        const double t = centre_dot(a.scentre[k]) + (double)ex0[a.first_block[k]];
+        const double cd = centre_dot(a.scentre[k]), t = cd + (double)ex0[a.first_block[k]];
         nan |= t != t;
+        if (blockIdx.z) col = fmax(col, cd + (double)ex[a.first_block[k]]);
         if (t > best) {
             best = t;
             arg = k;
@@ -721,6 +742,7 @@ __global__ __launch_bounds__(512, 2) void k_mom_rows(RowArgs a)
         const double ob = __shfl_xor(best, off);
         const int oa = __shfl_xor(arg, off);
         nan |= __shfl_xor(nan, off);
+        col = fmax(col, __shfl_xor(col, off));
         if (ob > best || (ob == best && oa < arg)) {
             best = ob;
             arg = oa;
@@ -730,12 +752,14 @@ __global__ __launch_bounds__(512, 2) void k_mom_rows(RowArgs a)
         wbest[w] = best;
         warg[w] = arg;
         wnan[w] = nan;
+        wcol[w] = col;
     }
     __syncthreads();
     nan = 0;
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
         nan |= wnan[k];
+        col = fmax(col, wcol[k]);
         if (wbest[k] > best || (wbest[k] == best && warg[k] < arg)) {
             best = wbest[k];
             arg = warg[k];
@@ -752,7 +776,7 @@ __global__ __launch_bounds__(512, 2) void k_mom_rows(RowArgs a)
         }
         return;
     }
-    const double m = ceil(best);
+    const double m = ceil(best), mc = blockIdx.z ? (col > -INFINITY ? ceil(col) : 0.0) : m;
     const double4 yr = a.scentre[arg];
     auto segment = [&](int s0) __attribute__((always_inline)) {
         for (int i = tid; i < min(kSeg, round_up_32(a.ncell - s0)); i += 512) {
@@ -761,7 +785,7 @@ __global__ __launch_bounds__(512, 2) void k_mom_rows(RowArgs a)
             const int b = a.first_block[k];
             fb[i] = b;
             pair[i] = make_float4((float)(y.x - yr.x), (float)(y.y - yr.y), (float)(y.z - yr.z),
-                                  s0 + i < a.ncell ? (float)(centre_dot(y) + (double)ex[b] - m) : -INFINITY);
+                                  s0 + i < a.ncell ? (float)(centre_dot(y) + (double)ex[b] - mc) : -INFINITY);
         }
     };
     segment(0);
@@ -848,7 +872,7 @@ __global__ __launch_bounds__(512, 2) void k_mom_rows(RowArgs a)
         const int64_t i = a.perm[grp.y + 32 * w + lj];
         sum *= exp2(row - fl);
         if (blockIdx.z)
-            a.opart[i * a.p + blockIdx.z - 1] = (float)sum;   // (against the maximum that column 0 leaves)
+            a.opart[i * a.p + blockIdx.z - 1] = (float)(sum * exp2(mc - m));   // (against the maximum that column 0 leaves)
         else
             a.partial[i] = make_double2(m + fl, sum);
     }

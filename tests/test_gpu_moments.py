@@ -212,3 +212,96 @@ def test_large_clouds_take_moments_by_themselves():
     s = ((g.double() - (ys * ys).sum(1)) / eps)[None, :] + 2.0 / eps * xs @ ys.t()
     want = (xs * xs).sum(1) - eps * (torch.logsumexp(s, 1) - np.log(m))
     assert float((out[0][rows].double() - want).abs().max()) / eps <= TOL + float(want.abs().max()) * 2.0 ** -24 / eps
+
+
+def _gradient_error(ctx, oracle, x, y, a, b, eps, f, g, mode, wrt_y):
+    """Largest error of a gradient against the oracle, in units of the sums of |entries| times the largest |coordinate|."""
+    z, o, w = (y, x, b) if wrt_y else (x, y, a)
+    apply = oracle.apply_plan_T if wrt_y else oracle.apply_plan
+    T = apply(x, y, a, b, eps, f, g, o)
+    ones = apply(x, y, a, b, eps, f, g, np.ones((len(o), 1), np.float32))
+    want = 2 * (w[:, None] * z - T) if mode == 0 else 2 * (ones * z - T) if mode == 1 else z - T / w[:, None]
+    got = host((ctx.fs_grad_y if wrt_y else ctx.fs_grad_x)(make_problem(x, y, a, b), eps, dev(f), dev(g), mode))
+    assert np.isfinite(got).all()
+    # (the weighted row itself is a term of the difference)
+    scale = (np.abs(ones) + (w[:, None] if mode != 1 else 0)) * max(np.abs(o).max(), np.abs(z).max()) * (2.0 if mode < 2 else 1.0 / w[:, None])
+    return float(np.max(np.abs(got - want) / scale))
+
+
+@pytest.mark.parametrize("shift", [(10.0, -10.0, 3.0), (300.0, 300.0, 300.0), (1000.0, -1000.0, 0.0), (1.0e4, 1.0, -1.0e4)])
+@pytest.mark.parametrize("mode", [0, 1, 2])
+@pytest.mark.parametrize("rough", [False, True])
+def test_gradients_away_from_the_origin(ctx, oracle, shift, mode, rough):
+    """The values of a gradient's application are coordinates of any size, of one sign or both; rough potentials spread the weights of
+    a block over e^(+-24).  2 TOL as in test_gradients, and the float result's own 2^-24."""
+    rng = np.random.default_rng(21)
+    n, m, eps = 900, 1100, float(np.float32(0.1))
+    x = (_cloud(rng, "cube", n, 3) + np.array(shift)).astype(np.float32)
+    y = (_cloud(rng, "clusters", m, 3) + np.array(shift)).astype(np.float32)
+    a, b = _weights(rng, n), _weights(rng, m)
+    f, g = oracle.solve(x, y, a, b, eps, eps, 1, 5)
+    if rough:
+        f, g = f + 8.0 * eps * rng.standard_normal(n), g + 8.0 * eps * rng.standard_normal(m)
+    f, g = f.astype(np.float32), g.astype(np.float32)
+    say("moments gradient shifted by %s mode=%d rough=%d" % (shift, mode, rough))
+    for wrt_y in (False, True):
+        assert _gradient_error(ctx, oracle, x, y, a, b, eps, f, g, mode, wrt_y) <= 2 * TOL + 2.0 ** -23
+
+
+@pytest.mark.parametrize("d", [1, 2, 3])
+def test_gradients_do_not_depend_on_the_scale_of_the_points(ctx, oracle, d):
+    """Points times 2^k at eps times 4^k: the same gradient times 2^k, bit for bit (every scale on the way is a power of two)."""
+    rng = np.random.default_rng(d)
+    n, m, eps = 700, 800, 0.1
+    x, y = _cloud(rng, "cube", n, d) - np.float32(0.5), _cloud(rng, "clusters", m, d) - np.float32(0.4)
+    a, b = _weights(rng, n), _weights(rng, m)
+    eps = float(np.float32(eps))
+    f, g = oracle.solve(x, y, a, b, eps, eps, 1, 5)
+    f, g = f.astype(np.float32), g.astype(np.float32)
+    want = None
+    for k in (0, -31, -20, 10, 20):
+        s = np.float32(2.0 ** k)
+        say("moments gradient d=%d points times 2^%d" % (d, k))
+        got = host(ctx.fs_grad_x(make_problem(x * s, y * s, a, b), eps * 4.0 ** k, dev(f * s * s), dev(g * s * s), 2))
+        if want is None:
+            want = got
+            assert _gradient_error(ctx, oracle, x, y, a, b, eps, f, g, 2, False) <= 2 * TOL
+        else:
+            assert np.array_equal(got, want * 2.0 ** k)
+
+
+def test_gradients_with_values_only_where_there_is_no_weight(ctx):
+    """Points at the origin that hold the weight, and others of the same cell with 2^-128 of it: what these add is nothing."""
+    n, m, eps = 300, 256, float(np.float32(0.1))
+    x = np.linspace(0.0, 0.02, n, dtype=np.float32).reshape(n, 1).copy()
+    y = np.zeros((m, 1), np.float32)
+    y[::4, 0] = np.linspace(0.005, 0.01, m // 4, dtype=np.float32)
+    g = np.where(y[:, 0] > 0, -128.0 * np.log(2.0) * eps, 0.0).astype(np.float32)
+    prob = make_problem(x, y, None, None)
+    f = ctx.fs_update_f(prob, eps, dev(g))
+    say("moments gradient, values without weight")
+    got = host(ctx.fs_grad_x(prob, eps, f, dev(g), 2))
+    assert np.max(np.abs(got - x)) <= 2.0 ** -30
+
+
+def test_large_gradients_away_from_the_origin_take_moments_by_themselves():
+    """At a size where the library chooses: the same gradient as over the pairs, whose application keeps exponentials to 2^-17, in
+    units of the coordinates' size."""
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(4)
+    n, m, eps = 70001, 60007, float(np.float32(0.1))
+    x = torch.rand(n, 3, generator=gen, device="cuda:0") + 1000.0
+    y = torch.rand(m, 3, generator=gen, device="cuda:0") * 0.9 + 1000.0
+    prob = binding.Problem(x, y, None, None)
+    out = []
+    for mode in (0, 2):
+        c = binding.Context(0)
+        c.fs_debug_set("lowd_moments", mode)
+        say("moments gradient by themselves, mode %d" % mode)
+        f, g = torch.zeros(n, device="cuda:0"), torch.zeros(m, device="cuda:0")
+        c.fs_solve(prob, eps, eps, 1, 3, f, g)
+        out.append(c.fs_grad_x(prob, eps, f, g, 2))
+        torch.cuda.synchronize()
+        c.close()
+    assert bool(torch.isfinite(out[0]).all()) and not torch.equal(out[0], out[1])
+    assert float((out[0] - out[1]).abs().max()) <= 1001.0 * 2.0 ** -17
