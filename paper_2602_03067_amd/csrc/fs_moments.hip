@@ -1044,6 +1044,11 @@ fs_status mom_ready(Ctx *c, const Prepared *P, double eps, bool *use)
     if (!S.base || S.off || c->dbg_lowd_moments == 2) return FS_OK;
     // (the other low-d switches ask for kernels over the pairs)
     if (c->dbg_lowd_moments == 0 && (c->dbg_lowd_score || c->dbg_lowd_splits || c->dbg_lowd_precise_valu)) return FS_OK;
+    // Moments stand for passes over the pairs with fp32 scores.  Where float64-grade ones are asked for they are not accurate enough:
+    // after 50 iterations at n = 3000, m = 2500 in the unit cube at eps = 0.005 f and g are off by 4e-7 eps and, over the pairs, by
+    // 2e-7 and 7e-8 (d = 3), after 1000 at d = 1 by 3.5e-6 and 5e-8.  (The switch that forces moments does so for solves and
+    // gradients of any size, measurements are never taken through them.)
+    if (P->force_precise || (c->dbg_lowd_moments == 0 && lowd_precise(P, eps))) return FS_OK;
     if (S.eps == eps) {
         *use = S.on;
         return FS_OK;

@@ -305,3 +305,42 @@ def test_large_gradients_away_from_the_origin_take_moments_by_themselves():
         c.close()
     assert bool(torch.isfinite(out[0]).all()) and not torch.equal(out[0], out[1])
     assert float((out[0] - out[1]).abs().max()) <= 1001.0 * 2.0 ** -17
+
+
+def test_float64_grade_scores_stay_over_the_pairs():
+    """Measurements (marginal error, dual value), small eps and many iterations ask for float64-grade scores; moments, which a few
+    iterations of the same problem take, do not stand in for those: the results are those of the passes over the pairs, bit for bit."""
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(6)
+    n, m, eps = 50021, 40013, float(np.float32(0.05))
+    x, y = torch.rand(n, 3, generator=gen, device="cuda:0"), torch.rand(m, 3, generator=gen, device="cuda:0")
+    x[0], y[0] = 0.0, 1.0     # |x|^2 = 0.75 after centring in both corners: scores of 2 log2(e) / 0.05 * 0.75 = 43
+    prob = binding.Problem(x, y, None, None)
+    zero = torch.zeros(n, device="cuda:0"), torch.zeros(m, device="cuda:0")
+
+    def both(what, call):
+        out = []
+        for mode in (0, 2):
+            c = binding.Context(0)
+            c.fs_debug_set("lowd_moments", mode)
+            say("moments mode %d: %s" % (mode, what))
+            out.append([float(v) if not torch.is_tensor(v) else v.clone() for v in call(c)])
+            torch.cuda.synchronize()
+            c.close()
+        return all(torch.equal(u, v) if torch.is_tensor(u) else u == v for u, v in zip(*out)), out[0]
+
+    def solve(c, iters):
+        f, g = zero[0].clone(), zero[1].clone()
+        c.fs_solve(prob, eps, eps, 1, iters, f, g)
+        return f, g
+
+    same, (f, g) = both("five iterations", lambda c: solve(c, 5))
+    assert not same
+    assert both("marginal errors", lambda c: c.fs_marginal_err(prob, eps, f, g))[0]
+    assert both("dual value", lambda c: [c.fs_ot_value(prob, eps, f, g)])[0]
+    # 140 half-steps at scores of 43 ask for float64-grade ones (Mag T > 5000), and so do scores beyond 480
+    assert both("seventy iterations", lambda c: solve(c, 70))[0]
+    small = float(np.float32(0.004))
+    assert both("half-step at small eps", lambda c: [c.fs_update_f(prob, small, g)])[0]
+    # potentials are given up to a constant, and a large one is a large score
+    assert both("large potentials", lambda c: [c.fs_update_f(prob, eps, g + 300.0)])[0]
