@@ -218,7 +218,7 @@ size_t layout_with(const Ctx *c, const fs_problem *p, Prepared *P, char *base, s
     P->gauge_part = base ? (double *)(base + o) : nullptr;
     o = A.take((size_t)ceil_div(big, 256) * 16);
     P->gauge_part_x = base ? (double *)(base + o) : nullptr;
-    o = A.take(16 * 8);
+    o = A.take(kScalars * 8);
     P->scalars = base ? (double *)(base + o) : nullptr;
     o = A.take((size_t)(256 + 1) * 16 * 8);
     P->mean = base ? (double *)(base + o) : nullptr;

@@ -354,6 +354,7 @@ struct MomState {
     std::vector<int> host;
 };
 
+constexpr int kScalars = 32, kScalarBounds = 16;   // Prepared::scalars
 struct Prepared {
     Path path = Path::LowD;
     int64_t d = 0;
@@ -379,7 +380,7 @@ struct Prepared {
     double *dev_part = nullptr;  // [ceil(max(n,m)/256)] per-block sums of the marginal deviation
     double *gauge_part = nullptr;   // [2][ceil(max(n,m)/256)] per-block sums of the plan's mass seen by a g-update
     double *gauge_part_x = nullptr; // the same for an f-update (averaged schedule: both passes measure, halves by parity)
-    double *scalars = nullptr;   // [16] device doubles (marginal errors, centring sums...; [8], [9]: gauge drift, see GaugeMode; [10], [11]: FxGate::r2 and the origin of the digits; LowD: [10..15] bounds of the centred clouds, see k_mean_final)
+    double *scalars = nullptr;   // [kScalars] device doubles (marginal errors, centring sums...; [8], [9]: gauge drift, see GaugeMode; [10], [11]: FxGate::r2 and the origin of the digits; from kScalarBounds on: bounds of the centred clouds, see k_mean_final)
     double *mean = nullptr;      // [kLowdMaxD] common mean (LowD)
     char *extra = nullptr;       // entry-point specific scratch (plan application partials)
     size_t extra_bytes = 0;

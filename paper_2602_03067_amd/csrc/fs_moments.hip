@@ -926,7 +926,7 @@ bool geometry(const MomState &S, int d, double eps, double tau, MomGeom (&g)[2],
         for (int k = 0; k < 3; ++k) {
             double ext = k < d ? S.hi[side][k] - S.lo[side][k] : 0.0;
             const double mid = k < d ? 0.5 * (S.hi[side][k] + S.lo[side][k]) : 0.0;
-            ext *= 1.0 + 1e-6;   // (the bounds are rounded to floats)
+            ext *= 1.0 + 1e-6;   // (points on the bounds fall inside, whatever the corner and the edges round to)
             const bool cut = k < d && S.hi[0][k] > S.lo[0][k] && S.hi[1][k] > S.lo[1][k];
             const double n = cut ? ceil(ext / h) : 1.0;
             cells *= n;

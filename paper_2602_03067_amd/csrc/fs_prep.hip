@@ -2,8 +2,6 @@
 // clouds and their squared norms (Prop. 1: alpha, beta), the per-point bias
 // (Alg. 1, "precompute bias"), and the merge of the per-split LSE statistics into
 // the new shifted potential.
-#include <string.h>
-
 #include "fs_finalize.h"
 #include "fs_internal.h"
 
@@ -119,9 +117,11 @@ __global__ __launch_bounds__(256) void k_coord_sums(CloudIn c0, CloudIn c1, int 
 // stage 2: mean[k] = (sum of partX[.][k] + sum of partY[.][k]) / (n + m).  One block of 256: thread
 // (group g, coordinate k) sums the blocks b = g mod 16, then coordinate k's 16 group sums are added
 // in a fixed order.  Also clears zeroed[0..2] (the slots the next kernels take maxima into), and where `bounds` is given (d <= 3) leaves the bounds
-// of the centred clouds as floats in bounds[2 side + 0 (smallest) / 1 (largest)][coordinate] (a NaN where one is).
+// of the centred clouds in bounds[2 side + 0 (smallest) / 1 (largest)][coordinate] (a NaN where one is): the largest and the
+// smallest of the centred coordinates to the last bit, since the same subtraction makes those (rounded to floats, a cloud narrower
+// than the last place of its distance from the mean was one point).
 __global__ __launch_bounds__(256) void k_mean_final(const double *partX, const double *partY, int blocks, double inv_cnt,
-                                                    double *mean, double *zeroed, int d, float *bounds)
+                                                    double *mean, double *zeroed, int d, double *bounds)
 {
     static_assert(kLowdMaxD == 16, "thread mapping below");
     __shared__ double sh[16][kLowdMaxD];
@@ -153,7 +153,7 @@ __global__ __launch_bounds__(256) void k_mean_final(const double *partX, const d
         float b = -INFINITY;
         for (int q = 0; q < 16; ++q) b = max_or_nan(b, shb[side][q][top ? 8 + c : 4 + c]);
         // (column 4 + c holds the largest -v)
-        bounds[(2 * side + top) * 3 + c] = c < d ? (float)((top ? (double)b : -(double)b) - mean[c]) : 0.0f;
+        bounds[(2 * side + top) * 3 + c] = c < d ? (top ? (double)b : -(double)b) - mean[c] : 0.0;
     }
     if (threadIdx.x < 3) zeroed[threadIdx.x] = 0.0;
 }
@@ -1103,7 +1103,7 @@ fs_status launch_prepare(Ctx *c, const fs_problem *p, Prepared *P)
         hipLaunchKernelGGL(k_coord_sums, dim3(half, 2), dim3(256), 0, c->stream, cx, cy, dtype, (int)p->d, bounds);
         // (also clears scalars[5..7]: the sizes of the biases and the largest squared norm, all taken by atomic maxima)
         hipLaunchKernelGGL(k_mean_final, dim3(1), dim3(256), 0, c->stream, partX, partY, half,
-                           1.0 / (double)(p->n + p->m), P->mean, P->scalars + 5, (int)p->d, bounds ? reinterpret_cast<float *>(P->scalars + 10) : nullptr);
+                           1.0 / (double)(p->n + p->m), P->mean, P->scalars + 5, (int)p->d, bounds ? P->scalars + kScalarBounds : nullptr);
         hipLaunchKernelGGL(k_prep_lowd, dim3((unsigned)ceil_div(pad_max, 256), 2), dim3(256), 0, c->stream, sd[0], sd[1], dtype,
                            (int)p->d, P->dp, P->dpd, P->kp, P->mean, P->ks, reinterpret_cast<unsigned long long *>(P->scalars + 7));
         // (the host reads rho_max back together with the sizes of the biases, see launch_bias_from_user)
@@ -1156,18 +1156,17 @@ fs_status launch_bias_from_user(Ctx *c, Prepared *P, Side *side, const float *po
                        absmax);
     FS_HIP(c, hipGetLastError());
     if (absmax && last) {
-        double h[11] = {};   // |log w| part, potential part, rho_max; [5..]: bounds of the clouds, see k_mean_final
-        FS_HIP(c, hipMemcpyAsync(h, P->scalars + 5, sizeof h, hipMemcpyDeviceToHost, c->stream));
+        double h[kScalarBounds - 5 + 12] = {};   // |log w| part, potential part, rho_max; at the end bounds of the clouds, see k_mean_final
+        FS_HIP(c, hipMemcpyAsync(h, P->scalars + 5, P->mom.base ? sizeof h : 3 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
         FS_HIP(c, hipStreamSynchronize(c->stream));
         if (h[0] > P->logw_mag) P->logw_mag = h[0];
         if (h[1] * eps > P->pot_mag_eps) P->pot_mag_eps = h[1] * eps;
         P->rho_max = h[2];
-        float b[12];
-        memcpy(b, h + 5, sizeof b);
+        const double *b = h + kScalarBounds - 5;
         for (int s = 0; s < 2 && P->mom.base; ++s)
             for (int k = 0; k < 3; ++k) {
-                P->mom.lo[s][k] = (double)b[6 * s + k];
-                P->mom.hi[s][k] = (double)b[6 * s + 3 + k];
+                P->mom.lo[s][k] = b[6 * s + k];
+                P->mom.hi[s][k] = b[6 * s + 3 + k];
             }
         if (c->kept_valid) c->kept_rho_max = h[2];   // belongs to the kept derived copies (no-op when they are another problem's)
     }

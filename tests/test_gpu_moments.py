@@ -344,3 +344,17 @@ def test_float64_grade_scores_stay_over_the_pairs():
     assert both("half-step at small eps", lambda c: [c.fs_update_f(prob, small, g)])[0]
     # potentials are given up to a constant, and a large one is a large score
     assert both("large potentials", lambda c: [c.fs_update_f(prob, eps, g + 300.0)])[0]
+
+
+def test_cloud_narrower_than_a_float_at_its_distance(ctx, oracle):
+    """Points 2e-9 apart at a distance of 0.5 from the common mean, where floats are 3e-8 apart: their potentials differ by 4e-4 eps."""
+    rng = np.random.default_rng(8)
+    n, m, eps = 300, 280, float(np.float32(1e-5))
+    x = (2e-9 * rng.random((n, 1))).astype(np.float32)
+    y = (1.0 + 5e-4 * rng.random((m, 1))).astype(np.float32)
+    a, b = _weights(rng, n), _weights(rng, m)
+    g = (y[:, 0].astype(np.float64) ** 2).astype(np.float32)   # (takes the cost out: f is of the size of eps)
+    say("moments narrow cloud")
+    got, want = host(ctx.fs_update_f(make_problem(x, y, a, b), eps, dev(g))), oracle.update_f(x, y, b, eps, g)
+    assert np.ptp(want) >= 1e-4 * eps
+    assert max_err_over_eps(got, want, eps) <= _tol(want, eps)
