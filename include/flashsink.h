@@ -371,6 +371,7 @@ fs_status fs_points_release(fs_ctx *ctx);
  *   "lowd_precise_any_bias"  1: those matrix-core records also for biases beyond their digit range
  *   "lowd_moments"       d <= 3: 1: half-steps and gradients through cell moments wherever the clouds allow it, 2: never
  *   "fx_any_size"        1: fixed-point scores (16 < d <= 128, FS_COMPUTE_FP32) for problems of any size
+ *   "ws_limit"           the workspace gets at most this many bytes (0: what the device has), as if there were no more
  *   "fx_splits"          number of splits of the streamed side of a fixed-point pass, 0..1024
  * Unknown keys and values out of range: FS_ERR_INVALID_ARG.  key: HOST string.
  */

@@ -222,10 +222,11 @@ size_t layout_with(const Ctx *c, const fs_problem *p, Prepared *P, char *base, s
     P->scalars = base ? (double *)(base + o) : nullptr;
     o = A.take((size_t)(256 + 1) * 16 * 8);
     P->mean = base ? (double *)(base + o) : nullptr;
-    const bool moments = P->path == Path::LowD && mom_size(c, p->n, p->m, p->d);
-    P->mom.bytes = moments ? mom_bytes(p->n, p->m) : 0;
+    // (behind everything that is kept between entry calls: only some of them have it)
+    P->mom.bytes = P->path == Path::LowD && P->mom.wanted && mom_size(c, p->n, p->m, p->d) ? mom_bytes(p->n, p->m) : 0;
+    if (P->mom.bytes >= c->mom_denied) P->mom.bytes = 0;
     o = A.take(P->mom.bytes);
-    P->mom.base = base && moments ? base + o : nullptr;
+    P->mom.base = base && P->mom.bytes ? base + o : nullptr;
     o = A.take(extra);
     (void)o;
     return A.off;
@@ -250,13 +251,14 @@ fs_status ensure_ws(Ctx *c, size_t need)
     if (need <= c->ws_bytes) return FS_OK;
     if (c->ws_static) return fail(c, FS_ERR_BAD_SHAPE, "the problem needs %zu bytes of workspace, the static scratch holds %zu", need, c->ws_bytes);
     FS_HIP(c, hipStreamSynchronize(c->stream));
+    c->kept_valid = false;   // (a new allocation may have the address of the old one)
     if (c->ws) {
         FS_HIP(c, hipFree(c->ws));
         c->ws = nullptr;
         c->ws_bytes = 0;
     }
     void *pnew = nullptr;
-    hipError_t e = hipMalloc(&pnew, need);
+    hipError_t e = c->dbg_ws_limit && need > c->dbg_ws_limit ? hipErrorOutOfMemory : hipMalloc(&pnew, need);
     if (e != hipSuccess) {
         (void)hipGetLastError();   // (reported here, not by the check after the next launch)
         return fail(c, FS_ERR_ALLOC, "workspace of %zu bytes: %s", need, hipGetErrorString(e));
@@ -273,6 +275,12 @@ fs_status prepare(Ctx *c, const fs_problem *p, Prepared *P, size_t extra, char *
     if (c->device < 0) return fail(c, FS_ERR_DEVICE, "host-only context: arguments are valid, nothing was launched");
     size_t need = layout(c, p, P, nullptr, extra);
     fs_status st = ensure_ws(c, need);
+    if (st == FS_ERR_ALLOC && P->mom.bytes) {   // the passes over the pairs need less (and later calls on clouds as large don't ask)
+        c->mom_denied = P->mom.bytes;
+        c->err.clear();
+        need = layout(c, p, P, nullptr, extra);
+        st = ensure_ws(c, need);
+    }
     if (st != FS_OK) return st;
     layout(c, p, P, c->ws, extra);
     P->dbg_score = c->dbg_lowd_score;
@@ -289,7 +297,7 @@ fs_status prepare(Ctx *c, const fs_problem *p, Prepared *P, size_t extra, char *
     Ctx::PointsKey declared = key;
     key.ws = c->ws;
     key.partial_budget = c->partial_budget;
-    if (c->keep_on && c->kept_valid && key.same(c->kept_key)) {
+    if (c->keep_on && c->kept_valid && key.same(c->kept_key) && (c->kept_bounds || !P->mom.base)) {
         P->rho_max = c->kept_rho_max;
         return FS_OK;
     }
@@ -298,6 +306,7 @@ fs_status prepare(Ctx *c, const fs_problem *p, Prepared *P, size_t extra, char *
     // (not in the static scratch array: other contexts on this GPU write there too)
     if (st2 == FS_OK && c->keep_on && !c->ws_static && declared.same(c->keep_key)) {
         c->kept_key = key;
+        c->kept_bounds = P->mom.base != nullptr;
         c->kept_rho_max = -1.0;   // (low-d path: set when the host reads it back, see launch_bias_from_user)
         c->kept_valid = true;
     }
@@ -437,6 +446,7 @@ fs_status grad_common(Ctx *c, const fs_problem *prob, float eps, const float *f,
     const size_t mass_bytes = ((size_t)rows * 4 + 255) & ~size_t(255);
     const size_t tail_bytes = mass_bytes + (convert ? (size_t)orows * d * 4 : 0);
     Prepared P;
+    P.mom.wanted = true;
     char *tail = nullptr;
     if ((st = apply_begin(c, prob, eps, f, g, d, wrt_y, tail_bytes, &P, &tail)) != FS_OK) return st;
     float *mass = reinterpret_cast<float *>(tail);
@@ -448,7 +458,6 @@ fs_status grad_common(Ctx *c, const fs_problem *prob, float eps, const float *f,
         V = vf;
         ldv = d;
     }
-    P.mom.values_finite = true;   // (mom_ready looks at the bounds of both clouds)
     if ((st = apply_run(c, &P, eps, wrt_y, V, d, ldv, grad, ldg, mode == 1 ? mass : nullptr)) != FS_OK) return st;
     return launch_grad_assemble(c, grad, ldg, wrt_y ? prob->y : prob->x, prob->dtype, wrt_y ? prob->ldy : prob->ldx, rows, d,
                                 wrt_y ? prob->b : prob->a, mass, mode);
@@ -588,6 +597,7 @@ fs_status fs_update_f(fs_ctx *ctx, const fs_problem *prob, float eps, const floa
     if (overlap(f_out, (size_t)prob->n * 4, g, (size_t)prob->m * 4))
         return fail(c, FS_ERR_INVALID_ARG, "f_out overlaps g");
     Prepared P;
+    P.mom.wanted = true;
     if ((st = prepare(c, prob, &P, 0, nullptr)) != FS_OK) return st;
     if ((st = launch_bias_from_user(c, &P, &P.Y, g, eps)) != FS_OK) return st;
     int64_t none = 0;
@@ -606,6 +616,7 @@ fs_status fs_update_g(fs_ctx *ctx, const fs_problem *prob, float eps, const floa
     if (overlap(g_out, (size_t)prob->m * 4, f, (size_t)prob->n * 4))
         return fail(c, FS_ERR_INVALID_ARG, "g_out overlaps f");
     Prepared P;
+    P.mom.wanted = true;
     if ((st = prepare(c, prob, &P, 0, nullptr)) != FS_OK) return st;
     if ((st = launch_bias_from_user(c, &P, &P.X, f, eps)) != FS_OK) return st;
     int64_t none = 0;
@@ -668,6 +679,7 @@ static fs_status solve_impl(Ctx *c, const fs_problem *prob, float eps_start, flo
     if (iters_per_stage == 0) return c->device < 0 ? fail(c, FS_ERR_DEVICE, "host-only context") : FS_OK;
 
     Prepared P;
+    P.mom.wanted = true;
     P.halfsteps_per_eps = 2 * iters_per_stage;
     if ((st = prepare(c, prob, &P, 0, nullptr)) != FS_OK) return st;
     double eps0 = stage_eps(eps_start, eps_end, n_stages, 0);
@@ -789,6 +801,7 @@ fs_status fs_solve_tol(fs_ctx *ctx, const fs_problem *prob, float eps_in, int32_
 
     const double eps = (double)eps_in;
     Prepared P;
+    P.mom.wanted = true;
     P.halfsteps_per_eps = 2 * max_iters;
     char *extra = nullptr;
     if ((st = prepare(c, prob, &P, (size_t)prob->n * 8, &extra)) != FS_OK) return st;
@@ -855,7 +868,6 @@ fs_status fs_solve_symmetric(fs_ctx *ctx, const fs_problem *prob, float eps_in, 
     const double eps = (double)eps_in;
     Prepared P;
     P.halfsteps_per_eps = 2 * iters;
-    P.mom.off = true;   // (both passes of an iteration are one launch over the pairs)
     // Both passes of an iteration read the old potentials, so the second one must not overwrite
     // the split partials of the first before they are merged: it gets a partial buffer of its own.
     Prepared sizing;
@@ -1219,6 +1231,9 @@ fs_status fs_debug_set(fs_ctx *ctx, const char *key, int64_t value)
     else if (k == "lowd_moments" && value >= 0 && value <= 2) {
         c->dbg_lowd_moments = (int)value;
         c->kept_valid = false;   // (the layout depends on it)
+    } else if (k == "ws_limit" && value >= 0) {
+        c->dbg_ws_limit = (size_t)value;
+        c->mom_denied = SIZE_MAX;
     } else if (k == "fx_any_size" && (value == 0 || value == 1)) {
         c->dbg_fx_any_size = (int)value;
         c->kept_valid = false;   // (the layout depends on it)

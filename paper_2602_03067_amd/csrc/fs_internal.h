@@ -234,6 +234,8 @@ struct Ctx {
     bool keep_on = false;
     PointsKey keep_key;                // declared by the caller (ws and partial_budget unset)
     bool kept_valid = false;
+    bool kept_bounds = false;   // ... and whether the bounds that the cell moments need are there as well
+    size_t mom_denied = SIZE_MAX;   // bytes of moment buffers that there was no memory for
     PointsKey kept_key;
     double kept_rho_max = -1.0;
     // test and experiment switches of this context (fs_debug_set); 0 = the library decides
@@ -243,6 +245,7 @@ struct Ctx {
     int dbg_lowd_any_bias = 0;       // 1: the precise records also for biases beyond their digit range (tests of that case)
     int dbg_lowd_moments = 0;        // d <= 3: 1: half-steps through cell moments wherever they can be, 2: never
     int dbg_fx_any_size = 0;         // 1: digit images for problems of any size
+    size_t dbg_ws_limit = 0;         // the workspace does not get more bytes than this (0: no limit)
     int dbg_fx_splits = 0;           // forced split count of the streamed side of a fixed-point pass
     // profiling of the streaming LSE launches
     bool prof_on = false;
@@ -337,9 +340,10 @@ struct MomSide {
 struct MomState {
     char *base = nullptr;   // nullptr: no buffers
     size_t bytes = 0;
-    bool off = false;       // the caller's schedule does not take them
-    bool values_finite = false;   // the values of this application are points of a cloud (an infinite one would reach whole
-                                  // cells as NaN)
+    // Set by the entry points whose passes may take them (half-steps of the alternating schedule, gradients): buffers and bounds are
+    // made for these alone.  An application may where its values are points of a cloud, which the bounds say are finite (an
+    // infinite value would reach whole cells as NaN).
+    bool wanted = false;
     double lo[2][3], hi[2][3];   // bounds of both centred clouds (host)
     double eps = 0.0;
     bool on = false;        // ... whether half-steps at that eps run through moments

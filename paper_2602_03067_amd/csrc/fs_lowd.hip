@@ -1424,7 +1424,7 @@ fs_status lowd_apply(Ctx *c, const Prepared *P, const Side *res, const Side *str
                      int64_t p, int64_t ldv, float *out, int64_t ldo, float *mass_out, const float *had_A, int64_t lda)
 {
     float *opart = (float *)P->extra;
-    if (!had_A && P->mom.values_finite && p <= kMomMaxP) {
+    if (!had_A && p <= kMomMaxP) {
         bool moments = false;
         fs_status st = mom_ready(c, P, eps, &moments);
         if (st != FS_OK) return st;

@@ -1041,7 +1041,7 @@ fs_status mom_ready(Ctx *c, const Prepared *P, double eps, bool *use)
 {
     MomState &S = P->mom;
     *use = false;
-    if (!S.base || S.off || c->dbg_lowd_moments == 2) return FS_OK;
+    if (!S.base || c->dbg_lowd_moments == 2) return FS_OK;
     // (the other low-d switches ask for kernels over the pairs)
     if (c->dbg_lowd_moments == 0 && (c->dbg_lowd_score || c->dbg_lowd_splits || c->dbg_lowd_precise_valu)) return FS_OK;
     // Moments stand for passes over the pairs with fp32 scores.  Where float64-grade ones are asked for they are not accurate enough:

@@ -358,3 +358,87 @@ def test_cloud_narrower_than_a_float_at_its_distance(ctx, oracle):
     got, want = host(ctx.fs_update_f(make_problem(x, y, a, b), eps, dev(g))), oracle.update_f(x, y, b, eps, g)
     assert np.ptp(want) >= 1e-4 * eps
     assert max_err_over_eps(got, want, eps) <= _tol(want, eps)
+
+
+def _large(seed, n=20011, m=16001):
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(seed)
+    x, y = torch.rand(n, 3, generator=gen, device="cuda:0"), torch.rand(m, 3, generator=gen, device="cuda:0")
+    return binding.Problem(x, y, None, None)
+
+
+def _taken(call, **switches):
+    """What `call` returns on a new context with these switches, and how much device memory the context holds behind it."""
+    c = binding.Context(0)
+    for k, v in switches.items():
+        c.fs_debug_set(k, v)
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    out = call(c)
+    torch.cuda.synchronize()
+    held = before - torch.cuda.mem_get_info()[0]
+    c.close()
+    return out, held
+
+
+def test_moment_buffers_only_where_they_are_used():
+    """Calls that never run through moments hold what they hold without them; half-steps and gradients hold the buffers."""
+    prob, eps = _large(12), float(np.float32(0.1))
+    f, g = torch.zeros(prob.n, device="cuda:0"), torch.zeros(prob.m, device="cuda:0")
+    V, A = torch.rand(prob.m, 2, device="cuda:0"), torch.rand(prob.n, 3, device="cuda:0")
+    calls = dict(
+        symmetric=lambda c: c.fs_solve_symmetric(prob, eps, 1, f.clone(), g.clone()),
+        apply=lambda c: c.fs_apply_plan(prob, eps, f, g, V),
+        hadamard=lambda c: c.fs_apply_plan_hadamard(prob, eps, f, g, A, V),
+        hvp=lambda c: c.fs_hvp(prob, eps, f, g, A, 1e-3, 1e-2, 1),
+        marginals=lambda c: c.fs_marginal_err(prob, eps, f, g),
+        value=lambda c: c.fs_ot_value(prob, eps, f, g))
+    for name, call in calls.items():
+        _taken(call)   # (what torch keeps for the outputs)
+        say("moment buffers: %s" % name)
+        assert _taken(call, lowd_moments=0)[1] == _taken(call, lowd_moments=2)[1]
+    call = lambda c: c.fs_update_f(prob, eps, g)
+    assert _taken(call, lowd_moments=0)[1] >= _taken(call, lowd_moments=2)[1] + (64 << 20)
+
+
+def test_without_memory_for_the_buffers_passes_run_over_the_pairs():
+    prob, eps = _large(13), float(np.float32(0.1))
+
+    def solve(c):
+        f, g = torch.zeros(prob.n, device="cuda:0"), torch.zeros(prob.m, device="cuda:0")
+        c.fs_solve(prob, eps, eps, 1, 2, f, g)
+        return f, g, c.fs_grad_x(prob, eps, f, g, 2)
+
+    _taken(solve)   # (what torch keeps for the outputs)
+    say("moment buffers: none")
+    pairs, held = _taken(solve, lowd_moments=2)
+    forced, _ = _taken(solve, lowd_moments=1)
+    assert not torch.equal(forced[0], pairs[0])
+    denied, held_denied = _taken(lambda c: solve(c) and solve(c), lowd_moments=1, ws_limit=held + (1 << 20))
+    assert all(torch.equal(u, v) for u, v in zip(denied, pairs)) and held_denied == held
+    # what does not fit without the buffers either is still an error
+    c = binding.Context(0)
+    c.fs_debug_set("ws_limit", 1 << 20)
+    with pytest.raises(binding.FlashSinkError):
+        solve(c)
+    c.fs_debug_set("ws_limit", 0)
+    assert torch.equal(solve(c)[0], _taken(solve, lowd_moments=0)[0][0])
+    c.close()
+
+
+def test_kept_points_with_and_without_bounds():
+    """Copies kept by a call without moments have no bounds of the clouds: the next half-step makes them, and results stay the same."""
+    prob, eps = _large(14), float(np.float32(0.1))
+    g, V = 0.01 * torch.ones(prob.m, device="cuda:0"), torch.rand(prob.m, 2, device="cuda:0")
+    f = torch.zeros(prob.n, device="cuda:0")
+    say("moments, kept points")
+    want = _taken(lambda c: c.fs_update_f(prob, eps, g), lowd_moments=1)[0]
+    plan = _taken(lambda c: c.fs_apply_plan(prob, eps, f, g, V), lowd_moments=1)[0]
+    c = binding.Context(0)
+    c.fs_debug_set("lowd_moments", 1)
+    c.fs_points_keep(prob)
+    for _ in range(3):
+        assert torch.equal(c.fs_apply_plan(prob, eps, f, g, V), plan)
+        assert torch.equal(c.fs_update_f(prob, eps, g), want)
+    c.fs_points_release()
+    c.close()
