@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -355,7 +356,7 @@ struct MomState {
     float coef[kMomTerms];
     double s[3];
     unsigned char *M = nullptr;
-    std::vector<int> host;
+    std::unique_ptr<int[]> host;   // what the host has read back of the cells (see Layout::counts in fs_moments.hip)
 };
 
 constexpr int kScalars = 32, kScalarBounds = 16;   // Prepared::scalars

@@ -33,6 +33,8 @@
 // bound it), 6.9 with shared ones and moments as floats split by the rows' kernel.
 #include <math.h>
 
+#include <new>
+
 #include "fs_internal.h"
 
 namespace fs {
@@ -966,6 +968,7 @@ size_t slab_bytes(int64_t n, int64_t m)
     const double mb = 256.0 * ((double)n / 262144.0) * ((double)m / 262144.0);
     return (size_t)(mb < 64.0 ? 64.0 : mb > 256.0 ? 256.0 : mb) << 20;
 }
+constexpr size_t kHostInts = 8 + 2 * (kMomMaxCells + 1);
 struct Layout {
     size_t slab;
     size_t key[2], perm[2], xi[2], hist[2], total[2], cell[2], block[2], rows[2], centre[2], several[2], fb[2], fr[2], counts, M, bytes;
@@ -997,7 +1000,7 @@ Layout lay(int64_t n, int64_t m)
         L.fb[s] = A.take((size_t)(kMomMaxCells + 1) * 4);
     }
     // what the host reads back, in one piece: counts of both sides (four each), the first group of rows of every cell
-    L.counts = A.take((size_t)(8 + 2 * (kMomMaxCells + 1)) * 4);
+    L.counts = A.take(kHostInts * 4);
     for (int s = 0; s < 2; ++s) L.fr[s] = L.counts + (size_t)(8 + s * (kMomMaxCells + 1)) * 4;
     L.slab = slab_bytes(n, m);
     L.M = A.take(L.slab);
@@ -1093,6 +1096,8 @@ fs_status mom_ready(Ctx *c, const Prepared *P, double eps, bool *use)
 
     const Layout L = lay(n, m);
     if (L.bytes > S.bytes) return fail(c, FS_ERR_DEVICE, "internal: moment buffers");
+    if (!S.host) S.host.reset(new (std::nothrow) int[kHostInts]);   // (no exception may leave an entry point)
+    if (!S.host) return fail(c, FS_ERR_ALLOC, "host memory for the cells of the moment passes");
     SortSide a[2];
     int most_cells = 0;
     for (int s = 0; s < 2; ++s) {
@@ -1115,8 +1120,7 @@ fs_status mom_ready(Ctx *c, const Prepared *P, double eps, bool *use)
     hipLaunchKernelGGL(k_mom_lists, dim3(1, 2), dim3(1024), 0, c->stream, a[0], a[1]);
     hipLaunchKernelGGL(k_mom_scatter, dim3(chunks, 2), dim3(256), 0, c->stream, a[0], a[1], d, P->dpd);
     FS_HIP(c, hipGetLastError());
-    S.host.resize(8 + 2 * (kMomMaxCells + 1));
-    FS_HIP(c, hipMemcpyAsync(S.host.data(), S.base + L.counts, S.host.size() * 4, hipMemcpyDeviceToHost, c->stream));
+    FS_HIP(c, hipMemcpyAsync(S.host.get(), S.base + L.counts, kHostInts * 4, hipMemcpyDeviceToHost, c->stream));
     FS_HIP(c, hipStreamSynchronize(c->stream));
     for (int s = 0; s < 2; ++s) {
         S.g[s] = g[s];
@@ -1181,7 +1185,7 @@ fs_status mom_pass(Ctx *c, const Prepared *P, const Side *res, const Side *str, 
     if (span < 32 || cols > 1 + kMomMaxP) return fail(c, FS_ERR_DEVICE, "internal: moment slab");
     if (span > 65535 / cols / 32 * 32) span = 65535 / cols / 32 * 32;   // (grid of k_mom_reduce)
     if (span > S.cells[t]) span = S.cells[t];
-    const int *first_rows = S.host.data() + 8 + t * (kMomMaxCells + 1);
+    const int *first_rows = S.host.get() + 8 + t * (kMomMaxCells + 1);
     if (!V) prof_begin(c, (double)res->cnt * (double)str->cnt, 2);
     float *ex = reinterpret_cast<float *>(S.M + (size_t)cols * span * S.blocks[s] * RP * 4);   // (behind the moments)
     for (int64_t x0 = 0; x0 < S.cells[t]; x0 += span) {
