@@ -1411,13 +1411,21 @@ void launch_apply_split(dim3 grid, hipStream_t st, const SplitArgs &a, bool two_
 // (n = m = 65536, d = 3: 0.71 against 0.89 ms), and for up to four columns at d = 16, where the matrix-core form takes 2.85 ms
 // instead of 2.81 for both directions at n = 60000, m = 65000, at four times the error (it keeps exponentials to 2^-17).  Elsewhere the matrix-core form: 0.92 against 1.06 ms for three columns at d = 3, 0.97 against 2.02 ms for eight.
 static bool apply_on_valu(int ks, bool precise, int64_t p) { return (p == 1 && (precise || ks <= 3)) || (!precise && ks == 7 && p <= 4); }
-template <int KS>
-void launch_apply_split_valu(dim3 grid, hipStream_t st, const SplitArgs &a)
+template <int KS, int PCU>
+void launch_apply_valu(dim3 grid, hipStream_t st, const SplitArgs &a)
 {
-    if constexpr (KS <= 3)
-        hipLaunchKernelGGL((k_apply_lowd_split<KS, kSplitR, kSplitTJ, kSplitCH, false, kApplyPC, 1>), grid, dim3(kBlock), 0, st, a);
-    if constexpr (KS == 7)
-        hipLaunchKernelGGL((k_apply_lowd_split<KS, kSplitR, kSplitTJ, kSplitCH, false, kApplyPC, kApplyPC>), grid, dim3(kBlock), 0, st, a);
+    hipLaunchKernelGGL((k_apply_lowd_split<KS, kSplitR, kSplitTJ, kSplitCH, false, kApplyPC, PCU>), grid, dim3(kBlock), 0, st, a);
+}
+// (false: there is no such kernel for these k-steps, see apply_on_valu)
+bool launch_apply_split_valu(int ks, dim3 grid, hipStream_t st, const SplitArgs &a)
+{
+    switch (ks) {
+    case 1: launch_apply_valu<1, 1>(grid, st, a); return true;
+    case 2: launch_apply_valu<2, 1>(grid, st, a); return true;
+    case 3: launch_apply_valu<3, 1>(grid, st, a); return true;
+    case 7: launch_apply_valu<7, kApplyPC>(grid, st, a); return true;
+    }
+    return false;
 }
 
 fs_status lowd_apply(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, const float *V,
@@ -1460,8 +1468,8 @@ fs_status lowd_apply(Ctx *c, const Prepared *P, const Side *res, const Side *str
                 if (precise) {
                     hipLaunchKernelGGL((k_apply_lowd_split<3, kSplitR, kSplitTJ, kSplitCH, true, kApplyPC, 1>), grid, dim3(kBlock), 0,
                                        c->stream, a);
-                } else {
-                    FS_SPLIT_KS_DISPATCH(P->ks, (launch_apply_split_valu<KS_>(grid, c->stream, a)));
+                } else if (!launch_apply_split_valu(P->ks, grid, c->stream, a)) {
+                    return fail(c, FS_ERR_DEVICE, "internal: no vector-ALU application at d = %d", (int)P->d);
                 }
                 FS_HIP(c, hipGetLastError());
                 return launch_apply_finalize(c, P, res, precise ? res->norm : res->norm_f, a.splits, eps, opart, kApplyPC, 0, (int)p, out, ldo,

@@ -53,7 +53,7 @@ def test_row_norms(ctx, oracle):
     np.testing.assert_allclose(got, oracle.row_norms(pts[:, :33]), rtol=1e-6)
 
 
-# d = 1..16 covers every record length of the matrix-core pass (1..9 contraction steps), sizes
+# d = 1..16 covers every record length of the matrix-core pass (1..7 contraction steps), sizes
 # cover one lane, ragged tails of row blocks and streamed tiles, and several splits
 @pytest.mark.parametrize("n,m,d", [(1, 1, 3), (5, 3, 1), (255, 257, 2), (1000, 777, 3),
                                    (1024, 1024, 3), (2049, 513, 5), (300, 4100, 8), (700, 900, 16),
@@ -314,7 +314,7 @@ def test_full_size_lowdim_every_stage_sampled(ctx, oracle):
         % (worst, 2 * w.total_iters, sum_abs / eps_end))
 
 
-# (p = 1 runs the kernel with the products on the vector ALU, as does p <= 4 at d = 16; everything else has them on the
+# (p = 1 runs the kernel with the products on the vector ALU up to d = 7, as does p <= 4 at d = 16; everything else has them on the
 # matrix cores: up to eight columns in one pass with the values in three bf16 pieces, more in passes of fifteen with two
 # pieces: p = 9 and 12 are one pass, 16 and 17 two (the second with one and two columns), 31 three)
 @pytest.mark.parametrize("n,m,d,p", [(300, 200, 3, 3), (1000, 1300, 3, 1), (513, 255, 2, 7), (260, 300, 8, 5), (700, 900, 3, 8),
@@ -629,3 +629,23 @@ def test_records_do_not_depend_on_the_scale_of_the_points(ctx, oracle, n, m, d):
             assert np.abs(f - exact).max() <= 2e-5 * eps + 2e-7 * np.abs(exact).max()
         else:
             assert np.array_equal(f, want * 4.0 ** k)
+
+
+@pytest.mark.parametrize("d", range(1, 17))
+def test_applications_at_every_dimension(ctx, oracle, d):
+    """Every record length with the column counts at which the form of the application changes (one column, up to four, up to eight):
+    each has a kernel of its own.  The bars of this file."""
+    rng = np.random.default_rng(40 + d)
+    n, m, eps = 301, 417, float(np.float32(0.3 * max(1.0, d / 4)))
+    x, y, a, b = _rand_problem(rng, n, m, d)
+    fo, go = oracle.solve(x, y, a, b, eps, eps, 1, 4)
+    f32, g32 = fo.astype(np.float32), go.astype(np.float32)
+    V = rng.standard_normal((m, 9)).astype(np.float32)
+    want, r = oracle.apply_plan(x, y, a, b, eps, f32, g32, V, return_mass=True)
+    prob = make_problem(x, y, a, b)
+    for p in (1, 2, 4, 5, 8, 9):
+        say("apply_plan d=%d p=%d" % (d, p))
+        out, mass = ctx.fs_apply_plan(prob, eps, dev(f32), dev(g32), dev(V[:, :p].copy()), want_mass=True)
+        for k in range(p):
+            assert np.linalg.norm(host(out)[:, k] - want[:, k]) <= 2e-4 * np.linalg.norm(want[:, k])
+        np.testing.assert_allclose(host(mass), r, rtol=2e-4)
