@@ -572,8 +572,10 @@ bool mom_fits(const Prepared *P, const Side *str, int p);
 constexpr int kMomMaxP = 8;   // columns of an application through moments
 // a half-step and its merge in one launch (small problems); *done = false: not applicable.  It leaves one gauge sum per 32
 // rows, the merge kernels one per 256.
-// The line, from half-steps in two launches and in one (us): d = 3: n = m = 1024 10.4 / 6.4, 4096 12.0 / 10.1, 8192
-// 16.8 / 16.0, 12000 28 / 31; d = 10: 3000 14.2 / 13.2, 6000 18.2 / 21.6; d = 16: 6000 21.6 / 29.6.
+// The line, from half-steps in two launches and in one (us, of solves): d = 2: n = m = 3000 12.9 / 9.7, 8000 16.9 / 16.1; d = 4: 5400
+// 15.4 / 13.2, 7000 17.0 / 15.6; d = 7: 5400 16.3 / 14.0; d = 10: 4900 16.6 / 14.2; d = 12: 4400 17.5 / 17.1, 5400 18.3 / 19.4; d = 14: 4000
+// 19.8 / 17.9, 8000 27.9 / 28.7; d = 16: 3700 18.5 / 18.2, 4400 19.0 / 20.2, 8000 26.0 / 31.4.  (Below twelve dimensions one launch
+// would also win a little beyond it: d = 10, n = m = 7000 19.1 / 17.4.)
 inline bool lowd_small(int64_t n, int64_t m, int64_t d)
 {
     return n <= 8192 && m <= 8192 && (double)n * (double)m * split_ksteps(d) <= 1.0e8;

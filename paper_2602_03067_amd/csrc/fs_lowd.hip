@@ -1397,18 +1397,32 @@ size_t lowd_apply_ws(const Ctx *c, int64_t n_res, int64_t n_str, int64_t d, int6
 // Matrix-core application on the split records: eight value columns per pass.  Two blocks of 32 resident rows per
 // wave while the records are short; one block for KS > 4, where two would not leave registers for the operands.
 // (One block per wave and three workgroups per CU instead of two measured 4-6 % slower at d = 2..4.)
-template <int KS>
-void launch_apply_split(dim3 grid, hipStream_t st, const SplitArgs &a, bool two_pieces)
+// At KS = 4 (d = 8..10) both fit, and two blocks pay where there are rows enough for them.  Calls of three columns at d = 8 with two
+// blocks and with one (us): n = m = 1000 43.5 / 41.9, 3000 48.3 / 43.7, 12000 81.0 / 80.9, 15000 101 / 105, 35000 334 / 357; 2000 x 50000
+// 85 / 82, 2000 x 200000 177 / 181, 200000 x 2000 185 / 180, 60000 x 8000 161 / 167.
+static int apply_row_blocks(int ks, int64_t n, int64_t m)
+{
+    return ks <= 3 || (ks == 4 && (double)n * (double)m >= 2.0e8) ? kSplitR : 1;
+}
+template <int KS, int R>
+void launch_apply_split_blocks(dim3 grid, hipStream_t st, const SplitArgs &a, bool two_pieces)
 {
     if (two_pieces)
-        hipLaunchKernelGGL((k_apply_lowd_split<KS, (KS <= 4 ? kSplitR : 1), kSplitTJ, kSplitCH, false, 16, 16>), grid, dim3(kBlock), 0,
-                           st, a);
+        hipLaunchKernelGGL((k_apply_lowd_split<KS, R, kSplitTJ, kSplitCH, false, 16, 16>), grid, dim3(kBlock), 0, st, a);
     else
-        hipLaunchKernelGGL((k_apply_lowd_split<KS, (KS <= 4 ? kSplitR : 1), kSplitTJ, kSplitCH, false, kApplyMM, kApplyMM>), grid,
-                           dim3(kBlock), 0, st, a);
+        hipLaunchKernelGGL((k_apply_lowd_split<KS, R, kSplitTJ, kSplitCH, false, kApplyMM, kApplyMM>), grid, dim3(kBlock), 0, st, a);
 }
-// The form with the products on the vector ALU is kept for a single column on short records, where it measured faster
-// (n = m = 65536, d = 3: 0.71 against 0.89 ms), and for up to four columns at d = 16, where the matrix-core form takes 2.85 ms
+// (rblocks: as apply_row_blocks says, which the launch shape was made for)
+template <int KS>
+void launch_apply_split(int rblocks, dim3 grid, hipStream_t st, const SplitArgs &a, bool two_pieces)
+{
+    if constexpr (KS == 4) {
+        if (rblocks == 1) return launch_apply_split_blocks<KS, 1>(grid, st, a, two_pieces);
+    }
+    launch_apply_split_blocks<KS, (KS <= 4 ? kSplitR : 1)>(grid, st, a, two_pieces);
+}
+// The form with the products on the vector ALU is kept for a single column on short records (up to three k-steps, d <= 7), where it
+// measured faster (n = m = 65536, d = 3: 0.71 against 0.89 ms; d = 5 and 7: 0.70 and 0.72 against 0.86 and 0.88), and for up to four columns at d = 16, where the matrix-core form takes 2.85 ms
 // instead of 2.81 for both directions at n = 60000, m = 65000, at four times the error (it keeps exponentials to 2^-17).  Elsewhere the matrix-core form: 0.92 against 1.06 ms for three columns at d = 3, 0.97 against 2.02 ms for eight.
 static bool apply_on_valu(int ks, bool precise, int64_t p) { return (p == 1 && (precise || ks <= 3)) || (!precise && ks == 7 && p <= 4); }
 template <int KS, int PCU>
@@ -1450,7 +1464,7 @@ fs_status lowd_apply(Ctx *c, const Prepared *P, const Side *res, const Side *str
         bool precise = false;
         fs_status st;
         const bool valu = apply_on_valu(P->ks, lowd_precise(P, eps), p);
-        const int rblocks = (valu || lowd_precise(P, eps) || P->ks <= 4) ? kSplitR : 1;
+        const int rblocks = valu || lowd_precise(P, eps) ? kSplitR : apply_row_blocks(P->ks, res->cnt, str->cnt);
         if (split_pass_args(c, P, res, str, eps, P->partial, &a, &precise, &st, rblocks)) {
             const size_t ob = lowd_opart_bytes(a.splits, res->cnt_pad);
             const int64_t units = (int64_t)a.n_tiles * (kSplitTJ / 32) * 128;
@@ -1491,7 +1505,7 @@ fs_status lowd_apply(Ctx *c, const Prepared *P, const Side *res, const Side *str
                         hipLaunchKernelGGL((k_apply_lowd_split<3, kSplitR, kSplitTJ, kSplitCH, true, kApplyMM, kApplyMM>), grid,
                                            dim3(kBlock), 0, c->stream, a);
                 } else {
-                    FS_SPLIT_KS_DISPATCH(P->ks, (launch_apply_split<KS_>(grid, c->stream, a, two)));
+                    FS_SPLIT_KS_DISPATCH(P->ks, (launch_apply_split<KS_>(rblocks, grid, c->stream, a, two)));
                 }
                 FS_HIP(c, hipGetLastError());
                 st = launch_apply_finalize(c, P, res, precise ? res->norm : res->norm_f, a.splits, eps, opart, width, p0, p_end, out,

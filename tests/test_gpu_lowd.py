@@ -649,3 +649,28 @@ def test_applications_at_every_dimension(ctx, oracle, d):
         for k in range(p):
             assert np.linalg.norm(host(out)[:, k] - want[:, k]) <= 2e-4 * np.linalg.norm(want[:, k])
         np.testing.assert_allclose(host(mass), r, rtol=2e-4)
+
+
+@pytest.mark.parametrize("n,m", [(14143, 14141), (14143, 14143), (200001, 1000), (1001, 200000)])
+@pytest.mark.parametrize("d", [8, 10])
+@pytest.mark.parametrize("p", [3, 9])
+def test_applications_with_one_and_two_row_blocks(n, m, d, p):
+    """Both sides of the line between the two launch shapes of d = 8..10 (n m = 2e8), against sums in float64 on sampled rows."""
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(n + d + p)
+    x, y = torch.rand(n, d, generator=gen, device="cuda:0"), torch.rand(m, d, generator=gen, device="cuda:0")
+    V = torch.randn(m, p, generator=gen, device="cuda:0")
+    f, g = 0.1 * torch.randn(n, generator=gen, device="cuda:0"), 0.1 * torch.randn(m, generator=gen, device="cuda:0")
+    eps = float(np.float32(0.2))
+    c = binding.Context(0)
+    say("apply_plan n=%d m=%d d=%d p=%d" % (n, m, d, p))
+    out, mass = c.fs_apply_plan(binding.Problem(x, y, None, None), eps, f, g, V, want_mass=True)
+    torch.cuda.synchronize()
+    rows = torch.cat([torch.arange(0, n, max(1, n // 300), device="cuda:0"), torch.arange(n - 70, n, device="cuda:0")])
+    cost = ((x[rows].double() ** 2).sum(1)[:, None] + (y.double() ** 2).sum(1)[None, :] - 2.0 * x[rows].double() @ y.double().t())
+    P = torch.exp((f[rows].double()[:, None] + g.double()[None, :] - cost) / eps) / (float(n) * m)
+    want, r = P @ V.double(), P.sum(1)
+    # (the bars of this file, per row: entries to 2^-17 of the row's mass times the largest value)
+    assert float(((out[rows].double() - want).abs() / r[:, None]).max()) <= 2e-4 * float(V.abs().max())
+    assert float((mass[rows].double() / r - 1.0).abs().max()) <= 2e-4
+    c.close()
