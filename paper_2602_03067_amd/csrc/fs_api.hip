@@ -223,7 +223,7 @@ size_t layout_with(const Ctx *c, const fs_problem *p, Prepared *P, char *base, s
     o = A.take((size_t)(256 + 1) * 16 * 8);
     P->mean = base ? (double *)(base + o) : nullptr;
     // (behind everything that is kept between entry calls: only some of them have it)
-    P->mom.bytes = P->path == Path::LowD && P->mom.wanted && mom_size(c, p->n, p->m, p->d) ? mom_bytes(p->n, p->m) : 0;
+    P->mom.bytes = P->path == Path::LowD && mom_size(c, P->mom, p->n, p->m, p->d) ? mom_bytes(p->n, p->m) : 0;
     if (P->mom.bytes >= c->mom_denied) P->mom.bytes = 0;
     o = A.take(P->mom.bytes);
     P->mom.base = base && P->mom.bytes ? base + o : nullptr;
@@ -446,7 +446,8 @@ fs_status grad_common(Ctx *c, const fs_problem *prob, float eps, const float *f,
     const size_t mass_bytes = ((size_t)rows * 4 + 255) & ~size_t(255);
     const size_t tail_bytes = mass_bytes + (convert ? (size_t)orows * d * 4 : 0);
     Prepared P;
-    P.mom.wanted = true;
+    P.mom.passes = 1;
+    P.mom.cols = 1 + (int)d;
     char *tail = nullptr;
     if ((st = apply_begin(c, prob, eps, f, g, d, wrt_y, tail_bytes, &P, &tail)) != FS_OK) return st;
     float *mass = reinterpret_cast<float *>(tail);
@@ -597,7 +598,7 @@ fs_status fs_update_f(fs_ctx *ctx, const fs_problem *prob, float eps, const floa
     if (overlap(f_out, (size_t)prob->n * 4, g, (size_t)prob->m * 4))
         return fail(c, FS_ERR_INVALID_ARG, "f_out overlaps g");
     Prepared P;
-    P.mom.wanted = true;
+    P.mom.passes = 1;
     if ((st = prepare(c, prob, &P, 0, nullptr)) != FS_OK) return st;
     if ((st = launch_bias_from_user(c, &P, &P.Y, g, eps)) != FS_OK) return st;
     int64_t none = 0;
@@ -616,7 +617,7 @@ fs_status fs_update_g(fs_ctx *ctx, const fs_problem *prob, float eps, const floa
     if (overlap(g_out, (size_t)prob->m * 4, f, (size_t)prob->n * 4))
         return fail(c, FS_ERR_INVALID_ARG, "g_out overlaps f");
     Prepared P;
-    P.mom.wanted = true;
+    P.mom.passes = 1;
     if ((st = prepare(c, prob, &P, 0, nullptr)) != FS_OK) return st;
     if ((st = launch_bias_from_user(c, &P, &P.X, f, eps)) != FS_OK) return st;
     int64_t none = 0;
@@ -679,8 +680,7 @@ static fs_status solve_impl(Ctx *c, const fs_problem *prob, float eps_start, flo
     if (iters_per_stage == 0) return c->device < 0 ? fail(c, FS_ERR_DEVICE, "host-only context") : FS_OK;
 
     Prepared P;
-    P.mom.wanted = true;
-    P.halfsteps_per_eps = 2 * iters_per_stage;
+    P.mom.passes = P.halfsteps_per_eps = 2 * iters_per_stage;
     if ((st = prepare(c, prob, &P, 0, nullptr)) != FS_OK) return st;
     double eps0 = stage_eps(eps_start, eps_end, n_stages, 0);
     if ((st = launch_bias_from_user(c, &P, &P.Y, g, eps0)) != FS_OK) return st;
@@ -801,8 +801,7 @@ fs_status fs_solve_tol(fs_ctx *ctx, const fs_problem *prob, float eps_in, int32_
 
     const double eps = (double)eps_in;
     Prepared P;
-    P.mom.wanted = true;
-    P.halfsteps_per_eps = 2 * max_iters;
+    P.mom.passes = P.halfsteps_per_eps = 2 * max_iters;
     char *extra = nullptr;
     if ((st = prepare(c, prob, &P, (size_t)prob->n * 8, &extra)) != FS_OK) return st;
     double *f_before = reinterpret_cast<double *>(extra);   // f of the last completed iteration at a check

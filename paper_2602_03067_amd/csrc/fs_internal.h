@@ -341,10 +341,11 @@ struct MomSide {
 struct MomState {
     char *base = nullptr;   // nullptr: no buffers
     size_t bytes = 0;
-    // Set by the entry points whose passes may take them (half-steps of the alternating schedule, gradients): buffers and bounds are
-    // made for these alone.  An application may where its values are points of a cloud, which the bounds say are finite (an
-    // infinite value would reach whole cells as NaN).
-    bool wanted = false;
+    // Set by the entry points whose passes may take them (half-steps of the alternating schedule, gradients), for which alone buffers
+    // and bounds are made: how many passes the call makes at one eps, and their columns (1, and the values' of an application).  An
+    // application may where its values are points of a cloud, which the bounds say are finite (an infinite value would reach whole
+    // cells as NaN).
+    int passes = 0, cols = 1;
     double lo[2][3], hi[2][3];   // bounds of both centred clouds (host)
     double eps = 0.0;
     bool on = false;        // ... whether half-steps at that eps run through moments
@@ -560,15 +561,22 @@ inline const double *lowd_norm(const Prepared *P, const Side *res, double eps)
 }
 // fs_moments.hip
 size_t mom_bytes(int64_t n, int64_t m);
-// (below this a pass over the pairs takes less than the cells' launches)
-inline bool mom_size(const Ctx *c, int64_t n, int64_t m, int64_t d)
+// time of a pass over the pairs on the split records (us): 9 to 12 pairs a ns, in an application 7 to 9.3 (d = 1) and 5.1 to 6.5
+inline double mom_pair_cost(int64_t n, int64_t m, int64_t d, int cols)
 {
-    return d <= 3 && !c->ws_static && c->dbg_lowd_moments != 2 && ((double)n * (double)m >= 3.0e8 || c->dbg_lowd_moments == 1);
+    return (double)n * (double)m / (cols == 1 ? 11.4e6 : d == 1 ? 9.0e6 : 6.2e6) + 8.0;
 }
-fs_status mom_ready(Ctx *c, const Prepared *P, double eps, bool *use);
+// Whether moments can pay for `passes` passes at one eps: dealing the clouds to cells takes some 70 us, a pass through few cells 30 (and 10 a column).
+// (Where they can't, the clouds' bounds would only cost: 4 of 100 us of a half-step call at n = 43577, m = 7343.)
+inline bool mom_size(const Ctx *c, const MomState &S, int64_t n, int64_t m, int64_t d)
+{
+    if (!S.passes || d > 3 || c->ws_static || c->dbg_lowd_moments == 2) return false;
+    return c->dbg_lowd_moments == 1 || ((double)n * (double)m >= 3.0e8 && S.passes * (mom_pair_cost(n, m, d, S.cols) - 20.0 - 10.0 * S.cols) > 40.0);
+}
+// (t: side of the rows, 0: X)
+fs_status mom_ready(Ctx *c, const Prepared *P, double eps, int t, bool *use);
 // V != nullptr: the plan application to the p columns of V as well, accumulators [rows][p] in opart
 fs_status mom_pass(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, const float *V, int p, int64_t ldv, float *opart);
-bool mom_fits(const Prepared *P, const Side *str, int p);
 constexpr int kMomMaxP = 8;   // columns of an application through moments
 // a half-step and its merge in one launch (small problems); *done = false: not applicable.  It leaves one gauge sum per 32
 // rows, the merge kernels one per 256.

@@ -1223,7 +1223,7 @@ fs_status lowd_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, 
 {
     {
         bool moments = false;
-        fs_status ms = mom_ready(c, P, eps, &moments);
+        fs_status ms = mom_ready(c, P, eps, res == &P->Y, &moments);
         if (ms != FS_OK) return ms;
         if (moments) {
             *splits_out = 1;
@@ -1446,11 +1446,11 @@ fs_status lowd_apply(Ctx *c, const Prepared *P, const Side *res, const Side *str
                      int64_t p, int64_t ldv, float *out, int64_t ldo, float *mass_out, const float *had_A, int64_t lda)
 {
     float *opart = (float *)P->extra;
-    if (!had_A && p <= kMomMaxP) {
+    if (!had_A && p < kMomMaxP && 1 + p == P->mom.cols) {
         bool moments = false;
-        fs_status st = mom_ready(c, P, eps, &moments);
+        fs_status st = mom_ready(c, P, eps, res == &P->Y, &moments);
         if (st != FS_OK) return st;
-        if (moments && mom_fits(P, str, (int)p)) {
+        if (moments) {
             if (!opart || (size_t)res->cnt_pad * p * 4 > P->extra_bytes) return fail(c, FS_ERR_DEVICE, "internal: low-d apply workspace");
             if ((st = mom_pass(c, P, res, str, eps, V, (int)p, ldv, opart)) != FS_OK) return st;
             return launch_apply_finalize(c, P, res, res->norm, 1, eps, opart, (int)p, 0, (int)p, out, ldo, mass_out);

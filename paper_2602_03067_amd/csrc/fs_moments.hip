@@ -950,17 +950,47 @@ bool geometry(const MomState &S, int d, double eps, double tau, MomGeom (&g)[2],
     return true;
 }
 
-// Time of a half-step (us).  nt, cells: rows and their cells; ns, scells: streamed points and their cells.  Cycles of a SIMD at the
-// 0.6 of them that both kernels keep busy: per point and 32 row cells 6 RT for the products and 40 for the weights; per 32 rows and
-// 32 streamed cells 192 RT for the products and 500 for what is made of them; 8 us for each round of workgroups.
-double mom_cost(int rt, double nt, double cells, double ns, double scells, int num_cu)
+// Time of a pass (us).  nt, ct, gt: rows, their cells and groups; ns, cs, bs: streamed points, their cells and blocks; cols: 1 and the
+// value columns of an application.  A launch takes as many row cells as the slab has place for, and its workgroups run in rounds of
+// one per CU: k_mom_gather's take 2.1 us and 0.64 us per tile of monomials and stage of 32 points (half of that where `halves` is set),
+// k_mom_rows' 3.6 us and 0.34 us per tile and 32 streamed cells, on top of what the chip's matrix cores and the moments' way
+// through memory take.  Fitted to 887 passes (150 problems, d = 1..3, n m = 3e8 .. 3e10, cells from 1 to 7000, 33 us to 62 ms): half of the
+// passes within 0.9 to 1.1 times, nine out of ten within 0.75 to 1.2 times what this says.
+double mom_cost(int rt, double nt, double ct, double gt, double ns, double cs, double bs, int cols, size_t slab, int num_cu)
 {
-    const double cycles = ceil(cells / 32.0) * ns * (6.0 * rt + 40.0) + (nt / 32.0 + 0.5 * cells) * ceil(scells / 32.0) * (192.0 * rt + 500.0);
-    const double rounds = ceil((scells + ns / 1024.0) * ceil(cells / 256.0) / num_cu) + ceil((cells + nt / kMomRows) / num_cu);
-    return cycles / (0.6 * num_cu * 4.0 * 2200.0) + 8.0 * rounds + 15.0;
+    const double span = floor((double)slab / (cols * bs * (128.0 * rt + 4.0)) / 32.0) * 32.0;
+    if (!(span >= 32.0)) return INFINITY;   // (moments of 32 row cells are the least that a launch forms)
+    const double launches = ceil(ct / span), cells = ceil(ct / launches), tiles = ceil(cs / 32.0);
+    const bool halves = cells <= 128.0;
+    const double gather = ceil(cols * bs * ceil(cells / (halves ? 128.0 : 256.0)) / num_cu) * (2.1 + 0.64 * rt * (halves ? 0.5 : 1.0) * ceil(ns / bs / 32.0));
+    const double rows = ceil(cols * gt / launches / num_cu) * (3.6 + 0.34 * rt * tiles);
+    const double reduce = bs > cs ? 9.0 + 0.06 * bs / cs : 0.0;
+    return 8.0 + launches * (gather + rows + reduce) + cols * (1.45e-4 * (nt / 32.0 + 0.5 * ct) * tiles + 5.4e-5 * ct * bs) * rt;
 }
-// ... and over the pairs, on the split records
-double pair_cost(double n, double m) { return n * m / 11.4e6 + 8.0; }
+// streamed points of a block: longer ones, where there are workgroups enough for them (one per block and 32 cells of the other
+// cloud), have fewer moments to write
+int block_points(double cells, double other_cells, int64_t cnt, int num_cu)
+{
+    int block = 4 * kMomBlock;
+    while (block > kMomBlock && ceil(other_cells / 32.0) * fmax(cells, (double)cnt / block) < 1.5 * num_cu) block /= 2;
+    return block;
+}
+// The passes of a call at one eps: of P->mom.passes passes with rows on side t where there is only one, otherwise on either side in
+// turn.  cells: those that hold points; blocks, groups: of either side, 0: not known yet.
+double mom_cost_of(const Prepared *P, int t, int rt, const double (&cells)[2], const int (&blocks)[2], const int (&groups)[2], size_t slab,
+                   int num_cu)
+{
+    const int64_t cnt[2] = {P->X.cnt, P->Y.cnt};
+    double cost = 0.0;
+    for (int side = 0; side < 2; ++side) {   // of the rows
+        if (P->mom.passes == 1 && side != t) continue;
+        const int o = 1 - side;
+        const double g = groups[side] ? groups[side] : fmax(cells[side], 0.5 * cells[side] + (double)cnt[side] / kMomRows);
+        const double b = blocks[o] ? blocks[o] : fmax(cells[o], 0.5 * cells[o] + (double)cnt[o] / block_points(cells[o], cells[side], cnt[o], num_cu));
+        cost += mom_cost(rt, (double)cnt[side], cells[side], g, (double)cnt[o], cells[o], b, P->mom.cols, slab, num_cu);
+    }
+    return P->mom.passes == 1 ? cost : 0.5 * P->mom.passes * cost;
+}
 
 // bytes for the moments of a launch: at n = m = 262144 what a hundred row cells take, less where there are fewer blocks
 size_t slab_bytes(int64_t n, int64_t m)
@@ -1039,8 +1069,8 @@ MomSide side_of(const Layout &L, char *base, int s)
 
 size_t mom_bytes(int64_t n, int64_t m) { return lay(n, m).bytes; }
 
-// Decides whether the half-steps at `eps` go through moments and, if so, deals the clouds to their cells.
-fs_status mom_ready(Ctx *c, const Prepared *P, double eps, bool *use)
+// Decides whether the passes at `eps` (rows on side t) go through moments and, if so, deals the clouds to their cells.
+fs_status mom_ready(Ctx *c, const Prepared *P, double eps, int t, bool *use)
 {
     MomState &S = P->mom;
     *use = false;
@@ -1065,34 +1095,41 @@ fs_status mom_ready(Ctx *c, const Prepared *P, double eps, bool *use)
     if (!finite) return FS_OK;
     const int64_t n = P->X.cnt, m = P->Y.cnt;
     const bool force = c->dbg_lowd_moments == 1;
-    const double pair = 2.0 * pair_cost((double)n, (double)m);
-    // the kind of expansion that is cheapest if half of the cells hold points
+    // What moments may take at most.  (The model of their time and that of the pairs are each off by up to a quarter.)
+    const double limit = 0.85 * S.passes * mom_pair_cost(n, m, d, S.cols);
+    const size_t slab = slab_bytes(n, m);
+    const int unknown[2] = {0, 0};
+    // The kind of expansion that is cheapest between the two cases that all cells hold points and half of many do.
     int best = -1;
-    double best_cost = 0.0;
+    double half_cost = 0.0, all_cost = 0.0;
     MomGeom g[2];
     for (int k = 0; k < kKinds; ++k) {
         if (kKind[k].d != d) continue;
-        MomGeom t[2];
-        double s[3];
-        if (!geometry(S, d, eps, kKind[k].tau, t, s)) continue;
-        double nc[2];
+        MomGeom geo[2];
+        double s[3], all[2], half[2];
+        if (!geometry(S, d, eps, kKind[k].tau, geo, s)) continue;
         for (int q = 0; q < 2; ++q) {
-            nc[q] = (double)t[q].nc[0] * t[q].nc[1] * t[q].nc[2];
-            if (nc[q] > 64.0) nc[q] = fmax(64.0, 0.5 * nc[q]);
+            const double grid = (double)geo[q].nc[0] * geo[q].nc[1] * geo[q].nc[2], most = (double)(q ? m : n);
+            all[q] = fmin(grid, most);
+            half[q] = fmin(grid > 64.0 ? fmax(64.0, 0.5 * grid) : grid, most);
         }
-        const double cost = mom_cost(kKind[k].rt, (double)n, nc[0], (double)m, nc[1], c->num_cu) +
-                            mom_cost(kKind[k].rt, (double)m, nc[1], (double)n, nc[0], c->num_cu);
-        if (best < 0 || cost < best_cost) {
+        const double hc = mom_cost_of(P, t, kKind[k].rt, half, unknown, unknown, slab, c->num_cu);
+        const double ac = mom_cost_of(P, t, kKind[k].rt, all, unknown, unknown, slab, c->num_cu);
+        if (best < 0 || hc + ac < half_cost + all_cost) {
             best = k;
-            best_cost = cost;
-            g[0] = t[0];
-            g[1] = t[1];
+            half_cost = hc;
+            all_cost = ac;
+            g[0] = geo[0];
+            g[1] = geo[1];
             for (int q = 0; q < 3; ++q) S.s[q] = s[q];
         }
     }
     if (best < 0) return FS_OK;
-    const double iterations = 0.5 * P->halfsteps_per_eps, setup = 60.0;   // (four launches and a read-back)
-    if (!force && iterations * best_cost + setup > 0.9 * iterations * pair) return FS_OK;
+    // Dealing the points to their cells (four launches and a read-back) takes some time as well.  It is spent where moments pay even if
+    // every cell holds points (as in a cube full of them), and where they do if half of them hold any and it is little beside the
+    // passes: how many do is not known before.
+    const double setup = 45.0 + 1.0e-4 * (double)(n + m);
+    if (!force && setup + all_cost > limit && (setup + half_cost > limit || setup > 0.04 * limit)) return FS_OK;
 
     const Layout L = lay(n, m);
     if (L.bytes > S.bytes) return fail(c, FS_ERR_DEVICE, "internal: moment buffers");
@@ -1100,17 +1137,14 @@ fs_status mom_ready(Ctx *c, const Prepared *P, double eps, bool *use)
     if (!S.host) return fail(c, FS_ERR_ALLOC, "host memory for the cells of the moment passes");
     SortSide a[2];
     int most_cells = 0;
+    double many[2];   // (half of many cells hold points)
+    for (int q = 0; q < 2; ++q) {
+        many[q] = (double)g[q].nc[0] * g[q].nc[1] * g[q].nc[2];
+        if (many[q] > 256.0) many[q] = fmax(256.0, 0.5 * many[q]);
+    }
     for (int s = 0; s < 2; ++s) {
         const Side &sd = s ? P->Y : P->X;
-        // longer blocks, where there are workgroups enough for them (one per block and 32 cells of the other cloud): fewer
-        // moments to write
-        double cells[2];   // (half of many cells hold points)
-        for (int q = 0; q < 2; ++q) {
-            cells[q] = (double)g[q].nc[0] * g[q].nc[1] * g[q].nc[2];
-            if (cells[q] > 256.0) cells[q] = fmax(256.0, 0.5 * cells[q]);
-        }
-        int block = 4 * kMomBlock;
-        while (block > kMomBlock && ceil(cells[1 - s] / 32.0) * fmax(cells[s], (double)sd.cnt / block) < 1.5 * c->num_cu) block /= 2;
+        const int block = block_points(many[s], many[1 - s], sd.cnt, c->num_cu);
         a[s] = SortSide{sd.packed_d, sd.cnt, L.chunk[s], g[s].nc[0] * g[s].nc[1] * g[s].nc[2], L.chunks[s], block, g[s], side_of(L, S.base, s)};
         if (a[s].ncell > most_cells) most_cells = a[s].ncell;
     }
@@ -1154,24 +1188,14 @@ fs_status mom_ready(Ctx *c, const Prepared *P, double eps, bool *use)
             S.coef[q] = (float)ldexp(v, kCoefShift);
         }
     }
-    const int rt = kKind[best].rt;
-    // moments of 32 row cells are the least that a launch forms
-    for (int s = 0; s < 2; ++s)
-        if (32.0 * S.blocks[s] * (rt * 128.0 + 4.0) > (double)L.slab) return FS_OK;
-    const double cost = mom_cost(rt, (double)n, S.cells[0], (double)m, S.cells[1], c->num_cu) +
-                        mom_cost(rt, (double)m, S.cells[1], (double)n, S.cells[0], c->num_cu);
+    const double cells[2] = {(double)S.cells[0], (double)S.cells[1]};
+    const double cost = mom_cost_of(P, t, kKind[best].rt, cells, S.blocks, S.groups, L.slab, c->num_cu);
+    if (!(cost < INFINITY)) return FS_OK;
     S.M = reinterpret_cast<unsigned char *>(S.base + L.M);
     S.slab = L.slab;
-    S.on = force || cost < 0.9 * pair;
+    S.on = force || cost < limit;
     *use = S.on;
     return FS_OK;
-}
-
-// an application to p columns fits the buffers (after mom_ready)
-bool mom_fits(const Prepared *P, const Side *str, int p)
-{
-    const MomState &S = P->mom;
-    return p <= kMomMaxP && 32.0 * (1 + p) * S.blocks[str == &P->Y ? 1 : 0] * (kKind[S.kind].rt * 128.0 + 4.0) <= (double)S.slab;
 }
 
 fs_status mom_pass(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, const float *V, int p, int64_t ldv, float *opart)

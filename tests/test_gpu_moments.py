@@ -382,13 +382,15 @@ def _taken(call, **switches):
 
 
 def test_moment_buffers_only_where_they_are_used():
-    """Calls that never run through moments hold what they hold without them; half-steps and gradients hold the buffers."""
+    """Calls that never run through moments hold what they hold without them, and so do those that are too short for them; a solve
+    holds the buffers."""
     prob, eps = _large(12), float(np.float32(0.1))
     f, g = torch.zeros(prob.n, device="cuda:0"), torch.zeros(prob.m, device="cuda:0")
     V, A = torch.rand(prob.m, 2, device="cuda:0"), torch.rand(prob.n, 3, device="cuda:0")
     calls = dict(
         symmetric=lambda c: c.fs_solve_symmetric(prob, eps, 1, f.clone(), g.clone()),
         apply=lambda c: c.fs_apply_plan(prob, eps, f, g, V),
+        update=lambda c: c.fs_update_f(prob, eps, g),
         hadamard=lambda c: c.fs_apply_plan_hadamard(prob, eps, f, g, A, V),
         hvp=lambda c: c.fs_hvp(prob, eps, f, g, A, 1e-3, 1e-2, 1),
         marginals=lambda c: c.fs_marginal_err(prob, eps, f, g),
@@ -397,7 +399,7 @@ def test_moment_buffers_only_where_they_are_used():
         _taken(call)   # (what torch keeps for the outputs)
         say("moment buffers: %s" % name)
         assert _taken(call, lowd_moments=0)[1] == _taken(call, lowd_moments=2)[1]
-    call = lambda c: c.fs_update_f(prob, eps, g)
+    call = lambda c: c.fs_solve(prob, eps, eps, 1, 10, f.clone(), g.clone())
     assert _taken(call, lowd_moments=0)[1] >= _taken(call, lowd_moments=2)[1] + (64 << 20)
 
 
