@@ -381,8 +381,10 @@ fs_status fs_debug_set(fs_ctx *ctx, const char *key /* host */, int64_t value);
  * Timing hook for benchmarks: average duration in milliseconds of the streaming
  * LSE kernel launches recorded with HIP events on the context's stream since the
  * last call of this function, and their count.  Where a solve mixes two LSE
- * kernels (low-d problems: fp32-accuracy and float64-score half-steps), the
- * figures are those of the kernel with the larger total time (the dominant one).
+ * kernels (low-d problems: fp32-accuracy and float64-score half-steps, half-steps
+ * through cell moments), the figures are those of the kernel with the larger total
+ * time (the dominant one).  pairs_per_launch: pairs that a launch evaluates, 0 where
+ * half-steps through cell moments dominate, which evaluate none.
  * Recording is off until fs_profile_enable(ctx, 1).  Synchronises the stream.
  */
 fs_status fs_profile_enable(fs_ctx *ctx, int32_t on);

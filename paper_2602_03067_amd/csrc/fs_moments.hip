@@ -1210,7 +1210,7 @@ fs_status mom_pass(Ctx *c, const Prepared *P, const Side *res, const Side *str, 
     if (span > 65535 / cols / 32 * 32) span = 65535 / cols / 32 * 32;   // (grid of k_mom_reduce)
     if (span > S.cells[t]) span = S.cells[t];
     const int *first_rows = S.host.get() + 8 + t * (kMomMaxCells + 1);
-    if (!V) prof_begin(c, (double)res->cnt * (double)str->cnt, 2);
+    if (!V) prof_begin(c, 0.0, 2);   // (no pairs are evaluated)
     float *ex = reinterpret_cast<float *>(S.M + (size_t)cols * span * S.blocks[s] * RP * 4);   // (behind the moments)
     for (int64_t x0 = 0; x0 < S.cells[t]; x0 += span) {
         const int cells = (int)(S.cells[t] - x0 < span ? S.cells[t] - x0 : span);

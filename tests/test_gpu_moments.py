@@ -444,3 +444,18 @@ def test_kept_points_with_and_without_bounds():
         assert torch.equal(c.fs_update_f(prob, eps, g), want)
     c.fs_points_release()
     c.close()
+
+
+def test_profile_says_what_ran():
+    """Half-steps through moments are booked as launches that evaluate no pairs, half-steps over the pairs with their pairs."""
+    prob, eps = _large(15), float(np.float32(0.1))
+    f, g = torch.zeros(prob.n, device="cuda:0"), torch.zeros(prob.m, device="cuda:0")
+    for mode, pairs in ((1, 0.0), (2, float(prob.n) * prob.m)):
+        c = binding.Context(0)
+        c.fs_debug_set("lowd_moments", mode)
+        c.fs_profile_enable(True)
+        say("moments profile, mode %d" % mode)
+        c.fs_solve(prob, eps, eps, 1, 3, f, g)
+        avg, launches, per_launch = c.fs_profile_read()
+        assert avg > 0.0 and launches == 6 and per_launch == pairs
+        c.close()
