@@ -773,9 +773,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, KS <=
     lse_split_body<KS, R, TJ, CH, PRECISE>(a, blockIdx.x, blockIdx.y);
 }
 
-// plan application on the split records (PC value columns per launch; workgroups per CU as above)
+// plan application on the split records (PC value columns per launch; workgroups per CU as above; the one-column form on the vector
+// ALU asks for three at least: left to itself the compiler takes registers for two, and a column at n = 100000, m = 90000, d = 3 takes 1345 us
+// instead of 1163)
 template <int KS, int R, int TJ, int CH, bool PRECISE, int PC, int PCU>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, KS <= 2 ? 8 : 2))) void k_apply_lowd_split(SplitArgs a)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(PC == 4 && KS <= 2 ? 3 : 2, KS <= 2 ? 8 : 2))) void k_apply_lowd_split(SplitArgs a)
 {
     lse_split_body<KS, R, TJ, CH, PRECISE, PC, PCU>(a, blockIdx.x, blockIdx.y);
 }
