@@ -17,6 +17,8 @@
 //
 // Score precision: fp32 when (log2e/eps) * max|x|^2 is small enough for fp32 scores to hold the
 // 1e-4 target, float64 otherwise (a score of magnitude 500 has an fp32 ulp of 6e-5).
+#include <type_traits>
+
 #include "fs_finalize.h"
 #include "fs_internal.h"
 
@@ -818,23 +820,19 @@ __global__ __launch_bounds__(64 * kSmallWaves) void k_half_lowd_small(SplitArgs 
         for (int ks = 0; ks < KS; ++ks) av[ks] = *reinterpret_cast<const bf8 *>(str + (int64_t)g * (64 * KS) + 64 * ks + l);   // (see split_unit)
     };
     static_assert(kSmallWaves % 2 == 0, "a wave's groups are all even or all odd");
-    const float sign = w & 1 ? -1.0f : 1.0f;
     auto scores = [&](const bf8 (&av)[KS], f16v &dd) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) dd[e] = 0.0f;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) dd = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[ks], b[ks], dd, 0, 0, 0);
-        if constexpr (!PRECISE) {   // (a wave's groups are all even or all odd, see split_negated)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) dd[e] *= sign;
-        }
     };
-    auto sums = [&](const f16v &dd) {
+    // (neg: whether the scores are negated, see split_negated; a constant, so that the sign is part of the instructions)
+    auto sums = [&](const f16v &dd, auto neg) {
         float s0 = 0.0f, s1 = 0.0f;
 #pragma unroll
         for (int e = 0; e < 16; e += 2) {
-            s0 += fast_exp2(dd[e]);
-            s1 += fast_exp2(dd[e + 1]);
+            s0 += fast_exp2(neg ? -dd[e] : dd[e]);
+            s1 += fast_exp2(neg ? -dd[e + 1] : dd[e + 1]);
         }
         return s0 + s1;
     };
@@ -854,32 +852,38 @@ __global__ __launch_bounds__(64 * kSmallWaves) void k_half_lowd_small(SplitArgs 
     float m = kNegInit;
     double s = 0.0;
     set_max(-kNegInit);
-    for (int g = w; g < n_groups; g += kSmallWaves) {
-        bf8 nx[KS];
-        load_a(min(g + kSmallWaves, n_groups - 1), nx);
-        f16v dd;
-        scores(av, dd);
-        float cs = sums(dd);
-        // lift the max, common to the two lane halves (see lse_split_body); sixteen scores at or below it sum to 16 at most,
-        // and a wave sees too few groups to start far below its largest score: 5 base-2 units here, 60 there
-        if (__any(!(cs < 32.0f))) {
-            set_max(0.0f);
+    auto groups = [&](auto neg) {
+        for (int g = w; g < n_groups; g += kSmallWaves) {
+            bf8 nx[KS];
+            load_a(min(g + kSmallWaves, n_groups - 1), nx);
+            f16v dd;
             scores(av, dd);
-            float mx = kNegInit;
+            float cs = sums(dd, neg);
+            // lift the max, common to the two lane halves (see lse_split_body); sixteen scores at or below it sum to 16 at most,
+            // and a wave sees too few groups to start far below its largest score: 5 base-2 units here, 60 there
+            if (__any(!(cs < 32.0f))) {
+                set_max(0.0f);
+                scores(av, dd);
+                float mx = kNegInit;
 #pragma unroll
-            for (int e = 0; e < 16; ++e) mx = fmaxf(mx, dd[e]);
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
-            const float mnew = fmaxf(m, lifted_max<PRECISE>(mx));
-            s *= (double)fast_exp2(m - mnew);
-            m = mnew;
-            set_max(-mnew);
-            scores(av, dd);
-            cs = sums(dd);
+                for (int e = 0; e < 16; ++e) mx = fmaxf(mx, neg ? -dd[e] : dd[e]);
+                mx = fmaxf(mx, __shfl_xor(mx, 32));
+                const float mnew = fmaxf(m, lifted_max<PRECISE>(mx));
+                s *= (double)fast_exp2(m - mnew);
+                m = mnew;
+                set_max(-mnew);
+                scores(av, dd);
+                cs = sums(dd, neg);
+            }
+            s += (double)cs;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) av[ks] = nx[ks];
         }
-        s += (double)cs;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) av[ks] = nx[ks];
-    }
+    };
+    if (!PRECISE && (w & 1))
+        groups(std::true_type{});
+    else
+        groups(std::false_type{});
     s += __shfl_xor(s, 32);
     if (lh == 0) {
         sm[w][lj] = m;
