@@ -768,9 +768,11 @@ __device__ __forceinline__ void lse_split_body(const SplitArgs &a, const int bx,
 // (From three k-steps on two workgroups per CU at most: the dispatcher fills one CU after the other, and the launch shape counts on two.
 // Where the registers let it put three on a CU, the 630 workgroups of both half-steps at n = 12000, m = 20011, d = 5 took 210 CUs and
 // 93 us instead of 73.  With one or two k-steps the wait for a tile shows more than that: six iterations and the gradient at n = 9000,
-// m = 30000, d = 4 take 810 us with two, 731 with what the registers allow.)
+// m = 30000, d = 4 take 810 us with two, 731 with what the registers allow; but not five, as they do at d = 2, in the paired launch: ten
+// averaged iterations at n = 1611, m = 24195 398 us with five, 322 with three.  At six k-steps the cap makes the compiler spill 19 registers, and
+// there is room for two only without it: ten iterations at n = 5614, m = 4541, d = 13 472 us with it, 419 without.)
 template <int KS, int R, int TJ, int CH, bool PRECISE>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, KS <= 2 ? 8 : 2))) void k_lse_lowd_split(SplitArgs a)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, KS <= 2 || KS == 6 ? 8 : 2))) void k_lse_lowd_split(SplitArgs a)
 {
     lse_split_body<KS, R, TJ, CH, PRECISE>(a, blockIdx.x, blockIdx.y);
 }
@@ -788,7 +790,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(PC == 4 
 // same old potentials, so the row blocks of the f-pass (a0) and of the g-pass (a1) share a grid;
 // grid.y covers the larger of the two split counts.
 template <int KS, int R, int TJ, int CH, bool PRECISE>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, KS <= 2 ? 8 : 2))) void k_lse_lowd_split_pair(SplitArgs a0, SplitArgs a1)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, KS == 6 ? 8 : KS <= 2 ? 3 : 2))) void k_lse_lowd_split_pair(SplitArgs a0, SplitArgs a1)
 {
     const bool second = (int)blockIdx.x >= a0.row_blocks;   // uniform over the workgroup
     const SplitArgs &a = second ? a1 : a0;
