@@ -26,14 +26,21 @@
  *    reads back a few scalars (largest squared norm, size of the given
  *    potentials) that select the score arithmetic, fs_hvp reads back the scalars
  *    of its conjugate-gradient loop, and a call that has to grow the context's
- *    workspace synchronises once before the old workspace is released.
+ *    workspace synchronises once before the old workspace is released.  At d <= 3
+ *    and n m >= 3e8, half-steps and gradients may run through cell moments (see
+ *    FS_COMPUTE_FP32): dealing the points to cells reads back their number, once
+ *    for every eps that a call comes to, so an annealed solve waits for the passes
+ *    of a stage before it launches those of the next.
  *  - Errors are reported by status code only; nothing throws or aborts.
  *    Argument validation happens on the host before any launch.  The message
  *    of the last failure on a context is available from fs_last_error.
  *  - A context is not thread-safe; use one per thread/stream.
  *  - The library allocates device memory only for the context's workspace
  *    (derived copies of x and y, squared norms, bias vectors, partial
- *    reductions); it is grown on demand and released by fs_destroy.
+ *    reductions; the buffers of cell moments, 64 to 256 MB and 30 bytes a point,
+ *    where they are used, which is not where there is no memory for them); it is
+ *    grown on demand and released by fs_destroy.  fs_hvp keeps 64 bytes of pinned
+ *    host memory with the context.
  */
 #ifndef FLASHSINK_H
 #define FLASHSINK_H
@@ -70,6 +77,12 @@ typedef enum { FS_F32 = 0, FS_BF16 = 1 } fs_dtype;
  *                        contraction runs on the fp64 matrix cores, because at
  *                        |score| ~ 1e3 fp32 products cannot hold 1e-4 absolute.
  *                        Potentials agree with a float64 reference to 1e-4*eps.
+ *                        d <= 3, n m >= 3e8: half-steps of the alternating schedule and
+ *                        gradients for which fp32 scores would do run through cell moments
+ *                        (operands of 22 bits, fp32 sums) where that is faster: 5e-8 to 3e-7
+ *                        eps from 64 bits, nearer than fp32 scores (1e-7 to 3e-6) up to an
+ *                        eps of a tenth of the squared extent of the clouds, and 1e-7 to
+ *                        2e-7 instead of 2e-8 to 5e-8 beyond; "lowd_moments" switches it off.
  *  FS_COMPUTE_BF16_MFMA  x, y rounded to bfloat16 (RNE), products on the bf16 matrix
  *                        cores with fp32 accumulation; norms are taken from the
  *                        rounded points.  Needs d >= 16.  Agreement 2e-2*eps.
@@ -154,7 +167,7 @@ fs_status fs_solve(fs_ctx *ctx, const fs_problem *prob, float eps_start, float e
  * most 8 MiB (so a pass may be cut into fewer column splits than fs_solve would choose).  The call
  * performs no hipMalloc / hipFree and leaves the context's own workspace untouched.  Problems whose
  * workspace does not fit are refused with FS_ERR_BAD_SHAPE before anything is launched (n = m up to
- * 54272 at d = 3, 15360 at d = 16, 22528 at d = 64, 5120 at d = 1024 in bfloat16 mode).
+ * 54272 at d = 3, 16384 at d = 16, 22528 at d = 64, 5120 at d = 1024 in bfloat16 mode).
  * Every GPU holds ONE such array for the whole process: calls of this entry point that overlap in time
  * on one GPU -- from any context or stream -- race on it.  Nothing is assumed about its contents on
  * entry (it keeps what the previous call left).  Synchronises like fs_solve.
@@ -369,7 +382,8 @@ fs_status fs_points_release(fs_ctx *ctx);
  *                        application (fs_marginal_err and fs_ot_value always take float64-grade scores)
  *   "lowd_precise_valu"  1: float64-grade scores at d <= 3 on the vector ALU instead of the matrix cores
  *   "lowd_precise_any_bias"  1: those matrix-core records also for biases beyond their digit range
- *   "lowd_moments"       d <= 3: 1: half-steps and gradients through cell moments wherever the clouds allow it, 2: never
+ *   "lowd_moments"       d <= 3: 1: half-steps and gradients through cell moments wherever the clouds allow it (also where
+ *                        float64-grade scores would be taken, but for the two measurements above), 2: never
  *   "fx_any_size"        1: fixed-point scores (16 < d <= 128, FS_COMPUTE_FP32) for problems of any size
  *   "ws_limit"           the workspace gets at most this many bytes (0: what the device has), as if there were no more
  *   "fx_splits"          number of splits of the streamed side of a fixed-point pass, 0..1024

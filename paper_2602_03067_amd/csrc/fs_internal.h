@@ -30,16 +30,6 @@ inline int max_splits(size_t budget, int64_t n_res)
     return s < 1 ? 1 : (s > 1024 ? 1024 : (int)s);
 }
 
-// fp32-accurate scores on the bf16 matrix cores (low-d path).  A float v is the sum of three bf16
-// pieces v1 + v2 + v3 (each the bf16 rounding of what the previous ones leave).  A product c x_k y_k
-// is then the sum of the eight piece products of relative size >= 2^-24,
-//     x1 y1, x1 y2, x2 y1, x1 y3, x2 y2, x3 y1, x2 y3, x3 y2,
-// so a point is stored as one 16-byte "piece" of eight bf16 per coordinate:
-//     streamed role, coordinate k:  y1 y2 y1 y3 y2 y1 y3 y2      resident role:  x1 x1 x2 x1 x2 x3 x2 x3
-//     piece d (streamed):           b1 b2 b3  1  1  1  0  0      (resident):      1  1  1 m1 m2 m3  0  0
-// with b = the point's bias and m = minus the resident row's running max (an integer, exact in
-// three pieces).  One row of MFMA 32x32x16 steps over 16 ks = 8 (d + 1) padded slots then yields
-// score - max directly, with fp32 accumulation; measured error equals that of an fp32 FMA chain.
 // Direct global -> LDS loads (no registers in between): lane l's 16 (4) bytes land at
 // lds_off + 16 l (4 l); lds_off must be wave-uniform.  Issued as inline assembly so that the
 // compiler does not serialise them against the LDS reads of OTHER ring slots; completion is
@@ -76,10 +66,10 @@ __device__ inline void dma4s(const void *g_uniform, unsigned lane_off, unsigned 
 //     (p0, .) x (p0, .)                              word split_lead(ks, d) + k / 2
 // come before the bias (three pieces and a one for the running max: the last two words, see split_bias_words).  In this order
 // the sums are small until the last k-step or two, where the leading products meet the bias and what is left of both is small
-// again: the matrix cores round (and where they align a product, truncate) at the size of the sum so far.  Errors of half-steps and
-// short solves against 64 bits (n = 3001, m = 2500; normal and cube, d = 1 .. 16): 0.2 to 1.05 times, mostly 0.6 to 0.8 times,
-// those of eight products a coordinate in order
-// with the bias behind them; with the bias before them they were 1.0 to 2.6 times those.
+// again: the matrix cores round (and where they align a product, truncate) at the size of the sum so far.  Errors against 64 bits
+// (n = 3001, m = 2500; normal and cube, d = 1 .. 16) beside those of eight products a coordinate (p1 p2 and p2 p1 as well) in order with
+// the bias behind them: half-steps and short solves 0.16 to 0.99 times, mostly 0.6 to 0.8 times, gradients, which keep exponentials
+// to 2^-17, up to 1.05 times; with the bias before the products they were 1.0 to 2.6 times those.
 // Measured (both half-steps of an averaged iteration, n = m = 20011, d = 10): 8 d + 6 slots 157 us, 6 d + 4 131.  Three fp16
 // pieces, whose products carry more digits, took 140 us and a common scale of the coordinates; two of them 125 us, at 1.1 to 1.8 times
 // the errors.

@@ -245,7 +245,8 @@ template <bool PRECISE> __device__ __forceinline__ void put_max(bf8 &b, const fl
     } else
         b[7] = (__bf16)neg_m;
 }
-// the running max for scores up to mx: an integer at or above it that its slots hold exactly
+// the running max for scores up to mx: an integer at or above it that its slots hold exactly.  One bf16 slot has eight bits: beyond 256 the
+// max is up to 2^-7 of itself too high, 4 of the 126 base-2 units below it at |max| = 480 (see lowd_precise) and 15 for iterates at four times that.
 template <bool PRECISE> __device__ __forceinline__ float lifted_max(const float mx)
 {
     const float m = ceilf(mx);

@@ -19,12 +19,23 @@
 // exponential per pair.  Everything that a potential or a product of full coordinates enters is float64 up to a difference that is
 // small where it counts: biases against the largest of a block, cell pairs against the largest of a row cell.
 //
-// Error of a half-step in units of eps (rms, 64-bit sums on sampled rows): n = 50021, m = 40013, unit cube, eps = 0.05: 6e-8, of
-// which the float output is 1e-8; over the pairs with fp32 scores 2.7e-7.  Mixture, eps = 0.01: 2e-7 against 2.5e-6.
+// What is held in fewer bits than over the pairs: weights, monomials and moments (22 bits there), and the series (3e-8).  Exponents are
+// floats of at most 48 (points of a cell) and 96 (rows) in size, differences that are no larger than the scores of the pairs.  So
+// moments stand for fp32 scores only; where float64-grade ones are asked for (lowd_precise, and every measurement) passes run over
+// the pairs.  Errors of a half-step in units of eps (rms of f and of g against 64 bits; n = 20021, m = 18013) here, over the pairs with
+// fp32 scores, and what rounding f to float costs:
+//     d = 3, cube     eps 0.01 1.3e-7 7e-8   2.6e-6 2.6e-6   1.1e-7      d = 2, cube     eps 0.01 1.4e-7 1.0e-7  1.9e-6 1.9e-6   1.1e-7
+//                     0.03     1.0e-7 5e-8   2.3e-7 2.1e-7   0.9e-7                      0.03     1.1e-7 0.9e-7  2.1e-7 1.9e-7   0.7e-7
+//                     0.1      0.9e-7 6e-8   1.1e-7 0.8e-7   0.6e-7                      0.1      0.8e-7 0.6e-7  0.9e-7 0.6e-7   0.4e-7
+//                     1        0.7e-7 8e-8   0.5e-7 0.3e-7   0.1e-7                      1        0.6e-7 1.0e-7  0.5e-7 0.3e-7   0.1e-7
+//             mixture 0.01     3.1e-7 9e-8   2.2e-6 2.7e-6   2.9e-7              mixture 0.01     2.7e-7 1.0e-7  1.7e-6 1.7e-6   2.5e-7
+//             normal  0.3      1.5e-7 7e-8   4.2e-7 4.1e-7   1.4e-7              normal  0.3      1.5e-7 1.3e-7  3.4e-7 3.8e-7   1.0e-7
+// so they are nearer up to an eps of about a tenth of the squared extent, and beyond it (where a cloud is a few cells and nothing averages) off by
+// 1e-7 to 2e-7 instead of 2e-8 to 5e-8.  A spare monomial with what two pieces leave of the moment of degree 0 did not change that.
 // Sums are formed in a fixed order (the sort is stable), so a result does not depend on the run.
 //
-// Measured (half-step, us, over the pairs and here): n = m = 262144, d = 3, mixture and cube, eps = 0.01: 6000 -> 1950, 0.046: 6000
-// -> 270, 1: 6000 -> 80; n = 50021, m = 40013, cube, eps = 0.05: 219 -> 58.
+// Measured (half-step, us, over the pairs and here): n = m = 262144, d = 3, mixture and cube, eps = 0.01: 5900 -> 1950, 0.046: 5900
+// -> 270, 1: 5900 -> 80; n = 50021, m = 40013, cube, eps = 0.05: 219 -> 57.
 // Bound at large sizes: vector and matrix instructions of k_mom_gather (a weight costs its exponential, three fma and the split, 130
 // instructions per 16 points and 32 cells beside 42 products at RT = 7), moments through LDS in k_mom_rows; at small ones
 // latency, both kernels take 8 us without their loops.
@@ -359,7 +370,7 @@ struct GatherArgs {
     int d, kind;
     int rt, tsplit;              // tiles of monomials, and over how many workgroups they are spread
     int halves;                  // see k_mom_gather
-    const float *V;              // applications: the values; moments of 1 and of each column
+    const float *V;              // applications: the values, of any size; moments of 1 and of each column
     int64_t ldv;
     float *ex;                   // [1 + columns][cells of the launch][nblock] power of two of the moments, -inf: all are zero
     unsigned char *M;            // [1 + columns][cells of the launch][nblock] moments: 32 RT leading pieces, then 32 RT trailing ones

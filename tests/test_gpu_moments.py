@@ -1,6 +1,7 @@
-"""GPU parity of the half-steps and gradients through cell moments (d <= 3) against the float64 oracle.
+"""GPU parity of the half-steps and gradients through cell moments (d <= 3) against the float64 oracle, where they are left out, and
+what they hold.
 
-The passes are forced with the context's "lowd_moments" switch, so that small clouds reach every part of them: cells of several
+The passes are mostly forced with the context's "lowd_moments" switch, so that small clouds reach every part of them: cells of several
 blocks, more streamed cells than one segment, several launches, ragged groups of rows, empty cells, one-cell clouds.
 
 Tolerance of a half-step in units of eps (= relative error of a row sum): the series of e^t is off by 3e-8, monomials, weights and
