@@ -1090,8 +1090,9 @@ fs_status mom_ready(Ctx *c, const Prepared *P, double eps, int t, bool *use)
     if (c->dbg_lowd_moments == 0 && (c->dbg_lowd_score || c->dbg_lowd_splits || c->dbg_lowd_precise_valu)) return FS_OK;
     // Moments stand for passes over the pairs with fp32 scores.  Where float64-grade ones are asked for they are not accurate enough:
     // after 50 iterations at n = 3000, m = 2500 in the unit cube at eps = 0.005 f and g are off by 4e-7 eps and, over the pairs, by
-    // 2e-7 and 7e-8 (d = 3), after 1000 at d = 1 by 3.5e-6 and 5e-8.  (The switch that forces moments does so for solves and
-    // gradients of any size, measurements are never taken through them.)
+    // 2e-7 and 7e-8 (d = 3), after 1000 at d = 1 by 3.5e-6 and 5e-8; the dual value (unit cube, d = 2 and 3, eps = 0.03 to 0.1, n m = 6e8 to
+    // 5e9) is off by up to 2e-8 of itself and by 2e-9, marginal errors by up to 3e-8 and 6e-10.  (The switch that forces moments does so
+    // for solves and gradients of any size, measurements are never taken through them.)
     if (P->force_precise || (c->dbg_lowd_moments == 0 && lowd_precise(P, eps))) return FS_OK;
     if (S.eps == eps) {
         *use = S.on;
