@@ -37,10 +37,10 @@
  *  - A context is not thread-safe; use one per thread/stream.
  *  - The library allocates device memory only for the context's workspace
  *    (derived copies of x and y, squared norms, bias vectors, partial
- *    reductions; the buffers of cell moments, 64 to 256 MB and 30 bytes a point,
- *    where they are used, which is not where there is no memory for them); it is
- *    grown on demand and released by fs_destroy.  fs_hvp keeps 64 bytes of pinned
- *    host memory with the context.
+ *    reductions; the buffers of cell moments, 64 to 256 MB, tables of up to 40 MB
+ *    and 22 bytes a point, where they are used, which is not where there is no
+ *    memory for them); it is grown on demand and released by fs_destroy.  fs_hvp
+ *    keeps 64 bytes of pinned host memory with the context.
  */
 #ifndef FLASHSINK_H
 #define FLASHSINK_H
@@ -80,7 +80,7 @@ typedef enum { FS_F32 = 0, FS_BF16 = 1 } fs_dtype;
  *                        d <= 3, n m >= 3e8: half-steps of the alternating schedule and
  *                        gradients for which fp32 scores would do run through cell moments
  *                        (operands of 22 bits, fp32 sums) where that is faster: 5e-8 to 3e-7
- *                        eps from 64 bits, nearer than fp32 scores (1e-7 to 3e-6) up to an
+ *                        eps (rms) from 64 bits, nearer than fp32 scores (1e-7 to 3e-6) up to an
  *                        eps of a tenth of the squared extent of the clouds, and 1e-7 to
  *                        2e-7 instead of 2e-8 to 5e-8 beyond; "lowd_moments" switches it off.
  *  FS_COMPUTE_BF16_MFMA  x, y rounded to bfloat16 (RNE), products on the bf16 matrix

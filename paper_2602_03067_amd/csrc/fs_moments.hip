@@ -20,7 +20,8 @@
 // small where it counts: biases against the largest of a block, cell pairs against the largest of a row cell.
 //
 // What is held in fewer bits than over the pairs: weights, monomials and moments (22 bits there), and the series (3e-8).  Exponents are
-// floats of at most 48 (points of a cell) and 96 (rows) in size, differences that are no larger than the scores of the pairs.  So
+// floats of at most 48 (points of a cell) and 96 (rows) in size, differences that are no larger than the scores of the pairs and round no
+// more (2e-6 and 4e-6 of a term at most).  So
 // moments stand for fp32 scores only; where float64-grade ones are asked for (lowd_precise, and every measurement) passes run over
 // the pairs.  Errors of a half-step in units of eps (rms of f and of g against 64 bits; n = 20021, m = 18013) here, over the pairs with
 // fp32 scores, and what rounding f to float costs:

@@ -6,7 +6,9 @@ blocks, more streamed cells than one segment, several launches, ragged groups of
 
 Tolerance of a half-step in units of eps (= relative error of a row sum): the series of e^t is off by 3e-8, monomials, weights and
 moments are kept to 2^-22, and a row in a corner of its cell can lose e^(2 tau) = 14 of that to cancellation: 14 (3e-8 + 3 2^-22) =
-1.1e-5; the float output adds |f| 2^-24 / eps.
+1.1e-5; the float output adds |f| 2^-24 / eps.  The exponents are floats as well: up to 18 between the points of a cell and 36 between
+its rows and a cell in the clouds of this file, which adds up to 54 ln2 2^-24 = 2e-6 where one term makes a row and is left to the slack
+of the bound above (they may reach 48 and 96, with the scores: fp32 scores of that size round as much).
 """
 import numpy as np
 import pytest
