@@ -30,16 +30,20 @@
 // fragments in lane order ([tile of 32 points][k-step of 32][digit][64 lanes][16 bytes]), so LDS is
 // filled by linear direct loads and read without bank conflicts.
 //
-// A workgroup is four waves = 128 resident rows (their digits stay in registers) over a run of
-// streamed tiles that pass through an LDS ring; two workgroups per CU, one where two rings do not fit (fx_wg_per_cu).
+// A workgroup is four waves = 128 resident rows (their digits stay in registers) over a run of streamed tiles that pass
+// through an LDS ring.  In the half-steps, and in applications on the vector ALU, three workgroups share a CU: a wave alone issues a vector
+// instruction every 2.5 ns, two of a SIMD 1.3 (full rate; 2.1 for conversions, shifts by an immediate, three-way maxima and
+// whatever reads a scalar register), three or four 1.0 (1.9), and an MFMA of 13.6 ns hides behind those of other waves.  With two
+// workgroups a CU ran the MFMAs and the vector work of its waves one after the other (matrix pipe busy 46 %, vector ALU 52 %).
+// 168 registers for that: sums of one weight are shifted before the next ones join them (32 accumulators at a time
+// instead of 48), the leading products come first and the tile's digits are held only as far as LDS reads would be the bound
+// (FxShape::kHold).  Half-step with its merge, two and three workgroups (us): n = m = 10000, d = 64, ten products 81.5 / 76.2,
+// thirteen 89.4 / 86.1; n = m = 16384, d = 64 181 / 173 and 212 / 203; n = m = 10000, d = 128 134 / 120.  Four workgroups at d = 64 took
+// 78.5, and 228 at n = m = 16384 with thirteen products (spills).
 //
-// Bound: matrix and vector instructions together, which do not hide behind each other with these operands.  A loop of
-// nothing but this MFMA takes 15.6 ns per instruction and SIMD with constant operands and 20 with random ones; with seven
-// vector instructions after two of every three MFMAs 17.7 and 24 (whether they come from the same wave or another), so the
-// chip's power is what runs out.  A tile of 32 x 32 scores at d = 64 is 20 or 26 MFMAs and about 190 vector instructions:
-// 700 to 800 ns (counters: matrix pipe busy 46 %, vector ALU 48 %, clock 2.0 GHz).
-// Tried without gain: tile g + 1's MFMAs interleaved with tile g's vector work in one wave (216-226 us
-// against 211 at n = m = 16384, d = 64), three workgroups per CU, digits read from LDS twice instead of held.
+// Bound: matrix and vector instructions, and with them the chip's power: a tile of 32 x 32 scores at d = 64 is 20 or 26 MFMAs and about
+// 175 vector instructions; at n = m = 16384 a CU takes 305000 cycles for a ten-product half-step at 1.85 GHz, and with all points but
+// two at zero 283000 at 2.19 GHz.
 // Measured (half-step with its merge, us, fp64 and here; the other kernel's empty launch included): n = m = 10000, d = 64:
 // 232 -> 81 (ten products); n = m = 16384, d = 64: 577 -> 217 (thirteen); n = 9973, m = 12007, d = 128: 545 -> 156 (ten);
 // n = 9973, m = 12007, d = 20: 71 (ten).
@@ -111,11 +115,13 @@ constexpr int fx_stage_bytes(int ks, int mode, int nc)
     return ks * 4096 + kRecBytes + (mode == 0 ? 0 : mode == 1 ? (nc + 1) / 2 * 256 : nc * 6 * 1024);
 }
 constexpr int fx_stages(int stage_bytes) { return stage_bytes <= 13 * 1024 ? 4 : 3; }
-// Workgroups per CU: two where two rings fit the 160 KB of LDS, which the widest applications do not (four column blocks
-// at any d, three at d > 64, two at d > 96).  HAD: one, the second set of resident digits takes the registers.
+// Workgroups per CU.  Half-steps and applications on the vector ALU: three (see the header).  Products on the matrix cores: two where two rings fit the 160 KB of LDS, which the widest applications
+// do not (four column blocks at any d, three at d > 64, two at d > 96).  HAD: one, the second set of resident digits takes the
+// registers.
 constexpr int fx_wg_per_cu(int ks, int mode, int nc, bool had)
 {
     const int stage = fx_stage_bytes(ks, mode, nc);
+    if (mode < 2) return 3;
     return had || 2 * fx_stages(stage) * stage > 160 * 1024 ? 1 : 2;
 }
 template <int KS, int MODE, int NC, bool HAD = false> struct FxShape {
@@ -125,7 +131,8 @@ template <int KS, int MODE, int NC, bool HAD = false> struct FxShape {
     static constexpr int kLoads = KS + 1 + (MODE == 0 ? 0 : MODE == 1 ? 1 : (NC * 6 + 3) / 4);
     static constexpr int kWgPerCu = fx_wg_per_cu(KS, MODE, NC, HAD);
     static constexpr int kPC = MODE == 2 ? 32 * NC : NC;
-    static constexpr bool kHold = KS <= 2;
+    // digits of a tile that stay in registers while it lasts: all of them, or the leading two, or none
+    static constexpr int kHold(bool full) { return KS <= 2 ? 4 : KS == 3 || !full ? 2 : 0; }
 };
 
 template <int KS, int MODE, int NC, bool FULL, bool HAD = false>
@@ -144,7 +151,8 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
     const unsigned l16 = l * 16, l4 = l * 4;
 
     const double u3d = a.gate.unit(22), u5d = a.gate.unit(38);
-    const float u3 = (float)u3d, u5 = (float)u5d;
+    float u3 = (float)u3d, u5 = (float)u5d;
+    asm volatile("" : "+v"(u3), "+v"(u5));   // (an instruction that reads a scalar register takes twice the time)
     const int lazy = (int)fmin(4.0 / u3d, 1073741824.0);   // see settle
 
     int issued = 0;
@@ -246,73 +254,105 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
 
     // ---- scores of a tile: the digit products ------------------------------------------------------------------
     struct Tile {
-        i16v H, P, Q;
-        int kind;   // of the tile: 0 whole, 1 flagged, 2 with points without weight
+        i16v H, L;
+        i4 av[KS][4];   // digits of the streamed points
+        int kind;       // of the tile: 0 whole, 1 flagged, 2 with points without weight
     };
-#define FX_MM(ACC, I, J) T.ACC = __builtin_amdgcn_mfma_i32_32x32x32_i8(av[S::kHold ? ks : 0][I], b[ks][J], T.ACC, 0, 0, 0)
-    // (beyond two k-steps the digits of the streamed points are read from LDS once per phase instead of held)
-#define FX_DIGITS(KS_)                                                                                                     \
-    if constexpr (!S::kHold) {                                                                                             \
-        _Pragma("unroll") for (int dg = 0; dg < 4; ++dg) av[0][dg] = *reinterpret_cast<const i4 *>(fr + (KS_ * 4 + dg) * 1024); \
-    }
-    auto contract = [&](const unsigned char *sb, Tile &T) __attribute__((always_inline)) {
-        const int *rec = reinterpret_cast<const int *>(sb + KS * 4096);
-        const unsigned char *fr = sb + l16;
-        i4 av[S::kHold ? KS : 1][4];
-        if constexpr (S::kHold) {
+#define FX_MM(ACC, I, J) ACC = __builtin_amdgcn_mfma_i32_32x32x32_i8(T.av[ks][I], b[ks][J], ACC, 0, 0, 0)
+    auto digits = [&](const unsigned char *sb, Tile &T, int ks, int first, int last) __attribute__((always_inline)) {
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-                for (int dg = 0; dg < 4; ++dg) av[ks][dg] = *reinterpret_cast<const i4 *>(fr + (ks * 4 + dg) * 1024);
-        }
+        for (int dg = first; dg <= last; ++dg) T.av[ks][dg] = *reinterpret_cast<const i4 *>(sb + l16 + (ks * 4 + dg) * 1024);
+    };
+    auto biases = [&](const unsigned char *sb, int which) __attribute__((always_inline)) {
+        const int *rec = reinterpret_cast<const int *>(sb + KS * 4096) + 32 * which + 4 * lh;
+        i16v v;
 #pragma unroll
         for (int g4 = 0; g4 < 4; ++g4) {
-            const i4 v0 = *reinterpret_cast<const i4 *>(rec + 8 * g4 + 4 * lh);
-            const i4 v1 = *reinterpret_cast<const i4 *>(rec + 32 + 8 * g4 + 4 * lh);
-            const i4 v2 = FULL ? *reinterpret_cast<const i4 *>(rec + 64 + 8 * g4 + 4 * lh) : i4{0, 0, 0, 0};
+            const i4 q = *reinterpret_cast<const i4 *>(rec + 8 * g4);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                T.H[4 * g4 + q] = v0[q];
-                T.Q[4 * g4 + q] = v1[q];
-                T.P[4 * g4 + q] = v2[q];
-            }
+            for (int z = 0; z < 4; ++z) v[4 * g4 + z] = q[z];
         }
-        T.kind = __builtin_amdgcn_readfirstlane(rec[96]);
-        if constexpr (FULL) {
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                FX_DIGITS(ks)
-                FX_MM(P, 3, 1);
-                FX_MM(P, 2, 2);
-                FX_MM(P, 1, 3);
-            }
-#pragma unroll
-            for (int r = 0; r < 16; ++r) T.P[r] = T.P[r] >> 8;
-        }
+        return v;
+    };
+    auto contract_high = [&](const unsigned char *sb, Tile &T) __attribute__((always_inline)) {
+        T.kind = __builtin_amdgcn_readfirstlane(reinterpret_cast<const int *>(sb + KS * 4096)[96]);
+        T.H = biases(sb, 0);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            FX_DIGITS(ks)
-            FX_MM(H, 0, 0);
-            FX_MM(Q, 2, 0);
-            FX_MM(Q, 1, 1);
-            FX_MM(Q, 0, 2);
+            digits(sb, T, ks, 0, 1);
+            FX_MM(T.H, 0, 0);
         }
 #pragma unroll
         for (int r = 0; r < 16; ++r)   // (wraps are undone by what follows: only the difference counts)
             T.H[r] = (int)(((unsigned)T.H[r] << 8) + (unsigned)nhm);
-        if constexpr (!S::kHold) asm volatile("" : "+v"(fr));
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            FX_DIGITS(ks)
-            FX_MM(H, 0, 1);
-            FX_MM(H, 1, 0);
-            FX_MM(P, 0, 3);
-            FX_MM(P, 1, 2);
-            FX_MM(P, 2, 1);
-            FX_MM(P, 3, 0);
+            FX_MM(T.H, 0, 1);
+            FX_MM(T.H, 1, 0);
         }
     };
-#undef FX_DIGITS
+    auto contract_low = [&](const unsigned char *sb, Tile &T) __attribute__((always_inline)) {
+        constexpr int HOLD = S::kHold(FULL);
+        if constexpr (FULL && HOLD < 4) {
+            // one pass over the digits, three accumulators
+            i16v P = biases(sb, 2), Q = biases(sb, 1);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) T.L[r] = 0;
+            if constexpr (HOLD == 0) asm volatile("" : "+s"(sb));   // (read again rather than kept)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                digits(sb, T, ks, HOLD, 3);
+                FX_MM(P, 3, 1);
+                FX_MM(Q, 2, 0);
+                FX_MM(T.L, 0, 3);
+                FX_MM(P, 2, 2);
+                FX_MM(Q, 1, 1);
+                FX_MM(T.L, 1, 2);
+                FX_MM(P, 1, 3);
+                FX_MM(Q, 0, 2);
+                FX_MM(T.L, 2, 1);
+                FX_MM(T.L, 3, 0);
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) T.L[r] = (int)(((unsigned)Q[r] << 8) + (unsigned)T.L[r] + (unsigned)(P[r] >> 8));
+        } else {
+            // sums of one weight are shifted before those of the next one join them: fewer accumulators at a time
+            i16v P;
+            if constexpr (HOLD == 4) {
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) digits(sb, T, ks, 2, 3);
+            }
+            if constexpr (FULL) {
+                P = biases(sb, 2);
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    FX_MM(P, 3, 1);
+                    FX_MM(P, 2, 2);
+                    FX_MM(P, 1, 3);
+                }
+            }
+            T.L = biases(sb, 1);
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                if constexpr (HOLD < 4) digits(sb, T, ks, 2, 2);
+                FX_MM(T.L, 2, 0);
+                FX_MM(T.L, 1, 1);
+                FX_MM(T.L, 0, 2);
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                T.L[r] = FULL ? (int)(((unsigned)T.L[r] << 8) + (unsigned)(P[r] >> 8)) : (int)((unsigned)T.L[r] << 8);
+            if constexpr (HOLD < 4) asm volatile("" : "+s"(sb));
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                if constexpr (HOLD < 4) digits(sb, T, ks, 2, 3);
+                FX_MM(T.L, 0, 3);
+                FX_MM(T.L, 1, 2);
+                FX_MM(T.L, 2, 1);
+                FX_MM(T.L, 3, 0);
+            }
+        }
+    };
 #undef FX_MM
 
     // ---- before the exponentials of tile g: the slow path of a tile, and the lift of the max ------------------
@@ -329,24 +369,23 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
 #pragma unroll
         for (int r = 0; r < 16; ++r) T.H[r] = none >> (8 * (r >> 2) + (r & 3)) & 1 ? INT32_MIN : T.H[r];
     };
-    auto far_tile = [&](int g, Tile &T) __attribute__((always_inline)) {
-        // float64 scores (the record of a flagged tile holds no bias); what they leave above the max is handed on in the
-        // same two-integer form, units 2^-16 and 2^-32
+    auto far_tile = [&](int g, const Tile &T, float (&e)[16]) __attribute__((always_inline)) {
+        // float64 scores (the record of a flagged tile holds no bias)
         const double *bd = a.bias + ((int64_t)(t_begin + g)) * 32 + 4 * lh;
-        const unsigned back = 0u - (unsigned)nhm;
+        unsigned back = 0u - (unsigned)nhm;
         // (the record's biases are in where the tile is not flagged, but for points without weight)
         const unsigned add = T.kind == 1 ? 0xffffffffu : T.kind == 2 ? none_of_lane(g) : 0u;
-        double u3x = u3d;
         auto score = [&](int r) __attribute__((always_inline)) {
-            const int Ha = (int)((unsigned)T.H[r] + back);
-            const int L = (int)(((unsigned)T.Q[r] << 8) + (unsigned)T.P[r]);
-            const double v = fma((double)L, u5d, (double)Ha * u3x);
+            const double v = fma((double)T.L[r], u5d, (double)(int)((unsigned)T.H[r] + back) * u3d);
             return add >> (8 * (r >> 2) + (r & 3)) & 1 ? v + bd[8 * (r >> 2) + (r & 3)] : v;
         };
         float mx = kNegInit;
         double seen = s;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, (float)score(r));
+        for (int r = 0; r < 16; ++r) {
+            mx = fmaxf(mx, (float)score(r));
+            asm volatile("" : "+v"(mx));   // (one after the other)
+        }
         if constexpr (MODE == 2) {   // m is common to the two lane halves
             mx = fmaxf(mx, __shfl_xor(mx, 32));
             seen = fmax(s, __shfl_xor(s, 32));
@@ -362,16 +401,15 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
             far = out;
             mfar = mx;
         }
-        asm volatile("" : "+v"(u3x));   // (the scores are formed anew rather than kept in 32 registers)
         bool nan = false;
+        asm volatile("" : "+v"(back));   // (the scores are formed anew rather than kept in 32 registers)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const double v = score(r) - md;
             nan = nan || v != v;
-            const double c = fmax(v, -30000.0) * 65536.0, h = floor(c);
-            T.H[r] = (int)h;
-            T.P[r] = (int)((c - h) * 65536.0);
-            T.Q[r] = 0;
+            float x = (float)fmax(v, -30000.0);
+            asm volatile("" : "+v"(x));
+            e[r] = fast_exp2(x);
         }
         // (MODE 2: a lane's outputs are columns, half of them, while the NaN score is in one lane half: common to the two)
         if constexpr (MODE == 2) {
@@ -391,8 +429,7 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
     // rounded by 2^-23); in MODE 2 both lane halves move together, since the second MFMA sums over them.  The factor of the old sums is a
     // rounded power: what it is off by counts with the weight 2^(old m - new m) of those sums, at most 3e-8 of the new one.
     // (masked: a tile with points without weight)
-    auto settle = [&](int g, Tile &T, auto masked) __attribute__((always_inline)) {
-        if constexpr (decltype(masked)::value) mask_none(g, T);
+    auto settle = [&](int g, Tile &T) __attribute__((always_inline)) {
         int hx = T.H[0];
 #pragma unroll
         for (int r = 1; r < 16; ++r) hx = max(hx, T.H[r]);
@@ -407,18 +444,20 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
             nhm -= dh;
 #pragma unroll
             for (int r = 0; r < 16; ++r) T.H[r] = (int)((unsigned)T.H[r] - (unsigned)dh);
-            if constexpr (decltype(masked)::value) mask_none(g, T);   // (the subtraction has wrapped)
+            if (MODE != 2 && T.kind == 2) mask_none(g, T);   // (the subtraction has wrapped)
         }
     };
-    // ---- exponentials of tile g (score - m = u3v H + u5v L), their sum and what they are applied to -----------
-    auto finish = [&](int g, const unsigned char *sb, const Tile &T, const float u3v, const float u5v) __attribute__((always_inline)) {
+    // ---- exponentials of a tile, score - m = u3 H + u5 L ------------------------------------------------------
+    auto exponentials = [&](const Tile &T, float (&e)[16]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) e[r] = fast_exp2(fmaf((float)T.L[r], u5, (float)T.H[r] * u3));
+    };
+    // ---- their sum and what they are applied to ----------------------------------------------------------------
+    auto finish = [&](int g, const unsigned char *sb, float (&e)[16]) __attribute__((always_inline)) {
         const unsigned char *vals = sb + KS * 4096 + kRecBytes;
-        float e[16];
         float s0 = 0.0f, s1 = 0.0f;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const int L = (int)(((unsigned)T.Q[r] << 8) + (unsigned)T.P[r]);
-            e[r] = fast_exp2(fmaf((float)L, u5v, (float)T.H[r] * u3v));
             if (r & 1)
                 s1 += e[r];
             else
@@ -562,28 +601,19 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
         if (issued < G) issue();     // into the predecessor's slot
         const unsigned char *sb = ring + (g % NS) * S::kStage;
         Tile T;
-        contract(sb, T);
-        float u3v = u3, u5v = u5;
-        // (Whole tiles, and those with points without weight, have code copies of their own: where the others' scores join
-        // theirs, the compiler moves all of them from one set of registers to another in every tile, 3 % of a half-step.  In
-        // MODE 2 the copies would spill, and points without weight take the float64 epilogue.)
-        const bool near = !__any(far);
-        if (__builtin_expect(T.kind == 0 && near, 1)) {
-            settle(g, T, std::bool_constant<false>{});
-            if constexpr (MODE != 2) {
-                finish(g, sb, T, u3, u5);
-                continue;
-            }
-        } else if (MODE != 2 && T.kind == 2 && near) {
-            settle(g, T, std::bool_constant<true>{});
-            finish(g, sb, T, u3, u5);
-            continue;
-        } else {
-            far_tile(g, T);
-            u3v = 1.52587890625e-05f;
-            u5v = 2.3283064365386963e-10f;
+        contract_high(sb, T);
+        float e[16];
+        const bool direct = T.kind != 1 && (MODE != 2 || T.kind == 0) && !__any(far);
+        if (direct) {
+            if (MODE != 2 && T.kind == 2) mask_none(g, T);
+            settle(g, T);
         }
-        finish(g, sb, T, u3v, u5v);
+        contract_low(sb, T);
+        if (__builtin_expect(direct, 1))
+            exponentials(T, e);
+        else
+            far_tile(g, T, e);
+        finish(g, sb, e);
     }
 
     // merge the two lane halves of every resident row
@@ -765,7 +795,7 @@ PassShape fx_shape(const Ctx *c, int64_t n_res, int64_t n_str, int occ)
         if ((int)ceil_div(n_tiles, tps) != sp) continue;
         const int64_t wg = ceil_div((int64_t)s.row_blocks * sp, (int64_t)c->num_cu);
         const int rem = (int)(wg % occ);
-        const double units = (double)(wg - rem) + (rem ? 2.0 : 0.0);
+        const double units = (double)(wg - rem) + (rem == 0 ? 0.0 : rem == 1 ? 2.0 : 2.6);
         const double cost = units * ((double)tps + startup) + 0.05 * sp;
         if (best == 0.0 || cost < best * 0.995) {
             best = cost;
