@@ -145,7 +145,7 @@ double stage_eps(double e0, double e1, int stages, int s)
 
 // Lay the prepared problem out in the workspace; returns bytes needed.  With base == nullptr
 // only the size is computed.
-size_t layout_with(const Ctx *c, const fs_problem *p, Prepared *P, char *base, size_t extra, int fx_ks)
+size_t layout_with(const Ctx *c, const fs_problem *p, Prepared *P, char *base, size_t extra, int fx_ks, bool seeds)
 {
     Arena A;
     P->path = choose_path(p);
@@ -227,6 +227,14 @@ size_t layout_with(const Ctx *c, const fs_problem *p, Prepared *P, char *base, s
     if (P->mom.bytes >= c->mom_denied) P->mom.bytes = 0;
     o = A.take(P->mom.bytes);
     P->mom.base = base && P->mom.bytes ? base + o : nullptr;
+    P->seeds = Prepared::Seeds();
+    for (int t = 0; t < 2 && P->fx_ks && seeds && P->want_seeds; ++t) {
+        P->seeds.bytes[t] = fx_seed_bytes(t == 0 ? P->X.cnt_pad : P->Y.cnt_pad);
+        for (int k = 0; k < 2; ++k) {
+            o = A.take(P->seeds.bytes[t]);
+            P->seeds.buf[t][k] = base ? base + o : nullptr;
+        }
+    }
     o = A.take(extra);
     (void)o;
     return A.off;
@@ -241,9 +249,10 @@ size_t layout(const Ctx *c, const fs_problem *p, Prepared *P, char *base, size_t
     // ten iterations 4660 / 4703 at n = m = 10000.
     const bool worth = (double)p->n * (double)p->m * (double)p->d >= 4.0e8 || c->dbg_fx_any_size;
     const int ks = choose_path(p) == Path::F64 && worth ? fx_ksteps(p->d) : 0;
-    // digit images are left out where only the problem without them fits the static scratch array
-    if (ks && c->ws_static && layout_with(c, p, P, nullptr, extra, ks) > c->ws_bytes) return layout_with(c, p, P, base, extra, 0);
-    return layout_with(c, p, P, base, extra, ks);
+    // seeds, and then digit images, are left out where only the problem without them fits the static scratch array
+    if (ks && c->ws_static && layout_with(c, p, P, nullptr, extra, ks, true) > c->ws_bytes)
+        return layout_with(c, p, P, base, extra, layout_with(c, p, P, nullptr, extra, ks, false) > c->ws_bytes ? 0 : ks, false);
+    return layout_with(c, p, P, base, extra, ks, true);
 }
 
 fs_status ensure_ws(Ctx *c, size_t need)
@@ -277,6 +286,12 @@ fs_status prepare(Ctx *c, const fs_problem *p, Prepared *P, size_t extra, char *
     fs_status st = ensure_ws(c, need);
     if (st == FS_ERR_ALLOC && P->mom.bytes) {   // the passes over the pairs need less (and later calls on clouds as large don't ask)
         c->mom_denied = P->mom.bytes;
+        c->err.clear();
+        need = layout(c, p, P, nullptr, extra);
+        st = ensure_ws(c, need);
+    }
+    if (st == FS_ERR_ALLOC && P->seeds.bytes[0]) {
+        P->want_seeds = false;
         c->err.clear();
         need = layout(c, p, P, nullptr, extra);
         st = ensure_ws(c, need);
@@ -681,6 +696,7 @@ static fs_status solve_impl(Ctx *c, const fs_problem *prob, float eps_start, flo
 
     Prepared P;
     P.mom.passes = P.halfsteps_per_eps = 2 * iters_per_stage;
+    P.want_seeds = n_stages * (int64_t)iters_per_stage > 1;
     if ((st = prepare(c, prob, &P, 0, nullptr)) != FS_OK) return st;
     double eps0 = stage_eps(eps_start, eps_end, n_stages, 0);
     if ((st = launch_bias_from_user(c, &P, &P.Y, g, eps0)) != FS_OK) return st;
@@ -802,6 +818,7 @@ fs_status fs_solve_tol(fs_ctx *ctx, const fs_problem *prob, float eps_in, int32_
     const double eps = (double)eps_in;
     Prepared P;
     P.mom.passes = P.halfsteps_per_eps = 2 * max_iters;
+    P.want_seeds = max_iters > 1;
     char *extra = nullptr;
     if ((st = prepare(c, prob, &P, (size_t)prob->n * 8, &extra)) != FS_OK) return st;
     double *f_before = reinterpret_cast<double *>(extra);   // f of the last completed iteration at a check
@@ -867,6 +884,7 @@ fs_status fs_solve_symmetric(fs_ctx *ctx, const fs_problem *prob, float eps_in, 
     const double eps = (double)eps_in;
     Prepared P;
     P.halfsteps_per_eps = 2 * iters;
+    P.want_seeds = iters > 1;
     // Both passes of an iteration read the old potentials, so the second one must not overwrite
     // the split partials of the first before they are merged: it gets a partial buffer of its own.
     Prepared sizing;

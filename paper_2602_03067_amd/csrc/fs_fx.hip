@@ -31,22 +31,26 @@
 // filled by linear direct loads and read without bank conflicts.
 //
 // A workgroup is four waves = 128 resident rows (their digits stay in registers) over a run of streamed tiles that pass
-// through an LDS ring.  In the half-steps, and in applications on the vector ALU, three workgroups share a CU: a wave alone issues a vector
-// instruction every 2.5 ns, two of a SIMD 1.3 (full rate; 2.1 for conversions, shifts by an immediate, three-way maxima and
-// whatever reads a scalar register), three or four 1.0 (1.9), and an MFMA of 13.6 ns hides behind those of other waves.  With two
-// workgroups a CU ran the MFMAs and the vector work of its waves one after the other (matrix pipe busy 46 %, vector ALU 52 %).
-// 168 registers for that: sums of one weight are shifted before the next ones join them (32 accumulators at a time
-// instead of 48), the leading products come first and the tile's digits are held only as far as LDS reads would be the bound
-// (FxShape::kHold).  Half-step with its merge, two and three workgroups (us): n = m = 10000, d = 64, ten products 81.5 / 76.2,
-// thirteen 89.4 / 86.1; n = m = 16384, d = 64 181 / 173 and 212 / 203; n = m = 10000, d = 128 134 / 120.  Four workgroups at d = 64 took
-// 78.5, and 228 at n = m = 16384 with thirteen products (spills).
+// through an LDS ring; two workgroups per CU, one where two rings do not fit, three in MODE 3 (fx_wg_per_cu).
 //
-// Bound: matrix and vector instructions, and with them the chip's power: a tile of 32 x 32 scores at d = 64 is 20 or 26 MFMAs and about
-// 175 vector instructions; at n = m = 16384 a CU takes 305000 cycles for a ten-product half-step at 1.85 GHz, and with all points but
-// two at zero 283000 at 2.19 GHz.
+// Long half-steps (MODE 3).  Where the scores of a row spread over hundreds of base-2 units, few tiles hold a point that counts
+// (shifted normal points, n = m = 16384, d = 64, eps = 0.1: one tile of four holds a pair within 60 units of its row's largest).  The three
+// leading products of a tile say so: a tile none of whose scores comes near m is left at them, with 7 or 10 of its products,
+// the conversions and the exponentials undone.  m must be near the row's largest from the first tile on for that: it starts at the
+// score, at the biases of this pass, of a point that the last pass over these rows in the same call found (FxSeed), which bounds
+// the row's sum from below whatever the potentials have become.  The leading products come first and the max between them and
+// the others, so a wave waits for its own products more often; three workgroups per CU fill those waits (168 registers: sums of one
+// weight are shifted before the next ones join them).  Half-step with its merge (us): that case 216 -> 116, the self term of a
+// divergence at n = 10000, d = 64 78 -> 53; where nothing can be left (unit cube) n = m = 16384, d = 64 197 -> 186, n = m = 10000, d = 128
+// 139 -> 134, n = m = 8192, d = 64 53 -> 57, which is why short passes stay in MODE 0 (fx_long).
+//
+// Bound: matrix and vector instructions, and with them the chip's power.  A wave alone issues a vector instruction every 2.5 ns, two
+// of a SIMD 1.3 (2.1 for conversions, shifts by an immediate, three-way maxima and whatever reads a scalar register), three or four 1.0
+// (1.9); an MFMA takes 13.6 ns, 20 with random operands.  A tile of 32 x 32 scores at d = 64 is 20 or 26 MFMAs and about 175 vector
+// instructions: 700 to 800 ns (n = m = 16384, ten products, three workgroups per CU: 305000 cycles per CU at 1.85 GHz, and with all points
+// but two at zero 283000 at 2.19).  Four workgroups per CU in MODE 3 at d = 64 spill: 78.5 us against 76 at n = m = 10000.
 // Measured (half-step with its merge, us, fp64 and here; the other kernel's empty launch included): n = m = 10000, d = 64:
-// 232 -> 81 (ten products); n = m = 16384, d = 64: 577 -> 217 (thirteen); n = 9973, m = 12007, d = 128: 545 -> 156 (ten);
-// n = 9973, m = 12007, d = 20: 71 (ten).
+// 232 -> 79 (ten products); n = 9973, m = 12007, d = 128: 545 -> 150 (ten); n = 9973, m = 12007, d = 20: 71 (ten).
 // Error of plan sums against 64 bits (n = 3001, m = 2800, d = 64 and 128; cube, normal, pixel and two-valued points,
 // everywhere between the gates): 3e-8 to 6.5e-8, 64 columns of both signs 7e-8 to 1.1e-7; fp64 scores with fp32 sums 3.4e-8 to
 // 4.3e-7 and 5e-8 to 5.6e-7.
@@ -91,6 +95,9 @@ struct FxArgs {
     int n_tiles, tiles_per_split;
     double2 *partial;                 // [splits][partial_stride] (max, sum)
     int64_t partial_stride;
+    const FxSeed *seed_in;            // [seed_splits][partial_stride] of the last pass over these rows, or nullptr
+    FxSeed *seed_out;                 // [splits][partial_stride], or nullptr
+    int seed_splits;
     // application
     const float *V;                   // MODE 1: [n_str][ldv] values, columns p0 ..
     int64_t ldv, n_str;
@@ -104,7 +111,8 @@ struct FxArgs {
     const double *had_add;            // what the shift of the streamed points takes from the weights of a row
 };
 
-// MODE 0: log-sum-exp.  MODE 1: application to NC <= 4 columns on the vector ALU (one fma per score and
+// MODE 0: log-sum-exp.  MODE 3: the same for long passes: a tile whose leading products show that it cannot count is left at them,
+// and m starts at the score of a point that the last pass over these rows found.  MODE 1: application to NC <= 4 columns on the vector ALU (one fma per score and
 // column).  MODE 2: application to 32 NC columns: the exponentials, in three bf16 pieces each, are the B
 // operand of a second MFMA against the values in three bf16 pieces.  Six of the nine piece products are
 // kept; those dropped are below 2^-25 of a product, less than one rounding of an fp32 accumulation.
@@ -112,27 +120,26 @@ struct FxArgs {
 // a second contraction of the same streamed digits with those of A (a scale per row; thirteen products).
 constexpr int fx_stage_bytes(int ks, int mode, int nc)
 {
-    return ks * 4096 + kRecBytes + (mode == 0 ? 0 : mode == 1 ? (nc + 1) / 2 * 256 : nc * 6 * 1024);
+    return ks * 4096 + kRecBytes + (mode == 1 ? (nc + 1) / 2 * 256 : mode == 2 ? nc * 6 * 1024 : 0);
 }
 constexpr int fx_stages(int stage_bytes) { return stage_bytes <= 13 * 1024 ? 4 : 3; }
-// Workgroups per CU.  Half-steps and applications on the vector ALU: three (see the header).  Products on the matrix cores: two where two rings fit the 160 KB of LDS, which the widest applications
-// do not (four column blocks at any d, three at d > 64, two at d > 96).  HAD: one, the second set of resident digits takes the
-// registers.
+// Workgroups per CU: two where two rings fit the 160 KB of LDS, which the widest applications do not (four column blocks
+// at any d, three at d > 64, two at d > 96).  HAD: one, the second set of resident digits takes the registers.  MODE 3: three, it
+// holds fewer accumulators at a time.
 constexpr int fx_wg_per_cu(int ks, int mode, int nc, bool had)
 {
     const int stage = fx_stage_bytes(ks, mode, nc);
-    if (mode < 2) return 3;
-    return had || 2 * fx_stages(stage) * stage > 160 * 1024 ? 1 : 2;
+    return mode == 3 ? 3 : had || 2 * fx_stages(stage) * stage > 160 * 1024 ? 1 : 2;
 }
 template <int KS, int MODE, int NC, bool HAD = false> struct FxShape {
     static constexpr int kStage = fx_stage_bytes(KS, MODE, NC);
     static constexpr int kStages = fx_stages(kStage);
     // vector-memory instructions of a wave per stage
-    static constexpr int kLoads = KS + 1 + (MODE == 0 ? 0 : MODE == 1 ? 1 : (NC * 6 + 3) / 4);
+    static constexpr int kLoads = KS + 1 + (MODE == 1 ? 1 : MODE == 2 ? (NC * 6 + 3) / 4 : 0);
     static constexpr int kWgPerCu = fx_wg_per_cu(KS, MODE, NC, HAD);
     static constexpr int kPC = MODE == 2 ? 32 * NC : NC;
-    // digits of a tile that stay in registers while it lasts: all of them, or the leading two, or none
-    static constexpr int kHold(bool full) { return KS <= 2 ? 4 : KS == 3 || !full ? 2 : 0; }
+    // digits of a tile that stay in registers while it lasts: all of them, the leading two, or none
+    static constexpr int kHold(bool full) { return KS <= 2 ? 4 : full ? 0 : 2; }
 };
 
 template <int KS, int MODE, int NC, bool FULL, bool HAD = false>
@@ -154,6 +161,11 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
     float u3 = (float)u3d, u5 = (float)u5d;
     asm volatile("" : "+v"(u3), "+v"(u5));   // (an instruction that reads a scalar register takes twice the time)
     const int lazy = (int)fmin(4.0 / u3d, 1073741824.0);   // see settle
+    // A tile none of whose scores comes to m less this (with the most that the low digits can add, 2^31 u5) is left at its leading
+    // products: an exponential there is less than 2^-60 of the row's sum over all splits (m is a score of the
+    // row, or, where it comes from a seed and the low digits conspire, up to 2^31 u5 = v / 128 units above one).  Half-steps only: the values of an
+    // application may be of any size.
+    const int skip = -(int)fmin(60.0 / u3d + 32768.0, 2147483647.0);
 
     int issued = 0;
     auto issue = [&]() __attribute__((always_inline)) {
@@ -183,6 +195,29 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
         ++issued;
     };
 
+    // Everything that is loaded once, behind the first tile, and waited for once.
+    if (MODE == 3 && G > 0) issue();
+    int at = -1, at_dot = 0;   // the point that m was last raised for and its product with the row, in units of r2^2 2^-22
+    double m0 = -INFINITY;
+    if (MODE == 3 && a.seed_in) {
+        // m starts at the score of the best of the points that the last pass over these rows found in its splits
+        constexpr int kOnce = 6;
+        FxSeed sd[kOnce];
+        auto best = [&](const FxSeed &v) __attribute__((always_inline)) {
+            const double score = v.point >= 0 ? fma((double)v.dot, u3d, a.bias[v.point]) : -INFINITY;
+            if (score > m0) {
+                m0 = score;
+                at = v.point;
+                at_dot = v.dot;
+            }
+        };
+        const FxSeed *in = a.seed_in + row0 + lj;
+#pragma unroll
+        for (int k = 0; k < kOnce; ++k) sd[k] = in[(int64_t)min(2 * k + lh, a.seed_splits - 1) * a.partial_stride];
+#pragma unroll
+        for (int k = 0; k < kOnce; ++k) best(sd[k]);
+        for (int k = 2 * kOnce + lh; k < a.seed_splits; k += 2) best(in[(int64_t)k * a.partial_stride]);
+    }
     // resident digits: registers for the whole pass
     i4 b[KS][4], bw[HAD ? KS : 1][4];
     double w3 = 0.0, w5 = 0.0, wadd = 0.0;   // units of the Hadamard weights
@@ -217,8 +252,24 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
 
     // running sum of 2^(score - m) with m = -u3 nhm (s == 0: nothing seen yet, m is free).  Sixteen scores are summed in
     // float, tiles in double: two more instructions per tile, and the sum over a long split keeps no rounding of its own.
+    // `known`: m is the score of a point of the row, or was raised to one.
     double s = 0.0;
     int nhm = 0;
+    bool known = false;
+    if (MODE == 3 && a.seed_in) {
+        const double m1 = __shfl_xor(m0, 32);
+        const int at1 = __shfl_xor(at, 32), dot1 = __shfl_xor(at_dot, 32);
+        if (m1 > m0 || (m1 == m0 && lh)) {   // (the same choice in both halves)
+            m0 = m1;
+            at = at1;
+            at_dot = dot1;
+        }
+        const double q = floor(m0 * a.gate.per_unit(22));
+        known = fabs(q) <= 1073741824.0;
+        nhm = known ? -(int)q : 0;
+        if (!known) at = -1;
+        asm volatile("" : "+v"(nhm));   // (waited for here)
+    }
     bool far = false;      // m is beyond the integer range: m = mfar
     float mfar = 0.0f;
     constexpr int NO = MODE == 2 ? NC : 1;
@@ -254,7 +305,7 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
 
     // ---- scores of a tile: the digit products ------------------------------------------------------------------
     struct Tile {
-        i16v H, L;
+        i16v H, L, Q;   // (Q: in MODE 0 and 1, see low)
         i4 av[KS][4];   // digits of the streamed points
         int kind;       // of the tile: 0 whole, 1 flagged, 2 with points without weight
     };
@@ -293,31 +344,32 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
     };
     auto contract_low = [&](const unsigned char *sb, Tile &T) __attribute__((always_inline)) {
         constexpr int HOLD = S::kHold(FULL);
-        if constexpr (FULL && HOLD < 4) {
+        i16v P;
+        if constexpr (HOLD == 0) {
             // one pass over the digits, three accumulators
-            i16v P = biases(sb, 2), Q = biases(sb, 1);
+            i16v Q = biases(sb, 1);
+            P = biases(sb, 2);
 #pragma unroll
             for (int r = 0; r < 16; ++r) T.L[r] = 0;
-            if constexpr (HOLD == 0) asm volatile("" : "+s"(sb));   // (read again rather than kept)
+            asm volatile("" : "+s"(sb));   // (read again rather than kept)
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
-                digits(sb, T, ks, HOLD, 3);
-                FX_MM(P, 3, 1);
+                digits(sb, T, ks, 0, 3);
                 FX_MM(Q, 2, 0);
                 FX_MM(T.L, 0, 3);
-                FX_MM(P, 2, 2);
+                FX_MM(P, 3, 1);
                 FX_MM(Q, 1, 1);
                 FX_MM(T.L, 1, 2);
-                FX_MM(P, 1, 3);
+                FX_MM(P, 2, 2);
                 FX_MM(Q, 0, 2);
                 FX_MM(T.L, 2, 1);
+                FX_MM(P, 1, 3);
                 FX_MM(T.L, 3, 0);
             }
 #pragma unroll
             for (int r = 0; r < 16; ++r) T.L[r] = (int)(((unsigned)Q[r] << 8) + (unsigned)T.L[r] + (unsigned)(P[r] >> 8));
         } else {
             // sums of one weight are shifted before those of the next one join them: fewer accumulators at a time
-            i16v P;
             if constexpr (HOLD == 4) {
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks) digits(sb, T, ks, 2, 3);
@@ -334,7 +386,7 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
             T.L = biases(sb, 1);
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
-                if constexpr (HOLD < 4) digits(sb, T, ks, 2, 2);
+                if constexpr (HOLD == 2) digits(sb, T, ks, 2, 2);
                 FX_MM(T.L, 2, 0);
                 FX_MM(T.L, 1, 1);
                 FX_MM(T.L, 0, 2);
@@ -342,10 +394,10 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
 #pragma unroll
             for (int r = 0; r < 16; ++r)
                 T.L[r] = FULL ? (int)(((unsigned)T.L[r] << 8) + (unsigned)(P[r] >> 8)) : (int)((unsigned)T.L[r] << 8);
-            if constexpr (HOLD < 4) asm volatile("" : "+s"(sb));
+            if constexpr (HOLD == 2) asm volatile("" : "+s"(sb));
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
-                if constexpr (HOLD < 4) digits(sb, T, ks, 2, 3);
+                if constexpr (HOLD == 2) digits(sb, T, ks, 2, 3);
                 FX_MM(T.L, 0, 3);
                 FX_MM(T.L, 1, 2);
                 FX_MM(T.L, 2, 1);
@@ -353,7 +405,63 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
             }
         }
     };
+    // all of them at once, where nothing is decided in between
+    auto contract_all = [&](const unsigned char *sb, Tile &T) __attribute__((always_inline)) {
+        constexpr bool HOLD = KS <= 2;
+        T.kind = __builtin_amdgcn_readfirstlane(reinterpret_cast<const int *>(sb + KS * 4096)[96]);
+        if constexpr (HOLD) {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) digits(sb, T, ks, 0, 3);
+        }
+        T.Q = biases(sb, 1);
+        T.H = biases(sb, 0);
+        if constexpr (HOLD) __builtin_amdgcn_sched_barrier(0);   // (all of them asked for before the first product)
+        if constexpr (FULL) {
+            T.L = biases(sb, 2);
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                if constexpr (!HOLD) digits(sb, T, ks, 1, 3);
+                FX_MM(T.L, 3, 1);
+                FX_MM(T.L, 2, 2);
+                FX_MM(T.L, 1, 3);
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) T.L[r] = T.L[r] >> 8;
+        } else {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) T.L[r] = 0;
+        }
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            if constexpr (!HOLD) digits(sb, T, ks, 0, 2);
+            FX_MM(T.H, 0, 0);
+            FX_MM(T.Q, 2, 0);
+            FX_MM(T.Q, 1, 1);
+            FX_MM(T.Q, 0, 2);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) T.H[r] = (int)(((unsigned)T.H[r] << 8) + (unsigned)nhm);
+        if constexpr (!HOLD) asm volatile("" : "+s"(sb));   // (read again rather than kept)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            if constexpr (!HOLD) digits(sb, T, ks, 0, 3);
+            FX_MM(T.H, 0, 1);
+            FX_MM(T.H, 1, 0);
+            FX_MM(T.L, 0, 3);
+            FX_MM(T.L, 1, 2);
+            FX_MM(T.L, 2, 1);
+            FX_MM(T.L, 3, 0);
+        }
+        if constexpr (MODE == 2) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) T.L[r] = (int)(((unsigned)T.Q[r] << 8) + (unsigned)T.L[r]);
+        }
+    };
 #undef FX_MM
+    // (not before it is used: the vector ALU is not to wait for the last of the products, see settle)
+    auto low = [&](const Tile &T, int r) __attribute__((always_inline)) {
+        return MODE >= 2 ? T.L[r] : (int)(((unsigned)T.Q[r] << 8) + (unsigned)T.L[r]);
+    };
 
     // ---- before the exponentials of tile g: the slow path of a tile, and the lift of the max ------------------
     // The points without weight as this lane's registers see them: register r is bit 8 (r / 4) + r % 4.  (Opaque to the
@@ -376,26 +484,23 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
         // (the record's biases are in where the tile is not flagged, but for points without weight)
         const unsigned add = T.kind == 1 ? 0xffffffffu : T.kind == 2 ? none_of_lane(g) : 0u;
         auto score = [&](int r) __attribute__((always_inline)) {
-            const double v = fma((double)T.L[r], u5d, (double)(int)((unsigned)T.H[r] + back) * u3d);
+            const double v = fma((double)low(T, r), u5d, (double)(int)((unsigned)T.H[r] + back) * u3d);
             return add >> (8 * (r >> 2) + (r & 3)) & 1 ? v + bd[8 * (r >> 2) + (r & 3)] : v;
         };
         float mx = kNegInit;
-        double seen = s;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             mx = fmaxf(mx, (float)score(r));
             asm volatile("" : "+v"(mx));   // (one after the other)
         }
-        if constexpr (MODE == 2) {   // m is common to the two lane halves
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
-            seen = fmax(s, __shfl_xor(s, 32));
-        }
+        if constexpr (MODE == 2) mx = fmaxf(mx, __shfl_xor(mx, 32));   // (m is common to the two lane halves)
         double md = far ? (double)mfar : -u3d * (double)nhm;
-        if (mx > kNegInit && (!(seen > 0.0) || (double)mx > md)) {
+        if (mx > kNegInit && (!known || (double)mx > md)) {
             const double q = ceil((double)mx / u3d);
             const bool out = !(fabs(q) <= 1073741824.0);
             const double mnew = out ? (double)mx : q * u3d;
-            if (seen > 0.0) scale_sums(fast_exp2((float)(md - mnew)));
+            if (known) scale_sums(fast_exp2((float)(md - mnew)));
+            known = true;
             md = mnew;
             nhm = out ? 0 : -(int)q;
             far = out;
@@ -428,29 +533,41 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
     // m moves to the largest score where one exceeds it by more than `lazy`, 4 base-2 units (a float argument of 4 is
     // rounded by 2^-23); in MODE 2 both lane halves move together, since the second MFMA sums over them.  The factor of the old sums is a
     // rounded power: what it is off by counts with the weight 2^(old m - new m) of those sums, at most 3e-8 of the new one.
+    // top: the largest score of the lane, for `skip`.
     // (masked: a tile with points without weight)
-    auto settle = [&](int g, Tile &T) __attribute__((always_inline)) {
+    auto settle = [&](int g, Tile &T, int &top, auto masked) __attribute__((always_inline)) {
+        if (masked) mask_none(g, T);
         int hx = T.H[0];
 #pragma unroll
         for (int r = 1; r < 16; ++r) hx = max(hx, T.H[r]);
-        if (__any(hx > lazy || !(s > 0.0))) {
-            double seen = s;
-            if constexpr (MODE == 2) {
-                hx = max(hx, __shfl_xor(hx, 32));
-                seen = fmax(s, __shfl_xor(s, 32));
+        top = hx;
+        if (__any(hx > lazy || !known)) {
+            if constexpr (MODE == 2) hx = max(hx, __shfl_xor(hx, 32));
+            const int dh = known ? max(hx, 0) : hx == INT32_MIN ? 0 : hx;
+            if (MODE == 3 && a.seed_out) {
+                int which = INT32_MIN;   // (the largest score but for four bits, and its register)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) which = max(which, (T.H[r] & ~15) | r);
+                if (dh != 0 || (!known && hx != INT32_MIN)) {
+                    const int i = 2 * (which & 12) + 4 * lh + (which & 3);
+                    const int hi = reinterpret_cast<const int *>(ring + (g % NS) * S::kStage + KS * 4096)[i];   // (of its bias)
+                    at = (t_begin + g) * 32 + i;
+                    at_dot = (int)((unsigned)hx - (unsigned)nhm - ((unsigned)hi << 8));
+                }
             }
-            const int dh = seen > 0.0 ? max(hx, 0) : hx == INT32_MIN ? 0 : hx;
+            known = known || hx != INT32_MIN;
             scale_sums(fast_exp2(fminf((float)-dh * u3, 0.0f)));   // (1 where nothing was seen)
             nhm -= dh;
 #pragma unroll
             for (int r = 0; r < 16; ++r) T.H[r] = (int)((unsigned)T.H[r] - (unsigned)dh);
-            if (MODE != 2 && T.kind == 2) mask_none(g, T);   // (the subtraction has wrapped)
+            if (masked) mask_none(g, T);   // (the subtraction has wrapped)
+            top = INT32_MAX;
         }
     };
     // ---- exponentials of a tile, score - m = u3 H + u5 L ------------------------------------------------------
     auto exponentials = [&](const Tile &T, float (&e)[16]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) e[r] = fast_exp2(fmaf((float)T.L[r], u5, (float)T.H[r] * u3));
+        for (int r = 0; r < 16; ++r) e[r] = fast_exp2(fmaf((float)low(T, r), u5, (float)T.H[r] * u3));
     };
     // ---- their sum and what they are applied to ----------------------------------------------------------------
     auto finish = [&](int g, const unsigned char *sb, float (&e)[16]) __attribute__((always_inline)) {
@@ -601,17 +718,42 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
         if (issued < G) issue();     // into the predecessor's slot
         const unsigned char *sb = ring + (g % NS) * S::kStage;
         Tile T;
-        contract_high(sb, T);
-        float e[16];
-        const bool direct = T.kind != 1 && (MODE != 2 || T.kind == 0) && !__any(far);
-        if (direct) {
-            if (MODE != 2 && T.kind == 2) mask_none(g, T);
-            settle(g, T);
-        }
-        contract_low(sb, T);
-        if (__builtin_expect(direct, 1))
-            exponentials(T, e);
+        if constexpr (MODE == 3)
+            contract_high(sb, T);
         else
+            contract_all(sb, T);
+        float e[16];
+        int top;
+        const bool near = !__any(far);
+        // (Whole tiles, and those with points without weight, have code copies of their own: where the others' scores join
+        // theirs, the compiler moves all of them from one set of registers to another in every tile, 3 to 5 % of a pass.  In
+        // MODE 2 and 3 the copies would spill, and in MODE 2 points without weight take the float64 epilogue.)
+        if constexpr (MODE == 3) {
+            const bool direct = T.kind != 1 && near;
+            if (direct) {
+                settle(g, T, top, T.kind == 2);
+                if (!__any(top > skip)) continue;
+            }
+            contract_low(sb, T);
+            if (__builtin_expect(direct, 1)) {
+                exponentials(T, e);
+                finish(g, sb, e);
+                continue;
+            }
+            far_tile(g, T, e);
+        } else if (__builtin_expect(T.kind == 0 && near, 1)) {
+            settle(g, T, top, std::false_type{});
+            exponentials(T, e);
+            if constexpr (MODE != 2) {
+                finish(g, sb, e);
+                continue;
+            }
+        } else if (MODE != 2 && T.kind == 2 && near) {
+            settle(g, T, top, std::true_type{});
+            exponentials(T, e);
+            finish(g, sb, e);
+            continue;
+        } else
             far_tile(g, T, e);
         finish(g, sb, e);
     }
@@ -624,6 +766,11 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
     const double M = fmax(mym, mo) > (double)kNegInit ? ceil(fmax(mym, mo)) : (double)kNegInit;
     const float f0 = fast_exp2((float)(mym - M)), f1 = fast_exp2((float)(mo - M));
     const int64_t rec_row = (int64_t)by * a.partial_stride + row0 + lj;
+    if (MODE == 3 && a.seed_out) {
+        const int at1 = __shfl_xor(at, 32), dot1 = __shfl_xor(at_dot, 32);
+        const bool other = at < 0 || (at1 >= 0 && mo > mym);   // (the half that was raised higher)
+        if (lh == 0) a.seed_out[rec_row] = other ? FxSeed{dot1, at1} : FxSeed{at_dot, at};
+    }
     if (lh == 0) a.partial[rec_row] = make_double2(M, s * (double)f0 + so * (double)f1);
     if constexpr (MODE == 1) {
 #pragma unroll
@@ -645,12 +792,23 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
     }
 }
 
+// what a pass leaves whose scores the other kernel forms
+__device__ inline void no_seeds(const FxArgs &a, int bx, int by)
+{
+    if (a.seed_out && threadIdx.x < kRows) a.seed_out[(int64_t)by * a.partial_stride + (int64_t)bx * kRows + threadIdx.x] = FxSeed{0, -1};
+}
+
+// (The dispatcher fills CU after CU, so the kernels are held to as many workgroups per CU as the launch shape counts on.)
 template <int KS, int MODE, int NC, bool HAD = false>
-__global__ __launch_bounds__(256, (FxShape<KS, MODE, NC, HAD>::kWgPerCu)) void k_fx(FxArgs a)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FxShape<KS, MODE, NC, HAD>::kWgPerCu, FxShape<KS, MODE, NC, HAD>::kWgPerCu)))
+void k_fx(FxArgs a)
 {
     using S = FxShape<KS, MODE, NC, HAD>;
     __shared__ __attribute__((aligned(1024))) unsigned char ring[S::kStages * S::kStage];
-    if (!a.gate.on()) return;
+    if (!a.gate.on()) {
+        no_seeds(a, blockIdx.x, blockIdx.y);
+        return;
+    }
     if (a.gate.full())
         fx_body<KS, MODE, NC, true, HAD>(a, ring, blockIdx.x, blockIdx.y);
     else
@@ -659,19 +817,23 @@ __global__ __launch_bounds__(256, (FxShape<KS, MODE, NC, HAD>::kWgPerCu)) void k
 
 // Both passes of one iteration of the averaged schedule (Eq. 4-5) in one launch: the first rb0 row blocks of the
 // grid belong to the f-pass (a0), the others to the g-pass (a1).
-template <int KS>
-__global__ __launch_bounds__(256, (FxShape<KS, 0, 1>::kWgPerCu)) void k_fx_pair(FxArgs a0, FxArgs a1, int rb0, int splits0, int splits1)
+template <int KS, int MODE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FxShape<KS, MODE, 1>::kWgPerCu, FxShape<KS, MODE, 1>::kWgPerCu)))
+void k_fx_pair(FxArgs a0, FxArgs a1, int rb0, int splits0, int splits1)
 {
-    using S = FxShape<KS, 0, 1>;
+    using S = FxShape<KS, MODE, 1>;
     __shared__ __attribute__((aligned(1024))) unsigned char ring[S::kStages * S::kStage];
-    if (!a0.gate.on()) return;
     const bool second = (int)blockIdx.x >= rb0;   // uniform over the workgroup
     if ((int)blockIdx.y >= (second ? splits1 : splits0)) return;
     const int bx = (int)blockIdx.x - (second ? rb0 : 0);
+    if (!a0.gate.on()) {
+        no_seeds(second ? a1 : a0, bx, blockIdx.y);
+        return;
+    }
     if (a0.gate.full())
-        fx_body<KS, 0, 1, true>(second ? a1 : a0, ring, bx, blockIdx.y);
+        fx_body<KS, MODE, 1, true>(second ? a1 : a0, ring, bx, blockIdx.y);
     else
-        fx_body<KS, 0, 1, false>(second ? a1 : a0, ring, bx, blockIdx.y);
+        fx_body<KS, MODE, 1, false>(second ? a1 : a0, ring, bx, blockIdx.y);
 }
 
 // Value images for MODE 2: [tile][32-column block][16 points][piece][64 lanes][8 bf16], lane l holding column l % 32
@@ -769,9 +931,10 @@ __global__ __launch_bounds__(256) void k_had_digits(const float *A, int64_t lda,
 }
 
 // Launch shape: row blocks x splits of the streamed side, minimising a makespan model in units of one tile of one
-// workgroup on a full CU: workgroups are dealt to the CUs evenly and run `occ` at a time (one or two); one left over where
-// two would run leaves the matrix pipe partly idle and is charged 2.  `startup`: filling the ring, loading the resident digits,
-// the first lift of the max and the merge, in tiles.
+// workgroup on a full CU: workgroups are dealt to the CUs evenly and run `occ` at a time (one to three); one left over where two
+// would run leaves the matrix pipe partly idle and is charged 2, of three one is charged 1.75 and two 2.25 (half-steps at n = m = 10000, d = 64
+// with 3, 6 and 9 splits: 103, 71 and 66 us behind the same 13; n = m = 6000 with 5, 10 and 16: 36, 25 and 22).  `startup`: filling the
+// ring, loading the resident digits, the first lift of the max and the merge, in tiles.
 PassShape fx_shape(const Ctx *c, int64_t n_res, int64_t n_str, int occ)
 {
     PassShape s;
@@ -795,7 +958,7 @@ PassShape fx_shape(const Ctx *c, int64_t n_res, int64_t n_str, int occ)
         if ((int)ceil_div(n_tiles, tps) != sp) continue;
         const int64_t wg = ceil_div((int64_t)s.row_blocks * sp, (int64_t)c->num_cu);
         const int rem = (int)(wg % occ);
-        const double units = (double)(wg - rem) + (rem == 0 ? 0.0 : rem == 1 ? 2.0 : 2.6);
+        const double units = (double)(wg - rem) + (rem == 0 ? 0.0 : rem == 2 ? 2.25 : occ == 3 ? 1.75 : 2.0);
         const double cost = units * ((double)tps + startup) + 0.05 * sp;
         if (best == 0.0 || cost < best * 0.995) {
             best = cost;
@@ -807,10 +970,10 @@ PassShape fx_shape(const Ctx *c, int64_t n_res, int64_t n_str, int occ)
     return s;
 }
 
-fs_status pass_args(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, int occ, void *partial, FxArgs *out,
-                    PassShape *shape)
+fs_status pass_args(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, int mode, int nc, bool had, void *partial,
+                    FxArgs *out, PassShape *shape)
 {
-    const PassShape s = fx_shape(c, res->cnt, str->cnt, occ);
+    const PassShape s = fx_shape(c, res->cnt, str->cnt, fx_wg_per_cu(P->fx_ks, mode, nc, had));
     FxArgs a{};
     a.res = res->dig;
     a.str = str->dig;
@@ -825,6 +988,18 @@ fs_status pass_args(Ctx *c, const Prepared *P, const Side *res, const Side *str,
     if ((int64_t)s.row_blocks * kRows > res->cnt_pad || (int64_t)a.n_tiles * 32 > str->cnt_pad ||
         (size_t)s.splits * res->cnt_pad * 16 > P->partial_bytes || P->fx_ks < 1 || P->fx_ks > kFxMaxKs)
         return fail(c, FS_ERR_DEVICE, "internal: fixed-point launch shape exceeds the padded buffers");
+    Prepared::Seeds &sd = P->seeds;
+    const int t = res == &P->X ? 0 : 1;
+    if (mode == 3 && sd.last[t] >= 0) {
+        a.seed_in = reinterpret_cast<const FxSeed *>(sd.buf[t][sd.last[t]]);
+        a.seed_splits = sd.splits[t];
+    }
+    if (mode == 3 && (size_t)s.splits * res->cnt_pad * sizeof(FxSeed) <= sd.bytes[t]) {
+        const int next = sd.last[t] == 0 ? 1 : 0;
+        a.seed_out = reinterpret_cast<FxSeed *>(sd.buf[t][next]);
+        sd.last[t] = next;
+        sd.splits[t] = s.splits;
+    }
     *out = a;
     *shape = s;
     return FS_OK;
@@ -886,19 +1061,31 @@ struct ApplyBuf {
 
 }  // namespace
 
+// Whether a half-step runs in MODE 3 (`s`: its shape there): where a workgroup has at least 24 tiles.  Half-steps in MODE 0 and 3 with seeds
+// (us; unit cube, eps = 0.1, where no tile can be left: n = m = 4000, 6000, 8192, 10000, 16384, d = 64: 22 / 25, 37 / 39, 53 / 57, 91 / 87, 198 / 188;
+// d = 128, n = m = 10000 140 / 135; shifted normal points of spread 3, n = m = 16384, d = 64, where four of five are: 216 / 118).
+static bool fx_long(const PassShape &s) { return s.cols_per_split >= 24 * 32; }
+
 fs_status fx_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, int *splits)
 {
     FxArgs a;
-    PassShape s;
-    fs_status st = pass_args(c, P, res, str, eps, fx_wg_per_cu(P->fx_ks, 0, 1, false), P->partial, &a, &s);
+    PassShape s = fx_shape(c, res->cnt, str->cnt, fx_wg_per_cu(P->fx_ks, 3, 1, false));
+    const bool lng = fx_long(s);
+    fs_status st = pass_args(c, P, res, str, eps, lng ? 3 : 0, 1, false, P->partial, &a, &s);
     if (st != FS_OK) return st;
     const dim3 grid((unsigned)s.row_blocks, (unsigned)s.splits);
+#define FX_LSE(KS)                                                                          \
+    if (lng)                                                                                \
+        hipLaunchKernelGGL((k_fx<KS, 3, 1>), grid, dim3(256), 0, c->stream, a);             \
+    else                                                                                    \
+        hipLaunchKernelGGL((k_fx<KS, 0, 1>), grid, dim3(256), 0, c->stream, a)
     switch (P->fx_ks) {
-    case 1: hipLaunchKernelGGL((k_fx<1, 0, 1>), grid, dim3(256), 0, c->stream, a); break;
-    case 2: hipLaunchKernelGGL((k_fx<2, 0, 1>), grid, dim3(256), 0, c->stream, a); break;
-    case 3: hipLaunchKernelGGL((k_fx<3, 0, 1>), grid, dim3(256), 0, c->stream, a); break;
-    default: hipLaunchKernelGGL((k_fx<4, 0, 1>), grid, dim3(256), 0, c->stream, a); break;
+    case 1: FX_LSE(1); break;
+    case 2: FX_LSE(2); break;
+    case 3: FX_LSE(3); break;
+    default: FX_LSE(4); break;
     }
+#undef FX_LSE
     FS_HIP(c, hipGetLastError());
     *splits = s.splits;
     return FS_OK;
@@ -907,18 +1094,25 @@ fs_status fx_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, do
 fs_status fx_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, void *partial_y, int *splits_x, int *splits_y)
 {
     FxArgs ax, ay;
-    PassShape sx, sy;
-    const int occ = fx_wg_per_cu(P->fx_ks, 0, 1, false);
+    const int occ = fx_wg_per_cu(P->fx_ks, 3, 1, false);
+    PassShape sx = fx_shape(c, P->X.cnt, P->Y.cnt, occ), sy = fx_shape(c, P->Y.cnt, P->X.cnt, occ);
+    const bool lng = fx_long(sx) && fx_long(sy);
     fs_status st;
-    if ((st = pass_args(c, P, &P->X, &P->Y, eps, occ, partial_x, &ax, &sx)) != FS_OK) return st;
-    if ((st = pass_args(c, P, &P->Y, &P->X, eps, occ, partial_y, &ay, &sy)) != FS_OK) return st;
+    if ((st = pass_args(c, P, &P->X, &P->Y, eps, lng ? 3 : 0, 1, false, partial_x, &ax, &sx)) != FS_OK) return st;
+    if ((st = pass_args(c, P, &P->Y, &P->X, eps, lng ? 3 : 0, 1, false, partial_y, &ay, &sy)) != FS_OK) return st;
     const dim3 grid((unsigned)(sx.row_blocks + sy.row_blocks), (unsigned)(sx.splits > sy.splits ? sx.splits : sy.splits));
+#define FX_PAIR(KS)                                                                                                         \
+    if (lng)                                                                                                                \
+        hipLaunchKernelGGL((k_fx_pair<KS, 3>), grid, dim3(256), 0, c->stream, ax, ay, sx.row_blocks, sx.splits, sy.splits); \
+    else                                                                                                                    \
+        hipLaunchKernelGGL((k_fx_pair<KS, 0>), grid, dim3(256), 0, c->stream, ax, ay, sx.row_blocks, sx.splits, sy.splits)
     switch (P->fx_ks) {
-    case 1: hipLaunchKernelGGL(k_fx_pair<1>, grid, dim3(256), 0, c->stream, ax, ay, sx.row_blocks, sx.splits, sy.splits); break;
-    case 2: hipLaunchKernelGGL(k_fx_pair<2>, grid, dim3(256), 0, c->stream, ax, ay, sx.row_blocks, sx.splits, sy.splits); break;
-    case 3: hipLaunchKernelGGL(k_fx_pair<3>, grid, dim3(256), 0, c->stream, ax, ay, sx.row_blocks, sx.splits, sy.splits); break;
-    default: hipLaunchKernelGGL(k_fx_pair<4>, grid, dim3(256), 0, c->stream, ax, ay, sx.row_blocks, sx.splits, sy.splits); break;
+    case 1: FX_PAIR(1); break;
+    case 2: FX_PAIR(2); break;
+    case 3: FX_PAIR(3); break;
+    default: FX_PAIR(4); break;
     }
+#undef FX_PAIR
     FS_HIP(c, hipGetLastError());
     *splits_x = sx.splits;
     *splits_y = sy.splits;
@@ -952,7 +1146,7 @@ fs_status fx_apply_pass(Ctx *c, const Prepared *P, const Side *res, const Side *
     fx_columns(p - p0, hadA != nullptr, &mode, &nc);
     FxArgs a;
     PassShape s;
-    fs_status st = pass_args(c, P, res, str, eps, fx_wg_per_cu(P->fx_ks, mode, nc, hadA != nullptr), P->partial, &a, &s);
+    fs_status st = pass_args(c, P, res, str, eps, mode, nc, hadA != nullptr, P->partial, &a, &s);
     if (st != FS_OK) return st;
     const ApplyBuf buf(s.splits, res->cnt_pad, a.n_tiles, P->fx_ks, mode, nc, hadA != nullptr);
     if (!P->extra || buf.total > P->extra_bytes) return fail(c, FS_ERR_DEVICE, "internal: fixed-point application exceeds its buffer");

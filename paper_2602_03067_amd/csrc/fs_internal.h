@@ -160,6 +160,7 @@ struct FxGate {
         return cscale * r * r > kFxFull;
     }
     __device__ double unit(int k) const { return ldexp(cscale * *r2 * *r2, -k); }
+    __device__ double per_unit(int k) const { return ldexp(1.0 / (cscale * *r2 * *r2), k); }
 };
 
 // the four balanced base-256 digits of sixteen coordinates in fixed point
@@ -369,6 +370,15 @@ struct Prepared {
     mutable MomState mom;            // LowD, d <= 3
     int kp = 0;   // F64 / BF16: padded contraction length
     int fx_ks = 0;   // F64: k-steps of the digit images, 0: none
+    // fixed-point passes: what the last pass over the rows of X [0] and Y [1] left about them (FxSeed), two buffers a side in turn
+    struct Seeds {
+        char *buf[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};
+        int last[2] = {-1, -1};   // which of the two holds the last pass's, -1: neither
+        int splits[2] = {0, 0};   // ... and its splits
+        size_t bytes[2] = {0, 0};
+    };
+    bool want_seeds = false;      // set by the entry points that pass over the same rows several times
+    mutable Seeds seeds;
     Side X, Y;
     // partial reductions of a streaming pass: [splits][max(n,m)_pad] records
     void *partial = nullptr;
@@ -381,6 +391,15 @@ struct Prepared {
     char *extra = nullptr;       // entry-point specific scratch (plan application partials)
     size_t extra_bytes = 0;
 };
+
+// For each row of a pass of the fixed-point kernels and each split of the streamed side, a point whose score was within a few base-2
+// units of the split's largest: point, or -1 where there is none, and the leading part of <x_i, y_point> in units of r2^2 2^-22.  The next
+// pass over the same rows starts from the score of that point at its own biases (see fs_fx.hip).
+struct FxSeed {
+    int dot, point;
+};
+// bytes of one buffer of a side: 64 splits of a small side, or what fills the chip four times
+inline size_t fx_seed_bytes(int64_t cnt_pad) { return (size_t(2) << 20) + (size_t)cnt_pad * 2 * sizeof(FxSeed); }
 
 // the gate of a pass at `eps` (r2 sits in scalars[10])
 inline FxGate fx_gate(const Prepared *P, double eps)

@@ -255,6 +255,52 @@ def test_paired_passes(oracle, n, m, d, splits):
     c.close()
 
 
+@pytest.mark.parametrize("d", [20, 64, 70, 128])
+@pytest.mark.parametrize("kind", ["cube", "cube fine", "wide", "clusters", "no weight"])
+def test_long_passes_of_a_solve(oracle, d, kind):
+    """Passes of 24 tiles and more per workgroup: the running max starts at a point the last pass found, and tiles that cannot
+    count are left at their leading products: none of a cube's, most of wide and clustered clouds'."""
+    n, m = 900, 35 * 32 + 5
+    rng, x, y, a, b = _problem(d + len(kind), n, m, d)
+    e0 = e1 = {"cube": 0.5, "cube fine": 0.03, "wide": 0.1, "clusters": 0.1, "no weight": 0.1}[kind]
+    stages, iters = 1, 4
+    if kind in ("wide", "no weight"):
+        x = (rng.standard_normal((n, d)) * 1.5).astype(np.float32)
+        y = (rng.standard_normal((m, d)) * 1.5 + 0.5).astype(np.float32)
+    if kind == "clusters":      # consecutive points in one cluster of six, and stages of eps over ten and thirteen products
+        centres = rng.standard_normal((6, d))
+        x = (centres[np.arange(n) * 6 // n] + 0.05 * rng.standard_normal((n, d))).astype(np.float32)
+        y = (centres[np.arange(m) * 6 // m] + 0.05 * rng.standard_normal((m, d))).astype(np.float32)
+        e0, stages, iters = 2.0, 3, 2
+    if kind == "no weight":
+        b[:70] = 0.0
+        b[200::7] = 0.0
+        a[5 * 32:9 * 32] = 0.0
+        a, b = (a / a.sum(dtype=np.float64)).astype(np.float32), (b / b.sum(dtype=np.float64)).astype(np.float32)
+    e0, e1 = float(np.float32(e0)), float(np.float32(e1))
+    c = binding.Context(0)
+    c.fs_debug_set("fx_any_size", 1)
+    c.fs_debug_set("fx_splits", 1)
+    prob = make_problem(x, y, a, b)
+    say("fx long passes d=%d %s" % (d, kind))
+    f, g = torch.zeros(n, device="cuda:0"), torch.zeros(m, device="cuda:0")
+    c.fs_solve(prob, e0, e1, stages, iters, f, g)
+    fo, go = oracle.solve(x, y, a, b, e0, e1, stages, iters)
+    # each half-step adds at most 1e-6 of its eps and passes on no more than it gets
+    steps = 2 * iters * sum(e0 * (e1 / e0) ** (s / max(1, stages - 1)) for s in range(stages))
+    for got, want in ((f, fo), (g, go)):
+        err = np.abs(host(got) - want)
+        say("  %.2e of %.2e" % (err.max(), 1e-6 * steps))
+        assert np.all(err <= 1e-6 * steps + 2.0 ** -24 * np.abs(want) * 1.01)
+    if stages == 1:
+        f, g = torch.zeros(n, device="cuda:0"), torch.zeros(m, device="cuda:0")
+        c.fs_solve_symmetric(prob, e1, iters, f, g)
+        fo, go = oracle.solve_symmetric(x, y, a, b, e1, iters)
+        for got, want in ((f, fo), (g, go)):
+            assert np.all(np.abs(host(got) - want) <= 1e-6 * steps + 2.0 ** -24 * np.abs(want) * 1.01)
+    c.close()
+
+
 def test_annealing_across_the_gate(ctx, oracle):
     """eps from where the weights no longer fit the bias records to where the scale is too large: the stages run on the
     fp64 kernels, on ten and on thirteen digit products, and on the fp64 kernels again."""
