@@ -4,6 +4,7 @@
 #include <math.h>
 #include <stdarg.h>
 #include <stdio.h>
+#include <string.h>
 
 #include <new>
 
@@ -314,6 +315,7 @@ fs_status prepare(Ctx *c, const fs_problem *p, Prepared *P, size_t extra, char *
     key.partial_budget = c->partial_budget;
     if (c->keep_on && c->kept_valid && key.same(c->kept_key) && (c->kept_bounds || !P->mom.base)) {
         P->rho_max = c->kept_rho_max;
+        P->fx_stamp = c->kept_fx_stamp;
         return FS_OK;
     }
     c->kept_valid = false;   // whatever was kept is overwritten now
@@ -323,6 +325,7 @@ fs_status prepare(Ctx *c, const fs_problem *p, Prepared *P, size_t extra, char *
         c->kept_key = key;
         c->kept_bounds = P->mom.base != nullptr;
         c->kept_rho_max = -1.0;   // (low-d path: set when the host reads it back, see launch_bias_from_user)
+        c->kept_fx_stamp = P->fx_stamp;
         c->kept_valid = true;
     }
     return st2;
@@ -556,8 +559,15 @@ fs_status fs_create(fs_ctx **ctx, int device, void *hip_stream)
     // this device's copy of the static scratch array (the device is current here)
     void *sp = nullptr;
     const hipError_t se = hipGetSymbolAddress(&sp, HIP_SYMBOL(scratch));
+    if (hipHostMalloc((void **)&c->box, kBoxWords * 8, hipHostMallocDefault) == hipSuccess)
+        memset(c->box, 0, kBoxWords * 8);
+    else {
+        c->box = nullptr;
+        (void)hipGetLastError();
+    }
     if (had_prev && prev != device) (void)hipSetDevice(prev);
     if (se != hipSuccess || !sp) {
+        if (c->box) (void)hipHostFree(c->box);
         delete c;
         return FS_ERR_DEVICE;
     }
@@ -578,6 +588,7 @@ fs_status fs_destroy(fs_ctx *ctx)
         if (c->ws) (void)hipFree(c->ws);
         if (c->aux) (void)hipFree(c->aux);
         if (c->pin) (void)hipHostFree(c->pin);
+        if (c->box) (void)hipHostFree(c->box);
         if (c->pin_ready) (void)hipEventDestroy(c->pin_ready);
     }
     delete c;

@@ -634,14 +634,16 @@ fs_status f64_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, d
     if (st != FS_OK) return st;
     prof_begin(c, (double)res->cnt * (double)str->cnt, prof_kind);
     int fx_splits = 0;
-    if (P->fx_ks && (st = fx_lse(c, P, res, str, eps, &fx_splits)) != FS_OK) return st;
+    const int which = fx_known(c, P, eps);
+    if (P->fx_ks && (st = fx_lse(c, P, res, str, eps, &fx_splits, which != 0)) != FS_OK) return st;
     const dim3 grid((unsigned)s.row_blocks, (unsigned)s.splits);
     if (P->path == Path::LowD)
         hipLaunchKernelGGL((k_pass_f64<false, false, 4, kLseJT, kLseNW, true>), grid, dim3(64 * kLseNW), 0, c->stream, a);
-    else if (P->fx_ks)
-        hipLaunchKernelGGL((k_pass_f64<false, false, 4, kLseJT, kLseNW, false, true>),
-                           dim3(gated_grid(c, (int64_t)s.row_blocks * s.splits, kLseWgPerCu)), dim3(64 * kLseNW), 0, c->stream, a);
-    else
+    else if (P->fx_ks) {
+        if (which != 1)
+            hipLaunchKernelGGL((k_pass_f64<false, false, 4, kLseJT, kLseNW, false, true>),
+                               dim3(gated_grid(c, (int64_t)s.row_blocks * s.splits, kLseWgPerCu)), dim3(64 * kLseNW), 0, c->stream, a);
+    } else
         hipLaunchKernelGGL((k_pass_f64<false, false, 4, kLseJT, kLseNW, false>), grid, dim3(64 * kLseNW), 0, c->stream, a);
     prof_end(c);
     FS_HIP(c, hipGetLastError());
@@ -661,15 +663,17 @@ fs_status f64_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, v
     const dim3 grid((unsigned)(sx.row_blocks + sy.row_blocks), (unsigned)(sx.splits > sy.splits ? sx.splits : sy.splits));
     prof_begin(c, 2.0 * (double)P->X.cnt * (double)P->Y.cnt, P->path == Path::LowD ? 1 : 0);
     int fx_x = 0, fx_y = 0;
-    if (P->fx_ks && (st = fx_lse_pair(c, P, eps, partial_x, partial_y, &fx_x, &fx_y)) != FS_OK) return st;
+    const int which = fx_known(c, P, eps);
+    if (P->fx_ks && (st = fx_lse_pair(c, P, eps, partial_x, partial_y, &fx_x, &fx_y, which != 0)) != FS_OK) return st;
     if (P->path == Path::LowD)
         hipLaunchKernelGGL((k_pass_f64_pair<kLseJT, kLseNW, true>), grid, dim3(64 * kLseNW), 0, c->stream, ax, ay, sx.row_blocks,
                            sx.splits, sy.splits);
-    else if (P->fx_ks)
-        hipLaunchKernelGGL((k_pass_f64_pair<kLseJT, kLseNW, false, true>),
-                           dim3(gated_grid(c, (int64_t)sx.row_blocks * sx.splits + (int64_t)sy.row_blocks * sy.splits, kLseWgPerCu)),
-                           dim3(64 * kLseNW), 0, c->stream, ax, ay, sx.row_blocks, sx.splits, sy.splits);
-    else
+    else if (P->fx_ks) {
+        if (which != 1)
+            hipLaunchKernelGGL((k_pass_f64_pair<kLseJT, kLseNW, false, true>),
+                               dim3(gated_grid(c, (int64_t)sx.row_blocks * sx.splits + (int64_t)sy.row_blocks * sy.splits, kLseWgPerCu)),
+                               dim3(64 * kLseNW), 0, c->stream, ax, ay, sx.row_blocks, sx.splits, sy.splits);
+    } else
         hipLaunchKernelGGL((k_pass_f64_pair<kLseJT, kLseNW, false>), grid, dim3(64 * kLseNW), 0, c->stream, ax, ay, sx.row_blocks,
                            sx.splits, sy.splits);
     prof_end(c);
@@ -716,6 +720,7 @@ fs_status f64_apply(Ctx *c, const Prepared *P, const Side *res, const Side *str,
     a.d = (int)P->d;
     const bool fx = P->fx_ks > 0;   // (the gate chooses between the fixed-point kernel and this file's)
     if (fx) a.gate = fx_gate(P, eps);
+    const int which = fx_known(c, P, eps);
     for (int p0 = 0; p0 < p;) {
         a.p0 = p0;
         // more than 64 columns left: a wide pass (128 columns) -- every pass repeats the score contraction
@@ -733,13 +738,15 @@ fs_status f64_apply(Ctx *c, const Prepared *P, const Side *res, const Side *str,
         int pc = width;
         if (fx) {
             int fx_splits = 0;
-            fs_status st = fx_apply_pass(c, P, res, str, eps, V, p, ldv, p0, hadA, lda, &fx_splits, &pc, &a.had_add);
+            fs_status st = fx_apply_pass(c, P, res, str, eps, V, p, ldv, p0, hadA, lda, &fx_splits, &pc, &a.had_add, which != 0);
             if (st != FS_OK) return st;
             splits = Splits(fx_splits, s.splits);
         }
         const dim3 grid((unsigned)s.row_blocks, (unsigned)s.splits);
 #define FS_F64_APPLY(H, N)                                                                                                         \
     do {                                                                                                                           \
+        if (fx && which == 1)                                                                                                      \
+            break;                                                                                                                 \
         if (fx)                                                                                                                    \
             hipLaunchKernelGGL((k_pass_f64<true, H, N, kApplyJT, kApplyNW, true, true>), grid, dim3(64 * kApplyNW), 0, c->stream, a); \
         else                                                                                                                       \

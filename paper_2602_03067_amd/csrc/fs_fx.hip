@@ -1066,13 +1066,18 @@ struct ApplyBuf {
 // d = 128, n = m = 10000 140 / 135; shifted normal points of spread 3, n = m = 16384, d = 64, where four of five are: 216 / 118).
 static bool fx_long(const PassShape &s) { return s.cols_per_split >= 24 * 32; }
 
-fs_status fx_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, int *splits)
+fs_status fx_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, int *splits, bool launch)
 {
     FxArgs a;
     PassShape s = fx_shape(c, res->cnt, str->cnt, fx_wg_per_cu(P->fx_ks, 3, 1, false));
     const bool lng = fx_long(s);
     fs_status st = pass_args(c, P, res, str, eps, lng ? 3 : 0, 1, false, P->partial, &a, &s);
     if (st != FS_OK) return st;
+    *splits = s.splits;
+    if (!launch) {
+        P->seeds.last[res == &P->X ? 0 : 1] = -1;   // (nothing writes the seeds of this pass)
+        return FS_OK;
+    }
     const dim3 grid((unsigned)s.row_blocks, (unsigned)s.splits);
 #define FX_LSE(KS)                                                                          \
     if (lng)                                                                                \
@@ -1087,11 +1092,10 @@ fs_status fx_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, do
     }
 #undef FX_LSE
     FS_HIP(c, hipGetLastError());
-    *splits = s.splits;
     return FS_OK;
 }
 
-fs_status fx_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, void *partial_y, int *splits_x, int *splits_y)
+fs_status fx_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, void *partial_y, int *splits_x, int *splits_y, bool launch)
 {
     FxArgs ax, ay;
     const int occ = fx_wg_per_cu(P->fx_ks, 3, 1, false);
@@ -1100,6 +1104,12 @@ fs_status fx_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, vo
     fs_status st;
     if ((st = pass_args(c, P, &P->X, &P->Y, eps, lng ? 3 : 0, 1, false, partial_x, &ax, &sx)) != FS_OK) return st;
     if ((st = pass_args(c, P, &P->Y, &P->X, eps, lng ? 3 : 0, 1, false, partial_y, &ay, &sy)) != FS_OK) return st;
+    *splits_x = sx.splits;
+    *splits_y = sy.splits;
+    if (!launch) {
+        P->seeds.last[0] = P->seeds.last[1] = -1;
+        return FS_OK;
+    }
     const dim3 grid((unsigned)(sx.row_blocks + sy.row_blocks), (unsigned)(sx.splits > sy.splits ? sx.splits : sy.splits));
 #define FX_PAIR(KS)                                                                                                         \
     if (lng)                                                                                                                \
@@ -1114,8 +1124,6 @@ fs_status fx_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, vo
     }
 #undef FX_PAIR
     FS_HIP(c, hipGetLastError());
-    *splits_x = sx.splits;
-    *splits_y = sy.splits;
     return FS_OK;
 }
 
@@ -1140,7 +1148,7 @@ size_t fx_apply_ws(const Ctx *c, int64_t n_res, int64_t n_str, int64_t d, int64_
 // one pass of an application: columns p0 .. of V; *pc = row length of the accumulators in P->extra.  hadA != nullptr:
 // Hadamard-weighted, with the rows of hadA [res->cnt][lda]; *had_add: see FxArgs.
 fs_status fx_apply_pass(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, const float *V, int64_t p, int64_t ldv,
-                        int p0, const float *hadA, int64_t lda, int *splits, int *pc, const double **had_add)
+                        int p0, const float *hadA, int64_t lda, int *splits, int *pc, const double **had_add, bool launch)
 {
     int mode, nc;
     fx_columns(p - p0, hadA != nullptr, &mode, &nc);
@@ -1158,7 +1166,7 @@ fs_status fx_apply_pass(Ctx *c, const Prepared *P, const Side *res, const Side *
     a.opart = (float *)P->extra;
     a.vimg = x + buf.vimg;
     a.vflag = reinterpret_cast<const int *>(x + buf.vflag);
-    if (mode == 2)
+    if (mode == 2 && launch)
         hipLaunchKernelGGL(k_vimg_fx, dim3((unsigned)a.n_tiles), dim3(128 * nc), 0, c->stream, V, ldv, str->cnt, p0, (int)p, nc,
                            x + buf.vimg, reinterpret_cast<int *>(x + buf.vflag), a.gate);
     if (hadA) {
@@ -1170,6 +1178,8 @@ fs_status fx_apply_pass(Ctx *c, const Prepared *P, const Side *res, const Side *
         hipLaunchKernelGGL(k_had_digits, dim3((unsigned)(res->cnt_pad / 32)), dim3(256), 0, c->stream, hadA, lda, res->cnt, (int)P->d,
                            P->fx_ks, P->scalars + 11, x + buf.had, reinterpret_cast<float *>(x + buf.scale), add);
     }
+    *splits = s.splits;
+    if (!launch) return FS_OK;
     const dim3 grid((unsigned)s.row_blocks, (unsigned)s.splits);
     switch (P->fx_ks) {
     case 1: launch_apply<1>(c, a, grid, mode, nc); break;
@@ -1178,7 +1188,6 @@ fs_status fx_apply_pass(Ctx *c, const Prepared *P, const Side *res, const Side *
     default: launch_apply<4>(c, a, grid, mode, nc); break;
     }
     FS_HIP(c, hipGetLastError());
-    *splits = s.splits;
     return FS_OK;
 }
 

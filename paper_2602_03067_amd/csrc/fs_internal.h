@@ -3,6 +3,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 #include <memory>
@@ -207,6 +208,10 @@ struct Ctx {
     // numbers that a kernel hands to the host (pinned), and when they are there: the conjugate gradients' (made when first used)
     double *pin = nullptr;
     hipEvent_t pin_ready = nullptr;
+    // Scalars that decide what the host launches next, written there by the kernels that have them (pinned; every word carries the
+    // stamp of its call in the upper half, so no order of the writes is asked for; nullptr: copies instead)
+    unsigned long long *box = nullptr;
+    uint32_t box_stamp = 0;
     std::string err;
     // Derived copies kept across entry calls (fs_points_keep): what identifies the clouds the caller has declared
     // unchanged, whether the workspace currently holds their derived copies, and the host-side value that belongs
@@ -230,6 +235,7 @@ struct Ctx {
     size_t mom_denied = SIZE_MAX;   // bytes of moment buffers that there was no memory for
     PointsKey kept_key;
     double kept_rho_max = -1.0;
+    uint32_t kept_fx_stamp = 0;
     // test and experiment switches of this context (fs_debug_set); 0 = the library decides
     int dbg_lowd_splits = 0;         // forced split count of the streamed side of a low-d pass
     int dbg_lowd_score = 0;          // 32: fp32 scores, 64: float64 scores in every low-d half-step
@@ -370,6 +376,7 @@ struct Prepared {
     mutable MomState mom;            // LowD, d <= 3
     int kp = 0;   // F64 / BF16: padded contraction length
     int fx_ks = 0;   // F64: k-steps of the digit images, 0: none
+    uint32_t fx_stamp = 0;           // the stamp under which r2 comes to the host (see fx_known), 0: it does not
     // fixed-point passes: what the last pass over the rows of X [0] and Y [1] left about them (FxSeed), two buffers a side in turn
     struct Seeds {
         char *buf[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};
@@ -401,6 +408,10 @@ struct FxSeed {
 // bytes of one buffer of a side: 64 splits of a small side, or what fills the chip four times
 inline size_t fx_seed_bytes(int64_t cnt_pad) { return (size_t(2) << 20) + (size_t)cnt_pad * 2 * sizeof(FxSeed); }
 
+// Ctx::box: one word for the exponent of r2, two for each scalar of the low-d prologue (see launch_bias_from_user)
+constexpr int kBoxFx = 0, kBoxLowd = 8, kBoxWords = 64;
+constexpr int kFxNoScale = 0x4000;   // instead of the exponent: the scale is not finite
+
 // the gate of a pass at `eps` (r2 sits in scalars[10])
 inline FxGate fx_gate(const Prepared *P, double eps)
 {
@@ -408,6 +419,19 @@ inline FxGate fx_gate(const Prepared *P, double eps)
     g.r2 = P->fx_ks ? P->scalars + 10 : nullptr;
     g.cscale = 2.0 * kLog2e * (1.0 / eps);   // (as store_fx_record forms it)
     return g;
+}
+
+// Which of the two kernels of a pass runs, as far as the host knows: 1 the fixed-point one, 0 the other, -1 not known yet, launch both.
+// The scale arrives while the first passes of a call run; nothing waits for it.
+inline int fx_known(const Ctx *c, const Prepared *P, double eps)
+{
+    if (!c->box || !P->fx_ks || !P->fx_stamp) return -1;
+    const unsigned long long w = __atomic_load_n(c->box + kBoxFx, __ATOMIC_RELAXED);
+    if ((uint32_t)(w >> 32) != P->fx_stamp) return -1;
+    const int ex = (int)(int16_t)(w & 0xffff);
+    if (ex == kFxNoScale) return 0;
+    const double r = ldexp(1.0, ex), v = 2.0 * kLog2e * (1.0 / eps) * r * r;   // (as FxGate::on has it)
+    return v >= kFxLow && v <= kFxHigh;
 }
 
 // Where the bias of point i of a side lives, by path, and the squared norms that turn the
@@ -620,11 +644,12 @@ fs_status f64_apply(Ctx *c, const Prepared *P, const Side *res, const Side *str,
                     const float *hadA = nullptr, int64_t lda = 0);
 
 // fs_fx.hip: the fixed-point kernels of a pass (P->fx_ks > 0); they leave at once where the gate is off
-fs_status fx_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, int *splits);
-fs_status fx_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, void *partial_y, int *splits_x, int *splits_y);
+// (launch = false: the host knows that the gate is off, only the shapes are asked for)
+fs_status fx_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, int *splits, bool launch);
+fs_status fx_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, void *partial_y, int *splits_x, int *splits_y, bool launch);
 size_t fx_apply_ws(const Ctx *c, int64_t n_res, int64_t n_str, int64_t d, int64_t p);
 fs_status fx_apply_pass(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, const float *V, int64_t p, int64_t ldv,
-                        int p0, const float *hadA, int64_t lda, int *splits, int *pc, const double **had_add);
+                        int p0, const float *hadA, int64_t lda, int *splits, int *pc, const double **had_add, bool launch);
 
 // fs_bf16.hip
 fs_status bf16_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps,

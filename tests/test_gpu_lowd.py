@@ -674,3 +674,25 @@ def test_applications_with_one_and_two_row_blocks(n, m, d, p):
     assert float(((out[rows].double() - want).abs() / r[:, None]).max()) <= 2e-4 * float(V.abs().max())
     assert float((mass[rows].double() / r - 1.0).abs().max()) <= 2e-4
     c.close()
+
+
+@pytest.mark.parametrize("n,m,d", [(300, 200, 3), (300, 200, 10)])
+def test_scalars_of_the_prologue_behind_long_work(n, m, d):
+    """The host looks for the scalars that choose the score arithmetic, and waits for the stream where they take long: the same result
+    behind work of a few milliseconds as on an idle stream, with two contexts in turn."""
+    rng = np.random.default_rng(n + d)
+    prob = make_problem(rng.standard_normal((n, d)).astype(np.float32), rng.standard_normal((m, d)).astype(np.float32), None, None)
+    g = dev((rng.standard_normal(m) * 0.1).astype(np.float32))
+    say("scalars behind long work d=%d" % d)
+    ctxs = [binding.Context(0), binding.Context(0)]
+    want = host(ctxs[0].fs_update_f(prob, 0.1, g))
+    big = torch.rand(6000, 6000, device="cuda:0")
+    for k in range(4):
+        torch.cuda.synchronize()
+        out = big
+        for _ in range(4):
+            out = out @ big
+        got = ctxs[k & 1].fs_update_f(prob, 0.1, g)
+        assert np.array_equal(host(got), want)
+    for c in ctxs:
+        c.close()
