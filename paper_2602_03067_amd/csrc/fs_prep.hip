@@ -379,43 +379,64 @@ __global__ void k_prep_f64(const void *pts, int dtype, int64_t cnt, int64_t cnt_
 // needs in LDS, so the streaming kernel fills LDS with linear direct loads, each wave a contiguous run
 // of it, and reads MFMA fragments without bank conflicts; the contraction loop of a tile walks through
 // memory linearly.
-__global__ void k_prep_bf16(const void *pts, int dtype, int64_t cnt, int64_t cnt_pad, int64_t d, int64_t ld, int kp,
-                            uint16_t *out, float *bias, double *norm)
+typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));       // four floats, sixteen bytes at an address that is only
+typedef uint32_t u4_any __attribute__((ext_vector_type(4), aligned(2)));    // a multiple of the element's size (one load here)
+// A workgroup makes sixteen rows, a wave a whole 1 KB tile at a time (lane: row l / 4, piece l % 4), every fourth chunk.  Bound by the
+// memory, 330 MB at n = 40009, m = 30011, d = 784 in fp32: 158 us with a wave per row and a load per coordinate, 68 here (what is read
+// last is still in the last-level cache).
+__global__ __launch_bounds__(256) void k_prep_bf16(const void *pts, int dtype, int64_t cnt, int64_t d, int64_t ld, int kp, uint16_t *out, float *bias,
+                                                   double *norm)
 {
-    int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    int lane = threadIdx.x & 63;
-    if (row >= cnt_pad) return;
-    const int n_chunks = kp >> 5;
-    const int64_t rb = row >> 4;
-    const int rl = (int)(row & 15);
+    __shared__ double shn[4][16];
+    const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
+    const int64_t rb = blockIdx.x, row = rb * 16 + (l >> 2);
+    const int n_chunks = kp >> 5, piece = l & 3;
+    const int64_t base = row * ld;
+    const bool real = row < cnt;
+    unsigned char *dst = reinterpret_cast<unsigned char *>(out) + (((rb >> 4) * n_chunks * 16 + (rb & 15)) << 10) + (l >> 2) * 64 +
+                         ((piece ^ ((l >> 4) & 3)) << 4);
     double nrm = 0.0;
-    for (int pi = lane; pi < (kp >> 3); pi += 64) {   // one 16-byte piece = 8 coordinates
+#pragma unroll 4
+    for (int ch = w; ch < n_chunks; ch += 4) {
+        const int k0 = ch * 32 + piece * 8;
         uint16_t h[8];
+        if (real && k0 + 8 <= d) {
+            if (dtype == FS_BF16) {
+                const u4_any v = *reinterpret_cast<const u4_any *>((const uint16_t *)pts + base + k0);
+                const uint32_t q[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            int k = pi * 8 + e;
-            h[e] = 0;
-            if (row < cnt && k < d) {
-                h[e] = dtype == FS_BF16 ? ((const uint16_t *)pts)[row * ld + k]
-                                        : float_to_bf16(((const float *)pts)[row * ld + k]);
-                double v = (double)bf16_to_float(h[e]);
-                nrm += v * v;
+                for (int e = 0; e < 8; ++e) h[e] = (uint16_t)(q[e >> 1] >> (16 * (e & 1)));
+            } else {
+                const f4_any v0 = *reinterpret_cast<const f4_any *>((const float *)pts + base + k0);
+                const f4_any v1 = *reinterpret_cast<const f4_any *>((const float *)pts + base + k0 + 4);
+                const float q[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+#pragma unroll
+                for (int e = 0; e < 8; ++e) h[e] = float_to_bf16(q[e]);
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                h[e] = 0;
+                if (real && k0 + e < d)
+                    h[e] = dtype == FS_BF16 ? ((const uint16_t *)pts)[base + k0 + e] : float_to_bf16(((const float *)pts)[base + k0 + e]);
             }
         }
-        const int ch = pi >> 2, piece = pi & 3;
-        const int pos = piece ^ ((rl >> 2) & 3);
-        uint4 v;
-        v.x = (uint32_t)h[0] | ((uint32_t)h[1] << 16);
-        v.y = (uint32_t)h[2] | ((uint32_t)h[3] << 16);
-        v.z = (uint32_t)h[4] | ((uint32_t)h[5] << 16);
-        v.w = (uint32_t)h[6] | ((uint32_t)h[7] << 16);
-        *reinterpret_cast<uint4 *>(reinterpret_cast<unsigned char *>(out) +
-                                   ((((rb >> 4) * n_chunks + ch) * 16 + (rb & 15)) << 10) + rl * 64 + pos * 16) = v;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const double v = (double)bf16_to_float(h[e]);
+            nrm += v * v;
+        }
+        *reinterpret_cast<uint4 *>(dst + ((int64_t)ch << 14)) =
+            make_uint4((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16), (uint32_t)h[4] | ((uint32_t)h[5] << 16),
+                       (uint32_t)h[6] | ((uint32_t)h[7] << 16));
     }
-    for (int off = 32; off > 0; off >>= 1) nrm += __shfl_xor(nrm, off, 64);
-    if (lane == 0) {
-        norm[row] = nrm;
-        bias[row] = -INFINITY;
+    nrm += __shfl_xor(nrm, 1);
+    nrm += __shfl_xor(nrm, 2);
+    if (piece == 0) shn[w][l >> 2] = nrm;
+    __syncthreads();
+    if (tid < 16) {
+        norm[rb * 16 + tid] = shn[0][tid] + shn[1][tid] + shn[2][tid] + shn[3][tid];
+        bias[rb * 16 + tid] = -INFINITY;
     }
 }
 
@@ -1145,8 +1166,8 @@ fs_status launch_prepare(Ctx *c, const fs_problem *p, Prepared *P)
                                dtype, s.S->cnt, s.S->cnt_pad, p->d, s.ld, P->kp, s.S->pts_d, s.S->bias_d, s.S->norm);
     } else {
         for (auto &s : in)
-            hipLaunchKernelGGL(k_prep_bf16, dim3((unsigned)ceil_div(s.S->cnt_pad, 4)), dim3(256), 0, c->stream, s.pts,
-                               dtype, s.S->cnt, s.S->cnt_pad, p->d, s.ld, P->kp, s.S->pts_b, s.S->bias_f, s.S->norm);
+            hipLaunchKernelGGL(k_prep_bf16, dim3((unsigned)(s.S->cnt_pad / 16)), dim3(256), 0, c->stream, s.pts, dtype, s.S->cnt, p->d, s.ld,
+                               P->kp, s.S->pts_b, s.S->bias_f, s.S->norm);
     }
     FS_HIP(c, hipGetLastError());
     return FS_OK;

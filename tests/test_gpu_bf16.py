@@ -322,3 +322,33 @@ def test_stored_plan_workspace_is_bounded(n, m, d, p, most):
     say("  workspace %.0f MiB" % used)
     problem = (n + m) * (d + 32) * 2 / 2 ** 20 + 2 * 64   # bf16 copies, potentials, split records
     assert used <= problem + most
+
+
+@pytest.mark.parametrize("storage", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("d,pad,off", [(16, 0, 0), (24, 8, 0), (24, 8, 1), (40, 0, 0), (41, 0, 0), (52, 12, 4), (100, 4, 3), (784, 0, 0)])
+def test_derived_copies_of_clouds_of_any_stride_and_alignment(storage, d, pad, off):
+    """The prologue takes eight coordinates at a time, at any address, and one at a time in a ragged end: the same copies and
+    norms, hence the same potentials bit for bit, from a view of any stride and offset and from a copy of it in aligned rows."""
+    n, m = 300, 77
+    gen = torch.Generator(device="cuda:0").manual_seed(d + off)
+    def view(k):
+        return torch.randn(k, d + pad, generator=gen, device="cuda:0").to(storage)[:, off:off + d]
+    x, y = view(n), view(m)
+    ctx = binding.Context(0)
+    say("bf16 derived copies d=%d pad=%d off=%d %s" % (d, pad, off, storage))
+    out = []
+    for X, Y in ((x, y), tuple(torch.nn.functional.pad(t, (0, -d % 8))[:, :d] for t in (x, y))):
+        f, g = torch.zeros(n, device="cuda:0"), torch.zeros(m, device="cuda:0")
+        ctx.fs_solve(binding.Problem(X, Y, None, None, binding.FS_COMPUTE_BF16_MFMA), 0.3 * d, 0.3 * d, 1, 2, f, g)
+        out.append((host(f), host(g)))
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+    # and against float64 half-steps on the rounded points
+    X, Y = (t.to(torch.bfloat16).double().cpu().numpy() for t in (x, y))
+    eps = float(np.float32(0.3 * d))
+    C = ((X[:, None, :] - Y[None, :, :]) ** 2).sum(2)
+    fo, go = np.zeros(n), np.zeros(m)
+    for _ in range(2):
+        fo = -eps * np.log(np.exp((go[None, :] - C) / eps).mean(1))
+        go = -eps * np.log(np.exp((fo[:, None] - C) / eps).mean(0))
+    assert np.abs(out[0][0] - fo).max() <= 1e-4 * eps and np.abs(out[0][1] - go).max() <= 1e-4 * eps
+    ctx.close()
