@@ -36,10 +36,16 @@
 // Sums are formed in a fixed order (the sort is stable), so a result does not depend on the run.
 //
 // Measured (half-step, us, over the pairs and here): n = m = 262144, d = 3, mixture and cube, eps = 0.01: 5900 -> 1950, 0.046: 5900
-// -> 270, 1: 5900 -> 80; n = 50021, m = 40013, cube, eps = 0.05: 219 -> 57.
-// Bound at large sizes: vector and matrix instructions of k_mom_gather (a weight costs its exponential, three fma and the split, 130
-// instructions per 16 points and 32 cells beside 42 products at RT = 7), moments through LDS in k_mom_rows; at small ones
-// latency, both kernels take 8 us without their loops.
+// -> 270, 1: 5900 -> 80; n = 50021, m = 40013, cube, eps = 0.05: 219 -> 57 (all before the waves of a SIMD took turns, see below).
+// Bound at large sizes: what a SIMD's two waves do not overlap of the vector, matrix and LDS instructions of k_mom_gather (a weight
+// costs its exponential, three fma and the split, 110 instructions per 16 points and 32 cells beside 21 products at RT = 7; products
+// alone would take a third of its time), products of k_mom_rows (three quarters of its loop); at small ones latency, both kernels
+// take 8 us without their loops.
+// What helps both is that the two waves of a SIMD (w and w + 4) do not do the same at a time, so that one's products run beside the
+// other's vector instructions, and that reads from LDS are on their way before they are waited for, where the compiler would place each
+// at its use.  At n = m = 262144: gather of 763 blocks for 384 cells at RT = 7 350 -> 310 us, rows of 568 groups over 1331 cells 336 -> 272.
+// Tried: the exponents as fp32 products on the matrix cores, 295 us for the 310 above, but 30 for 28.6 where a wave has every other
+// k-step, and other roundings; four tiles of monomials at a time and two workgroups per CU, weights formed twice: 302, 31.8.
 // Tried, as the whole call of four stages of one iteration at n = m = 262144 (48 ms over the pairs, 4.8 here): fp32 matrix
 // instructions 9.4 ms; three bf16 pieces and six products 6.7 with every wave forming the monomials for itself (their LDS reads
 // bound it), 6.9 with shared ones and moments as floats split by the rows' kernel.
@@ -55,6 +61,7 @@ namespace {
 typedef float f16v __attribute__((ext_vector_type(16)));
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 
 // Power tables in LDS: row = power (see pow_stride), then ones, biases, values; column = point
 constexpr int kOne = 30, kBias = 31, kValue = 32;
@@ -105,7 +112,7 @@ constexpr Basis kBasisHost = make_basis();
 __device__ const Basis kBasis = make_basis();
 
 // powers of a point's coordinates in half cells
-template <int STRIDE> __device__ __forceinline__ void fill_powers(float *tab, const int pt, const float4 v, const int d)
+template <int STRIDE> __device__ __forceinline__ void fill_powers(float *tab, const int pt, const float4 v, const int d, const float first = 1.0f)
 {
     const int st = pow_stride(d);
     const float c[3] = {v.x, v.y, v.z};
@@ -113,7 +120,7 @@ template <int STRIDE> __device__ __forceinline__ void fill_powers(float *tab, co
     for (int k = 0; k < 3; ++k) {
         if (k >= d) break;
         float *o = tab + k * st * STRIDE + pt;
-        float q = 1.0f;
+        float q = k ? 1.0f : first;
         for (int e = 0; e < st; ++e) {
             o[e * STRIDE] = q;
             q *= c[k];
@@ -127,13 +134,20 @@ template <int STRIDE> __device__ __forceinline__ void fill_powers(float *tab, co
 __device__ __forceinline__ void split8(const float (&v)[8], h8 (&o)[2])
 {
 #pragma unroll
-    for (int z = 0; z < 8; ++z) {
-        float x = v[z];
+    for (int z = 0; z < 8; z += 2) {
+        float x = v[z], y = v[z + 1];
         // (opaque: the compiler folds the product that v comes from into one of the two conversions of it, and where that rounds
         // once instead of twice the pieces are a leading digit apart)
-        asm("" : "+v"(x));
-        o[0][z] = (_Float16)x;
-        o[1][z] = (_Float16)(x - (float)o[0][z]);
+        asm("" : "+v"(x), "+v"(y));
+        h2 hi{(_Float16)x, (_Float16)y};
+        asm("" : "+v"(hi));   // (or it converts each a second time for the difference)
+        // (x - hi in one instruction, which takes its fp16 operand from either half: 16 instructions for eight floats, not 32)
+        float dx, dy;
+        asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(dx) : "v"(hi), "v"(x));
+        asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(dy) : "v"(hi), "v"(y));
+        const h2 lo{(_Float16)dx, (_Float16)dy};
+        o[0][z] = hi[0], o[0][z + 1] = hi[1];
+        o[1][z] = lo[0], o[1][z + 1] = lo[1];
     }
 }
 __device__ __forceinline__ f16v mm2(const h8 (&a)[2], const h8 (&b)[2], f16v c)
@@ -380,7 +394,8 @@ struct GatherArgs {
 // for 4 where `halves` is set; then waves w and w + 4 share their cells and take every other k-step of 16 points each.
 // A stage is 32 points.  Their monomials (A operand: a lane holds those of eight points) are formed once for all waves, in two
 // fp16 pieces in LDS, while the stage before is multiplied; a wave's own are the weights of the points for its 32 cells (B operand:
-// eight exponentials per lane and k-step).
+// eight exponentials per lane and k-step).  Waves 0 to 3 form their share of the next stage's monomials before this stage's products,
+// waves 4 to 7 after them.
 template <int TW>
 __global__ __launch_bounds__(512, 2) void k_mom_gather(GatherArgs a)
 {
@@ -433,14 +448,15 @@ __global__ __launch_bounds__(512, 2) void k_mom_gather(GatherArgs a)
     top = ceil(top);
     const int vexp = col && vtop > 0.0f ? ilogbf(vtop) + 1 : 0;
 #pragma unroll
-    for (int z = 0; z < 2; ++z) vb[z] = sign * ldexpf(vb[z], -vexp);
+    for (int z = 0; z < 2; ++z) vb[z] = ldexpf(vb[z], -vexp);
 
     const int xt = a.halves ? (int)blockIdx.y * 4 + (w & 3) : (int)blockIdx.y * 8 + w;
     const int cell = xt * 32 + lj;
     const bool busy = xt * 32 < a.ncells;
-    const int ks0 = a.halves ? w >> 2 : 0, ks1 = a.halves ? ks0 + 1 : 2;
+    const int ks0 = a.halves ? w >> 2 : 0, ks1 = !busy ? ks0 : a.halves ? ks0 + 1 : 2;
+    const bool late = w >= 4;   // (the other wave of this SIMD is not)
     const double4 c0 = a.centre[min(cell, a.ncells - 1)];
-    const float tilt[3] = {(float)(a.cscale * c0.x * 0.5 * a.sg.h[0]), a.d > 1 ? (float)(a.cscale * c0.y * 0.5 * a.sg.h[1]) : 0.0f,
+    const float tilt[3] = {sign * (float)(a.cscale * c0.x * 0.5 * a.sg.h[0]), a.d > 1 ? (float)(a.cscale * c0.y * 0.5 * a.sg.h[1]) : 0.0f,
                            a.d > 2 ? (float)(a.cscale * c0.z * 0.5 * a.sg.h[2]) : 0.0f};
     const int st = pow_stride(a.d);
     const int p1 = (a.d > 1 ? st + 1 : kOne) * ST, p2 = (a.d > 2 ? 2 * st + 1 : kOne) * ST;
@@ -465,14 +481,13 @@ __global__ __launch_bounds__(512, 2) void k_mom_gather(GatherArgs a)
         for (int i = 0; i < NU; ++i) {
             const int u = tid + 512 * i;
             if (NU * 512 != 2 * TW * 64 && u >= 2 * TW * 64) break;
-            float m[8], c[8];
+            float m[8], c[2][8];
             eight(tab + uo[i][0] + pt, m);
-            eight(tab + uo[i][1] + pt, c);
+            eight(tab + uo[i][1] + pt, c[0]);
+            eight(tab + uo[i][2] + pt, c[1]);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int z = 0; z < 8; ++z) m[z] *= c[z];
-            eight(tab + uo[i][2] + pt, c);
-#pragma unroll
-            for (int z = 0; z < 8; ++z) m[z] *= c[z];
+            for (int z = 0; z < 8; ++z) m[z] = m[z] * c[0][z] * c[1][z];
             h8 o[2];
             split8(m, o);
 #pragma unroll
@@ -492,7 +507,7 @@ __global__ __launch_bounds__(512, 2) void k_mom_gather(GatherArgs a)
         if ((tid >> 8) == (base >> 8 & 1)) {
             const int z = base >> 9, i = tid & 255;
             const double u = z ? ub[1] : ub[0];
-            fill_powers<ST>(tab, i, z ? xb[1] : xb[0], a.d);
+            fill_powers<ST>(tab, i, z ? xb[1] : xb[0], a.d, sign);
             tab[kBias * ST + i] = u == -INFINITY ? -INFINITY : (float)(u - top);
             tab[kValue * ST + i] = z ? vb[1] : vb[0];
         }
@@ -501,23 +516,20 @@ __global__ __launch_bounds__(512, 2) void k_mom_gather(GatherArgs a)
         int cur = 0;
         for (int pt = 0; pt < cnt; pt += 32, cur ^= 1) {
             __syncthreads();   // this stage's monomials are there, and the other buffer is read
-            if (pt + 32 < cnt) monomials(pt + 32, frag[cur ^ 1]);
-            if (!busy) continue;
+            const bool more = pt + 32 < cnt;
+            if (more && !late) monomials(pt + 32, frag[cur ^ 1]);
             for (int ks = ks0; ks < ks1; ++ks) {
                 const float *q = tab + pt + 16 * ks + 8 * lh;
-                float e[8], c[8];
+                float e[8], x[3][8];
                 eight(q + kBias * ST, e);
-                eight(q + ST, c);
-#pragma unroll
-                for (int z = 0; z < 8; ++z) e[z] = fmaf(tilt[0], c[z], e[z]);
-                eight(q + p1, c);
-#pragma unroll
-                for (int z = 0; z < 8; ++z) e[z] = fmaf(tilt[1], c[z], e[z]);
-                eight(q + p2, c);
+                eight(q + ST, x[0]);
+                eight(q + p1, x[1]);
+                eight(q + p2, x[2]);
+                __builtin_amdgcn_sched_barrier(0);   // (all reads on their way before the first wait)
                 float big = -INFINITY;
 #pragma unroll
                 for (int z = 0; z < 8; ++z) {
-                    e[z] = fmaf(tilt[2], c[z], e[z]);
+                    e[z] = fmaf(tilt[2], x[2][z], fmaf(tilt[1], x[1][z], fmaf(tilt[0], x[0][z], e[z])));
                     big = fmaxf(big, e[z]);
                 }
                 if (__any(big > off + 14.0f)) {
@@ -530,24 +542,35 @@ __global__ __launch_bounds__(512, 2) void k_mom_gather(GatherArgs a)
 #pragma unroll
                         for (int r = 0; r < 16; ++r) acc[t][r] *= f;
                 }
-                eight(q + kValue * ST, c);
 #pragma unroll
-                for (int z = 0; z < 8; ++z) {
-                    e[z] = c[z] * __builtin_amdgcn_exp2f(e[z] - off);
-                    mass += fabsf(e[z]);
+                for (int z = 0; z < 8; ++z) e[z] = __builtin_amdgcn_exp2f(e[z] - off);
+                if (col) {
+                    eight(q + kValue * ST, x[0]);
+#pragma unroll
+                    for (int z = 0; z < 8; ++z) e[z] *= x[0][z];
                 }
+                mass += ((fabsf(e[0]) + fabsf(e[1])) + (fabsf(e[2]) + fabsf(e[3]))) + ((fabsf(e[4]) + fabsf(e[5])) + (fabsf(e[6]) + fabsf(e[7])));
+                asm("" : "+v"(mass));   // (here: later, the weights would be copied for it)
                 h8 eb[2];
                 split8(e, eb);
                 const unsigned char *f = frag[cur] + ks * (TW * 2 * 1024) + l * 16;
+                // a tile's monomials are read two tiles before their products (the compiler would read them right there, and wait)
+                h8 ma[3][2];
+                auto operand = [&](int t) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) ma[t % 3][k] = *reinterpret_cast<const h8 *>(f + (t * 2 + k) * 1024);
+                };
+                operand(0);
+                if (TW > 1) operand(1);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int t = 0; t < TW; ++t) {
-                    if (t >= nt) break;
-                    h8 ma[2];
-#pragma unroll
-                    for (int k = 0; k < 2; ++k) ma[k] = *reinterpret_cast<const h8 *>(f + (t * 2 + k) * 1024);
-                    acc[t] = mm2(ma, eb, acc[t]);
+                    if (t + 2 < TW) operand(t + 2);
+                    acc[t] = mm2(ma[t % 3], eb, acc[t]);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
             }
+            if (more && late) monomials(pt + 32, frag[cur ^ 1]);
         }
     }
     mass += __shfl_xor(mass, 32);
@@ -681,13 +704,13 @@ struct RowArgs {
 // One workgroup of eight waves: up to 256 rows of one cell, 32 per wave, against all streamed cells, 32 at a time.  Their moments
 // (A operand) arrive in a ring of three tiles in LDS; the rows' monomials with their coefficients stay in registers in two pieces (B
 // operand).  What comes out is, in lane j, sixteen cells' sums for row j, which get the factor 2^(...) that is left of the pair of
-// cells and the row.
+// cells and the row: right away in waves 0 to 3, after the next tile's barrier, before its products, in waves 4 to 7.
 // A cell's 8 RT units of 16 bytes are rotated by a number of units that depends on its place in the tile, so that the reads of
 // sixteen cells at one unit fall on different banks.
 __device__ __forceinline__ int round_up_32(int v) { return (v + 31) & ~31; }
 template <int RT> __device__ __forceinline__ int unit_rot(int c) { return (RT % 2 ? c >> 1 : c) & (RT == 1 ? 7 : 15); }
 template <int RT>
-__global__ __launch_bounds__(512, 2) void k_mom_rows(RowArgs a)
+__global__ __launch_bounds__(512, RT <= 2 ? 4 : 2) void k_mom_rows(RowArgs a)
 {
     constexpr int RP = 32 * RT, KS = 2 * RT, UN = 8 * RT;   // units of a cell
     constexpr int ST = kMomRows + 4;
@@ -717,15 +740,19 @@ __global__ __launch_bounds__(512, 2) void k_mom_rows(RowArgs a)
 #pragma unroll
     for (int i = 0; i < NF; ++i) {
         const int u = (w * NF + i) * 64 + l, c = u / UN, p = u - c * UN - unit_rot<RT>(c) % UN;
-        fc[i] = c;
+        fc[i] = min(c, 31);   // (units beyond the tile are not fetched)
         fo[i] = (p < 0 ? p + UN : p) * 16;
     }
     // (k0: within the segment; no global load but the copies themselves, or a wait for it would be one for them)
     auto fetch = [&](int k0, int buf) __attribute__((always_inline)) {
+        int b[NF];
+#pragma unroll
+        for (int i = 0; i < NF; ++i) b[i] = fb[k0 + fc[i]];
+        __builtin_amdgcn_sched_barrier(0);   // (one wait for all of them)
 #pragma unroll
         for (int i = 0; i < NF; ++i) {
             if (RT % 2 && w * NF + i >= 4 * RT) break;
-            dma16(M + (int64_t)fb[k0 + fc[i]] * (RP * 4) + fo[i], ring_off + buf * kTile + (w * NF + i) * 1024);
+            dma16(M + (int64_t)b[i] * (RP * 4) + fo[i], ring_off + buf * kTile + (w * NF + i) * 1024);
         }
     };
     const double4 x0 = a.tcentre[grp.x];
@@ -835,7 +862,23 @@ __global__ __launch_bounds__(512, 2) void k_mom_rows(RowArgs a)
     // (8 RT units per cell: leading pieces, then trailing ones)
     const int rot = unit_rot<RT>(lj) % UN;
     double sum = 0.0;
-    const bool busy = 32 * w < grp.z;
+    const bool busy = 32 * w < grp.z, late = w >= 4;
+    f16v acc;
+    auto settle = [&](int k0) __attribute__((always_inline)) {
+        constexpr int B = RT <= 2 ? 4 : 8;   // reads at a time (at RT <= 2 eight would take a CU's second workgroup: 27 -> 37 us at 1040 groups)
+        float s = 0.0f;
+#pragma unroll
+        for (int h = 0; h < 16; h += B) {
+            float4 e[B];
+#pragma unroll
+            for (int r = 0; r < B; ++r) e[r] = pair[k0 + 8 * ((h + r) >> 2) + 4 * lh + (r & 3)];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int r = 0; r < B; ++r)
+                s = fmaf(acc[h + r], __builtin_amdgcn_exp2f(fmaf(r0, e[r].x, fmaf(r1, e[r].y, fmaf(r2, e[r].z, e[r].w)))), s);
+        }
+        sum += (double)s;
+    };
     for (int s0 = 0; s0 < a.ncell; s0 += kSeg) {
         if (s0) {
             __syncthreads();
@@ -855,7 +898,7 @@ __global__ __launch_bounds__(512, 2) void k_mom_rows(RowArgs a)
             __syncthreads();
             if (k0 + 64 < n) fetch(k0 + 64, buf == 0 ? 2 : buf - 1);
             if (!busy) continue;
-            f16v acc;
+            if (late && k0) settle(k0 - 32);
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
             const unsigned char *src = ring + buf * kTile + lj * (RP * 4);
@@ -870,14 +913,9 @@ __global__ __launch_bounds__(512, 2) void k_mom_rows(RowArgs a)
                 }
                 acc = mm2(v, psi[k], acc);
             }
-            float s = 0.0f;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float4 e = pair[k0 + 8 * (r >> 2) + 4 * lh + (r & 3)];
-                s = fmaf(acc[r], __builtin_amdgcn_exp2f(fmaf(r0, e.x, fmaf(r1, e.y, fmaf(r2, e.z, e.w)))), s);
-            }
-            sum += (double)s;
+            if (!late) settle(k0);
         }
+        if (late && busy) settle((n - 1) / 32 * 32);
     }
     sum += __shfl_xor(sum, 32);
     sum *= (double)sign;
@@ -967,7 +1005,8 @@ bool geometry(const MomState &S, int d, double eps, double tau, MomGeom (&g)[2],
 // one per CU: k_mom_gather's take 2.1 us and 0.64 us per tile of monomials and stage of 32 points (half of that where `halves` is set),
 // k_mom_rows' 3.6 us and 0.34 us per tile and 32 streamed cells, on top of what the chip's matrix cores and the moments' way
 // through memory take.  Fitted to 887 passes (150 problems, d = 1..3, n m = 3e8 .. 3e10, cells from 1 to 7000, 33 us to 62 ms): half of the
-// passes within 0.9 to 1.1 times, nine out of ten within 0.75 to 1.2 times what this says.
+// passes within 0.9 to 1.1 times, nine out of ten within 0.75 to 1.2 times what this says.  (The kernels take a tenth to a fifth less since;
+// the line to the passes over the pairs was left where it is.)
 double mom_cost(int rt, double nt, double ct, double gt, double ns, double cs, double bs, int cols, size_t slab, int num_cu)
 {
     const double span = floor((double)slab / (cols * bs * (128.0 * rt + 4.0)) / 32.0) * 32.0;
