@@ -185,7 +185,8 @@ def run_workload(name, steps, warmup, schedule="alternating", n_override=None, c
                 "unit": "TFLOP/s"}
         dtype = "bf16"
     elif digit_products(w):
-        # fixed-point scores on the int8 matrix cores
+        # fixed-point scores on the int8 matrix cores (the products of every tile are counted; long half-steps leave those of tiles
+        # whose scores cannot count undone but for the three leading ones, so this is the rate of the work asked for)
         flops = 2.0 * ((w.d + 31) // 32 * 32) * digit_products(w) * pairs
         roof = {"bound": "mfma", "achieved": flops / (avg_ms * 1e-3) / 1e12, "peak": PEAKS["i8"] / 1e12,
                 "unit": "TOP/s"}

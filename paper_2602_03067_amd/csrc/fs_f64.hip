@@ -1,7 +1,7 @@
 // fp32-accuracy path for d > 16: the score contraction <x_i, y_j> runs on the fp64 matrix
 // cores (v_mfma_f64_16x16x4_f64).  For 16 < d <= 128 and all but small problems the fixed-point kernels of
-// fs_fx.hip take its place (three times faster) wherever the points' scale allows; these kernels are then launched as
-// well (GATED) and leave at once.
+// fs_fx.hip take its place (three times faster) wherever the points' scale allows; where the host does not know that
+// scale yet these kernels are launched as well (GATED) and leave at once.
 //
 // Why fp64: with d = 64 and eps = 0.1 a score (2<x,y> - |y|^2 + g)/eps reaches ~2e3, where an
 // fp32 ulp is 1.2e-4 -- the whole error budget of 1e-4.  MI355X has 78.6 TFLOP/s of fp64 MFMA,

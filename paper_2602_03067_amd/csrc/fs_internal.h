@@ -127,9 +127,9 @@ enum class Path { LowD, F64, BF16 };
 constexpr int kFxMaxKs = 4;
 __host__ __device__ inline int fx_ksteps(int64_t d) { return d > kLowdMaxD && d <= 32 * kFxMaxKs ? (int)((d + 31) / 32) : 0; }
 
-// Decides on the device which of the two kernels of a pass runs: every pass of a problem with digit images is launched
-// twice, fixed point and float64, and one of the two leaves at once (the scale of the clouds is known on the device only,
-// and a read-back would make every entry call wait).  cscale r2^2 is the size of a score's unit-scale product in base-2
+// Decides on the device which of the two kernels of a pass runs, fixed point or float64: the scale of the clouds is known there
+// first.  Where it has reached the host's pinned box by the time of a launch (fx_known) only the kernel that runs is launched,
+// otherwise both are, and one of them leaves at once: no call waits for it.  cscale r2^2 is the size of a score's unit-scale product in base-2
 // units, v below; r2 covers the distance of the coordinates from the middle of their range, where k_prep_fx puts the origin.
 //
 // The upper line lies where the error of a score reaches the rounding of the exponential's float argument.  What counts there
