@@ -39,11 +39,12 @@
 // -> 270, 1: 5900 -> 80; n = 50021, m = 40013, cube, eps = 0.05: 219 -> 57 (all before the waves of a SIMD took turns, see below).
 // Bound at large sizes: what a SIMD's two waves do not overlap of the vector, matrix and LDS instructions of k_mom_gather (a weight
 // costs its exponential, three fma and the split, 110 instructions per 16 points and 32 cells beside 21 products at RT = 7; products
-// alone would take a third of its time), products of k_mom_rows (three quarters of its loop); at small ones latency, both kernels
-// take 8 us without their loops.
+// alone would take a third of its time), products of k_mom_rows (three quarters of its loop); at small ones latency, the gather takes
+// 8 us without its loops (as the rows did, 4 less now).
 // What helps both is that the two waves of a SIMD (w and w + 4) do not do the same at a time, so that one's products run beside the
 // other's vector instructions, and that reads from LDS are on their way before they are waited for, where the compiler would place each
-// at its use.  At n = m = 262144: gather of 763 blocks for 384 cells at RT = 7 350 -> 310 us, rows of 568 groups over 1331 cells 336 -> 272.
+// at its use.  At n = m = 262144: gather of 763 blocks for 384 cells at RT = 7 350 -> 310 us, rows of 568 groups over 1331 cells 336 -> 272
+// (259 since their monomials are formed in registers).
 // Tried: the exponents as fp32 products on the matrix cores, 295 us for the 310 above, but 30 for 28.6 where a wave has every other
 // k-step, and other roundings; four tiles of monomials at a time and two workgroups per CU, weights formed twice: 302, 31.8.
 // Tried, as the whole call of four stages of one iteration at n = m = 262144 (48 ms over the pairs, 4.8 here): fp32 matrix
@@ -691,7 +692,6 @@ struct RowArgs {
     const int *perm;
     MomGeom tg;
     double cscale;
-    int d, kind;
     float coef[kMaxTerms];              // c_alpha
     const int *first_block;             // where a streamed cell's moments are
     int nblock, cells, groups;          // blocks of the streamed side, row cells and groups of rows of the launch
@@ -709,18 +709,23 @@ struct RowArgs {
 // sixteen cells at one unit fall on different banks.
 __device__ __forceinline__ int round_up_32(int v) { return (v + 31) & ~31; }
 template <int RT> __device__ __forceinline__ int unit_rot(int c) { return (RT % 2 ? c >> 1 : c) & (RT == 1 ? 7 : 15); }
-template <int RT>
-__global__ __launch_bounds__(512, RT <= 2 ? 4 : 2) void k_mom_rows(RowArgs a)
+// power of coordinate k in a monomial of the basis
+constexpr int row_power(uint32_t e, int k, int stride)
 {
+    const int at = (int)(e >> 8 * k & 255);
+    return at == kOne ? 0 : at - k * stride;
+}
+template <int KIND>
+__global__ __launch_bounds__(512, kKind[KIND].rt <= 2 ? 4 : 2) void k_mom_rows(RowArgs a)
+{
+    constexpr int RT = kKind[KIND].rt, DIM = kKind[KIND].d, TOP = kKind[KIND].p;
     constexpr int RP = 32 * RT, KS = 2 * RT, UN = 8 * RT;   // units of a cell
-    constexpr int ST = kMomRows + 4;
-    constexpr int kTile = 32 * RP * 4, kTab = kTabRows * ST * 4;
-    __shared__ __attribute__((aligned(1024))) unsigned char ring[3 * kTile > kTile + kTab ? 3 * kTile : (kTile + kTab + 1023) / 1024 * 1024];
+    constexpr int kTile = 32 * RP * 4;
+    __shared__ __attribute__((aligned(1024))) unsigned char ring[3 * kTile];
     // of the streamed cells of a segment: what is left of the pair of cells, and where the moments are
     constexpr int kSeg = 1024;
     __shared__ float4 pair[kSeg];
     __shared__ int fb[kSeg];
-    __shared__ __attribute__((aligned(16))) uint32_t bas[RP];
     __shared__ __attribute__((aligned(16))) float cf[RP];
     __shared__ double wbest[8], wcol[8];
     __shared__ int warg[8], wnan[8];
@@ -758,14 +763,8 @@ __global__ __launch_bounds__(512, RT <= 2 ? 4 : 2) void k_mom_rows(RowArgs a)
     const double4 x0 = a.tcentre[grp.x];
     auto centre_dot = [&](const double4 &y) __attribute__((always_inline)) { return a.cscale * (x0.x * y.x + x0.y * y.y + x0.z * y.z); };
 
-    // coefficients, and the rows' power tables
-    float *tab = reinterpret_cast<float *>(ring + kTile);
-    if (tid < RP) {
-        bas[tid] = kBasis.e[a.kind][tid];
-        cf[tid] = a.coef[tid];
-    }
-    if (tid < kMomRows)
-        fill_powers<ST>(tab, tid, tid < grp.z ? a.xi[grp.y + tid] : make_float4(0.0f, 0.0f, 0.0f, 0.0f), a.d);
+    if (tid < RP) cf[tid] = a.coef[tid];
+    float4 row = 32 * w + lj < grp.z ? a.xi[grp.y + 32 * w + lj] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     // the streamed cell that counts most for this cell of rows: its size is the sums' scale, its centre their origin.  The sums of a
     // column of values have a scale of their own, that of their largest cell (col).
     double best = -INFINITY, col = -INFINITY;
@@ -830,33 +829,50 @@ __global__ __launch_bounds__(512, RT <= 2 ? 4 : 2) void k_mom_rows(RowArgs a)
         }
     };
     segment(0);
+    asm volatile("" : "+v"(row.x), "+v"(row.y), "+v"(row.z));   // (here: a wait for it further down would be one for the copies)
+    __syncthreads();
+    // (nothing below waits for memory before the first tile is needed)
+    fetch(0, 0);
+    if (a.ncell > 32) fetch(32, 1);
 
-    // the rows' monomials, eight neighbouring ones of a k-step's sixteen from either lane half
+    // The rows' monomials, eight neighbouring ones of a k-step's sixteen from either lane half, from powers in registers (out of
+    // tables in LDS, 48 reads a k-step with an address each, and with the first tiles asked for after them, 256 groups over 125 cells
+    // at RT = 7 took 21.5 us, 17.2 now).
     h8 psi[KS][2];
-    const float *q = tab + 32 * w + lj;
     const float sign = lj & 1 ? -1.0f : 1.0f;   // (see k_mom_gather: every other row sums over negated monomials)
+    float pw[3][TOP + 1];
+    {
+        const float c[3] = {row.x, row.y, row.z};
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            pw[k][0] = 1.0f;
+#pragma unroll
+            for (int e = 1; e <= TOP; ++e) pw[k][e] = k < DIM ? pw[k][e - 1] * c[k] : 1.0f;
+        }
+    }
+    constexpr int st = pow_stride(DIM);
 #pragma unroll
     for (int k = 0; k < KS; ++k) {
         float v[8];
 #pragma unroll
         for (int h = 0; h < 8; h += 4) {
-            const int al = 16 * k + 8 * lh + h;
-            const uint4 e4 = *reinterpret_cast<const uint4 *>(bas + al);
-            const float4 c4 = *reinterpret_cast<const float4 *>(cf + al);
-            const uint32_t e[4] = {e4.x, e4.y, e4.z, e4.w};
+            const float4 c4 = *reinterpret_cast<const float4 *>(cf + 16 * k + 8 * lh + h);
             const float cc[4] = {c4.x, c4.y, c4.z, c4.w};
 #pragma unroll
-            for (int z = 0; z < 4; ++z) v[h + z] = sign * cc[z] * q[(e[z] & 255) * ST] * (q[(e[z] >> 8 & 255) * ST] * q[(e[z] >> 16 & 255) * ST]);
+            for (int z = 0; z < 4; ++z) {
+                const uint32_t e0 = kBasisHost.e[KIND][16 * k + h + z], e1 = kBasisHost.e[KIND][16 * k + 8 + h + z];
+                const float x0 = pw[0][row_power(e0, 0, st)], x1 = pw[0][row_power(e1, 0, st)];
+                const float y0 = pw[1][row_power(e0, 1, st)] * pw[2][row_power(e0, 2, st)];
+                const float y1 = pw[1][row_power(e1, 1, st)] * pw[2][row_power(e1, 2, st)];
+                v[h + z] = sign * cc[z] * (lh ? x1 : x0) * (lh ? y1 : y0);
+            }
         }
         split8(v, psi[k]);
         // (sixteen at a time: the reads of all of them in flight would take the registers)
         if (k & 1) asm volatile("" : "+v"(psi[k][0]), "+v"(psi[k][1]), "+v"(psi[k - 1][0]), "+v"(psi[k - 1][1])::"memory");
     }
-    double dx[3];
-    const int st = pow_stride(a.d);
-    dx[0] = (double)q[ST] * 0.5 * a.tg.h[0];
-    dx[1] = a.d > 1 ? (double)q[(st + 1) * ST] * 0.5 * a.tg.h[1] : 0.0;
-    dx[2] = a.d > 2 ? (double)q[(2 * st + 1) * ST] * 0.5 * a.tg.h[2] : 0.0;
+    const double dx[3] = {(double)row.x * 0.5 * a.tg.h[0], DIM > 1 ? (double)row.y * 0.5 * a.tg.h[1] : 0.0,
+                          DIM > 2 ? (double)row.z * 0.5 * a.tg.h[2] : 0.0};
     const float r0 = (float)(a.cscale * dx[0]), r1 = (float)(a.cscale * dx[1]), r2 = (float)(a.cscale * dx[2]);
 
     // (8 RT units per cell: leading pieces, then trailing ones)
@@ -880,14 +896,14 @@ __global__ __launch_bounds__(512, RT <= 2 ? 4 : 2) void k_mom_rows(RowArgs a)
         sum += (double)s;
     };
     for (int s0 = 0; s0 < a.ncell; s0 += kSeg) {
+        const int n = min(kSeg, a.ncell - s0);
         if (s0) {
             __syncthreads();
             segment(s0);
+            __syncthreads();
+            fetch(0, 0);
+            if (n > 32) fetch(32, 1);
         }
-        __syncthreads();   // the segment is there (and, at first, the power tables are read: their place is the ring's)
-        const int n = min(kSeg, a.ncell - s0);
-        fetch(0, 0);
-        if (n > 32) fetch(32, 1);
         int buf = 0;
         for (int k0 = 0; k0 < n; k0 += 32, buf = buf == 2 ? 0 : buf + 1) {
             // this tile has landed (the next one may be on its way), and its predecessor's place is read
@@ -920,9 +936,9 @@ __global__ __launch_bounds__(512, RT <= 2 ? 4 : 2) void k_mom_rows(RowArgs a)
     sum += __shfl_xor(sum, 32);
     sum *= (double)sign;
     if (has_row) {
-        const double row = a.cscale * (dx[0] * yr.x + dx[1] * yr.y + dx[2] * yr.z), fl = floor(row);
+        const double shift = a.cscale * (dx[0] * yr.x + dx[1] * yr.y + dx[2] * yr.z), fl = floor(shift);
         const int64_t i = a.perm[grp.y + 32 * w + lj];
-        sum *= exp2(row - fl);
+        sum *= exp2(shift - fl);
         if (blockIdx.z)
             a.opart[i * a.p + blockIdx.z - 1] = (float)(sum * exp2(mc - m));   // (against the maximum that column 0 leaves)
         else
@@ -1306,8 +1322,6 @@ fs_status mom_pass(Ctx *c, const Prepared *P, const Side *res, const Side *str, 
         ra.perm = ts.perm;
         ra.tg = S.g[t];
         ra.cscale = ga.cscale;
-        ra.d = (int)P->d;
-        ra.kind = S.kind;
         for (int k = 0; k < kMaxTerms; ++k) ra.coef[k] = S.coef[k];
         ra.first_block = ss.first_block;
         ra.nblock = S.blocks[s];
@@ -1319,7 +1333,16 @@ fs_status mom_pass(Ctx *c, const Prepared *P, const Side *res, const Side *str, 
         ra.p = p;
         ra.groups = first_rows[x0 + cells] - first_rows[x0];
         const dim3 groups((unsigned)round_up(ra.groups, 8), 1, cols);
-        FS_MOM_DISPATCH(rt, hipLaunchKernelGGL(k_mom_rows<RT_>, groups, dim3(512), 0, c->stream, ra))
+        switch (S.kind) {
+        case 0: hipLaunchKernelGGL(k_mom_rows<0>, groups, dim3(512), 0, c->stream, ra); break;
+        case 1: hipLaunchKernelGGL(k_mom_rows<1>, groups, dim3(512), 0, c->stream, ra); break;
+        case 2: hipLaunchKernelGGL(k_mom_rows<2>, groups, dim3(512), 0, c->stream, ra); break;
+        case 3: hipLaunchKernelGGL(k_mom_rows<3>, groups, dim3(512), 0, c->stream, ra); break;
+        case 4: hipLaunchKernelGGL(k_mom_rows<4>, groups, dim3(512), 0, c->stream, ra); break;
+        case 5: hipLaunchKernelGGL(k_mom_rows<5>, groups, dim3(512), 0, c->stream, ra); break;
+        default: hipLaunchKernelGGL(k_mom_rows<6>, groups, dim3(512), 0, c->stream, ra); break;
+        }
+        static_assert(kKinds == 7, "kinds of k_mom_rows");
     }
     if (!V) prof_end(c);
     FS_HIP(c, hipGetLastError());

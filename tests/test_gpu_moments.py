@@ -87,6 +87,13 @@ def test_half_steps(ctx, oracle, n, m, d, eps, kind, pot):
     assert np.array_equal(f1, host(ctx.fs_update_f(prob, eps, dev(g))))
 
 
+# the rows' kernel is compiled per kind of expansion: the one between the least and the largest in two dimensions, and full, ragged and
+# single groups of rows for it
+@pytest.mark.parametrize("n,m,eps", [(600, 500, 0.01), (3000, 2500, 0.006), (3000, 2500, 0.01), (2561, 2049, 0.008)])
+def test_middle_expansion_in_two_dimensions(ctx, oracle, n, m, eps):
+    test_half_steps(ctx, oracle, n, m, 2, eps, "cube", "smooth")
+
+
 def test_runs_through_moments_and_falls_back(oracle):
     """Forced and left out the results differ (they are other sums); where the cells would be too many both run over the pairs."""
     rng = np.random.default_rng(3)
