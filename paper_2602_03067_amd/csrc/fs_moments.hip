@@ -43,10 +43,11 @@
 // 8 us without its loops (as the rows did, 4 less now).
 // What helps both is that the two waves of a SIMD (w and w + 4) do not do the same at a time, so that one's products run beside the
 // other's vector instructions, and that reads from LDS are on their way before they are waited for, where the compiler would place each
-// at its use.  At n = m = 262144: gather of 763 blocks for 384 cells at RT = 7 350 -> 310 us, rows of 568 groups over 1331 cells 336 -> 272
+// at its use; loads of a workgroup's constants go out with those of its points.  At n = m = 262144: gather of 763 blocks for 384 cells at
+// RT = 7 350 -> 304 us, rows of 568 groups over 1331 cells 336 -> 272
 // (259 since their monomials are formed in registers).
-// Tried: the exponents as fp32 products on the matrix cores, 295 us for the 310 above, but 30 for 28.6 where a wave has every other
-// k-step, and other roundings; four tiles of monomials at a time and two workgroups per CU, weights formed twice: 302, 31.8.
+// Tried: the exponents as fp32 products on the matrix cores, 295 us for 310, but 30 for 28.6 where a wave has every other
+// k-step, and other roundings; powers of 512 points at a time, or monomials over four workgroups: no change; four tiles of monomials at a time and two workgroups per CU, weights formed twice: 302, 31.8.
 // Tried, as the whole call of four stages of one iteration at n = m = 262144 (48 ms over the pairs, 4.8 here): fp32 matrix
 // instructions 9.4 ms; three bf16 pieces and six products 6.7 with every wave forming the monomials for itself (their LDS reads
 // bound it), 6.9 with shared ones and moments as floats split by the rows' kernel.
@@ -426,6 +427,28 @@ __global__ __launch_bounds__(512, 2) void k_mom_gather(GatherArgs a)
         } else if (col)
             vb[z] = 0.0f;
     }
+    const int xt = a.halves ? (int)blockIdx.y * 4 + (w & 3) : (int)blockIdx.y * 8 + w;
+    const int cell = xt * 32 + lj;
+    const bool busy = xt * 32 < a.ncells;
+    const int ks0 = a.halves ? w >> 2 : 0, ks1 = !busy ? ks0 : a.halves ? ks0 + 1 : 2;
+    const bool late = w >= 4;   // (the other wave of this SIMD is not)
+    const double4 c0 = a.centre[min(cell, a.ncells - 1)];
+    const float tilt[3] = {sign * (float)(a.cscale * c0.x * 0.5 * a.sg.h[0]), a.d > 1 ? (float)(a.cscale * c0.y * 0.5 * a.sg.h[1]) : 0.0f,
+                           a.d > 2 ? (float)(a.cscale * c0.z * 0.5 * a.sg.h[2]) : 0.0f};
+    const int st = pow_stride(a.d);
+    const int p1 = (a.d > 1 ? st + 1 : kOne) * ST, p2 = (a.d > 2 ? 2 * st + 1 : kOne) * ST;
+    // this thread's units of a stage: (k-step, tile, lane) = eight points of one monomial
+    constexpr int NU = (2 * TW * 64 + 511) / 512;
+    int uo[NU][3];
+#pragma unroll
+    for (int i = 0; i < NU; ++i) {
+        const int u = tid + 512 * i, ul = u & 63, ut = (u >> 6) % TW, uk = (u >> 6) / TW;
+        const uint32_t e = kBasis.e[a.kind][min(32 * (t0 + ut) + (ul & 31), kMaxTerms - 1)];
+        const int pt = 16 * uk + 8 * (ul >> 5);
+        uo[i][0] = (e & 255) * ST + pt;
+        uo[i][1] = (e >> 8 & 255) * ST + pt;
+        uo[i][2] = (e >> 16 & 255) * ST + pt;
+    }
     // Values are of any size and weights close to the end of the fp16 range: a power of two that takes the block's largest value
     // below 1 comes out of them (vexp).
     double top = fmax(ub[0], ub[1]);
@@ -451,28 +474,6 @@ __global__ __launch_bounds__(512, 2) void k_mom_gather(GatherArgs a)
 #pragma unroll
     for (int z = 0; z < 2; ++z) vb[z] = ldexpf(vb[z], -vexp);
 
-    const int xt = a.halves ? (int)blockIdx.y * 4 + (w & 3) : (int)blockIdx.y * 8 + w;
-    const int cell = xt * 32 + lj;
-    const bool busy = xt * 32 < a.ncells;
-    const int ks0 = a.halves ? w >> 2 : 0, ks1 = !busy ? ks0 : a.halves ? ks0 + 1 : 2;
-    const bool late = w >= 4;   // (the other wave of this SIMD is not)
-    const double4 c0 = a.centre[min(cell, a.ncells - 1)];
-    const float tilt[3] = {sign * (float)(a.cscale * c0.x * 0.5 * a.sg.h[0]), a.d > 1 ? (float)(a.cscale * c0.y * 0.5 * a.sg.h[1]) : 0.0f,
-                           a.d > 2 ? (float)(a.cscale * c0.z * 0.5 * a.sg.h[2]) : 0.0f};
-    const int st = pow_stride(a.d);
-    const int p1 = (a.d > 1 ? st + 1 : kOne) * ST, p2 = (a.d > 2 ? 2 * st + 1 : kOne) * ST;
-    // this thread's units of a stage: (k-step, tile, lane) = eight points of one monomial
-    constexpr int NU = (2 * TW * 64 + 511) / 512;
-    int uo[NU][3];
-#pragma unroll
-    for (int i = 0; i < NU; ++i) {
-        const int u = tid + 512 * i, ul = u & 63, ut = (u >> 6) % TW, uk = (u >> 6) / TW;
-        const uint32_t e = kBasis.e[a.kind][min(32 * (t0 + ut) + (ul & 31), kMaxTerms - 1)];
-        const int pt = 16 * uk + 8 * (ul >> 5);
-        uo[i][0] = (e & 255) * ST + pt;
-        uo[i][1] = (e >> 8 & 255) * ST + pt;
-        uo[i][2] = (e >> 16 & 255) * ST + pt;
-    }
     auto eight = [&](const float *p, float (&o)[8]) __attribute__((always_inline)) {
         const float4 x = *reinterpret_cast<const float4 *>(p), y = *reinterpret_cast<const float4 *>(p + 4);
         o[0] = x.x, o[1] = x.y, o[2] = x.z, o[3] = x.w, o[4] = y.x, o[5] = y.y, o[6] = y.z, o[7] = y.w;
