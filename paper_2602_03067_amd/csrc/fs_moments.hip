@@ -42,13 +42,13 @@
 // alone would take a third of its time), products of k_mom_rows (three quarters of its loop); at small ones latency, the gather takes
 // 8 us without its loops (as the rows did, 4 less now).
 // What helps both is that the two waves of a SIMD (w and w + 4) do not do the same at a time, so that one's products run beside the
-// other's vector instructions, and that reads from LDS are on their way before they are waited for, where the compiler would place each
-// at its use; loads of a workgroup's constants go out with those of its points.  At n = m = 262144: gather of 763 blocks for 384 cells at
-// RT = 7 350 -> 304 us, rows of 568 groups over 1331 cells 336 -> 272
-// (259 since their monomials are formed in registers).
-// Tried: the exponents as fp32 products on the matrix cores, 295 us for 310, but 30 for 28.6 where a wave has every other
-// k-step, and other roundings; powers of 512 points at a time, or monomials over four workgroups: no change; four tiles of monomials at a time and two workgroups per CU, weights formed twice: 302, 31.8.
-// Tried, as the whole call of four stages of one iteration at n = m = 262144 (48 ms over the pairs, 4.8 here): fp32 matrix
+// other's vector instructions, that reads from LDS are on their way before they are waited for, where the compiler would place each
+// at its use, and that a workgroup's constants and first tiles are asked for with its points.  At n = m = 262144 and RT = 7: gather of
+// 763 blocks for 384 cells 350 -> 304 us, rows of 568 groups over 1331 cells 336 -> 259.
+// Tried since: the exponents as fp32 products on the matrix cores, 295 us for 310, but 30 for 28.6 where a wave has every other
+// k-step, and other roundings; four tiles of monomials at a time and two workgroups per CU, weights formed twice: 302, 31.8; powers
+// of 512 points at a time, or monomials over four workgroups: no change.
+// Tried, as the whole call of four stages of one iteration at n = m = 262144 (48 ms over the pairs, 4.8 here then): fp32 matrix
 // instructions 9.4 ms; three bf16 pieces and six products 6.7 with every wave forming the monomials for itself (their LDS reads
 // bound it), 6.9 with shared ones and moments as floats split by the rows' kernel.
 #include <math.h>
