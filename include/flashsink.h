@@ -168,6 +168,7 @@ fs_status fs_solve(fs_ctx *ctx, const fs_problem *prob, float eps_start, float e
  * performs no hipMalloc / hipFree and leaves the context's own workspace untouched.  Problems whose
  * workspace does not fit are refused with FS_ERR_BAD_SHAPE before anything is launched (n = m up to
  * 54272 at d = 3, 16384 at d = 16, 22528 at d = 64, 5120 at d = 1024 in bfloat16 mode).
+ * A graph that records the call (d > 16) holds no memory of the context and may be replayed after fs_destroy.
  * Every GPU holds ONE such array for the whole process: calls of this entry point that overlap in time
  * on one GPU -- from any context or stream -- race on it.  Nothing is assumed about its contents on
  * entry (it keeps what the previous call left).  Synchronises like fs_solve.

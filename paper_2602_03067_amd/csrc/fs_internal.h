@@ -412,6 +412,15 @@ inline size_t fx_seed_bytes(int64_t cnt_pad) { return (size_t(2) << 20) + (size_
 constexpr int kBoxFx = 0, kBoxLowd = 8, kBoxWords = 64;
 constexpr int kFxNoScale = 0x4000;   // instead of the exponent: the scale is not finite
 
+// whether the context's stream records a graph (or may not be asked: the default stream while another one records)
+inline bool capturing(const Ctx *c)
+{
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &s) == hipSuccess) return s != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 // the gate of a pass at `eps` (r2 sits in scalars[10])
 inline FxGate fx_gate(const Prepared *P, double eps)
 {

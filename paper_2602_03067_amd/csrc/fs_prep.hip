@@ -1158,8 +1158,12 @@ fs_status launch_prepare(Ctx *c, const fs_problem *p, Prepared *P)
             sd[k] = PrepFxSide{in[k].pts, S->cnt, S->cnt_pad, in[k].ld, S->pts_d, S->bias_d, S->norm, S->dig, S->brec};
         }
         const int64_t pad_max = P->X.cnt_pad > P->Y.cnt_pad ? P->X.cnt_pad : P->Y.cnt_pad;
+        // (A graph does not write to the box: no launch of the call is decided by what its replays would leave there, and a replay may
+        // come after fs_destroy, which frees the box, while a graph of fs_solve_noalloc holds no other memory of the context.)
+        unsigned long long *const box = capturing(c) ? nullptr : c->box;
+        if (box) P->fx_stamp = next_stamp(c);
         hipLaunchKernelGGL(k_prep_fx, dim3((unsigned)(pad_max / 32), 2), dim3(256), 0, c->stream, sd[0], sd[1], dtype, (int)p->d, P->kp,
-                           P->fx_ks, part, P->scalars + 10, c->box, c->box ? P->fx_stamp = next_stamp(c) : 0);
+                           P->fx_ks, part, P->scalars + 10, box, P->fx_stamp);
     } else if (P->path == Path::F64) {
         for (auto &s : in)
             hipLaunchKernelGGL(k_prep_f64, dim3((unsigned)ceil_div(s.S->cnt_pad, 4)), dim3(256), 0, c->stream, s.pts,

@@ -62,3 +62,45 @@ def test_noalloc_solve_refuses_what_does_not_fit():
     assert ei.value.status == 2 and "fs_solve_noalloc" in str(ei.value)
     assert float(f.abs().max()) == 0.0 and float(g.abs().max()) == 0.0     # nothing was launched
     ctx.close()
+
+
+def test_graph_of_a_noalloc_solve_outlives_its_context(oracle):
+    """A recorded fs_solve_noalloc refers to the caller's tensors and the static scratch array only, so its graph may be replayed after
+    the context is gone, on whatever the tensors hold then: every replay is the eager call bit for bit."""
+    rng = np.random.default_rng(11)
+    n, m, d = 700, 900, 40
+    eps = float(np.float32(0.3))
+    stream = torch.cuda.Stream()
+    x, y = torch.empty(n, d, device="cuda:0"), torch.empty(m, d, device="cuda:0")
+    f, g = torch.zeros(n, device="cuda:0"), torch.zeros(m, device="cuda:0")
+    prob = binding.Problem(x, y)
+    clouds = [(rng.random((n, d)).astype(np.float32), rng.random((m, d)).astype(np.float32)) for _ in range(3)]
+
+    def fill(k):
+        x.copy_(torch.from_numpy(clouds[k][0]))
+        y.copy_(torch.from_numpy(clouds[k][1]))
+        f.zero_()
+        g.zero_()
+        torch.cuda.synchronize()
+
+    say("graph of fs_solve_noalloc n=%d m=%d d=%d" % (n, m, d))
+    ctx = binding.Context(0, stream)
+    ctx.fs_debug_set("fx_any_size", 1)
+    want = []
+    for k in range(3):
+        fill(k)
+        ctx.fs_solve_noalloc(prob, eps, eps, 1, 3, f, g)
+        torch.cuda.synchronize()
+        want.append((host(f), host(g)))
+    fo, go = oracle.solve(clouds[2][0], clouds[2][1], np.full(n, 1.0 / n), np.full(m, 1.0 / m), eps, eps, 1, 3)
+    assert max_err_over_eps(want[2][0], fo, eps) <= TOL and max_err_over_eps(want[2][1], go, eps) <= TOL
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        ctx.fs_solve_noalloc(prob, eps, eps, 1, 3, f, g)
+    ctx.close()
+    for k in (0, 1, 2, 0):
+        say("  replay on clouds %d" % k)
+        fill(k)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(host(f), want[k][0]) and np.array_equal(host(g), want[k][1])
