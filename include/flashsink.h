@@ -39,8 +39,10 @@
  *    (derived copies of x and y, squared norms, bias vectors, partial
  *    reductions; the buffers of cell moments, 64 to 256 MB, tables of up to 40 MB
  *    and 22 bytes a point, where they are used, which is not where there is no
- *    memory for them); it is grown on demand and released by fs_destroy.  fs_hvp
- *    keeps 64 bytes of pinned host memory with the context.
+ *    memory for them); it is grown on demand and released by fs_destroy.  Pinned
+ *    host memory: 64 bytes that fs_hvp keeps with the context, 512 that the first
+ *    call in FS_COMPUTE_FP32 at d <= 128 does (but for fs_solve_noalloc), and 512 a
+ *    process and GPU, taken by its first fs_create there.
  */
 #ifndef FLASHSINK_H
 #define FLASHSINK_H

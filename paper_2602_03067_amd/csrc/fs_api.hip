@@ -6,6 +6,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <atomic>
 #include <new>
 
 #include "fs_internal.h"
@@ -58,6 +59,31 @@ namespace {
 constexpr size_t kStaticScratchBytes = size_t(32) << 20;
 constexpr size_t kStaticPartialBudget = size_t(8) << 20;   // of which the partial records of a pass may take
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+
+// pinned words for kernels to write to (see Ctx::box), on the current device; nullptr: there are none
+unsigned long long *new_box()
+{
+    void *p = nullptr;
+    if (hipHostMalloc(&p, kBoxWords * 8, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    memset(p, 0, kBoxWords * 8);
+    return static_cast<unsigned long long *>(p);
+}
+
+// those that go with this device's static scratch array: made with the first context and, like the array, there until the process ends
+unsigned long long *static_box_of(int device)
+{
+    static std::atomic<unsigned long long *> boxes[16];
+    if (device < 0 || device >= 16) return nullptr;
+    unsigned long long *p = boxes[device].load();
+    if (p) return p;
+    unsigned long long *q = new_box();
+    if (!q || boxes[device].compare_exchange_strong(p, q)) return q;
+    (void)hipHostFree(q);   // (another thread was first)
+    return p;
+}
 
 // Makes the context's device current for the duration of an entry call and restores the caller's.
 struct DeviceGuard {
@@ -299,6 +325,10 @@ fs_status prepare(Ctx *c, const fs_problem *p, Prepared *P, size_t extra, char *
     }
     if (st != FS_OK) return st;
     layout(c, p, P, c->ws, extra);
+    if (P->path == Path::LowD || P->fx_ks) {
+        if (!c->box && !c->ws_static && !capturing(c)) c->box = new_box();
+        P->box = c->ws_static ? c->static_box : c->box;
+    }
     P->dbg_score = c->dbg_lowd_score;
     P->dbg_precise_valu = c->dbg_lowd_precise_valu != 0;
     P->dbg_any_bias = c->dbg_lowd_any_bias != 0;
@@ -559,15 +589,9 @@ fs_status fs_create(fs_ctx **ctx, int device, void *hip_stream)
     // this device's copy of the static scratch array (the device is current here)
     void *sp = nullptr;
     const hipError_t se = hipGetSymbolAddress(&sp, HIP_SYMBOL(scratch));
-    if (hipHostMalloc((void **)&c->box, kBoxWords * 8, hipHostMallocDefault) == hipSuccess)
-        memset(c->box, 0, kBoxWords * 8);
-    else {
-        c->box = nullptr;
-        (void)hipGetLastError();
-    }
+    c->static_box = static_box_of(device);
     if (had_prev && prev != device) (void)hipSetDevice(prev);
     if (se != hipSuccess || !sp) {
-        if (c->box) (void)hipHostFree(c->box);
         delete c;
         return FS_ERR_DEVICE;
     }

@@ -634,7 +634,7 @@ fs_status f64_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, d
     if (st != FS_OK) return st;
     prof_begin(c, (double)res->cnt * (double)str->cnt, prof_kind);
     int fx_splits = 0;
-    const int which = fx_known(c, P, eps);
+    const int which = fx_known(P, eps);
     if (P->fx_ks && (st = fx_lse(c, P, res, str, eps, &fx_splits, which != 0)) != FS_OK) return st;
     const dim3 grid((unsigned)s.row_blocks, (unsigned)s.splits);
     if (P->path == Path::LowD)
@@ -663,7 +663,7 @@ fs_status f64_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, v
     const dim3 grid((unsigned)(sx.row_blocks + sy.row_blocks), (unsigned)(sx.splits > sy.splits ? sx.splits : sy.splits));
     prof_begin(c, 2.0 * (double)P->X.cnt * (double)P->Y.cnt, P->path == Path::LowD ? 1 : 0);
     int fx_x = 0, fx_y = 0;
-    const int which = fx_known(c, P, eps);
+    const int which = fx_known(P, eps);
     if (P->fx_ks && (st = fx_lse_pair(c, P, eps, partial_x, partial_y, &fx_x, &fx_y, which != 0)) != FS_OK) return st;
     if (P->path == Path::LowD)
         hipLaunchKernelGGL((k_pass_f64_pair<kLseJT, kLseNW, true>), grid, dim3(64 * kLseNW), 0, c->stream, ax, ay, sx.row_blocks,
@@ -720,7 +720,7 @@ fs_status f64_apply(Ctx *c, const Prepared *P, const Side *res, const Side *str,
     a.d = (int)P->d;
     const bool fx = P->fx_ks > 0;   // (the gate chooses between the fixed-point kernel and this file's)
     if (fx) a.gate = fx_gate(P, eps);
-    const int which = fx_known(c, P, eps);
+    const int which = fx_known(P, eps);
     for (int p0 = 0; p0 < p;) {
         a.p0 = p0;
         // more than 64 columns left: a wide pass (128 columns) -- every pass repeats the score contraction

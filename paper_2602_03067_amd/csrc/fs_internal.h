@@ -209,9 +209,11 @@ struct Ctx {
     double *pin = nullptr;
     hipEvent_t pin_ready = nullptr;
     // Scalars that decide what the host launches next, written there by the kernels that have them (pinned; every word carries the
-    // stamp of its call in the upper half, so no order of the writes is asked for; nullptr: copies instead)
+    // stamp of its call in the upper half, so no order of the writes is asked for; nullptr: copies instead).  Made by the first call
+    // that uses it (in fs_create it took 10 to 35 us of every context, and as much of its fs_destroy, also where only bf16 problems
+    // follow); calls in the static scratch array, which may not allocate, have this device's one that lives as long as that array.
     unsigned long long *box = nullptr;
-    uint32_t box_stamp = 0;
+    unsigned long long *static_box = nullptr;
     std::string err;
     // Derived copies kept across entry calls (fs_points_keep): what identifies the clouds the caller has declared
     // unchanged, whether the workspace currently holds their derived copies, and the host-side value that belongs
@@ -376,6 +378,7 @@ struct Prepared {
     mutable MomState mom;            // LowD, d <= 3
     int kp = 0;   // F64 / BF16: padded contraction length
     int fx_ks = 0;   // F64: k-steps of the digit images, 0: none
+    unsigned long long *box = nullptr;   // where kernels of this call write for the host (Ctx::box or Ctx::static_box), or nullptr
     uint32_t fx_stamp = 0;           // the stamp under which r2 comes to the host (see fx_known), 0: it does not
     // fixed-point passes: what the last pass over the rows of X [0] and Y [1] left about them (FxSeed), two buffers a side in turn
     struct Seeds {
@@ -408,7 +411,7 @@ struct FxSeed {
 // bytes of one buffer of a side: 64 splits of a small side, or what fills the chip four times
 inline size_t fx_seed_bytes(int64_t cnt_pad) { return (size_t(2) << 20) + (size_t)cnt_pad * 2 * sizeof(FxSeed); }
 
-// Ctx::box: one word for the exponent of r2, two for each scalar of the low-d prologue (see launch_bias_from_user)
+// Prepared::box: one word for the exponent of r2, two for each scalar of the low-d prologue (see launch_bias_from_user)
 constexpr int kBoxFx = 0, kBoxLowd = 8, kBoxWords = 64;
 constexpr int kFxNoScale = 0x4000;   // instead of the exponent: the scale is not finite
 
@@ -432,10 +435,10 @@ inline FxGate fx_gate(const Prepared *P, double eps)
 
 // Which of the two kernels of a pass runs, as far as the host knows: 1 the fixed-point one, 0 the other, -1 not known yet, launch both.
 // The scale arrives while the first passes of a call run; nothing waits for it.
-inline int fx_known(const Ctx *c, const Prepared *P, double eps)
+inline int fx_known(const Prepared *P, double eps)
 {
-    if (!c->box || !P->fx_ks || !P->fx_stamp) return -1;
-    const unsigned long long w = __atomic_load_n(c->box + kBoxFx, __ATOMIC_RELAXED);
+    if (!P->box || !P->fx_ks || !P->fx_stamp) return -1;
+    const unsigned long long w = __atomic_load_n(P->box + kBoxFx, __ATOMIC_RELAXED);
     if ((uint32_t)(w >> 32) != P->fx_stamp) return -1;
     const int ex = (int)(int16_t)(w & 0xffff);
     if (ex == kFxNoScale) return 0;

@@ -4,6 +4,7 @@
 // the new shifted potential.
 #include <string.h>
 
+#include <atomic>
 #include <chrono>
 
 #include "fs_finalize.h"
@@ -501,7 +502,7 @@ struct PrepFxSide {
     unsigned char *dig;
     int *brec;
 };
-// box, stamp: where the host learns r2 (see Ctx::box)
+// box, stamp: where the host learns r2 (see Prepared::box)
 __global__ __launch_bounds__(256) void k_prep_fx(PrepFxSide s0, PrepFxSide s1, int dtype, int d, int kp, int ks, const uint2 *part,
                                                  double *r2_out, unsigned long long *box, uint32_t stamp)
 {
@@ -1102,10 +1103,13 @@ fs_status launch_row_norms(Ctx *c, const void *pts, int dtype, int64_t rows, int
     return FS_OK;
 }
 
-static uint32_t next_stamp(Ctx *c)
+// (of the whole process: contexts share the box of the static scratch array)
+static uint32_t next_stamp()
 {
-    if (++c->box_stamp == 0) c->box_stamp = 1;
-    return c->box_stamp;
+    static std::atomic<uint32_t> last{0};
+    uint32_t s = ++last;
+    if (s == 0) s = ++last;
+    return s;
 }
 
 fs_status launch_prepare(Ctx *c, const fs_problem *p, Prepared *P)
@@ -1160,8 +1164,8 @@ fs_status launch_prepare(Ctx *c, const fs_problem *p, Prepared *P)
         const int64_t pad_max = P->X.cnt_pad > P->Y.cnt_pad ? P->X.cnt_pad : P->Y.cnt_pad;
         // (A graph does not write to the box: no launch of the call is decided by what its replays would leave there, and a replay may
         // come after fs_destroy, which frees the box, while a graph of fs_solve_noalloc holds no other memory of the context.)
-        unsigned long long *const box = capturing(c) ? nullptr : c->box;
-        if (box) P->fx_stamp = next_stamp(c);
+        unsigned long long *const box = capturing(c) ? nullptr : P->box;
+        if (box) P->fx_stamp = next_stamp();
         hipLaunchKernelGGL(k_prep_fx, dim3((unsigned)(pad_max / 32), 2), dim3(256), 0, c->stream, sd[0], sd[1], dtype, (int)p->d, P->kp,
                            P->fx_ks, part, P->scalars + 10, box, P->fx_stamp);
     } else if (P->path == Path::F64) {
@@ -1190,21 +1194,21 @@ __global__ __launch_bounds__(64) void k_publish(const double *src, int cnt, unsi
 // launch arrives; with a copy to host memory and a wait for the stream, two half-step calls at n = 1000, m = 777, d = 3 took 82 us,
 // with a kernel that writes to pinned memory and a host that looks there 59 (kernels 44).  Where the stream has long work
 // ahead of it, the host stops looking after a fifth of a millisecond and waits for the stream.
-static fs_status read_scalars(Ctx *c, const double *src, int cnt, double *dst)
+static fs_status read_scalars(Ctx *c, unsigned long long *box, const double *src, int cnt, double *dst)
 {
     static_assert(kBoxLowd + 2 * (kScalarBounds - 5 + 12) <= kBoxWords, "scalars fit the box");
-    if (!c->box) {
+    if (!box) {
         FS_HIP(c, hipMemcpyAsync(dst, src, cnt * sizeof(double), hipMemcpyDeviceToHost, c->stream));
         FS_HIP(c, hipStreamSynchronize(c->stream));
         return FS_OK;
     }
-    const uint32_t stamp = next_stamp(c);
-    hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, c->stream, src, cnt, c->box + kBoxLowd, stamp);
+    const uint32_t stamp = next_stamp();
+    hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, c->stream, src, cnt, box + kBoxLowd, stamp);
     FS_HIP(c, hipGetLastError());
     const auto t0 = std::chrono::steady_clock::now();
     bool waited = false;
     for (int k = 0; k < 2 * cnt;) {
-        const unsigned long long w = __atomic_load_n(c->box + kBoxLowd + k, __ATOMIC_RELAXED);
+        const unsigned long long w = __atomic_load_n(box + kBoxLowd + k, __ATOMIC_RELAXED);
         if ((uint32_t)(w >> 32) == stamp) {
             uint32_t half = (uint32_t)w;
             memcpy(reinterpret_cast<char *>(dst) + 4 * k, &half, 4);
@@ -1238,7 +1242,7 @@ fs_status launch_bias_from_user(Ctx *c, Prepared *P, Side *side, const float *po
     FS_HIP(c, hipGetLastError());
     if (absmax && last) {
         double h[kScalarBounds - 5 + 12] = {};   // |log w| part, potential part, rho_max; at the end bounds of the clouds, see k_mean_final
-        const fs_status st = read_scalars(c, P->scalars + 5, P->mom.base ? (int)(sizeof h / sizeof *h) : 3, h);
+        const fs_status st = read_scalars(c, P->box, P->scalars + 5, P->mom.base ? (int)(sizeof h / sizeof *h) : 3, h);
         if (st != FS_OK) return st;
         if (h[0] > P->logw_mag) P->logw_mag = h[0];
         if (h[1] * eps > P->pot_mag_eps) P->pot_mag_eps = h[1] * eps;

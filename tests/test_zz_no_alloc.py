@@ -104,3 +104,45 @@ def test_graph_of_a_noalloc_solve_outlives_its_context(oracle):
         graph.replay()
         torch.cuda.synchronize()
         assert np.array_equal(host(f), want[k][0]) and np.array_equal(host(g), want[k][1])
+
+
+def test_contexts_share_the_words_of_the_static_scratch():
+    """The scalars that come to the host in fs_solve_noalloc pass through one pinned box a GPU: calls of two contexts in turn, with
+    ordinary calls (whose box is the context's own) between them, give what they give alone."""
+    rng = np.random.default_rng(12)
+    ctxs = [binding.Context(0) for _ in range(2)]
+    cases = []
+    for n, m, d in ((300, 200, 3), (250, 310, 40)):
+        x, y = (torch.from_numpy(rng.random((k, d)).astype(np.float32)).to("cuda:0") for k in (n, m))
+        cases.append(binding.Problem(x, y))
+    for c in ctxs:
+        c.fs_debug_set("fx_any_size", 1)
+
+    def solve(c, prob, name):
+        f, g = torch.zeros(prob.n, device="cuda:0"), torch.zeros(prob.m, device="cuda:0")
+        getattr(c, name)(prob, 0.3, 0.3, 1, 3, f, g)
+        return host(f), host(g)
+
+    say("shared pinned box")
+    want = [solve(ctxs[0], p, "fs_solve_noalloc") for p in cases]
+    for k in range(12):
+        p = (k + k // 4) % 2
+        got = solve(ctxs[k % 2], cases[p], ("fs_solve", "fs_solve_noalloc", "fs_solve_noalloc")[k % 3])
+        assert max(np.abs(u - v).max() for u, v in zip(got, want[p])) <= (0.0 if k % 3 else 1e-5)
+    for c in ctxs:
+        c.close()
+
+
+def test_a_context_costs_next_to_nothing():
+    """fs_create and fs_destroy take no memory of the GPU's or pinned: 1.3 us together, 20 with a pinned page."""
+    import time
+    lib, stream = binding.load_library(), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    took = []
+    say("contexts made and destroyed")
+    for _ in range(300):
+        h = ctypes.c_void_p()
+        t0 = time.perf_counter()
+        assert lib.fs_create(ctypes.byref(h), 0, stream) == 0 and lib.fs_destroy(h) == 0
+        took.append(time.perf_counter() - t0)
+    say("  %.2f us" % (np.median(took) * 1e6))
+    assert np.median(took) <= 8e-6
