@@ -282,19 +282,24 @@ size_t layout(const Ctx *c, const fs_problem *p, Prepared *P, char *base, size_t
     return layout_with(c, p, P, base, extra, ks, true);
 }
 
-fs_status ensure_ws(Ctx *c, size_t need)
+// optional: what is there stays where there is no memory for more
+fs_status ensure_ws(Ctx *c, size_t need, bool optional = false)
 {
     if (need <= c->ws_bytes) return FS_OK;
     if (c->ws_static) return fail(c, FS_ERR_BAD_SHAPE, "the problem needs %zu bytes of workspace, the static scratch holds %zu", need, c->ws_bytes);
     FS_HIP(c, hipStreamSynchronize(c->stream));
-    c->kept_valid = false;   // (a new allocation may have the address of the old one)
-    if (c->ws) {
-        FS_HIP(c, hipFree(c->ws));
-        c->ws = nullptr;
-        c->ws_bytes = 0;
-    }
     void *pnew = nullptr;
-    hipError_t e = c->dbg_ws_limit && need > c->dbg_ws_limit ? hipErrorOutOfMemory : hipMalloc(&pnew, need);
+    auto take = [&]() { return c->dbg_ws_limit && need > c->dbg_ws_limit ? hipErrorOutOfMemory : hipMalloc(&pnew, need); };
+    hipError_t e = optional ? take() : hipSuccess;
+    if (e == hipSuccess) {
+        c->kept_valid = false;   // (a new allocation may have the address of the old one)
+        if (c->ws) {
+            FS_HIP(c, hipFree(c->ws));
+            c->ws = nullptr;
+            c->ws_bytes = 0;
+        }
+        if (!optional) e = take();
+    }
     if (e != hipSuccess) {
         (void)hipGetLastError();   // (reported here, not by the check after the next launch)
         return fail(c, FS_ERR_ALLOC, "workspace of %zu bytes: %s", need, hipGetErrorString(e));
@@ -310,15 +315,28 @@ fs_status prepare(Ctx *c, const fs_problem *p, Prepared *P, size_t extra, char *
 {
     if (c->device < 0) return fail(c, FS_ERR_DEVICE, "host-only context: arguments are valid, nothing was launched");
     size_t need = layout(c, p, P, nullptr, extra);
-    fs_status st = ensure_ws(c, need);
+    fs_status st = FS_OK;
+    // Seeds are a help: a workspace that holds the call without them is not given up for them, and not grown where it cannot be
+    // (while a graph is recorded) or where there was no memory for as much before.
+    if (P->seeds.bytes[0] && need > c->ws_bytes) {
+        const size_t with_seeds = need;
+        P->want_seeds = false;
+        need = layout(c, p, P, nullptr, extra);
+        if (with_seeds < c->seeds_denied && !capturing(c)) {
+            st = ensure_ws(c, with_seeds, need <= c->ws_bytes);
+            if (st == FS_OK) {
+                P->want_seeds = true;
+                need = with_seeds;
+            } else if (st == FS_ERR_ALLOC) {
+                c->seeds_denied = with_seeds;
+                c->err.clear();
+            } else
+                return st;
+        }
+    }
+    st = ensure_ws(c, need);
     if (st == FS_ERR_ALLOC && P->mom.bytes) {   // the passes over the pairs need less (and later calls on clouds as large don't ask)
         c->mom_denied = P->mom.bytes;
-        c->err.clear();
-        need = layout(c, p, P, nullptr, extra);
-        st = ensure_ws(c, need);
-    }
-    if (st == FS_ERR_ALLOC && P->seeds.bytes[0]) {
-        P->want_seeds = false;
         c->err.clear();
         need = layout(c, p, P, nullptr, extra);
         st = ensure_ws(c, need);
@@ -1285,7 +1303,7 @@ fs_status fs_debug_set(fs_ctx *ctx, const char *key, int64_t value)
         c->kept_valid = false;   // (the layout depends on it)
     } else if (k == "ws_limit" && value >= 0) {
         c->dbg_ws_limit = (size_t)value;
-        c->mom_denied = SIZE_MAX;
+        c->mom_denied = c->seeds_denied = SIZE_MAX;
     } else if (k == "fx_any_size" && (value == 0 || value == 1)) {
         c->dbg_fx_any_size = (int)value;
         c->kept_valid = false;   // (the layout depends on it)

@@ -235,6 +235,7 @@ struct Ctx {
     bool kept_valid = false;
     bool kept_bounds = false;   // ... and whether the bounds that the cell moments need are there as well
     size_t mom_denied = SIZE_MAX;   // bytes of moment buffers that there was no memory for
+    size_t seeds_denied = SIZE_MAX; // ... of a workspace with FxSeed buffers
     PointsKey kept_key;
     double kept_rho_max = -1.0;
     uint32_t kept_fx_stamp = 0;

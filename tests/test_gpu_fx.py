@@ -505,3 +505,96 @@ def test_workspace_covers_every_pass_of_a_wide_application(ctx, n, m, d):
         assert np.abs(out[:, :3] - one).max() <= 1e-6 * np.abs(one).max()
         assert np.isfinite(out).all()
         assert np.isfinite(host(ctx.fs_apply_plan_hadamard(prob, eps, f, g, A, dev(V[:, :p].copy())))).all()
+
+
+def _long_context(stream=None):
+    """Half-steps of 24 tiles and more a workgroup at small sizes."""
+    c = binding.Context(0, stream)
+    c.fs_debug_set("fx_any_size", 1)
+    c.fs_debug_set("fx_splits", 1)
+    return c
+
+
+def _check_solve(got, want, eps, iters):
+    """Each half-step adds at most 1e-6 of its eps and passes on no more than it gets."""
+    for u, v in zip(got, want):
+        assert np.all(np.abs(host(u) - v) <= 2e-6 * iters * eps + 2.0 ** -24 * np.abs(v) * 1.01)
+
+
+def test_recorded_solve_after_other_calls(oracle):
+    """A solve that is recorded into a graph runs in the workspace that other calls on the problem have left: what it would hold beside
+    (starts of the running max) is not worth an allocation that cannot be made then."""
+    n, m, d, eps, iters = 900, 35 * 32 + 5, 40, float(np.float32(0.1)), 3
+    rng, x, y, a, b = _problem(3, n, m, d)
+    stream = torch.cuda.Stream()
+    c = _long_context(stream)
+    prob = make_problem(x, y, a, b)
+    f, g = torch.zeros(n, device="cuda:0"), torch.zeros(m, device="cuda:0")
+    torch.cuda.synchronize()
+    say("fx recorded solve")
+    c.fs_update_f(prob, eps, g)
+    c.fs_update_g(prob, eps, f)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        c.fs_solve(prob, eps, eps, 1, iters, f, g)
+    want = oracle.solve(x, y, a, b, eps, eps, 1, iters)
+    first = None
+    for k in range(4):
+        say("  replay %d" % k)
+        f.fill_(float(k))
+        g.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        _check_solve((f, g), want, eps, iters)
+        first = (host(f), host(g)) if first is None else first
+        assert np.array_equal(host(f), first[0]) and np.array_equal(host(g), first[1])
+    del graph
+    c.close()
+
+
+def test_solves_where_there_is_no_memory_for_starts(oracle):
+    """Without memory for the starts of the running max a solve takes as much workspace as a half-step and leaves what there is alone:
+    the kept copies of the clouds survive it, the first time and afterwards."""
+    n, m, d, eps, iters = 900, 35 * 32 + 5, 40, float(np.float32(0.1)), 3
+    rng, x, y, a, b = _problem(4, n, m, d)
+    xd, yd = dev(x), dev(y)
+    prob = binding.Problem(xd, yd, dev(a), dev(b))
+    g0 = torch.zeros(m, device="cuda:0")
+
+    def fits(limit):
+        c = _long_context()
+        c.fs_debug_set("ws_limit", limit)
+        try:
+            c.fs_update_f(prob, eps, g0)
+            return True
+        except binding.FlashSinkError as e:
+            assert e.status == 6
+            return False
+        finally:
+            c.close()
+
+    lo, hi = 0, 1 << 28
+    while hi - lo > 256:
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if fits(mid) else (mid, hi)
+    say("fx solves in %d bytes" % hi)
+    c = _long_context()
+    c.fs_debug_set("ws_limit", hi)
+    c.fs_points_keep(prob)
+    old = host(c.fs_update_f(prob, eps, g0))
+    want = oracle.solve(x, y, a, b, eps, eps, 1, iters)
+    xd.mul_(2.0)
+    for k in range(2):   # (from the copies of the old coordinates)
+        f, g = torch.zeros(n, device="cuda:0"), torch.zeros(m, device="cuda:0")
+        c.fs_solve(prob, eps, eps, 1, iters, f, g)
+        _check_solve((f, g), want, eps, iters)
+    assert np.array_equal(host(c.fs_update_f(prob, eps, g0)), old)
+    xd.mul_(0.5)
+    c.fs_points_release()
+    c.fs_debug_set("ws_limit", 0)
+    f, g = torch.zeros(n, device="cuda:0"), torch.zeros(m, device="cuda:0")
+    c.fs_solve(prob, eps, eps, 1, iters, f, g)
+    _check_solve((f, g), want, eps, iters)
+    c.close()
