@@ -215,3 +215,42 @@ def test_kept_derived_copies_change_nothing(oracle, d, compute):
     want = oracle.update_f(host(xd), y, b, eps, kept[1])
     assert max_err_over_eps(fresh, want, eps) <= (2e-2 if compute == "bf16" else 1e-4)
     assert not np.array_equal(fresh, stale)
+
+
+@pytest.mark.parametrize("d,compute", [(40, "fp32"), (150, "fp32"), (48, "bf16")])
+def test_copies_that_are_only_recorded_are_not_kept(d, compute):
+    """fs_points_keep before the first call on the clouds is recorded into a graph: its copies are not there yet, so the next call makes
+    them."""
+    rng = np.random.default_rng(700 + d)
+    n, m = 700, 900
+    cm = BF if compute == "bf16" else binding.FS_COMPUTE_FP32
+    probs = []
+    for k in range(2):
+        x, y, a, b = _cloud(rng, n, m, d, 0.4)
+        probs.append(binding.Problem(dev(x), dev(y), dev(a), dev(b), cm))
+    g = dev((0.1 * rng.standard_normal(m)).astype(np.float32))
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    say("recorded copies d=%d %s" % (d, compute))
+    ctx = binding.Context(0, stream)
+
+    def now():
+        out = ctx.fs_update_f(probs[0], 0.25, g)
+        torch.cuda.synchronize()
+        return host(out)
+
+    want = now()
+    ctx.fs_update_f(probs[1], 0.25, g)   # (other copies at the same place)
+    torch.cuda.synchronize()
+    ctx.fs_points_keep(probs[0])
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        recorded = ctx.fs_update_f(probs[0], 0.25, g)
+    assert np.array_equal(now(), want)
+    for _ in range(3):
+        recorded.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(host(recorded), want) and np.array_equal(now(), want)
+    ctx.close()
