@@ -387,12 +387,26 @@ fs_status fs_points_release(fs_ctx *ctx);
  *   "lowd_precise_any_bias"  1: those matrix-core records also for biases beyond their digit range
  *   "lowd_moments"       d <= 3: 1: half-steps and gradients through cell moments wherever the clouds allow it (also where
  *                        float64-grade scores would be taken, but for the two measurements above), 2: never
+ *   "moment_kind"        expansion of those passes by rising degree: 1, 2, 3 at d = 3, 4, 5, 6 at d = 2, 7 at d = 1 (with "lowd_moments" 1)
  *   "fx_any_size"        1: fixed-point scores (16 < d <= 128, FS_COMPUTE_FP32) for problems of any size
  *   "ws_limit"           the workspace gets at most this many bytes (0: what the device has), as if there were no more
  *   "fx_splits"          number of splits of the streamed side of a fixed-point pass, 0..1024
+ *   "fx_long"            1: fixed-point half-steps of any length as long ones, which leave tiles that cannot count early, 2: none
+ *   "fx_count"           1: count the tiles of long fixed-point half-steps from zero (16 bytes of device memory; kernels of their
+ *                        own, slower ones), 0: don't.  Synchronises the stream.
  * Unknown keys and values out of range: FS_ERR_INVALID_ARG.  key: HOST string.
  */
 fs_status fs_debug_set(fs_ctx *ctx, const char *key /* host */, int64_t value);
+
+/*
+ * What tests and benchmarks look at of ONE context.
+ *   "fx_tiles", "fx_tiles_left"  since "fx_count" was set: tiles (32 rows x 32 points) of long fixed-point half-steps of the
+ *                        alternating schedules, and those of them that were left at their leading products; 0 without that
+ *                        switch.  Synchronise the stream.
+ *   "moment_kind"        which expansion the last pass through cell moments took, numbered as in the switch; 0: none has run
+ * Unknown keys: FS_ERR_INVALID_ARG.  key, value: HOST.
+ */
+fs_status fs_debug_get(fs_ctx *ctx, const char *key /* host */, int64_t *value /* host */);
 
 /*
  * Timing hook for benchmarks: average duration in milliseconds of the streaming

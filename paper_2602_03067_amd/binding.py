@@ -22,7 +22,7 @@ FS_COMPUTE_FP32, FS_COMPUTE_BF16_MFMA = 0, 1
 EXPORTS = (
     "fs_create", "fs_destroy", "fs_status_str", "fs_last_error", "fs_version", "fs_row_norms",
     "fs_update_f", "fs_update_g", "fs_solve", "fs_solve_noalloc", "fs_solve_labeled", "fs_solve_symmetric", "fs_solve_tol", "fs_marginal_err", "fs_ot_value", "fs_check_weights", "fs_check_finite", "fs_divergence", "fs_apply_plan",
-    "fs_apply_plan_T", "fs_apply_plan_hadamard", "fs_grad_x", "fs_grad_y", "fs_hvp", "fs_points_keep", "fs_points_release", "fs_debug_set", "fs_profile_enable", "fs_profile_read",
+    "fs_apply_plan_T", "fs_apply_plan_hadamard", "fs_grad_x", "fs_grad_y", "fs_hvp", "fs_points_keep", "fs_points_release", "fs_debug_set", "fs_debug_get", "fs_profile_enable", "fs_profile_read",
 )
 
 
@@ -86,6 +86,7 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
     lib.fs_grad_y.argtypes = [vp, PP, f32, vp, vp, i32, vp, i64]
     lib.fs_hvp.argtypes = [vp, PP, f32, vp, vp, vp, i64, f32, f32, i32, vp, i64, ctypes.POINTER(i32)]
     lib.fs_debug_set.argtypes = [vp, ctypes.c_char_p, i64]
+    lib.fs_debug_get.argtypes = [vp, ctypes.c_char_p, ctypes.POINTER(i64)]
     lib.fs_points_keep.argtypes = [vp, PP]
     lib.fs_points_release.argtypes = [vp]
     lib.fs_profile_enable.argtypes = [vp, i32]
@@ -354,6 +355,11 @@ class Context:
     def fs_debug_set(self, key: str, value: int) -> None:
         """Test and experiment switches of this context (0 = the library decides)."""
         self._check(self.lib.fs_debug_set(self.h, key.encode(), int(value)), "fs_debug_set")
+
+    def fs_debug_get(self, key: str) -> int:
+        v = ctypes.c_int64()
+        self._check(self.lib.fs_debug_get(self.h, key.encode(), ctypes.byref(v)), "fs_debug_get")
+        return v.value
 
     def fs_profile_enable(self, on: bool) -> None:
         self._check(self.lib.fs_profile_enable(self.h, 1 if on else 0), "fs_profile_enable")

@@ -630,6 +630,7 @@ fs_status fs_destroy(fs_ctx *ctx)
         for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
         if (c->ws) (void)hipFree(c->ws);
         if (c->aux) (void)hipFree(c->aux);
+        if (c->fx_count) (void)hipFree(c->fx_count);
         if (c->pin) (void)hipHostFree(c->pin);
         if (c->box) (void)hipHostFree(c->box);
         if (c->pin_ready) (void)hipEventDestroy(c->pin_ready);
@@ -1310,8 +1311,49 @@ fs_status fs_debug_set(fs_ctx *ctx, const char *key, int64_t value)
         c->kept_valid = false;   // (the layout depends on it)
     } else if (k == "fx_splits" && value >= 0 && value <= 1024)
         c->dbg_fx_splits = (int)value;
+    else if (k == "moment_kind" && value >= 0 && value <= 7)
+        c->dbg_moment_kind = (int)value;
+    else if (k == "fx_long" && value >= 0 && value <= 2)
+        c->dbg_fx_long = (int)value;
+    else if (k == "fx_count" && (value == 0 || value == 1)) {
+        if (c->device < 0) return FS_OK;
+        FS_HIP(c, hipStreamSynchronize(c->stream));   // (kernels in flight may be counting)
+        if (c->fx_count) (void)hipFree(c->fx_count);
+        c->fx_count = nullptr;
+        if (value) {
+            void *p = nullptr;
+            if (hipMalloc(&p, 2 * sizeof(unsigned long long)) != hipSuccess) {
+                (void)hipGetLastError();
+                return fail(c, FS_ERR_ALLOC, "no memory for the counters");
+            }
+            c->fx_count = static_cast<unsigned long long *>(p);
+            return launch_fill_f64(c, reinterpret_cast<double *>(p), 0.0, 2);
+        }
+    }
     else
         return fail(c, FS_ERR_INVALID_ARG, "unknown switch or value out of range: %s = %lld", key, (long long)value);
+    return FS_OK;
+}
+
+fs_status fs_debug_get(fs_ctx *ctx, const char *key, int64_t *value)
+{
+    Ctx *c = reinterpret_cast<Ctx *>(ctx);
+    DeviceGuard device_guard(c);
+    if (!c) return FS_ERR_INVALID_ARG;
+    c->err.clear();
+    if (!key || !value) return fail(c, FS_ERR_INVALID_ARG, "key or value is NULL");
+    const std::string k(key);
+    if (k == "fx_tiles" || k == "fx_tiles_left") {
+        unsigned long long h[2] = {0, 0};
+        if (c->fx_count) {
+            FS_HIP(c, hipMemcpyAsync(h, c->fx_count, sizeof h, hipMemcpyDeviceToHost, c->stream));
+            FS_HIP(c, hipStreamSynchronize(c->stream));
+        }
+        *value = (int64_t)h[k == "fx_tiles"];
+    } else if (k == "moment_kind")
+        *value = c->moment_kind;
+    else
+        return fail(c, FS_ERR_INVALID_ARG, "unknown value: %s", key);
     return FS_OK;
 }
 

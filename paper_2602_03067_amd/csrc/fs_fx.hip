@@ -98,6 +98,7 @@ struct FxArgs {
     const FxSeed *seed_in;            // [seed_splits][partial_stride] of the last pass over these rows, or nullptr
     FxSeed *seed_out;                 // [splits][partial_stride], or nullptr
     int seed_splits;
+    unsigned long long *count;        // COUNT: [0] tiles left at their leading products, [1] all tiles (of a wave each)
     // application
     const float *V;                   // MODE 1: [n_str][ldv] values, columns p0 ..
     int64_t ldv, n_str;
@@ -142,7 +143,9 @@ template <int KS, int MODE, int NC, bool HAD = false> struct FxShape {
     static constexpr int kHold(bool full) { return KS <= 2 ? 4 : full ? 0 : 2; }
 };
 
-template <int KS, int MODE, int NC, bool FULL, bool HAD = false>
+// COUNT (with MODE 3): tiles are counted, in kernels of their own: a counter across the loop takes the others up to twenty registers,
+// and where they have none left spills.
+template <int KS, int MODE, int NC, bool FULL, bool HAD = false, bool COUNT = false>
 __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, const int bx, const int by)
 {
     using S = FxShape<KS, MODE, NC, HAD>;
@@ -705,6 +708,7 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
         }
     };
 
+    [[maybe_unused]] int left = 0;   // (COUNT: tiles that were left at their leading products)
     for (; issued < NS - 1 && issued < G;) issue();
     for (int g = 0; g < G; ++g) {
         const int newer = issued - g - 1;
@@ -732,7 +736,10 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
             const bool direct = T.kind != 1 && near;
             if (direct) {
                 settle(g, T, top, T.kind == 2);
-                if (!__any(top > skip)) continue;
+                if (!__any(top > skip)) {
+                    if constexpr (COUNT) ++left;
+                    continue;
+                }
             }
             contract_low(sb, T);
             if (__builtin_expect(direct, 1)) {
@@ -771,6 +778,12 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
         const bool other = at < 0 || (at1 >= 0 && mo > mym);   // (the half that was raised higher)
         if (lh == 0) a.seed_out[rec_row] = other ? FxSeed{dot1, at1} : FxSeed{at_dot, at};
     }
+    if constexpr (COUNT) {
+        if (l == 0) {
+            atomicAdd(a.count, (unsigned long long)left);
+            atomicAdd(a.count + 1, (unsigned long long)G);
+        }
+    }
     if (lh == 0) a.partial[rec_row] = make_double2(M, s * (double)f0 + so * (double)f1);
     if constexpr (MODE == 1) {
 #pragma unroll
@@ -799,7 +812,7 @@ __device__ inline void no_seeds(const FxArgs &a, int bx, int by)
 }
 
 // (The dispatcher fills CU after CU, so the kernels are held to as many workgroups per CU as the launch shape counts on.)
-template <int KS, int MODE, int NC, bool HAD = false>
+template <int KS, int MODE, int NC, bool HAD = false, bool COUNT = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FxShape<KS, MODE, NC, HAD>::kWgPerCu, FxShape<KS, MODE, NC, HAD>::kWgPerCu)))
 void k_fx(FxArgs a)
 {
@@ -810,9 +823,9 @@ void k_fx(FxArgs a)
         return;
     }
     if (a.gate.full())
-        fx_body<KS, MODE, NC, true, HAD>(a, ring, blockIdx.x, blockIdx.y);
+        fx_body<KS, MODE, NC, true, HAD, COUNT>(a, ring, blockIdx.x, blockIdx.y);
     else
-        fx_body<KS, MODE, NC, false, HAD>(a, ring, blockIdx.x, blockIdx.y);
+        fx_body<KS, MODE, NC, false, HAD, COUNT>(a, ring, blockIdx.x, blockIdx.y);
 }
 
 // Both passes of one iteration of the averaged schedule (Eq. 4-5) in one launch: the first rb0 row blocks of the
@@ -985,6 +998,7 @@ fs_status pass_args(Ctx *c, const Prepared *P, const Side *res, const Side *str,
     a.partial = (double2 *)partial;
     a.partial_stride = res->cnt_pad;
     a.n_str = str->cnt;
+    a.count = c->fx_count;
     if ((int64_t)s.row_blocks * kRows > res->cnt_pad || (int64_t)a.n_tiles * 32 > str->cnt_pad ||
         (size_t)s.splits * res->cnt_pad * 16 > P->partial_bytes || P->fx_ks < 1 || P->fx_ks > kFxMaxKs)
         return fail(c, FS_ERR_DEVICE, "internal: fixed-point launch shape exceeds the padded buffers");
@@ -1064,13 +1078,13 @@ struct ApplyBuf {
 // Whether a half-step runs in MODE 3 (`s`: its shape there): where a workgroup has at least 24 tiles.  Half-steps in MODE 0 and 3 with seeds
 // (us; unit cube, eps = 0.1, where no tile can be left: n = m = 4000, 6000, 8192, 10000, 16384, d = 64: 22 / 25, 37 / 39, 53 / 57, 91 / 87, 198 / 188;
 // d = 128, n = m = 10000 140 / 135; shifted normal points of spread 3, n = m = 16384, d = 64, where four of five are: 216 / 118).
-static bool fx_long(const PassShape &s) { return s.cols_per_split >= 24 * 32; }
+static bool fx_long(const Ctx *c, const PassShape &s) { return c->dbg_fx_long ? c->dbg_fx_long == 1 : s.cols_per_split >= 24 * 32; }
 
 fs_status fx_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, int *splits, bool launch)
 {
     FxArgs a;
     PassShape s = fx_shape(c, res->cnt, str->cnt, fx_wg_per_cu(P->fx_ks, 3, 1, false));
-    const bool lng = fx_long(s);
+    const bool lng = fx_long(c, s);
     fs_status st = pass_args(c, P, res, str, eps, lng ? 3 : 0, 1, false, P->partial, &a, &s);
     if (st != FS_OK) return st;
     *splits = s.splits;
@@ -1080,7 +1094,9 @@ fs_status fx_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, do
     }
     const dim3 grid((unsigned)s.row_blocks, (unsigned)s.splits);
 #define FX_LSE(KS)                                                                          \
-    if (lng)                                                                                \
+    if (lng && a.count)                                                                     \
+        hipLaunchKernelGGL((k_fx<KS, 3, 1, false, true>), grid, dim3(256), 0, c->stream, a); \
+    else if (lng)                                                                           \
         hipLaunchKernelGGL((k_fx<KS, 3, 1>), grid, dim3(256), 0, c->stream, a);             \
     else                                                                                    \
         hipLaunchKernelGGL((k_fx<KS, 0, 1>), grid, dim3(256), 0, c->stream, a)
@@ -1100,7 +1116,7 @@ fs_status fx_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, vo
     FxArgs ax, ay;
     const int occ = fx_wg_per_cu(P->fx_ks, 3, 1, false);
     PassShape sx = fx_shape(c, P->X.cnt, P->Y.cnt, occ), sy = fx_shape(c, P->Y.cnt, P->X.cnt, occ);
-    const bool lng = fx_long(sx) && fx_long(sy);
+    const bool lng = fx_long(c, sx) && fx_long(c, sy);
     fs_status st;
     if ((st = pass_args(c, P, &P->X, &P->Y, eps, lng ? 3 : 0, 1, false, partial_x, &ax, &sx)) != FS_OK) return st;
     if ((st = pass_args(c, P, &P->Y, &P->X, eps, lng ? 3 : 0, 1, false, partial_y, &ay, &sy)) != FS_OK) return st;

@@ -248,6 +248,10 @@ struct Ctx {
     int dbg_fx_any_size = 0;         // 1: digit images for problems of any size
     size_t dbg_ws_limit = 0;         // the workspace does not get more bytes than this (0: no limit)
     int dbg_fx_splits = 0;           // forced split count of the streamed side of a fixed-point pass
+    int dbg_fx_long = 0;             // 1: fixed-point half-steps of any length as long ones (MODE 3), 2: none
+    unsigned long long *fx_count = nullptr;   // device: tiles that long half-steps have left at their leading products, and all of theirs
+    int dbg_moment_kind = 0;         // 1 + the expansion that passes through cell moments take
+    int moment_kind = 0;             // 1 + the one that the last such pass took
     // profiling of the streaming LSE launches
     bool prof_on = false;
     std::vector<hipEvent_t> ev_pool;   // pairs (start, stop)

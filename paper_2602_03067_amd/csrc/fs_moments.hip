@@ -1173,7 +1173,7 @@ fs_status mom_ready(Ctx *c, const Prepared *P, double eps, int t, bool *use)
     double half_cost = 0.0, all_cost = 0.0;
     MomGeom g[2];
     for (int k = 0; k < kKinds; ++k) {
-        if (kKind[k].d != d) continue;
+        if (kKind[k].d != d || (c->dbg_moment_kind && c->dbg_moment_kind != 1 + k)) continue;
         MomGeom geo[2];
         double s[3], all[2], half[2];
         if (!geometry(S, d, eps, kKind[k].tau, geo, s)) continue;
@@ -1334,6 +1334,7 @@ fs_status mom_pass(Ctx *c, const Prepared *P, const Side *res, const Side *str, 
         ra.p = p;
         ra.groups = first_rows[x0 + cells] - first_rows[x0];
         const dim3 groups((unsigned)round_up(ra.groups, 8), 1, cols);
+        c->moment_kind = 1 + S.kind;
         switch (S.kind) {
         case 0: hipLaunchKernelGGL(k_mom_rows<0>, groups, dim3(512), 0, c->stream, ra); break;
         case 1: hipLaunchKernelGGL(k_mom_rows<1>, groups, dim3(512), 0, c->stream, ra); break;

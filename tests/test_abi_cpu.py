@@ -228,6 +228,15 @@ def test_debug_switches_are_per_context(lib, hctx):
     assert lib.fs_debug_set(hctx, b"fx_any_size", 1) == 0 and lib.fs_debug_set(hctx, b"fx_any_size", 0) == 0
     assert lib.fs_debug_set(hctx, b"fx_splits", 3) == 0 and lib.fs_debug_set(hctx, b"fx_splits", 0) == 0
     assert lib.fs_debug_set(hctx, b"fx_splits", 1025) == 1
+    assert lib.fs_debug_set(hctx, b"fx_long", 2) == 0 and lib.fs_debug_set(hctx, b"fx_long", 0) == 0 and lib.fs_debug_set(hctx, b"fx_long", 3) == 1
+    assert lib.fs_debug_set(hctx, b"moment_kind", 7) == 0 and lib.fs_debug_set(hctx, b"moment_kind", 0) == 0
+    assert lib.fs_debug_set(hctx, b"moment_kind", 8) == 1
+    assert lib.fs_debug_set(hctx, b"fx_count", 1) == 0 and lib.fs_debug_set(hctx, b"fx_count", 2) == 1
+    value = ctypes.c_int64(-5)
+    for key in (b"fx_tiles", b"fx_tiles_left", b"moment_kind"):      # (nothing has run)
+        assert lib.fs_debug_get(hctx, key, ctypes.byref(value)) == 0 and value.value == 0
+    assert lib.fs_debug_get(hctx, b"no_such_value", ctypes.byref(value)) == 1 and lib.fs_debug_get(hctx, b"fx_tiles", None) == 1
+    assert lib.fs_debug_get(hctx, None, ctypes.byref(value)) == 1 and lib.fs_debug_get(None, b"fx_tiles", ctypes.byref(value)) == 1
     assert lib.fs_debug_set(hctx, b"lowd_score", 16) == 1            # value out of range
     assert lib.fs_debug_set(hctx, b"lowd_splits", -1) == 1
     assert lib.fs_debug_set(hctx, b"no_such_switch", 1) == 1 and b"no_such_switch" in lib.fs_last_error(hctx)
