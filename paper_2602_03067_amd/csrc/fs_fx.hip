@@ -31,7 +31,7 @@
 // filled by linear direct loads and read without bank conflicts.
 //
 // A workgroup is four waves = 128 resident rows (their digits stay in registers) over a run of streamed tiles that pass
-// through an LDS ring; two workgroups per CU, one where two rings do not fit, three in MODE 3 (fx_wg_per_cu).
+// through an LDS ring; two workgroups per CU, one where two rings do not fit, three in MODE 3 at d <= 96 (fx_wg_per_cu).
 //
 // Long half-steps (MODE 3).  Where the scores of a row spread over hundreds of base-2 units, few tiles hold a point that counts
 // (shifted normal points, n = m = 16384, d = 64, eps = 0.1: one tile of four holds a pair within 60 units of its row's largest).  The three
@@ -39,8 +39,8 @@
 // the conversions and the exponentials undone.  m must be near the row's largest from the first tile on for that: it starts at the
 // score, at the biases of this pass, of a point that the last pass over these rows in the same call found (FxSeed), which bounds
 // the row's sum from below whatever the potentials have become.  The leading products come first and the max between them and
-// the others, so a wave waits for its own products more often; three workgroups per CU fill those waits (168 registers: sums of one
-// weight are shifted before the next ones join them).  Half-step with its merge (us): that case 216 -> 116, the self term of a
+// the others, so a wave waits for its own products more often; three workgroups per CU fill those waits at d <= 96 (168 registers: sums
+// of one weight are shifted before the next ones join them).  Half-step with its merge (us): that case 216 -> 116, the self term of a
 // divergence at n = 10000, d = 64 78 -> 53; where nothing can be left (unit cube) n = m = 16384, d = 64 197 -> 186, n = m = 10000, d = 128
 // 139 -> 134, n = m = 8192, d = 64 53 -> 57, which is why short passes stay in MODE 0 (fx_long).
 //
@@ -126,11 +126,13 @@ constexpr int fx_stage_bytes(int ks, int mode, int nc)
 constexpr int fx_stages(int stage_bytes) { return stage_bytes <= 13 * 1024 ? 4 : 3; }
 // Workgroups per CU: two where two rings fit the 160 KB of LDS, which the widest applications do not (four column blocks
 // at any d, three at d > 64, two at d > 96).  HAD: one, the second set of resident digits takes the registers.  MODE 3: three, it
-// holds fewer accumulators at a time.
+// holds fewer accumulators at a time, but two at d > 96, where the resident digits alone take 64 registers: with three, 44 more were
+// spilled, whose reloads wait for the ring (solves in the unit cube, n = m = 10000, d = 128, us a half-step: ten products 128 -> 122,
+// thirteen 172 -> 154, and 136 and 153 in MODE 0).
 constexpr int fx_wg_per_cu(int ks, int mode, int nc, bool had)
 {
     const int stage = fx_stage_bytes(ks, mode, nc);
-    return mode == 3 ? 3 : had || 2 * fx_stages(stage) * stage > 160 * 1024 ? 1 : 2;
+    return mode == 3 ? (ks <= 3 ? 3 : 2) : had || 2 * fx_stages(stage) * stage > 160 * 1024 ? 1 : 2;
 }
 template <int KS, int MODE, int NC, bool HAD = false> struct FxShape {
     static constexpr int kStage = fx_stage_bytes(KS, MODE, NC);
