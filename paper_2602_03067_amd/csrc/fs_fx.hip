@@ -976,7 +976,7 @@ PassShape fx_shape(const Ctx *c, int64_t n_res, int64_t n_str, int occ)
         const double units = (double)(wg - rem) + (rem == 0 ? 0.0 : rem == 2 ? 2.25 : occ == 3 ? 1.75 : 2.0);
         const double cost = units * ((double)tps + startup) + 0.05 * sp;
         if (best == 0.0 || cost < best * 0.995) {
-            best = cost;
+            best = s.cost = cost;
             best_tps = tps;
         }
     }
@@ -1077,21 +1077,36 @@ struct ApplyBuf {
 
 }  // namespace
 
-// Whether a half-step runs in MODE 3 (`s`: its shape there): where a workgroup has at least 24 tiles.  Half-steps in MODE 0 and 3 with seeds
-// (us; unit cube, eps = 0.1, where no tile can be left: n = m = 4000, 6000, 8192, 10000, 16384, d = 64: 22 / 25, 37 / 39, 53 / 57, 91 / 87, 198 / 188;
-// d = 128, n = m = 10000 140 / 135; shifted normal points of spread 3, n = m = 16384, d = 64, where four of five are: 216 / 118).
-static bool fx_long(const Ctx *c, const PassShape &s) { return c->dbg_fx_long ? c->dbg_fx_long == 1 : s.cols_per_split >= 24 * 32; }
+// Whether a half-step runs in MODE 3 (`s` is its shape there, `s0` in MODE 0): where a workgroup has at least 24 tiles.  At d <= 64, where
+// its three workgroups per CU bring least, they also have to fill their places: the model of the shapes may expect no more than
+// 1.05 times the time in MODE 0, or, for `seeds`, the calls that pass over the rows several times, 1.09 (d <= 32) or 1.11: only
+// there are tiles left early, if the clouds allow it at all.  MODE 0 over MODE 3 in time, unit cube with ten products / with
+// thirteen, where no tile can be left / normal points of spread 1, a unit apart, where many are, at the model's 1.0, 1.08, 1.10 and
+// 1.125 (n = m = 14500, 12500, 9000; n = 20000, m = 3000):
+//     solves, d = 20     1.08 1.05 1.10    1.02 1.00 1.03    0.96 0.97 0.96    0.93 0.94 0.94
+//     d = 64             1.05 1.03 1.44    1.01 1.00 1.31    0.99 0.97 1.17    0.97 0.96 1.08
+//     d = 96             1.11 1.01 1.56    1.07 0.98 1.42    1.05 0.96 1.28    1.05 0.96 1.15
+//     single, d = 20     1.08 1.04 1.03    1.00 0.98 0.98    0.96 0.96 0.96    0.91 0.97 0.92
+//     d = 64             1.04 1.02 1.04    1.01 1.00 1.00    1.01 0.96 0.99    0.99 0.94 0.95
+//     d = 96             1.09 1.01 1.02    1.06 0.97 0.98    1.05 0.97 0.97    1.03 0.99 1.00
+// (d = 128, two workgroups per CU as in MODE 0: 1.04 to 1.11, 0.98 to 1.03, 1.11 to 1.52, and single 1.06 to 1.10, 0.98 to 1.02, 1.00 to 1.10.)
+static bool fx_long(const Ctx *c, const PassShape &s, const PassShape &s0, int ks, bool seeds)
+{
+    if (c->dbg_fx_long) return c->dbg_fx_long == 1;
+    return s.cols_per_split >= 24 * 32 && (ks > 2 || s.cost <= (!seeds ? 1.05 : ks == 1 ? 1.09 : 1.11) * s0.cost);
+}
 
 fs_status fx_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, int *splits, bool launch)
 {
     FxArgs a;
     PassShape s = fx_shape(c, res->cnt, str->cnt, fx_wg_per_cu(P->fx_ks, 3, 1, false));
-    const bool lng = fx_long(c, s);
+    const int t = res == &P->X ? 0 : 1;
+    const bool lng = fx_long(c, s, fx_shape(c, res->cnt, str->cnt, fx_wg_per_cu(P->fx_ks, 0, 1, false)), P->fx_ks, P->seeds.bytes[t] != 0);
     fs_status st = pass_args(c, P, res, str, eps, lng ? 3 : 0, 1, false, P->partial, &a, &s);
     if (st != FS_OK) return st;
     *splits = s.splits;
     if (!launch) {
-        P->seeds.last[res == &P->X ? 0 : 1] = -1;   // (nothing writes the seeds of this pass)
+        P->seeds.last[t] = -1;   // (nothing writes the seeds of this pass)
         return FS_OK;
     }
     const dim3 grid((unsigned)s.row_blocks, (unsigned)s.splits);
@@ -1118,7 +1133,8 @@ fs_status fx_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, vo
     FxArgs ax, ay;
     const int occ = fx_wg_per_cu(P->fx_ks, 3, 1, false);
     PassShape sx = fx_shape(c, P->X.cnt, P->Y.cnt, occ), sy = fx_shape(c, P->Y.cnt, P->X.cnt, occ);
-    const bool lng = fx_long(c, sx) && fx_long(c, sy);
+    // (two passes fill the places of one launch: n = m = 9000, d = 20 44.8 us a half-step in MODE 0 and 42.3 in MODE 3, 48.8 and 45.1)
+    const bool lng = fx_long(c, sx, sx, P->fx_ks, true) && fx_long(c, sy, sy, P->fx_ks, true);
     fs_status st;
     if ((st = pass_args(c, P, &P->X, &P->Y, eps, lng ? 3 : 0, 1, false, partial_x, &ax, &sx)) != FS_OK) return st;
     if ((st = pass_args(c, P, &P->Y, &P->X, eps, lng ? 3 : 0, 1, false, partial_y, &ay, &sy)) != FS_OK) return st;

@@ -513,6 +513,7 @@ struct PassShape {
     int row_blocks = 0;
     int splits = 1;
     int64_t cols_per_split = 0;   // multiple of the column tile
+    double cost = 0.0;            // fixed-point passes: what the model of fx_shape expects
 };
 
 // fs_prep.hip
