@@ -256,8 +256,8 @@ size_t layout_with(const Ctx *c, const fs_problem *p, Prepared *P, char *base, s
     P->mom.base = base && P->mom.bytes ? base + o : nullptr;
     P->seeds = Prepared::Seeds();
     for (int t = 0; t < 2 && P->fx_ks && seeds && P->want_seeds; ++t) {
-        P->seeds.bytes[t] = fx_seed_bytes(t == 0 ? P->X.cnt_pad : P->Y.cnt_pad);
-        for (int k = 0; k < 2; ++k) {
+        P->seeds.bytes[t] = fx_seed_bytes(c, P, t, P->pairs);
+        for (int k = 0; k < 2 && P->seeds.bytes[t]; ++k) {
             o = A.take(P->seeds.bytes[t]);
             P->seeds.buf[t][k] = base ? base + o : nullptr;
         }
@@ -318,7 +318,7 @@ fs_status prepare(Ctx *c, const fs_problem *p, Prepared *P, size_t extra, char *
     fs_status st = FS_OK;
     // Seeds are a help: a workspace that holds the call without them is not given up for them, and not grown where it cannot be
     // (while a graph is recorded) or where there was no memory for as much before.
-    if (P->seeds.bytes[0] && need > c->ws_bytes) {
+    if ((P->seeds.bytes[0] || P->seeds.bytes[1]) && need > c->ws_bytes) {
         const size_t with_seeds = need;
         P->want_seeds = false;
         need = layout(c, p, P, nullptr, extra);
@@ -940,6 +940,7 @@ fs_status fs_solve_symmetric(fs_ctx *ctx, const fs_problem *prob, float eps_in, 
     Prepared P;
     P.halfsteps_per_eps = 2 * iters;
     P.want_seeds = iters > 1;
+    P.pairs = true;
     // Both passes of an iteration read the old potentials, so the second one must not overwrite
     // the split partials of the first before they are merged: it gets a partial buffer of its own.
     Prepared sizing;

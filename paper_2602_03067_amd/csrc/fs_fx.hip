@@ -985,10 +985,9 @@ PassShape fx_shape(const Ctx *c, int64_t n_res, int64_t n_str, int occ)
     return s;
 }
 
-fs_status pass_args(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, int mode, int nc, bool had, void *partial,
-                    FxArgs *out, PassShape *shape)
+fs_status pass_args(Ctx *c, const Prepared *P, const Side *res, const Side *str, const PassShape &s, double eps, int mode, void *partial,
+                    FxArgs *out)
 {
-    const PassShape s = fx_shape(c, res->cnt, str->cnt, fx_wg_per_cu(P->fx_ks, mode, nc, had));
     FxArgs a{};
     a.res = res->dig;
     a.str = str->dig;
@@ -1017,7 +1016,6 @@ fs_status pass_args(Ctx *c, const Prepared *P, const Side *res, const Side *str,
         sd.splits[t] = s.splits;
     }
     *out = a;
-    *shape = s;
     return FS_OK;
 }
 
@@ -1096,13 +1094,38 @@ static bool fx_long(const Ctx *c, const PassShape &s, const PassShape &s0, int k
     return s.cols_per_split >= 24 * 32 && (ks > 2 || s.cost <= (!seeds ? 1.05 : ks == 1 ? 1.09 : 1.11) * s0.cost);
 }
 
+// the shape of a half-step over the rows of side t (0: X)
+static const PassShape &fx_half_step(const Ctx *c, const Prepared *P, int t, bool lng)
+{
+    PassShape &s = P->fx_shapes[t][lng];
+    if (s.row_blocks == 0) s = fx_shape(c, (t ? P->Y : P->X).cnt, (t ? P->X : P->Y).cnt, fx_wg_per_cu(P->fx_ks, lng ? 3 : 0, 1, false));
+    return s;
+}
+static bool fx_long_pass(const Ctx *c, const Prepared *P, int t, bool seeds)
+{
+    return fx_long(c, fx_half_step(c, P, t, true), fx_half_step(c, P, t, false), P->fx_ks, seeds);
+}
+// (both passes of one launch fill its places together: n = m = 9000, d = 20, us a half-step: 44.8 in MODE 0 and 42.3 in MODE 3, 48.8 and
+// 45.1)
+static bool fx_long_pair(const Ctx *c, const Prepared *P)
+{
+    const PassShape &sx = fx_half_step(c, P, 0, true), &sy = fx_half_step(c, P, 1, true);
+    return fx_long(c, sx, sx, P->fx_ks, true) && fx_long(c, sy, sy, P->fx_ks, true);
+}
+
+size_t fx_seed_bytes(const Ctx *c, const Prepared *P, int t, bool pairs)
+{
+    if (!(pairs ? fx_long_pair(c, P) : fx_long_pass(c, P, t, true))) return 0;
+    return (size_t)fx_half_step(c, P, t, true).splits * (t ? P->Y : P->X).cnt_pad * sizeof(FxSeed);
+}
+
 fs_status fx_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, int *splits, bool launch)
 {
     FxArgs a;
-    PassShape s = fx_shape(c, res->cnt, str->cnt, fx_wg_per_cu(P->fx_ks, 3, 1, false));
     const int t = res == &P->X ? 0 : 1;
-    const bool lng = fx_long(c, s, fx_shape(c, res->cnt, str->cnt, fx_wg_per_cu(P->fx_ks, 0, 1, false)), P->fx_ks, P->seeds.bytes[t] != 0);
-    fs_status st = pass_args(c, P, res, str, eps, lng ? 3 : 0, 1, false, P->partial, &a, &s);
+    const bool lng = fx_long_pass(c, P, t, P->seeds.bytes[t] != 0);
+    const PassShape &s = fx_half_step(c, P, t, lng);
+    fs_status st = pass_args(c, P, res, str, s, eps, lng ? 3 : 0, P->partial, &a);
     if (st != FS_OK) return st;
     *splits = s.splits;
     if (!launch) {
@@ -1131,13 +1154,11 @@ fs_status fx_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, do
 fs_status fx_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, void *partial_y, int *splits_x, int *splits_y, bool launch)
 {
     FxArgs ax, ay;
-    const int occ = fx_wg_per_cu(P->fx_ks, 3, 1, false);
-    PassShape sx = fx_shape(c, P->X.cnt, P->Y.cnt, occ), sy = fx_shape(c, P->Y.cnt, P->X.cnt, occ);
-    // (two passes fill the places of one launch: n = m = 9000, d = 20 44.8 us a half-step in MODE 0 and 42.3 in MODE 3, 48.8 and 45.1)
-    const bool lng = fx_long(c, sx, sx, P->fx_ks, true) && fx_long(c, sy, sy, P->fx_ks, true);
+    const bool lng = fx_long_pair(c, P);
+    const PassShape &sx = fx_half_step(c, P, 0, lng), &sy = fx_half_step(c, P, 1, lng);
     fs_status st;
-    if ((st = pass_args(c, P, &P->X, &P->Y, eps, lng ? 3 : 0, 1, false, partial_x, &ax, &sx)) != FS_OK) return st;
-    if ((st = pass_args(c, P, &P->Y, &P->X, eps, lng ? 3 : 0, 1, false, partial_y, &ay, &sy)) != FS_OK) return st;
+    if ((st = pass_args(c, P, &P->X, &P->Y, sx, eps, lng ? 3 : 0, partial_x, &ax)) != FS_OK) return st;
+    if ((st = pass_args(c, P, &P->Y, &P->X, sy, eps, lng ? 3 : 0, partial_y, &ay)) != FS_OK) return st;
     *splits_x = sx.splits;
     *splits_y = sy.splits;
     if (!launch) {
@@ -1187,8 +1208,8 @@ fs_status fx_apply_pass(Ctx *c, const Prepared *P, const Side *res, const Side *
     int mode, nc;
     fx_columns(p - p0, hadA != nullptr, &mode, &nc);
     FxArgs a;
-    PassShape s;
-    fs_status st = pass_args(c, P, res, str, eps, mode, nc, hadA != nullptr, P->partial, &a, &s);
+    const PassShape s = fx_shape(c, res->cnt, str->cnt, fx_wg_per_cu(P->fx_ks, mode, nc, hadA != nullptr));
+    fs_status st = pass_args(c, P, res, str, s, eps, mode, P->partial, &a);
     if (st != FS_OK) return st;
     const ApplyBuf buf(s.splits, res->cnt_pad, a.n_tiles, P->fx_ks, mode, nc, hadA != nullptr);
     if (!P->extra || buf.total > P->extra_bytes) return fail(c, FS_ERR_DEVICE, "internal: fixed-point application exceeds its buffer");

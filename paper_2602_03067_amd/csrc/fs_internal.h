@@ -364,6 +364,15 @@ struct MomState {
     std::unique_ptr<int[]> host;   // what the host has read back of the cells (see Layout::counts in fs_moments.hip)
 };
 
+// Launch-shape decision of one streaming pass.
+struct PassShape {
+    int rows_per_block = 0;
+    int row_blocks = 0;
+    int splits = 1;
+    int64_t cols_per_split = 0;   // multiple of the column tile
+    double cost = 0.0;            // fixed-point passes: what the model of fx_shape expects
+};
+
 constexpr int kScalars = 32, kScalarBounds = 16;   // Prepared::scalars
 struct Prepared {
     Path path = Path::LowD;
@@ -393,7 +402,9 @@ struct Prepared {
         size_t bytes[2] = {0, 0};
     };
     bool want_seeds = false;      // set by the entry points that pass over the same rows several times
+    bool pairs = false;           // ... two passes a launch (fs_solve_symmetric)
     mutable Seeds seeds;
+    mutable PassShape fx_shapes[2][2];   // of half-steps over the rows of X [0] and Y [1] in MODE 0 and 3, once asked for
     Side X, Y;
     // partial reductions of a streaming pass: [splits][max(n,m)_pad] records
     void *partial = nullptr;
@@ -413,8 +424,6 @@ struct Prepared {
 struct FxSeed {
     int dot, point;
 };
-// bytes of one buffer of a side: 64 splits of a small side, or what fills the chip four times
-inline size_t fx_seed_bytes(int64_t cnt_pad) { return (size_t(2) << 20) + (size_t)cnt_pad * 2 * sizeof(FxSeed); }
 
 // Prepared::box: one word for the exponent of r2, two for each scalar of the low-d prologue (see launch_bias_from_user)
 constexpr int kBoxFx = 0, kBoxLowd = 8, kBoxWords = 64;
@@ -506,15 +515,6 @@ struct FinalizeArgs {
 // ---------------------------------------------------------------------------------------
 // kernel launchers (implemented in the path-specific translation units)
 // ---------------------------------------------------------------------------------------
-
-// Launch-shape decision of one streaming pass.
-struct PassShape {
-    int rows_per_block = 0;
-    int row_blocks = 0;
-    int splits = 1;
-    int64_t cols_per_split = 0;   // multiple of the column tile
-    double cost = 0.0;            // fixed-point passes: what the model of fx_shape expects
-};
 
 // fs_prep.hip
 fs_status launch_prepare(Ctx *c, const fs_problem *p, Prepared *P);
@@ -665,6 +665,8 @@ fs_status f64_apply(Ctx *c, const Prepared *P, const Side *res, const Side *str,
 // (launch = false: the host knows that the gate is off, only the shapes are asked for)
 fs_status fx_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, int *splits, bool launch);
 fs_status fx_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, void *partial_y, int *splits_x, int *splits_y, bool launch);
+// bytes of one buffer of seeds of the rows of side t (0: X) in a call that passes over them several times; pairs: two passes a launch
+size_t fx_seed_bytes(const Ctx *c, const Prepared *P, int t, bool pairs);
 size_t fx_apply_ws(const Ctx *c, int64_t n_res, int64_t n_str, int64_t d, int64_t p);
 fs_status fx_apply_pass(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, const float *V, int64_t p, int64_t ldv,
                         int p0, const float *hadA, int64_t lda, int *splits, int *pc, const double **had_add, bool launch);

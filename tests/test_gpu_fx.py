@@ -598,3 +598,34 @@ def test_solves_where_there_is_no_memory_for_starts(oracle):
     c.fs_solve(prob, eps, eps, 1, iters, f, g)
     _check_solve((f, g), want, eps, iters)
     c.close()
+
+
+def test_starts_of_many_row_blocks_and_splits():
+    """The starts of the running max are there at every launch shape: where many row blocks meet many splits (13 here), most tiles of
+    clouds of consecutive clusters are left early, and the result is that of passes that leave none."""
+    n, d, eps, iters = 30000, 32, float(np.float32(0.1)), 3
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(5)
+    centres = torch.randn(8, d, generator=gen, device="cuda:0")
+    x, y = (centres[torch.arange(n, device="cuda:0") * 8 // n] + 0.05 * torch.randn(n, d, generator=gen, device="cuda:0") for _ in range(2))
+    prob = binding.Problem(x, y)
+    say("fx starts of many splits n=m=%d" % n)
+    out = []
+    for long in (0, 2):
+        c = binding.Context(0)
+        c.fs_debug_set("fx_long", long)
+        c.fs_debug_set("fx_count", 1)
+        f, g = torch.zeros(n, device="cuda:0"), torch.zeros(n, device="cuda:0")
+        c.fs_solve(prob, eps, eps, 1, iters, f, g)
+        tiles, left = c.fs_debug_get("fx_tiles"), c.fs_debug_get("fx_tiles_left")
+        say("  %d of %d tiles left" % (left, tiles))
+        if long == 0:
+            assert tiles == 2 * iters * 940 * 938   # (235 row blocks of four waves, 938 tiles)
+            # (seven clusters of eight are out of reach from the second pass over a side on)
+            assert left >= 0.8 * (iters - 1) / iters * 7 / 8 * tiles
+        else:
+            assert tiles == 0
+        out.append((f, g))
+        c.close()
+    for u, v in zip(*out):
+        assert float((u - v).abs().max()) <= 2 * 2e-6 * iters * eps + 2.0 ** -23 * float(u.abs().max()) * 1.01
