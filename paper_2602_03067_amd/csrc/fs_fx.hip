@@ -166,11 +166,12 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
     float u3 = (float)u3d, u5 = (float)u5d;
     asm volatile("" : "+v"(u3), "+v"(u5));   // (an instruction that reads a scalar register takes twice the time)
     const int lazy = (int)fmin(4.0 / u3d, 1073741824.0);   // see settle
-    // A tile none of whose scores comes to m less this (with the most that the low digits can add, 2^31 u5) is left at its leading
-    // products: an exponential there is less than 2^-60 of the row's sum over all splits (m is a score of the
-    // row, or, where it comes from a seed and the low digits conspire, up to 2^31 u5 = v / 128 units above one).  Half-steps only: the values of an
-    // application may be of any size.
-    const int skip = -(int)fmin(60.0 / u3d + 32768.0, 2147483647.0);
+    // A tile none of whose scores comes to m less this is left at its leading products.  What low digits and a bias's remainder add to a
+    // score is between -193 d and 193 d + 257 of the leading digits' units (three products of 2^14 per coordinate and 2^8, the others a
+    // 1/192 of that), and m is the leading part of a score or, from a seed, one with its whole bias and 15 units at most above it,
+    // so with this slack an exponential that is left is less than 2^-59 of the row's largest, over all splits and whatever the digits.
+    // Half-steps only: the values of an application may be of any size.
+    const int skip = -(int)fmin(60.0 / u3d + (2.0 * 193.0 * 32.0 * KS + 273.0), 2147483647.0);
 
     int issued = 0;
     auto issue = [&]() __attribute__((always_inline)) {
