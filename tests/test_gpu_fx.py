@@ -259,7 +259,7 @@ def test_paired_passes(oracle, n, m, d, splits):
 @pytest.mark.parametrize("kind", ["cube", "cube fine", "wide", "clusters", "no weight"])
 def test_long_passes_of_a_solve(oracle, d, kind):
     """Passes of 24 tiles and more per workgroup: the running max starts at a point the last pass found, and tiles that cannot
-    count are left at their leading products: none of a cube's, most of wide and clustered clouds'."""
+    count are left at their leading products (how many: the tests below)."""
     n, m = 900, 35 * 32 + 5
     rng, x, y, a, b = _problem(d + len(kind), n, m, d)
     e0 = e1 = {"cube": 0.5, "cube fine": 0.03, "wide": 0.1, "clusters": 0.1, "no weight": 0.1}[kind]
@@ -519,6 +519,154 @@ def _check_solve(got, want, eps, iters):
     """Each half-step adds at most 1e-6 of its eps and passes on no more than it gets."""
     for u, v in zip(got, want):
         assert np.all(np.abs(host(u) - v) <= 2e-6 * iters * eps + 2.0 ** -24 * np.abs(v) * 1.01)
+
+
+def _long_clouds(kind, n, m, d):
+    """Clouds, weights and eps by what a long half-step may leave of them."""
+    rng, x, y, a, b = _problem(d + len(kind), n, m, d)
+    e0 = e1 = {"cube": 0.5, "cube fine": 0.03}.get(kind, 0.1)
+    if kind == "wide":
+        x = (rng.standard_normal((n, d)) * 1.5).astype(np.float32)
+        y = (rng.standard_normal((m, d)) * 1.5 + 0.5).astype(np.float32)
+    if kind == "clusters":
+        centres = rng.standard_normal((6, d))
+        x = (centres[np.arange(n) * 6 // n] + 0.05 * rng.standard_normal((n, d))).astype(np.float32)
+        y = (centres[np.arange(m) * 6 // m] + 0.05 * rng.standard_normal((m, d))).astype(np.float32)
+    return x, y, a, b, float(np.float32(e1))
+
+
+# three splits of 25 tiles a side; 14 splits of a few rows (more than the twelve that are looked through at once), against one or two
+# tiles a workgroup of the other side
+@pytest.mark.parametrize("n,m,splits", [(2400, 2390, 3), (200, 14 * 24 * 32 + 5, 14)])
+@pytest.mark.parametrize("d", [20, 64, 70, 128])
+@pytest.mark.parametrize("kind", ["cube", "cube fine", "wide", "clusters"])
+def test_long_passes_over_several_splits(oracle, n, m, splits, d, kind):
+    """The best of several splits' starts, from either lane half and from the first pass's own: solves of both schedules at the bounds of
+    one split, and how many tiles are left early: none of a cube's, some of wide clouds', and of clusters in a row most of those out of
+    reach."""
+    iters = 3
+    x, y, a, b, eps = _long_clouds(kind, n, m, d)
+    c = binding.Context(0)
+    c.fs_debug_set("fx_any_size", 1)
+    c.fs_debug_set("fx_long", 1)
+    c.fs_debug_set("fx_splits", splits)
+    c.fs_debug_set("fx_count", 1)
+    prob = make_problem(x, y, a, b)
+    say("fx long passes n=%d m=%d splits=%d d=%d %s" % (n, m, splits, d, kind))
+    f, g = torch.zeros(n, device="cuda:0"), torch.zeros(m, device="cuda:0")
+    c.fs_solve(prob, eps, eps, 1, iters, f, g)
+    tiles, left = c.fs_debug_get("fx_tiles"), c.fs_debug_get("fx_tiles_left")
+    rows = [-(-k // 128) * 4 for k in (n, m)]
+    assert tiles == iters * (rows[0] * -(-m // 32) + rows[1] * -(-n // 32))
+    say("  %.3f of the tiles left" % (left / tiles))
+    if kind == "cube":
+        assert left == 0
+    if kind == "wide":
+        assert left > 0
+    if kind == "clusters":   # (from the second pass over a side on; a tile of rows or points may lie in two clusters)
+        assert left >= (iters - 1) / iters * (5 / 6 - 0.35) * tiles
+    _check_solve((f, g), oracle.solve(x, y, a, b, eps, eps, 1, iters), eps, iters)
+    f.zero_()
+    g.zero_()
+    c.fs_debug_set("fx_count", 0)
+    c.fs_solve_symmetric(prob, eps, iters, f, g)
+    _check_solve((f, g), oracle.solve_symmetric(x, y, a, b, eps, iters), eps, iters)
+    c.close()
+
+
+def test_early_tiles_change_nothing_that_is_seen():
+    """Clouds many of whose tiles are left early, against passes that leave none: the same to the rounding of the potentials."""
+    n, m, d, iters = 900, 35 * 32 + 5, 64, 4
+    for kind in ("wide", "clusters"):
+        x, y, a, b, eps = _long_clouds(kind, n, m, d)
+        out = []
+        for long in (1, 2):
+            c = _long_context()
+            c.fs_debug_set("fx_long", long)
+            c.fs_debug_set("fx_count", 1)
+            say("fx long=%d %s" % (long, kind))
+            f, g = torch.zeros(n, device="cuda:0"), torch.zeros(m, device="cuda:0")
+            c.fs_solve(make_problem(x, y, a, b), eps, eps, 1, iters, f, g)
+            tiles, left = c.fs_debug_get("fx_tiles"), c.fs_debug_get("fx_tiles_left")
+            say("  %d of %d tiles left" % (left, tiles))
+            assert (left > 0.05 * tiles) if long == 1 else tiles == 0
+            out.append((host(f), host(g)))
+            c.close()
+        for u, v in zip(*out):
+            assert np.all(np.abs(u - v) <= 4e-6 * iters * eps + 2.0 ** -23 * np.abs(u) * 1.01)
+
+
+def test_long_passes_across_the_gate(oracle):
+    """Stages of eps on the fp64 kernels, on ten and on thirteen products and on the fp64 kernels again, in long half-steps: starts that a
+    pass on the other kernels left behind are none."""
+    n, m, d = 900, 35 * 32 + 5, 40
+    rng, x, y, a, b = _problem(8, n, m, d)
+    prob = make_problem(x, y, a, b)
+    e0, e1, stages, iters = float(np.float32(200.0)), float(np.float32(2e-4)), 12, 2
+    fo, go = oracle.solve(x, y, a, b, e0, e1, stages, iters)
+    steps = 2 * iters * sum(e0 * (e1 / e0) ** (s / (stages - 1)) for s in range(stages))
+    ulp = 2.0 ** -23 * max(np.abs(fo).max(), np.abs(go).max()) * 1.01
+    for splits in (1, 2):
+        c = _long_context()
+        c.fs_debug_set("fx_splits", splits)
+        c.fs_debug_set("fx_long", 1)
+        say("fx long passes across the gate, splits=%d" % splits)
+        f, g = torch.zeros(n, device="cuda:0"), torch.zeros(m, device="cuda:0")
+        c.fs_solve(prob, e0, e1, stages, iters, f, g)
+        t = float(np.median(host(f) - fo))   # (common to all points and not damped, see test_annealing_across_the_gate)
+        say("  common shift %.2e" % t)
+        assert abs(t) <= 1e-6 * steps
+        for got, want, sign in ((f, fo, 1.0), (g, go, -1.0)):
+            assert np.abs(host(got) - sign * t - want).max() <= 1e-5 * e1 + ulp
+        c.close()
+
+
+@pytest.mark.parametrize("splits", [1, 2])
+@pytest.mark.parametrize("where", ["nan", "inf", "-inf", "all -inf", "far"])
+def test_long_passes_with_potentials_that_are_not_finite(where, splits):
+    """Half-steps and solves from such potentials: what is not finite is what it is in short half-steps, the rest agrees."""
+    n, m, d, iters = 900, 35 * 32 + 5, 40, 3
+    x, y, a, b, eps = _long_clouds("wide", n, m, d)
+    g0 = np.zeros(m, np.float32)
+    if where == "all -inf":
+        g0[:] = -np.inf
+    else:
+        g0[[5, 700, m - 1]] = {"nan": np.nan, "inf": np.inf, "-inf": -np.inf, "far": -3e6}[where]
+    prob = make_problem(x, y, a, b)
+    out = []
+    for long in (1, 2):
+        c = _long_context()
+        c.fs_debug_set("fx_splits", splits)
+        c.fs_debug_set("fx_long", long)
+        say("fx long=%d %s splits=%d" % (long, where, splits))
+        f, g = torch.zeros(n, device="cuda:0"), dev(g0)
+        one = host(c.fs_update_f(prob, eps, g))
+        c.fs_solve(prob, eps, eps, 1, iters, f, g)
+        out.append((one, host(f), host(g)))
+        c.close()
+    for u, v in zip(*out):
+        assert np.array_equal(np.isnan(u), np.isnan(v)) and np.array_equal(np.isposinf(u), np.isposinf(v))
+        assert np.array_equal(np.isneginf(u), np.isneginf(v))
+        ok = np.isfinite(u)
+        assert np.all(np.abs(u[ok] - v[ok]) <= 4e-6 * iters * eps + 2.0 ** -23 * np.abs(u[ok]) * 1.01)
+
+
+@pytest.mark.parametrize("splits", [1, 2])
+def test_long_passes_with_early_stopping(oracle, splits):
+    """fs_solve_tol looks at the error between half-steps of one call: the iterations and potentials of the oracle."""
+    n, m, d, iters = 900, 35 * 32 + 5, 40, 5
+    for kind in ("cube", "clusters"):
+        x, y, a, b, eps = _long_clouds(kind, n, m, d)
+        c = _long_context()
+        c.fs_debug_set("fx_splits", splits)
+        c.fs_debug_set("fx_long", 1)
+        say("fx long passes, early stopping, %s splits=%d" % (kind, splits))
+        f, g = torch.zeros(n, device="cuda:0"), torch.zeros(m, device="cuda:0")
+        done, err = c.fs_solve_tol(make_problem(x, y, a, b), eps, iters, 2, 0.0, f, g)
+        want = oracle.solve(x, y, a, b, eps, eps, 1, iters)
+        assert done == iters and abs(err - oracle.marginal_err(x, y, a, b, eps, *want)[0]) <= 1e-5
+        _check_solve((f, g), want, eps, iters)
+        c.close()
 
 
 def test_recorded_solve_after_other_calls(oracle):

@@ -92,6 +92,34 @@ def test_half_steps(ctx, oracle, n, m, d, eps, kind, pot):
 @pytest.mark.parametrize("n,m,eps", [(600, 500, 0.01), (3000, 2500, 0.006), (3000, 2500, 0.01), (2561, 2049, 0.008)])
 def test_middle_expansion_in_two_dimensions(ctx, oracle, n, m, eps):
     test_half_steps(ctx, oracle, n, m, 2, eps, "cube", "smooth")
+    assert ctx.fs_debug_get("moment_kind") == 5
+
+
+# Every kind of expansion, forced: rows that fill a group of a cell but for one, it and one row more (and one row, all in one cell), and
+# several cells with ragged and full groups each; the widest cells that a kind allows have 2, 4 or 7 tiles of moments to themselves
+@pytest.mark.parametrize("kind", [1, 2, 3, 4, 5, 6, 7])
+@pytest.mark.parametrize("n,m,extent", [(1, 300, 0.1), (255, 40, 0.1), (256, 33, 0.1), (257, 300, 0.1), (513, 1, 0.1), (900, 1500, 1.0),
+                                        (3000, 2049, 1.0)])
+def test_every_kind_of_expansion(oracle, kind, n, m, extent):
+    d = {1: 3, 2: 3, 3: 3, 4: 2, 5: 2, 6: 2, 7: 1}[kind]
+    rng = np.random.default_rng(n + m + kind)
+    x, y = ((extent * rng.random((k, d))).astype(np.float32) for k in (n, m))
+    a, b = _weights(rng, n), _weights(rng, m)
+    eps = float(np.float32(0.1))
+    g, f = ((0.3 * rng.standard_normal(1) * v[:, 0] + eps * rng.standard_normal(len(v))).astype(np.float32) for v in (y, x))
+    c = binding.Context(0)
+    c.fs_debug_set("lowd_moments", 1)
+    c.fs_debug_set("moment_kind", kind)
+    assert c.fs_debug_get("moment_kind") == 0
+    say("moments kind %d n=%d m=%d extent=%g" % (kind, n, m, extent))
+    prob = make_problem(x, y, a, b)
+    f1 = host(c.fs_update_f(prob, eps, dev(g)))
+    assert c.fs_debug_get("moment_kind") == kind
+    g1 = host(c.fs_update_g(prob, eps, dev(f)))
+    fw, gw = oracle.update_f(x, y, b, eps, g), oracle.update_g(x, y, a, eps, f)
+    assert max_err_over_eps(f1, fw, eps) <= _tol(fw, eps)
+    assert max_err_over_eps(g1, gw, eps) <= _tol(gw, eps)
+    c.close()
 
 
 def test_runs_through_moments_and_falls_back(oracle):
