@@ -141,6 +141,17 @@ def run_workload(name, steps, warmup, schedule="alternating", n_override=None, c
         ctx.fs_solve(prob, w.eps_start, w.eps_end, w.n_stages, w.iters, f, g)
     se1.record()
     torch.cuda.synchronize()
+    # digit products of a tile that run: long half-steps leave a tile whose scores cannot count at its three leading ones.  (How many
+    # do is counted in one more solve, outside the timed region too; the paired launches of the averaged schedule count none.)
+    products = digit_products(w)
+    left = None if schedule == "symmetric" else 0.0
+    if products and schedule != "symmetric":
+        ctx.fs_debug_set("fx_count", 1)
+        f.zero_()
+        g.zero_()
+        ctx.fs_solve(prob, w.eps_start, w.eps_end, w.n_stages, w.iters, f, g)
+        left = ctx.fs_debug_get("fx_tiles_left") / max(1, ctx.fs_debug_get("fx_tiles"))
+        ctx.fs_debug_set("fx_count", 0)
     ctx.fs_points_release()
     solve_ms = se0.elapsed_time(se1)
     # A plan application with 64 value columns (outside the timed region too): at d <= 16 the step's own applications
@@ -184,13 +195,12 @@ def run_workload(name, steps, warmup, schedule="alternating", n_override=None, c
         roof = {"bound": "mfma", "achieved": flops / (avg_ms * 1e-3) / 1e12, "peak": PEAKS["bf16"] / 1e12,
                 "unit": "TFLOP/s"}
         dtype = "bf16"
-    elif digit_products(w):
-        # fixed-point scores on the int8 matrix cores (the products of every tile are counted; long half-steps leave those of tiles
-        # whose scores cannot count undone but for the three leading ones, so this is the rate of the work asked for)
-        flops = 2.0 * ((w.d + 31) // 32 * 32) * digit_products(w) * pairs
-        roof = {"bound": "mfma", "achieved": flops / (avg_ms * 1e-3) / 1e12, "peak": PEAKS["i8"] / 1e12,
-                "unit": "TOP/s"}
-        # the contraction itself as float operations against the fp32 vector peak (157.3 TFLOP/s)
+    elif products:
+        # fixed-point scores on the int8 matrix cores: the products that ran, and beside them what was asked for, all of every tile's
+        asked = 2.0 * ((w.d + 31) // 32 * 32) * products * pairs / (avg_ms * 1e-3) / 1e12
+        roof = {"bound": "mfma", "achieved": None if left is None else asked * (1.0 - left * (products - 3) / products),
+                "peak": PEAKS["i8"] / 1e12, "unit": "TOP/s", "asked_for_rate": asked, "tiles_left_early": left}
+        # the contraction itself, that of all pairs, as float operations against the fp32 vector peak (157.3 TFLOP/s)
         roof["frac_of_fp32_vector_peak"] = 2.0 * w.d * pairs / (avg_ms * 1e-3) / 157.3e12
         dtype = "f32"
     elif w.d > 16:
@@ -211,7 +221,7 @@ def run_workload(name, steps, warmup, schedule="alternating", n_override=None, c
     if moments:
         roof.update(bound="mfma + alu", achieved=None, peak=None, unit=None, frac=None)
     else:
-        roof["frac"] = roof["achieved"] / roof["peak"]
+        roof["frac"] = None if roof["achieved"] is None else roof["achieved"] / roof["peak"]
     traffic = MEASURED_TRAFFIC.get(w.name) if n_override is None and not moments else None
     roof["traffic"] = traffic[0] if traffic else None
     roof["traffic_source"] = (traffic[1] + " (rocprofv3 counters of an earlier run of this command, not of this run)") \
@@ -220,7 +230,8 @@ def run_workload(name, steps, warmup, schedule="alternating", n_override=None, c
     # second, and the measured HBM traffic as a rate and as a fraction of the 8 TB/s peak (far from it: the
     # pass is not HBM-bound; the re-reads of the streamed cloud are served by L2 and the memory-side cache)
     per_s = None if moments else pairs / (avg_ms * 1e-3)
-    rates = {"pair_evals_per_s": per_s, "exp2_per_s": per_s}
+    # (of a tile that is left early the scores are known to be too small, and no exponential is evaluated)
+    rates = {"pair_evals_per_s": per_s, "exp2_per_s": per_s if not products else None if left is None else per_s * (1.0 - left)}
     if roof["traffic"]:
         rates["hbm_GB_per_s"] = roof["traffic"] / (avg_ms * 1e-3) / 1e9
         rates["hbm_frac_of_peak"] = rates["hbm_GB_per_s"] / 8000.0
