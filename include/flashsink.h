@@ -163,7 +163,7 @@ fs_status fs_solve(fs_ctx *ctx, const fs_problem *prob, float eps_start, float e
 
 /*
  * fs_solve for callers that cannot allocate device memory (code under HIP graph capture, tight serving
- * loops, harnesses that forbid hipMalloc): the same arguments, arithmetic and results as fs_solve, but
+ * loops, harnesses that forbid hipMalloc): the arguments and arithmetic of fs_solve, and its results up to the order of sums, but
  * the workspace (derived copies of x and y, norms, biases, potentials, partial reductions) lives in a
  * static device array of 32 MiB inside the library, of which the partial reductions of a pass take at
  * most 8 MiB (so a pass may be cut into fewer column splits than fs_solve would choose).  The call

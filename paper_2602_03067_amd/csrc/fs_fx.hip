@@ -42,15 +42,15 @@
 // the others, so a wave waits for its own products more often; three workgroups per CU fill those waits at d <= 96 (168 registers: sums
 // of one weight are shifted before the next ones join them).  Half-step with its merge (us): that case 216 -> 116, the self term of a
 // divergence at n = 10000, d = 64 78 -> 53; where nothing can be left (unit cube) n = m = 16384, d = 64 197 -> 186, n = m = 10000, d = 128
-// 139 -> 134, n = m = 8192, d = 64 53 -> 57, which is why short passes stay in MODE 0 (fx_long).
+// 136 -> 122, n = m = 8192, d = 64 53 -> 57, which is why short passes stay in MODE 0 (fx_long).
 //
 // Bound: matrix and vector instructions, and with them the chip's power.  A wave alone issues a vector instruction every 2.5 ns, two
 // of a SIMD 1.3 (2.1 for conversions, shifts by an immediate, three-way maxima and whatever reads a scalar register), three or four 1.0
 // (1.9); an MFMA takes 13.6 ns, 20 with random operands.  A tile of 32 x 32 scores at d = 64 is 20 or 26 MFMAs and about 175 vector
 // instructions: 700 to 800 ns (n = m = 16384, ten products, three workgroups per CU: 305000 cycles per CU at 1.85 GHz, and with all points
 // but two at zero 283000 at 2.19).  Four workgroups per CU in MODE 3 at d = 64 spill: 78.5 us against 76 at n = m = 10000.
-// Measured (half-step with its merge, us, fp64 and here; the other kernel's empty launch included; before MODE 3): n = m = 10000, d = 64:
-// 232 -> 79 (ten products); n = 9973, m = 12007, d = 128: 545 -> 150 (ten); n = 9973, m = 12007, d = 20: 71 (ten).
+// Measured (half-step with its merge, us, fp64 and here; unit cube, ten products): n = m = 10000, d = 64: 232 -> 77; n = 9973, m = 12007, d = 128:
+// 545 -> 145; n = 9973, m = 12007, d = 20: 63.
 // Error of plan sums against 64 bits (n = 3001, m = 2800, d = 64 and 128; cube, normal, pixel and two-valued points,
 // everywhere between the gates): 3e-8 to 6.5e-8, 64 columns of both signs 7e-8 to 1.1e-7; fp64 scores with fp32 sums 3.4e-8 to
 // 4.3e-7 and 5e-8 to 5.6e-7.

@@ -35,8 +35,8 @@
 // 1e-7 to 2e-7 instead of 2e-8 to 5e-8.  A spare monomial with what two pieces leave of the moment of degree 0 did not change that.
 // Sums are formed in a fixed order (the sort is stable), so a result does not depend on the run.
 //
-// Measured (half-step, us, over the pairs and here): n = m = 262144, d = 3, mixture and cube, eps = 0.01: 5900 -> 1950, 0.046: 5900
-// -> 270, 1: 5900 -> 80; n = 50021, m = 40013, cube, eps = 0.05: 219 -> 57 (all before the waves of a SIMD took turns, see below).
+// Measured (half-step of a solve, us, over the pairs and here): n = m = 262144, d = 3, mixture / cube, eps = 0.01: 5900 -> 1290 / 1700, 0.046:
+// 5900 -> 207 / 202, 1: 5900 -> 76 / 73; n = 50021, m = 40013, cube, eps = 0.05: 219 -> 48.
 // Bound at large sizes: what a SIMD's two waves do not overlap of the vector, matrix and LDS instructions of k_mom_gather (a weight
 // costs its exponential, three fma and the split, 110 instructions per 16 points and 32 cells beside 21 products at RT = 7; products
 // alone would take a third of its time), products of k_mom_rows (three quarters of its loop); at small ones latency, the gather takes
