@@ -4,7 +4,7 @@
 
 Every .hip file under csrc/ is compiled to an object (only when stale) and linked
 into paper_2602_03067_amd/libflashsink.so.  Packed-fp32 instructions are switched
-off for the device pass, as this GPU pool requires.
+off for the device pass: some of their forms have given wrong results now and then.
 """
 from __future__ import annotations
 
