@@ -164,7 +164,8 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
 
     const double u3d = a.gate.unit(22), u5d = a.gate.unit(38);
     float u3 = (float)u3d, u5 = (float)u5d;
-    asm volatile("" : "+v"(u3), "+v"(u5));   // (an instruction that reads a scalar register takes twice the time)
+    constexpr bool kOneStep = MODE == 1 && KS == 1;
+    if (!kOneStep) asm volatile("" : "+v"(u3), "+v"(u5));   // (an instruction that reads a scalar register takes twice the time)
     const int lazy = (int)fmin(4.0 / u3d, 1073741824.0);   // see settle
     // A tile none of whose scores comes to m less this is left at its leading products.  What low digits and a bias's remainder add to a
     // score is between -193 d and 193 d + 257 of the leading digits' units (three products of 2^14 per coordinate and 2^8, the others a
@@ -421,7 +422,9 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
         }
         T.Q = biases(sb, 1);
         T.H = biases(sb, 0);
-        if constexpr (HOLD) __builtin_amdgcn_sched_barrier(0);   // (all of them asked for before the first product)
+        // (all of them asked for before the first product; not where that costs more than it brings: one wave a SIMD waits for them, and
+        // at one k-step and one column 16384 x 16384 took 194 us for 190 with this and the two other lines for kOneStep)
+        if constexpr (HOLD && !HAD && !kOneStep) __builtin_amdgcn_sched_barrier(0);
         if constexpr (FULL) {
             T.L = biases(sb, 2);
 #pragma unroll
@@ -458,7 +461,7 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
             FX_MM(T.L, 2, 1);
             FX_MM(T.L, 3, 0);
         }
-        if constexpr (MODE == 2) {
+        if constexpr (MODE == 2 && !HAD) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) T.L[r] = (int)(((unsigned)T.Q[r] << 8) + (unsigned)T.L[r]);
         }
@@ -466,7 +469,7 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
 #undef FX_MM
     // (not before it is used: the vector ALU is not to wait for the last of the products, see settle)
     auto low = [&](const Tile &T, int r) __attribute__((always_inline)) {
-        return MODE >= 2 ? T.L[r] : (int)(((unsigned)T.Q[r] << 8) + (unsigned)T.L[r]);
+        return MODE >= 2 && !HAD ? T.L[r] : (int)(((unsigned)T.Q[r] << 8) + (unsigned)T.L[r]);
     };
 
     // ---- before the exponentials of tile g: the slow path of a tile, and the lift of the max ------------------
@@ -547,7 +550,7 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
 #pragma unroll
         for (int r = 1; r < 16; ++r) hx = max(hx, T.H[r]);
         top = hx;
-        if (__any(hx > lazy || !known)) {
+        if (__any(hx > lazy || !(kOneStep ? s > 0.0 : known))) {
             if constexpr (MODE == 2) hx = max(hx, __shfl_xor(hx, 32));
             const int dh = known ? max(hx, 0) : hx == INT32_MIN ? 0 : hx;
             if (MODE == 3 && a.seed_out) {
@@ -734,7 +737,9 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
         const bool near = !__any(far);
         // (Whole tiles, and those with points without weight, have code copies of their own: where the others' scores join
         // theirs, the compiler moves all of them from one set of registers to another in every tile, 3 to 5 % of a pass.  In
-        // MODE 2 and 3 the copies would spill, and in MODE 2 points without weight take the float64 epilogue.)
+        // MODE 2 and 3 the copies would spill, and in MODE 2 points without weight take the float64 epilogue.  HAD has the registers, and
+        // its exponentials run beside the products of the weights only from the same piece of code: 16384 x 16384, d = 64, 8 columns,
+        // 667 us where they join, 619 here.)
         if constexpr (MODE == 3) {
             const bool direct = T.kind != 1 && near;
             if (direct) {
@@ -754,7 +759,7 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
         } else if (__builtin_expect(T.kind == 0 && near, 1)) {
             settle(g, T, top, std::false_type{});
             exponentials(T, e);
-            if constexpr (MODE != 2) {
+            if constexpr (MODE != 2 || HAD) {
                 finish(g, sb, e);
                 continue;
             }
