@@ -847,9 +847,10 @@ fs_status fs_solve_labeled(fs_ctx *ctx, const fs_problem *prob, const int32_t *l
     if ((st = solve_impl(c, &aug, eps_a, eps_a, 1, iters, fa, ga, false)) != FS_OK) return st;
     if ((st = launch_label_potential(c, fa, nullptr, l1, l1, false, n, f)) != FS_OK) return st;
     if ((st = launch_label_potential(c, ga, vc, 0.0, l1, false, m, g)) != FS_OK) return st;
+    double word = 0.0;   // (eight bytes, cleared together, of which the count is the first four)
+    if ((st = read_back(c, reinterpret_cast<double *>(bad), 1, &word)) != FS_OK) return st;
     unsigned nbad = 0;
-    FS_HIP(c, hipMemcpyAsync(&nbad, bad, sizeof nbad, hipMemcpyDeviceToHost, c->stream));
-    FS_HIP(c, hipStreamSynchronize(c->stream));
+    memcpy(&nbad, &word, sizeof nbad);
     if (nbad) return fail(c, FS_ERR_INVALID_ARG, "%u labels are outside [0, V)", nbad);
     return FS_OK;
 }
@@ -909,8 +910,7 @@ fs_status fs_solve_tol(fs_ctx *ctx, const fs_problem *prob, float eps_in, int32_
             FS_OK)
             return st;
         gauge_pending = false;
-        FS_HIP(c, hipMemcpyAsync(&err, P.scalars, sizeof(double), hipMemcpyDeviceToHost, c->stream));
-        FS_HIP(c, hipStreamSynchronize(c->stream));
+        if ((st = read_back(c, P.scalars, 1, &err)) != FS_OK) return st;
         if (err <= (double)tol || t == max_iters) break;
         pending = true;
     }
@@ -1025,8 +1025,7 @@ fs_status fs_marginal_err(fs_ctx *ctx, const fs_problem *prob, float eps, const 
         if ((st = finalize(c, &P, &P.Y, splits, eps, 0.0, nullptr, P.scalars + 1)) != FS_OK) return st;
     }
     double host[2] = {0.0, 0.0};
-    FS_HIP(c, hipMemcpyAsync(host, P.scalars, sizeof host, hipMemcpyDeviceToHost, c->stream));
-    FS_HIP(c, hipStreamSynchronize(c->stream));
+    if ((st = read_back(c, P.scalars, 2, host)) != FS_OK) return st;
     if (err_row_l1) *err_row_l1 = (float)host[0];
     if (err_col_l1) *err_col_l1 = (float)host[1];
     return FS_OK;
@@ -1054,8 +1053,7 @@ fs_status fs_ot_value(fs_ctx *ctx, const fs_problem *prob, float eps, const floa
         FS_OK)
         return st;
     double h[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    FS_HIP(c, hipMemcpyAsync(h, P.scalars, sizeof h, hipMemcpyDeviceToHost, c->stream));
-    FS_HIP(c, hipStreamSynchronize(c->stream));
+    if ((st = read_back(c, P.scalars, 5, h)) != FS_OK) return st;
     // App. B: <a,f> + <b,g> - eps (sum_ij P_ij - sum_ij a_i b_j)
     *value = h[1] + h[3] - (double)eps * (h[0] - h[2] * h[4]);
     return FS_OK;
@@ -1076,8 +1074,7 @@ fs_status fs_check_finite(fs_ctx *ctx, const float *v, int64_t cnt, int64_t *bad
     double *res = reinterpret_cast<double *>(c->aux);
     if ((st = launch_count_nonfinite(c, v, cnt, res + 1, res)) != FS_OK) return st;
     double h = 0.0;
-    FS_HIP(c, hipMemcpyAsync(&h, res, sizeof h, hipMemcpyDeviceToHost, c->stream));
-    FS_HIP(c, hipStreamSynchronize(c->stream));
+    if ((st = read_back(c, res, 1, &h)) != FS_OK) return st;
     if (bad_count) *bad_count = (int64_t)h;
     if (h > 0.0) return fail(c, FS_ERR_NONFINITE, "%.0f of %lld values are not finite", h, (long long)cnt);
     return FS_OK;
@@ -1100,9 +1097,8 @@ fs_status fs_check_weights(fs_ctx *ctx, const fs_problem *prob, float tol, doubl
     double h[4] = {1.0, 0.0, 1.0, 0.0};
     if (prob->a && (st = launch_weight_stats(c, prob->a, prob->n, scratch, res)) != FS_OK) return st;
     if (prob->b && (st = launch_weight_stats(c, prob->b, prob->m, scratch + 2 * ba, res + 2)) != FS_OK) return st;
-    if (prob->a) FS_HIP(c, hipMemcpyAsync(h, res, 2 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-    if (prob->b) FS_HIP(c, hipMemcpyAsync(h + 2, res + 2, 2 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-    FS_HIP(c, hipStreamSynchronize(c->stream));
+    // (of a side without weights nothing was written)
+    if ((st = read_back(c, prob->a ? res : res + 2, prob->a && prob->b ? 4 : 2, prob->a ? h : h + 2)) != FS_OK) return st;
     if (sum_a) *sum_a = h[0];
     if (sum_b) *sum_b = h[2];
     if (h[1] > 0.0) return fail(c, FS_ERR_BAD_WEIGHTS, "%.0f weights of a are not positive and finite", h[1]);

@@ -518,6 +518,9 @@ struct FinalizeArgs {
 
 // fs_prep.hip
 fs_status launch_prepare(Ctx *c, const fs_problem *p, Prepared *P);
+// cnt doubles (at most kMostReadBack) of the device to the host, once everything before on the stream has run
+constexpr int kMostReadBack = 28;
+fs_status read_back(Ctx *c, const double *src, int cnt, double *dst);
 // `first` / `last`: an entry point that brings in both potentials passes (true, false) and then
 // (false, true); the low-d read-back of the sizes that choose the score arithmetic (largest squared
 // norm, size of the biases) happens once, in the call with last = true.

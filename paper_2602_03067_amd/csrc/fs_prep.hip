@@ -1194,9 +1194,13 @@ __global__ __launch_bounds__(64) void k_publish(const double *src, int cnt, unsi
 // launch arrives; with a copy to host memory and a wait for the stream, two half-step calls at n = 1000, m = 777, d = 3 took 82 us,
 // with a kernel that writes to pinned memory and a host that looks there 59 (kernels 44).  Where the stream has long work
 // ahead of it, the host stops looking after a fifth of a millisecond and waits for the stream.
-static fs_status read_scalars(Ctx *c, unsigned long long *box, const double *src, int cnt, double *dst)
+// All reads of a call go this way: a copy behind kernels that the host has not waited for costs more than one behind a wait (dual
+// value at n = 200, m = 150, d = 3: prologue and value by copies 71 us, prologue through the box and value by a copy 80, both through
+// the box 46; a half-step and fs_check_finite at n = m = 3000, d = 3 73, 87 and 62).
+fs_status read_back(Ctx *c, const double *src, int cnt, double *dst)
 {
-    static_assert(kBoxLowd + 2 * (kScalarBounds - 5 + 12) <= kBoxWords, "scalars fit the box");
+    static_assert(kBoxLowd + 2 * kMostReadBack <= kBoxWords && kMostReadBack <= 32, "scalars fit the box, and a wave of k_publish");
+    unsigned long long *const box = c->ws_static ? c->static_box : c->box;
     if (!box) {
         FS_HIP(c, hipMemcpyAsync(dst, src, cnt * sizeof(double), hipMemcpyDeviceToHost, c->stream));
         FS_HIP(c, hipStreamSynchronize(c->stream));
@@ -1242,8 +1246,9 @@ fs_status launch_bias_from_user(Ctx *c, Prepared *P, Side *side, const float *po
     FS_HIP(c, hipGetLastError());
     if (absmax && last) {
         double h[kScalarBounds - 5 + 12] = {};   // |log w| part, potential part, rho_max; at the end bounds of the clouds, see k_mean_final
-        const fs_status st = read_scalars(c, P->box, P->scalars + 5, P->mom.base ? (int)(sizeof h / sizeof *h) : 3, h);
+        const fs_status st = read_back(c, P->scalars + 5, P->mom.base ? (int)(sizeof h / sizeof *h) : 3, h);
         if (st != FS_OK) return st;
+        static_assert(sizeof h / sizeof *h <= kMostReadBack, "read back at once");
         if (h[0] > P->logw_mag) P->logw_mag = h[0];
         if (h[1] * eps > P->pot_mag_eps) P->pot_mag_eps = h[1] * eps;
         P->rho_max = h[2];

@@ -118,3 +118,41 @@ def test_divergence_entry_point(ctx, oracle, n, m, d, eps, iters):
         assert value == terms[0] - 0.5 * terms[1] - 0.5 * terms[2]
         assert value > 0.0
         assert abs(value - ref) <= 4e-5 * (max(abs(r) for r in ref_terms) + eps)
+
+
+@pytest.mark.parametrize("d,compute", [(3, binding.FS_COMPUTE_FP32), (40, binding.FS_COMPUTE_FP32), (48, binding.FS_COMPUTE_BF16_MFMA)])
+def test_host_values_behind_long_work(d, compute):
+    """Values that come to the host: the same on an idle stream and behind work of a few milliseconds, which the host stops looking for
+    and waits for, from a context's first call on."""
+    rng = np.random.default_rng(d)
+    n, m, eps = 300, 200, 0.3
+    prob = binding.Problem(*(torch.from_numpy(rng.random((k, d)).astype(np.float32)).to("cuda:0") for k in (n, m)),
+                           *(torch.full((k,), 1.0 / k, device="cuda:0") for k in (n, m)), compute)
+    f, g = (torch.from_numpy((0.1 * rng.standard_normal(k)).astype(np.float32)).to("cuda:0") for k in (n, m))
+    big = torch.rand(6000, 6000, device="cuda:0")
+    bad = f.clone()
+    bad[7] = float("nan")
+    say("host values behind long work d=%d" % d)
+    want = None
+    for busy in (False, True, True, False):
+        ctx = binding.Context(0)
+
+        def queue():
+            torch.cuda.synchronize()
+            out = big
+            for _ in range(4 if busy else 0):
+                out = out @ big
+
+        got = []
+        for call in (lambda: ctx.fs_check_finite(g), lambda: ctx.fs_ot_value(prob, eps, f, g), lambda: ctx.fs_marginal_err(prob, eps, f, g),
+                     lambda: ctx.fs_check_weights(prob), lambda: ctx.fs_solve_tol(prob, eps, 4, 2, 0.0, f.clone(), g.clone()),
+                     lambda: ctx.fs_divergence(prob, eps, 2)[:2]):
+            queue()
+            got.append(call())
+        queue()
+        with pytest.raises(binding.FlashSinkError) as e:
+            ctx.fs_check_finite(bad)
+        assert e.value.status == 8 and "1 of %d" % n in str(e.value)
+        want = got if want is None else want
+        assert got == want
+        ctx.close()
