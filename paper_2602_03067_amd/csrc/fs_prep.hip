@@ -382,13 +382,14 @@ __global__ void k_prep_f64(const void *pts, int dtype, int64_t cnt, int64_t cnt_
 // memory linearly.
 typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));       // four floats, sixteen bytes at an address that is only
 typedef uint32_t u4_any __attribute__((ext_vector_type(4), aligned(2)));    // a multiple of the element's size (one load here)
-// A workgroup makes sixteen rows, a wave a whole 1 KB tile at a time (lane: row l / 4, piece l % 4), every fourth chunk.  Bound by the
-// memory, 330 MB at n = 40009, m = 30011, d = 784 in fp32: 158 us with a wave per row and a load per coordinate, 68 here (what is read
+// A workgroup of NW waves makes sixteen rows, a wave a whole 1 KB tile at a time (lane: row l / 4, piece l % 4), every NW-th chunk.  Bound by
+// the memory, 330 MB at n = 40009, m = 30011, d = 784 in fp32: 158 us with a wave per row and a load per coordinate, 68 here (what is read
 // last is still in the last-level cache).
-__global__ __launch_bounds__(256) void k_prep_bf16(const void *pts, int dtype, int64_t cnt, int64_t d, int64_t ld, int kp, uint16_t *out, float *bias,
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void k_prep_bf16(const void *pts, int dtype, int64_t cnt, int64_t d, int64_t ld, int kp, uint16_t *out, float *bias,
                                                    double *norm)
 {
-    __shared__ double shn[4][16];
+    __shared__ double shn[NW][16];
     const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
     const int64_t rb = blockIdx.x, row = rb * 16 + (l >> 2);
     const int n_chunks = kp >> 5, piece = l & 3;
@@ -398,7 +399,7 @@ __global__ __launch_bounds__(256) void k_prep_bf16(const void *pts, int dtype, i
                          ((piece ^ ((l >> 4) & 3)) << 4);
     double nrm = 0.0;
 #pragma unroll 4
-    for (int ch = w; ch < n_chunks; ch += 4) {
+    for (int ch = w; ch < n_chunks; ch += NW) {
         const int k0 = ch * 32 + piece * 8;
         uint16_t h[8];
         if (real && k0 + 8 <= d) {
@@ -436,7 +437,10 @@ __global__ __launch_bounds__(256) void k_prep_bf16(const void *pts, int dtype, i
     if (piece == 0) shn[w][l >> 2] = nrm;
     __syncthreads();
     if (tid < 16) {
-        norm[rb * 16 + tid] = shn[0][tid] + shn[1][tid] + shn[2][tid] + shn[3][tid];
+        double sum = shn[0][tid];
+#pragma unroll
+        for (int k = 1; k < NW; ++k) sum += shn[k][tid];
+        norm[rb * 16 + tid] = sum;
         bias[rb * 16 + tid] = -INFINITY;
     }
 }
@@ -1173,9 +1177,19 @@ fs_status launch_prepare(Ctx *c, const fs_problem *p, Prepared *P)
             hipLaunchKernelGGL(k_prep_f64, dim3((unsigned)ceil_div(s.S->cnt_pad, 4)), dim3(256), 0, c->stream, s.pts,
                                dtype, s.S->cnt, s.S->cnt_pad, p->d, s.ld, P->kp, s.S->pts_d, s.S->bias_d, s.S->norm);
     } else {
-        for (auto &s : in)
-            hipLaunchKernelGGL(k_prep_bf16, dim3((unsigned)(s.S->cnt_pad / 16)), dim3(256), 0, c->stream, s.pts, dtype, s.S->cnt, p->d, s.ld,
-                               P->kp, s.S->pts_b, s.S->bias_f, s.S->norm);
+        // Few rows do not fill the chip, and four waves walk through many chunks each, one after the other: sixteen there.  A half-step in
+        // fp32 storage, us, with a wave per row as it was before / four waves / sixteen: n = m = 100, d = 500: 28.3 / 30.5 / 27.9, d = 1024: 39.9 / 44.1 /
+        // 37.6, d = 2048: 63.8 / 72.5 / 58.9; n = m = 2000, d = 1024: 47.7 / 48.6 / 43.9; d = 256, n = m = 1000: 25.1 / 24.1 / 23.7.  From
+        // n = m = 3000 on the four are ahead of the wave per row (54.1 / 51.9 at d = 1024).
+        for (auto &s : in) {
+            const dim3 grid((unsigned)(s.S->cnt_pad / 16));
+            if (s.S->cnt_pad <= 2048 && P->kp >= 256)
+                hipLaunchKernelGGL(k_prep_bf16<16>, grid, dim3(1024), 0, c->stream, s.pts, dtype, s.S->cnt, p->d, s.ld, P->kp, s.S->pts_b,
+                                   s.S->bias_f, s.S->norm);
+            else
+                hipLaunchKernelGGL(k_prep_bf16<4>, grid, dim3(256), 0, c->stream, s.pts, dtype, s.S->cnt, p->d, s.ld, P->kp, s.S->pts_b,
+                                   s.S->bias_f, s.S->norm);
+        }
     }
     FS_HIP(c, hipGetLastError());
     return FS_OK;

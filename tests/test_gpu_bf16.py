@@ -352,3 +352,25 @@ def test_derived_copies_of_clouds_of_any_stride_and_alignment(storage, d, pad, o
         go = -eps * np.log(np.exp((fo[:, None] - C) / eps).mean(0))
     assert np.abs(out[0][0] - fo).max() <= 1e-4 * eps and np.abs(out[0][1] - go).max() <= 1e-4 * eps
     ctx.close()
+
+
+@pytest.mark.parametrize("storage", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("n,m", [(300, 77), (2100, 77), (2100, 2050)])   # (few rows of many coordinates have sixteen waves for sixteen rows)
+@pytest.mark.parametrize("d,pad,off", [(224, 0, 0), (225, 2, 1), (300, 3, 1), (1000, 0, 0)])
+def test_derived_copies_by_four_and_by_sixteen_waves(storage, n, m, d, pad, off):
+    """Either width of the prologue's workgroups, on one side or both: the same from views and aligned copies, and against float64."""
+    gen = torch.Generator(device="cuda:0").manual_seed(d + off + n)
+    x, y = (torch.randn(k, d + pad, generator=gen, device="cuda:0").to(storage)[:, off:off + d] for k in (n, m))
+    eps = float(np.float32(0.3 * d))
+    g = 0.1 * torch.randn(m, generator=gen, device="cuda:0")
+    ctx = binding.Context(0)
+    say("bf16 copies n=%d m=%d d=%d pad=%d off=%d %s" % (n, m, d, pad, off, storage))
+    out = [host(ctx.fs_update_f(binding.Problem(X, Y, None, None, binding.FS_COMPUTE_BF16_MFMA), eps, g))
+           for X, Y in ((x, y), tuple(torch.nn.functional.pad(t, (0, -d % 8))[:, :d] for t in (x, y)))]
+    assert np.array_equal(out[0], out[1])
+    X, Y = (t.to(torch.bfloat16).double().cpu().numpy() for t in (x, y))
+    s = (2.0 * X @ Y.T - (Y ** 2).sum(1) + host(g)) / eps
+    top = s.max(1, keepdims=True)
+    want = (X ** 2).sum(1) - eps * (np.log(np.exp(s - top).mean(1)) + top[:, 0])
+    assert np.abs(out[0] - want).max() <= 1e-4 * eps
+    ctx.close()
