@@ -1008,7 +1008,7 @@ fs_status pass_args(Ctx *c, const Prepared *P, const Side *res, const Side *str,
     a.partial = (double2 *)partial;
     a.partial_stride = res->cnt_pad;
     a.n_str = str->cnt;
-    a.count = c->fx_count;
+    a.count = c->fx_count && !capturing(c) ? c->fx_count : nullptr;   // (the counters may be gone before a graph is)
     if ((int64_t)s.row_blocks * kRows > res->cnt_pad || (int64_t)a.n_tiles * 32 > str->cnt_pad ||
         (size_t)s.splits * res->cnt_pad * 16 > P->partial_bytes || P->fx_ks < 1 || P->fx_ks > kFxMaxKs)
         return fail(c, FS_ERR_DEVICE, "internal: fixed-point launch shape exceeds the padded buffers");
