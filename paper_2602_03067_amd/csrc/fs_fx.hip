@@ -31,7 +31,7 @@
 // filled by linear direct loads and read without bank conflicts.
 //
 // A workgroup is four waves = 128 resident rows (their digits stay in registers) over a run of streamed tiles that pass
-// through an LDS ring; two workgroups per CU, one where two rings do not fit, three in MODE 3 at d <= 96 (fx_wg_per_cu).
+// through an LDS ring; two workgroups per CU, one where two rings do not fit, three in MODE 3 (fx_wg_per_cu).
 //
 // Long half-steps (MODE 3).  Where the scores of a row spread over hundreds of base-2 units, few tiles hold a point that counts
 // (shifted normal points, n = m = 16384, d = 64, eps = 0.1: one tile of four holds a pair within 60 units of its row's largest).  The three
@@ -39,8 +39,8 @@
 // the conversions and the exponentials undone.  m must be near the row's largest from the first tile on for that: it starts at the
 // score, at the biases of this pass, of a point that the last pass over these rows in the same call found (FxSeed), which bounds
 // the row's sum from below whatever the potentials have become.  The leading products come first and the max between them and
-// the others, so a wave waits for its own products more often; three workgroups per CU fill those waits at d <= 96 (168 registers: sums
-// of one weight are shifted before the next ones join them).  Half-step with its merge (us): that case 216 -> 116, the self term of a
+// the others, so a wave waits for its own products more often; three workgroups per CU fill those waits (168 registers: sums of one
+// weight are shifted before the next ones join them).  Half-step with its merge (us): that case 216 -> 116, the self term of a
 // divergence at n = 10000, d = 64 78 -> 53; where nothing can be left (unit cube) n = m = 16384, d = 64 197 -> 186, n = m = 10000, d = 128
 // 136 -> 122, n = m = 8192, d = 64 53 -> 57, which is why short passes stay in MODE 0 (fx_long).
 //
@@ -126,13 +126,11 @@ constexpr int fx_stage_bytes(int ks, int mode, int nc)
 constexpr int fx_stages(int stage_bytes) { return stage_bytes <= 13 * 1024 ? 4 : 3; }
 // Workgroups per CU: two where two rings fit the 160 KB of LDS, which the widest applications do not (four column blocks
 // at any d, three at d > 64, two at d > 96).  HAD: one, the second set of resident digits takes the registers.  MODE 3: three, it
-// holds fewer accumulators at a time, but two at d > 96, where the resident digits alone take 64 registers: with three, 44 more were
-// spilled, whose reloads wait for the ring (solves in the unit cube, n = m = 10000, d = 128, us a half-step: ten products 128 -> 122,
-// thirteen 172 -> 154, and 136 and 153 in MODE 0).
+// holds fewer accumulators at a time.
 constexpr int fx_wg_per_cu(int ks, int mode, int nc, bool had)
 {
     const int stage = fx_stage_bytes(ks, mode, nc);
-    return mode == 3 ? (ks <= 3 ? 3 : 2) : had || 2 * fx_stages(stage) * stage > 160 * 1024 ? 1 : 2;
+    return mode == 3 ? 3 : mode == 4 ? 2 : had || 2 * fx_stages(stage) * stage > 160 * 1024 ? 1 : 2;
 }
 template <int KS, int MODE, int NC, bool HAD = false> struct FxShape {
     static constexpr int kStage = fx_stage_bytes(KS, MODE, NC);
@@ -141,16 +139,20 @@ template <int KS, int MODE, int NC, bool HAD = false> struct FxShape {
     static constexpr int kLoads = KS + 1 + (MODE == 1 ? 1 : MODE == 2 ? (NC * 6 + 3) / 4 : 0);
     static constexpr int kWgPerCu = fx_wg_per_cu(KS, MODE, NC, HAD);
     static constexpr int kPC = MODE == 2 ? 32 * NC : NC;
-    // digits of a tile that stay in registers while it lasts: all of them, the leading two, or none
-    static constexpr int kHold(bool full) { return KS <= 2 ? 4 : full ? 0 : 2; }
+    // digits of a tile that stay in registers while it lasts: all of them, the leading two, or none, and then in one pass over the digits
+    // (0) or in two (1): at four k-steps, where the resident digits take 64 registers of 168, the three accumulators of one pass were spilled, and
+    // reloads in the loop wait for the ring (half-step in the unit cube, n = m = 15000, d = 120, thirteen products, 352 us; 331 in MODE 0, 335 here)
+    static constexpr int kHold(bool full) { return KS <= 2 ? 4 : !full ? 2 : KS == 4 && MODE == 3 ? 1 : 0; }
 };
 
+// MODE 4: MODE 3 with two workgroups per CU, at four k-steps (see fx_mode).
 // COUNT (with MODE 3): tiles are counted, in kernels of their own: a counter across the loop takes the others up to twenty registers,
 // and where they have none left spills.
 template <int KS, int MODE, int NC, bool FULL, bool HAD = false, bool COUNT = false>
 __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, const int bx, const int by)
 {
     using S = FxShape<KS, MODE, NC, HAD>;
+    constexpr bool LONG = MODE >= 3;
     constexpr int NS = S::kStages;
     const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
@@ -203,10 +205,10 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
     };
 
     // Everything that is loaded once, behind the first tile, and waited for once.
-    if (MODE == 3 && G > 0) issue();
+    if (LONG && G > 0) issue();
     int at = -1, at_dot = 0;   // the point that m was last raised for and its product with the row, in units of r2^2 2^-22
     double m0 = -INFINITY;
-    if (MODE == 3 && a.seed_in) {
+    if (LONG && a.seed_in) {
         // m starts at the score of the best of the points that the last pass over these rows found in its splits
         constexpr int kOnce = 6;
         FxSeed sd[kOnce];
@@ -263,7 +265,7 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
     double s = 0.0;
     int nhm = 0;
     bool known = false;
-    if (MODE == 3 && a.seed_in) {
+    if (LONG && a.seed_in) {
         const double m1 = __shfl_xor(m0, 32);
         const int at1 = __shfl_xor(at, 32), dot1 = __shfl_xor(at_dot, 32);
         if (m1 > m0 || (m1 == m0 && lh)) {   // (the same choice in both halves)
@@ -352,7 +354,36 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
     auto contract_low = [&](const unsigned char *sb, Tile &T) __attribute__((always_inline)) {
         constexpr int HOLD = S::kHold(FULL);
         i16v P;
-        if constexpr (HOLD == 0) {
+        if constexpr (HOLD == 1) {
+            // the products of least weight first, then one pass over the digits, two accumulators at a time beside H
+            if constexpr (FULL) {
+                P = biases(sb, 2);
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    digits(sb, T, ks, 1, 3);
+                    FX_MM(P, 3, 1);
+                    FX_MM(P, 2, 2);
+                    FX_MM(P, 1, 3);
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) T.L[r] = FULL ? P[r] >> 8 : 0;
+            asm volatile("" : "+s"(sb));   // (read again rather than kept)
+            i16v Q = biases(sb, 1);
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                digits(sb, T, ks, 0, 3);
+                FX_MM(Q, 2, 0);
+                FX_MM(T.L, 0, 3);
+                FX_MM(Q, 1, 1);
+                FX_MM(T.L, 1, 2);
+                FX_MM(Q, 0, 2);
+                FX_MM(T.L, 2, 1);
+                FX_MM(T.L, 3, 0);
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) T.L[r] = (int)(((unsigned)Q[r] << 8) + (unsigned)T.L[r]);
+        } else if constexpr (HOLD == 0) {
             // one pass over the digits, three accumulators
             i16v Q = biases(sb, 1);
             P = biases(sb, 2);
@@ -553,7 +584,7 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
         if (__any(hx > lazy || !(kOneStep ? s > 0.0 : known))) {
             if constexpr (MODE == 2) hx = max(hx, __shfl_xor(hx, 32));
             const int dh = known ? max(hx, 0) : hx == INT32_MIN ? 0 : hx;
-            if (MODE == 3 && a.seed_out) {
+            if (LONG && a.seed_out) {
                 int which = INT32_MIN;   // (the largest score but for four bits, and its register)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) which = max(which, (T.H[r] & ~15) | r);
@@ -728,7 +759,7 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
         if (issued < G) issue();     // into the predecessor's slot
         const unsigned char *sb = ring + (g % NS) * S::kStage;
         Tile T;
-        if constexpr (MODE == 3)
+        if constexpr (LONG)
             contract_high(sb, T);
         else
             contract_all(sb, T);
@@ -740,7 +771,7 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
         // MODE 2 and 3 the copies would spill, and in MODE 2 points without weight take the float64 epilogue.  HAD has the registers, and
         // its exponentials run beside the products of the weights only from the same piece of code: 16384 x 16384, d = 64, 8 columns,
         // 667 us where they join, 619 here.)
-        if constexpr (MODE == 3) {
+        if constexpr (LONG) {
             const bool direct = T.kind != 1 && near;
             if (direct) {
                 settle(g, T, top, T.kind == 2);
@@ -781,7 +812,7 @@ __device__ __forceinline__ void fx_body(const FxArgs &a, unsigned char *ring, co
     const double M = fmax(mym, mo) > (double)kNegInit ? ceil(fmax(mym, mo)) : (double)kNegInit;
     const float f0 = fast_exp2((float)(mym - M)), f1 = fast_exp2((float)(mo - M));
     const int64_t rec_row = (int64_t)by * a.partial_stride + row0 + lj;
-    if (MODE == 3 && a.seed_out) {
+    if (LONG && a.seed_out) {
         const int at1 = __shfl_xor(at, 32), dot1 = __shfl_xor(at_dot, 32);
         const bool other = at < 0 || (at1 >= 0 && mo > mym);   // (the half that was raised higher)
         if (lh == 0) a.seed_out[rec_row] = other ? FxSeed{dot1, at1} : FxSeed{at_dot, at};
@@ -1014,11 +1045,11 @@ fs_status pass_args(Ctx *c, const Prepared *P, const Side *res, const Side *str,
         return fail(c, FS_ERR_DEVICE, "internal: fixed-point launch shape exceeds the padded buffers");
     Prepared::Seeds &sd = P->seeds;
     const int t = res == &P->X ? 0 : 1;
-    if (mode == 3 && sd.last[t] >= 0) {
+    if (mode >= 3 && sd.last[t] >= 0) {
         a.seed_in = reinterpret_cast<const FxSeed *>(sd.buf[t][sd.last[t]]);
         a.seed_splits = sd.splits[t];
     }
-    if (mode == 3 && (size_t)s.splits * res->cnt_pad * sizeof(FxSeed) <= sd.bytes[t]) {
+    if (mode >= 3 && (size_t)s.splits * res->cnt_pad * sizeof(FxSeed) <= sd.bytes[t]) {
         const int next = sd.last[t] == 0 ? 1 : 0;
         a.seed_out = reinterpret_cast<FxSeed *>(sd.buf[t][next]);
         sd.last[t] = next;
@@ -1087,8 +1118,8 @@ struct ApplyBuf {
 // Whether a half-step runs in MODE 3 (`s` is its shape there, `s0` in MODE 0): where a workgroup has at least 24 tiles.  At d <= 64, where
 // its three workgroups per CU bring least, they also have to fill their places: the model of the shapes may expect no more than
 // 1.05 times the time in MODE 0, or, for `seeds`, the calls that pass over the rows several times, 1.09 (d <= 32) or 1.11: only
-// there are tiles left early, if the clouds allow it at all.  MODE 0 over MODE 3 in time, unit cube with ten products / with
-// thirteen, where no tile can be left / normal points of spread 1, a unit apart, where many are, at the model's 1.0, 1.08, 1.10 and
+// there are tiles left early, if the clouds allow it at all.  (d > 96: see fx_mode.)  MODE 0 over MODE 3 in time, unit cube with ten products /
+// with thirteen, where no tile can be left / normal points of spread 1, a unit apart, where many are, at the model's 1.0, 1.08, 1.10 and
 // 1.125 (n = m = 14500, 12500, 9000; n = 20000, m = 3000):
 //     solves, d = 20     1.08 1.05 1.10    1.02 1.00 1.03    0.96 0.97 0.96    0.93 0.94 0.94
 //     d = 64             1.05 1.03 1.44    1.01 1.00 1.31    0.99 0.97 1.17    0.97 0.96 1.08
@@ -1096,45 +1127,62 @@ struct ApplyBuf {
 //     single, d = 20     1.08 1.04 1.03    1.00 0.98 0.98    0.96 0.96 0.96    0.91 0.97 0.92
 //     d = 64             1.04 1.02 1.04    1.01 1.00 1.00    1.01 0.96 0.99    0.99 0.94 0.95
 //     d = 96             1.09 1.01 1.02    1.06 0.97 0.98    1.05 0.97 0.97    1.03 0.99 1.00
-// (d = 128, two workgroups per CU as in MODE 0: 1.04 to 1.11, 0.98 to 1.03, 1.11 to 1.52, and single 1.06 to 1.10, 0.98 to 1.02, 1.00 to 1.10.)
-static bool fx_long(const Ctx *c, const PassShape &s, const PassShape &s0, int ks, bool seeds)
+constexpr int64_t kFxLong = 24 * 32;
+constexpr double kFxFilled = 1.025;   // (four k-steps)
+static bool fx_long(const PassShape &s, const PassShape &s0, int ks, bool seeds)
 {
-    if (c->dbg_fx_long) return c->dbg_fx_long == 1;
-    return s.cols_per_split >= 24 * 32 && (ks > 2 || s.cost <= (!seeds ? 1.05 : ks == 1 ? 1.09 : 1.11) * s0.cost);
+    const double most = ks == 4 ? kFxFilled : ks == 3 ? INFINITY : !seeds ? 1.05 : ks == 1 ? 1.09 : 1.11;
+    return s.cols_per_split >= kFxLong && s.cost <= most * s0.cost;
 }
 
 // the shape of a half-step over the rows of side t (0: X)
-static const PassShape &fx_half_step(const Ctx *c, const Prepared *P, int t, bool lng)
+static const PassShape &fx_half_step(const Ctx *c, const Prepared *P, int t, int mode)
 {
-    PassShape &s = P->fx_shapes[t][lng];
-    if (s.row_blocks == 0) s = fx_shape(c, (t ? P->Y : P->X).cnt, (t ? P->X : P->Y).cnt, fx_wg_per_cu(P->fx_ks, lng ? 3 : 0, 1, false));
+    PassShape &s = P->fx_shapes[t][mode ? mode - 2 : 0];
+    if (s.row_blocks == 0) s = fx_shape(c, (t ? P->Y : P->X).cnt, (t ? P->X : P->Y).cnt, fx_wg_per_cu(P->fx_ks, mode, 1, false));
     return s;
 }
-static bool fx_long_pass(const Ctx *c, const Prepared *P, int t, bool seeds)
+// ... and its mode: 0, 3 or 4.  At four k-steps three workgroups per CU pay where tiles are left early, and cost where none can be and
+// they do not fill their places: three for `seeds` and shapes that fill them, two for the others, and for those that have 24 tiles a
+// workgroup only with two.  MODE 0 over MODE 3 and over MODE 4 at d = 120, clouds as above: solves at n = m = 15000 (the model's 1.02) 1.10 0.99
+// 1.68 and 1.11 1.02 1.35, 10000 (1.026) 1.08 0.96 1.39 and 1.11 1.01 1.30, 12500 (1.084) 1.06 0.93 1.41 and 1.10 1.01 1.39; single
+// half-steps at 15000 1.10 0.98 0.99 and 1.10 1.00 1.04.
+static int fx_mode(const Ctx *c, const Prepared *P, int t, bool seeds)
 {
-    return fx_long(c, fx_half_step(c, P, t, true), fx_half_step(c, P, t, false), P->fx_ks, seeds);
+    const bool two = P->fx_ks > 3;
+    if (c->dbg_fx_long) return c->dbg_fx_long == 2 ? 0 : two && !seeds ? 4 : 3;
+    const PassShape &s0 = fx_half_step(c, P, t, 0);
+    if ((seeds || !two) && fx_long(fx_half_step(c, P, t, 3), s0, P->fx_ks, seeds)) return 3;
+    return two && fx_long(fx_half_step(c, P, t, 4), s0, P->fx_ks, seeds) ? 4 : 0;
 }
-// (both passes of one launch fill its places together: n = m = 9000, d = 20, us a half-step: 44.8 in MODE 0 and 42.3 in MODE 3, 48.8 and
-// 45.1)
-static bool fx_long_pair(const Ctx *c, const Prepared *P)
+// (Both passes of one launch fill its places together, n = m = 9000, d = 20, us a half-step: 44.8 in MODE 0 and 42.3 in MODE 3, 48.8 and
+// 45.1.  At four k-steps that is not enough, n = m = 12500, d = 120, thirteen products: 226 in MODE 0, 243 in MODE 3,
+// 222 in MODE 4; n = 7000, m = 24000: 263, 259 and 262, ten products 231, 190, 220.)
+static int fx_pair_mode(const Ctx *c, const Prepared *P)
 {
-    const PassShape &sx = fx_half_step(c, P, 0, true), &sy = fx_half_step(c, P, 1, true);
-    return fx_long(c, sx, sx, P->fx_ks, true) && fx_long(c, sy, sy, P->fx_ks, true);
+    const bool two = P->fx_ks > 3;
+    if (c->dbg_fx_long) return c->dbg_fx_long == 2 ? 0 : 3;
+    for (int mode = 3; mode <= (two ? 4 : 3); ++mode) {
+        const PassShape &sx = fx_half_step(c, P, 0, mode), &sy = fx_half_step(c, P, 1, mode);
+        if (sx.cols_per_split < kFxLong || sy.cols_per_split < kFxLong) continue;
+        if (mode == 4 || !two || sx.cost + sy.cost <= kFxFilled * (fx_half_step(c, P, 0, 0).cost + fx_half_step(c, P, 1, 0).cost)) return mode;
+    }
+    return 0;
 }
 
 size_t fx_seed_bytes(const Ctx *c, const Prepared *P, int t, bool pairs)
 {
-    if (!(pairs ? fx_long_pair(c, P) : fx_long_pass(c, P, t, true))) return 0;
-    return (size_t)fx_half_step(c, P, t, true).splits * (t ? P->Y : P->X).cnt_pad * sizeof(FxSeed);
+    const int mode = pairs ? fx_pair_mode(c, P) : fx_mode(c, P, t, true);
+    return mode == 0 ? 0 : (size_t)fx_half_step(c, P, t, mode).splits * (t ? P->Y : P->X).cnt_pad * sizeof(FxSeed);
 }
 
 fs_status fx_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, double eps, int *splits, bool launch)
 {
     FxArgs a;
     const int t = res == &P->X ? 0 : 1;
-    const bool lng = fx_long_pass(c, P, t, P->seeds.bytes[t] != 0);
-    const PassShape &s = fx_half_step(c, P, t, lng);
-    fs_status st = pass_args(c, P, res, str, s, eps, lng ? 3 : 0, P->partial, &a);
+    const int mode = fx_mode(c, P, t, P->seeds.bytes[t] != 0);
+    const PassShape &s = fx_half_step(c, P, t, mode);
+    fs_status st = pass_args(c, P, res, str, s, eps, mode, P->partial, &a);
     if (st != FS_OK) return st;
     *splits = s.splits;
     if (!launch) {
@@ -1143,9 +1191,11 @@ fs_status fx_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, do
     }
     const dim3 grid((unsigned)s.row_blocks, (unsigned)s.splits);
 #define FX_LSE(KS)                                                                          \
-    if (lng && a.count)                                                                     \
+    if (mode && a.count)                                                                    \
         hipLaunchKernelGGL((k_fx<KS, 3, 1, false, true>), grid, dim3(256), 0, c->stream, a); \
-    else if (lng)                                                                           \
+    else if (KS == 4 && mode == 4)                                                          \
+        hipLaunchKernelGGL((k_fx<4, 4, 1>), grid, dim3(256), 0, c->stream, a);              \
+    else if (mode)                                                                          \
         hipLaunchKernelGGL((k_fx<KS, 3, 1>), grid, dim3(256), 0, c->stream, a);             \
     else                                                                                    \
         hipLaunchKernelGGL((k_fx<KS, 0, 1>), grid, dim3(256), 0, c->stream, a)
@@ -1163,11 +1213,11 @@ fs_status fx_lse(Ctx *c, const Prepared *P, const Side *res, const Side *str, do
 fs_status fx_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, void *partial_y, int *splits_x, int *splits_y, bool launch)
 {
     FxArgs ax, ay;
-    const bool lng = fx_long_pair(c, P);
-    const PassShape &sx = fx_half_step(c, P, 0, lng), &sy = fx_half_step(c, P, 1, lng);
+    const int mode = fx_pair_mode(c, P);
+    const PassShape &sx = fx_half_step(c, P, 0, mode), &sy = fx_half_step(c, P, 1, mode);
     fs_status st;
-    if ((st = pass_args(c, P, &P->X, &P->Y, sx, eps, lng ? 3 : 0, partial_x, &ax)) != FS_OK) return st;
-    if ((st = pass_args(c, P, &P->Y, &P->X, sy, eps, lng ? 3 : 0, partial_y, &ay)) != FS_OK) return st;
+    if ((st = pass_args(c, P, &P->X, &P->Y, sx, eps, mode, partial_x, &ax)) != FS_OK) return st;
+    if ((st = pass_args(c, P, &P->Y, &P->X, sy, eps, mode, partial_y, &ay)) != FS_OK) return st;
     *splits_x = sx.splits;
     *splits_y = sy.splits;
     if (!launch) {
@@ -1176,7 +1226,9 @@ fs_status fx_lse_pair(Ctx *c, const Prepared *P, double eps, void *partial_x, vo
     }
     const dim3 grid((unsigned)(sx.row_blocks + sy.row_blocks), (unsigned)(sx.splits > sy.splits ? sx.splits : sy.splits));
 #define FX_PAIR(KS)                                                                                                         \
-    if (lng)                                                                                                                \
+    if (KS == 4 && mode == 4)                                                                                               \
+        hipLaunchKernelGGL((k_fx_pair<4, 4>), grid, dim3(256), 0, c->stream, ax, ay, sx.row_blocks, sx.splits, sy.splits);  \
+    else if (mode)                                                                                                          \
         hipLaunchKernelGGL((k_fx_pair<KS, 3>), grid, dim3(256), 0, c->stream, ax, ay, sx.row_blocks, sx.splits, sy.splits); \
     else                                                                                                                    \
         hipLaunchKernelGGL((k_fx_pair<KS, 0>), grid, dim3(256), 0, c->stream, ax, ay, sx.row_blocks, sx.splits, sy.splits)

@@ -248,7 +248,7 @@ struct Ctx {
     int dbg_fx_any_size = 0;         // 1: digit images for problems of any size
     size_t dbg_ws_limit = 0;         // the workspace does not get more bytes than this (0: no limit)
     int dbg_fx_splits = 0;           // forced split count of the streamed side of a fixed-point pass
-    int dbg_fx_long = 0;             // 1: fixed-point half-steps of any length as long ones (MODE 3), 2: none
+    int dbg_fx_long = 0;             // 1: fixed-point half-steps of any length as long ones (MODE 3 or 4), 2: none
     unsigned long long *fx_count = nullptr;   // device: tiles that long half-steps have left at their leading products, and all of theirs
     int dbg_moment_kind = 0;         // 1 + the expansion that passes through cell moments take
     int moment_kind = 0;             // 1 + the one that the last such pass took
@@ -404,7 +404,7 @@ struct Prepared {
     bool want_seeds = false;      // set by the entry points that pass over the same rows several times
     bool pairs = false;           // ... two passes a launch (fs_solve_symmetric)
     mutable Seeds seeds;
-    mutable PassShape fx_shapes[2][2];   // of half-steps over the rows of X [0] and Y [1] in MODE 0 and 3, once asked for
+    mutable PassShape fx_shapes[2][3];   // of half-steps over the rows of X [0] and Y [1] in MODE 0, 3 and 4, once asked for
     Side X, Y;
     // partial reductions of a streaming pass: [splits][max(n,m)_pad] records
     void *partial = nullptr;

@@ -777,3 +777,30 @@ def test_starts_of_many_row_blocks_and_splits():
         c.close()
     for u, v in zip(*out):
         assert float((u - v).abs().max()) <= 2 * 2e-6 * iters * eps + 2.0 ** -23 * float(u.abs().max()) * 1.01
+
+
+@pytest.mark.parametrize("d,n", [(30, 9000), (100, 9000), (100, 7000), (128, 15000)])
+def test_every_form_of_long_half_steps_by_itself(d, n):
+    """Sizes at which the library chooses each form of its own accord (three and two workgroups per CU, none, alone, in solves and in pairs),
+    against forced short half-steps: the same to the rounding of the potentials."""
+    eps, iters = float(np.float32(0.1)), 3
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(n + d)
+    x, y = torch.randn(n, d, generator=gen, device="cuda:0"), torch.randn(n - 77, d, generator=gen, device="cuda:0") + 0.5
+    prob = binding.Problem(x, y)
+    say("fx forms n=%d d=%d" % (n, d))
+    out = []
+    for long in (0, 2):
+        c = binding.Context(0)
+        c.fs_debug_set("fx_long", long)
+        f, g = torch.zeros(prob.n, device="cuda:0"), torch.zeros(prob.m, device="cuda:0")
+        got = [c.fs_update_f(prob, eps, g), c.fs_update_g(prob, eps, f)]
+        for solve in (lambda: c.fs_solve(prob, eps, eps, 1, iters, f, g), lambda: c.fs_solve_symmetric(prob, eps, iters, f, g)):
+            f.zero_()
+            g.zero_()
+            solve()
+            got += [f.clone(), g.clone()]
+        out.append([host(v) for v in got])
+        c.close()
+    for u, v in zip(*out):
+        assert np.all(np.abs(u - v) <= 4e-6 * iters * eps + 2.0 ** -23 * np.abs(u) * 1.01)
