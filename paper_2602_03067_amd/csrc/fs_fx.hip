@@ -42,7 +42,7 @@
 // the others, so a wave waits for its own products more often; three workgroups per CU fill those waits (168 registers: sums of one
 // weight are shifted before the next ones join them).  Half-step with its merge (us): that case 216 -> 116, the self term of a
 // divergence at n = 10000, d = 64 78 -> 53; where nothing can be left (unit cube) n = m = 16384, d = 64 197 -> 186, n = m = 10000, d = 128
-// 136 -> 122, n = m = 8192, d = 64 53 -> 57, which is why short passes stay in MODE 0 (fx_long).
+// 132 -> 119, n = m = 8192, d = 64 53 -> 57, which is why short passes stay in MODE 0 (fx_long).
 //
 // Bound: matrix and vector instructions, and with them the chip's power.  A wave alone issues a vector instruction every 2.5 ns, two
 // of a SIMD 1.3 (2.1 for conversions, shifts by an immediate, three-way maxima and whatever reads a scalar register), three or four 1.0
@@ -1145,7 +1145,7 @@ static const PassShape &fx_half_step(const Ctx *c, const Prepared *P, int t, int
 // ... and its mode: 0, 3 or 4.  At four k-steps three workgroups per CU pay where tiles are left early, and cost where none can be and
 // they do not fill their places: three for `seeds` and shapes that fill them, two for the others, and for those that have 24 tiles a
 // workgroup only with two.  MODE 0 over MODE 3 and over MODE 4 at d = 120, clouds as above: solves at n = m = 15000 (the model's 1.02) 1.10 0.99
-// 1.68 and 1.11 1.02 1.35, 10000 (1.026) 1.08 0.96 1.39 and 1.11 1.01 1.30, 12500 (1.084) 1.06 0.93 1.41 and 1.10 1.01 1.39; single
+// 1.68 and 1.11 1.02 1.35, 10000 (1.026) 1.08 0.96 1.39 and 1.11 1.01 1.28, 12500 (1.084) 1.06 0.93 1.41 and 1.11 1.02 1.34; single
 // half-steps at 15000 1.10 0.98 0.99 and 1.10 1.00 1.04.
 static int fx_mode(const Ctx *c, const Prepared *P, int t, bool seeds)
 {
@@ -1156,16 +1156,22 @@ static int fx_mode(const Ctx *c, const Prepared *P, int t, bool seeds)
     return two && fx_long(fx_half_step(c, P, t, 4), s0, P->fx_ks, seeds) ? 4 : 0;
 }
 // (Both passes of one launch fill its places together, n = m = 9000, d = 20, us a half-step: 44.8 in MODE 0 and 42.3 in MODE 3, 48.8 and
-// 45.1.  At four k-steps that is not enough, n = m = 12500, d = 120, thirteen products: 226 in MODE 0, 243 in MODE 3,
-// 222 in MODE 4; n = 7000, m = 24000: 263, 259 and 262, ten products 231, 190, 220.)
+// 45.1.  At four k-steps that is enough where one side is more than 1.5 times as long as the other, since workgroups of unequal length fill
+// each other's gaps, or where the model expects both passes filled; elsewhere two per CU.  MODE 0 over MODE 3 and over MODE 4 at d = 112,
+// clouds as above: n = 30000, m = 7000 (the model's 1.036) 1.29 1.11 1.84 and 1.03 0.99 1.45; 28000, 8000 (1.007) 1.17 1.02 1.75 and 1.06
+// 1.01 1.48; 13500, 12000 (0.95) 1.13 1.01 1.69 and 1.09 1.02 1.51; 16000, 12500 (1.059) 1.06 0.95 1.66 and 1.09 1.01 1.51; n = m = 12500
+// (1.085) 1.04 0.92 1.55 and 1.09 1.01 1.46.  The line is not sharp: 12000, 20000 (1.002) 1.08 0.95 1.72 and 1.10 1.01 1.53, in MODE 3.)
 static int fx_pair_mode(const Ctx *c, const Prepared *P)
 {
     const bool two = P->fx_ks > 3;
     if (c->dbg_fx_long) return c->dbg_fx_long == 2 ? 0 : 3;
+    const int64_t n = P->X.cnt, m = P->Y.cnt;
+    const bool unequal = 2 * n > 3 * m || 2 * m > 3 * n;
     for (int mode = 3; mode <= (two ? 4 : 3); ++mode) {
         const PassShape &sx = fx_half_step(c, P, 0, mode), &sy = fx_half_step(c, P, 1, mode);
         if (sx.cols_per_split < kFxLong || sy.cols_per_split < kFxLong) continue;
-        if (mode == 4 || !two || sx.cost + sy.cost <= kFxFilled * (fx_half_step(c, P, 0, 0).cost + fx_half_step(c, P, 1, 0).cost)) return mode;
+        if (mode == 4 || !two || unequal || sx.cost + sy.cost <= kFxFilled * (fx_half_step(c, P, 0, 0).cost + fx_half_step(c, P, 1, 0).cost))
+            return mode;
     }
     return 0;
 }

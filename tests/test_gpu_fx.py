@@ -779,16 +779,16 @@ def test_starts_of_many_row_blocks_and_splits():
         assert float((u - v).abs().max()) <= 2 * 2e-6 * iters * eps + 2.0 ** -23 * float(u.abs().max()) * 1.01
 
 
-@pytest.mark.parametrize("d,n", [(30, 9000), (100, 9000), (100, 7000), (128, 15000)])
-def test_every_form_of_long_half_steps_by_itself(d, n):
+@pytest.mark.parametrize("d,n,m", [(30, 9000, 8923), (100, 9000, 8923), (100, 7000, 6923), (128, 15000, 14923), (100, 25000, 6000)])
+def test_every_form_of_long_half_steps_by_itself(d, n, m):
     """Sizes at which the library chooses each form of its own accord (three and two workgroups per CU, none, alone, in solves and in pairs),
     against forced short half-steps: the same to the rounding of the potentials."""
     eps, iters = float(np.float32(0.1)), 3
     gen = torch.Generator(device="cuda:0")
     gen.manual_seed(n + d)
-    x, y = torch.randn(n, d, generator=gen, device="cuda:0"), torch.randn(n - 77, d, generator=gen, device="cuda:0") + 0.5
+    x, y = torch.randn(n, d, generator=gen, device="cuda:0"), torch.randn(m, d, generator=gen, device="cuda:0") + 0.5
     prob = binding.Problem(x, y)
-    say("fx forms n=%d d=%d" % (n, d))
+    say("fx forms n=%d m=%d d=%d" % (n, m, d))
     out = []
     for long in (0, 2):
         c = binding.Context(0)
